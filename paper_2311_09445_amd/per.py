@@ -1,9 +1,11 @@
-"""Thin ctypes binding of ``libper_hip.so`` (the C-ABI declared in ``include/per.h``).
+"""Thin binding of ``libper_hip.so`` (the C-ABI declared in ``include/per.h``).
 
 Argument marshalling only: every step runs in the library's HIP kernels.  PyTorch
 supplies device memory (the arena and the I/O arrays are torch tensors) and the
-stream.  There is no CPU fallback: if the library has not been built, loading
-fails with an error that says how to build it.
+stream.  The calls a training loop makes every iteration take their tensors apart in
+``_per_binding.so`` (``csrc/per_binding.cpp``: their checks and messages are there);
+set-up and inspection go through ctypes.  There is no CPU fallback: if the library has
+not been built, loading fails with an error that says how to build it.
 """
 from __future__ import annotations
 
@@ -13,6 +15,7 @@ from typing import Optional, Sequence
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libper_hip.so")
+BINDING_PATH = os.path.join(_HERE, "_per_binding.so")
 MAX_FIELDS = 8
 
 OK, EINVAL, ENOMEM, EEMPTY, ERANGE, EHIP = 0, -1, -2, -3, -4, -5
@@ -144,6 +147,15 @@ def _lib():
     return lib
 
 
+def _binding():
+    import torch  # noqa: F401  (its libraries must be loaded before the binding)
+    _lib()
+    if not os.path.exists(BINDING_PATH):
+        raise ImportError(f"{BINDING_PATH} is missing: build it with `python -m paper_2311_09445_amd.build`.")
+    from . import _per_binding
+    return _per_binding
+
+
 def make_config(fanout: int, capacity: int, n_trees: int = 1, field_bytes: Sequence[int] = (),
                 init_max_priority: float = 1.0) -> PerConfig:
     cfg = PerConfig()
@@ -204,6 +216,7 @@ class PrioritizedReplay:
             raise PerError(rc, "per_create")
         self._h = h
         self.H = self.lib.per_height(self._h)
+        self._calls = _binding().Calls(h.value, self.T, self.field_bytes, self.arena.device.index)
 
     def __del__(self):
         h = getattr(self, "_h", None)
@@ -218,37 +231,29 @@ class PrioritizedReplay:
         if rc != OK:
             raise PerError(rc, what)
 
-    def _ptr_array(self, tensors, n_rows):
-        if tensors is None:
-            return None, None
-        if len(tensors) != len(self.field_bytes):
-            raise ValueError("one tensor (or None) per payload field is required")
-        arr = (C.c_void_p * max(1, len(tensors)))()
-        for f, t in enumerate(tensors):
-            if t is None:
-                arr[f] = None
-                continue
-            if t.numel() * t.element_size() != self.T * n_rows * self.field_bytes[f]:
-                raise ValueError(f"field {f}: expected {self.T}x{n_rows}x{self.field_bytes[f]} bytes")
-            arr[f] = _dptr(t).value
-        return arr, C.cast(arr, C.c_void_p)
-
     # ---------------------------------------------------------------- operations
     def insert(self, n: int, rows=None, prio=None, out_idx=None, protect=None):
         """``protect`` ([T, m] indices): rows whose ring slot is among them are deferred (per_insert_protected)."""
+        rc = self._calls.insert(n, rows, prio, out_idx, protect)
+        if rc:
+            self._check(rc, "per_insert")
+
+    def _outputs(self, u, B, want_weights, want_prio, out_idx, out_weight, out_prio):
+        """Arrays for the results the caller has brought none for."""
         torch = self._torch
-        _keep, src = self._ptr_array(rows, n)
-        if prio is not None and prio.numel() != self.T * n:
-            raise ValueError("prio must hold T*n values")
-        if out_idx is not None and out_idx.numel() != self.T * n:
-            raise ValueError("out_idx must hold T*n values")
-        if protect is not None:
-            rc = self.lib.per_insert_protected(self._h, n, src, _dptr(prio, torch.float32), _dptr(out_idx, torch.int32),
-                                               protect.numel() // self.T, _dptr(protect, torch.int32), self._stream())
+        if u is None:
+            if B is None:
+                raise ValueError("without uniforms the batch size B must be given")
         else:
-            rc = self.lib.per_insert(self._h, n, src, _dptr(prio, torch.float32), _dptr(out_idx, torch.int32),
-                                     self._stream())
-        self._check(rc, "per_insert")
+            B = u.numel() // self.T
+        shape = (self.T, B)
+        if out_idx is None:
+            out_idx = torch.empty(shape, dtype=torch.int32, device=self.device)
+        if want_weights and out_weight is None:
+            out_weight = torch.empty(shape, dtype=torch.float32, device=self.device)
+        if want_prio and out_prio is None:
+            out_prio = torch.empty(shape, dtype=torch.float32, device=self.device)
+        return out_idx, out_weight, out_prio
 
     def sample(self, u, beta: float = 0.4, want_weights: bool = True, want_prio: bool = True,
                out_idx=None, out_weight=None, out_prio=None, rows_out=None, update=None, B=None):
@@ -259,39 +264,17 @@ class PrioritizedReplay:
         With ``rows_out`` (one [T,B,bytes] uint8 tensor or None per field) the sampled rows are
         gathered by the same call (per_sample_gather).  With ``update=(idx, prio)`` that priority
         update is applied after the sampling, still in the same call (per_sample_gather_update)."""
-        torch = self._torch
-        if u is None:
-            if B is None:
-                raise ValueError("without uniforms the batch size B must be given")
-        else:
-            B = u.numel() // self.T
-            if u.numel() != B * self.T:
-                raise ValueError("u must hold T*B values")
-        shape = (self.T, B)
-        if out_idx is None:
-            out_idx = torch.empty(shape, dtype=torch.int32, device=self.device)
-        if want_weights and out_weight is None:
-            out_weight = torch.empty(shape, dtype=torch.float32, device=self.device)
-        if want_prio and out_prio is None:
-            out_prio = torch.empty(shape, dtype=torch.float32, device=self.device)
-        args = (self._h, B, float(beta), _dptr(u, torch.float32), _dptr(out_idx, torch.int32),
-                _dptr(out_weight, torch.float32) if want_weights else None,
-                _dptr(out_prio, torch.float32) if want_prio else None)
-        dst = None
-        if rows_out is not None:
-            _keep, dst = self._ptr_array(rows_out, B)
-        if update is not None:
-            uidx, uprio = update
-            if uprio.numel() != uidx.numel():
-                raise ValueError("update idx and prio must have the same number of elements")
-            rc = self.lib.per_sample_gather_update(*args, dst, uidx.numel() // self.T, _dptr(uidx, torch.int32),
-                                                   _dptr(uprio, torch.float32), self._stream())
-        elif rows_out is None:
-            rc = self.lib.per_sample(*args, self._stream())
-        else:
-            rc = self.lib.per_sample_gather(*args, dst, self._stream())
-        self._check(rc, "per_sample")
-        return out_idx, (out_weight if want_weights else None), (out_prio if want_prio else None)
+        upd_idx, upd_prio = (None, None) if update is None else update
+        if out_idx is None or (want_weights and out_weight is None) or (want_prio and out_prio is None):
+            out_idx, out_weight, out_prio = self._outputs(u, B, want_weights, want_prio, out_idx, out_weight, out_prio)
+        if not want_weights:
+            out_weight = None
+        if not want_prio:
+            out_prio = None
+        rc = self._calls.sample(u, beta, out_idx, out_weight, out_prio, rows_out, B, upd_idx, upd_prio)
+        if rc:
+            self._check(rc, "per_sample")
+        return out_idx, out_weight, out_prio
 
     def step(self, u, beta, upd_prio, upd_pos=None, want_weights: bool = True, want_prio: bool = True,
              out_idx=None, out_weight=None, out_prio=None, rows_out=None, B=None, insert=None):
@@ -300,44 +283,16 @@ class PrioritizedReplay:
 
         ``insert=(n, rows, prio, out_idx)`` (as for ``insert``; the last three may be None): per_insert_step, the
         insertion of n rows per tree followed by the step, as one call."""
-        torch = self._torch
-        if u is None:
-            if B is None:
-                raise ValueError("without uniforms the batch size B must be given")
-        else:
-            B = u.numel() // self.T
-        shape = (self.T, B)
-        if upd_prio.numel() != self.T * B or (upd_pos is not None and upd_pos.numel() != self.T * B):
-            raise ValueError("upd_prio and upd_pos must hold T*B values")
-        if out_idx is None:
-            out_idx = torch.empty(shape, dtype=torch.int32, device=self.device)
-        if want_weights and out_weight is None:
-            out_weight = torch.empty(shape, dtype=torch.float32, device=self.device)
-        if want_prio and out_prio is None:
-            out_prio = torch.empty(shape, dtype=torch.float32, device=self.device)
-        dst = None
-        if rows_out is not None:
-            _keep, dst = self._ptr_array(rows_out, B)
-        if insert is not None:
-            n, ins_rows, ins_prio, ins_out = insert
-            _keep_src, src = self._ptr_array(ins_rows, n)
-            if ins_prio is not None and ins_prio.numel() != self.T * n:
-                raise ValueError("the insertion's prio must hold T*n values")
-            if ins_out is not None and ins_out.numel() != self.T * n:
-                raise ValueError("the insertion's out_idx must hold T*n values")
-            rc = self.lib.per_insert_step(self._h, n, src, _dptr(ins_prio, torch.float32), _dptr(ins_out, torch.int32),
-                                          B, float(beta), _dptr(u, torch.float32), _dptr(out_idx, torch.int32),
-                                          _dptr(out_weight, torch.float32) if want_weights else None,
-                                          _dptr(out_prio, torch.float32) if want_prio else None, dst,
-                                          _dptr(upd_prio, torch.float32), _dptr(upd_pos, torch.int32), self._stream())
-            self._check(rc, "per_insert_step")
-            return out_idx, (out_weight if want_weights else None), (out_prio if want_prio else None)
-        rc = self.lib.per_step(self._h, B, float(beta), _dptr(u, torch.float32), _dptr(out_idx, torch.int32),
-                               _dptr(out_weight, torch.float32) if want_weights else None,
-                               _dptr(out_prio, torch.float32) if want_prio else None, dst,
-                               _dptr(upd_prio, torch.float32), _dptr(upd_pos, torch.int32), self._stream())
-        self._check(rc, "per_step")
-        return out_idx, (out_weight if want_weights else None), (out_prio if want_prio else None)
+        if out_idx is None or (want_weights and out_weight is None) or (want_prio and out_prio is None):
+            out_idx, out_weight, out_prio = self._outputs(u, B, want_weights, want_prio, out_idx, out_weight, out_prio)
+        if not want_weights:
+            out_weight = None
+        if not want_prio:
+            out_prio = None
+        rc = self._calls.step(u, beta, upd_prio, upd_pos, out_idx, out_weight, out_prio, rows_out, B, insert)
+        if rc:
+            self._check(rc, "per_step" if insert is None else "per_insert_step")
+        return out_idx, out_weight, out_prio
 
     def run_steps_fits(self) -> bool:
         return bool(self.lib.per_run_steps_fits(self._h))
@@ -347,52 +302,10 @@ class PrioritizedReplay:
         """A list of steps (insert -> sample -> gather -> update) in one launch on an LDS copy of the tree.
         ``u``: [steps, T, B]; ``beta``: [steps] device tensor; the other arrays as in per.h (leading step
         dimension).  ``upd_prio`` without ``upd_idx`` updates, in every step, the batch just sampled."""
-        torch = self._torch
-        steps, B = int(u.shape[0]), int(u.shape[-1])
-        if u.numel() != steps * self.T * B or beta.numel() != steps:
-            raise ValueError("u must be [steps, T, B] and beta [steps]")
-        for name, x in (("out_idx", out_idx), ("out_weight", out_weight), ("out_prio", out_prio),
-                        ("upd_prio", upd_prio), ("upd_idx", upd_idx)):
-            if x is not None and x.numel() != u.numel():
-                raise ValueError(f"{name} must hold steps*T*B values")
-        if ins_prio is not None and ins_prio.numel() != steps * self.T * n_insert:
-            raise ValueError("ins_prio must hold steps*T*n_insert values")
-        io = PerStreamIO()
-        io.struct_size = C.sizeof(PerStreamIO)
-        keep = []
-
-        def table(tensors, rows_per_tree):
-            if tensors is None:
-                return None
-            if len(tensors) != len(self.field_bytes):
-                raise ValueError("one tensor (or None) per payload field is required")
-            arr = (C.c_void_p * max(1, len(tensors)))()
-            for f, t in enumerate(tensors):
-                if t is None:
-                    arr[f] = None
-                    continue
-                if t.numel() * t.element_size() != steps * self.T * rows_per_tree * self.field_bytes[f]:
-                    raise ValueError(f"field {f}: expected steps*T*rows*{self.field_bytes[f]} bytes")
-                arr[f] = _dptr(t).value
-            keep.append(arr)
-            return C.cast(arr, C.c_void_p)
-
-        def ptr(x, dtype):
-            p = _dptr(x, dtype)
-            return None if p is None else p.value
-
-        io.d_ins_rows = table(ins_rows, n_insert)
-        io.d_ins_prio = ptr(ins_prio, torch.float32)
-        io.d_u = ptr(u, torch.float32)
-        io.d_beta = ptr(beta, torch.float32)
-        io.d_out_idx = ptr(out_idx, torch.int32)
-        io.d_out_weight = ptr(out_weight, torch.float32)
-        io.d_out_prio = ptr(out_prio, torch.float32)
-        io.d_rows_out = table(rows_out, B)
-        io.d_upd_idx = ptr(upd_idx, torch.int32)
-        io.d_upd_prio = ptr(upd_prio, torch.float32)
-        rc = self.lib.per_run_steps(self._h, steps, int(n_insert), B, C.byref(io), self._stream())
-        self._check(rc, "per_run_steps")
+        rc = self._calls.run_steps(u, beta, out_idx, out_weight, out_prio, rows_out, upd_prio, upd_idx, n_insert, ins_rows,
+                                   ins_prio)
+        if rc:
+            self._check(rc, "per_run_steps")
 
     def prepare_requests(self, requests):
         """Encodes a list of requests for run_requests: a host array of per_request and its device copy.
@@ -476,54 +389,43 @@ class PrioritizedReplay:
         return int(self.lib.per_rng_calls(self._h))
 
     def gather(self, idx, out=None):
-        torch = self._torch
-        B = idx.numel() // self.T
         if out is None:
+            torch = self._torch
+            B = idx.numel() // self.T
             out = [torch.empty((self.T, B, b), dtype=torch.uint8, device=self.device) for b in self.field_bytes]
-        _keep, dst = self._ptr_array(out, B)
-        rc = self.lib.per_gather(self._h, B, _dptr(idx, torch.int32), dst, self._stream())
-        self._check(rc, "per_gather")
+        rc = self._calls.gather(idx, out)
+        if rc:
+            self._check(rc, "per_gather")
         return out
 
     def update(self, idx, prio):
-        torch = self._torch
-        B = idx.numel() // self.T
-        if prio.numel() != idx.numel():
-            raise ValueError("idx and prio must have the same number of elements")
-        rc = self.lib.per_update(self._h, B, _dptr(idx, torch.int32), _dptr(prio, torch.float32), self._stream())
-        self._check(rc, "per_update")
+        rc = self._calls.update(idx, prio)
+        if rc:
+            self._check(rc, "per_update")
 
     def update_td(self, idx, td, eps: float = 1e-6, alpha: float = 0.6):
         """per_update with the priorities computed on the device from temporal-difference errors."""
-        torch = self._torch
-        B = idx.numel() // self.T
-        if td.numel() != idx.numel():
-            raise ValueError("idx and td must have the same number of elements")
-        rc = self.lib.per_update_td(self._h, B, _dptr(idx, torch.int32), _dptr(td, torch.float32), float(eps),
-                                    float(alpha), self._stream())
-        self._check(rc, "per_update_td")
+        rc = self._calls.update_td(idx, td, eps, alpha)
+        if rc:
+            self._check(rc, "per_update_td")
 
     def update_delta(self, idx, delta):
         """The paper's form of the update: add delta[j] to leaf idx[j] and to all its ancestors."""
-        torch = self._torch
-        B = idx.numel() // self.T
-        if delta.numel() != idx.numel():
-            raise ValueError("idx and delta must have the same number of elements")
-        rc = self.lib.per_update_delta(self._h, B, _dptr(idx, torch.int32), _dptr(delta, torch.float32), self._stream())
-        self._check(rc, "per_update_delta")
+        rc = self._calls.update_delta(idx, delta)
+        if rc:
+            self._check(rc, "per_update_delta")
 
     def rebuild(self):
         """Recomputes every node above the leaves from its children (full bottom-up rebuild)."""
         self._check(self.lib.per_rebuild(self._h, self._stream()), "per_rebuild")
 
     def get_priority(self, idx, out=None):
-        torch = self._torch
-        n = idx.numel() // self.T
         if out is None:
-            out = torch.empty((self.T, n), dtype=torch.float32, device=self.device)
-        rc = self.lib.per_get_priority(self._h, n, _dptr(idx, torch.int32), _dptr(out, torch.float32),
-                                       self._stream())
-        self._check(rc, "per_get_priority")
+            torch = self._torch
+            out = torch.empty((self.T, idx.numel() // self.T), dtype=torch.float32, device=self.device)
+        rc = self._calls.get_priority(idx, out)
+        if rc:
+            self._check(rc, "per_get_priority")
         return out
 
     # ---------------------------------------------------------------- inspection
