@@ -236,27 +236,36 @@ __device__ __forceinline__ unsigned walk_chunks(const float (&s)[1 << M], float&
   }
 }
 
+// Two and four floats behind a plain pointer (which the compiler traces to LDS or memory) or a GlobalPtr.
+typedef float Floats2 __attribute__((ext_vector_type(2)));
+typedef float Floats4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ Floats2 load_floats2(const float* p) { return *reinterpret_cast<const Floats2*>(p); }
+__device__ __forceinline__ Floats4 load_floats4(const float* p) { return *reinterpret_cast<const Floats4*>(p); }
+#if defined(__HIP_DEVICE_COMPILE__)
+__device__ __forceinline__ Floats2 load_floats2(GlobalPtr<const float> p) { return *(GlobalPtr<const Floats2>)p; }
+__device__ __forceinline__ Floats4 load_floats4(GlobalPtr<const float> p) { return *(GlobalPtr<const Floats4>)p; }
+#endif
+
 // grp points at the K children (LDS or global).  Returns the chosen child, its value and the
 // residual.  The chosen chunk is read a second time instead of keeping all K children live.
-template <int LOGK>
-__device__ __forceinline__ void descend_lane(const float* grp, float& r, unsigned& child, float& val) {
+template <int LOGK, typename P>
+__device__ __forceinline__ void descend_lane(P grp, float& r, unsigned& child, float& val) {
   if constexpr (LOGK == 1) {
-    const float2 c = *reinterpret_cast<const float2*>(grp);
+    const Floats2 c = load_floats2(grp);
     const bool right = (c.y != 0.0f) && !(r < c.x);
     r = right ? r - c.x : r;
     child = right ? 1u : 0u;
     val = right ? c.y : c.x;
   } else {
     constexpr int C = (1 << LOGK) / 4;
-    const float4* g4 = reinterpret_cast<const float4*>(grp);
     float s[C];
 #pragma unroll
     for (int c = 0; c < C; ++c) {
-      const float4 x = g4[c];
+      const Floats4 x = load_floats4(grp + 4 * c);
       s[c] = (x.x + x.y) + (x.z + x.w);
     }
     const unsigned pos = walk_chunks<LOGK - 2>(s, r);
-    const float4 x = g4[pos];
+    const Floats4 x = load_floats4(grp + 4 * pos);
     const float p0 = x.x + x.y, p1 = x.z + x.w;
     const bool r1 = (p1 != 0.0f) && !(r < p0);
     r = r1 ? r - p0 : r;
@@ -268,25 +277,16 @@ __device__ __forceinline__ void descend_lane(const float* grp, float& r, unsigne
   }
 }
 
-// (sixteens by the butterfly moves of the vector unit, the last two steps across them by LDS permutes)
+// Called by whole waves.  Sixteens by the butterfly moves of the vector unit, then a lane of each by scalar reads: no trip
+// through LDS (two of them, by lane permutes, were a tenth of a microsecond in a chain that nothing else overlaps).
 __device__ __forceinline__ uint32_t wave_min_u32(uint32_t x) {
-  x = butterfly_min<4>(x);
-#pragma unroll
-  for (int m = 16; m <= 32; m <<= 1) {
-    const uint32_t y = (uint32_t)__shfl_xor((int)x, m);
-    x = y < x ? y : x;
-  }
-  return x;
+  const int y = (int)butterfly_min<4>(x);
+  const uint32_t a = (uint32_t)__builtin_amdgcn_readlane(y, 0), b = (uint32_t)__builtin_amdgcn_readlane(y, 16),
+                 c = (uint32_t)__builtin_amdgcn_readlane(y, 32), d = (uint32_t)__builtin_amdgcn_readlane(y, 48);
+  const uint32_t e = a < b ? a : b, f = c < d ? c : d;
+  return e < f ? e : f;
 }
-__device__ __forceinline__ uint32_t wave_max_u32(uint32_t x) {
-  x = ~butterfly_min<4>(~x);
-#pragma unroll
-  for (int m = 16; m <= 32; m <<= 1) {
-    const uint32_t y = (uint32_t)__shfl_xor((int)x, m);
-    x = y > x ? y : x;
-  }
-  return x;
-}
+__device__ __forceinline__ uint32_t wave_max_u32(uint32_t x) { return ~wave_min_u32(~x); }
 
 // Smallest positive leaf of tree t from the partial minima k_min_reduce has left (their number is part
 // of the weight mode), folded by every calling wave for itself.  Called by whole waves.

@@ -29,196 +29,33 @@ struct StreamKernelArgs {           // one kernel argument, so that both parts s
 };
 
 // Sum of the 4*N children behind g4 in the balanced pairwise order, by a single lane.
-template <int N>
-__device__ __forceinline__ float sum_chunks(const float4* g4) {
+template <int N, typename P>
+__device__ __forceinline__ float sum_chunks(P grp) {
   if constexpr (N == 1) {
-    const float4 x = g4[0];
+    const Floats4 x = load_floats4(grp);
     return (x.x + x.y) + (x.z + x.w);
   } else {
-    return sum_chunks<N / 2>(g4) + sum_chunks<N / 2>(g4 + N / 2);
+    return sum_chunks<N / 2>(grp) + sum_chunks<N / 2>(grp + 2 * N);
   }
 }
-template <int LOGK>
-__device__ __forceinline__ float lane_group_sum(const float* grp) {
+template <int LOGK, typename P>
+__device__ __forceinline__ float lane_group_sum(P grp) {
   if constexpr (LOGK == 1) {
-    const float2 c = *reinterpret_cast<const float2*>(grp);
+    const Floats2 c = load_floats2(grp);
     return c.x + c.y;
   } else {
-    return sum_chunks<(1 << LOGK) / 4>(reinterpret_cast<const float4*>(grp));
+    return sum_chunks<(1 << LOGK) / 4>(grp);
   }
 }
 
-// Every active lane recomputes the ancestors of its leaf in the LDS tree, one height per barrier.
-// (leaves_mem: the leaves in memory, or null when they are part of the LDS copy)
-template <int LOGK>
-__device__ __forceinline__ void resum_paths_lds(float* tree, const uint32_t* off, uint32_t H, bool active, uint32_t leaf,
-                                                const float* leaves_mem) {
-  constexpr int K = Fan<LOGK>::K;
-  for (uint32_t h = 1; h <= H; ++h) {
-    __syncthreads();   // (also makes the leaf stores of the other waves visible: one compute unit, one first-level cache)
-    if (active) {
-      const uint32_t parent = leaf >> (h * LOGK);
-      if (h == 1 && leaves_mem) tree[off[h] + parent] = lane_group_sum<LOGK>(leaves_mem + (size_t)parent * K);
-      else tree[off[h] + parent] = lane_group_sum<LOGK>(tree + off[h - 1] + (size_t)parent * K);
-    }
-  }
-}
-
-// One tree in the LDS of its workgroup, and the few words the operations below share.
+// One tree in the LDS of its workgroup.
 struct LdsTree {
   float* tree;              // heights 0 .. H back to back, zero padding included (height 0 left out when leaves_mem is set)
   float* leaves_mem;        // null, or the tree's leaves in memory (zero padded to whole groups)
   const uint32_t* off;      // off[h]: where height h starts (floats); off[H + 1]: all floats
-  uint32_t* sampled;        // [1024] indices of the latest sampling operation
   uint32_t* max_bits;       // running maximum priority (fp32 bits)
-  uint32_t* vmin_bits;      // minimum of the batch being sampled (fp32 bits)
-  uint32_t* bmin_bits;      // smallest positive leaf of the tree (fp32 bits), when the weights are relative to it
-  uint32_t* skip;           // [32] bit j: row j of the insertion under way is deferred
   uint32_t H, N;
 };
-
-// The three operations are called by all 1024 lanes of the workgroup.  Each leaves the tree
-// consistent, but its last phase may still be under way in other waves when it returns: the next
-// operation starts with a barrier of its own (lds_sample), or the caller places one.
-
-// Insertion of n <= 1024 rows: rows, leaves (given value, or the running maximum on entry), ancestors.
-// prio, out_idx and protect point at this tree's part (or are null).
-template <int LOGK>
-__device__ __forceinline__ void lds_insert(const LdsTree& lt, const FieldTable& rows, uint32_t t, uint64_t dense_row0,
-                                           uint32_t n, const float* prio, uint32_t* out_idx, const uint32_t* protect,
-                                           uint32_t n_protect, uint32_t& cursor, uint32_t& size, uint32_t& flags) {
-  const uint32_t tid = threadIdx.x;
-  const uint32_t N = lt.N;
-  if (protect) {   // collision-free insertion: rows aimed at a protected slot are deferred (see k_insert_small)
-    if (tid < 32) lt.skip[tid] = 0;
-    __syncthreads();
-    for (uint32_t k = tid; k < n_protect; k += blockDim.x) {
-      const uint32_t i = protect[k];
-      if (i < N) {
-        const uint32_t j = i >= cursor ? i - cursor : i + (N - cursor);   // position in the ring window
-        if (j < n) atomicOr(&lt.skip[j >> 5], 1u << (j & 31u));
-      }
-    }
-    __syncthreads();
-  }
-  (void)move_rows_one_workgroup<false>(rows, t, dense_row0, n, cursor, N, nullptr, protect ? lt.skip : nullptr);
-  __syncthreads();   // (also: the tree is loaded, the operation before this one is complete)
-  const float max_on_entry = __uint_as_float(*lt.max_bits);
-  __syncthreads();
-  bool ok = false;
-  uint32_t slot = 0;
-  if (tid < n) {
-    uint64_t sl = (uint64_t)cursor + tid;
-    if (sl >= N) sl -= N;
-    slot = (uint32_t)sl;
-    const bool deferred = protect && ((lt.skip[tid >> 5] >> (tid & 31u)) & 1u);
-    if (out_idx) out_idx[tid] = deferred ? 0xFFFFFFFFu : slot;
-    if (!deferred) {
-      float v = max_on_entry;
-      ok = true;
-      if (prio) {
-        v = prio[tid];
-        ok = valid_priority(v);
-        if (ok && v > 0.0f) atomicMax(lt.max_bits, __float_as_uint(v));
-        if (!ok) flags |= 2u;
-      }
-      if (ok) (lt.leaves_mem ? lt.leaves_mem : lt.tree + lt.off[0])[slot] = v;
-    }
-  }
-  resum_paths_lds<LOGK>(lt.tree, lt.off, lt.H, ok, slot, lt.leaves_mem);
-  const uint64_t end = (uint64_t)cursor + n;
-  cursor = (uint32_t)(end >= N ? end - N : end);
-  size = size + n > N ? N : size + n;
-}
-
-// Priority sampling of B <= 1024 indices with importance weights, and the rows of the sampled
-// indices.  u_i: this lane's uniform (lanes >= B: any value).  out_idx (never null), out_w, out_prio
-// point at this tree's part.  Returns this lane's index.
-template <int LOGK>
-__device__ __forceinline__ uint32_t lds_sample(const LdsTree& lt, const FieldTable& rows, uint32_t t, uint64_t dense_row0,
-                                               uint32_t B, float u_i, float beta, uint32_t* out_idx, float* out_w,
-                                               float* out_prio, bool buffer_norm, uint32_t& flags) {
-  constexpr int K = Fan<LOGK>::K;
-  const uint32_t tid = threadIdx.x;
-  if (tid == 0) {
-    *lt.vmin_bits = kNoMin;
-    *lt.bmin_bits = kNoMin;
-  }
-  __syncthreads();
-  const float total = lt.tree[lt.off[lt.H]];
-  if (buffer_norm && out_w) {   // weights relative to the whole tree: its smallest positive leaf, by a sweep over the LDS copy
-    uint32_t m = kNoMin;
-    const float* all_leaves = lt.leaves_mem ? lt.leaves_mem : lt.tree + lt.off[0];
-    for (uint32_t e = tid; e < lt.N; e += blockDim.x) m = min_u32(m, positive_bits(all_leaves[e]));
-    m = wave_min_u32(m);
-    if ((tid & 63u) == 0 && m != kNoMin) atomicMin(lt.bmin_bits, m);
-  }
-  uint32_t node = 0xFFFFFFFFu;
-  float val = 0.0f;
-  if (total > 0.0f) {
-    const uint32_t si = tid < B ? tid : B - 1;
-    float r = ((float)si + u_i) * (total / (float)B);
-    node = 0;
-    val = total;
-    for (uint32_t h = lt.H; h-- > 0;) {
-      unsigned child;
-      if (h == 0 && lt.leaves_mem) descend_lane<LOGK>(lt.leaves_mem + (size_t)node * K, r, child, val);
-      else descend_lane<LOGK>(lt.tree + lt.off[h] + (size_t)node * K, r, child, val);
-      node = node * K + child;
-    }
-    if (out_w && tid < B) atomicMin(lt.vmin_bits, __float_as_uint(val));
-  } else if (tid == 0) {
-    flags |= 4u;
-  }
-  if (tid < B) {
-    lt.sampled[tid] = node;
-    out_idx[tid] = node;
-    if (out_prio) out_prio[tid] = val;
-  }
-  __syncthreads();
-  // (the weights, a power per sample, are computed while the rows are on their way: every lane that
-  // owns a sample also owns a row element of the first sweep, so no wave runs the power twice)
-  auto weights = [&]() {
-    if (out_w && tid < B)
-      out_w[tid] = total > 0.0f ? importance_weight(val, __uint_as_float(buffer_norm ? *lt.bmin_bits : *lt.vmin_bits), beta)
-                                : 0.0f;
-  };
-  if (move_rows_one_workgroup<true>(rows, t, dense_row0, B, 0, lt.N, lt.sampled, nullptr, weights)) flags |= 1u;
-  return node;
-}
-
-// Priority update of B <= 1024 elements: lane tid < B sets leaf i to v.  Last writer by LDS
-// atomics (see the head of this file), then the ancestors.
-template <int LOGK>
-__device__ __forceinline__ void lds_update(const LdsTree& lt, uint32_t B, uint32_t i, float v, uint32_t size,
-                                           uint32_t& flags) {
-  const uint32_t tid = threadIdx.x;
-  bool valid = false;
-  if (tid < B) {
-    if (!(i < size)) flags |= 1u;
-    else if (!valid_priority(v)) flags |= 2u;
-    else valid = true;
-  }
-  const uint32_t mark = 0x80000001u + tid;
-  bool won;
-  if (lt.leaves_mem) {   // (the markers go through memory: atomics there, and a read that passes by the first-level cache)
-    uint32_t* leaf_bits = reinterpret_cast<uint32_t*>(lt.leaves_mem);
-    if (valid) atomicMax(&leaf_bits[i], mark);
-    __syncthreads();
-    won = valid && __hip_atomic_load(&leaf_bits[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == mark;
-    __syncthreads();
-    if (won) lt.leaves_mem[i] = v;
-  } else {
-    uint32_t* leaf_bits = reinterpret_cast<uint32_t*>(lt.tree + lt.off[0]);
-    if (valid) atomicMax(&leaf_bits[i], mark);
-    __syncthreads();
-    won = valid && leaf_bits[i] == mark;
-    __syncthreads();
-    if (won) lt.tree[lt.off[0] + i] = v;
-  }
-  if (valid && v > 0.0f) atomicMax(lt.max_bits, __float_as_uint(v));
-  resum_paths_lds<LOGK>(lt.tree, lt.off, lt.H, valid, i, lt.leaves_mem);
-}
 
 // Loads every height of tree t into LDS (lanes 64 .. 64 + H + 1 have filled s_off, lane 0 the maximum).  The heights
 // are arrays of their own in memory and lie back to back in LDS; the copy runs over the LDS floats as one range, eight
@@ -262,37 +99,35 @@ __device__ __forceinline__ void lds_tree_store(const Geom& g, uint32_t t, const 
 }
 
 // ---- rows of the stream kernels
-// The pieces (16 bytes or the field's access width) in which the rows of a step move are shared out over the lanes
-// that carry rows, and which piece a lane has (field, row, place in the row) is the same in every step: it is worked
-// out once per launch (a chain of selects over the fields and a division: several hundred cycles for a lone wave).
-struct RowPiece {
-  uint8_t* stored;    // the piece in row 0 of the tree's payload
-  uint8_t* dense;     // the piece in the caller's array, step 0
-  uint32_t what;      // row of the step's batch << 8 | field << 5 | bytes moved
-  __device__ __forceinline__ uint32_t row() const { return what >> 8; }
-  __device__ __forceinline__ uint32_t field() const { return (what >> 5) & 7u; }
-  __device__ __forceinline__ uint32_t w() const { return what & 31u; }
-};
-// What the lanes ask of one list of fields, in LDS (the kernel arguments would take a hundred scalar registers).
-struct PieceFields {
-  uint8_t* io[kMaxFields];         // the caller's array: the rows of this tree in step 0
+// The rows of a batch move in pieces (16 bytes, or the field's access width), 64 pieces of one field at a time by one
+// wave: an item.  A wave then works with one access width and one field's constants (with the pieces of all fields
+// shared out lane by lane, every lane paid for a chain of selects over the fields, a division, and the loads and
+// stores of every width that occurs in its wave).
+struct PieceFields {               // what the waves ask of one list of fields, in LDS
+  uint8_t* io[kMaxFields];         // the caller's array: the rows of this tree (in step 0)
   uint8_t* col[kMaxFields];        // the field in row 0 of this tree
   uint64_t step[kMaxFields];       // bytes of the caller's array per step
   uint32_t bytes[kMaxFields], vec[kMaxFields];
-  uint32_t end[kMaxFields];        // pieces of this field and all before it
+  uint32_t pieces[kMaxFields];     // pieces of this field
+  uint32_t recip[kMaxFields];      // floor(2^32 / pieces per row) + 1
+  uint32_t end[kMaxFields];        // items of this field and all before it
+  __device__ __forceinline__ uint32_t items() const { return (uint32_t)__builtin_amdgcn_readfirstlane((int)end[kMaxFields - 1]); }
 };
-// Called by one wave: n rows per tree and step of tree t of T.
-__device__ __forceinline__ void fill_piece_fields(const FieldTable* ft, uint32_t t, uint32_t T, uint32_t n, PieceFields* pf) {
+// Called by one wave: n rows per tree; field f's array is `io` for tree 0 (null: not asked for), `step` bytes from step to step.
+__device__ __forceinline__ void fill_piece_fields(const FieldTable* ft, uint8_t* io, uint32_t t, uint32_t n, uint64_t step_rows,
+                                                  PieceFields* pf) {
   const uint32_t f = threadIdx.x & 63u;
   if (f < (uint32_t)kMaxFields) {
-    const bool on = f < ft->n_fields && ft->io[f] && n;
-    const uint32_t E = ft->bytes[f];
-    pf->io[f] = on ? ft->io[f] + (uint64_t)t * n * E : nullptr;
+    const bool on = f < ft->n_fields && io && n;
+    const uint32_t E = on ? ft->bytes[f] : 1u, v = on ? ft->vec[f] : 1u, epr = row_elements(E, v);
+    pf->io[f] = on ? io + (uint64_t)t * n * E : nullptr;
     pf->col[f] = ft->col[f] + (uint64_t)t * ft->col_stride[f];
-    pf->step[f] = (uint64_t)T * n * E;
+    pf->step[f] = step_rows * E;
     pf->bytes[f] = E;
-    pf->vec[f] = ft->vec[f];
-    uint32_t end = on ? n * row_elements(E, ft->vec[f]) : 0u;
+    pf->vec[f] = v;
+    pf->pieces[f] = on ? n * epr : 0u;
+    pf->recip[f] = epr > 1 ? 0xFFFFFFFFu / epr + 1u : 0u;
+    uint32_t end = on ? (n * epr + 63u) / 64u : 0u;
 #pragma unroll
     for (int d = 1; d < kMaxFields; d <<= 1) {
       const uint32_t before = (uint32_t)__shfl_up((int)end, d);
@@ -301,26 +136,39 @@ __device__ __forceinline__ void fill_piece_fields(const FieldTable* ft, uint32_t
     pf->end[f] = end;
   }
 }
-// Piece e < pf.end[last]: fields one after the other, row after row.
-__device__ __forceinline__ RowPiece find_piece(const PieceFields& pf, uint32_t e) {
+struct RowItem {        // this lane's piece of an item
+  bool on;
+  uint32_t f, w, row;   // field and access width (the same for the wave), row of the batch
+  uint8_t* stored;      // the piece in row 0 of the tree's payload
+  uint8_t* dense;       // the piece in the caller's array (step 0)
+};
+__device__ __forceinline__ uint32_t wave_value(uint32_t x) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)x); }   // (the same in all lanes)
+// Item i < pf.items(): fields one after the other.
+__device__ __forceinline__ RowItem find_item(const PieceFields& pf, uint32_t i) {
   uint32_t f = 0;
 #pragma unroll
-  for (uint32_t k = 0; k + 1 < (uint32_t)kMaxFields; ++k) f += e >= pf.end[k] ? 1u : 0u;
-  const uint32_t E = pf.bytes[f], v = pf.vec[f], el = e - (f ? pf.end[f - 1] : 0u);
+  for (uint32_t k = 0; k + 1 < (uint32_t)kMaxFields; ++k) f += i >= pf.end[k] ? 1u : 0u;
+  f = wave_value(f);
+  const uint32_t E = wave_value(pf.bytes[f]), v = wave_value(pf.vec[f]);
+  const uint32_t el = (i - (f ? wave_value(pf.end[f - 1]) : 0u)) * 64u + (threadIdx.x & 63u);
   const bool wide = moves_wide(E, v);
   const uint32_t epr = row_elements(E, v), w = wide ? 16u : v;
-  const uint32_t row = el / epr, k = el - row * epr;
+  RowItem p;
+  p.on = el < pf.pieces[f];
+  p.f = f;
+  p.w = w;
+  // (at most 1024 rows: the reciprocal is exact for less than 2048 pieces per row)
+  p.row = epr == 1 ? el : epr < 2048u ? __umulhi(el, wave_value(pf.recip[f])) : el / epr;
+  const uint32_t k = el - p.row * epr;
   const uint32_t at = wide && 16u * k + 16u > E ? E - 16u : k * w;
-  RowPiece p;
   p.stored = pf.col[f] + at;
-  p.dense = pf.io[f] + (uint64_t)row * E + at;
-  p.what = row << 8 | f << 5 | w;
+  p.dense = pf.io[f] + (uint64_t)p.row * E + at;
   return p;
 }
 typedef uint32_t Words4 __attribute__((ext_vector_type(4), aligned(4)));   // (16-byte pieces of some fields lie on 4-byte boundaries)
 typedef uint32_t Words2 __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ uint4 load_piece(const uint8_t* src, uint32_t w) {
-  uint4 v = make_uint4(0, 0, 0, 0);
+  uint4 v;   // (what a narrow piece leaves of it stays undefined: setting it would make the wave wait for loads under way)
   switch (w) {
     case 16: { const Words4 x = *(GlobalPtr<const Words4>)src; v = make_uint4(x.x, x.y, x.z, x.w); } break;
     case 8: { const Words2 x = *(GlobalPtr<const Words2>)src; v.x = x.x; v.y = x.y; } break;
@@ -343,6 +191,84 @@ __device__ __forceinline__ uint32_t ring_slot(uint32_t cursor, uint32_t j, uint3
   const uint64_t s = (uint64_t)cursor + j;
   return (uint32_t)(s >= N ? s - N : s);
 }
+// Items i .. end of one field of a gather (nodes: the batch's slots; one beyond the tree gives zeros and a flag), four at a
+// time: the loads of all, then the stores of all.
+template <typename V>
+__device__ __forceinline__ void gather_span(uint32_t i, uint32_t end, uint32_t pieces, uint32_t epr, uint32_t recip, uint32_t E,
+                                            uint32_t row_stride, const uint8_t* col, uint8_t* io, const uint32_t* nodes, uint32_t N,
+                                            uint32_t& flags) {
+  constexpr int U = 4;
+#pragma unroll 1
+  for (; i < end; i += U) {
+    V v[U];
+    uint32_t slot[U], el[U], at[U];
+#pragma unroll
+    for (int k = 0; k < U; ++k) {   // (beyond the end: the first piece again, so that no load stands in a branch)
+      el[k] = (i + k) * 64u + (threadIdx.x & 63u);
+      if (i + k >= end || el[k] >= pieces) el[k] = 0xFFFFFFFFu;
+      const uint32_t e = el[k] == 0xFFFFFFFFu ? 0u : el[k];
+      const uint32_t row = epr == 1 ? e : epr < 2048u ? __umulhi(e, recip) : e / epr, within = (e - row * epr) * (uint32_t)sizeof(V);
+      at[k] = within + (uint32_t)sizeof(V) > E ? E - (uint32_t)sizeof(V) : within;   // (wide pieces: the last one ends with the field)
+      slot[k] = nodes[row];
+      el[k] = el[k] == 0xFFFFFFFFu ? el[k] : row;
+    }
+#pragma unroll
+    for (int k = 0; k < U; ++k) v[k] = *(GlobalPtr<const V>)(col + (uint64_t)(slot[k] < N ? slot[k] : 0u) * row_stride + at[k]);
+#pragma unroll
+    for (int k = 0; k < U; ++k)
+      if (el[k] != 0xFFFFFFFFu) {
+        if (!(slot[k] < N)) {
+          v[k] = V{};
+          flags |= 1u;
+        }
+        *(GlobalPtr<V>)(io + (uint64_t)el[k] * E + at[k]) = v[k];
+      }
+  }
+}
+// This wave's share (number `part` of `parts`) of a gather: a run of items, so that it has to do with few fields.  `step`:
+// which step's part of the caller's arrays.  (Looped and not unrolled over the items: the code a round goes through has
+// to stay within the instruction cache.)
+__device__ __forceinline__ void gather_rows(const PieceFields& pf, uint32_t part, uint32_t parts, const uint32_t* nodes, uint32_t N,
+                                            uint32_t row_stride, uint64_t step, uint32_t& flags) {
+  const uint32_t items = pf.items(), per = (items + parts - 1) / parts;
+  uint32_t i = part * per;
+  const uint32_t last = i + per < items ? i + per : items;
+#pragma unroll 1
+  while (i < last) {
+    uint32_t f = 0;
+#pragma unroll
+    for (uint32_t k = 0; k + 1 < (uint32_t)kMaxFields; ++k) f += i >= pf.end[k] ? 1u : 0u;
+    f = wave_value(f);
+    const uint32_t E = wave_value(pf.bytes[f]), v = wave_value(pf.vec[f]), first = f ? wave_value(pf.end[f - 1]) : 0u;
+    const uint32_t fend = wave_value(pf.end[f]), pieces = wave_value(pf.pieces[f]), recip = wave_value(pf.recip[f]);
+    const uint32_t end = fend < last ? fend : last, epr = row_elements(E, v);
+    const uint8_t* col = pf.col[f];
+    uint8_t* io = pf.io[f] + step * pf.step[f];
+    switch (moves_wide(E, v) ? 16u : v) {
+      case 16: gather_span<Words4>(i - first, end - first, pieces, epr, recip, E, row_stride, col, io, nodes, N, flags); break;
+      case 8: gather_span<Words2>(i - first, end - first, pieces, epr, recip, E, row_stride, col, io, nodes, N, flags); break;
+      case 4: gather_span<uint32_t>(i - first, end - first, pieces, epr, recip, E, row_stride, col, io, nodes, N, flags); break;
+      case 2: gather_span<uint16_t>(i - first, end - first, pieces, epr, recip, E, row_stride, col, io, nodes, N, flags); break;
+      default: gather_span<uint8_t>(i - first, end - first, pieces, epr, recip, E, row_stride, col, io, nodes, N, flags); break;
+    }
+    i = end;
+  }
+}
+// The rows of an insertion at ring slot `cursor`, items first, first + every, ..; row j is left out where bit j of skip is set.
+__device__ __forceinline__ void place_row_piece(const RowItem& p, uint32_t cursor, uint32_t N, uint32_t row_stride, const uint32_t* skip,
+                                                const uint4& v) {
+  if (skip && ((skip[p.row >> 5] >> (p.row & 31u)) & 1u)) return;
+  store_piece(p.stored + (uint64_t)ring_slot(cursor, p.row, N) * row_stride, p.w, v);
+}
+__device__ __forceinline__ void insert_rows(const PieceFields& pf, uint32_t first, uint32_t every, uint32_t cursor, uint32_t N,
+                                            uint32_t row_stride, uint64_t step, const uint32_t* skip) {
+  const uint32_t items = pf.items();
+#pragma unroll 1
+  for (uint32_t e = first; e < items; e += every) {
+    const RowItem p = find_item(pf, e);
+    if (p.on) place_row_piece(p, cursor, N, row_stride, skip, load_piece(p.dense + step * pf.step[p.f], p.w));
+  }
+}
 // Waits until this wave's loads have arrived and its stores have been acknowledged.
 __device__ __forceinline__ void wait_memory() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 // Orders LDS accesses of one wave (which the hardware keeps in order) for the compiler.
@@ -350,6 +276,221 @@ __device__ __forceinline__ void wave_order() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// The tree work of one round, as the lanes of the team see it.  MEM: the leaves are in memory.  (A compile-time choice:
+// one pointer for both places would make flat accesses, and the wait for one of those is a wait for every load and
+// store the wave has under way; a branch at every access costs the registers of both sides.)
+template <bool MEM>
+struct TreeView {
+  float* tree;               // the LDS copy
+  float* leaves;             // MEM: the leaves (else they are in the copy, height 0 at offset 0)
+  uint32_t off_reg, n_reg;   // lane h of every wave: off[h], real nodes of height h (read from there: an LDS trip less per height)
+  uint32_t H, N;
+  uint32_t* s_max;           // running maximum (WAVE: the team keeps its own copy)
+  uint32_t* s_arrived;       // team waves that have come to one of its barriers, over all barriers (LDS)
+  bool apart;                // there are waves outside the team
+  uint32_t team;             // lanes of the team
+  uint2* s_runs;             // [16] of every team wave: the leaf its elements begin with, what is known of them (see change_tree)
+  uint32_t met;              // what s_arrived has to reach at the team's next barrier, less a team's waves
+  __device__ __forceinline__ uint32_t off(uint32_t h) const { return (uint32_t)__builtin_amdgcn_readlane((int)off_reg, (int)h); }
+  __device__ __forceinline__ void set_leaf(uint32_t i, float v) const {
+    if constexpr (MEM) as_global(leaves)[i] = v;
+    else tree[i] = v;
+  }
+  __device__ __forceinline__ float leaf(uint32_t i) const {
+    if constexpr (MEM) return as_global(leaves)[i];
+    else return tree[i];
+  }
+  __device__ __forceinline__ uint32_t n(uint32_t h) const { return (uint32_t)__builtin_amdgcn_readlane((int)n_reg, (int)h); }
+  // Barrier of the team between phases that hand leaves or sums to other waves of it.  The hardware's barrier would hold
+  // the team until the row waves come by; the team's waves count themselves in LDS instead (all of them are resident, and
+  // each comes to every barrier, so the wait ends).
+  __device__ __forceinline__ void sync() {
+    if constexpr (MEM) wait_memory();
+    if (!apart) {
+      lds_barrier();
+      return;
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    if ((threadIdx.x & 63u) == 0) atomicAdd(s_arrived, 1u);
+    met += team >> 6;
+    while ((int)(wave_value(*(volatile uint32_t*)s_arrived) - met) < 0) {}
+    asm volatile("" ::: "memory");
+  }
+};
+template <int LOGK, bool MEM>
+__device__ __forceinline__ float child_group_sum(const TreeView<MEM>& v, uint32_t h, uint32_t parent) {
+  constexpr int K = Fan<LOGK>::K;
+  if constexpr (MEM) {
+    if (h == 1) return lane_group_sum<LOGK>(as_global(v.leaves) + (size_t)parent * K);
+  }
+  return lane_group_sum<LOGK>(v.tree + v.off(h - 1) + (size_t)parent * K);
+}
+
+// An update of n elements (lane tid < n of the team: leaf ui gets uv) and then an insertion (lanes with `inserts`: row at
+// ring slot `slot`, value in_v or the running maximum), and the ancestors of both in one pass.  Called by the team.  `sorted`: the indices do not decrease from lane to lane.
+struct UpdateWork {
+  bool on, mine, sorted;
+  uint32_t n, i, size;
+  float v;
+};
+struct InsertWork {
+  bool on, mine, given;      // given: the value is `v`, else the running maximum
+  uint32_t n, slot;
+  float v;
+};
+template <int LOGK, bool WAVE, bool MEM>
+__device__ __forceinline__ void change_tree(TreeView<MEM>& tv, const UpdateWork& u, const InsertWork& ins, uint32_t& max_bits,
+                                            uint32_t& flags) {
+  const uint32_t tid = threadIdx.x;
+  bool valid = false, placed = false;
+  if (u.on) {
+    if (u.mine) {
+      if (!(u.i < u.size)) flags |= 1u;
+      else if (!valid_priority(u.v)) flags |= 2u;
+      else valid = true;
+    }
+    const uint32_t mx = valid && u.v > 0.0f ? __float_as_uint(u.v) : 0u;
+    bool won = valid;
+    const uint32_t mark = 0x80000001u + tid;
+    if (WAVE && u.sorted && !__any(u.mine && !valid)) {
+      // (elements of one leaf are neighbours, and the last of them wins)
+      const uint32_t next = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)u.i, 0x130 /* wave_shl:1: from the lane above */, 0xF, 0xF, true);
+      won = valid && (tid + 1 >= u.n || next != u.i);
+    } else if (!WAVE && u.sorted) {
+      // The last valid element of every run of equal leaves wins.  Within a wave that is read off two masks: where runs
+      // begin, and which elements are valid.  A run that reaches the end of its wave may go on in the next ones: each
+      // wave leaves the leaf it begins with and whether that first run has a valid element (1) and is all there is (2).
+      const unsigned lane = tid & 63u;
+      const uint32_t below = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)u.i, 0x138 /* wave_shr:1: from the lane below */, 0xF, 0xF, true);
+      const unsigned long long begins = __ballot(u.mine && (lane == 0 || below != u.i)), good = __ballot(valid);
+      const unsigned long long later = lane == 63u ? 0ull : begins >> (lane + 1u);
+      const unsigned run_end = later ? lane + 1u + (unsigned)__builtin_ctzll(later) : 64u;   // first lane behind this lane's run
+      const unsigned long long behind = lane == 63u ? 0ull : (good >> (lane + 1u)) & (run_end == 64u && lane == 0 ? ~0ull : (1ull << (run_end - lane - 1u)) - 1ull);
+      const unsigned long long first_run = begins & ~1ull ? (1ull << __builtin_ctzll(begins & ~1ull)) - 1ull : ~0ull;
+      if (lane == 0) tv.s_runs[tid >> 6] = make_uint2(u.mine ? u.i : 0xFFFFFFFFu, ((good & first_run) ? 1u : 0u) | ((begins & ~1ull) ? 0u : 2u));
+      won = valid && !behind;
+      const uint32_t m = wave_max_u32(mx);
+      if (lane == 0 && m) atomicMax(tv.s_max, m);
+      tv.sync();
+      if (won && run_end == 64u)
+        for (uint32_t w = (tid >> 6) + 1u; w < (tv.team >> 6); ++w) {
+          const uint2 r = tv.s_runs[w];
+          if (r.x != u.i) break;
+          if (r.y & 1u) won = false;
+          if (!(r.y & 2u) || !won) break;
+        }
+    } else if constexpr (MEM) {   // (markers in memory: atomics there, and a read that passes by the first-level cache)
+      GlobalPtr<uint32_t> bits = (GlobalPtr<uint32_t>)tv.leaves;
+      if (valid) __hip_atomic_fetch_max(&bits[u.i], mark, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if constexpr (WAVE) wait_memory(); else tv.sync();
+      won = valid && __hip_atomic_load(&bits[u.i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == mark;
+      if constexpr (WAVE) wait_memory(); else tv.sync();
+    } else {
+      uint32_t* bits = reinterpret_cast<uint32_t*>(tv.tree);
+      if (valid) atomicMax(&bits[u.i], mark);
+      if constexpr (WAVE) wave_order(); else tv.sync();
+      won = valid && bits[u.i] == mark;
+      if constexpr (WAVE) wave_order(); else tv.sync();
+    }
+    if (won) tv.set_leaf(u.i, u.v);
+    if constexpr (WAVE) {
+      const uint32_t m = wave_max_u32(mx);
+      max_bits = m > max_bits ? m : max_bits;
+      wave_order();
+    } else {
+      if (!u.sorted && mx) atomicMax(tv.s_max, mx);
+      if (ins.on || !u.sorted) tv.sync();   // (the insertion comes behind the update)
+    }
+  }
+  if (ins.on) {
+    uint32_t mx = 0;
+    if (ins.mine) {
+      float v = __uint_as_float(WAVE ? max_bits : *tv.s_max);
+      placed = true;
+      if (ins.given) {
+        v = ins.v;
+        placed = valid_priority(v);
+        if (!placed) flags |= 2u;
+        mx = placed && v > 0.0f ? __float_as_uint(v) : 0u;
+      }
+      if (placed) tv.set_leaf(ins.slot, v);
+    }
+    if (ins.given) {
+      if constexpr (WAVE) {
+        const uint32_t m = wave_max_u32(mx);
+        max_bits = m > max_bits ? m : max_bits;
+      } else if (mx) {
+        atomicMax(tv.s_max, mx);
+      }
+    }
+  }
+  // the ancestors (elements that share a parent store the same sum)
+  if (u.on || ins.on) {
+    if constexpr (WAVE) {
+      const bool together = !u.on || !ins.on || u.n + ins.n <= 64u;   // (no lane has both)
+      for (int pass = 0; pass < (together ? 1 : 2); ++pass) {
+        const bool act = together ? valid || placed : pass == 0 ? valid : placed;
+        const uint32_t leaf = together ? (placed ? ins.slot : u.i) : pass == 0 ? u.i : ins.slot;
+        for (uint32_t h = 1; h <= tv.H; ++h) {
+          wave_order();
+          if (act) {
+            const uint32_t parent = leaf >> (h * LOGK);
+            tv.tree[tv.off(h) + parent] = child_group_sum<LOGK, MEM>(tv, h, parent);
+          }
+        }
+      }
+      wave_order();
+    } else {
+      // A height of no more nodes than there are elements is recomputed whole (fewer lanes than elements); from the
+      // first height of at most 64 nodes on one wave goes up to the root without barriers.
+      const uint32_t elements = (u.on ? u.n : 0u) + (ins.on ? ins.n : 0u);
+      for (uint32_t h = 1; h <= tv.H; ++h) {
+        tv.sync();
+        const uint32_t nodes = tv.n(h);
+        if (nodes <= 64u) {
+          if (tid < 64u)
+            for (; h <= tv.H; ++h) {
+              if (tid < tv.n(h)) tv.tree[tv.off(h) + tid] = child_group_sum<LOGK, MEM>(tv, h, tid);
+              wave_order();
+            }
+          break;
+        }
+        if (nodes <= elements) {
+          for (uint32_t j = tid; j < nodes; j += tv.team) tv.tree[tv.off(h) + j] = child_group_sum<LOGK, MEM>(tv, h, j);
+          continue;
+        }
+        const uint32_t pu = u.i >> (h * LOGK), pi = ins.slot >> (h * LOGK);
+        if (valid) tv.tree[tv.off(h) + pu] = child_group_sum<LOGK, MEM>(tv, h, pu);
+        if (placed) tv.tree[tv.off(h) + pi] = child_group_sum<LOGK, MEM>(tv, h, pi);
+      }
+    }
+  }
+}
+
+// Sample i of n (lane i of the team; lanes beyond repeat the last one), uniform u: leaf and value, 0xFFFFFFFF and 0 where
+// nothing can be sampled.
+template <int LOGK, bool MEM>
+__device__ __forceinline__ void walk_tree(const TreeView<MEM>& tv, uint32_t i, uint32_t n, float u, uint32_t& node, float& val) {
+  constexpr int K = Fan<LOGK>::K;
+  const float total = tv.tree[tv.off(tv.H)];
+  node = 0xFFFFFFFFu;
+  val = 0.0f;
+  if (!(total > 0.0f)) return;
+  float r = ((float)(i < n ? i : n - 1) + u) * (total / (float)n);
+  node = 0;
+  val = total;
+  for (uint32_t h = tv.H; h-- > 0;) {
+    unsigned child;
+    if constexpr (MEM) {
+      if (h == 0) descend_lane<LOGK>(as_global(tv.leaves) + (size_t)node * K, r, child, val);
+      else descend_lane<LOGK>(tv.tree + tv.off(h) + (size_t)node * K, r, child, val);
+    } else {
+      descend_lane<LOGK>(tv.tree + tv.off(h) + (size_t)node * K, r, child, val);
+    }
+    node = node * K + child;
+  }
 }
 
 // The list of steps.  What bounds it is one chain of instructions and LDS trips from step to step (the tree as one
@@ -361,25 +502,25 @@ __device__ __forceinline__ void wave_order() {
 //  - The update of step s and the insertion of step s + 1 are adjacent tree changes with nothing read in between: the
 //    leaves are written one after the other and the ancestors of both recomputed in one pass.
 //  - WAVE: with at most 64 samples and 64 new rows the team is one wave, whose LDS accesses stay in order by
-//    themselves: no barriers inside the tree work, two per step in all.
+//    themselves: no barriers inside the tree work, two per step in all.  Several team waves meet at barriers of their own
+//    (counted in LDS), which do not wait for the row waves.
 //  - Barriers wait for LDS only.  A __syncthreads() also waits for every store of the wave to be acknowledged from
 //    memory, a microsecond at each phase that writes results or rows.
 // The order that memory needs: the stored rows of an insertion are read by the gather of the same step at the earliest
 // (its lanes wait for their stores before the barrier that ends the sampling), and overwrite what the gather of the
 // step before has read (all of whose loads have arrived at the barrier in front of the insertion's stores).
-// 100 steps on 10 000 leaves at K = 16 (32 samples, 4 new rows of 41 bytes): 282 us; 1001 us as one phase after the
+// 100 steps on 10 000 leaves at K = 16 (32 samples, 4 new rows of 41 bytes): 266 us; 1001 us as one phase after the
 // other by the whole workgroup with a full barrier between them.
-template <int LOGK, bool WAVE>
+template <int LOGK, bool WAVE, bool MEM>
 __global__ void __launch_bounds__(1024)
 k_run_steps(StreamKernelArgs ka) {
-  constexpr int K = Fan<LOGK>::K;
-  constexpr int kGather = 4, kInsert = 2;   // pieces a lane holds in registers; a longer list of pieces goes on in a loop
   const Geom& g = ka.g;
   const StreamArgs& a = ka.a;
   extern __shared__ __attribute__((aligned(16))) float tree[];
   __shared__ LevelTable tab;
   __shared__ uint32_t s_off[kMaxHeight + 2];
-  __shared__ uint32_t s_max, s_vmin[2], s_bmin[2], s_flags;
+  __shared__ uint32_t s_max, s_vmin[2], s_bmin[2], s_flags, s_arrived;
+  __shared__ uint2 s_runs[16];
   __shared__ PieceFields s_rows, s_ins;
   const uint32_t t = blockIdx.x;
   const uint32_t tid = threadIdx.x, lane = tid & 63u;
@@ -391,32 +532,34 @@ k_run_steps(StreamKernelArgs ka) {
     s_max = read_max_bits(g, t);
     s_vmin[0] = s_vmin[1] = s_bmin[0] = s_bmin[1] = kNoMin;
     s_flags = 0;
+    s_arrived = 0;
   }
   // lanes of the team, of the rows, of the weights
-  const uint32_t team = WAVE ? 64u : ((B > n_ins ? B : n_ins) + 63u) / 64u * 64u;
-  const bool apart = WAVE || team <= 512u;
+  const uint32_t wanted = WAVE ? 64u : ((B > n_ins ? B : n_ins) + 63u) / 64u * 64u;
+  const bool apart = wanted <= 512u;
+  const uint32_t team = apart ? wanted : 1024u;   // (not apart: every wave comes to the team's barriers)
   const bool in_team = tid < team, in_rows = !apart || tid >= team;
   const uint32_t rn = apart ? 1024u - team : 1024u, rl = apart ? tid - team : tid;
+  const uint32_t rw = wave_value(rl >> 6), rws = rn >> 6;   // number of this wave among the row waves, and how many there are
   const uint32_t w0 = apart ? 1024u - (B + 63u) / 64u * 64u : 0u;
   const bool weigher = tid >= w0 && tid - w0 < B;
   // (the field tables from the argument segment by vector loads, a lane per field)
-  if (tid >= 128 && tid < 192) fill_piece_fields(kernarg_at<FieldTable>(offsetof(StreamKernelArgs, a) + offsetof(StreamArgs, rows)), t, T, B, &s_rows);
-  if (tid >= 192 && tid < 256) fill_piece_fields(kernarg_at<FieldTable>(offsetof(StreamKernelArgs, a) + offsetof(StreamArgs, ins)), t, T, n_ins, &s_ins);
+  if (tid >= 128 && tid < 256) {
+    const bool rows = tid < 192;
+    const FieldTable* ft = kernarg_at<FieldTable>(offsetof(StreamKernelArgs, a) + (rows ? offsetof(StreamArgs, rows) : offsetof(StreamArgs, ins)));
+    const uint32_t n = rows ? B : n_ins;
+    fill_piece_fields(ft, lane < (uint32_t)kMaxFields ? ft->io[lane] : nullptr, t, n, (uint64_t)T * n, rows ? &s_rows : &s_ins);
+  }
   __syncthreads();
-  const uint32_t gather_pieces = s_rows.end[kMaxFields - 1], insert_pieces = s_ins.end[kMaxFields - 1];
-  RowPiece gp[kGather], ip[kInsert];
-  uint4 gv[kGather], iv[kInsert];
-#pragma unroll
-  for (int k = 0; k < kGather; ++k)
-    if (in_rows && rl + k * rn < gather_pieces) gp[k] = find_piece(s_rows, rl + k * rn);
-#pragma unroll
-  for (int k = 0; k < kInsert; ++k)
-    if (in_rows && rl + k * rn < insert_pieces) {
-      ip[k] = find_piece(s_ins, rl + k * rn);
-      iv[k] = load_piece(ip[k].dense, ip[k].w());
-    }
+  const uint32_t insert_items = in_rows ? s_ins.items() : 0u;
+  RowItem ip;
+  uint4 iv;
+  if (rw < insert_items) {   // (the first item of an insertion is fetched a step ahead)
+    ip = find_item(s_ins, rw);
+    if (ip.on) iv = load_piece(ip.dense, ip.w);
+  }
   // inputs of the team: the uniform of the step to sample, value (and index) of the update to apply, inserted priority
-  float u_i = 0.0f, up_v = 0.0f, in_v = 0.0f;
+  float u_i = 0.0f, u_next = 0.0f, up_v = 0.0f, in_v = 0.0f;
   uint32_t up_i = 0;
   const uint32_t j_ins = WAVE ? lane - (64u - n_ins) : tid;   // (WAVE: the last lanes of the wave, so that samples and rows share it)
   const bool inserts = in_team && (!WAVE || lane >= 64u - n_ins) && j_ins < n_ins;
@@ -425,63 +568,40 @@ k_run_steps(StreamKernelArgs ka) {
   __syncthreads();
   LdsTree lt;
   lt.tree = tree;
-  lt.leaves_mem = a.leaves_in_memory ? tab.lvl[0] : nullptr;
+  lt.leaves_mem = MEM ? tab.lvl[0] : nullptr;
   lt.off = s_off;
   lt.max_bits = &s_max;
-  lt.vmin_bits = lt.bmin_bits = nullptr;
-  lt.skip = nullptr;
-  lt.sampled = nullptr;
   lt.H = H;
   lt.N = N;
   lds_tree_load(tab, lt);
   uint32_t* nodes = reinterpret_cast<uint32_t*>(tree + s_off[H + 1]);   // [B] sampled leaves of the step
   float* values = reinterpret_cast<float*>(nodes + 512);                // [B] and their values (apart only: B <= 512)
-  const bool mem = lt.leaves_mem != nullptr;
-  float* leaves = mem ? lt.leaves_mem : tree;                           // (height 0 starts at LDS offset 0)
-  const uint32_t off_reg = s_off[lane <= H + 1 ? lane : H + 1];         // offsets from lane registers: an LDS trip less per height
-  auto off = [&](uint32_t h) -> uint32_t { return (uint32_t)__builtin_amdgcn_readlane((int)off_reg, (int)h); };
+  TreeView<MEM> tv;
+  tv.tree = tree;
+  tv.leaves = lt.leaves_mem;
+  tv.off_reg = s_off[lane <= H + 1 ? lane : H + 1];
+  tv.n_reg = tab.n[lane <= H ? lane : H];
+  tv.H = H;
+  tv.N = N;
+  tv.s_max = &s_max;
+  tv.s_arrived = &s_arrived;
+  tv.s_runs = s_runs;
+  tv.apart = apart;
+  tv.team = team;
+  tv.met = 0;
   uint32_t cursor = a.cursor, size = a.size, upd_size = 0;
   uint32_t flags = 0;
   __syncthreads();
   uint32_t max_bits = s_max;      // (WAVE: the team's copy; else s_max counts)
   uint32_t node = 0xFFFFFFFFu;    // this lane's sample of the step before
   float val = 0.0f;
-  // barrier between phases of the tree work
-  auto sync = [&]() {
-    if (mem) wait_memory();
-    lds_barrier();
-  };
-  auto leaf_group_sum = [&](uint32_t h, uint32_t parent) -> float {
-    return h == 1 && mem ? lane_group_sum<LOGK>(lt.leaves_mem + (size_t)parent * K)
-                         : lane_group_sum<LOGK>(tree + off(h - 1) + (size_t)parent * K);
-  };
-
   for (uint32_t s = 0;; ++s) {
     const bool more = s < a.n_steps;
-    // ---- rows and weights of the step before: loads
+    // ---- rows and weights of the step before
     float w_out = 0.0f, v_out = 0.0f;
     uint32_t n_out = 0;
     if (s) {
-      if (in_rows) {
-#pragma unroll
-        for (int k = 0; k < kGather; ++k)
-          if (rl + k * rn < gather_pieces) {
-            const uint32_t slot = nodes[gp[k].row()];
-            const bool ok = slot < N;
-            if (!ok) flags |= 1u;
-            gv[k] = load_piece(gp[k].stored + (uint64_t)(ok ? slot : 0u) * a.rows.row_stride, gp[k].w());
-            if (!ok) gv[k] = make_uint4(0, 0, 0, 0);
-          }
-        for (uint32_t e = rl + kGather * rn; e < gather_pieces; e += rn) {
-          const RowPiece p = find_piece(s_rows, e);
-          const uint32_t slot = nodes[p.row()];
-          const bool ok = slot < N;
-          if (!ok) flags |= 1u;
-          uint4 v = load_piece(p.stored + (uint64_t)(ok ? slot : 0u) * a.rows.row_stride, p.w());
-          if (!ok) v = make_uint4(0, 0, 0, 0);
-          store_piece(p.dense + (uint64_t)(s - 1) * s_rows.step[p.field()], p.w(), v);
-        }
-      }
+      if (in_rows) gather_rows(s_rows, rw, rws, nodes, N, a.rows.row_stride, s - 1, flags);
       if (weigher) {
         n_out = nodes[tid - w0];
         v_out = apart ? values[tid - w0] : val;
@@ -494,94 +614,10 @@ k_run_steps(StreamKernelArgs ka) {
     }
     // ---- the tree: update of the step before, insertion of this one
     const bool do_upd = s > 0 && a.upd_prio != nullptr, do_ins = more && n_ins > 0;
-    if (!WAVE || tid < 64u) {
-      const uint32_t ui = a.upd_is_sampled ? node : up_i;
-      bool valid = false, placed = false;
-      uint32_t slot = 0;
-      if (do_upd) {
-        const bool mine = in_team && tid < B;
-        if (mine) {
-          if (!(ui < upd_size)) flags |= 1u;
-          else if (!valid_priority(up_v)) flags |= 2u;
-          else valid = true;
-        }
-        const uint32_t mx = valid && up_v > 0.0f ? __float_as_uint(up_v) : 0u;
-        bool won = valid;
-        const uint32_t mark = 0x80000001u + tid;
-        uint32_t* bits = reinterpret_cast<uint32_t*>(leaves);
-        if (WAVE && a.upd_is_sampled && !__any(mine && !valid)) {
-          // (samples come out in leaf order: elements of one leaf are neighbours, and the last of them wins)
-          const uint32_t next = (uint32_t)__shfl_down((int)ui, 1);
-          won = valid && (tid + 1 >= B || next != ui);
-        } else if (mem) {   // (markers in memory: atomics there, and a read that passes by the first-level cache)
-          if (valid) atomicMax(&bits[ui], mark);
-          if constexpr (WAVE) wait_memory(); else sync();
-          won = valid && __hip_atomic_load(&bits[ui], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == mark;
-          if constexpr (WAVE) wait_memory(); else sync();
-        } else {
-          if (valid) atomicMax(&bits[ui], mark);
-          if constexpr (WAVE) wave_order(); else sync();
-          won = valid && bits[ui] == mark;
-          if constexpr (WAVE) wave_order(); else sync();
-        }
-        if (won) leaves[ui] = up_v;
-        if constexpr (WAVE) {
-          const uint32_t m = wave_max_u32(mx);
-          max_bits = m > max_bits ? m : max_bits;
-          wave_order();
-        } else {
-          if (mx) atomicMax(&s_max, mx);
-          sync();
-        }
-      }
-      if (do_ins) {
-        uint32_t mx = 0;
-        if (inserts) {
-          slot = ring_slot(cursor, j_ins, N);
-          float v = __uint_as_float(WAVE ? max_bits : s_max);
-          placed = true;
-          if (a.ins_prio) {
-            v = in_v;
-            placed = valid_priority(v);
-            if (!placed) flags |= 2u;
-            mx = placed && v > 0.0f ? __float_as_uint(v) : 0u;
-          }
-          if (placed) leaves[slot] = v;
-        }
-        if (a.ins_prio) {
-          if constexpr (WAVE) {
-            const uint32_t m = wave_max_u32(mx);
-            max_bits = m > max_bits ? m : max_bits;
-          } else if (mx) {
-            atomicMax(&s_max, mx);
-          }
-        }
-      }
-      // ancestors of both (elements that share a parent store the same sum)
-      if (do_upd || do_ins) {
-        if constexpr (WAVE) {
-          const bool together = !do_upd || !do_ins || B + n_ins <= 64u;
-          for (int pass = 0; pass < (together ? 1 : 2); ++pass) {
-            const bool act = together ? valid || placed : pass == 0 ? valid : placed;
-            const uint32_t leaf = together ? (placed ? slot : ui) : pass == 0 ? ui : slot;
-            for (uint32_t h = 1; h <= H; ++h) {
-              wave_order();
-              if (act) {
-                const uint32_t parent = leaf >> (h * LOGK);
-                tree[off(h) + parent] = leaf_group_sum(h, parent);
-              }
-            }
-          }
-          wave_order();
-        } else {
-          for (uint32_t h = 1; h <= H; ++h) {
-            sync();
-            const uint32_t pu = ui >> (h * LOGK), pi = slot >> (h * LOGK);
-            if (valid) tree[off(h) + pu] = leaf_group_sum(h, pu);
-            if (placed) tree[off(h) + pi] = leaf_group_sum(h, pi);
-          }
-        }
-      }
+    if (in_team) {
+      const UpdateWork up{do_upd, in_team && tid < B, a.upd_is_sampled != 0, B, a.upd_is_sampled ? node : up_i, upd_size, up_v};
+      const InsertWork in{do_ins, inserts, a.ins_prio != nullptr, n_ins, inserts ? ring_slot(cursor, j_ins, N) : 0u, in_v};
+      change_tree<LOGK, WAVE, MEM>(tv, up, in, max_bits, flags);
       // inputs of the next round
       if (in_team && tid < B) {
         const size_t bo = ((size_t)s * T + t) * B + tid;
@@ -589,6 +625,7 @@ k_run_steps(StreamKernelArgs ka) {
           up_v = a.upd_prio[bo];
           if (!a.upd_is_sampled) up_i = a.upd_idx[bo];
         }
+        if (s + 1 < a.n_steps) u_next = a.u[bo + (size_t)T * B];   // (here and not behind the walk: the next wait would be for it)
       }
     }
     if (do_ins) {
@@ -596,28 +633,16 @@ k_run_steps(StreamKernelArgs ka) {
       size = size + n_ins > N ? N : size + n_ins;
     }
     upd_size = size;
-    // ---- all loads of stored rows have arrived; the tree is whole
-    if (in_rows || (mem && (!WAVE || a.buffer_norm))) wait_memory();
+    // ---- the rows of the step before have been read; the tree is whole
+    if (WAVE && MEM && a.buffer_norm) wait_memory();   // (!WAVE: the team has waited for its leaves)
     lds_barrier();
     if (do_ins && in_rows) {
       const uint32_t first = cursor >= n_ins ? cursor - n_ins : cursor + (N - n_ins);
-#pragma unroll
-      for (int k = 0; k < kInsert; ++k)
-        if (rl + k * rn < insert_pieces)
-          store_piece(ip[k].stored + (uint64_t)ring_slot(first, ip[k].row(), N) * a.ins.row_stride, ip[k].w(), iv[k]);
-      for (uint32_t e = rl + kInsert * rn; e < insert_pieces; e += rn) {
-        const RowPiece p = find_piece(s_ins, e);
-        store_piece(p.stored + (uint64_t)ring_slot(first, p.row(), N) * a.ins.row_stride, p.w(),
-                    load_piece(p.dense + (uint64_t)s * s_ins.step[p.field()], p.w()));
-      }
+      if (rw < insert_items && ip.on) place_row_piece(ip, first, N, a.ins.row_stride, nullptr, iv);
+      insert_rows(s_ins, rw + rws, rws, first, N, a.ins.row_stride, s, nullptr);
       wait_memory();
     }
     if (s) {
-      if (in_rows) {
-#pragma unroll
-        for (int k = 0; k < kGather; ++k)
-          if (rl + k * rn < gather_pieces) store_piece(gp[k].dense + (uint64_t)(s - 1) * s_rows.step[gp[k].field()], gp[k].w(), gv[k]);
-      }
       if (weigher) {
         const size_t o = ((size_t)(s - 1) * T + t) * B + (tid - w0);
         a.out_idx[o] = n_out;
@@ -627,52 +652,34 @@ k_run_steps(StreamKernelArgs ka) {
     }
     if (!more) break;
     if (s + 1 < a.n_steps && n_ins) {
-      if (in_rows) {
-#pragma unroll
-        for (int k = 0; k < kInsert; ++k)
-          if (rl + k * rn < insert_pieces) iv[k] = load_piece(ip[k].dense + (uint64_t)(s + 1) * s_ins.step[ip[k].field()], ip[k].w());
-      }
+      if (rw < insert_items && ip.on) iv = load_piece(ip.dense + (uint64_t)(s + 1) * s_ins.step[ip.f], ip.w);
       if (inserts && a.ins_prio) in_v = a.ins_prio[((size_t)(s + 1) * T + t) * n_ins + j_ins];
     }
     if (tid == 0) s_vmin[(s + 1) & 1u] = s_bmin[(s + 1) & 1u] = kNoMin;   // (read by the weights of step s - 1, before the barrier)
     // ---- weights relative to the whole tree: its smallest positive leaf
     if (a.buffer_norm && a.out_w && in_rows) {
       uint32_t m = kNoMin;
-      for (uint32_t e = rl; e < N; e += rn) m = min_u32(m, positive_bits(leaves[e]));
+      for (uint32_t e = rl; e < N; e += rn) m = min_u32(m, positive_bits(tv.leaf(e)));
       m = wave_min_u32(m);
       if (lane == 0 && m != kNoMin) atomicMin(&s_bmin[s & 1u], m);
     }
     // ---- sampling
-    if (in_team) {
-      const float total = tree[off(H)];
-      node = 0xFFFFFFFFu;
-      val = 0.0f;
-      if (total > 0.0f) {
-        const uint32_t si = tid < B ? tid : B - 1;
-        float r = ((float)si + u_i) * (total / (float)B);
-        node = 0;
-        val = total;
-        for (uint32_t h = H; h-- > 0;) {
-          unsigned child;
-          if (h == 0 && mem) descend_lane<LOGK>(lt.leaves_mem + (size_t)node * K, r, child, val);
-          else descend_lane<LOGK>(tree + off(h) + (size_t)node * K, r, child, val);
-          node = node * K + child;
+    if (in_team && (WAVE || (tid & ~63u) < B)) {
+      walk_tree<LOGK, MEM>(tv, tid, B, u_i, node, val);
+      if (node == 0xFFFFFFFFu) {
+        if (tid == 0) flags |= 4u;
+      } else if (a.out_w) {
+        const uint32_t m = wave_min_u32(tid < B ? __float_as_uint(val) : kNoMin);
+        if (lane == 0) {
+          if constexpr (WAVE) s_vmin[s & 1u] = m;
+          else atomicMin(&s_vmin[s & 1u], m);
         }
-        if (a.out_w) {
-          const uint32_t m = wave_min_u32(tid < B ? __float_as_uint(val) : kNoMin);
-          if (lane == 0) {
-            if constexpr (WAVE) s_vmin[s & 1u] = m;
-            else atomicMin(&s_vmin[s & 1u], m);
-          }
-        }
-      } else if (tid == 0) {
-        flags |= 4u;
       }
       if (tid < B) {
         nodes[tid] = node;
         if (apart) values[tid] = val;
       }
-      if (tid < B && s + 1 < a.n_steps) u_i = a.u[((size_t)(s + 1) * T + t) * B + tid];
+      u_i = u_next;
     }
     lds_barrier();
   }
@@ -688,74 +695,325 @@ k_run_steps(StreamKernelArgs ka) {
 // fixed step: each request names its operation (the paper's unified operation code, Section V-A)
 // and is decoded when its turn comes.  The queue's length is fixed at launch; the kernel ends after
 // its last request.
+//
+// The requests are taken in rounds of at most one update, then one insertion, then one sampling request: what a step
+// of k_run_steps does between two of its samplings, with parts left out where the queue has something else.  A round
+// runs as a step does there (see above): its tree changes in one pass over the ancestors, rows and weights of the
+// sampling request before it beside them, and what it reads fetched in the round before.  The requests themselves come
+// in two rounds ahead (three at a time: a round takes no more).
+// Fetching ahead is only right where a request reads nothing that one just before it writes (an update whose index
+// array is the sampled one, say).  The host has checked that (QueueArgs::ahead); where it does not hold, every
+// request is a round of its own with an empty one behind it, which brings all results to memory.
+// 20 times (insert 16 rows, sample 512, update them) on 30 000 leaves at K = 16: 185 us; 353 us one request after the
+// other by the whole workgroup with a full barrier between their phases.
 struct QueueKernelArgs {            // one kernel argument (Geom first: see fill_level_table)
   Geom g;
   QueueArgs a;
 };
-
-template <int LOGK>
+constexpr uint32_t kRoundRequests = 3, kRequestWords = sizeof(per_request) / 4;
+struct QueueRound {                 // what a round takes: places of its requests among the three fetched for it (3: none)
+  uint32_t upd, ins, smp, used;
+};
+// The round that starts with the `left` requests of q (at most three are looked at).
+__device__ __forceinline__ QueueRound take_round(const per_request* q, uint32_t left, bool single) {
+  QueueRound r{3, 3, 3, 0};
+  uint32_t stage = 0;   // 1: past the update, 2: past the insertion, 3: past the sampling
+#pragma unroll
+  for (uint32_t k = 0; k < kRoundRequests; ++k) {
+    const uint32_t op = k < left ? (uint32_t)__builtin_amdgcn_readfirstlane((int)q[k].op) : 0u;
+    const bool u = op == PER_OP_UPDATE && stage < 1, i = op == PER_OP_INSERT && stage < 2, s = op == PER_OP_SAMPLE && stage < 3;
+    if (r.used == k && (u || i || s) && !(single && k)) {
+      if (u) r.upd = k, stage = 1;
+      if (i) r.ins = k, stage = 2;
+      if (s) r.smp = k, stage = 3;
+      r.used = k + 1;
+    }
+  }
+  if (r.used == 0 && left) r.used = 1;   // (an unknown operation is passed over: the kernel ends whatever the queue holds)
+  return r;
+}
+template <int LOGK, bool WAVE, bool MEM>
 __global__ void __launch_bounds__(1024)
 k_run_requests(QueueKernelArgs ka) {
   const Geom& g = ka.g;
   const QueueArgs& a = ka.a;
   extern __shared__ __attribute__((aligned(16))) float tree[];
   __shared__ LevelTable tab;
-  __shared__ FieldTable s_ft;        // the buffer's columns with the current request's row arrays
   __shared__ uint32_t s_off[kMaxHeight + 2];
-  __shared__ uint32_t s_skip[32];
-  __shared__ uint32_t s_max, s_vmin, s_bmin, s_flags;
+  __shared__ per_request s_req[3][kRoundRequests];   // round i: s_req[i % 3]
+  __shared__ PieceFields s_rows[2], s_ins[2];        // by parity of the round
+  __shared__ uint32_t s_skip[2][32];                 // bit j: row j of the round's insertion is deferred
+  __shared__ uint32_t s_max, s_vmin[2], s_bmin[2], s_flags, s_arrived;
+  __shared__ uint2 s_runs[16];
   const uint32_t t = blockIdx.x;
-  const uint32_t tid = threadIdx.x;
-  const uint32_t H = g.H;
+  const uint32_t tid = threadIdx.x, lane = tid & 63u;
+  const uint32_t H = g.H, N = g.N, n_requests = a.n_requests;
+  const FieldTable* fields = kernarg_at<FieldTable>(offsetof(QueueKernelArgs, a) + offsetof(QueueArgs, fields));
+  const uint32_t* queue = reinterpret_cast<const uint32_t*>(a.queue);
   fill_level_table(H, t, &tab);
   if (tid >= 64 && tid <= 64 + H + 1)
     s_off[tid - 64] = kernarg_at<QueueArgs>(offsetof(QueueKernelArgs, a))->off[tid - 64];
   if (tid == 0) {
     s_max = read_max_bits(g, t);
+    s_vmin[0] = s_vmin[1] = s_bmin[0] = s_bmin[1] = kNoMin;
     s_flags = 0;
-    s_ft = a.fields;
+    s_arrived = 0;
   }
+  // words of the three requests from `at` on, two per lane of one wave
+  const bool fetcher = tid >= 960;
+  constexpr uint32_t kFetch = kRoundRequests * kRequestWords;
+  static_assert(kFetch <= 128, "two words per lane");
+  auto fetch = [&](uint32_t at, uint32_t& x, uint32_t& y) {
+    const uint64_t w0 = (uint64_t)at * kRequestWords, all = (uint64_t)n_requests * kRequestWords;
+    x = y = 0;
+    if (w0 + lane < all) x = queue[w0 + lane];
+    if (lane + 64u < kFetch && w0 + lane + 64u < all) y = queue[w0 + lane + 64u];
+  };
+  auto park = [&](uint32_t slot, uint32_t x, uint32_t y) {
+    uint32_t* dst = reinterpret_cast<uint32_t*>(&s_req[slot][0]);
+    dst[lane] = x;
+    if (lane + 64u < kFetch) dst[lane + 64u] = y;
+  };
+  if (fetcher) {
+    uint32_t x, y;
+    fetch(0, x, y);
+    park(0, x, y);
+  }
+  // lanes of the team, of the rows (the weights: see k_run_steps)
+  const uint32_t wanted = WAVE ? 64u : (a.most + 63u) / 64u * 64u;
+  const bool apart = wanted <= 512u;
+  const uint32_t team = apart ? wanted : 1024u;   // (not apart: every wave comes to the team's barriers)
+  const bool in_team = tid < team, in_rows = !apart || tid >= team;
+  const uint32_t rn = apart ? 1024u - team : 1024u, rl = apart ? tid - team : tid;
+  const uint32_t rw = wave_value(rl >> 6), rws = rn >> 6;   // number of this wave among the row waves, and how many there are
   __syncthreads();
   LdsTree lt;
   lt.tree = tree;
-  lt.leaves_mem = a.leaves_in_memory ? tab.lvl[0] : nullptr;
+  lt.leaves_mem = MEM ? tab.lvl[0] : nullptr;
   lt.off = s_off;
-  lt.sampled = reinterpret_cast<uint32_t*>(tree + s_off[H + 1]);
   lt.max_bits = &s_max;
-  lt.vmin_bits = &s_vmin;
-  lt.bmin_bits = &s_bmin;
-  lt.skip = s_skip;
   lt.H = H;
-  lt.N = g.N;
+  lt.N = N;
   lds_tree_load(tab, lt);
+  uint32_t* nodes = reinterpret_cast<uint32_t*>(tree + s_off[H + 1]);   // sampled leaves of the round
+  float* values = reinterpret_cast<float*>(nodes + 512);                // and their values (apart only: at most 512)
+  TreeView<MEM> tv;
+  tv.tree = tree;
+  tv.leaves = lt.leaves_mem;
+  tv.off_reg = s_off[lane <= H + 1 ? lane : H + 1];
+  tv.n_reg = tab.n[lane <= H ? lane : H];
+  tv.H = H;
+  tv.N = N;
+  tv.s_max = &s_max;
+  tv.s_arrived = &s_arrived;
+  tv.s_runs = s_runs;
+  tv.apart = apart;
+  tv.team = team;
+  tv.met = 0;
   uint32_t cursor = a.cursor, size = a.size;
   uint32_t flags = 0;
-  uint32_t last_node = 0xFFFFFFFFu;   // this lane's index from the latest sampling request
-
-  for (uint32_t r = 0; r < a.n_requests; ++r) {
-    const per_request& q = a.queue[r];
-    const uint32_t n = q.n;
-    const size_t to = (size_t)t * n;
-    __syncthreads();   // the request before this one is complete (and has finished with s_ft)
-    if (tid < (uint32_t)kMaxFields) s_ft.io[tid] = static_cast<uint8_t*>(q.field[tid]);
-    __syncthreads();
-    if (q.op == PER_OP_INSERT) {
-      lds_insert<LOGK>(lt, s_ft, t, to, n, q.prio ? q.prio + to : nullptr, q.idx ? q.idx + to : nullptr,
-                       q.protect ? q.protect + (size_t)t * q.n_protect : nullptr, q.n_protect, cursor, size, flags);
-    } else if (q.op == PER_OP_SAMPLE) {
-      const float u_i = tid < n ? q.u[to + tid] : 0.0f;
-      last_node = lds_sample<LOGK>(lt, s_ft, t, to, n, u_i, q.beta, q.idx + to, q.out_weight ? q.out_weight + to : nullptr,
-                                   q.out_prio ? q.out_prio + to : nullptr, a.buffer_norm != 0, flags);
-    } else if (q.op == PER_OP_UPDATE) {
-      float v = 0.0f;
-      uint32_t i = last_node;
-      if (tid < n) {
-        v = q.prio[to + tid];
-        if (q.idx) i = q.idx[to + tid];
-      }
-      lds_update<LOGK>(lt, n, i, v, size, flags);
+  uint32_t node = 0xFFFFFFFFu;    // this lane's sample of the latest sampling request
+  float val = 0.0f;
+  // the round under way, the next one, and where the one after that starts in the queue
+  const bool single = a.ahead == 0;
+  QueueRound cur = take_round(s_req[0], n_requests, single);
+  uint32_t pos = cur.used, pos_cur = 0;
+  // what the rounds read: uniform; value and index of the update; inserted priority; rows
+  float u_i = 0.0f, u_next = 0.0f, up_v = 0.0f, in_v = 0.0f;
+  uint32_t up_i = 0;
+  RowItem ip;
+  uint4 iv;
+  uint32_t sample_n = 0, before_smp = 3;   // the sampling request of the round before: its batch (0: none) and place
+  auto inserted_by = [&](const per_request& q) -> uint32_t {   // the row of the insertion that this lane places (>= n: none)
+    const uint32_t j = WAVE ? lane - (64u - q.n) : tid;
+    return in_team && (!WAVE || lane >= 64u - q.n) ? j : 0xFFFFFFFFu;
+  };
+  auto fill_fields = [&](const per_request* q, PieceFields* pf) {
+    fill_piece_fields(fields, q && lane < (uint32_t)kMaxFields ? static_cast<uint8_t*>(q->field[lane]) : nullptr, t, q ? q->n : 0u, 0, pf);
+  };
+  // fetches what round r (its requests in q, its insertion at ring slot `at`) reads
+  auto fetch_inputs = [&](const QueueRound& r, const per_request* q, uint32_t parity, uint32_t at) {
+    if (r.smp < 3) {
+      const per_request& w = q[r.smp];
+      if (in_team && tid < w.n) u_next = as_global(w.u)[(size_t)t * w.n + tid];
     }
+    if (r.upd < 3) {
+      const per_request& w = q[r.upd];
+      if (in_team && tid < w.n) {
+        up_v = as_global(w.prio)[(size_t)t * w.n + tid];
+        if (w.idx) up_i = as_global(w.idx)[(size_t)t * w.n + tid];
+      }
+    }
+    if (r.ins < 3) {
+      const per_request& w = q[r.ins];
+      const uint32_t j = inserted_by(w);
+      if (j < w.n && w.prio) in_v = as_global(w.prio)[(size_t)t * w.n + j];
+      if (w.protect && in_rows) {   // collision-free insertion: rows aimed at a protected slot are deferred (see k_insert_small)
+        const uint32_t* protect = w.protect + (size_t)t * w.n_protect;
+        for (uint32_t k = rl; k < w.n_protect; k += rn) {
+          const uint32_t i = as_global(protect)[k];
+          if (i < N) {
+            const uint32_t p = i >= at ? i - at : i + (N - at);   // position in the ring window
+            if (p < w.n) atomicOr(&s_skip[parity][p >> 5], 1u << (p & 31u));
+          }
+        }
+      }
+      if (in_rows && rw < s_ins[parity].items()) {   // (the first item of the insertion; the others come when it is their turn)
+        ip = find_item(s_ins[parity], rw);
+        if (ip.on) iv = load_piece(ip.dense, ip.w);
+      }
+    }
+  };
+  {   // round 0, and the requests of round 1
+    if (tid >= 896 && tid < 960) fill_fields(cur.ins < 3 ? &s_req[0][cur.ins] : nullptr, &s_ins[0]);
+    if (fetcher) {
+      uint32_t x, y;
+      fetch(single ? 0u : pos, x, y);   // (single: round 1 is empty)
+      park(1, x, y);
+    }
+    if (tid < 64) s_skip[tid >> 5][tid & 31u] = 0;
+    __syncthreads();
+    fetch_inputs(cur, s_req[0], 0, cursor);
+    u_i = u_next;
   }
+  __syncthreads();
+  uint32_t max_bits = s_max;      // (WAVE: the team's copy; else s_max counts)
+
+  for (uint32_t i = 0;; ++i) {
+    const uint32_t par = i & 1u, slot_cur = i % 3u, slot_next = (i + 1u) % 3u, slot_before = (i + 2u) % 3u;
+    const per_request* q = s_req[slot_cur];
+    const bool more = pos_cur < n_requests;
+    // (single: a round with nothing in it behind every request)
+    const bool gap = single && cur.used != 0;
+    const QueueRound next = gap ? QueueRound{3, 3, 3, 0} : take_round(s_req[slot_next], n_requests - (pos < n_requests ? pos : n_requests), single);
+    // ---- rows and weights of the round before
+    const uint32_t w0 = apart ? 1024u - (sample_n + 63u) / 64u * 64u : 0u;
+    const bool weigher = sample_n && tid >= w0 && tid - w0 < sample_n;
+    float w_out = 0.0f, v_out = 0.0f;
+    uint32_t n_out = 0;
+    uint32_t* out_idx = nullptr;
+    float *out_w = nullptr, *out_prio = nullptr;
+    if (sample_n && in_rows) gather_rows(s_rows[par ^ 1u], rw, rws, nodes, N, a.fields.row_stride, 0, flags);
+    if (weigher) {
+      const per_request& w = s_req[slot_before][before_smp];
+      n_out = nodes[tid - w0];
+      v_out = apart ? values[tid - w0] : val;
+      const size_t o = (size_t)t * sample_n + (tid - w0);
+      out_idx = w.idx + o;
+      if (w.out_prio) out_prio = w.out_prio + o;
+      if (w.out_weight) {
+        out_w = w.out_weight + o;
+        const uint32_t vmin = s_vmin[par ^ 1u];
+        const uint32_t least = a.buffer_norm ? s_bmin[par ^ 1u] : vmin;
+        w_out = vmin == kNoMin ? 0.0f : importance_weight(v_out, __uint_as_float(least), w.beta);
+      }
+    }
+    // ---- the requests of the round after the next one are asked for
+    const uint32_t pos_after = pos + next.used;
+    uint32_t req_x = 0, req_y = 0;
+    if (fetcher) fetch(single && next.used ? 0u : pos_after < n_requests ? pos_after : n_requests, req_x, req_y);
+    // ---- the tree: update, insertion
+    const bool do_upd = cur.upd < 3, do_ins = cur.ins < 3;
+    const uint32_t n_ins = do_ins ? wave_value(q[cur.ins].n) : 0u;
+    const uint32_t cursor0 = cursor;
+    if (in_team) {
+      UpdateWork up{};
+      up.on = do_upd;
+      if (do_upd) {
+        const per_request& w = q[cur.upd];
+        up.n = wave_value(w.n);
+        up.mine = in_team && tid < up.n;
+        up.sorted = w.idx == nullptr;
+        up.i = w.idx ? up_i : node;
+        up.size = size;
+        up.v = up_v;
+      }
+      InsertWork in{};
+      in.on = do_ins;
+      if (do_ins) {
+        const uint32_t j = inserted_by(q[cur.ins]);
+        in.n = n_ins;
+        in.mine = j < n_ins && !((s_skip[par][(j & 1023u) >> 5] >> (j & 31u)) & 1u);
+        in.given = q[cur.ins].prio != nullptr;
+        in.slot = in.mine ? ring_slot(cursor, j, N) : 0u;
+        in.v = in_v;
+      }
+      change_tree<LOGK, WAVE, MEM>(tv, up, in, max_bits, flags);
+    }
+    if (do_ins) {
+      cursor = ring_slot(cursor, n_ins, N);
+      size = size + n_ins > N ? N : size + n_ins;
+    }
+    // ---- tables of the next round's insertion and of this round's sample; the next round's deferred rows, none so far
+    if (tid >= 896 && tid < 960) {
+      fill_fields(next.ins < 3 ? &s_req[slot_next][next.ins] : nullptr, &s_ins[par ^ 1u]);
+      // (s_rows of the round before is still in use: this round's is the other one)
+      fill_fields(cur.smp < 3 ? &q[cur.smp] : nullptr, &s_rows[par]);
+      if (lane < 32) s_skip[par ^ 1u][lane] = 0;
+    }
+    // ---- the rows of the round before have been read; the tree is whole
+    if (WAVE && MEM) wait_memory();   // (!WAVE: the team has waited for its leaves)
+    lds_barrier();
+    if (do_ins && in_rows) {
+      auto deferred = [&](uint32_t row) -> bool { return ((s_skip[par][row >> 5] >> (row & 31u)) & 1u) != 0; };
+      if (rw < s_ins[par].items() && ip.on) place_row_piece(ip, cursor0, N, a.fields.row_stride, s_skip[par], iv);
+      insert_rows(s_ins[par], rw + rws, rws, cursor0, N, a.fields.row_stride, 0, s_skip[par]);
+      if (q[cur.ins].idx) {
+        uint32_t* slots = q[cur.ins].idx + (size_t)t * n_ins;
+        for (uint32_t j = rl; j < n_ins; j += rn) as_global(slots)[j] = deferred(j) ? 0xFFFFFFFFu : ring_slot(cursor0, j, N);
+      }
+      wait_memory();
+    }
+    if (weigher) {
+      *as_global(out_idx) = n_out;
+      if (out_prio) *as_global(out_prio) = v_out;
+      if (out_w) *as_global(out_w) = w_out;
+    }
+    if (!more) break;
+    if (single) {   // (what this round has stored is there before the next one's inputs are read)
+      wait_memory();
+      lds_barrier();
+    }
+    fetch_inputs(next, s_req[slot_next], par ^ 1u, cursor);
+    if (tid == 0) s_vmin[par ^ 1u] = s_bmin[par ^ 1u] = kNoMin;   // (read by the weights of the round before, in front of the barrier)
+    if (fetcher) park(slot_before, req_x, req_y);                 // (likewise)
+    const per_request* smp = cur.smp < 3 ? &q[cur.smp] : nullptr;
+    sample_n = smp ? wave_value(smp->n) : 0u;
+    before_smp = cur.smp;
+    if (smp) {
+      // ---- weights relative to the whole tree: its smallest positive leaf
+      if (a.buffer_norm && smp->out_weight && in_rows) {
+        uint32_t m = kNoMin;
+        for (uint32_t e = rl; e < N; e += rn) m = min_u32(m, positive_bits(tv.leaf(e)));
+        m = wave_min_u32(m);
+        if (lane == 0 && m != kNoMin) atomicMin(&s_bmin[par], m);
+      }
+      // ---- sampling
+      if (in_team && (WAVE || (tid & ~63u) < sample_n)) {
+        walk_tree<LOGK, MEM>(tv, tid, sample_n, u_i, node, val);
+        if (node == 0xFFFFFFFFu) {
+          if (tid == 0) flags |= 4u;
+        } else if (smp->out_weight) {
+          const uint32_t m = wave_min_u32(tid < sample_n ? __float_as_uint(val) : kNoMin);
+          if (lane == 0) {
+            if constexpr (WAVE) s_vmin[par] = m;
+            else atomicMin(&s_vmin[par], m);
+          }
+        }
+        if (tid < sample_n) {
+          nodes[tid] = node;
+          if (apart) values[tid] = val;
+        }
+      }
+    }
+    u_i = u_next;
+    if (in_rows) wait_memory();   // (the next sampling request may return its results in the same arrays)
+    pos_cur = pos;
+    pos = pos_after;
+    cur = next;
+    lds_barrier();
+  }
+  if (WAVE && tid == 0) s_max = max_bits;
   __syncthreads();
   lds_tree_store(g, t, tab, lt, flags, &s_flags);
 }
@@ -792,15 +1050,19 @@ static hipError_t launch_run_steps_k(const Geom& g, const Tuning& tn, StreamArgs
   const size_t bytes = ((size_t)floats + 1024) * 4;   // the tree and the sampled indices of one step
   // always the largest workgroup, also for small batches: measured faster than a workgroup of the batch's
   // size (the tree copy and the row movers use all lanes)
-  if (a.B <= 64 && a.n_insert <= 64) {
-    hipError_t e = grant_lds<&k_run_steps<LOGK, true>>(tn, bytes);
-    if (e != hipSuccess) return e;
-    PER_LAUNCH(KID_RUN_STEPS, (k_run_steps<LOGK, true>), dim3(g.T), dim3(1024), bytes, s, ka);
+  const bool wave = a.B <= 64 && a.n_insert <= 64, mem = ka.a.leaves_in_memory != 0;
+#define PER_RUN(W, M)                                                                                   \
+  do {                                                                                                  \
+    hipError_t e = grant_lds<&k_run_steps<LOGK, W, M>>(tn, bytes);                                      \
+    if (e != hipSuccess) return e;                                                                      \
+    PER_LAUNCH(KID_RUN_STEPS, (k_run_steps<LOGK, W, M>), dim3(g.T), dim3(1024), bytes, s, ka);          \
+  } while (0)
+  if (wave) {
+    if (mem) PER_RUN(true, true); else PER_RUN(true, false);
   } else {
-    hipError_t e = grant_lds<&k_run_steps<LOGK, false>>(tn, bytes);
-    if (e != hipSuccess) return e;
-    PER_LAUNCH(KID_RUN_STEPS, (k_run_steps<LOGK, false>), dim3(g.T), dim3(1024), bytes, s, ka);
+    if (mem) PER_RUN(false, true); else PER_RUN(false, false);
   }
+#undef PER_RUN
   return hipGetLastError();
 }
 
@@ -818,9 +1080,19 @@ static hipError_t launch_run_requests_k(const Geom& g, const Tuning& tn, const Q
   const uint32_t floats = stream_tree_floats(g, ka.a.off, &ka.a.leaves_in_memory);
   if (!floats) return hipErrorInvalidValue;
   const size_t bytes = ((size_t)floats + 1024) * 4;   // the tree and the indices of the latest sampling request
-  hipError_t e = grant_lds<&k_run_requests<LOGK>>(tn, bytes);
-  if (e != hipSuccess) return e;
-  PER_LAUNCH(KID_RUN_REQUESTS, k_run_requests<LOGK>, dim3(g.T), dim3(1024), bytes, s, ka);
+  const bool wave = a.most <= 64, mem = ka.a.leaves_in_memory != 0;
+#define PER_RUN(W, M)                                                                                   \
+  do {                                                                                                  \
+    hipError_t e = grant_lds<&k_run_requests<LOGK, W, M>>(tn, bytes);                                   \
+    if (e != hipSuccess) return e;                                                                      \
+    PER_LAUNCH(KID_RUN_REQUESTS, (k_run_requests<LOGK, W, M>), dim3(g.T), dim3(1024), bytes, s, ka);    \
+  } while (0)
+  if (wave) {
+    if (mem) PER_RUN(true, true); else PER_RUN(true, false);
+  } else {
+    if (mem) PER_RUN(false, true); else PER_RUN(false, false);
+  }
+#undef PER_RUN
   return hipGetLastError();
 }
 

@@ -770,6 +770,50 @@ int per_run_steps(per_t* p, uint32_t n_steps, uint32_t n_insert, uint32_t B, con
   return hip_rc(e);
 }
 
+// A byte range a request reads or writes.
+struct Span { uintptr_t lo, hi; };
+static void add_span(Span* s, uint32_t* n, const void* p, uint64_t bytes) {
+  if (p) s[(*n)++] = Span{reinterpret_cast<uintptr_t>(p), reinterpret_cast<uintptr_t>(p) + bytes};
+}
+static bool spans_meet(const Span* a, uint32_t na, const Span* b, uint32_t nb) {
+  for (uint32_t i = 0; i < na; ++i)
+    for (uint32_t j = 0; j < nb; ++j)
+      if (a[i].lo < b[j].hi && b[j].lo < a[i].hi) return true;
+  return false;
+}
+// What the requests of a queue read and write, the last few of them: whether one may be fetched ahead of those before it.
+struct RequestSpans {
+  static constexpr uint32_t kBack = 6;   // (two rounds of the kernel: results of older requests are in memory by then)
+  Span out[kBack][3 + PER_MAX_FIELDS];
+  uint32_t n_out[kBack] = {}, at = 0;
+  bool apart(const per_t* p, const per_request& q) {
+    Span in[4 + PER_MAX_FIELDS], o[3 + PER_MAX_FIELDS];
+    uint32_t ni = 0, no = 0;
+    const uint64_t T = p->g.T, words = T * q.n * 4;
+    add_span(in, &ni, q.prio, q.op == PER_OP_SAMPLE ? 0 : words);
+    if (q.op == PER_OP_SAMPLE) {
+      add_span(in, &ni, q.u, words);
+      add_span(o, &no, q.out_weight, words);
+      add_span(o, &no, q.out_prio, words);
+    }
+    if (q.op == PER_OP_UPDATE) add_span(in, &ni, q.idx, words);
+    else add_span(o, &no, q.idx, words);
+    if (q.op == PER_OP_INSERT) add_span(in, &ni, q.protect, T * q.n_protect * 4);
+    if (q.op != PER_OP_UPDATE)
+      for (uint32_t f = 0; f < p->cfg.n_fields; ++f) {
+        if (q.op == PER_OP_SAMPLE) add_span(o, &no, q.field[f], T * q.n * p->cfg.field_bytes[f]);
+        else add_span(in, &ni, q.field[f], T * q.n * p->cfg.field_bytes[f]);
+      }
+    bool ok = true;
+    for (uint32_t b = 0; b < kBack && ok; ++b)
+      ok = !spans_meet(in, ni, out[b], n_out[b]) && !(q.op == PER_OP_INSERT && spans_meet(o, no, out[b], n_out[b]));
+    memcpy(out[at], o, no * sizeof(Span));
+    n_out[at] = no;
+    at = (at + 1) % kBack;
+    return ok;
+  }
+};
+
 int per_run_requests(per_t* p, uint32_t n_requests, const per_request* h_requests, const per_request* d_requests,
                      void* stream) {
   if (!p) return PER_EINVAL;
@@ -783,6 +827,8 @@ int per_run_requests(per_t* p, uint32_t n_requests, const per_request* h_request
   const uint64_t N = p->cfg.capacity;
   uint64_t cursor = p->cursor, size = p->size;
   uint32_t sampled_n = 0;   // batch of the latest SAMPLE request (0: none yet)
+  RequestSpans spans;
+  a.ahead = 1;
   for (uint32_t r = 0; r < n_requests; ++r) {
     const per_request& q = h_requests[r];
     if (q.op != PER_OP_INSERT && q.op != PER_OP_SAMPLE && q.op != PER_OP_UPDATE) return PER_EINVAL;
@@ -804,6 +850,8 @@ int per_run_requests(per_t* p, uint32_t n_requests, const per_request* h_request
     } else {
       if (!q.prio || (!q.idx && sampled_n != q.n)) return PER_EINVAL;
     }
+    if (q.n > a.most) a.most = q.n;
+    if (a.ahead && !spans.apart(p, q)) a.ahead = 0;
   }
   hipStream_t s = static_cast<hipStream_t>(stream);
   CaptureGuard capture(p, s);

@@ -164,6 +164,8 @@ struct QueueArgs {
   uint32_t n_requests;
   uint32_t cursor, size;            // ring state before the first request
   uint32_t buffer_norm;             // importance weights relative to the whole tree (else to the batch)
+  uint32_t most;                    // largest count of a request
+  uint32_t ahead;                   // what a request reads may be fetched before the ones just before it are done
   const per_request* queue;         // device copy of the requests
   FieldTable fields;                // columns, row sizes and access widths; the io pointers come from the requests
   uint32_t off[kMaxHeight + 2];     // as in StreamArgs

@@ -1295,6 +1295,72 @@ def test_run_requests_equals_the_separate_calls(K, N, T, fb, seed):
     m.compare_tree()
 
 
+@pytest.mark.parametrize("dependent", [False, True])
+@pytest.mark.parametrize("K,N,T,fb,sizes", [
+    (2, 3000, 1, (16, 4, 4, 16, 1), (1, 31, 64)), (16, 30000, 2, (68, 24, 4, 68, 1), (1, 33, 64)),
+    (8, 513, 3, (), (63, 64)), (16, 100000, 1, (5, 16), (2, 60)), (64, 9000, 1, (128,), (64, 65)),
+    (16, 30000, 1, (16, 1), (500, 512, 513))])
+def test_run_requests_in_rounds(K, N, T, fb, sizes, dependent):
+    """Queues whose requests fall into rounds of the kernel in every way, at the batch sizes where its lanes are shared
+    out differently.  `dependent`: updates, protected inserts and inserted rows take what a sampling request of the
+    same queue returns, by address."""
+    from paper_2311_09445_amd.per import OP_INSERT, OP_SAMPLE, OP_UPDATE
+    log(f"run_requests in rounds K={K} N={N} T={T} fb={fb} sizes={sizes} dependent={dependent}")
+    rng = np.random.default_rng(N + dependent)
+    m = Mirror(K, N, T, fb)
+    m.insert(N - 20, prio=wl._draw_priorities("exponential_1", rng, (T, N - 20)), chunk=max(5000, N // 8))
+    queue, checks, last = [], [], None
+    order = "SUISUISSUUIISIUSUIUSIS"
+    for r, op in enumerate(order):
+        n = min(int(rng.choice(sizes)), N // 4)
+        if op == "I":
+            counters = m.counter + np.arange(n)
+            m.counter += n
+            rows = [np.stack([wl.row_bytes(t, counters, f, b) for t in range(T)]) for f, b in enumerate(fb)] if fb else None
+            d_rows = None if rows is None else [dev(x) for x in rows]
+            protect = d_protect = None
+            if dependent and last is not None:
+                protect, d_protect = last["ci"], last["oi"]
+                if fb and last["rows"] and last["n"] >= n:         # rows of the batch, stored again
+                    rows = [np.ascontiguousarray(x.reshape(-1)[:T * n * b].reshape(T, n, b)) for x, b in zip(last["crow"], fb)]
+                    d_rows = last["rows"]
+            out = torch.full((T, n), -7, dtype=torch.int32, device="cuda")
+            queue.append({"op": OP_INSERT, "n": n, "idx": out, "protect": d_protect,
+                          "rows": None if d_rows is None else [x.view(-1)[:T * n * b].view(T, n, b) for x, b in zip(d_rows, fb)]})
+            checks.append((out, m.cpu.insert(n, rows, None, protect=protect)))
+        elif op == "S":
+            u = wl.uniform01(rng, (T, n))
+            oi = torch.empty((T, n), dtype=torch.int32, device="cuda")
+            ow, ov = torch.empty((T, n), device="cuda"), torch.empty((T, n), device="cuda")
+            rows_out = [torch.empty((T, n, b), dtype=torch.uint8, device="cuda") for b in fb] if fb else None
+            queue.append({"op": OP_SAMPLE, "u": dev(u), "beta": 0.5, "idx": oi, "out_weight": ow, "out_prio": ov, "rows": rows_out})
+            ci, cw, cv = m.cpu.sample(u, 0.5, True)
+            crow = m.cpu.gather(ci) if fb else []
+            last = {"n": n, "ci": ci, "oi": oi, "rows": rows_out, "crow": crow}
+            checks.append((oi, ci, ow, cw, ov, cv, rows_out or [], crow))
+        else:
+            idx, n = (last["ci"], last["n"]) if dependent else (rng.integers(0, N + 2, (T, n)).astype(np.uint32), n)
+            prio = (rng.random((T, n)) * 3).astype(np.float32)
+            prio[:, ::13] = -1.0
+            by_address = dependent and r % 2
+            queue.append({"op": OP_UPDATE, "prio": dev(prio),
+                          "idx": last["oi"] if by_address else None if dependent else idx_to_dev(idx)})
+            m.cpu.update(idx, prio)
+    keep = m.gpu.run_requests(queue)
+    torch.cuda.synchronize()
+    del keep
+    for r, c in enumerate(checks):
+        assert np.array_equal(idx_to_host(c[0]), c[1]), f"check {r}: slots or indices"
+        if len(c) > 2:
+            np.testing.assert_allclose(c[2].cpu().numpy(), c[3], rtol=1e-6, atol=0)
+            assert c[4].cpu().numpy().tobytes() == c[5].tobytes(), f"check {r}: values"
+            for f, want in enumerate(c[7]):
+                assert np.array_equal(c[6][f].cpu().numpy(), want), f"check {r}: rows of field {f}"
+    m.compare_tree()
+    m.compare_status()
+    assert m.gpu.cursor == m.cpu.trees[0].cursor and m.gpu.size == m.cpu.trees[0].size
+
+
 def test_run_requests_argument_checks():
     from paper_2311_09445_amd.per import OP_SAMPLE, OP_UPDATE
     big = PrioritizedReplay(16, 1 << 20)
