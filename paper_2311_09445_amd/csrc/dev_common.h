@@ -246,6 +246,21 @@ __device__ __forceinline__ Floats2 load_floats2(GlobalPtr<const float> p) { retu
 __device__ __forceinline__ Floats4 load_floats4(GlobalPtr<const float> p) { return *(GlobalPtr<const Floats4>)p; }
 #endif
 
+// The walk from the sums s of a group's chunks down: the chunk, then the child in it (grp: the K children).
+template <int LOGK, typename P>
+__device__ __forceinline__ void descend_chunk(P grp, const float (&s)[(1 << LOGK) / 4], float& r, unsigned& child, float& val) {
+  const unsigned pos = walk_chunks<LOGK - 2>(s, r);
+  const Floats4 x = load_floats4(grp + 4 * pos);
+  const float p0 = x.x + x.y, p1 = x.z + x.w;
+  const bool r1 = (p1 != 0.0f) && !(r < p0);
+  r = r1 ? r - p0 : r;
+  const float a = r1 ? x.z : x.x, b = r1 ? x.w : x.y;
+  const bool r0 = (b != 0.0f) && !(r < a);
+  r = r0 ? r - a : r;
+  val = r0 ? b : a;
+  child = 4u * pos + (r1 ? 2u : 0u) + (r0 ? 1u : 0u);
+}
+
 // grp points at the K children (LDS or global).  Returns the chosen child, its value and the
 // residual.  The chosen chunk is read a second time instead of keeping all K children live.
 template <int LOGK, typename P>
@@ -264,16 +279,7 @@ __device__ __forceinline__ void descend_lane(P grp, float& r, unsigned& child, f
       const Floats4 x = load_floats4(grp + 4 * c);
       s[c] = (x.x + x.y) + (x.z + x.w);
     }
-    const unsigned pos = walk_chunks<LOGK - 2>(s, r);
-    const Floats4 x = load_floats4(grp + 4 * pos);
-    const float p0 = x.x + x.y, p1 = x.z + x.w;
-    const bool r1 = (p1 != 0.0f) && !(r < p0);
-    r = r1 ? r - p0 : r;
-    const float a = r1 ? x.z : x.x, b = r1 ? x.w : x.y;
-    const bool r0 = (b != 0.0f) && !(r < a);
-    r = r0 ? r - a : r;
-    val = r0 ? b : a;
-    child = 4u * pos + (r1 ? 2u : 0u) + (r0 ? 1u : 0u);
+    descend_chunk<LOGK>(grp, s, r, child, val);
   }
 }
 

@@ -21,8 +21,7 @@ struct TopCopy {
 // One lane per sample; grid (ceil(B / block), T).  Dynamic LDS holds the top copy followed by
 // one staging area per wave.  Below the copy each level costs one trip to memory: the wave
 // fetches its 64 child groups with fully coalesced 16-byte loads (K/4 adjacent lanes per
-// group), parks them in LDS rows of K+4 floats (the pad keeps 16-byte row reads conflict-free),
-// and every lane then walks its own row.
+// group), parks them in LDS rows (see StageRow) and every lane then walks the row of its group.
 //
 // Uniform of sample i of tree t when the caller supplies none ("uniformly generated random",
 // Section II-A): Philox4x32-10 (Salmon et al., SC 2011), ten rounds of two 32x32->64
@@ -47,12 +46,11 @@ __device__ __forceinline__ float counter_uniform(const RngArgs& rng, uint32_t i,
   return (float)(c0 >> 8) * (1.0f / 16777216.0f);
 }
 
-// Chunk (IT*64 + lane) of the wave's 64*C 16-byte chunks, for IT = 0 .. C-1: fetched from the
-// group of the lane that owns it and parked in that lane's staging row.  Written as a recursion over
-// IT (not a loop over an array of registers) so that every fetch is issued before the first LDS store
-// without the compiler having to promote an array.
+// Chunk (IT*64 + lane) of the wave's 64*C 16-byte chunks, for IT = 0 .. C-1: fetched from the group of the lane that owns
+// it and parked in that lane's staging row.  Written as a recursion over
+// IT so that every fetch is issued before the first LDS store without the compiler having to promote an array.
 template <int LOGK, int IT>
-__device__ __forceinline__ void stage_groups(const float* __restrict__ lvl, uint32_t node, unsigned lane, float* stage) {
+__device__ __forceinline__ void stage_group_per_lane(const float* __restrict__ lvl, uint32_t node, unsigned lane, float* stage) {
   constexpr int K = Fan<LOGK>::K;
   constexpr int C = K / 4;
   constexpr int ROW = K + 4;
@@ -60,9 +58,107 @@ __device__ __forceinline__ void stage_groups(const float* __restrict__ lvl, uint
     const unsigned gch = (unsigned)IT * 64u + lane;
     const uint32_t nd = (uint32_t)__shfl((int)node, (int)(gch / C));
     const float4 x = *reinterpret_cast<const float4*>(lvl + (size_t)nd * K + (gch % C) * 4u);
-    stage_groups<LOGK, IT + 1>(lvl, node, lane, stage);
+    stage_group_per_lane<LOGK, IT + 1>(lvl, node, lane, stage);
     *reinterpret_cast<float4*>(stage + (gch / C) * ROW + (gch % C) * 4u) = x;
   }
+}
+
+// The same for large batches (the kernel that loops over blocks of samples).  Samples come in leaf order, so lanes that stand on one
+// node are neighbours: each distinct group is fetched once, into the row of its rank among the wave's groups, and all
+// its lanes walk that row.  (A large batch is bound by what the walk reads and computes per sample, not by the tree's
+// bytes: 2^20 samples on 2^24 leaves at K = 32 fetched 128 bytes per sample and height, 400 MB between caches and compute
+// units for 60 MB of distinct groups.  Few samples seldom share a group, and the ranks cost the lone wave 0.7 us of its chain.)  Beside the K children a row holds the sums of its chunks (4 adjacent children),
+// which the lane that fetches a chunk computes once for all lanes of the group, and the number of its node:
+//   [K children][K / 4 chunk sums][node] pad
+// rows an odd number of 16-byte units apart, so that lanes on different rows read different banks.
+template <int LOGK>
+struct StageRow {
+  static constexpr int K = 1 << LOGK, C = K / 4;
+  static constexpr int UNITS = (K + C + 1 + 3) / 4;
+  static constexpr int FLOATS = 4 * (UNITS | 1);
+  static constexpr int SUMS = K, NODE = K + C;
+};
+static uint32_t stage_row_floats(uint32_t logK) {
+  return logK == 3 ? StageRow<3>::FLOATS : logK == 4 ? StageRow<4>::FLOATS : logK == 5 ? StageRow<5>::FLOATS : logK == 6 ? StageRow<6>::FLOATS : 0u;
+}
+// Chunk (IT*64 + lane) of the wave's `chunks` 16-byte chunks, for IT = 0 .. C-1: first the numbers of all their nodes, then
+// every fetch, then the LDS stores.  Written as recursions over IT (not loops over arrays of registers) so that each
+// phase is under way as a whole before the next one waits, without the compiler having to promote an array.
+template <int C>
+struct NodeNumbers {
+  uint32_t nd;
+  NodeNumbers<C - 1> rest;
+};
+template <>
+struct NodeNumbers<0> {};
+template <int LOGK, int IT, int C>
+__device__ __forceinline__ void read_nodes(const float* stage, unsigned lane, NodeNumbers<C>& n) {
+  using Row = StageRow<LOGK>;
+  if constexpr (C > 0) {
+    n.nd = __float_as_uint(stage[(size_t)(((unsigned)IT * 64u + lane) / Row::C) * Row::FLOATS + Row::NODE]);
+    read_nodes<LOGK, IT + 1>(stage, lane, n.rest);
+  }
+}
+template <int LOGK, int IT, int C>
+__device__ __forceinline__ void stage_chunks(const float* __restrict__ lvl, uint32_t chunks, unsigned lane, float* stage, NodeNumbers<C>& n) {
+  constexpr int K = Fan<LOGK>::K;
+  using Row = StageRow<LOGK>;
+  if constexpr (C > 0) {
+    if ((uint32_t)IT * 64u < chunks) {   // (the same for the wave)
+      const unsigned gch = (unsigned)IT * 64u + lane, c = gch % Row::C;
+      const bool mine = gch < chunks;
+      const float4 x = *reinterpret_cast<const float4*>(lvl + (size_t)(mine ? n.nd : 0u) * K + c * 4u);
+      stage_chunks<LOGK, IT + 1>(lvl, chunks, lane, stage, n.rest);
+      if (mine) {
+        float* row = stage + (size_t)(gch / Row::C) * Row::FLOATS;
+        *reinterpret_cast<float4*>(row + c * 4u) = x;
+        row[Row::SUMS + c] = (x.x + x.y) + (x.z + x.w);
+      }
+    }
+  }
+}
+__device__ __forceinline__ void order_within_wave() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+// Returns this lane's row.
+template <int LOGK>
+__device__ __forceinline__ const float* stage_groups(const float* __restrict__ lvl, uint32_t node, unsigned lane, float* stage) {
+  using Row = StageRow<LOGK>;
+  const uint32_t below = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)node, 0x138 /* wave_shr:1: from the lane below */, 0xF, 0xF, true);
+  const bool first = lane == 0 || below != node;
+  const unsigned long long firsts = __ballot(first);
+  const uint32_t rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(firsts >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)firsts, 0u)) + (first ? 1u : 0u) - 1u;
+  float* row = stage + (size_t)rank * Row::FLOATS;
+  if (first) row[Row::NODE] = __uint_as_float(node);
+  order_within_wave();
+  NodeNumbers<Row::C> nodes;
+  read_nodes<LOGK, 0>(stage, lane, nodes);
+  stage_chunks<LOGK, 0>(lvl, (uint32_t)__popcll(firsts) * Row::C, lane, stage, nodes);
+  order_within_wave();
+  return row;
+}
+// descend_lane on a staged row: the walk over the chunks from their sums, then the chosen chunk.
+template <int LOGK>
+__device__ __forceinline__ void descend_row(const float* row, float& r, unsigned& child, float& val) {
+  using Row = StageRow<LOGK>;
+  float s[Row::C];
+  if constexpr (Row::C == 2) {
+    const Floats2 x = load_floats2(row + Row::SUMS);
+    s[0] = x.x;
+    s[1] = x.y;
+  } else {
+#pragma unroll
+    for (int c = 0; c < Row::C; c += 4) {
+      const Floats4 x = load_floats4(row + Row::SUMS + c);
+      s[c] = x.x;
+      s[c + 1] = x.y;
+      s[c + 2] = x.z;
+      s[c + 3] = x.w;
+    }
+  }
+  descend_chunk<LOGK>(row, s, r, child, val);
 }
 
 // stale < 0: the tree in memory is whole.  stale >= 0: the last update left the root and the
@@ -96,7 +192,8 @@ __device__ __forceinline__ uint32_t plan_pos(const Range2& r, uint32_t node) {
 template <bool RIDE> using RideParam = typename std::conditional<RIDE, InsertRide, NoRide>::type;
 __device__ __forceinline__ void ride_rows(const InsertRide& ride, uint32_t t, uint32_t N, uint32_t part, uint32_t parts);   // (k_rows.h)
 
-template <int LOGK, bool RIDE>
+// LOOP: fewer sampling workgroups than blocks of samples; each takes blocks in turn.
+template <int LOGK, bool RIDE, bool LOOP>
 __global__ void __launch_bounds__(1024)
 k_sample(Geom g, TopCopy tc, uint32_t B, uint32_t size, float beta, const float* __restrict__ u,
          uint32_t* __restrict__ out_idx, float* __restrict__ out_prio, float* __restrict__ out_w,
@@ -104,7 +201,7 @@ k_sample(Geom g, TopCopy tc, uint32_t B, uint32_t size, float beta, const float*
          RideParam<RIDE> ride) {
   constexpr int K = Fan<LOGK>::K;
   constexpr int LPS = Fan<LOGK>::LPS;
-  constexpr int ROW = K + 4;                  // staging row, floats
+  constexpr int ROW = LOOP && LOGK >= 3 ? StageRow<LOGK>::FLOATS : K + 4;   // staging row, floats
   using Vec = typename std::conditional<LOGK == 1, float2, float4>::type;
   constexpr int VF = sizeof(Vec) / 4;
   // (lines 1, 3, 6, 7, 10, 11 of the geometry hold what this kernel does not read on trees of few heights: the upper
@@ -141,13 +238,14 @@ k_sample(Geom g, TopCopy tc, uint32_t B, uint32_t size, float beta, const float*
 
   PER_TRACE_DECL;
   PER_MARK(0);
-  const uint32_t s_raw = bx * blockDim.x + threadIdx.x;
-  const bool active = s_raw < B;
-  const uint32_t s = active ? s_raw : B - 1;
-  const size_t o = (size_t)t * B + s;
+  // (a lane's samples: a block of them per round of the sampling workgroups; most launches have a workgroup per block)
+  uint32_t s_raw = bx * blockDim.x + threadIdx.x;
+  bool active = s_raw < B;
+  uint32_t s = active ? s_raw : B - 1;
+  size_t o = (size_t)t * B + s;
   // the root, this lane's uniform and the top copy are all fetched in the same trip
   float total = tc.root[(size_t)t * tc.root_stride];
-  const float u_s = rng.on ? counter_uniform(rng, s, t) : u[o];
+  float u_s = rng.on ? counter_uniform(rng, s, t) : u[o];
   // which buffer of partial batch minima this call fills (stable while this kernel runs: the weights job of
   // the call before has written it), fetched in that same trip
   uint32_t vbuf = 0;
@@ -352,7 +450,8 @@ k_sample(Geom g, TopCopy tc, uint32_t B, uint32_t size, float beta, const float*
 
   if (!(total > 0.0f)) {   // nothing can be sampled from this tree (uniform over the block)
     store_rebuilt_top();
-    if (active) {
+    for (; s_raw < B; s_raw += sample_blocks * blockDim.x) {
+      o = (size_t)t * B + s_raw;
       out_idx[o] = 0xFFFFFFFFu;
       if (out_prio) out_prio[o] = 0.0f;
       if (out_w) out_w[o] = 0.0f;
@@ -368,11 +467,22 @@ k_sample(Geom g, TopCopy tc, uint32_t B, uint32_t size, float beta, const float*
 
   PER_MARK(2);
   const float seg = total / (float)B;
+  uint32_t node = 0, least = 0x7F800000u, claim_mx = 0, claim_flags = 0;
+  float val = total;
+  for (;;) {
+  // (the uniform of the next round travels beside this round's walk)
+  const uint32_t next_raw = s_raw + sample_blocks * blockDim.x;
+  const bool again = LOOP && next_raw - threadIdx.x < B;   // (the same for the workgroup)
+  float u_next = 0.0f, upd_next = 0.0f;
+  if (again) {
+    const uint32_t sn = next_raw < B ? next_raw : B - 1;
+    u_next = rng.on ? counter_uniform(rng, sn, t) : u[(size_t)t * B + sn];
+    if (claim_mode == 1) upd_next = c.prio[(size_t)t * B + sn];
+  }
   const float pos = (float)s + u_s;
   float r = pos * seg;
-
-  uint32_t node = 0;
-  float val = total;
+  node = 0;
+  val = total;
 #pragma unroll
   for (int i = 0; i < kTopSlots; ++i) {
     if (i < nslots) {
@@ -403,11 +513,12 @@ k_sample(Geom g, TopCopy tc, uint32_t B, uint32_t size, float beta, const float*
     if constexpr (LOGK <= 2) {
       if (RIDE && patched) descend_lane<LOGK>(patched, r, child, val);
       else descend_lane<LOGK>(lvl + (size_t)node * K, r, child, val);
-    } else {
-      stage_groups<LOGK, 0>(lvl, node, lane, stage);
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    } else if constexpr (LOOP) {
+      descend_row<LOGK>(stage_groups<LOGK>(lvl, node, lane, stage), r, child, val);
       __builtin_amdgcn_wave_barrier();
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    } else {
+      stage_group_per_lane<LOGK, 0>(lvl, node, lane, stage);
+      order_within_wave();
       descend_lane<LOGK>(RIDE && patched ? patched : stage + lane * ROW, r, child, val);
       __builtin_amdgcn_wave_barrier();
     }
@@ -418,6 +529,17 @@ k_sample(Geom g, TopCopy tc, uint32_t B, uint32_t size, float beta, const float*
   if (active) {
     out_idx[o] = node;
     if (out_prio) out_prio[o] = val;
+    if (out_w && sample_blocks > 1) out_w[o] = val;   // (turned into the weight by the weights job)
+    least = min_u32(least, __float_as_uint(val));
+  }
+  if (!again) break;
+  if (claim_mode == 1 && active) claim_element(g, t, size, c.group_mode, claim_first, s, node, upd_v, claim_mx, claim_flags);
+  s_raw = next_raw;
+  active = s_raw < B;
+  s = active ? s_raw : B - 1;
+  o = (size_t)t * B + s;
+  u_s = u_next;
+  upd_v = upd_next;
   }
   // Stores come last on purpose: on this hardware a wait for loaded data also waits for every
   // earlier store of the wave.
@@ -426,7 +548,7 @@ k_sample(Geom g, TopCopy tc, uint32_t B, uint32_t size, float beta, const float*
   PER_FLUSH_TAG(1);
   if (out_w) {
     // Importance weights need the batch minimum of the sampled values.
-    const uint32_t m = wave_min_u32(active ? __float_as_uint(val) : 0x7F800000u);
+    const uint32_t m = wave_min_u32(least);
     if (sample_blocks == 1) {   // the whole batch of this tree is in this block: finish here
       if (lane == 0) s_min[wave] = m;
       __syncthreads();
@@ -435,7 +557,6 @@ k_sample(Geom g, TopCopy tc, uint32_t B, uint32_t size, float beta, const float*
       if (weight_mode & kWeightBufferNorm) mm = buffer_min_bits(g, t, weight_mode);   // (uniform over the launch)
       if (active) out_w[o] = importance_weight(val, __uint_as_float(mm), beta);
     } else {                // partial minima, spread over kVminSlots addresses; the weights job finishes
-      if (active) out_w[o] = val;
       vbuf = not_before_here(vbuf) & 1u;
       if (bx == 0 && threadIdx.x == 0) g.vcur[t] = vbuf;   // tells the weights job of this call which buffer it is
       if (lane == 0)
@@ -443,15 +564,14 @@ k_sample(Geom g, TopCopy tc, uint32_t B, uint32_t size, float beta, const float*
     }
   }
   if (claim_mode == 1) {   // element s of the update batch is this lane's own sample
-    uint32_t mx = 0, flags = 0;
-    if (active) claim_element(g, t, size, c.group_mode, claim_first, s, node, upd_v, mx, flags);
+    if (active) claim_element(g, t, size, c.group_mode, claim_first, s, node, upd_v, claim_mx, claim_flags);
     if constexpr (RIDE) {
-      mx = wave_max_u32(mx);
-      if (lane == 0 && mx > max_seen) atomicMax(&g.max_pend[t], mx);
+      claim_mx = wave_max_u32(claim_mx);
+      if (lane == 0 && claim_mx > max_seen) atomicMax(&g.max_pend[t], claim_mx);
     } else {
-      raise_max(g, t, mx, max_seen);
+      raise_max(g, t, claim_mx, max_seen);
     }
-    if (flags) atomicOr(&g.status[t], flags);
+    if (claim_flags) atomicOr(&g.status[t], claim_flags);
     leave_claim_base(g, t, c.group_mode, bx == 0 && threadIdx.x == 0, claim_first);
   }
 }
@@ -518,11 +638,11 @@ struct SampleShape {
   TopCopy tc;
   uint32_t waves, wave_bytes, top_bytes;
 };
-static SampleShape sample_shape(const Geom& g, const Tuning& tn, uint32_t B, uint32_t stale_hb, bool carries_insert = false) {
+static SampleShape sample_shape(const Geom& g, const Tuning& tn, uint32_t B, uint32_t stale_hb, bool carries_insert = false, bool loop = false) {
   constexpr uint32_t kLdsCap = 128 * 1024;
   SampleShape sh{};
   const uint32_t K = g.K;
-  sh.wave_bytes = g.logK >= 3 ? 64u * (K + 4) * 4u : 0u;   // staging per wave
+  sh.wave_bytes = g.logK < 3 ? 0u : 64u * (loop ? stage_row_floats(g.logK) : K + 4u) * 4u;   // staging per wave
   // workgroup size: the whole batch in one workgroup when it is small (the weights are then finished
   // in-kernel), else the configured size; bounded by the LDS the staging rows need
   uint32_t max_waves = sh.wave_bytes ? (uint32_t)(kLdsCap / 2 / sh.wave_bytes) : 16u;
@@ -621,11 +741,28 @@ static hipError_t launch_sample_k(const Geom& g, const Tuning& tn, uint32_t B, u
                                   const float* u, const RngArgs& rng, uint32_t* out_idx, float* out_w,
                                   float* out_prio, uint32_t weight_mode, uint32_t stale_hb, const FieldTable* rows,
                                   const ClaimArgs* claim, int claim_mode, const InsertRide* ride, hipStream_t s) {
-  const SampleShape sh = sample_shape(g, tn, B, stale_hb, ride != nullptr);
+  SampleShape sh = sample_shape(g, tn, B, stale_hb, ride != nullptr);
+  // No more workgroups than the device holds at once (their staging rows fill its LDS): they take further blocks of
+  // samples in turn, with the top of the tree in place and the next uniforms under way, where workgroups of a second
+  // round would begin with their arguments and the top of the tree again, two of the five trips to memory of a block.
+  // (2^20 samples on 2^24 leaves at K = 32: 59 us with a workgroup per block, 27 so, with the rows of stage_groups.)
+  auto held = [&]() -> uint64_t {   // workgroups the device holds (256 compute units)
+    uint64_t bytes = (uint64_t)sh.top_bytes + (uint64_t)sh.waves * sh.wave_bytes, by_waves = 32 / sh.waves;
+    if (bytes < tn.sample_min_lds) bytes = tn.sample_min_lds;
+    const uint64_t by_lds = bytes ? (160 * 1024) / bytes : by_waves, n = by_lds < by_waves ? by_lds : by_waves;
+    return 256 * (n < 1 ? 1 : n);
+  };
+  const bool loop = !ride && (uint64_t)((B + sh.waves * 64 - 1) / (sh.waves * 64)) * g.T > held();
+  if (loop) sh = sample_shape(g, tn, B, stale_hb, false, true);
   const TopCopy& tc = sh.tc;
   const uint32_t waves = sh.waves;
   const uint32_t block = waves * 64;
-  const uint32_t gx = (B + block - 1) / block;
+  const uint32_t blocks = (B + block - 1) / block;
+  uint32_t gx = blocks;
+  if (loop) {
+    gx = (uint32_t)(held() / g.T < 2 ? 2 : held() / g.T);   // (at least two: one workgroup alone finishes the weights of the block it holds)
+    if (gx > blocks) gx = blocks;
+  }
   size_t bytes = (size_t)sh.top_bytes + (size_t)waves * sh.wave_bytes;
   hipError_t e;
   int stale = -1;
@@ -664,17 +801,22 @@ static hipError_t launch_sample_k(const Geom& g, const Tuning& tn, uint32_t B, u
     if (claim_blocks > 4096) claim_blocks = 4096;   // the claim job strides
   }
   if (ride) {
-    e = grant_lds<&k_sample<LOGK, true>>(tn, bytes);
+    e = grant_lds<&k_sample<LOGK, true, false>>(tn, bytes);
     if (e != hipSuccess) return e;
-    PER_LAUNCH(KID_SAMPLE, (k_sample<LOGK, true>), dim3(gx + claim_blocks + rd.movers, g.T), dim3(block), bytes, s, g, tc, B,
+    PER_LAUNCH(KID_SAMPLE, (k_sample<LOGK, true, false>), dim3(gx + claim_blocks + rd.movers, g.T), dim3(block), bytes, s, g, tc, B,
                size, beta, u, out_idx, out_prio, out_w, weight_mode, stale, claim_blocks, claim_here ? *claim : ClaimArgs{},
                claim_here ? claim_mode : (int)CLAIM_NONE, rng, rd);
   } else {
-    e = grant_lds<&k_sample<LOGK, false>>(tn, bytes);
-    if (e != hipSuccess) return e;
-    PER_LAUNCH(KID_SAMPLE, (k_sample<LOGK, false>), dim3(gx + claim_blocks, g.T), dim3(block), bytes, s, g, tc, B, size,
-               beta, u, out_idx, out_prio, out_w, weight_mode, stale, claim_blocks, claim_here ? *claim : ClaimArgs{},
-               claim_here ? claim_mode : (int)CLAIM_NONE, rng, NoRide{});
+#define PER_SAMPLE(LOOP)                                                                                                       \
+  do {                                                                                                                         \
+    e = grant_lds<&k_sample<LOGK, false, LOOP>>(tn, bytes);                                                                    \
+    if (e != hipSuccess) return e;                                                                                             \
+    PER_LAUNCH(KID_SAMPLE, (k_sample<LOGK, false, LOOP>), dim3(gx + claim_blocks, g.T), dim3(block), bytes, s, g, tc, B, size, \
+               beta, u, out_idx, out_prio, out_w, weight_mode, stale, claim_blocks, claim_here ? *claim : ClaimArgs{},         \
+               claim_here ? claim_mode : (int)CLAIM_NONE, rng, NoRide{});                                                      \
+  } while (0)
+    if (loop) PER_SAMPLE(true); else PER_SAMPLE(false);
+#undef PER_SAMPLE
   }
   e = hipGetLastError();
   if (e != hipSuccess) return e;

@@ -748,7 +748,7 @@ k_step(Geom g, StepShape sh, uint32_t B, uint32_t size, float beta, uint32_t wei
       }
       // ---- trip 3: the leaf groups, staged row by row
       __syncthreads();   // (the rows of the chunk before are no longer read)
-      stage_groups<LOGK, 0>(leaves, x, lane, stage);
+      stage_group_per_lane<LOGK, 0>(leaves, x, lane, stage);
       __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
       __builtin_amdgcn_wave_barrier();
       __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
