@@ -48,6 +48,37 @@ __device__ __forceinline__ void claim_in_group(const Geom& g, uint32_t t, uint32
   }
 }
 
+// Dense batches (ClaimArgs::runs: a group gets a quarter of an element or more on the average): consecutive elements of the
+// batch for leaves of one group, as a sampled batch has them (it is in leaf order), claim together.  The last of such a
+// run within a wave raises the group's entry for all of it; the entry then holds the run's length (2 .. 64) with the sign
+// bit set, which no valid priority has beside such bits, in place of the value, and the tree pass reads the run's elements
+// from the batch.  What is displaced from an entry, or does not get in, goes leaf by leaf as before, element by element if
+// it is a run.  Runs are disjoint pieces of the batch, so the run with the latest last element is later than every
+// element of the others.  (One element at a time, 2^20 elements on 2^24 leaves take 1.6 million atomics of the leaf by leaf
+// form besides 2^20 on the entries: 64 us; the tree pass then picks those leaves' stamps up one by one.)
+__device__ __forceinline__ uint32_t run_length(uint32_t lo) { return (lo >> 31) && (lo & 0x7FFFFFFFu) >= 2u && (lo & 0x7FFFFFFFu) <= 64u ? lo & 0x7Fu : 1u; }
+__device__ __forceinline__ void claim_run(const Geom& g, uint32_t t, const ClaimArgs& c, uint32_t base, uint32_t j, uint32_t i,
+                                          uint32_t vbits, uint32_t count) {
+  const uint32_t lg = g.logK == 6 ? 6u : 5u;
+  const uint32_t slot = i & ((1u << lg) - 1u);
+  const uint32_t mine_hi = ((base + j) << 6) | slot, mine_lo = count > 1 ? 0x80000000u | count : vbits;
+  const unsigned long long mine = ((unsigned long long)mine_hi << 32) | mine_lo;
+  const unsigned long long old =
+      atomicMax(reinterpret_cast<unsigned long long*>(g.nclaim) + (size_t)t * g.nclaim_stride + (i >> lg), mine);
+  const uint32_t old_hi = (uint32_t)(old >> 32);
+  if ((old_hi >> 6) < base) return;
+  const bool stays = mine > old;
+  const uint32_t out_hi = stays ? old_hi : mine_hi, out_lo = stays ? (uint32_t)old : mine_lo, n = run_length(out_lo);
+  if (n == 1) {
+    if (count == 1 && run_length((uint32_t)old) == 1 && (old_hi & 63u) == slot) return;   // (one leaf: the later of the two dominates)
+    claim_leaf(g, t, (i & ~((1u << lg) - 1u)) | (out_hi & 63u), out_hi >> 6, out_lo);
+  } else {
+    const uint32_t last = (out_hi >> 6) - base;
+    for (uint32_t e = last + 1 - n; e <= last; ++e)
+      claim_leaf(g, t, c.idx[(size_t)t * c.B + e], base + e, __float_as_uint(c.prio[(size_t)t * c.B + e]));
+  }
+}
+
 // base: the batch's first stamp (group_mode: from the device counter, see claim_base; else 1).
 __device__ __forceinline__ void claim_element(const Geom& g, uint32_t t, uint32_t size, uint32_t group_mode,
                                               uint32_t base, uint32_t j, uint32_t i, float v, uint32_t& mx,
@@ -75,8 +106,8 @@ __device__ __forceinline__ void leave_claim_base(const Geom& g, uint32_t t, uint
 
 // Claims elements of the batch, strided over the job's workgroups.  Called by whole workgroups.
 // TD: the batch may hold temporal-difference errors to be turned into priorities first (only the
-// stand-alone claim kernel carries that code).
-template <bool TD = false>
+// stand-alone claim kernel carries that code).  RUNS: see claim_run.
+template <bool TD = false, bool RUNS = false>
 __device__ __forceinline__ void claim_job(const Geom& g, uint32_t t, const ClaimArgs& c, uint32_t job_block,
                                           uint32_t job_blocks) {
   if (job_block * blockDim.x >= c.B) return;   // nothing to do for this workgroup
@@ -86,7 +117,32 @@ __device__ __forceinline__ void claim_job(const Geom& g, uint32_t t, const Claim
   uint32_t flags = 0;
   for (uint32_t base = job_block * blockDim.x; base < c.B; base += job_blocks * blockDim.x) {
     const uint32_t j = base + threadIdx.x;
-    if (j < c.B) {
+    if constexpr (RUNS) {
+      const unsigned lane = threadIdx.x & 63u;
+      uint32_t i = 0xFFFFFFFFu;
+      float v = 0.0f;
+      if (j < c.B) {
+        v = c.prio[(size_t)t * c.B + j];
+        i = c.idx[(size_t)t * c.B + j];
+      }
+      bool ok = false;
+      if (j < c.B) {
+        if (!(i < c.size)) flags |= 1u;
+        else if (!valid_priority(v)) flags |= 2u;
+        else ok = true;
+      }
+      const uint32_t group = ok ? i >> (g.logK == 6 ? 6u : 5u) : 0xFFFFFFC0u | lane;   // (an invalid element ends every run)
+      const uint32_t below = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)group, 0x138 /* wave_shr:1: from the lane below */, 0xF, 0xF, true);
+      const bool begins = lane == 0 || below != group;
+      const unsigned long long starts = __ballot(begins);
+      const bool ends = lane == 63u || ((starts >> (lane + 1u)) & 1u);
+      if (ok && ends) {
+        const unsigned start = 63u - (unsigned)__builtin_clzll(starts & (~0ull >> (63u - lane)));
+        claim_run(g, t, c, first, j, i, __float_as_uint(v), lane - start + 1u);
+      }
+      const uint32_t vb = ok && v > 0.0f ? __float_as_uint(v) : 0u;
+      mx = vb > mx ? vb : mx;
+    } else if (j < c.B) {
       float v = c.prio[(size_t)t * c.B + j];
       if constexpr (TD) {
         if (c.from_td)   // priority of a temporal-difference error; a non-finite error stays non-finite and is rejected
@@ -103,6 +159,7 @@ __device__ __forceinline__ void claim_job(const Geom& g, uint32_t t, const Claim
   leave_claim_base(g, t, c.group_mode, job_block == 0 && threadIdx.x == 0, first);
 }
 
+template <bool RUNS>
 __global__ void k_update_claim(Geom g, ClaimArgs c) {
-  claim_job<true>(g, blockIdx.y, c, blockIdx.x, gridDim.x);
+  claim_job<!RUNS, RUNS>(g, blockIdx.y, c, blockIdx.x, gridDim.x);
 }

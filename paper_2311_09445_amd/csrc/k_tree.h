@@ -39,11 +39,23 @@ constexpr uint32_t kDirtyListCap = 2048;
 template <int LOGK>
 constexpr int kMaxPassHeight = LOGK == 1 ? 13 : LOGK == 2 ? 7 : LOGK == 3 ? 5 : LOGK <= 5 ? 4 : 3;
 
+// The batch itself, for a tree pass over a batch that claimed in runs (see claim_run).
+struct BatchRef {
+  const uint32_t* idx;   // [T][B]
+  const float* prio;
+  uint32_t B;
+};
+struct NoBatch {};
+template <bool RUNS>
+using BatchParam = typename std::conditional<RUNS, BatchRef, NoBatch>::type;
+
 // The work of workgroup b of tree t (b = its subtree's root at height hb).  TRACK_MIN: also renew min1
 // (smallest positive leaf) of every rebuilt height-1 node; a compile-time choice, because even as a
 // never-taken branch that code cost the pass half a microsecond.
-template <int LOGK, bool TRACK_MIN>
-__device__ __forceinline__ void tree_job(const Geom& g, const SubLevels& sl, uint32_t t, uint32_t b, uint32_t chain) {
+// RUNS: the batch claimed in runs; an entry may stand for several elements, read from the batch.
+template <int LOGK, bool TRACK_MIN, bool RUNS = false>
+__device__ __forceinline__ void tree_job(const Geom& g, const SubLevels& sl, uint32_t t, uint32_t b, uint32_t chain,
+                                         BatchParam<RUNS> batch = BatchParam<RUNS>{}) {
   constexpr int K = Fan<LOGK>::K;
   constexpr int LPS = Fan<LOGK>::LPS;
   // dynamic LDS: the subtree's nodes, then the list of claimed height-1 nodes (see tree_lds_bytes)
@@ -95,6 +107,10 @@ __device__ __forceinline__ void tree_job(const Geom& g, const SubLevels& sl, uin
   auto fetch_entry = [&](uint32_t node) -> uint2 { return groups[LOGK >= 5 ? node : (node << LOGK) >> 5]; };
   auto decode_entry = [&](uint2 e, uint32_t node) -> uint2 {
     bool mine = (e.y >> 6) >= floor;
+    if constexpr (RUNS) {   // a run: its length in x, 0xC0000000 | the position of its last element in y (any node of the group may have a part in it)
+      const uint32_t n = run_length(e.x);
+      if (mine && n > 1) return make_uint2(n, 0xC0000000u | ((e.y >> 6) - floor));
+    }
     if constexpr (LOGK < 5) mine = mine && ((e.y & 31u) >> LOGK) == (node & ((32u >> LOGK) - 1u));
     e.y = mine ? 0x80000000u | (e.y & (uint32_t)(K - 1)) : 0u;
     return e;
@@ -172,9 +188,11 @@ __device__ __forceinline__ void tree_job(const Geom& g, const SubLevels& sl, uin
       uint32_t node, my;
       size_t at;
       LeafVec c;
-      uint2 s[4];
+      uint2 s[RUNS ? 1 : 4];   // (RUNS: of the lane's first dirty leaf; few leaves are)
       uint2 e;
       uint32_t mn;   // (TRACK_MIN only)
+      uint32_t ri[RUNS ? 4 : 1];   // (RUNS: the first elements of the entry's run; a longer one is read on in finish)
+      float rv[RUNS ? 4 : 1];
     };
     // A set bit means the leaf was claimed leaf by leaf in this batch: its stamp entry holds the winner's value.
     auto fetch = [&](uint32_t item) -> Item {
@@ -193,38 +211,100 @@ __device__ __forceinline__ void tree_job(const Geom& g, const SubLevels& sl, uin
       }
       it.c = *reinterpret_cast<const LeafVec*>(leaves + it.at);
       it.e = s_entry[li];
+      if constexpr (RUNS) {
+        if (it.e.y >= 0xC0000000u) {
+          const size_t e0 = (size_t)t * batch.B + (it.e.y & 0x3FFFFFFFu) + 1u - it.e.x;
 #pragma unroll
-      for (int k = 0; k < (LOGK == 1 ? 2 : 4); ++k) {
-        it.s[k] = make_uint2(0, 0);
-        if (it.my & (1u << k)) it.s[k] = owner[it.at + k];
+          for (uint32_t k = 0; k < 4; ++k)
+            if (k < it.e.x) {
+              it.ri[k] = batch.idx[e0 + k];
+              it.rv[k] = batch.prio[e0 + k];
+            }
+        }
+      }
+      if constexpr (RUNS) {
+        if (it.my) it.s[0] = owner[it.at + (uint32_t)(__ffs((int)it.my) - 1)];
+      } else {
+#pragma unroll
+        for (int k = 0; k < (LOGK == 1 ? 2 : 4); ++k) {
+          it.s[k] = make_uint2(0, 0);
+          if (it.my & (1u << k)) it.s[k] = owner[it.at + k];
+        }
       }
       return it;
     };
     auto finish = [&](Item& it) {
       float sum;
+      auto stamped = [&](uint32_t k) -> float {   // value of dirty leaf k
+        if constexpr (RUNS) {
+          if (it.my & ((1u << k) - 1u)) return __uint_as_float(owner[it.at + k].x);
+          return __uint_as_float(it.s[0].x);
+        } else {
+          return __uint_as_float(it.s[k].x);
+        }
+      };
       // the group entry's leaf, if it is one of this lane's
       const uint32_t el = it.e.y & 63u;
-      const bool here = it.e.y != 0 && (LOGK == 1 || (el >> 2) == q);
+      const bool here = it.e.y != 0 && (!RUNS || it.e.y < 0xC0000000u) && (LOGK == 1 || (el >> 2) == q);
       const uint32_t sel = here ? 1u << (el & (LOGK == 1 ? 1u : 3u)) : 0u;
       const float ev = __uint_as_float(it.e.x);
+      // the elements of a run, in their order (an element of another node of the group, or of another lane's leaves, is not taken)
+      [[maybe_unused]] auto take_run = [&](auto&& set) {
+        auto take = [&](uint32_t i, float v) {
+          if ((i >> LOGK) != it.node) return;
+          const uint32_t l = i & (uint32_t)(K - 1);
+          if (LOGK == 1 || (l >> 2) == q) set(LOGK == 1 ? l : l & 3u, v);
+        };
+#pragma unroll
+        for (uint32_t k = 0; k < 4; ++k)
+          if (k < it.e.x) take(it.ri[RUNS ? k : 0], it.rv[RUNS ? k : 0]);
+        if constexpr (RUNS) {
+          const size_t e0 = (size_t)t * batch.B + (it.e.y & 0x3FFFFFFFu) + 1u - it.e.x;
+          for (uint32_t k0 = 4; k0 < it.e.x; k0 += 4) {   // (four at a time: an element at a time is a trip to memory each)
+            uint32_t i[4];
+            float v[4];
+#pragma unroll
+            for (uint32_t k = 0; k < 4; ++k) {
+              const uint32_t at = k0 + k < it.e.x ? k0 + k : it.e.x - 1;
+              i[k] = batch.idx[e0 + at];
+              v[k] = batch.prio[e0 + at];
+            }
+#pragma unroll
+            for (uint32_t k = 0; k < 4; ++k) take(i[k], v[k]);   // (the last element again beyond the end)
+          }
+        }
+      };
       if constexpr (LOGK == 1) {
-        if (it.my & 1u) it.c.x = __uint_as_float(it.s[0].x);
-        if (it.my & 2u) it.c.y = __uint_as_float(it.s[1].x);
+        if (it.my & 1u) it.c.x = stamped(0);
+        if (it.my & 2u) it.c.y = stamped(1);
         if (sel & 1u) it.c.x = ev;
         if (sel & 2u) it.c.y = ev;
         it.my |= sel;
+        if constexpr (RUNS) {
+          if (it.e.y >= 0xC0000000u) take_run([&](uint32_t l, float v) { if (l) it.c.y = v; else it.c.x = v; it.my |= 1u << l; });
+        }
         sum = it.c.x + it.c.y;
         if constexpr (TRACK_MIN) it.mn = min_u32(positive_bits(it.c.x), positive_bits(it.c.y));
       } else {
-        if (it.my & 1u) it.c.x = __uint_as_float(it.s[0].x);
-        if (it.my & 2u) it.c.y = __uint_as_float(it.s[1].x);
-        if (it.my & 4u) it.c.z = __uint_as_float(it.s[2].x);
-        if (it.my & 8u) it.c.w = __uint_as_float(it.s[3].x);
+        if (it.my & 1u) it.c.x = stamped(0);
+        if (it.my & 2u) it.c.y = stamped(1);
+        if (it.my & 4u) it.c.z = stamped(2);
+        if (it.my & 8u) it.c.w = stamped(3);
         if (sel & 1u) it.c.x = ev;
         if (sel & 2u) it.c.y = ev;
         if (sel & 4u) it.c.z = ev;
         if (sel & 8u) it.c.w = ev;
         it.my |= sel;
+        if constexpr (RUNS) {
+          if (it.e.y >= 0xC0000000u)
+            take_run([&](uint32_t l, float v) {
+              it.c.x = l == 0 ? v : it.c.x;
+              it.c.y = l == 1 ? v : it.c.y;
+              it.c.z = l == 2 ? v : it.c.z;
+              it.c.w = l == 3 ? v : it.c.w;
+              it.my |= 1u << l;
+            });
+        }
         sum = butterfly_sum<Fan<LOGK>::LOGLPS>((it.c.x + it.c.y) + (it.c.z + it.c.w));
         if constexpr (TRACK_MIN) {
           uint32_t m = min_u32(min_u32(positive_bits(it.c.x), positive_bits(it.c.y)),
@@ -245,21 +325,35 @@ __device__ __forceinline__ void tree_job(const Geom& g, const SubLevels& sl, uin
         if constexpr (TRACK_MIN) g.min1[(size_t)t * g.min1_stride + it.node] = it.mn;
       }
     };
-    for (uint32_t base = 0; base < nd; base += 2 * ngrp) {
-      Item i0 = fetch(base + grp);
-      if (base + ngrp < nd) {   // uniform over the workgroup
-        Item i1 = fetch(base + ngrp + grp);
-        PER_MARK(4);
+    if constexpr (RUNS && LOGK >= 5) {   // (four nodes: these fanouts have few, large subtrees, and dense batches list most of their nodes)
+      for (uint32_t base = 0; base < nd; base += 4 * ngrp) {
+        Item i0 = fetch(base + grp), i1 = fetch(base + ngrp + grp), i2 = fetch(base + 2 * ngrp + grp), i3 = fetch(base + 3 * ngrp + grp);
         const float sum0 = finish(i0);
         const float sum1 = finish(i1);
-        PER_MARK(5);
+        const float sum2 = finish(i2);
+        const float sum3 = finish(i3);
         store(i0, sum0);
         store(i1, sum1);
-      } else {
-        PER_MARK(4);
-        const float sum0 = finish(i0);
-        PER_MARK(5);
-        store(i0, sum0);
+        store(i2, sum2);
+        store(i3, sum3);
+      }
+    } else {
+      for (uint32_t base = 0; base < nd; base += 2 * ngrp) {
+        Item i0 = fetch(base + grp);
+        if (base + ngrp < nd) {   // uniform over the workgroup
+          Item i1 = fetch(base + ngrp + grp);
+          PER_MARK(4);
+          const float sum0 = finish(i0);
+          const float sum1 = finish(i1);
+          PER_MARK(5);
+          store(i0, sum0);
+          store(i1, sum1);
+        } else {
+          PER_MARK(4);
+          const float sum0 = finish(i0);
+          PER_MARK(5);
+          store(i0, sum0);
+        }
       }
     }
     PER_MARK(2);
@@ -382,11 +476,11 @@ __device__ __forceinline__ void fold_pending_max(const Geom& g, uint32_t t, uint
 // stays within an eighth of the SIMD's scalar and vector registers (with one scalar register more the
 // second workgroup waits for the first to end and the kernel takes half as long again), and holding
 // the compiler to that budget made it spill; 512 lanes run the pass just as fast.
-template <int LOGK, bool TRACK_MIN>
+template <int LOGK, bool TRACK_MIN, bool RUNS>
 __global__ void __launch_bounds__(512)
-k_update_tree(Geom g, SubLevels sl, uint32_t chain) {
+k_update_tree(Geom g, SubLevels sl, uint32_t chain, BatchParam<RUNS> batch) {
   const uint32_t pend = (chain & 2u) && blockIdx.x == 0 ? read_word_with_the_loads(&g.max_pend[blockIdx.y]) : 0u;
-  tree_job<LOGK, TRACK_MIN>(g, sl, blockIdx.y, blockIdx.x, chain & 1u);
+  tree_job<LOGK, TRACK_MIN, RUNS>(g, sl, blockIdx.y, blockIdx.x, chain & 1u, batch);
   if ((chain & 2u) && blockIdx.x == 0) fold_pending_max(g, blockIdx.y, pend);
 }
 
@@ -526,13 +620,16 @@ static hipError_t launch_tree_k(const Geom& g, const Tuning& tn, const ClaimArgs
   if (e != hipSuccess) return e;
   if (tblock > 512) tblock = 512;
   const uint32_t chain = (lazy_top_height(g, tn) ? 0u : 1u) | (c.fold_max ? 2u : 0u);
-  if (c.track_min) {
-    PER_LAUNCH(KID_UPDATE_TREE, (k_update_tree<LOGK, true>), dim3(g.n[sl.hb], g.T), dim3(tblock), tree_lds_bytes<LOGK>(sl),
-               s, g, sl, chain);
+#define PER_UPDATE_TREE(TM, RN, BATCH)                                                                                     \
+  PER_LAUNCH(KID_UPDATE_TREE, (k_update_tree<LOGK, TM, RN>), dim3(g.n[sl.hb], g.T), dim3(tblock), tree_lds_bytes<LOGK>(sl), s, \
+             g, sl, chain, BATCH)
+  const BatchRef batch{c.idx, c.prio, c.B};
+  if (c.runs) {
+    if (c.track_min) { PER_UPDATE_TREE(true, true, batch); } else { PER_UPDATE_TREE(false, true, batch); }
   } else {
-    PER_LAUNCH(KID_UPDATE_TREE, (k_update_tree<LOGK, false>), dim3(g.n[sl.hb], g.T), dim3(tblock), tree_lds_bytes<LOGK>(sl),
-               s, g, sl, chain);
+    if (c.track_min) { PER_UPDATE_TREE(true, false, NoBatch{}); } else { PER_UPDATE_TREE(false, false, NoBatch{}); }
   }
+#undef PER_UPDATE_TREE
   return hipGetLastError();
 }
 
@@ -566,9 +663,19 @@ static hipError_t launch_tree_finish_k(const Geom& g, const Tuning& tn, const Cl
 }
 
 template <int LOGK>
-static hipError_t launch_update_k(const Geom& g, const Tuning& tn, const ClaimArgs& c, hipStream_t s) {
+static hipError_t launch_update_k(const Geom& g, const Tuning& tn, ClaimArgs c, hipStream_t s) {
   const uint32_t block = tn.update_block;
-  PER_LAUNCH(KID_UPDATE_CLAIM, k_update_claim, dim3((c.B + block - 1) / block, g.T), dim3(block), 0, s, g, c);
+  // In runs where that pays: plain priorities, a quarter of an element per group of 32 leaves on the average.  Where the
+  // tree pass has fewer subtrees than the device has compute units, its reading of the runs weighs more, and an element
+  // per group is the break-even (2^22 leaves at K = 32, 84 609 elements: both kernels 15.3 us leaf by leaf, 17.3 in runs;
+  // 262 144: 31.7 and 23.4).
+  const bool few = (uint64_t)g.n[tree_pass_height(g)] * g.T < 256;
+  c.runs = c.group_mode && !c.from_td && !c.pos && (uint64_t)c.B * (few ? 32u : 128u) >= g.N ? 1u : 0u;
+  if (c.runs) {
+    PER_LAUNCH(KID_UPDATE_CLAIM, k_update_claim<true>, dim3((c.B + block - 1) / block, g.T), dim3(block), 0, s, g, c);
+  } else {
+    PER_LAUNCH(KID_UPDATE_CLAIM, k_update_claim<false>, dim3((c.B + block - 1) / block, g.T), dim3(block), 0, s, g, c);
+  }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   return launch_tree_k<LOGK>(g, tn, c, s);

@@ -105,6 +105,7 @@ struct ClaimArgs {
   uint32_t group_mode;     // the batch claims through the group entries (else leaf by leaf)
   uint32_t track_min;      // the tree pass also renews min1 of the height-1 nodes it rebuilds
   uint32_t fold_max;       // the tree pass also folds max_pend into the running maximum
+  uint32_t runs;           // group_mode: consecutive elements for one group claim together (see claim_run)
   const uint32_t* idx;     // [T][B]
   const uint32_t* pos;     // null, or [T][B] positions: element j targets idx[pos[j]] (the leaf drawn by sample pos[j] of the
                            // sampling call the update is fused with); a position >= B makes the element invalid

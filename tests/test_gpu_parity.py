@@ -1203,6 +1203,69 @@ def test_buffer_wide_weights_in_the_fused_step_and_the_one_launch_forms(K, N, B)
     m.compare_status()
 
 
+@pytest.mark.parametrize("K,N,T,B", [(2, 5000, 1, 40000), (4, 70001, 3, 13000), (8, 70001, 1, 33000), (16, 70001, 1, 33021),
+                                     (32, 200003, 2, 20001), (64, 70001, 1, 65537)])
+def test_sampling_workgroups_take_blocks_in_turn(K, N, T, B):
+    """More blocks of samples than the device is taken to hold workgroups (an LDS request that leaves one per compute
+    unit): the looping kernel, alone, with inline claims, with drawn uniforms and on an empty tree."""
+    log(f"sampling in turn K={K} N={N} T={T} B={B}")
+    rng = np.random.default_rng(B)
+    m = Mirror(K, N, T, (12,))
+    m.gpu.set_tuning("sample_min_lds", 100_000)
+    m.gpu.set_tuning("step_kernel", 0)
+    m.insert(N, prio=np.zeros((T, N), np.float32))
+    m.sample(wl.uniform01(rng, (T, B)), 0.4)                       # nothing can be sampled
+    m.gpu.clear_status()
+    for o in m.cpu.trees:
+        o.clear_status()
+    prio = wl._draw_priorities("lognormal_0_1", rng, (T, N))
+    prio[:, rng.random(N) < 0.3] = 0.0
+    m.insert(N, prio=prio)
+    for beta in (0.4, 1.0):
+        m.sample(wl.uniform01(rng, (T, B)), beta, fused_rows=True)
+        m.sample_gather_update(wl.uniform01(rng, (T, B)), beta, True, (rng.random((T, B)) * 3).astype(np.float32), alias=True)
+        m.compare_tree()
+    m.compare_status()
+
+
+@pytest.mark.parametrize("K,N,T", [(2, 5000, 1), (4, 4097, 2), (8, 9000, 1), (16, 70001, 2), (32, 200003, 1), (64, 70001, 2)])
+@pytest.mark.parametrize("norm", ["batch", "buffer"])
+def test_updates_claimed_in_runs(K, N, T, norm):
+    """Dense batches: long and short runs of elements in one claim group, repeated leaves, invalid elements inside runs,
+    runs across waves, the same groups again later in the batch."""
+    log(f"updates in runs K={K} N={N} T={T} {norm}")
+    rng = np.random.default_rng(N + K)
+    m = Mirror(K, N, T, ())
+    m.gpu.set_weight_norm(norm)
+    m.cpu.set_weight_norm(norm)
+    m.insert(N, prio=wl._draw_priorities("exponential_1", rng, (T, N)))
+    m.sample(wl.uniform01(rng, (T, 100)), 0.5)
+    for B in (N // 100 + 1, 777, N // 3, 2 * N):
+        for kind in range(5):
+            idx = np.sort(rng.integers(0, N, (T, B)), axis=1)
+            if kind == 1:      # few leaves, each many times
+                idx = np.sort(rng.integers(0, max(1, B // 40), (T, B)) * 3 % N, axis=1)
+            elif kind == 2:    # pieces of a sorted batch in another order
+                idx = np.concatenate(np.array_split(idx, 7, axis=1)[::-1], axis=1)
+            elif kind == 3:    # the same stretch of leaves over and over
+                idx = np.tile(np.arange(B) % 150, (T, 1)) % N
+            elif kind == 4:    # no order
+                idx = rng.permuted(idx, axis=1)
+            idx = idx.astype(np.uint32)
+            prio = (rng.random((T, B)) * 3).astype(np.float32)
+            prio[:, ::9] = 0.0
+            prio[:, 1::17] = -0.0
+            if kind % 2:
+                prio[:, ::23] = np.float32("nan")
+                idx[:, 5::31] = N + 3
+            m.update(idx, prio)
+            m.compare_tree()
+    m.compare_status()
+    if norm == "buffer":
+        want = np.array([t.read_level(0)[t.read_level(0) > 0].min() for t in m.cpu.trees], dtype=np.float32)
+        assert m.gpu.min_priority().cpu().numpy().tobytes() == want.tobytes()
+
+
 # ---------------------------------------------------------------------------------------------
 # per_run_requests: a queue of op-coded requests in one launch.  Same results as the calls, in queue order.
 # ---------------------------------------------------------------------------------------------
