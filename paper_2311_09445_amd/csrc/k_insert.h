@@ -1,44 +1,9 @@
-// Insertion: leaf writes, and the single-kernel insert of a few rows.
+// Insertion of a few rows by one workgroup per tree.
 // Part of per_kernels.hip (included inside namespace per, in the order given there); not a stand-alone header.
 
 // ---------------------------------------------------------------------------------
-// insertion: leaf writes (rows go through k_rows<false>)
+// insertion of a few rows
 // ---------------------------------------------------------------------------------
-// Leaf of inserted row j (ring slot cursor + j): the given value, or the running maximum.
-__device__ __forceinline__ void insert_leaf(const Geom& g, uint32_t t, uint32_t n, uint32_t cursor, uint32_t j,
-                                            const float* __restrict__ prio, float max_on_entry,
-                                            uint32_t* __restrict__ out_idx, uint32_t& mx, bool& bad) {
-  uint64_t slot = (uint64_t)cursor + j;
-  if (slot >= g.N) slot -= g.N;
-  if (out_idx) out_idx[(size_t)t * n + j] = (uint32_t)slot;
-  float* leaf = g.level[0] + (size_t)t * g.stride[0] + slot;
-  if (prio) {
-    const float v = prio[(size_t)t * n + j];
-    if (valid_priority(v)) {
-      *leaf = v;
-      const uint32_t vb = v > 0.0f ? __float_as_uint(v) : 0u;
-      mx = vb > mx ? vb : mx;
-    } else {
-      bad = true;
-    }
-  } else {
-    *leaf = max_on_entry;   // running maximum as it was when the call started
-  }
-}
-
-__global__ void k_insert_leaves(Geom g, uint32_t n, uint32_t cursor, const float* __restrict__ prio,
-                                uint32_t* __restrict__ out_idx) {
-  const uint32_t t = blockIdx.y;
-  const uint32_t j = blockIdx.x * blockDim.x + threadIdx.x;
-  uint32_t mx = 0;
-  bool bad = false;
-  if (j < n) insert_leaf(g, t, n, cursor, j, prio, prio ? 0.0f : g.max_v[t], out_idx, mx, bad);
-  if (prio) {
-    raise_max(g, t, mx, read_max_bits(g, t));
-    if (bad) atomicOr(&g.status[t], 2u);
-  }
-}
-
 // A small insert as one kernel, one workgroup per tree: the rows, the leaves, and every ancestor
 // of the touched ring slots up to the root.  The touched nodes of a height form at most two
 // contiguous ranges (narrowed by K per height), known before anything is read, so the child groups
@@ -275,13 +240,6 @@ k_insert_small(InsertArgs a, FieldTable ft, uint32_t n, uint32_t cursor, const f
   }
   PER_MARK(4);
   PER_FLUSH();
-}
-
-hipError_t launch_insert_leaves(const Geom& g, const Tuning& tn, uint32_t n, uint32_t cursor, const float* prio,
-                                uint32_t* out_idx, hipStream_t s) {
-  PER_LAUNCH(KID_INSERT_LEAVES, k_insert_leaves, dim3((n + 255) / 256, g.T), dim3(256), 0, s, g, n, cursor, prio,
-             out_idx);
-  return hipGetLastError();
 }
 
 // True when an insert of n rows is small enough for k_insert_small: few bytes to move and few

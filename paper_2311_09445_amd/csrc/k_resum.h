@@ -57,13 +57,14 @@ __global__ void k_resum_tail(Geom g, uint32_t h_start, Range2 r) {
 // A single workgroup handles a height while the groups it must read stay below this many floats.
 constexpr uint64_t kTailFloats = 16384;
 
+// Re-sums the heights above `below`, of which the nodes r were rewritten (below = 0: leaf slots).
 template <int LOGK>
-static hipError_t launch_resum_ranges_k(const Geom& g, const Tuning& tn, Range2 r, hipStream_t s) {
+static hipError_t launch_resum_above_k(const Geom& g, const Tuning& tn, uint32_t below, Range2 r, hipStream_t s) {
   constexpr int K = Fan<LOGK>::K;
   constexpr int LPS = Fan<LOGK>::LPS;
   const uint32_t block = tn.update_block;
-  // r holds touched leaf slots; move to height 1
-  uint32_t h = 1;
+  // r holds the rewritten nodes; move to the height above
+  uint32_t h = below + 1;
   for (; h <= g.H; ++h) {
     if (r.b0 > r.a0) { r.a0 >>= LOGK; r.b0 = ((r.b0 - 1) >> LOGK) + 1; }
     if (r.b1 > r.a1) { r.a1 >>= LOGK; r.b1 = ((r.b1 - 1) >> LOGK) + 1; }
@@ -102,7 +103,7 @@ hipError_t launch_resum_top(const Geom& g, const Tuning& tn, uint32_t hb, hipStr
 }
 
 hipError_t launch_resum_ranges(const Geom& g, const Tuning& tn, Range2 r0, hipStream_t s) {
-#define CALL(L) launch_resum_ranges_k<L>(g, tn, r0, s)
+#define CALL(L) launch_resum_above_k<L>(g, tn, 0, r0, s)
   PER_DISPATCH_LOGK(g.logK, CALL)
 #undef CALL
 }

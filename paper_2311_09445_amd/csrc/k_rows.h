@@ -491,22 +491,19 @@ __global__ void k_finish(FieldTable ft, JobRanges jr, Geom g, FinishArgs a) {
     rows_job<true, WIDE>(ft, f, t, a.B, a.idx, 0, g.N, g.status, b - jr.first[2 + f], jr.first[3 + f] - jr.first[2 + f]);
 }
 
-// Stand-alone gather (GATHER) and insert scatter: one job per payload field (gathers: or one over whole rows).
-template <bool GATHER, bool WIDE>
-__global__ void k_rows(FieldTable ft, JobRanges jr, uint32_t B, const uint32_t* __restrict__ idx, uint32_t cursor,
-                       uint32_t N, uint32_t* status) {
+// Stand-alone gather: one job per payload field, or one over whole rows.
+template <bool WIDE>
+__global__ void k_rows(FieldTable ft, JobRanges jr, uint32_t B, const uint32_t* __restrict__ idx, uint32_t N, uint32_t* status) {
   const uint32_t t = blockIdx.y;
   const uint32_t b = blockIdx.x;
   const uint32_t f = job_field(jr, b);
-  if constexpr (GATHER) {
-    if (jr.whole_rows) {
-      extern __shared__ __attribute__((aligned(16))) uint8_t stage[];
-      move_whole_rows(ft, jr, t, B, idx, N, status, b - jr.first[2 + f], jr.first[3 + f] - jr.first[2 + f], stage);
-      return;
-    }
+  if (jr.whole_rows) {
+    extern __shared__ __attribute__((aligned(16))) uint8_t stage[];
+    move_whole_rows(ft, jr, t, B, idx, N, status, b - jr.first[2 + f], jr.first[3 + f] - jr.first[2 + f], stage);
+    return;
   }
   if (f < (uint32_t)kMaxFields)
-    rows_job<GATHER, WIDE>(ft, f, t, B, idx, cursor, N, status, b - jr.first[2 + f], jr.first[3 + f] - jr.first[2 + f]);
+    rows_job<true, WIDE>(ft, f, t, B, idx, 0, N, status, b - jr.first[2 + f], jr.first[3 + f] - jr.first[2 + f]);
 }
 
 // Workgroups per job: weights, claim, then each field with a destination.  A field gets the workgroups one
@@ -598,9 +595,9 @@ hipError_t launch_gather(const Geom& g, const Tuning& tn, const FieldTable& ft, 
   if (gx == 0) return hipSuccess;
   const size_t lds = whole_rows_lds(jr);
   if (!jr.whole_rows && any_field_moves_wide(&ft)) {
-    PER_LAUNCH(KID_GATHER, (k_rows<true, true>), dim3(gx, g.T), dim3(block), lds, s, ft, jr, B, idx, 0, g.N, g.status);
+    PER_LAUNCH(KID_GATHER, k_rows<true>, dim3(gx, g.T), dim3(block), lds, s, ft, jr, B, idx, g.N, g.status);
   } else {
-    PER_LAUNCH(KID_GATHER, (k_rows<true, false>), dim3(gx, g.T), dim3(block), lds, s, ft, jr, B, idx, 0, g.N, g.status);
+    PER_LAUNCH(KID_GATHER, k_rows<false>, dim3(gx, g.T), dim3(block), lds, s, ft, jr, B, idx, g.N, g.status);
   }
   return hipGetLastError();
 }
@@ -618,20 +615,6 @@ static hipError_t launch_finish(const Geom& g, const Tuning& tn, const FieldTabl
     PER_LAUNCH(KID_FINISH, k_finish<true>, dim3(jr.first[2 + kMaxFields], g.T), dim3(block), lds, s, ft, jr, g, a);
   } else {
     PER_LAUNCH(KID_FINISH, k_finish<false>, dim3(jr.first[2 + kMaxFields], g.T), dim3(block), lds, s, ft, jr, g, a);
-  }
-  return hipGetLastError();
-}
-
-hipError_t launch_scatter(const Geom& g, const Tuning& tn, const FieldTable& ft, uint32_t n, uint32_t cursor,
-                          hipStream_t s) {
-  const uint32_t block = tn.gather_block;
-  const JobRanges jr = job_ranges(&ft, n, block, 0, 0, g.T);
-  const uint32_t gx = jr.first[2 + kMaxFields];
-  if (gx == 0) return hipSuccess;
-  if (any_field_moves_wide(&ft)) {
-    PER_LAUNCH(KID_SCATTER, (k_rows<false, true>), dim3(gx, g.T), dim3(block), 0, s, ft, jr, n, nullptr, cursor, g.N, g.status);
-  } else {
-    PER_LAUNCH(KID_SCATTER, (k_rows<false, false>), dim3(gx, g.T), dim3(block), 0, s, ft, jr, n, nullptr, cursor, g.N, g.status);
   }
   return hipGetLastError();
 }

@@ -553,32 +553,40 @@ static size_t tree_lds_bytes(const SubLevels& sl) {
   return ((size_t)(sl.lds_floats + 3u) / 4u * 4u + (size_t)sl.list_cap * (LOGK == 6 ? 5u : 4u)) * 4u;
 }
 
-// Sub-level descriptors and workgroup size of the tree pass for the update batch claimed with `c`.
+// The heights 1 .. hb of a tree-pass workgroup's subtree (hb: tree_pass_height), and where it keeps them in LDS.
 template <int LOGK>
-static hipError_t tree_pass_shape(const Geom& g, const Tuning& tn, const ClaimArgs& c, SubLevels* out,
-                                  uint32_t* tblock_out) {
+static void sub_levels(const Geom& g, SubLevels* out) {
   constexpr int K = Fan<LOGK>::K;
-  const uint32_t B = c.B;
-  const uint32_t hb = tree_pass_height(g);
-  if (hb > (uint32_t)kSubSlots || hb > (uint32_t)kMaxPassHeight<LOGK>)
-    return hipErrorInvalidValue;   // cannot happen for fanouts and capacities accepted at create
   SubLevels sl{};
-  sl.hb = hb;
-  sl.group_batch = c.group_mode ? c.B : 0u;
+  sl.hb = tree_pass_height(g);
   uint32_t off = 0;
-  for (uint32_t h = 1; h <= hb; ++h) {
+  for (uint32_t h = 1; h <= sl.hb; ++h) {
     const uint32_t j = h - 1;
     sl.ptr[j] = g.level[h];
     sl.stride[j] = g.stride[h];
     sl.n[j] = g.n[h];
     sl.lds_off[j] = off;
     // nodes of this height under one workgroup root, padded to whole child groups
-    const uint64_t full = 1ull << ((hb - h) * LOGK);
-    const uint64_t padded = h < hb ? ((uint64_t)g.n[h] + K - 1) / K * K : 1;
+    const uint64_t full = 1ull << ((sl.hb - h) * LOGK);
+    const uint64_t padded = h < sl.hb ? ((uint64_t)g.n[h] + K - 1) / K * K : 1;
     off += (uint32_t)(full < padded ? full : padded);
   }
   sl.lds_floats = off;
-  sl.list_cap = hb > 1 ? sl.lds_off[1] : 1u;
+  sl.list_cap = sl.hb > 1 ? sl.lds_off[1] : 1u;
+  *out = sl;
+}
+
+// Sub-level descriptors and workgroup size of the tree pass for the update batch claimed with `c`.
+template <int LOGK>
+static hipError_t tree_pass_shape(const Geom& g, const Tuning& tn, const ClaimArgs& c, SubLevels* out,
+                                  uint32_t* tblock_out) {
+  const uint32_t B = c.B;
+  const uint32_t hb = tree_pass_height(g);
+  if (hb > (uint32_t)kSubSlots || hb > (uint32_t)kMaxPassHeight<LOGK>)
+    return hipErrorInvalidValue;   // cannot happen for fanouts and capacities accepted at create
+  SubLevels sl;
+  sub_levels<LOGK>(g, &sl);
+  sl.group_batch = c.group_mode ? c.B : 0u;
   // Unless told otherwise: enough lane groups to rebuild in one sweep twice the dirty height-1 nodes a
   // subtree gets on average (never more than it has), so that small batches do not launch idle waves.
   uint32_t tblock = tn.tree_block;

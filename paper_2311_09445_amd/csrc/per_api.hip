@@ -378,7 +378,11 @@ static int insert_impl(per_t* p, uint32_t n, const void* const* d_field_src, con
   const bool has_rows = fill_fields(p, const_cast<void* const*>(reinterpret_cast<const void* const*>(d_field_src)), &ft);
   const bool one_workgroup = insert_fits_one_workgroup(p->g, has_rows ? &ft : nullptr, n);
   if (n_protect && !one_workgroup) return PER_ERANGE;   // the protected form exists for small inserts only
-  if ((p->tn.insert_small || n_protect) && one_workgroup) {
+  // The one-workgroup kernel serves protected insertions, and the smallest ones on trees whose top is not left to its next
+  // reader (it goes up to the root with its nodes in registers; 4 rows on 4096 leaves at K = 2: 6.0 us against 7.1 by the
+  // kernel of large insertions, 16 rows: 6.5 against 6.7, 64 rows: 7.1 against 6.7).  Everywhere else the other one is
+  // faster from the first row on (a row on 2^20 leaves at K = 16: 3.3 against 4.8 us, 1024 rows: 3.7 against 55).
+  if (n_protect || (p->tn.insert_small && one_workgroup && n <= 16 && !lazy_top_height(p->g, p->tn))) {
     // one kernel: rows, leaves, ancestors, and the heights an update may have left stale
     hipError_t e1 = launch_insert_small(p->g, p->tn, has_rows ? &ft : nullptr, n, cursor, d_prio, d_out_idx, p->stale_hb,
                                         n_protect ? d_protect : nullptr, n_protect, tracks_min(p), s);
@@ -388,19 +392,13 @@ static int insert_impl(per_t* p, uint32_t n, const void* const* d_field_src, con
     p->size = p->size + n > N ? N : p->size + n;
     return PER_OK;
   }
-  p->min_stale = true;   // (the kernels of a large insert do not renew min1)
-  hipError_t e = ensure_top(p, s);
-  if (e == hipSuccess && has_rows) e = launch_scatter(p->g, p->tn, ft, n, cursor, s);
-  if (e == hipSuccess) e = launch_insert_leaves(p->g, p->tn, n, cursor, d_prio, d_out_idx, s);
-  if (e == hipSuccess) {
-    Range2 r;
-    const uint64_t end = p->cursor + n;
-    r.a0 = cursor;
-    r.b0 = (uint32_t)(end < N ? end : N);
-    r.a1 = 0;
-    r.b1 = (uint32_t)(end > N ? end - N : 0);
-    e = launch_resum_ranges(p->g, p->tn, r, s);
-  }
+  // one kernel for rows, leaves and the heights of the touched subtrees; the heights above are left stale, or re-summed
+  const uint32_t hb = lazy_top_height(p->g, p->tn);
+  hipError_t e = p->stale_hb && !hb ? ensure_top(p, s) : hipSuccess;
+  const bool track = tracks_min(p);
+  if (!track) p->min_stale = true;
+  if (e == hipSuccess) e = launch_insert_bulk(p->g, p->tn, has_rows ? &ft : nullptr, n, cursor, d_prio, d_out_idx, track, s);
+  if (hb) p->stale_hb = hb;
   // the mirrors advance even if a later launch failed: rows already enqueued have been placed
   p->cursor = (p->cursor + n) % N;
   p->size = p->size + n > N ? N : p->size + n;

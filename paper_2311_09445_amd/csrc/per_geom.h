@@ -213,7 +213,7 @@ struct InsertRide : InsertRideHead {
 
 // Optional per-kernel timing with HIP events attached to each launch (off by default).
 enum KernelId {
-  KID_FILL, KID_SAMPLE, KID_WEIGHTS, KID_GATHER, KID_FINISH, KID_SCATTER, KID_INSERT_LEAVES, KID_RESUM_DENSE,
+  KID_FILL, KID_SAMPLE, KID_WEIGHTS, KID_GATHER, KID_FINISH, KID_INSERT_BULK, KID_RESUM_DENSE,
   KID_RESUM_TAIL, KID_UPDATE_CLAIM, KID_UPDATE_TREE, KID_TREE_FINISH, KID_UPDATE_DELTA, KID_GET_PRIORITY,
   KID_INSERT_SMALL, KID_RUN_STEPS, KID_RUN_REQUESTS, KID_MIN_REBUILD, KID_MIN_REDUCE, KID_STEP, KID_STEP_TABLES, KID_STEP_EPILOGUE, KID_COUNT
 };
@@ -263,10 +263,8 @@ hipError_t launch_sample(const Geom& g, const Tuning& tn, uint32_t B, uint32_t s
 bool sample_can_carry_insert(const Geom& g, const Tuning& tn, uint32_t B, const FieldTable* ft, uint32_t n, uint32_t cursor);
 hipError_t launch_gather(const Geom& g, const Tuning& tn, const FieldTable& ft, uint32_t B, const uint32_t* idx,
                          hipStream_t s);
-hipError_t launch_scatter(const Geom& g, const Tuning& tn, const FieldTable& ft, uint32_t n, uint32_t cursor,
-                          hipStream_t s);
-hipError_t launch_insert_leaves(const Geom& g, const Tuning& tn, uint32_t n, uint32_t cursor, const float* prio,
-                                uint32_t* out_idx, hipStream_t s);
+hipError_t launch_insert_bulk(const Geom& g, const Tuning& tn, const FieldTable* rows, uint32_t n, uint32_t cursor, const float* prio,
+                              uint32_t* out_idx, bool track_min, hipStream_t s);
 bool insert_fits_one_workgroup(const Geom& g, const FieldTable* ft, uint32_t n);
 hipError_t launch_insert_small(const Geom& g, const Tuning& tn, const FieldTable* ft, uint32_t n, uint32_t cursor,
                                const float* prio, uint32_t* out_idx, uint32_t stale_hb, const uint32_t* protect,

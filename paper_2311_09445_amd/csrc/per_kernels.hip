@@ -23,7 +23,7 @@ namespace per {
 // ---------------------------------------------------------------------------------
 const char* kernel_name(int kid) {
   static const char* const names[KID_COUNT] = {
-      "k_fill_u32", "k_sample", "k_weights", "k_rows_gather", "k_finish", "k_rows_scatter", "k_insert_leaves",
+      "k_fill_u32", "k_sample", "k_weights", "k_rows_gather", "k_finish", "k_insert_bulk",
       "k_resum_dense", "k_resum_tail", "k_update_claim", "k_update_tree", "k_tree_finish", "k_update_delta",
       "k_get_priority", "k_insert_small", "k_run_steps", "k_run_requests", "k_min_rebuild", "k_min_reduce", "k_step",
       "k_step_tables", "k_step_epilogue"};
@@ -100,6 +100,7 @@ static hipError_t grant_lds(const Tuning& tn, size_t bytes) {
 #include "k_resum.h"
 #include "k_insert.h"
 #include "k_tree.h"
+#include "k_insert_bulk.h"
 #include "k_step.h"
 #include "k_delta.h"
 #include "k_stream.h"

@@ -1266,6 +1266,39 @@ def test_updates_claimed_in_runs(K, N, T, norm):
         assert m.gpu.min_priority().cpu().numpy().tobytes() == want.tobytes()
 
 
+@pytest.mark.parametrize("K,N,T,fb,sizes", [
+    (2, 3001, 1, (16, 4, 4, 16, 1), (17, 1500, 3001, 1)), (4, 70001, 1, (5,), (18, 333, 20000)), (8, 50001, 2, (68, 24, 4, 68, 1), (1, 700, 50001)),
+    (16, 70001, 3, (68, 24, 4, 68, 1), (15, 4097, 47000, 69999)), (32, 150001, 1, (5, 68, 2), (31, 33000, 140001)),
+    (64, 70001, 2, (128, 16), (63, 66000, 9)), (16, 9, 2, (3,), (1, 9, 8)), (8, 1 << 16, 2, (128,), (65, 65536))])
+@pytest.mark.parametrize("norm", ["batch", "buffer"])
+def test_insertions_of_many_rows(K, N, T, fb, sizes, norm):
+    """The kernel of large insertions at the edges of nodes, subtrees and passes: windows inside a node, over the ring's end,
+    of the whole ring; given priorities with invalid ones among them; rows stored whole (from 2^17 rows per call) and
+    field by field; right after updates that left the top to its next reader."""
+    log(f"insertions K={K} N={N} T={T} fb={fb} sizes={sizes} {norm}")
+    rng = np.random.default_rng(N + K)
+    m = Mirror(K, N, T, fb)
+    m.gpu.set_weight_norm(norm)
+    m.cpu.set_weight_norm(norm)
+    m.insert(N, prio=wl._draw_priorities("exponential_1", rng, (T, N)))
+    for r, n in enumerate(tuple(sizes) * 2):
+        prio = None
+        if r % 3 != 1:
+            prio = (rng.random((T, n)) * 4).astype(np.float32)
+            if r % 2:
+                prio[:, ::5] = np.float32("nan")
+                prio[:, 1::7] = -1.0
+        m.insert(n, prio=prio, with_rows=r % 4 != 3)
+        if r % 2:
+            m.compare_tree()
+        gi, ci = m.sample(wl.uniform01(rng, (T, 200)), 0.6, fused_rows=True)
+        every = np.tile(np.arange(N, dtype=np.uint32), (T, 1))
+        m.gather(idx_to_dev(every), every)
+        m.update(ci, (rng.random((T, 200)) * 2).astype(np.float32))
+        m.compare_tree()
+    m.compare_status()
+
+
 # ---------------------------------------------------------------------------------------------
 # per_run_requests: a queue of op-coded requests in one launch.  Same results as the calls, in queue order.
 # ---------------------------------------------------------------------------------------------
