@@ -33,11 +33,9 @@ struct SubLevels {
 //     workgroup finishes last.  No workgroup ever waits for another.  When there are only a
 //     few nodes at height hb this step is skipped (chain == 0): the agent-scope fences it
 //     needs cost more than recomputing those heights in the next kernel that reads them.
-constexpr uint32_t kDirtyListCap = 2048;
-// Largest hb that tree_pass_height can give a fanout: the whole tree when it has at most kDirtyListCap
-// height-1 nodes (H <= 1 + ceil(log_K 2048)), else the lowest height whose subtrees hold 64 of them.
+// Largest hb that tree_pass_height can give a fanout.
 template <int LOGK>
-constexpr int kMaxPassHeight = LOGK == 1 ? 13 : LOGK == 2 ? 7 : LOGK == 3 ? 5 : LOGK <= 5 ? 4 : 3;
+constexpr int kMaxPassHeight = LOGK == 1 ? 13 : LOGK == 2 ? 4 : LOGK <= 5 ? 3 : 2;
 
 // The batch itself, for a tree pass over a batch that claimed in runs (see claim_run).
 struct BatchRef {
@@ -533,8 +531,14 @@ k_tree_finish(Geom g, SubLevels sl, uint32_t chain, uint32_t tree_blocks, FieldT
 // Height of the workgroup roots of the tree pass: the whole tree for small trees, else the
 // lowest height whose subtrees hold at least 64 height-1 nodes (so that dirty words are never
 // shared between workgroups).
+// The lowest height whose subtrees hold 64 height-1 nodes, or the root of a tree of no more of them: the pass works
+// through a subtree's claimed nodes a few at a time, a trip to memory each, and what lies above is left to the next
+// sampling call, which has the top of the tree in LDS anyway.  (A tree of up to 2048 height-1 nodes as one subtree: 512
+// elements on 100 000 leaves at K = 64 took 11.3 us, 3.7 so; a step of 1024 on 30 000 at K = 16, insertion of 16 rows now
+// carried by the sampling, 21.5 and 12.3; 64 such trees 40.9 and 32.5.)  Not at K = 2, where the many heights to rebuild
+// cost the sampling as much as the pass gains: a step of 64 on 4096 leaves 13.5 us as one subtree, 14.7 as 32.
 static uint32_t tree_pass_height(const Geom& g) {
-  if (g.n[1] <= kDirtyListCap) return g.H;
+  if (g.n[1] <= (g.logK == 1 ? 2048u : 64u)) return g.H;
   uint32_t hb = 1;
   while (hb < g.H && (1ull << ((hb - 1) * g.logK)) < 64) ++hb;
   return hb;

@@ -1299,6 +1299,24 @@ def test_insertions_of_many_rows(K, N, T, fb, sizes, norm):
     m.compare_status()
 
 
+@pytest.mark.parametrize("K", (2, 4, 8, 16, 32, 64))
+@pytest.mark.parametrize("extra", (0, 1))
+def test_smallest_trees_of_several_subtrees(K, extra):
+    """Trees of 64 height-1 nodes are one subtree of the tree pass, those of one more node (at K = 2: of 2048) several."""
+    N, T, B = (2048 if K == 2 else 64) * K + extra, 2, 150
+    log(f"subtrees K={K} N={N}")
+    rng = np.random.default_rng(N)
+    m = Mirror(K, N, T, (16, 5))
+    m.insert(N, prio=wl._draw_priorities("lognormal_0_1", rng, (T, N)))
+    for r in range(4):
+        m.insert(3, prio=(rng.random((T, 3)) * 4).astype(np.float32) if r % 2 else None)
+        gi, ci = m.sample(wl.uniform01(rng, (T, B)), 0.5, fused_rows=True)
+        m.update(ci, wl._draw_priorities("lognormal_0_1", rng, (T, B)))
+        if r % 2:
+            m.compare_tree()
+    m.compare_status()
+
+
 # ---------------------------------------------------------------------------------------------
 # per_run_requests: a queue of op-coded requests in one launch.  Same results as the calls, in queue order.
 # ---------------------------------------------------------------------------------------------
