@@ -10,8 +10,9 @@
 // of its reduction, so the companion structure need not mirror the sum tree: min1 holds the
 // minimum under every height-1 node, kept current by the kernels that rewrite leaves of few nodes (the
 // update's tree pass, small inserts); everything else marks it stale on the host and k_min_rebuild
-// recomputes it from the leaves when it is next needed.  k_min_reduce folds min1 into a few partial
-// minima per tree before a sampling call that wants it.
+// recomputes it from the leaves when it is next needed.  min_job folds min1 into a few partial minima per
+// tree: in workgroups of the sampling kernel of a call that wants it (whose weights are then a job of the kernel behind
+// it; as a kernel in front of it the reduction took 2.9 us of the device and 4 of the host), or in k_min_reduce.
 
 // min1 of every height-1 node from its K leaves; LPS lanes per node.
 template <int LOGK>
@@ -31,18 +32,16 @@ k_min_rebuild(Geom g) {
   }
 }
 
-// vmin_buf[t][b] = minimum of the part of min1 of tree t that workgroup b has swept.  Plain stores, one
-// per workgroup, so nothing has to be armed beforehand; the readers fold the gridDim.x partial minima.
-__global__ void __launch_bounds__(256)
-k_min_reduce(Geom g) {
-  __shared__ uint32_t s_m[4];
-  const uint32_t t = blockIdx.y;
+// vmin_buf[t][b] = minimum of the part of min1 of tree t that workgroup b of `parts` has swept.  Plain stores, one
+// per workgroup, so nothing has to be armed beforehand; the readers fold the partial minima.
+__device__ __forceinline__ void min_job(const Geom& g, uint32_t t, uint32_t b, uint32_t parts) {
+  __shared__ uint32_t s_m[16];
   const uint32_t* min1 = g.min1 + (size_t)t * g.min1_stride;
   const uint32_t n1 = g.n[1];
   uint32_t m = kNoMin;
   // four entries per lane and load (the launch gives every lane one load for all but huge trees); the
   // entries beyond n1 up to the stride are not minima and are not read
-  const uint64_t lanes = (uint64_t)gridDim.x * blockDim.x, lane0 = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const uint64_t lanes = (uint64_t)parts * blockDim.x, lane0 = (uint64_t)b * blockDim.x + threadIdx.x;
   const uint32_t n4 = n1 / 4;
   const uint4* min4 = reinterpret_cast<const uint4*>(min1);
   for (uint64_t i = lane0; i < n4; i += lanes) {
@@ -53,8 +52,19 @@ k_min_reduce(Geom g) {
   m = wave_min_u32(m);
   if ((threadIdx.x & 63u) == 0) s_m[threadIdx.x >> 6] = m;
   __syncthreads();
-  if (threadIdx.x == 0)
-    g.vmin_buf[(size_t)t * kMinParts + blockIdx.x] = min_u32(min_u32(s_m[0], s_m[1]), min_u32(s_m[2], s_m[3]));
+  if (threadIdx.x == 0) {
+    for (uint32_t wv = 1; wv < (blockDim.x >> 6); ++wv) m = min_u32(m, s_m[wv]);
+    g.vmin_buf[(size_t)t * kMinParts + b] = m;
+  }
+}
+__global__ void __launch_bounds__(256)
+k_min_reduce(Geom g) {
+  min_job(g, blockIdx.y, blockIdx.x, gridDim.x);
+}
+// Workgroups of `block` lanes for that reduction.
+uint32_t min_parts(const Geom& g, uint32_t block) {
+  const uint64_t parts = ((uint64_t)g.n[1] + 4ull * block - 1) / (4ull * block);   // four entries per lane
+  return parts > kMinParts ? kMinParts : (uint32_t)parts;
 }
 
 template <int LOGK>
@@ -73,10 +83,9 @@ hipError_t launch_min_rebuild(const Geom& g, const Tuning& tn, hipStream_t s) {
 }
 
 hipError_t launch_min_reduce(const Geom& g, const Tuning& tn, uint32_t* weight_mode, hipStream_t s) {
-  uint64_t blocks = ((uint64_t)g.n[1] + 1023) / 1024;   // four entries per lane
-  if (blocks > kMinParts) blocks = kMinParts;
-  PER_LAUNCH(KID_MIN_REDUCE, k_min_reduce, dim3((unsigned)blocks, g.T), dim3(256), 0, s, g);
-  *weight_mode = kWeightBufferNorm | ((uint32_t)blocks << kWeightPartsShift);
+  const uint32_t blocks = min_parts(g, 256);
+  PER_LAUNCH(KID_MIN_REDUCE, k_min_reduce, dim3(blocks, g.T), dim3(256), 0, s, g);
+  *weight_mode = kWeightBufferNorm | (blocks << kWeightPartsShift);
   return hipGetLastError();
 }
 

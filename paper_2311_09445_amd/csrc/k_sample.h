@@ -222,6 +222,17 @@ k_sample(Geom g, TopCopy tc, uint32_t B, uint32_t size, float beta, const float*
     claim_job(g, t, c, blockIdx.x, claim_blocks);
     return;
   }
+  uint32_t front = claim_blocks;
+  if constexpr (!RIDE) {
+    if (weight_mode & kWeightMinHere) {   // then the workgroups of the whole tree's minimum
+      const uint32_t parts = weight_mode >> kWeightPartsShift;
+      if (blockIdx.x - front < parts) {
+        min_job(g, t, blockIdx.x - front, parts);
+        return;
+      }
+      front += parts;
+    }
+  }
   bool is_mover = false;
   uint32_t movers = 0;
   if constexpr (RIDE) {   // the last workgroups move the rows; the first of them also stores what the insertion changes in the tree
@@ -233,8 +244,9 @@ k_sample(Geom g, TopCopy tc, uint32_t B, uint32_t size, float beta, const float*
     }
     is_mover = blockIdx.x == first_mover;
   }
-  const uint32_t bx = blockIdx.x - claim_blocks;            // sampling workgroup number
-  const uint32_t sample_blocks = gridDim.x - claim_blocks - movers;
+  const uint32_t bx = blockIdx.x - front;                   // sampling workgroup number
+  const uint32_t sample_blocks = gridDim.x - front - movers;
+  const bool weights_here = sample_blocks == 1 && (RIDE || !(weight_mode & kWeightMinHere));   // (else the weights job of the kernel behind turns the values into weights)
 
   PER_TRACE_DECL;
   PER_MARK(0);
@@ -249,7 +261,7 @@ k_sample(Geom g, TopCopy tc, uint32_t B, uint32_t size, float beta, const float*
   // which buffer of partial batch minima this call fills (stable while this kernel runs: the weights job of
   // the call before has written it), fetched in that same trip
   uint32_t vbuf = 0;
-  const bool partial_minima = out_w && sample_blocks > 1;
+  const bool partial_minima = out_w && !weights_here;
   if (partial_minima) vbuf = read_word_with_the_loads(g.vnext + t);   // (its low bit; taken where it is used, so that nothing waits for the word here)
   // the new priority of this lane's sample and the running maximum, likewise
   float upd_v = 0.0f;
@@ -529,7 +541,7 @@ k_sample(Geom g, TopCopy tc, uint32_t B, uint32_t size, float beta, const float*
   if (active) {
     out_idx[o] = node;
     if (out_prio) out_prio[o] = val;
-    if (out_w && sample_blocks > 1) out_w[o] = val;   // (turned into the weight by the weights job)
+    if (out_w && !weights_here) out_w[o] = val;   // (turned into the weight by the weights job)
     least = min_u32(least, __float_as_uint(val));
   }
   if (!again) break;
@@ -549,7 +561,7 @@ k_sample(Geom g, TopCopy tc, uint32_t B, uint32_t size, float beta, const float*
   if (out_w) {
     // Importance weights need the batch minimum of the sampled values.
     const uint32_t m = wave_min_u32(least);
-    if (sample_blocks == 1) {   // the whole batch of this tree is in this block: finish here
+    if (weights_here) {   // the whole batch of this tree is in this block: finish here
       if (lane == 0) s_min[wave] = m;
       __syncthreads();
       uint32_t mm = 0x7F800000u;
@@ -766,6 +778,12 @@ static hipError_t launch_sample_k(const Geom& g, const Tuning& tn, uint32_t B, u
     gx = (uint32_t)(held() / g.T < 2 ? 2 : held() / g.T);   // (at least two: one workgroup alone finishes the weights of the block it holds)
     if (gx > blocks) gx = blocks;
   }
+  uint32_t parts = 0;
+  if (weight_mode & kWeightMinHere) {
+    if (ride) return hipErrorInvalidValue;
+    parts = min_parts(g, block);
+    weight_mode |= parts << kWeightPartsShift;
+  }
   size_t bytes = (size_t)sh.top_bytes + (size_t)waves * sh.wave_bytes;
   hipError_t e;
   int stale = -1;
@@ -814,7 +832,7 @@ static hipError_t launch_sample_k(const Geom& g, const Tuning& tn, uint32_t B, u
   do {                                                                                                                         \
     e = grant_lds<&k_sample<LOGK, false, LOOP>>(tn, bytes);                                                                    \
     if (e != hipSuccess) return e;                                                                                             \
-    PER_LAUNCH(KID_SAMPLE, (k_sample<LOGK, false, LOOP>), dim3(gx + claim_blocks, g.T), dim3(block), bytes, s, g, tc, B, size, \
+    PER_LAUNCH(KID_SAMPLE, (k_sample<LOGK, false, LOOP>), dim3(gx + claim_blocks + parts, g.T), dim3(block), bytes, s, g, tc, B, size, \
                beta, u, out_idx, out_prio, out_w, weight_mode, stale, claim_blocks, claim_here ? *claim : ClaimArgs{},         \
                claim_here ? claim_mode : (int)CLAIM_NONE, rng, NoRide{});                                                      \
   } while (0)
@@ -823,7 +841,7 @@ static hipError_t launch_sample_k(const Geom& g, const Tuning& tn, uint32_t B, u
   }
   e = hipGetLastError();
   if (e != hipSuccess) return e;
-  const bool finish_weights = out_w && gx > 1;
+  const bool finish_weights = out_w && (gx > 1 || parts);
   if (rows || claim) {   // fused call
     FinishArgs a{};
     a.B = B;
@@ -852,17 +870,6 @@ static hipError_t launch_sample_k(const Geom& g, const Tuning& tn, uint32_t B, u
   PER_LAUNCH(KID_WEIGHTS, k_weights, dim3((B + 255) / 256, g.T), dim3(256), 0, s, g, B, size, beta, out_w, weight_mode);
   return hipGetLastError();
 }
-
-#define PER_DISPATCH_LOGK(logK, CALL)            \
-  switch (logK) {                                \
-    case 1: return CALL(1);                      \
-    case 2: return CALL(2);                      \
-    case 3: return CALL(3);                      \
-    case 4: return CALL(4);                      \
-    case 5: return CALL(5);                      \
-    case 6: return CALL(6);                      \
-    default: return hipErrorInvalidValue;        \
-  }
 
 hipError_t launch_sample(const Geom& g, const Tuning& tn, uint32_t B, uint32_t size, float beta, const float* u,
                          const RngArgs& rng, uint32_t* out_idx, float* out_w, float* out_prio, uint32_t weight_mode,

@@ -44,16 +44,50 @@ struct BatchRef {
   uint32_t B;
 };
 struct NoBatch {};
-template <bool RUNS>
-using BatchParam = typename std::conditional<RUNS, BatchRef, NoBatch>::type;
+// A small batch that the tree pass claims itself (see gather_batch).
+struct SmallBatch {
+  ClaimArgs c;
+  uint32_t slots;        // of the table of claimed leaves: a power of two, at least twice the batch
+};
+template <bool RUNS, bool HERE = false>
+using BatchParam = typename std::conditional<HERE, SmallBatch, typename std::conditional<RUNS, BatchRef, NoBatch>::type>::type;
+
+// The claim phase of a small batch inside the tree pass: every workgroup reads the whole batch and takes the elements of
+// its own subtree into a table in LDS, keyed by leaf, where the latest valid element of a leaf wins by an LDS atomic; the
+// leaves' bits go into a word (two for K = 64) per height-1 node.  No stamps and no dirty bits in memory then, and no
+// kernel of its own: 512 temporal-difference errors on 100 000 leaves at K = 64, 5.2 us, 6.9 as two kernels.
+constexpr uint32_t kHereBatch = 2048;      // largest batch claimed so (the table has 12 bytes per slot, two slots per element)
+constexpr uint64_t kHereReads = 1u << 20;  // most elements read over all workgroups (2048 by 1024 of them: 10.5 us, 7.7 as two kernels; 1024: 6.2 and 7.6)
+struct LeafTable {
+  unsigned long long* last;   // element + 1, value bits
+  uint32_t* key;              // the leaf, or kNoLeaf
+  uint32_t slots;
+  static constexpr uint32_t kNoLeaf = 0xFFFFFFFFu;
+  __device__ __forceinline__ uint32_t first(uint32_t leaf) const { return (leaf * 0x9E3779B1u) >> (__builtin_clz(slots) + 1u); }
+  __device__ __forceinline__ void take(uint32_t leaf, uint32_t j, uint32_t vbits) const {
+    uint32_t h = first(leaf);
+    for (;;) {   // (the table is at most half full: a free slot comes)
+      const uint32_t was = atomicCAS(&key[h], kNoLeaf, leaf);
+      if (was == kNoLeaf || was == leaf) break;
+      h = (h + 1u) & (slots - 1u);
+    }
+    atomicMax(&last[h], ((unsigned long long)(j + 1u) << 32) | vbits);
+  }
+  __device__ __forceinline__ uint32_t value(uint32_t leaf) const {   // of a leaf that has been taken
+    uint32_t h = first(leaf);
+    while (key[h] != leaf) h = (h + 1u) & (slots - 1u);
+    return (uint32_t)last[h];
+  }
+};
 
 // The work of workgroup b of tree t (b = its subtree's root at height hb).  TRACK_MIN: also renew min1
 // (smallest positive leaf) of every rebuilt height-1 node; a compile-time choice, because even as a
 // never-taken branch that code cost the pass half a microsecond.
 // RUNS: the batch claimed in runs; an entry may stand for several elements, read from the batch.
-template <int LOGK, bool TRACK_MIN, bool RUNS = false>
+// HERE: the batch is claimed by this pass itself (see LeafTable).
+template <int LOGK, bool TRACK_MIN, bool RUNS = false, bool HERE = false>
 __device__ __forceinline__ void tree_job(const Geom& g, const SubLevels& sl, uint32_t t, uint32_t b, uint32_t chain,
-                                         BatchParam<RUNS> batch = BatchParam<RUNS>{}) {
+                                         BatchParam<RUNS, HERE> batch = BatchParam<RUNS, HERE>{}) {
   constexpr int K = Fan<LOGK>::K;
   constexpr int LPS = Fan<LOGK>::LPS;
   // dynamic LDS: the subtree's nodes, then the list of claimed height-1 nodes (see tree_lds_bytes)
@@ -62,6 +96,15 @@ __device__ __forceinline__ void tree_job(const Geom& g, const SubLevels& sl, uin
   uint32_t* s_list = reinterpret_cast<uint32_t*>(s_entry + sl.list_cap);
   uint32_t* s_bits = s_list + sl.list_cap;
   [[maybe_unused]] uint32_t* s_bits_hi = s_bits + sl.list_cap;   // K = 64 only
+  [[maybe_unused]] LeafTable table;
+  [[maybe_unused]] uint32_t* s_claimed = nullptr;   // HERE: claimed leaves of the subtree's height-1 nodes
+  if constexpr (HERE) {
+    table.slots = batch.slots;
+    const uint32_t words = (sl.lds_floats + 3u) / 4u * 4u + sl.list_cap * (LOGK == 6 ? 5u : 4u);   // (see tree_lds_bytes)
+    table.last = reinterpret_cast<unsigned long long*>(sub + (words + 1u) / 2u * 2u);
+    table.key = reinterpret_cast<uint32_t*>(table.last + table.slots);
+    s_claimed = table.key + table.slots;
+  }
   __shared__ uint32_t s_wave[16];
   __shared__ uint32_t s_last;
   const uint32_t hb = sl.hb;
@@ -85,7 +128,10 @@ __device__ __forceinline__ void tree_job(const Geom& g, const SubLevels& sl, uin
   uint2* owner = reinterpret_cast<uint2*>(g.owner) + (size_t)t * g.owner_stride;   // (value, stamp)
   // the K dirty bits of one height-1 node
   auto node_bits = [&](uint32_t node) -> unsigned long long {
-    if constexpr (LOGK == 6) {
+    if constexpr (HERE) {
+      const uint32_t i = node - lo1;
+      return LOGK == 6 ? ((unsigned long long)s_claimed[2 * i + 1] << 32) | s_claimed[2 * i] : s_claimed[i];
+    } else if constexpr (LOGK == 6) {
       const uint2 w = *reinterpret_cast<const uint2*>(dirty + 2 * (size_t)node);
       return ((unsigned long long)w.y << 32) | w.x;
     } else if constexpr (LOGK == 5) {
@@ -99,7 +145,7 @@ __device__ __forceinline__ void tree_job(const Geom& g, const SubLevels& sl, uin
   // (value bits, 0x80000000 | leaf within the node), else y = 0
   uint2* groups = g.nclaim + (size_t)t * g.nclaim_stride;
   // first stamp of this batch, left by its claim phase (a batch that claimed leaf by leaf has no entries)
-  const uint32_t floor = sl.group_batch ? read_word_with_the_loads(g.sfloor + t) : 0xFFFFFFFFu;
+  const uint32_t floor = !HERE && sl.group_batch ? read_word_with_the_loads(g.sfloor + t) : 0xFFFFFFFFu;
   // (fetched here, decoded there: the comparison would make the wave wait for the entry, and the floor, before it
   // issues the loads that follow)
   auto fetch_entry = [&](uint32_t node) -> uint2 { return groups[LOGK >= 5 ? node : (node << LOGK) >> 5]; };
@@ -117,7 +163,30 @@ __device__ __forceinline__ void tree_job(const Geom& g, const SubLevels& sl, uin
   const uint32_t f_first = lo1 + threadIdx.x;
   unsigned long long bits_first = 0;
   uint2 entry_first = make_uint2(0, 0);
-  if (f_first < hi1) {
+  // HERE: the batch, four elements per lane under way at a time
+  [[maybe_unused]] uint32_t el_i[HERE ? 4 : 1];
+  [[maybe_unused]] float el_v[HERE ? 4 : 1];
+  [[maybe_unused]] uint32_t max_seen = 0;
+  [[maybe_unused]] auto fetch_elements = [&](uint32_t first) {
+    if constexpr (HERE) {
+#pragma unroll
+      for (uint32_t k = 0; k < 4; ++k) {
+        const uint32_t j = first + k * blockDim.x + threadIdx.x;
+        const size_t o = (size_t)t * batch.c.B + (j < batch.c.B ? j : 0u);
+        el_i[k] = batch.c.idx[o];
+        el_v[k] = batch.c.prio[o];
+      }
+    }
+  };
+  if constexpr (HERE) {
+    fetch_elements(0);
+    max_seen = read_max_bits(g, t);
+    for (uint32_t i = threadIdx.x; i < table.slots; i += blockDim.x) {
+      table.key[i] = LeafTable::kNoLeaf;
+      table.last[i] = 0;
+    }
+    for (uint32_t i = threadIdx.x; i < sl.list_cap * (LOGK == 6 ? 2u : 1u); i += blockDim.x) s_claimed[i] = 0;
+  } else if (f_first < hi1) {
     bits_first = node_bits(f_first);
     entry_first = fetch_entry(f_first);
   }
@@ -138,6 +207,37 @@ __device__ __forceinline__ void tree_job(const Geom& g, const SubLevels& sl, uin
     for (uint32_t i = threadIdx.x + 4 * blockDim.x; i < sl.lds_floats; i += blockDim.x)
       sub[i] = from_memory(i) ? lvl1[lo1 + i] : 0.0f;
   }
+  [[maybe_unused]] uint32_t batch_max = 0, batch_flags = 0;
+  if constexpr (HERE) {
+    __syncthreads();   // (the table is clear)
+    const uint32_t sh = hb * LOGK;
+    for (uint32_t first = 0; first < batch.c.B; first += 4 * blockDim.x) {
+      if (first) fetch_elements(first);
+#pragma unroll
+      for (uint32_t k = 0; k < 4; ++k) {
+        const uint32_t j = first + k * blockDim.x + threadIdx.x, i = el_i[k];
+        if (j >= batch.c.B) continue;
+        if (!(i < batch.c.size)) {
+          if (b == 0) batch_flags |= 1u;   // (of no subtree: reported once)
+        } else if ((uint32_t)((unsigned long long)i >> sh) == b) {
+          float v = el_v[k];
+          if (batch.c.from_td) v = (float)pow(fabs((double)v) + batch.c.td_eps, batch.c.td_alpha);
+          if (!valid_priority(v)) {
+            batch_flags |= 2u;
+          } else {
+            table.take(i, j, __float_as_uint(v));
+            const uint32_t in = i - (lo1 << LOGK);
+            if constexpr (LOGK == 6) atomicOr(&s_claimed[in >> 5], 1u << (in & 31u));
+            else atomicOr(&s_claimed[in >> LOGK], 1u << (in & (uint32_t)(K - 1)));
+            const uint32_t vb = v > 0.0f ? __float_as_uint(v) : 0u;
+            batch_max = vb > batch_max ? vb : batch_max;
+          }
+        }
+      }
+    }
+    __syncthreads();
+    if (f_first < hi1) bits_first = node_bits(f_first);
+  }
   // compact the claimed nodes into s_list / s_bits / s_entry: ballot within the wave, wave totals through LDS
   const uint32_t nwaves = blockDim.x >> 6;
   uint32_t nd = 0;
@@ -150,9 +250,9 @@ __device__ __forceinline__ void tree_job(const Geom& g, const SubLevels& sl, uin
       entry = entry_first;
     } else if (f < hi1) {
       bits = node_bits(f);
-      entry = fetch_entry(f);
+      if constexpr (!HERE) entry = fetch_entry(f);
     }
-    entry = decode_entry(entry, f);
+    if constexpr (!HERE) entry = decode_entry(entry, f);
     if (!(f < hi1)) entry.y = 0;
     const bool listed = bits != 0 || entry.y != 0;
     const unsigned long long m = __ballot(listed);
@@ -226,7 +326,10 @@ __device__ __forceinline__ void tree_job(const Geom& g, const SubLevels& sl, uin
 #pragma unroll
         for (int k = 0; k < (LOGK == 1 ? 2 : 4); ++k) {
           it.s[k] = make_uint2(0, 0);
-          if (it.my & (1u << k)) it.s[k] = owner[it.at + k];
+          if (it.my & (1u << k)) {
+            if constexpr (HERE) it.s[k].x = table.value((uint32_t)it.at + k);
+            else it.s[k] = owner[it.at + k];
+          }
         }
       }
       return it;
@@ -406,7 +509,11 @@ __device__ __forceinline__ void tree_job(const Geom& g, const SubLevels& sl, uin
   // The dirty bits and the stamps of the dirty leaves are cleared again (both arrays are all zero between
   // batches).  Only now: a wait for loaded data also waits for every earlier store of the wave, so
   // stores that nothing depends on go last.
-  for (uint32_t i = threadIdx.x; i < nd; i += blockDim.x) {
+  if constexpr (HERE) {
+    raise_max(g, t, batch_max, max_seen);
+    if (batch_flags) atomicOr(&g.status[t], batch_flags);
+  }
+  for (uint32_t i = threadIdx.x; !HERE && i < nd; i += blockDim.x) {
     const uint32_t node = s_list[i];
     unsigned long long bits = s_bits[i];
     if constexpr (LOGK == 6) bits |= (unsigned long long)s_bits_hi[i] << 32;
@@ -425,7 +532,7 @@ __device__ __forceinline__ void tree_job(const Geom& g, const SubLevels& sl, uin
   }
   // The stamp counter of the group entries: the next batch starts after this one; when that is beyond the
   // turning point, every workgroup clears the entries of its subtree instead and the counter starts over.
-  if (sl.group_batch) {
+  if (!HERE && sl.group_batch) {
     const bool turn = floor + sl.group_batch > kGroupStampTurn;   // (uniform over the launch)
     if (turn) {
       const uint32_t e_lo = LOGK >= 5 ? lo1 : (lo1 << LOGK) >> 5;
@@ -474,11 +581,11 @@ __device__ __forceinline__ void fold_pending_max(const Geom& g, uint32_t t, uint
 // stays within an eighth of the SIMD's scalar and vector registers (with one scalar register more the
 // second workgroup waits for the first to end and the kernel takes half as long again), and holding
 // the compiler to that budget made it spill; 512 lanes run the pass just as fast.
-template <int LOGK, bool TRACK_MIN, bool RUNS>
+template <int LOGK, bool TRACK_MIN, bool RUNS, bool HERE>
 __global__ void __launch_bounds__(512)
-k_update_tree(Geom g, SubLevels sl, uint32_t chain, BatchParam<RUNS> batch) {
+k_update_tree(Geom g, SubLevels sl, uint32_t chain, BatchParam<RUNS, HERE> batch) {
   const uint32_t pend = (chain & 2u) && blockIdx.x == 0 ? read_word_with_the_loads(&g.max_pend[blockIdx.y]) : 0u;
-  tree_job<LOGK, TRACK_MIN, RUNS>(g, sl, blockIdx.y, blockIdx.x, chain & 1u, batch);
+  tree_job<LOGK, TRACK_MIN, RUNS, HERE>(g, sl, blockIdx.y, blockIdx.x, chain & 1u, batch);
   if ((chain & 2u) && blockIdx.x == 0) fold_pending_max(g, blockIdx.y, pend);
 }
 
@@ -633,7 +740,7 @@ static hipError_t launch_tree_k(const Geom& g, const Tuning& tn, const ClaimArgs
   if (tblock > 512) tblock = 512;
   const uint32_t chain = (lazy_top_height(g, tn) ? 0u : 1u) | (c.fold_max ? 2u : 0u);
 #define PER_UPDATE_TREE(TM, RN, BATCH)                                                                                     \
-  PER_LAUNCH(KID_UPDATE_TREE, (k_update_tree<LOGK, TM, RN>), dim3(g.n[sl.hb], g.T), dim3(tblock), tree_lds_bytes<LOGK>(sl), s, \
+  PER_LAUNCH(KID_UPDATE_TREE, (k_update_tree<LOGK, TM, RN, false>), dim3(g.n[sl.hb], g.T), dim3(tblock), tree_lds_bytes<LOGK>(sl), s, \
              g, sl, chain, BATCH)
   const BatchRef batch{c.idx, c.prio, c.B};
   if (c.runs) {
@@ -642,6 +749,33 @@ static hipError_t launch_tree_k(const Geom& g, const Tuning& tn, const ClaimArgs
     if (c.track_min) { PER_UPDATE_TREE(true, false, NoBatch{}); } else { PER_UPDATE_TREE(false, false, NoBatch{}); }
   }
 #undef PER_UPDATE_TREE
+  return hipGetLastError();
+}
+
+// The update of a small batch as one kernel.
+template <int LOGK>
+static hipError_t launch_update_here_k(const Geom& g, const Tuning& tn, ClaimArgs c, hipStream_t s) {
+  SubLevels sl;
+  uint32_t tblock;
+  c.group_mode = 0;
+  hipError_t e = tree_pass_shape<LOGK>(g, tn, c, &sl, &tblock);
+  if (e != hipSuccess) return e;
+  SmallBatch batch{c, 64};
+  while (batch.slots < 2 * c.B) batch.slots *= 2;
+  uint32_t want = (c.B + 255) / 256 * 64;   // (the batch in one sweep of four elements per lane)
+  if (want > tblock && !tn.tree_block) tblock = want;
+  if (tblock > 512) tblock = 512;
+  const uint32_t chain = lazy_top_height(g, tn) ? 0u : 1u;
+  const size_t words = sl.list_cap * (LOGK == 6 ? 2u : 1u);
+  const size_t lds = tree_lds_bytes<LOGK>(sl) + 4 + (size_t)batch.slots * 12 + words * 4;
+#define PER_UPDATE_HERE(TM)                                                                                               \
+  do {                                                                                                                    \
+    e = grant_lds<&k_update_tree<LOGK, TM, false, true>>(tn, lds);                                                        \
+    if (e != hipSuccess) return e;                                                                                        \
+    PER_LAUNCH(KID_UPDATE_TREE, (k_update_tree<LOGK, TM, false, true>), dim3(g.n[sl.hb], g.T), dim3(tblock), lds, s, g, sl, chain, batch); \
+  } while (0)
+  if (c.track_min) PER_UPDATE_HERE(true); else PER_UPDATE_HERE(false);
+#undef PER_UPDATE_HERE
   return hipGetLastError();
 }
 
@@ -677,6 +811,9 @@ static hipError_t launch_tree_finish_k(const Geom& g, const Tuning& tn, const Cl
 template <int LOGK>
 static hipError_t launch_update_k(const Geom& g, const Tuning& tn, ClaimArgs c, hipStream_t s) {
   const uint32_t block = tn.update_block;
+  if (c.group_mode && tn.claim_in_sample && !c.pos && c.B <= kHereBatch &&
+      (uint64_t)g.n[tree_pass_height(g)] * g.T * c.B <= kHereReads)
+    return launch_update_here_k<LOGK>(g, tn, c, s);
   // In runs where that pays: plain priorities, a quarter of an element per group of 32 leaves on the average.  Where the
   // tree pass has fewer subtrees than the device has compute units, its reading of the runs weighs more, and an element
   // per group is the break-even (2^22 leaves at K = 32, 84 609 elements: both kernels 15.3 us leaf by leaf, 17.3 in runs;

@@ -168,13 +168,16 @@ bool tracks_min(const per_t* p) { return p->weight_norm == PER_NORM_BUFFER && !p
 
 // Brings vmin_buf up to date for a reader: min1 from the leaves if it is stale, then its reduction.  Returns the
 // weight mode that tells the reader where the result is.
-hipError_t reduce_min(per_t* p, hipStream_t s, uint32_t* weight_mode) {
+// `here`: the reduction itself is left to the sampling kernel.
+hipError_t reduce_min(per_t* p, hipStream_t s, uint32_t* weight_mode, bool here = false) {
   if (p->min_stale) {
     hipError_t e = launch_min_rebuild(p->g, p->tn, s);
     if (e != hipSuccess) return e;
     p->min_stale = false;
   }
-  return launch_min_reduce(p->g, p->tn, weight_mode, s);
+  if (!here) return launch_min_reduce(p->g, p->tn, weight_mode, s);
+  *weight_mode = kWeightBufferNorm | kWeightMinHere;
+  return hipSuccess;
 }
 
 // Rebuilds the heights an update left stale, for readers that take them from memory.
@@ -494,7 +497,7 @@ static int sample_impl(per_t* p, uint32_t B, float beta, const float* d_u, uint3
   }
   uint32_t weight_mode = 0;
   if (d_out_weight && p->weight_norm == PER_NORM_BUFFER &&   // the weights refer to the tree as it is before this call's update
-      reduce_min(p, s, &weight_mode) != hipSuccess)
+      reduce_min(p, s, &weight_mode, !step_block) != hipSuccess)
     return PER_EHIP;
   if (step_block) {
     RngArgs rng{};

@@ -73,6 +73,7 @@ constexpr uint32_t kNoMin = 0x7F800000u;   // fp32 bits of +inf: above every val
 // smallest sampled value; else kWeightBufferNorm | (number of partial minima in vmin_buf << kWeightPartsShift) =
 // by the smallest positive leaf of the whole tree.
 constexpr uint32_t kWeightBufferNorm = 1u;
+constexpr uint32_t kWeightMinHere = 2u;   // the sampling kernel makes those partial minima itself, for the weights job behind it
 constexpr uint32_t kWeightPartsShift = 8u;
 
 // Payload.  Stored row-major: the fields of a row lie side by side (a row of several fields is then one or
@@ -251,6 +252,7 @@ struct Tuning {
 hipError_t launch_fill_u32(const Tuning& tn, uint32_t* p, uint64_t count, uint32_t value, hipStream_t s);
 hipError_t launch_init_scalars(const Geom& g, float init_max, hipStream_t s);
 hipError_t launch_min_rebuild(const Geom& g, const Tuning& tn, hipStream_t s);
+uint32_t min_parts(const Geom& g, uint32_t block);
 hipError_t launch_min_reduce(const Geom& g, const Tuning& tn, uint32_t* weight_mode, hipStream_t s);
 hipError_t static_scratch_address(int device, uint32_t** out);   // the static array of per_min_priority_static on `device` (which must be current)
 hipError_t launch_sample(const Geom& g, const Tuning& tn, uint32_t B, uint32_t size, float beta, const float* u,

@@ -91,10 +91,22 @@ static hipError_t grant_lds(const Tuning& tn, size_t bytes) {
   return e;
 }
 
+#define PER_DISPATCH_LOGK(logK, CALL)            \
+  switch (logK) {                                \
+    case 1: return CALL(1);                      \
+    case 2: return CALL(2);                      \
+    case 3: return CALL(3);                      \
+    case 4: return CALL(4);                      \
+    case 5: return CALL(5);                      \
+    case 6: return CALL(6);                      \
+    default: return hipErrorInvalidValue;        \
+  }
+
 #include "dev_trace.h"
 #include "dev_common.h"
 #include "k_scalars.h"
 #include "k_claim.h"
+#include "k_min.h"
 #include "k_sample.h"
 #include "k_rows.h"
 #include "k_resum.h"
@@ -105,6 +117,5 @@ static hipError_t grant_lds(const Tuning& tn, size_t bytes) {
 #include "k_delta.h"
 #include "k_stream.h"
 #include "k_retrieve.h"
-#include "k_min.h"
 
 }  // namespace per

@@ -1317,6 +1317,30 @@ def test_smallest_trees_of_several_subtrees(K, extra):
     m.compare_status()
 
 
+@pytest.mark.parametrize("K,N,T", [(2, 5000, 1), (4, 70001, 2), (8, 513, 3), (16, 70001, 1), (32, 150001, 1), (64, 64, 1), (64, 70001, 2), (16, 1 << 20, 1)])
+@pytest.mark.parametrize("norm", ["batch", "buffer"])
+def test_small_batches_claimed_in_the_tree_pass(K, N, T, norm):
+    """Updates of up to 2048 elements (and one more): many elements for few leaves in no order, indices and values that are
+    not valid, the whole batch in one subtree; weights relative to the whole buffer made beside the sampling."""
+    log(f"small batches K={K} N={N} T={T} {norm}")
+    rng = np.random.default_rng(N + K)
+    m = Mirror(K, N, T, (5,))
+    m.gpu.set_weight_norm(norm)
+    m.cpu.set_weight_norm(norm)
+    m.insert(N, prio=wl._draw_priorities("lognormal_0_1", rng, (T, N)))
+    for r, B in enumerate((1, 64, 65, 500, 2047, 2048, 2049)):
+        idx = rng.integers(0, N if r % 2 else min(N, 40), (T, B)).astype(np.uint32)
+        prio = (rng.random((T, B)) * 4).astype(np.float32)
+        if r > 1:
+            idx[:, ::9] = N + rng.integers(0, 100)
+            prio[:, 1::11] = np.float32("nan")
+            prio[:, 2::13] = 0.0
+        m.update(idx, prio)
+        m.compare_tree()
+        m.sample(wl.uniform01(rng, (T, 33 + 900 * (r % 2))), 0.5, fused_rows=bool(r % 3))
+    m.compare_status()
+
+
 # ---------------------------------------------------------------------------------------------
 # per_run_requests: a queue of op-coded requests in one launch.  Same results as the calls, in queue order.
 # ---------------------------------------------------------------------------------------------
