@@ -113,9 +113,10 @@ __device__ __forceinline__ void place_whole_rows(const FieldTable& ft, uint32_t 
     }
   }
 }
-// Rows of a pass, or 0 where rows are not stored whole.
+// Rows of a pass, or 0 where rows are not stored whole: where a stored row is no longer than a cache line, the parts of a
+// line come close enough after each other (2^20 rows of 25 bytes: 33 us a job per field, 72 whole; of 41 bytes 68 and 72).
 static uint32_t place_rows(const FieldTable* ft, uint64_t rows) {
-  if (!ft || rows < kPlaceRowsFrom || ft->n_fields < 2) return 0;
+  if (!ft || rows < kPlaceRowsFrom || ft->n_fields < 2 || ft->row_stride <= 128) return 0;
   for (uint32_t f = 0; f < ft->n_fields; ++f)
     if (!ft->io[f]) return 0;
   uint32_t R = kPlaceLds / ft->row_stride / 16u * 16u;
