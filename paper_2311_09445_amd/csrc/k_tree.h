@@ -814,12 +814,12 @@ static hipError_t launch_update_k(const Geom& g, const Tuning& tn, ClaimArgs c, 
   if (c.group_mode && tn.claim_in_sample && !c.pos && c.B <= kHereBatch &&
       (uint64_t)g.n[tree_pass_height(g)] * g.T * c.B <= kHereReads)
     return launch_update_here_k<LOGK>(g, tn, c, s);
-  // In runs where that pays: plain priorities, a quarter of an element per group of 32 leaves on the average.  Where the
-  // tree pass has fewer subtrees than the device has compute units, its reading of the runs weighs more, and an element
-  // per group is the break-even (2^22 leaves at K = 32, 84 609 elements: both kernels 15.3 us leaf by leaf, 17.3 in runs;
-  // 262 144: 31.7 and 23.4).
-  const bool few = (uint64_t)g.n[tree_pass_height(g)] * g.T < 256;
-  c.runs = c.group_mode && !c.from_td && !c.pos && (uint64_t)c.B * (few ? 32u : 128u) >= g.N ? 1u : 0u;
+  // In runs where that pays: plain priorities, a quarter of an element per group of 32 leaves on the average, and enough
+  // elements in all for the rate of the atomics to count, below which the tree pass's reading of the runs weighs more,
+  // at K = 32 with its large subtrees longest (2^20 leaves at K = 16: 43 000 elements 8.7 us leaf by leaf and 8.9 in runs,
+  // 65 536 11.4 and 9.5; at K = 32 65 536 18.3 and 21.1, 262 144 48 and 47; 2^24 leaves there 93.8 and 38.4 for 2^20).
+  c.runs = c.group_mode && !c.from_td && !c.pos && (uint64_t)c.B * 128u >= g.N &&
+           (uint64_t)c.B * g.T >= (LOGK == 5 ? 3u << 16 : 1u << 16) ? 1u : 0u;
   if (c.runs) {
     PER_LAUNCH(KID_UPDATE_CLAIM, k_update_claim<true>, dim3((c.B + block - 1) / block, g.T), dim3(block), 0, s, g, c);
   } else {
