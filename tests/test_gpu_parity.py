@@ -1268,8 +1268,8 @@ def test_updates_claimed_in_runs(K, N, T, norm):
 
 @pytest.mark.parametrize("K,N,T,fb,sizes", [
     (2, 3001, 1, (16, 4, 4, 16, 1), (17, 1500, 3001, 1)), (4, 70001, 1, (5,), (18, 333, 20000)), (8, 50001, 2, (68, 24, 4, 68, 1), (1, 700, 50001)),
-    (16, 70001, 3, (68, 24, 4, 68, 1), (15, 4097, 47000, 69999)), (32, 150001, 1, (5, 68, 2), (31, 33000, 140001)),
-    (64, 70001, 2, (128, 16), (63, 66000, 9)), (16, 9, 2, (3,), (1, 9, 8)), (8, 1 << 16, 2, (128,), (65, 65536))])
+    (16, 70001, 3, (68, 24, 4, 68, 1), (15, 4097, 47000, 69999)), (32, 150001, 1, (5, 129, 2), (31, 33000, 140001)),
+    (64, 70001, 2, (128, 16, 3), (63, 66000, 9)), (16, 9, 2, (3,), (1, 9, 8)), (8, 1 << 16, 2, (128,), (65, 65536))])
 @pytest.mark.parametrize("norm", ["batch", "buffer"])
 def test_insertions_of_many_rows(K, N, T, fb, sizes, norm):
     """The kernel of large insertions at the edges of nodes, subtrees and passes: windows inside a node, over the ring's end,
@@ -1299,11 +1299,12 @@ def test_insertions_of_many_rows(K, N, T, fb, sizes, norm):
     m.compare_status()
 
 
-@pytest.mark.parametrize("K", (2, 4, 8, 16, 32, 64))
-@pytest.mark.parametrize("extra", (0, 1))
-def test_smallest_trees_of_several_subtrees(K, extra):
-    """Trees of 64 height-1 nodes are one subtree of the tree pass, those of one more node (at K = 2: of 2048) several."""
-    N, T, B = (2048 if K == 2 else 64) * K + extra, 2, 150
+@pytest.mark.parametrize("K,N", [(K, (2048 if K == 2 else 64) * K + extra) for K in (2, 4, 8, 16, 32, 64) for extra in (0, 1)] +
+                         [(2, 4096 * 128 + 1), (2, 4096 * 512 + 1), (4, 4096 * 256 + 1), (8, 4096 * 512 + 1)])
+def test_subtrees_of_the_tree_pass(K, N):
+    """Trees of 64 height-1 nodes are one subtree of the tree pass, those of one more node (at K = 2: of 2048) several; on
+    tall trees the subtrees grow where there would be more than 4096 of them."""
+    T, B = 2, 150
     log(f"subtrees K={K} N={N}")
     rng = np.random.default_rng(N)
     m = Mirror(K, N, T, (16, 5))
