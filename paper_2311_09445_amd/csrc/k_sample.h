@@ -650,13 +650,15 @@ struct SampleShape {
   TopCopy tc;
   uint32_t waves, wave_bytes, top_bytes;
 };
-static SampleShape sample_shape(const Geom& g, const Tuning& tn, uint32_t B, uint32_t stale_hb, bool carries_insert = false, bool loop = false) {
+static SampleShape sample_shape(const Geom& g, const Tuning& tn, uint32_t B, uint32_t stale_hb, bool weights_behind, bool carries_insert = false, bool loop = false) {
   constexpr uint32_t kLdsCap = 128 * 1024;
   SampleShape sh{};
   const uint32_t K = g.K;
   sh.wave_bytes = g.logK < 3 ? 0u : 64u * (loop ? stage_row_floats(g.logK) : K + 4u) * 4u;   // staging per wave
-  // workgroup size: the whole batch in one workgroup when it is small (the weights are then finished
-  // in-kernel), else the configured size; bounded by the LDS the staging rows need
+  // workgroup size: the configured size, or the whole batch in one workgroup when it is small and no kernel comes behind
+  // that could finish the weights (where one does, several workgroups are faster from the third wave on: a step of 1024
+  // samples on 2^20 leaves at K = 4 takes 20.8 us with one and 16.3 with eight, of 512 at K = 16 12.8 and 11.7);
+  // bounded by the LDS the staging rows need
   uint32_t max_waves = sh.wave_bytes ? (uint32_t)(kLdsCap / 2 / sh.wave_bytes) : 16u;
   if (max_waves > 16) max_waves = 16;
   if (max_waves < 1) max_waves = 1;
@@ -666,7 +668,7 @@ static SampleShape sample_shape(const Geom& g, const Tuning& tn, uint32_t B, uin
   // on one tree the small ones stay ahead).  Only when the size was not asked for.
   if (carries_insert && tn.sample_block_auto && g.T >= 8 && waves < 8) waves = 8;
   const uint32_t need = (B + 63) / 64;
-  if (need <= max_waves) waves = need;
+  if (need <= (weights_behind ? waves : max_waves)) waves = need;
   if (waves > max_waves) waves = max_waves;
   sh.waves = waves;
   const uint32_t block = waves * 64;
@@ -737,7 +739,7 @@ bool sample_can_carry_insert(const Geom& g, const Tuning& tn, uint32_t B, const 
       if (ft->io[f]) bytes += (uint64_t)n * ft->bytes[f];
   if (bytes > 256 * 1024) return false;
   // the top copy must reach down to the height the top is rebuilt from
-  const SampleShape sh = sample_shape(g, tn, B, hb, true);
+  const SampleShape sh = sample_shape(g, tn, B, hb, true, true);
   if (sh.tc.nslots == 0 || g.H - sh.tc.nslots > hb) return false;
   // the runs of the patch must fit the workgroup, and the patch its share of the LDS
   InsertRide rd{};
@@ -756,7 +758,7 @@ static hipError_t launch_sample_k(const Geom& g, const Tuning& tn, uint32_t B, u
                                   const float* u, const RngArgs& rng, uint32_t* out_idx, float* out_w,
                                   float* out_prio, uint32_t weight_mode, uint32_t stale_hb, const FieldTable* rows,
                                   const ClaimArgs* claim, int claim_mode, const InsertRide* ride, hipStream_t s) {
-  SampleShape sh = sample_shape(g, tn, B, stale_hb, ride != nullptr);
+  SampleShape sh = sample_shape(g, tn, B, stale_hb, rows || claim, ride != nullptr);
   // No more workgroups than the device holds at once (their staging rows fill its LDS): they take further blocks of
   // samples in turn, with the top of the tree in place and the next uniforms under way, where workgroups of a second
   // round would begin with their arguments and the top of the tree again, two of the five trips to memory of a block.
@@ -768,7 +770,7 @@ static hipError_t launch_sample_k(const Geom& g, const Tuning& tn, uint32_t B, u
     return 256 * (n < 1 ? 1 : n);
   };
   const bool loop = !ride && (uint64_t)((B + sh.waves * 64 - 1) / (sh.waves * 64)) * g.T > held();
-  if (loop) sh = sample_shape(g, tn, B, stale_hb, false, true);
+  if (loop) sh = sample_shape(g, tn, B, stale_hb, rows || claim, false, true);
   const TopCopy& tc = sh.tc;
   const uint32_t waves = sh.waves;
   const uint32_t block = waves * 64;
