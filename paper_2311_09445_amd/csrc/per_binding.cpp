@@ -57,7 +57,15 @@ uint32_t* u32(const at::Tensor* t) { return static_cast<uint32_t*>(address(t, at
 float* f32(PyObject* o) { return f32(tensor(o)); }
 uint32_t* u32(PyObject* o) { return u32(tensor(o)); }
 
-uint64_t count(PyObject* o) { return (uint64_t)tensor(o)->numel(); }
+// Number of elements; None is refused (where an argument may be left out, the caller asks for None first).
+uint64_t count(PyObject* o) {
+  const at::Tensor* t = tensor(o);
+  if (!t) {
+    PyErr_SetString(PyExc_TypeError, "expected a tensor, got None");
+    throw Raised{};
+  }
+  return (uint64_t)t->numel();
+}
 
 uint32_t whole(PyObject* o) {
   const unsigned long v = PyLong_AsUnsignedLong(o);
@@ -161,12 +169,13 @@ PyObject* do_sample(Calls* c, Args a, Py_ssize_t n_args) {
   uint32_t* idx = u32(a[2]);
   float *w = f32(a[3]), *v = f32(a[4]);
   Fields rows(c, a[5], B);
+  const bool update = a[7] != Py_None || a[8] != Py_None;
+  const uint64_t n = update ? count(a[7]) : 0;
+  if (update && (a[8] == Py_None || count(a[8]) != n)) raise_value("update idx and prio must have the same number of elements");
+  const uint32_t* ui = u32(a[7]);
+  const float* up = f32(a[8]);
   void* s = stream_of(c);
-  if (a[7] != Py_None) {
-    const uint64_t n = count(a[7]);
-    if (a[8] == Py_None || count(a[8]) != n) raise_value("update idx and prio must have the same number of elements");
-    const uint32_t* ui = u32(a[7]);
-    const float* up = f32(a[8]);
+  if (update) {
     return unlocked([&] { return per_sample_gather_update(c->h, B, beta, u, idx, w, v, rows.table, (uint32_t)(n / c->T), ui, up, s); });
   }
   if (!rows.table) return unlocked([&] { return per_sample(c->h, B, beta, u, idx, w, v, s); });
@@ -304,7 +313,9 @@ PyObject* do_run_steps(Calls* c, Args a, Py_ssize_t n_args) {
 template <PyObject* (*F)(Calls*, Args, Py_ssize_t)>
 PyObject* method(PyObject* self, Args a, Py_ssize_t n) {
   try {
-    return F(reinterpret_cast<Calls*>(self), a, n);
+    Calls* c = reinterpret_cast<Calls*>(self);
+    if (!c->h) raise_value("no buffer");   // (an object that __init__ has not been through)
+    return F(c, a, n);
   } catch (const Raised&) {
   } catch (const std::exception& e) {
     if (!PyErr_Occurred()) PyErr_SetString(PyExc_RuntimeError, e.what());

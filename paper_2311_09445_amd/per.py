@@ -265,6 +265,8 @@ class PrioritizedReplay:
         gathered by the same call (per_sample_gather).  With ``update=(idx, prio)`` that priority
         update is applied after the sampling, still in the same call (per_sample_gather_update)."""
         upd_idx, upd_prio = (None, None) if update is None else update
+        if update is not None and (upd_idx is None or upd_prio is None):
+            raise TypeError("update must be (idx, prio), both tensors")
         if out_idx is None or (want_weights and out_weight is None) or (want_prio and out_prio is None):
             out_idx, out_weight, out_prio = self._outputs(u, B, want_weights, want_prio, out_idx, out_weight, out_prio)
         if not want_weights:

@@ -99,6 +99,34 @@ def test_binding_fails_loudly_without_the_library(monkeypatch):
         per._lib()
 
 
+def test_calls_without_their_tensors_raise():
+    """None where a call needs a tensor: an exception, with no work enqueued (the handle is never looked at)."""
+    import torch
+    T = 2
+    calls = per._binding().Calls(0x1000, T, (4,), 0)
+    prio, u = torch.zeros(T * 3), torch.zeros(T * 3)
+    idx = torch.zeros(T * 3, dtype=torch.int32)
+    for bad in (lambda: calls.update(None, prio), lambda: calls.update(idx, None), lambda: calls.update(None, None),
+                lambda: calls.update_td(None, prio, 1e-6, 0.6), lambda: calls.update_td(idx, None, 1e-6, 0.6),
+                lambda: calls.update_delta(None, prio), lambda: calls.update_delta(idx, None),
+                lambda: calls.gather(None, [None]), lambda: calls.get_priority(None, prio),
+                lambda: calls.sample(None, 0.4, None, None, None, None, 3, None, prio),
+                lambda: calls.sample(None, 0.4, None, None, None, None, 3, idx, None),
+                lambda: calls.step(None, 0.4, None, None, None, None, None, None, 3, None),
+                lambda: calls.run_steps(None, None, None, None, None, None, None, None, 0, None, None),
+                lambda: calls.insert(None, None, None, None, None)):
+        with pytest.raises((TypeError, ValueError)):
+            bad()
+    unfinished = per._binding().Calls.__new__(per._binding().Calls)
+    with pytest.raises(ValueError):
+        unfinished.update(idx, prio)
+    buf = per.PrioritizedReplay.__new__(per.PrioritizedReplay)   # (no GPU: the checks in front of the call)
+    buf._calls = calls
+    for update in ((None, prio), (idx, None), (None, None)):
+        with pytest.raises(TypeError):
+            buf.sample(u, out_idx=idx, out_weight=prio, out_prio=prio, update=update)
+
+
 def test_workload_generator_is_seeded_and_exact():
     w = wl.WORKLOADS["c4_stress"]
     a = wl.step_inputs(w, 3, 0, B=1024)
