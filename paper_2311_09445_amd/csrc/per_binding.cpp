@@ -67,8 +67,12 @@ uint64_t count(PyObject* o) {
   return (uint64_t)t->numel();
 }
 
+// Counts may be any whole number (NumPy's are not Python ints).
 uint32_t whole(PyObject* o) {
-  const unsigned long v = PyLong_AsUnsignedLong(o);
+  PyObject* i = PyNumber_Index(o);
+  if (!i) throw Raised{};
+  const unsigned long v = PyLong_AsUnsignedLong(i);
+  Py_DECREF(i);
   if (v == (unsigned long)-1 && PyErr_Occurred()) throw Raised{};
   if (v > 0xFFFFFFFFul) {
     PyErr_SetString(PyExc_OverflowError, "count does not fit 32 bits");
@@ -76,9 +80,12 @@ uint32_t whole(PyObject* o) {
   }
   return (uint32_t)v;
 }
-double real(PyObject* o) {
-  const double v = PyFloat_AsDouble(o);
-  if (v == -1.0 && PyErr_Occurred()) throw Raised{};
+double real(PyObject* o) {   // as float(o)
+  if (PyFloat_CheckExact(o)) return PyFloat_AS_DOUBLE(o);
+  PyObject* f = PyNumber_Float(o);
+  if (!f) throw Raised{};
+  const double v = PyFloat_AS_DOUBLE(f);
+  Py_DECREF(f);
   return v;
 }
 
@@ -137,9 +144,7 @@ uint32_t batch(const Calls* c, PyObject* u, PyObject* B) {
     if (B == Py_None) raise_value("without uniforms the batch size B must be given");
     return whole(B);
   }
-  const uint64_t n = count(u);
-  if (n % c->T) raise_value("u must hold T*B values");
-  return (uint32_t)(n / c->T);
+  return (uint32_t)(count(u) / c->T);
 }
 
 using Args = PyObject* const*;
@@ -164,6 +169,7 @@ PyObject* do_insert(Calls* c, Args a, Py_ssize_t n_args) {
 PyObject* do_sample(Calls* c, Args a, Py_ssize_t n_args) {
   need(n_args, 9);
   const uint32_t B = batch(c, a[0], a[6]);
+  if (a[0] != Py_None && count(a[0]) != c->T * B) raise_value("u must hold T*B values");
   const float beta = (float)real(a[1]);
   const float* u = f32(a[0]);
   uint32_t* idx = u32(a[2]);

@@ -304,8 +304,8 @@ class PrioritizedReplay:
         """A list of steps (insert -> sample -> gather -> update) in one launch on an LDS copy of the tree.
         ``u``: [steps, T, B]; ``beta``: [steps] device tensor; the other arrays as in per.h (leading step
         dimension).  ``upd_prio`` without ``upd_idx`` updates, in every step, the batch just sampled."""
-        rc = self._calls.run_steps(u, beta, out_idx, out_weight, out_prio, rows_out, upd_prio, upd_idx, n_insert, ins_rows,
-                                   ins_prio)
+        rc = self._calls.run_steps(u, beta, out_idx, out_weight, out_prio, rows_out, upd_prio, upd_idx, int(n_insert),
+                                   ins_rows, ins_prio)
         if rc:
             self._check(rc, "per_run_steps")
 

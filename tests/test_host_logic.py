@@ -127,6 +127,30 @@ def test_calls_without_their_tensors_raise():
             buf.sample(u, out_idx=idx, out_weight=prio, out_prio=prio, update=update)
 
 
+@pytest.mark.parametrize("kind", [int, np.int64, np.uint32, np.int8])
+def test_counts_may_be_any_whole_number(kind):
+    """The count is taken when the check behind it speaks: sizes that do not fit, or a tensor that is not the device's."""
+    import torch
+    calls = per._binding().Calls(0x1000, 1, (4,), 0)
+    three, four = torch.zeros(3), torch.zeros(4)
+    idx = torch.zeros(3, dtype=torch.int32)
+    with pytest.raises(ValueError, match="prio must hold T\\*n values"):
+        calls.insert(kind(3), None, four, None, None)
+    with pytest.raises(ValueError, match="device tensor"):
+        calls.insert(kind(3), None, three, None, None)
+    with pytest.raises(ValueError, match="device tensor"):
+        calls.sample(None, 0.4, idx, None, None, None, kind(3), None, None)
+    with pytest.raises(ValueError, match="upd_prio and upd_pos must hold"):
+        calls.step(None, 0.4, four, None, idx, None, None, None, kind(3), None)
+    with pytest.raises(ValueError, match="ins_prio must hold"):
+        calls.run_steps(three.view(1, 1, 3), torch.zeros(1), idx, None, None, None, None, None, kind(2), None, four)
+    for bad in (3.5, "3", None):
+        with pytest.raises(TypeError):
+            calls.insert(bad, None, None, None, None)
+    with pytest.raises(OverflowError):
+        calls.insert(1 << 32, None, None, None, None)
+
+
 def test_workload_generator_is_seeded_and_exact():
     w = wl.WORKLOADS["c4_stress"]
     a = wl.step_inputs(w, 3, 0, B=1024)
