@@ -231,6 +231,10 @@ int per_update_delta(per_t* p, uint32_t B, const uint32_t* d_idx /*[T][B]*/, con
  *   d_upd_prio   : [steps][T][B] new tree values, or NULL: no update
  *   d_upd_idx    : [steps][T][B] indices to update; NULL with d_upd_prio given: step s updates the batch
  *                  it has just sampled
+ * A step may read what steps before it return (say, update the indices drawn one step earlier, where they were
+ * returned, or store the rows drawn), and its update what the step itself returns; the inputs of a step are then
+ * fetched only once those results are in memory (a step takes about 1 us more), where they otherwise travel a step
+ * ahead.  Each tree has a workgroup of its own, which waits for no other: what one tree returns must not be read for another.
  * n_insert <= 1024 (0: no insertion), 1 <= B <= 1024.  PER_ERANGE when the tree does not fit
  * (per_run_steps_fits tells beforehand) or a count is out of range. */
 typedef struct {
@@ -262,7 +266,8 @@ int per_run_steps_fits(const per_t* p);   /* 1: the trees of this buffer fit (wh
  *                   [T][n][bytes] of the gathered rows (NULL entries skipped)
  *   PER_OP_UPDATE : per_update of n elements: idx [T][n] (NULL: the indices sampled by the latest SAMPLE
  *                   request of this queue, whose n must be the same), prio [T][n]
- * with the results of those calls issued one after the other.  1 <= n <= 1024.  All pointers are
+ * with the results of those calls issued one after the other, also where a request reads what earlier ones return
+ * (for the same tree: see per_run_steps).  1 <= n <= 1024.  All pointers are
  * device pointers; a field pointer must be aligned to the largest power of two (at most 16) that
  * divides the field's row size.
  *   h_requests : HOST array of n_requests requests: the call checks the arguments on it and derives the

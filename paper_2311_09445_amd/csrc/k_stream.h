@@ -498,7 +498,9 @@ __device__ __forceinline__ void walk_tree(const TreeView<MEM>& tv, uint32_t i, u
 //  - The waves split: the first ones (the team, a lane per sample and per inserted row) do the tree work, the others
 //    move the rows and turn values into weights, one step behind.  Batches of more than 512 leave no waves over; the
 //    team then does both in turn.
-//  - Inputs are fetched a step ahead.
+//  - Inputs are fetched a step ahead.  That is only right where no step reads what a step returns; the host has checked
+//    it (StreamArgs::ahead).  Where it does not hold, a step's results are stored and waited for before its update and
+//    the inputs of the step behind it are fetched.
 //  - The update of step s and the insertion of step s + 1 are adjacent tree changes with nothing read in between: the
 //    leaves are written one after the other and the ancestors of both recomputed in one pass.
 //  - WAVE: with at most 64 samples and 64 new rows the team is one wave, whose LDS accesses stay in order by
@@ -559,12 +561,14 @@ k_run_steps(StreamKernelArgs ka) {
     if (ip.on) iv = load_piece(ip.dense, ip.w);
   }
   // inputs of the team: the uniform of the step to sample, value (and index) of the update to apply, inserted priority
-  float u_i = 0.0f, u_next = 0.0f, up_v = 0.0f, in_v = 0.0f;
+  float u_i = 0.0f, u_next = 0.0f, up_v = 0.0f, in_v = 0.0f, beta_i = 0.0f;   // (beta_i: !ahead only)
   uint32_t up_i = 0;
+  const bool ahead = a.ahead != 0;
   const uint32_t j_ins = WAVE ? lane - (64u - n_ins) : tid;   // (WAVE: the last lanes of the wave, so that samples and rows share it)
   const bool inserts = in_team && (!WAVE || lane >= 64u - n_ins) && j_ins < n_ins;
   if (in_team && tid < B) u_i = a.u[(size_t)t * B + tid];
   if (inserts && a.ins_prio) in_v = a.ins_prio[(size_t)t * n_ins + j_ins];
+  if (!ahead) beta_i = a.beta[0];
   __syncthreads();
   LdsTree lt;
   lt.tree = tree;
@@ -608,8 +612,33 @@ k_run_steps(StreamKernelArgs ka) {
         if (a.out_w) {
           const uint32_t vmin = s_vmin[(s - 1) & 1u];
           const uint32_t least = a.buffer_norm ? s_bmin[(s - 1) & 1u] : vmin;
-          w_out = vmin == kNoMin ? 0.0f : importance_weight(v_out, __uint_as_float(least), a.beta[s - 1]);
+          w_out = vmin == kNoMin ? 0.0f : importance_weight(v_out, __uint_as_float(least), ahead ? a.beta[s - 1] : beta_i);
         }
+      }
+    }
+    auto store_results = [&]() {   // of the step before
+      if (!weigher) return;
+      const size_t o = ((size_t)(s - 1) * T + t) * B + (tid - w0);
+      a.out_idx[o] = n_out;
+      if (a.out_prio) a.out_prio[o] = v_out;
+      if (a.out_w) a.out_w[o] = w_out;
+    };
+    if (s && !ahead) {
+      store_results();
+      wait_memory();
+      lds_barrier();
+      if (in_team && tid < B) {
+        const size_t bo = ((size_t)(s - 1) * T + t) * B + tid;
+        if (a.upd_prio) {
+          up_v = a.upd_prio[bo];
+          if (!a.upd_is_sampled) up_i = a.upd_idx[bo];
+        }
+        if (more) u_i = a.u[bo + (size_t)T * B];
+      }
+      if (more) {
+        if (rw < insert_items && ip.on) iv = load_piece(ip.dense + (uint64_t)s * s_ins.step[ip.f], ip.w);
+        if (inserts && a.ins_prio) in_v = a.ins_prio[((size_t)s * T + t) * n_ins + j_ins];
+        beta_i = a.beta[s];
       }
     }
     // ---- the tree: update of the step before, insertion of this one
@@ -619,7 +648,7 @@ k_run_steps(StreamKernelArgs ka) {
       const InsertWork in{do_ins, inserts, a.ins_prio != nullptr, n_ins, inserts ? ring_slot(cursor, j_ins, N) : 0u, in_v};
       change_tree<LOGK, WAVE, MEM>(tv, up, in, max_bits, flags);
       // inputs of the next round
-      if (in_team && tid < B) {
+      if (ahead && tid < B) {
         const size_t bo = ((size_t)s * T + t) * B + tid;
         if (more && a.upd_prio) {
           up_v = a.upd_prio[bo];
@@ -642,16 +671,9 @@ k_run_steps(StreamKernelArgs ka) {
       insert_rows(s_ins, rw + rws, rws, first, N, a.ins.row_stride, s, nullptr);
       wait_memory();
     }
-    if (s) {
-      if (weigher) {
-        const size_t o = ((size_t)(s - 1) * T + t) * B + (tid - w0);
-        a.out_idx[o] = n_out;
-        if (a.out_prio) a.out_prio[o] = v_out;
-        if (a.out_w) a.out_w[o] = w_out;
-      }
-    }
+    if (s && ahead) store_results();
     if (!more) break;
-    if (s + 1 < a.n_steps && n_ins) {
+    if (ahead && s + 1 < a.n_steps && n_ins) {
       if (rw < insert_items && ip.on) iv = load_piece(ip.dense + (uint64_t)(s + 1) * s_ins.step[ip.f], ip.w);
       if (inserts && a.ins_prio) in_v = a.ins_prio[((size_t)(s + 1) * T + t) * n_ins + j_ins];
     }
@@ -679,7 +701,7 @@ k_run_steps(StreamKernelArgs ka) {
         nodes[tid] = node;
         if (apart) values[tid] = val;
       }
-      u_i = u_next;
+      if (ahead) u_i = u_next;
     }
     lds_barrier();
   }

@@ -734,6 +734,37 @@ int per_update_delta(per_t* p, uint32_t B, const uint32_t* d_idx, const float* d
 
 int per_run_steps_fits(const per_t* p) { return p && stream_tree_floats(p->g, nullptr) ? 1 : 0; }
 
+// A byte range of the caller's memory that a list of steps or a request reads or writes.
+struct Span { uintptr_t lo, hi; };
+static void add_span(Span* s, uint32_t* n, const void* p, uint64_t bytes) {
+  if (p && bytes) s[(*n)++] = Span{reinterpret_cast<uintptr_t>(p), reinterpret_cast<uintptr_t>(p) + bytes};
+}
+static bool spans_meet(const Span* a, uint32_t na, const Span* b, uint32_t nb) {
+  for (uint32_t i = 0; i < na; ++i)
+    for (uint32_t j = 0; j < nb; ++j)
+      if (a[i].lo < b[j].hi && b[j].lo < a[i].hi) return true;
+  return false;
+}
+// True where no step of the list reads memory that a step writes its results to.
+static bool step_inputs_apart(const per_t* p, uint32_t n_steps, uint32_t n_insert, uint32_t B, const per_stream_io* io) {
+  Span in[5 + PER_MAX_FIELDS], out[3 + PER_MAX_FIELDS];
+  uint32_t ni = 0, no = 0;
+  const uint64_t samples = (uint64_t)n_steps * p->g.T * B, rows = (uint64_t)n_steps * p->g.T * n_insert;
+  add_span(in, &ni, io->d_u, samples * 4);
+  add_span(in, &ni, io->d_beta, (uint64_t)n_steps * 4);
+  add_span(in, &ni, io->d_upd_idx, samples * 4);
+  add_span(in, &ni, io->d_upd_prio, samples * 4);
+  add_span(in, &ni, io->d_ins_prio, rows * 4);
+  add_span(out, &no, io->d_out_idx, samples * 4);
+  add_span(out, &no, io->d_out_weight, samples * 4);
+  add_span(out, &no, io->d_out_prio, samples * 4);
+  for (uint32_t f = 0; f < p->cfg.n_fields; ++f) {
+    if (io->d_ins_rows) add_span(in, &ni, io->d_ins_rows[f], rows * p->cfg.field_bytes[f]);
+    if (io->d_rows_out) add_span(out, &no, io->d_rows_out[f], samples * p->cfg.field_bytes[f]);
+  }
+  return !spans_meet(in, ni, out, no);
+}
+
 int per_run_steps(per_t* p, uint32_t n_steps, uint32_t n_insert, uint32_t B, const per_stream_io* io, void* stream) {
   if (!p || !io || io->struct_size != sizeof(per_stream_io)) return PER_EINVAL;
   if (n_steps == 0) return PER_OK;
@@ -755,6 +786,7 @@ int per_run_steps(per_t* p, uint32_t n_steps, uint32_t n_insert, uint32_t B, con
   a.size = (uint32_t)p->size;
   a.upd_is_sampled = io->d_upd_prio && !io->d_upd_idx ? 1u : 0u;
   a.buffer_norm = p->weight_norm == PER_NORM_BUFFER ? 1u : 0u;
+  a.ahead = step_inputs_apart(p, n_steps, n_insert, B, io) ? 1u : 0u;
   p->min_stale = true;   // (the kernel works on an LDS copy of the leaves and does not keep min1)
   p->tables_valid = false;
   a.u = io->d_u;
@@ -775,17 +807,6 @@ int per_run_steps(per_t* p, uint32_t n_steps, uint32_t n_insert, uint32_t B, con
   return hip_rc(e);
 }
 
-// A byte range a request reads or writes.
-struct Span { uintptr_t lo, hi; };
-static void add_span(Span* s, uint32_t* n, const void* p, uint64_t bytes) {
-  if (p) s[(*n)++] = Span{reinterpret_cast<uintptr_t>(p), reinterpret_cast<uintptr_t>(p) + bytes};
-}
-static bool spans_meet(const Span* a, uint32_t na, const Span* b, uint32_t nb) {
-  for (uint32_t i = 0; i < na; ++i)
-    for (uint32_t j = 0; j < nb; ++j)
-      if (a[i].lo < b[j].hi && b[j].lo < a[i].hi) return true;
-  return false;
-}
 // What the requests of a queue read and write, the last few of them: whether one may be fetched ahead of those before it.
 struct RequestSpans {
   static constexpr uint32_t kBack = 6;   // (two rounds of the kernel: results of older requests are in memory by then)

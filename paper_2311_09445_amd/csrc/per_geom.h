@@ -148,6 +148,7 @@ struct StreamArgs {
   uint32_t cursor, size;            // ring state before the first step
   uint32_t upd_is_sampled;          // a step updates the batch it has just sampled
   uint32_t buffer_norm;             // importance weights relative to the whole tree (else to the batch)
+  uint32_t ahead;                   // what a step reads may be fetched before the results of the step before are in memory
   const float* u;                   // [steps][T][B]
   const float* beta;                // [steps]
   uint32_t* out_idx;                // [steps][T][B]

@@ -713,6 +713,44 @@ def test_run_steps_limits_and_empty_tree():
     assert q.status() == FLAG_ZERO_TOTAL
 
 
+@pytest.mark.parametrize("K,N,T,B,fb", [(16, 3000, 2, 32, (16, 4, 4, 16, 1)), (2, 3000, 1, 64, (12,)), (16, 30000, 1, 300, (68, 24, 4, 68, 1)),
+                                        (8, 5000, 3, 65, ()), (4, 9000, 1, 700, (16, 1)), (16, 100000, 1, 64, (5,)), (32, 300000, 2, 513, (8, 4))])
+@pytest.mark.parametrize("what", ["late", "own"])
+def test_run_steps_that_read_what_steps_return(K, N, T, B, fb, what):
+    """Results handed back through the arrays they were returned in.  late: step s updates the indices that step s - 1
+    drew (with the values it returned) and stores the rows it drew; own: the updated indices and values are those of
+    the same step, by address."""
+    log(f"run_steps on its own results K={K} N={N} T={T} B={B} fb={fb} {what}")
+    rng = np.random.default_rng(N + B)
+    m = Mirror(K, N, T, fb)
+    m.insert(N - 10, prio=wl._draw_priorities("exponential_1", rng, (T, N - 10)), chunk=max(5000, N // 8))
+    steps, n_ins = 9, B if what == "late" and fb else 0
+    u = wl.uniform01(rng, (steps, T, B))
+    beta = np.linspace(0.4, 1.0, steps).astype(np.float32)
+    x = rng.integers(0, N - 10, (steps + 1, T, B)).astype(np.uint32)
+    v = (rng.random((steps + 1, T, B)) * 4).astype(np.float32)
+    y = [rng.integers(0, 256, (steps + 1, T, B, b)).astype(np.uint8) for b in fb]
+    dx, dv, dy = idx_to_dev(x), dev(v), [dev(r) for r in y]
+    out_w = torch.empty((steps, T, B), dtype=torch.float32, device="cuda")
+    behind = 0 if what == "late" else 1
+    m.gpu.run_steps(dev(u), dev(beta), dx[1:], out_w, dv[1:], [r[1:] for r in dy] if fb else None, upd_prio=dv[behind:steps + behind],
+                    upd_idx=dx[behind:steps + behind], n_insert=n_ins, ins_rows=[r[:steps] for r in dy] if n_ins else None)
+    for s in range(steps):
+        if n_ins:
+            m.cpu.insert(n_ins, [r[s] for r in y], None)
+        x[s + 1], w, v[s + 1] = m.cpu.sample(u[s], float(beta[s]), True)
+        np.testing.assert_allclose(out_w[s].cpu().numpy(), w, rtol=1e-6, atol=0)
+        for f, r in enumerate(m.cpu.gather(x[s + 1])):
+            y[f][s + 1] = r
+        m.cpu.update(x[s + behind], v[s + behind])
+    assert np.array_equal(idx_to_host(dx), x), "sampled indices"
+    assert dv.cpu().numpy().tobytes() == v.tobytes(), "sampled values"
+    for f, r in enumerate(dy):
+        assert np.array_equal(r.cpu().numpy(), y[f]), f"rows of field {f}"
+    m.compare_tree()
+    m.compare_status()
+
+
 # ---------------------------------------------------------------------------------------------
 # a captured fused step can be replayed: nothing of a sampling + update call lives in host counters
 # ---------------------------------------------------------------------------------------------
