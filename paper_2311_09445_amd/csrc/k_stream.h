@@ -291,7 +291,7 @@ struct TreeView {
   uint32_t* s_arrived;       // team waves that have come to one of its barriers, over all barriers (LDS)
   bool apart;                // there are waves outside the team
   uint32_t team;             // lanes of the team
-  uint2* s_runs;             // [16] of every team wave: the leaf its elements begin with, what is known of them (see change_tree)
+  uint4* s_runs;             // [16] of every team wave: the leaves its elements begin and end with, what is known of them (see change_tree)
   uint32_t met;              // what s_arrived has to reach at the team's next barrier, less a team's waves
   __device__ __forceinline__ uint32_t off(uint32_t h) const { return (uint32_t)__builtin_amdgcn_readlane((int)off_reg, (int)h); }
   __device__ __forceinline__ void set_leaf(uint32_t i, float v) const {
@@ -329,9 +329,9 @@ __device__ __forceinline__ float child_group_sum(const TreeView<MEM>& v, uint32_
 }
 
 // An update of n elements (lane tid < n of the team: leaf ui gets uv) and then an insertion (lanes with `inserts`: row at
-// ring slot `slot`, value in_v or the running maximum), and the ancestors of both in one pass.  Called by the team.  `sorted`: the indices do not decrease from lane to lane.
+// ring slot `slot`, value in_v or the running maximum), and the ancestors of both in one pass.  Called by the team.
 struct UpdateWork {
-  bool on, mine, sorted;
+  bool on, mine, sorted;     // sorted: the indices are those of a sampled batch
   uint32_t n, i, size;
   float v;
 };
@@ -354,14 +354,20 @@ __device__ __forceinline__ void change_tree(TreeView<MEM>& tv, const UpdateWork&
     const uint32_t mx = valid && u.v > 0.0f ? __float_as_uint(u.v) : 0u;
     bool won = valid;
     const uint32_t mark = 0x80000001u + tid;
-    if (WAVE && u.sorted && !__any(u.mine && !valid)) {
+    // Sampled leaves come in order from uniforms in [0, 1); uniforms outside may return them in any, which is looked at
+    // here (neighbours that decrease): the markers then decide.
+    bool in_order = u.sorted;
+    if (WAVE && in_order) {
       // (elements of one leaf are neighbours, and the last of them wins)
       const uint32_t next = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)u.i, 0x130 /* wave_shl:1: from the lane above */, 0xF, 0xF, true);
-      won = valid && (tid + 1 >= u.n || next != u.i);
-    } else if (!WAVE && u.sorted) {
+      const bool last = tid + 1 >= u.n;
+      in_order = __all(!u.mine || (valid && (last || next >= u.i)));
+      if (in_order) won = valid && (last || next != u.i);
+    } else if (!WAVE && in_order) {
       // The last valid element of every run of equal leaves wins.  Within a wave that is read off two masks: where runs
       // begin, and which elements are valid.  A run that reaches the end of its wave may go on in the next ones: each
-      // wave leaves the leaf it begins with and whether that first run has a valid element (1) and is all there is (2).
+      // wave leaves the leaves it begins and ends with and whether its first run has a valid element (1) and is all there
+      // is (2), and whether its leaves decrease (4).
       const unsigned lane = tid & 63u;
       const uint32_t below = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)u.i, 0x138 /* wave_shr:1: from the lane below */, 0xF, 0xF, true);
       const unsigned long long begins = __ballot(u.mine && (lane == 0 || below != u.i)), good = __ballot(valid);
@@ -369,30 +375,42 @@ __device__ __forceinline__ void change_tree(TreeView<MEM>& tv, const UpdateWork&
       const unsigned run_end = later ? lane + 1u + (unsigned)__builtin_ctzll(later) : 64u;   // first lane behind this lane's run
       const unsigned long long behind = lane == 63u ? 0ull : (good >> (lane + 1u)) & (run_end == 64u && lane == 0 ? ~0ull : (1ull << (run_end - lane - 1u)) - 1ull);
       const unsigned long long first_run = begins & ~1ull ? (1ull << __builtin_ctzll(begins & ~1ull)) - 1ull : ~0ull;
-      if (lane == 0) tv.s_runs[tid >> 6] = make_uint2(u.mine ? u.i : 0xFFFFFFFFu, ((good & first_run) ? 1u : 0u) | ((begins & ~1ull) ? 0u : 2u));
+      const uint32_t in_wave = (tid & ~63u) < u.n ? u.n - (tid & ~63u) : 0u;   // elements of this wave and all behind it
+      const uint32_t ends_with = (uint32_t)__builtin_amdgcn_readlane((int)u.i, in_wave > 64u ? 63 : in_wave ? (int)in_wave - 1 : 0);
+      const bool falls = __any(u.mine && lane != 0 && below > u.i);
+      if (lane == 0)
+        tv.s_runs[tid >> 6] = make_uint4(in_wave ? u.i : 0xFFFFFFFFu, in_wave ? ends_with : 0xFFFFFFFFu,
+                                         ((good & first_run) ? 1u : 0u) | ((begins & ~1ull) ? 0u : 2u) | (falls ? 4u : 0u), 0u);
       won = valid && !behind;
       const uint32_t m = wave_max_u32(mx);
       if (lane == 0 && m) atomicMax(tv.s_max, m);
       tv.sync();
-      if (won && run_end == 64u)
-        for (uint32_t w = (tid >> 6) + 1u; w < (tv.team >> 6); ++w) {
-          const uint2 r = tv.s_runs[w];
+      const uint32_t waves = tv.team >> 6;
+      const uint4 all = tv.s_runs[lane < waves ? lane : waves - 1u];
+      const uint32_t ended = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)all.y, 0x138, 0xF, 0xF, true);
+      in_order = !__any(lane < waves && ((all.z & 4u) || (lane != 0 && ended > all.x)));
+      if (in_order && won && run_end == 64u)
+        for (uint32_t w = (tid >> 6) + 1u; w < waves; ++w) {
+          const uint4 r = tv.s_runs[w];
           if (r.x != u.i) break;
-          if (r.y & 1u) won = false;
-          if (!(r.y & 2u) || !won) break;
+          if (r.z & 1u) won = false;
+          if (!(r.z & 2u) || !won) break;
         }
-    } else if constexpr (MEM) {   // (markers in memory: atomics there, and a read that passes by the first-level cache)
-      GlobalPtr<uint32_t> bits = (GlobalPtr<uint32_t>)tv.leaves;
-      if (valid) __hip_atomic_fetch_max(&bits[u.i], mark, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      if constexpr (WAVE) wait_memory(); else tv.sync();
-      won = valid && __hip_atomic_load(&bits[u.i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == mark;
-      if constexpr (WAVE) wait_memory(); else tv.sync();
-    } else {
-      uint32_t* bits = reinterpret_cast<uint32_t*>(tv.tree);
-      if (valid) atomicMax(&bits[u.i], mark);
-      if constexpr (WAVE) wave_order(); else tv.sync();
-      won = valid && bits[u.i] == mark;
-      if constexpr (WAVE) wave_order(); else tv.sync();
+    }
+    if (!in_order) {
+      if constexpr (MEM) {   // (markers in memory: atomics there, and a read that passes by the first-level cache)
+        GlobalPtr<uint32_t> bits = (GlobalPtr<uint32_t>)tv.leaves;
+        if (valid) __hip_atomic_fetch_max(&bits[u.i], mark, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if constexpr (WAVE) wait_memory(); else tv.sync();
+        won = valid && __hip_atomic_load(&bits[u.i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == mark;
+        if constexpr (WAVE) wait_memory(); else tv.sync();
+      } else {
+        uint32_t* bits = reinterpret_cast<uint32_t*>(tv.tree);
+        if (valid) atomicMax(&bits[u.i], mark);
+        if constexpr (WAVE) wave_order(); else tv.sync();
+        won = valid && bits[u.i] == mark;
+        if constexpr (WAVE) wave_order(); else tv.sync();
+      }
     }
     if (won) tv.set_leaf(u.i, u.v);
     if constexpr (WAVE) {
@@ -522,7 +540,7 @@ k_run_steps(StreamKernelArgs ka) {
   __shared__ LevelTable tab;
   __shared__ uint32_t s_off[kMaxHeight + 2];
   __shared__ uint32_t s_max, s_vmin[2], s_bmin[2], s_flags, s_arrived;
-  __shared__ uint2 s_runs[16];
+  __shared__ uint4 s_runs[16];
   __shared__ PieceFields s_rows, s_ins;
   const uint32_t t = blockIdx.x;
   const uint32_t tid = threadIdx.x, lane = tid & 63u;
@@ -766,7 +784,7 @@ k_run_requests(QueueKernelArgs ka) {
   __shared__ PieceFields s_rows[2], s_ins[2];        // by parity of the round
   __shared__ uint32_t s_skip[2][32];                 // bit j: row j of the round's insertion is deferred
   __shared__ uint32_t s_max, s_vmin[2], s_bmin[2], s_flags, s_arrived;
-  __shared__ uint2 s_runs[16];
+  __shared__ uint4 s_runs[16];
   const uint32_t t = blockIdx.x;
   const uint32_t tid = threadIdx.x, lane = tid & 63u;
   const uint32_t H = g.H, N = g.N, n_requests = a.n_requests;

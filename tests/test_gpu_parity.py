@@ -751,6 +751,45 @@ def test_run_steps_that_read_what_steps_return(K, N, T, B, fb, what):
     m.compare_status()
 
 
+@pytest.mark.parametrize("K,N,T,B", [(16, 3000, 2, 64), (2, 500, 1, 33), (4, 5000, 1, 130), (8, 9000, 2, 512), (16, 5000, 1, 700), (16, 100000, 1, 60), (16, 100000, 1, 300)])
+@pytest.mark.parametrize("queue", [False, True])
+def test_own_batch_updates_when_uniforms_leave_their_range(K, N, T, B, queue):
+    """Uniforms below 0, from 1 on, infinite and NaN give sampled batches in no order, with the same leaf in places far apart;
+    the last element for a leaf still wins."""
+    from paper_2311_09445_amd.per import OP_SAMPLE, OP_UPDATE
+    log(f"uniforms out of range K={K} N={N} T={T} B={B} queue={queue}")
+    rng = np.random.default_rng(N + B)
+    m = Mirror(K, N, T, ())
+    prio = wl._draw_priorities("exponential_1", rng, (T, N))
+    prio[:, rng.random(N) < 0.98] = 0.0          # few leaves to draw from
+    m.insert(N, prio=prio)
+    steps = 8
+    u = (rng.random((steps, T, B)) * 3 * B - B).astype(np.float32)
+    u[1, :, ::5] = np.float32("nan")
+    u[2, :, ::7] = np.float32("inf")
+    u[3] = np.where(rng.random((T, B)) < 0.02, 1.0 + rng.random((T, B)) * 40, rng.random((T, B))).astype(np.float32)   # a few, the others in order
+    u[4:6] = wl.uniform01(rng, (2, T, B))
+    up = (rng.random((steps, T, B)) * 4).astype(np.float32)
+    up[3, :, ::3] = -1.0
+    beta = np.full(steps, 0.5, dtype=np.float32)
+    oi = torch.empty((steps, T, B), dtype=torch.int32, device="cuda")
+    ov = torch.empty((steps, T, B), device="cuda")
+    if queue:
+        q = []
+        for s in range(steps):
+            q += [{"op": OP_SAMPLE, "u": dev(u[s]), "beta": 0.5, "idx": oi[s], "out_prio": ov[s]}, {"op": OP_UPDATE, "prio": dev(up[s])}]
+        keep = m.gpu.run_requests(q)
+    else:
+        m.gpu.run_steps(dev(u), dev(beta), oi, None, ov, upd_prio=dev(up))
+    for s in range(steps):
+        ci, _, cv = m.cpu.sample(u[s], 0.5, False)
+        assert np.array_equal(idx_to_host(oi)[s], ci), f"step {s}: sampled indices"
+        assert ov[s].cpu().numpy().tobytes() == cv.tobytes(), f"step {s}: sampled values"
+        m.cpu.update(ci, up[s])
+    m.compare_tree()
+    m.compare_status()
+
+
 # ---------------------------------------------------------------------------------------------
 # a captured fused step can be replayed: nothing of a sampling + update call lives in host counters
 # ---------------------------------------------------------------------------------------------
