@@ -743,9 +743,13 @@ static hipError_t launch_tree_k(const Geom& g, const Tuning& tn, const ClaimArgs
   if (e != hipSuccess) return e;
   if (tblock > 512) tblock = 512;
   const uint32_t chain = (lazy_top_height(g, tn) ? 0u : 1u) | (c.fold_max ? 2u : 0u);
+  const size_t lds = tree_lds_bytes<LOGK>(sl);   // (K = 2: up to 96 KB, above 2^24 leaves)
 #define PER_UPDATE_TREE(TM, RN, BATCH)                                                                                     \
-  PER_LAUNCH(KID_UPDATE_TREE, (k_update_tree<LOGK, TM, RN, false>), dim3(g.n[sl.hb], g.T), dim3(tblock), tree_lds_bytes<LOGK>(sl), s, \
-             g, sl, chain, BATCH)
+  do {                                                                                                                     \
+    e = grant_lds<&k_update_tree<LOGK, TM, RN, false>>(tn, lds);                                                           \
+    if (e != hipSuccess) return e;                                                                                         \
+    PER_LAUNCH(KID_UPDATE_TREE, (k_update_tree<LOGK, TM, RN, false>), dim3(g.n[sl.hb], g.T), dim3(tblock), lds, s, g, sl, chain, BATCH); \
+  } while (0)
   const BatchRef batch{c.idx, c.prio, c.B};
   if (c.runs) {
     if (c.track_min) { PER_UPDATE_TREE(true, true, batch); } else { PER_UPDATE_TREE(false, true, batch); }
@@ -802,7 +806,11 @@ static hipError_t launch_tree_finish_k(const Geom& g, const Tuning& tn, const Cl
   const dim3 grid(tree_blocks + jr.first[2 + kMaxFields], g.T);
   const bool wide = !jr.whole_rows && any_field_moves_wide(rows ? &ft : nullptr);
 #define PER_TREE_FINISH(TM, WD)                                                                                        \
-  PER_LAUNCH(KID_TREE_FINISH, (k_tree_finish<LOGK, TM, WD>), grid, dim3(tblock), lds, s, g, sl, chain, tree_blocks, ft, jr, a)
+  do {                                                                                                                 \
+    e = grant_lds<&k_tree_finish<LOGK, TM, WD>>(tn, lds);                                                              \
+    if (e != hipSuccess) return e;                                                                                     \
+    PER_LAUNCH(KID_TREE_FINISH, (k_tree_finish<LOGK, TM, WD>), grid, dim3(tblock), lds, s, g, sl, chain, tree_blocks, ft, jr, a); \
+  } while (0)
   if (c.track_min) {
     if (wide) { PER_TREE_FINISH(true, true); } else { PER_TREE_FINISH(true, false); }
   } else {

@@ -1395,6 +1395,32 @@ def test_subtrees_of_the_tree_pass(K, N):
     m.compare_status()
 
 
+@pytest.mark.parametrize("N", [(1 << 23) + 1, (1 << 24) + 1])
+@pytest.mark.parametrize("norm", ["batch", "buffer"])
+def test_largest_subtrees_of_the_tree_pass(N, norm, claim_form):
+    """K = 2 above 2^24 leaves: subtrees of 4096 height-1 nodes, whose workgroups take more LDS than is theirs without a
+    grant; every kernel that holds the tree pass."""
+    if claim_form != "group":
+        pytest.skip("one claim form is enough at this size")
+    log(f"largest subtrees N={N} {norm}")
+    rng = np.random.default_rng(N)
+    m = Mirror(2, N, 1, ())
+    m.gpu.set_weight_norm(norm)
+    m.cpu.set_weight_norm(norm)
+    prio = wl._draw_priorities("lognormal_0_1", rng, (1, N))
+    m.insert(N, prio=prio, chunk=1 << 22)
+    B = 3000
+    new = lambda n=B: wl._draw_priorities("lognormal_0_1", rng, (1, n))  # noqa: E731
+    for r in range(2):
+        m.insert_step_call(5, None, wl.uniform01(rng, (1, B)), 0.5, True, new())                       # tree pass beside the weights
+        m.sample_gather_update(wl.uniform01(rng, (1, B)), 0.5, True, new(2000), tail=2000)             # tree pass alone, behind the claims
+        gi, ci = m.sample(wl.uniform01(rng, (1, 400)), 0.5)
+        m.update(ci, new(400))                                                                         # claims inside the tree pass
+        m.update(np.sort(rng.integers(0, N, (1, N // 100)), axis=1).astype(np.uint32), new(N // 100))  # claims in runs
+        m.compare_tree(heights=range(0, m.gpu.H + 1, 1 if r else 6))
+    m.compare_status()
+
+
 @pytest.mark.parametrize("K,N,T", [(2, 5000, 1), (4, 70001, 2), (8, 513, 3), (16, 70001, 1), (32, 150001, 1), (64, 64, 1), (64, 70001, 2), (16, 1 << 20, 1)])
 @pytest.mark.parametrize("norm", ["batch", "buffer"])
 def test_small_batches_claimed_in_the_tree_pass(K, N, T, norm):
