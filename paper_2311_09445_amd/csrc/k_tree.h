@@ -823,15 +823,16 @@ static hipError_t launch_tree_finish_k(const Geom& g, const Tuning& tn, const Cl
 template <int LOGK>
 static hipError_t launch_update_k(const Geom& g, const Tuning& tn, ClaimArgs c, hipStream_t s) {
   const uint32_t block = tn.update_block;
-  if (c.group_mode && tn.claim_in_sample && !c.pos && c.B <= kHereBatch &&
+  const bool can_run = c.group_mode && !c.from_td && !c.pos, force_runs = can_run && tn.update_runs == 2;
+  if (c.group_mode && tn.claim_in_sample && !c.pos && !force_runs && c.B <= kHereBatch &&
       (uint64_t)g.n[tree_pass_height(g)] * g.T * c.B <= kHereReads)
     return launch_update_here_k<LOGK>(g, tn, c, s);
   // In runs where that pays: plain priorities, a quarter of an element per group of 32 leaves on the average, and enough
   // elements in all for the rate of the atomics to count, below which the tree pass's reading of the runs weighs more,
   // at K = 32 with its large subtrees longest (2^20 leaves at K = 16: 43 000 elements 8.7 us leaf by leaf and 8.9 in runs,
   // 65 536 11.4 and 9.5; at K = 32 65 536 18.3 and 21.1, 262 144 48 and 47; 2^24 leaves there 93.8 and 38.4 for 2^20).
-  c.runs = c.group_mode && !c.from_td && !c.pos && (uint64_t)c.B * 128u >= g.N &&
-           (uint64_t)c.B * g.T >= (LOGK == 5 ? 3u << 16 : 1u << 16) ? 1u : 0u;
+  c.runs = force_runs || (can_run && tn.update_runs && (uint64_t)c.B * 128u >= g.N &&
+                          (uint64_t)c.B * g.T >= (LOGK == 5 ? 3u << 16 : 1u << 16)) ? 1u : 0u;
   if (c.runs) {
     PER_LAUNCH(KID_UPDATE_CLAIM, k_update_claim<true>, dim3((c.B + block - 1) / block, g.T), dim3(block), 0, s, g, c);
   } else {

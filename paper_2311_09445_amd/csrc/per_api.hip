@@ -331,6 +331,7 @@ int per_create(const per_config* cfg, void* d_arena, size_t arena_bytes, void* s
   p->tn.claim_in_sample = 1;
   p->tn.insert_small = 1;
   p->tn.group_claim = 1;
+  p->tn.update_runs = 1;
   p->tn.step_kernel = 1;
   p->tn.step_tail = 0;   // (measured slower than the second kernel: see k_step)
   p->tn.insert_ride = 1;
@@ -1053,6 +1054,11 @@ int per_set_tuning(per_t* p, const char* name, int64_t value) {
   if (!strcmp(name, "group_claim")) {
     if (value != 0 && value != 1) return PER_EINVAL;
     p->tn.group_claim = (uint32_t)value;
+    return PER_OK;
+  }
+  if (!strcmp(name, "update_runs")) {
+    if (value < 0 || value > 2) return PER_EINVAL;
+    p->tn.update_runs = (uint32_t)value;
     return PER_OK;
   }
   if (!strcmp(name, "step_tail")) {

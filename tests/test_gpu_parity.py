@@ -1315,9 +1315,10 @@ def test_updates_claimed_in_runs(K, N, T, norm):
     m = Mirror(K, N, T, ())
     m.gpu.set_weight_norm(norm)
     m.cpu.set_weight_norm(norm)
+    m.gpu.set_tuning("update_runs", 2)   # (the rule takes this form from far more elements on)
     m.insert(N, prio=wl._draw_priorities("exponential_1", rng, (T, N)))
     m.sample(wl.uniform01(rng, (T, 100)), 0.5)
-    for B in (N // 100 + 1, 777, N // 3, 2 * N):
+    for B in (1, N // 100 + 1, 777, N // 3, 2 * N):
         for kind in range(5):
             idx = np.sort(rng.integers(0, N, (T, B)), axis=1)
             if kind == 1:      # few leaves, each many times
