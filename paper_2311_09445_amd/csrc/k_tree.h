@@ -820,6 +820,32 @@ static hipError_t launch_tree_finish_k(const Geom& g, const Tuning& tn, const Cl
   return hipGetLastError();
 }
 
+// Does a batch of B elements in leaf order claim faster in runs than leaf by leaf?  The atomics of the leaf by leaf form
+// cost by the element, wherever they go; in runs the tree pass waits for the elements that it reads back, the longer the
+// more of them one workgroup has.  So, from a quarter of an element per group of 32 leaves on:
+//  - from 65 536 elements in all on (leaf by leaf and in runs: 2^20 leaves at K = 16: 2^15 elements 8.3 and 8.8 us, 2^16
+//    11.7 and 10.9, 2^18 37.5 and 21.0; 16 trees of 2^16 leaves at K = 8: 4096 each 12.2 and 10.7);
+//  - where the pass has few workgroups of many elements, from 196 608 on: subtrees of 512 or more height-1 nodes (2^22
+//    leaves at K = 32: 2^17 elements 17.9 and 21.8, 2^18 31 and 27; 2^24 at K = 4: 2^18 55 and 57, 2^19 73 and 70), or fewer
+//    than 256 subtrees at K = 64, whose runs are the longest (286 877 leaves: 170 423 elements 40 and 64; 2^20 leaves:
+//    2^17 22.0 and 21.8);
+//  - not with fewer than 32 such large subtrees (86 850 leaves at K = 32, 3 of them: 221 563 elements 105 and 189; 16
+//    trees of 148 120 leaves, 80 of them: 39 182 each 92 and 53), nor from 2048 nodes on (2^24 leaves at K = 2: 2^20
+//    elements 255 and 302).
+// Over 419 shapes drawn (every fanout, 2^16 .. 2^24 leaves, 1 .. 16 trees, 2^14 .. 2^20 elements) the chosen form takes 1.3 %
+// longer than the better one in the mean, leaf by leaf throughout 40 %, runs throughout 9 %.
+template <int LOGK>
+static bool runs_pay(const Geom& g, uint32_t B) {
+  const uint64_t elements = (uint64_t)B * g.T;
+  if ((uint64_t)B * 128u < g.N || elements < 1u << 16) return false;
+  SubLevels sl;
+  sub_levels<LOGK>(g, &sl);
+  const uint64_t subtrees = (uint64_t)g.n[sl.hb] * g.T;
+  const bool large = sl.list_cap >= 512u;
+  if (large && (sl.list_cap >= 2048u || subtrees < 32u)) return false;
+  return elements >= (large || (LOGK == 6 && subtrees < 256u) ? 3u << 16 : 1u << 16);
+}
+
 template <int LOGK>
 static hipError_t launch_update_k(const Geom& g, const Tuning& tn, ClaimArgs c, hipStream_t s) {
   const uint32_t block = tn.update_block;
@@ -827,12 +853,7 @@ static hipError_t launch_update_k(const Geom& g, const Tuning& tn, ClaimArgs c, 
   if (c.group_mode && tn.claim_in_sample && !c.pos && !force_runs && c.B <= kHereBatch &&
       (uint64_t)g.n[tree_pass_height(g)] * g.T * c.B <= kHereReads)
     return launch_update_here_k<LOGK>(g, tn, c, s);
-  // In runs where that pays: plain priorities, a quarter of an element per group of 32 leaves on the average, and enough
-  // elements in all for the rate of the atomics to count, below which the tree pass's reading of the runs weighs more,
-  // at K = 32 with its large subtrees longest (2^20 leaves at K = 16: 43 000 elements 8.7 us leaf by leaf and 8.9 in runs,
-  // 65 536 11.4 and 9.5; at K = 32 65 536 18.3 and 21.1, 262 144 48 and 47; 2^24 leaves there 93.8 and 38.4 for 2^20).
-  c.runs = force_runs || (can_run && tn.update_runs && (uint64_t)c.B * 128u >= g.N &&
-                          (uint64_t)c.B * g.T >= (LOGK == 5 ? 3u << 16 : 1u << 16)) ? 1u : 0u;
+  c.runs = force_runs || (can_run && tn.update_runs && runs_pay<LOGK>(g, c.B)) ? 1u : 0u;
   if (c.runs) {
     PER_LAUNCH(KID_UPDATE_CLAIM, k_update_claim<true>, dim3((c.B + block - 1) / block, g.T), dim3(block), 0, s, g, c);
   } else {
