@@ -696,9 +696,18 @@ static SampleShape sample_shape(const Geom& g, const Tuning& tn, uint32_t B, uin
 // A carried insertion: the touched nodes of heights 1 .. hp (two ranges per height, narrowed by K from one height
 // to the next) and where their child groups, their new sums and the new leaves sit in LDS.
 // Most rows a sampling kernel carries: every workgroup of it sums the touched nodes anew, and beside the kernel of large
-// insertions that only pays for few (64 trees of 32 768 leaves at K = 8, 499 samples: 20.1 us with 64 rows carried, 22.0 not;
-// 256 rows: 26.6 and 24.2).
-constexpr uint32_t kRideRows = 128;
+// insertions that only pays for few.  The line is drawn by the width of those sums and, for wide ones, by how many trees
+// there are (insertion carried and apart, us per step with 165-byte rows):
+//  - up to K = 16, 128 rows: a tree of 2^20 leaves at K = 16, 4096 samples: 128 rows 13.8 and 15.3; 64 trees of 2^17: 64 rows
+//    26.7 and 28.2, 128 rows 28.1 and 30.0; 64 trees of 2^15 at K = 8, 499 samples: 64 rows 20.1 and 22.0, 256 rows 26.6
+//    and 24.2.  K = 32 the same on few trees (16 of 2^17, 1024 samples: 128 rows 19.4 and 21.4), on many 64 rows (64 of
+//    2^17: 32 rows 33.4 and 34.9, 64 rows 35.4 and 35.1, 128 rows 38.3 and 36.2);
+//  - K = 64: 16 rows, from 512 samples on (64 trees of 2^15, 512 samples: 16 rows 25.2 and 26.0, 32 rows 27.8 and 26.1, 64
+//    rows 35.2 and 26.5; 4 of 2^17: 1024 samples 16.8 and 16.9, 64 samples 16.5 and 15.3).
+static uint32_t most_rows_carried(const Geom& g, uint32_t B) {
+  if (g.logK == 6) return B >= 512u ? 16u : 0u;
+  return g.logK == 5 && g.T >= 32u ? 64u : 128u;
+}
 constexpr uint32_t kRideLdsBytes = 16 * 1024; // most LDS its patch may take
 // False when the insertion runs past the ring's end or a run of child groups is longer than the workgroup (`block`
 // lanes): the insertion then goes by itself.
@@ -732,7 +741,7 @@ static bool plan_ride(const Geom& g, const TopCopy& tc, uint32_t block, uint32_t
 
 bool sample_can_carry_insert(const Geom& g, const Tuning& tn, uint32_t B, const FieldTable* ft, uint32_t n, uint32_t cursor) {
   const uint32_t hb = lazy_top_height(g, tn);
-  if (!hb || hb > (uint32_t)kRideHeights || n == 0 || n > kRideRows || n > g.N) return false;
+  if (!hb || hb > (uint32_t)kRideHeights || n == 0 || n > most_rows_carried(g, B) || n > g.N) return false;
   uint64_t bytes = 0;
   if (ft)
     for (uint32_t f = 0; f < ft->n_fields; ++f)
