@@ -772,11 +772,12 @@ static hipError_t launch_sample_k(const Geom& g, const Tuning& tn, uint32_t B, u
   // samples in turn, with the top of the tree in place and the next uniforms under way, where workgroups of a second
   // round would begin with their arguments and the top of the tree again, two of the five trips to memory of a block.
   // (2^20 samples on 2^24 leaves at K = 32: 59 us with a workgroup per block, 27 so, with the rows of stage_groups.)
-  auto held = [&]() -> uint64_t {   // workgroups the device holds (256 compute units)
+  const uint64_t units = compute_units(tn.device);
+  auto held = [&]() -> uint64_t {   // workgroups the device holds
     uint64_t bytes = (uint64_t)sh.top_bytes + (uint64_t)sh.waves * sh.wave_bytes, by_waves = 32 / sh.waves;
     if (bytes < tn.sample_min_lds) bytes = tn.sample_min_lds;
     const uint64_t by_lds = bytes ? (160 * 1024) / bytes : by_waves, n = by_lds < by_waves ? by_lds : by_waves;
-    return 256 * (n < 1 ? 1 : n);
+    return (units ? units : 256) * (n < 1 ? 1 : n);
   };
   const bool loop = !ride && (uint64_t)((B + sh.waves * 64 - 1) / (sh.waves * 64)) * g.T > held();
   if (loop) sh = sample_shape(g, tn, B, stale_hb, rows || claim, false, true);

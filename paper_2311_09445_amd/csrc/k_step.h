@@ -1180,18 +1180,6 @@ static void step_shape(const Geom& g, uint32_t block, uint32_t B, bool with_map,
   *step_lds = (size_t)off * 4;
 }
 
-// Compute units of `device` (0 if the query fails).
-static uint32_t compute_units(int device) {
-  static std::atomic<int> known[kMaxDevices];
-  if (device < 0 || device >= kMaxDevices) return 0;
-  int n = known[device].load(std::memory_order_relaxed);
-  if (n == 0) {
-    if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess || n < 0) n = 0;
-    known[device].store(n, std::memory_order_relaxed);
-  }
-  return (uint32_t)n;
-}
-
 template <int LOGK>
 static hipError_t launch_step_k(const Geom& g, const Tuning& tn, uint32_t block, bool tables_valid, uint32_t B, uint32_t size,
                                 float beta, uint32_t weight_mode, const float* u, const RngArgs& rng, uint32_t* out_idx,

@@ -91,6 +91,18 @@ static hipError_t grant_lds(const Tuning& tn, size_t bytes) {
   return e;
 }
 
+// Compute units of `device` (0 if the query fails).
+static uint32_t compute_units(int device) {
+  static std::atomic<int> known[kMaxDevices];
+  if (device < 0 || device >= kMaxDevices) return 0;
+  int n = known[device].load(std::memory_order_relaxed);
+  if (n == 0) {
+    if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess || n < 0) n = 0;
+    known[device].store(n, std::memory_order_relaxed);
+  }
+  return (uint32_t)n;
+}
+
 #define PER_DISPATCH_LOGK(logK, CALL)            \
   switch (logK) {                                \
     case 1: return CALL(1);                      \
