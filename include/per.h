@@ -171,11 +171,12 @@ int per_step(per_t* p, uint32_t B, float beta, const float* d_u, uint32_t* d_out
 
 /* per_insert(n, d_field_src, d_ins_prio, d_ins_out_idx) followed by per_step(...) as one call with the same results:
  * the iteration of Listing 2 (Section IV-D) with the Actors' new rows put in first (Section II-A: insertion at
- * the maximum priority, or at given values).  Where the insertion is small (at most 1024 rows per tree, few
- * touched nodes), the buffer's weights refer to the batch, and the tree's topmost heights are rebuilt lazily
- * (tuning "lazy_top"), the sampling kernel of the step carries the insertion: each of its workgroups works out
- * the few new nodes for itself and samples from the tree as the insertion leaves it, one of them stores them,
- * one extra workgroup moves the rows; the step then takes two kernel launches, insertion included.  For that the
+ * the maximum priority, or at given values).  Where the insertion is small (at most 128 rows per tree, fewer on
+ * trees of large fanout; few touched nodes; not past the ring's end), the buffer's weights refer to the batch, and
+ * the tree's topmost heights are rebuilt lazily (tuning "lazy_top"), the sampling kernel of the step carries the
+ * insertion: each of its workgroups works out the few new nodes for itself and samples from the tree as the
+ * insertion leaves it, extra workgroups move the rows and the first of them stores the new nodes; the step then
+ * takes two kernel launches, insertion included.  For that the
  * insertion's arrays (d_field_src[f], d_ins_prio, d_ins_out_idx) must not overlap the step's outputs and
  * d_ins_out_idx none of the step's inputs either; otherwise, and for any other shape, the two calls are made one
  * after the other.  Arguments, flags and errors as for the two calls; an argument error of the step is
@@ -338,10 +339,11 @@ int per_set_ring(per_t* p, uint64_t cursor, uint64_t size);
  *   PER_NORM_BUFFER : the maximum over every stored row that can be sampled (priority > 0), the form
  *                     that implementations back with a min tree beside the sum tree.
  * Here the companion structure is the smallest positive leaf under every height-1 node, renewed by
- * per_update, the fused step and small inserts for the nodes they touch while this mode is on, rebuilt
- * from the leaves after calls that cannot (large inserts, per_update_delta, per_run_steps,
- * per_run_requests, per_set_ring), and reduced to one value per tree by a kernel in front of every
- * sampling call that returns weights.  per_run_steps and per_run_requests sweep the leaves (their LDS copy,
+ * per_update, the fused step and insertions for the nodes they touch while this mode is on, rebuilt
+ * from the leaves after calls that cannot (the one-kernel form of per_step, per_update_delta, per_run_steps,
+ * per_run_requests, per_set_ring), and reduced to one value per tree by extra workgroups of every sampling
+ * kernel whose call returns weights (by a kernel of its own in front of the one-kernel form of per_step and for
+ * per_min_priority).  per_run_steps and per_run_requests sweep the leaves (their LDS copy,
  * or memory) instead.  The mode applies to the calls made after it is set.
  * per_min_priority: d_out[t] = smallest positive leaf of tree t (+infinity if there is none). */
 #define PER_NORM_BATCH  0
@@ -388,9 +390,15 @@ uint64_t per_rng_calls(const per_t* p);
  *                  by a group of 32 leaves (64 for K = 64), an array small enough to stay in cache, and
  *                  goes to its leaf's own stamp only when two leaves of one group meet in a batch
  *                  (batches of more than 2^25 elements always use form 0)
- *   "lazy_top"   : 1 (default) lets per_update leave the few topmost heights to be rebuilt by
- *                  the next call that reads them; 0 makes per_update finish them itself
- *   "insert_small" : 1 (default) runs an insert of few rows as a single kernel, one workgroup per tree
+ *   "update_runs" : with "group_claim" 1, consecutive elements of a per_update batch for leaves of one group claim
+ *                  together, and the update's tree pass reads them from the batch: for large batches in leaf order, as
+ *                  sampling returns them.  0: never; 1 (default): where it is faster; 2: wherever it can be (batches of
+ *                  given priorities; tests)
+ *   "lazy_top"   : 1 (default) lets per_update and per_insert leave the few topmost heights to be rebuilt by
+ *                  the next call that reads them; 0 makes them finish those themselves
+ *   "insert_small" : 1 (default) runs insertions of at most 16 rows, on trees whose top is not left to its next reader, as a
+ *                  kernel of one workgroup per tree that goes up to the root; 0: as those of more rows (a workgroup per
+ *                  touched subtree, others for the rows).  Protected insertions are always of the first kind
  *   "step_tail"  : 1 lets the one-kernel step end inside that kernel (rows, weights and the next call's tables after a
  *                  wait of all its workgroups for each other) where all of them fit the GPU at once; 0 (default): a second
  *                  kernel does that, which was measured faster

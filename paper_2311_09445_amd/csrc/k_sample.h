@@ -47,8 +47,8 @@ __device__ __forceinline__ float counter_uniform(const RngArgs& rng, uint32_t i,
 }
 
 // Chunk (IT*64 + lane) of the wave's 64*C 16-byte chunks, for IT = 0 .. C-1: fetched from the group of the lane that owns
-// it and parked in that lane's staging row.  Written as a recursion over
-// IT so that every fetch is issued before the first LDS store without the compiler having to promote an array.
+// it and parked in that lane's staging row.  Written as a recursion over IT so that every fetch is issued before the first
+// LDS store without the compiler having to promote an array.
 template <int LOGK, int IT>
 __device__ __forceinline__ void stage_group_per_lane(const float* __restrict__ lvl, uint32_t node, unsigned lane, float* stage) {
   constexpr int K = Fan<LOGK>::K;
@@ -63,12 +63,13 @@ __device__ __forceinline__ void stage_group_per_lane(const float* __restrict__ l
   }
 }
 
-// The same for large batches (the kernel that loops over blocks of samples).  Samples come in leaf order, so lanes that stand on one
-// node are neighbours: each distinct group is fetched once, into the row of its rank among the wave's groups, and all
-// its lanes walk that row.  (A large batch is bound by what the walk reads and computes per sample, not by the tree's
-// bytes: 2^20 samples on 2^24 leaves at K = 32 fetched 128 bytes per sample and height, 400 MB between caches and compute
-// units for 60 MB of distinct groups.  Few samples seldom share a group, and the ranks cost the lone wave 0.7 us of its chain.)  Beside the K children a row holds the sums of its chunks (4 adjacent children),
-// which the lane that fetches a chunk computes once for all lanes of the group, and the number of its node:
+// The same for large batches (the kernel that loops over blocks of samples).  Samples come in leaf order, so lanes that
+// stand on one node are neighbours: each distinct group is fetched once, into the row of its rank among the wave's groups,
+// and all its lanes walk that row.  (A large batch is bound by what the walk reads and computes per sample, not by the
+// tree's bytes: 2^20 samples on 2^24 leaves at K = 32 fetched 128 bytes per sample and height, 400 MB between caches and
+// compute units for 60 MB of distinct groups.  Few samples seldom share a group, and the ranks cost the lone wave 0.7 us of
+// its chain.)  Beside the K children a row holds the sums of its chunks (4 adjacent children), which the lane that fetches a
+// chunk computes once for all lanes of the group, and the number of its node:
 //   [K children][K / 4 chunk sums][node] pad
 // rows an odd number of 16-byte units apart, so that lanes on different rows read different banks.
 template <int LOGK>
@@ -81,8 +82,8 @@ struct StageRow {
 static uint32_t stage_row_floats(uint32_t logK) {
   return logK == 3 ? StageRow<3>::FLOATS : logK == 4 ? StageRow<4>::FLOATS : logK == 5 ? StageRow<5>::FLOATS : logK == 6 ? StageRow<6>::FLOATS : 0u;
 }
-// Chunk (IT*64 + lane) of the wave's `chunks` 16-byte chunks, for IT = 0 .. C-1: first the numbers of all their nodes, then
-// every fetch, then the LDS stores.  Written as recursions over IT (not loops over arrays of registers) so that each
+// Chunk (IT*64 + lane) of the wave's `chunks` 16-byte chunks, for IT = 0 .. C-1: first the numbers of all their nodes,
+// then every fetch, then the LDS stores.  Written as recursions over IT (not loops over arrays of registers) so that each
 // phase is under way as a whole before the next one waits, without the compiler having to promote an array.
 template <int C>
 struct NodeNumbers {

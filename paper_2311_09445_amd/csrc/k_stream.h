@@ -744,7 +744,7 @@ k_run_steps(StreamKernelArgs ka) {
 // Fetching ahead is only right where a request reads nothing that one just before it writes (an update whose index
 // array is the sampled one, say).  The host has checked that (QueueArgs::ahead); where it does not hold, every
 // request is a round of its own with an empty one behind it, which brings all results to memory.
-// 20 times (insert 16 rows, sample 512, update them) on 30 000 leaves at K = 16: 185 us; 353 us one request after the
+// 20 times (insert 16 rows, sample 512, update them) on 30 000 leaves at K = 16: 191 us; 353 us one request after the
 // other by the whole workgroup with a full barrier between their phases.
 struct QueueKernelArgs {            // one kernel argument (Geom first: see fill_level_table)
   Geom g;

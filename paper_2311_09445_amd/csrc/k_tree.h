@@ -57,7 +57,8 @@ using BatchParam = typename std::conditional<HERE, SmallBatch, typename std::con
 // leaves' bits go into a word (two for K = 64) per height-1 node.  No stamps and no dirty bits in memory then, and no
 // kernel of its own: 512 temporal-difference errors on 100 000 leaves at K = 64, 5.2 us, 6.9 as two kernels.
 constexpr uint32_t kHereBatch = 2048;      // largest batch claimed so (the table has 12 bytes per slot, two slots per element)
-constexpr uint64_t kHereReads = 1u << 20;  // most elements read over all workgroups (2048 by 1024 of them: 10.5 us, 7.7 as two kernels; 1024: 6.2 and 7.6)
+// Most elements read over all workgroups (2048 by 1024 of them: 10.5 us, 7.7 as two kernels; 1024: 6.2 and 7.6).
+constexpr uint64_t kHereReads = 1u << 20;
 struct LeafTable {
   unsigned long long* last;   // element + 1, value bits
   uint32_t* key;              // the leaf, or kNoLeaf
@@ -635,15 +636,13 @@ k_tree_finish(Geom g, SubLevels sl, uint32_t chain, uint32_t tree_blocks, FieldT
   PER_FLUSH();
 }
 
-// Height of the workgroup roots of the tree pass: the whole tree for small trees, else the
-// lowest height whose subtrees hold at least 64 height-1 nodes (so that dirty words are never
-// shared between workgroups).
-// The lowest height whose subtrees hold 64 height-1 nodes, or the root of a tree of no more of them: the pass works
-// through a subtree's claimed nodes a few at a time, a trip to memory each, and what lies above is left to the next
-// sampling call, which has the top of the tree in LDS anyway.  (A tree of up to 2048 height-1 nodes as one subtree: 512
-// elements on 100 000 leaves at K = 64 took 11.3 us, 3.7 so; a step of 1024 on 30 000 at K = 16, insertion of 16 rows now
-// carried by the sampling, 21.5 and 12.3; 64 such trees 40.9 and 32.5.)  Not at K = 2, where the many heights to rebuild
-// cost the sampling as much as the pass gains: a step of 64 on 4096 leaves 13.5 us as one subtree, 14.7 as 32.
+// Height of the workgroup roots of the tree pass: the lowest whose subtrees hold 64 height-1 nodes (so that dirty words
+// are never shared between workgroups), or the root of a tree of no more of them.  The pass works through a subtree's
+// claimed nodes a few at a time, a trip to memory each, and what lies above is left to the next sampling call, which has
+// the top of the tree in LDS anyway.  (A tree of up to 2048 height-1 nodes as one subtree: 512 elements on 100 000 leaves
+// at K = 64 took 11.3 us, 3.7 so; a step of 1024 on 30 000 at K = 16, insertion of 16 rows now carried by the sampling,
+// 21.5 and 12.3; 64 such trees 40.9 and 32.5.)  Not at K = 2, where the many heights to rebuild cost the sampling as much
+// as the pass gains: a step of 64 on 4096 leaves 13.5 us as one subtree, 14.7 as 32.
 static uint32_t tree_pass_height(const Geom& g) {
   if (g.n[1] <= (g.logK == 1 ? 2048u : 64u)) return g.H;
   uint32_t hb = 1;
