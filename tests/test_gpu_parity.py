@@ -1015,6 +1015,40 @@ def test_insert_carried_by_the_step(K, N, T, B, fb, rides):
     m.compare_status()
 
 
+@pytest.mark.parametrize("K,N,T,B,most", [(16, 20000, 8, 300, 128), (8, 9000, 9, 600, 128), (4, 3000, 16, 512, 128), (32, 70001, 8, 513, 128), (32, 70001, 32, 512, 64),
+                                          (64, 9000, 4, 512, 16), (64, 9000, 4, 511, 0)])
+def test_largest_carried_insertions(K, N, T, B, most):
+    """Insertions of the most rows that a sampling kernel carries, and of one more, on many trees (larger sampling workgroups,
+    which leave room for the wider patches): beginning on a node's first leaf and inside a node, up to the ring's end."""
+    log(f"largest carried insertions K={K} N={N} T={T} B={B} most={most}")
+    rng = np.random.default_rng(K + N + B)
+    m = Mirror(K, N, T, (16, 5))
+    m.gpu.set_tuning("step_kernel", 0)
+    m.insert(N, prio=wl._draw_priorities("pareto_1.5", rng, (T, N)))
+    m.update(m.sample(wl.uniform01(rng, (T, B)), 0.4)[1], wl._draw_priorities("pareto_1.5", rng, (T, B)))
+    m.gpu.profile(True)
+    for start, n in ((0, most), (K * K + 1, most), (K, most + 1), (N - most, most), (N - most + 1, most)):
+        n = max(n, 1)
+        gap = (start - m.gpu.cursor) % N
+        if gap:
+            m.insert(gap, prio=wl._draw_priorities("pareto_1.5", rng, (T, gap)))
+        ins = None
+        if start:
+            ins = (wl._draw_priorities("pareto_1.5", rng, (T, n)) * 100).astype(np.float32)
+            ins[:, ::11] = np.float32(np.nan)
+        before = kernel_launches(m)
+        m.insert_step_call(n, ins, wl.uniform01(rng, (T, B)), 0.5, True, wl._draw_updates("absnormal1_eps_pow0.6", rng, (T, B)))
+        after = kernel_launches(m)
+        alone = any(v != before.get(k, 0) for k, v in after.items() if k.startswith("k_insert"))
+        if n > most or start + n > N:
+            assert alone, (start, n, after)
+        elif start == 0:
+            assert not alone, (start, n, after)
+        m.compare_tree()
+    m.gpu.profile(False)
+    m.compare_status()
+
+
 @pytest.mark.parametrize("K,N,T,B", [(32, 1 << 20, 1, 8192), (16, 1 << 18, 2, 2048), (8, 1 << 18, 1, 4096), (64, 1 << 19, 1, 3000)])
 def test_step_call_when_the_mass_sits_in_few_places(K, N, T, B):
     """The samples of one subtree are one workgroup's work in the one-kernel step.  Here nearly all mass sits in one
@@ -1342,6 +1376,21 @@ def test_updates_claimed_in_runs(K, N, T, norm):
     if norm == "buffer":
         want = np.array([t.read_level(0)[t.read_level(0) > 0].min() for t in m.cpu.trees], dtype=np.float32)
         assert m.gpu.min_priority().cpu().numpy().tobytes() == want.tobytes()
+
+
+@pytest.mark.parametrize("K,N,T,B", [(16, 70001, 1, 65535), (16, 70001, 1, 65536), (4, 20001, 4, 16384), (64, 70001, 1, 196607), (64, 70001, 1, 196608),
+                                     (64, 16500, 64, 1100), (32, 1 << 20, 1, 196608), (32, 1100000, 1, 196607), (32, 1100000, 1, 196608)])
+def test_updates_either_side_of_the_rule_for_runs(K, N, T, B):
+    """Sampled batches, then batches of no order, at the sizes where per_update changes from one form of claiming to the other."""
+    log(f"rule for runs K={K} N={N} T={T} B={B}")
+    rng = np.random.default_rng(N + K + B)
+    m = Mirror(K, N, T, ())
+    m.insert(N, prio=wl._draw_priorities("pareto_1.5", rng, (T, N)))
+    for r in range(2):
+        gi, ci = m.sample(wl.uniform01(rng, (T, B)), 0.5)
+        m.update(ci if r == 0 else rng.permuted(ci, axis=1), (rng.random((T, B)) * 3).astype(np.float32))
+        m.compare_tree()
+    m.compare_status()
 
 
 @pytest.mark.parametrize("K,N,T,fb,sizes", [
