@@ -291,7 +291,8 @@ struct TreeView {
   uint32_t* s_arrived;       // team waves that have come to one of its barriers, over all barriers (LDS)
   bool apart;                // there are waves outside the team
   uint32_t team;             // lanes of the team
-  uint4* s_runs;             // [16] of every team wave: the leaves its elements begin and end with, what is known of them (see change_tree)
+  uint32_t* s_wild;          // the latest sampling with a uniform outside [0, 1) (0: none)
+  uint2* s_runs;             // [16] of every team wave: the leaf its elements begin with, what is known of them (see change_tree)
   uint32_t met;              // what s_arrived has to reach at the team's next barrier, less a team's waves
   __device__ __forceinline__ uint32_t off(uint32_t h) const { return (uint32_t)__builtin_amdgcn_readlane((int)off_reg, (int)h); }
   __device__ __forceinline__ void set_leaf(uint32_t i, float v) const {
@@ -334,6 +335,7 @@ struct UpdateWork {
   bool on, mine, sorted;     // sorted: the indices are those of a sampled batch
   uint32_t n, i, size;
   float v;
+  uint32_t batch;            // sorted, !WAVE: the number of that sampling (from 1 on)
 };
 struct InsertWork {
   bool on, mine, given;      // given: the value is `v`, else the running maximum
@@ -354,50 +356,43 @@ __device__ __forceinline__ void change_tree(TreeView<MEM>& tv, const UpdateWork&
     const uint32_t mx = valid && u.v > 0.0f ? __float_as_uint(u.v) : 0u;
     bool won = valid;
     const uint32_t mark = 0x80000001u + tid;
-    // Sampled leaves come in order from uniforms in [0, 1); uniforms outside may return them in any, which is looked at
-    // here (neighbours that decrease): the markers then decide.
+    // Sampled leaves come in order from uniforms in [0, 1): the targets do not decrease then, and the walk keeps their order.
+    // Uniforms outside may return leaves in any order; the markers decide there.  (One wave looks at its leaves; several
+    // go by whether a uniform was out of range, in which case the sampling has left its number in *tv.s_wild.)
     bool in_order = u.sorted;
     if (WAVE && in_order) {
       // (elements of one leaf are neighbours, and the last of them wins)
       const uint32_t next = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)u.i, 0x130 /* wave_shl:1: from the lane above */, 0xF, 0xF, true);
-      const bool last = tid + 1 >= u.n;
+      const bool last = not_before_here(tid) + 1u >= u.n;   // (worked out here each time: as a mask kept over the steps it costs more, scalar registers are short)
       in_order = __all(!u.mine || (valid && (last || next >= u.i)));
       if (in_order) won = valid && (last || next != u.i);
     } else if (!WAVE && in_order) {
       // The last valid element of every run of equal leaves wins.  Within a wave that is read off two masks: where runs
       // begin, and which elements are valid.  A run that reaches the end of its wave may go on in the next ones: each
-      // wave leaves the leaves it begins and ends with and whether its first run has a valid element (1) and is all there
-      // is (2), and whether its leaves decrease (4).
+      // wave leaves the leaf it begins with and whether that first run has a valid element (1) and is all there is (2).
       const unsigned lane = tid & 63u;
+      const uint32_t wild = *tv.s_wild;   // (read here, looked at behind the barrier, which hides the trip)
       const uint32_t below = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)u.i, 0x138 /* wave_shr:1: from the lane below */, 0xF, 0xF, true);
       const unsigned long long begins = __ballot(u.mine && (lane == 0 || below != u.i)), good = __ballot(valid);
       const unsigned long long later = lane == 63u ? 0ull : begins >> (lane + 1u);
       const unsigned run_end = later ? lane + 1u + (unsigned)__builtin_ctzll(later) : 64u;   // first lane behind this lane's run
       const unsigned long long behind = lane == 63u ? 0ull : (good >> (lane + 1u)) & (run_end == 64u && lane == 0 ? ~0ull : (1ull << (run_end - lane - 1u)) - 1ull);
       const unsigned long long first_run = begins & ~1ull ? (1ull << __builtin_ctzll(begins & ~1ull)) - 1ull : ~0ull;
-      const uint32_t in_wave = (tid & ~63u) < u.n ? u.n - (tid & ~63u) : 0u;   // elements of this wave and all behind it
-      const uint32_t ends_with = (uint32_t)__builtin_amdgcn_readlane((int)u.i, in_wave > 64u ? 63 : in_wave ? (int)in_wave - 1 : 0);
-      const bool falls = __any(u.mine && lane != 0 && below > u.i);
-      if (lane == 0)
-        tv.s_runs[tid >> 6] = make_uint4(in_wave ? u.i : 0xFFFFFFFFu, in_wave ? ends_with : 0xFFFFFFFFu,
-                                         ((good & first_run) ? 1u : 0u) | ((begins & ~1ull) ? 0u : 2u) | (falls ? 4u : 0u), 0u);
+      if (lane == 0) tv.s_runs[tid >> 6] = make_uint2(u.mine ? u.i : 0xFFFFFFFFu, ((good & first_run) ? 1u : 0u) | ((begins & ~1ull) ? 0u : 2u));
       won = valid && !behind;
       const uint32_t m = wave_max_u32(mx);
       if (lane == 0 && m) atomicMax(tv.s_max, m);
       tv.sync();
-      const uint32_t waves = tv.team >> 6;
-      const uint4 all = tv.s_runs[lane < waves ? lane : waves - 1u];
-      const uint32_t ended = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)all.y, 0x138, 0xF, 0xF, true);
-      in_order = !__any(lane < waves && ((all.z & 4u) || (lane != 0 && ended > all.x)));
+      in_order = wave_value(wild) != u.batch;
       if (in_order && won && run_end == 64u)
-        for (uint32_t w = (tid >> 6) + 1u; w < waves; ++w) {
-          const uint4 r = tv.s_runs[w];
+        for (uint32_t w = (tid >> 6) + 1u; w < (tv.team >> 6); ++w) {
+          const uint2 r = tv.s_runs[w];
           if (r.x != u.i) break;
-          if (r.z & 1u) won = false;
-          if (!(r.z & 2u) || !won) break;
+          if (r.y & 1u) won = false;
+          if (!(r.y & 2u) || !won) break;
         }
     }
-    if (!in_order) {
+    if (__builtin_expect(!in_order, 0)) {   // (out of the way: the code of a round is fetched line by line as it goes)
       if constexpr (MEM) {   // (markers in memory: atomics there, and a read that passes by the first-level cache)
         GlobalPtr<uint32_t> bits = (GlobalPtr<uint32_t>)tv.leaves;
         if (valid) __hip_atomic_fetch_max(&bits[u.i], mark, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -487,6 +482,12 @@ __device__ __forceinline__ void change_tree(TreeView<MEM>& tv, const UpdateWork&
   }
 }
 
+// Waves of the team with a uniform outside [0, 1) (or -0, which does no harm) leave the number of the sampling.  Lanes without
+// a sample hold 0, or a uniform of an earlier one.
+__device__ __forceinline__ void note_wild(float u, uint32_t batch, uint32_t* s_wild) {
+  if (__builtin_expect(__any(__float_as_uint(u) >= 0x3F800000u), 0)) *s_wild = batch;
+}
+
 // Sample i of n (lane i of the team; lanes beyond repeat the last one), uniform u: leaf and value, 0xFFFFFFFF and 0 where
 // nothing can be sampled.
 template <int LOGK, bool MEM>
@@ -518,7 +519,8 @@ __device__ __forceinline__ void walk_tree(const TreeView<MEM>& tv, uint32_t i, u
 //    team then does both in turn.
 //  - Inputs are fetched a step ahead.  That is only right where no step reads what a step returns; the host has checked
 //    it (StreamArgs::ahead).  Where it does not hold, a step's results are stored and waited for before its update and
-//    the inputs of the step behind it are fetched.
+//    the inputs of the step behind it are fetched (a build of its own: as a branch it costs the other lists 2 to 5 %, 50
+//    steps of 100 samples on 15 000 leaves at K = 8 198 -> 214 us).
 //  - The update of step s and the insertion of step s + 1 are adjacent tree changes with nothing read in between: the
 //    leaves are written one after the other and the ancestors of both recomputed in one pass.
 //  - WAVE: with at most 64 samples and 64 new rows the team is one wave, whose LDS accesses stay in order by
@@ -531,7 +533,8 @@ __device__ __forceinline__ void walk_tree(const TreeView<MEM>& tv, uint32_t i, u
 // step before has read (all of whose loads have arrived at the barrier in front of the insertion's stores).
 // 100 steps on 10 000 leaves at K = 16 (32 samples, 4 new rows of 41 bytes): 266 us; 1001 us as one phase after the
 // other by the whole workgroup with a full barrier between them.
-template <int LOGK, bool WAVE, bool MEM>
+// AHEAD: no step reads what a step returns.
+template <int LOGK, bool WAVE, bool MEM, bool AHEAD>
 __global__ void __launch_bounds__(1024)
 k_run_steps(StreamKernelArgs ka) {
   const Geom& g = ka.g;
@@ -539,8 +542,8 @@ k_run_steps(StreamKernelArgs ka) {
   extern __shared__ __attribute__((aligned(16))) float tree[];
   __shared__ LevelTable tab;
   __shared__ uint32_t s_off[kMaxHeight + 2];
-  __shared__ uint32_t s_max, s_vmin[2], s_bmin[2], s_flags, s_arrived;
-  __shared__ uint4 s_runs[16];
+  __shared__ uint32_t s_max, s_vmin[2], s_bmin[2], s_wild, s_flags, s_arrived;
+  __shared__ uint2 s_runs[16];
   __shared__ PieceFields s_rows, s_ins;
   const uint32_t t = blockIdx.x;
   const uint32_t tid = threadIdx.x, lane = tid & 63u;
@@ -551,6 +554,7 @@ k_run_steps(StreamKernelArgs ka) {
   if (tid == 0) {
     s_max = read_max_bits(g, t);
     s_vmin[0] = s_vmin[1] = s_bmin[0] = s_bmin[1] = kNoMin;
+    s_wild = 0;
     s_flags = 0;
     s_arrived = 0;
   }
@@ -579,14 +583,14 @@ k_run_steps(StreamKernelArgs ka) {
     if (ip.on) iv = load_piece(ip.dense, ip.w);
   }
   // inputs of the team: the uniform of the step to sample, value (and index) of the update to apply, inserted priority
-  float u_i = 0.0f, u_next = 0.0f, up_v = 0.0f, in_v = 0.0f, beta_i = 0.0f;   // (beta_i: !ahead only)
+  float u_i = 0.0f, u_next = 0.0f, up_v = 0.0f, in_v = 0.0f;
+  [[maybe_unused]] float beta_i = 0.0f;
   uint32_t up_i = 0;
-  const bool ahead = a.ahead != 0;
   const uint32_t j_ins = WAVE ? lane - (64u - n_ins) : tid;   // (WAVE: the last lanes of the wave, so that samples and rows share it)
   const bool inserts = in_team && (!WAVE || lane >= 64u - n_ins) && j_ins < n_ins;
   if (in_team && tid < B) u_i = a.u[(size_t)t * B + tid];
   if (inserts && a.ins_prio) in_v = a.ins_prio[(size_t)t * n_ins + j_ins];
-  if (!ahead) beta_i = a.beta[0];
+  if constexpr (!AHEAD) beta_i = a.beta[0];
   __syncthreads();
   LdsTree lt;
   lt.tree = tree;
@@ -607,6 +611,7 @@ k_run_steps(StreamKernelArgs ka) {
   tv.N = N;
   tv.s_max = &s_max;
   tv.s_arrived = &s_arrived;
+  tv.s_wild = &s_wild;
   tv.s_runs = s_runs;
   tv.apart = apart;
   tv.team = team;
@@ -630,7 +635,7 @@ k_run_steps(StreamKernelArgs ka) {
         if (a.out_w) {
           const uint32_t vmin = s_vmin[(s - 1) & 1u];
           const uint32_t least = a.buffer_norm ? s_bmin[(s - 1) & 1u] : vmin;
-          w_out = vmin == kNoMin ? 0.0f : importance_weight(v_out, __uint_as_float(least), ahead ? a.beta[s - 1] : beta_i);
+          w_out = vmin == kNoMin ? 0.0f : importance_weight(v_out, __uint_as_float(least), AHEAD ? a.beta[s - 1] : beta_i);
         }
       }
     }
@@ -641,7 +646,7 @@ k_run_steps(StreamKernelArgs ka) {
       if (a.out_prio) a.out_prio[o] = v_out;
       if (a.out_w) a.out_w[o] = w_out;
     };
-    if (s && !ahead) {
+    if (!AHEAD && s) {
       store_results();
       wait_memory();
       lds_barrier();
@@ -656,17 +661,17 @@ k_run_steps(StreamKernelArgs ka) {
       if (more) {
         if (rw < insert_items && ip.on) iv = load_piece(ip.dense + (uint64_t)s * s_ins.step[ip.f], ip.w);
         if (inserts && a.ins_prio) in_v = a.ins_prio[((size_t)s * T + t) * n_ins + j_ins];
-        beta_i = a.beta[s];
+        if constexpr (!AHEAD) beta_i = a.beta[s];
       }
     }
     // ---- the tree: update of the step before, insertion of this one
     const bool do_upd = s > 0 && a.upd_prio != nullptr, do_ins = more && n_ins > 0;
     if (in_team) {
-      const UpdateWork up{do_upd, in_team && tid < B, a.upd_is_sampled != 0, B, a.upd_is_sampled ? node : up_i, upd_size, up_v};
+      const UpdateWork up{do_upd, in_team && tid < B, a.upd_is_sampled != 0, B, a.upd_is_sampled ? node : up_i, upd_size, up_v, s};
       const InsertWork in{do_ins, inserts, a.ins_prio != nullptr, n_ins, inserts ? ring_slot(cursor, j_ins, N) : 0u, in_v};
       change_tree<LOGK, WAVE, MEM>(tv, up, in, max_bits, flags);
       // inputs of the next round
-      if (ahead && tid < B) {
+      if (AHEAD && in_team && tid < B) {
         const size_t bo = ((size_t)s * T + t) * B + tid;
         if (more && a.upd_prio) {
           up_v = a.upd_prio[bo];
@@ -689,9 +694,9 @@ k_run_steps(StreamKernelArgs ka) {
       insert_rows(s_ins, rw + rws, rws, first, N, a.ins.row_stride, s, nullptr);
       wait_memory();
     }
-    if (s && ahead) store_results();
+    if (AHEAD && s) store_results();
     if (!more) break;
-    if (ahead && s + 1 < a.n_steps && n_ins) {
+    if (AHEAD && s + 1 < a.n_steps && n_ins) {
       if (rw < insert_items && ip.on) iv = load_piece(ip.dense + (uint64_t)(s + 1) * s_ins.step[ip.f], ip.w);
       if (inserts && a.ins_prio) in_v = a.ins_prio[((size_t)(s + 1) * T + t) * n_ins + j_ins];
     }
@@ -705,6 +710,7 @@ k_run_steps(StreamKernelArgs ka) {
     }
     // ---- sampling
     if (in_team && (WAVE || (tid & ~63u) < B)) {
+      if constexpr (!WAVE) note_wild(u_i, s + 1u, &s_wild);
       walk_tree<LOGK, MEM>(tv, tid, B, u_i, node, val);
       if (node == 0xFFFFFFFFu) {
         if (tid == 0) flags |= 4u;
@@ -719,7 +725,7 @@ k_run_steps(StreamKernelArgs ka) {
         nodes[tid] = node;
         if (apart) values[tid] = val;
       }
-      if (ahead) u_i = u_next;
+      if constexpr (AHEAD) u_i = u_next;
     }
     lds_barrier();
   }
@@ -783,8 +789,8 @@ k_run_requests(QueueKernelArgs ka) {
   __shared__ per_request s_req[3][kRoundRequests];   // round i: s_req[i % 3]
   __shared__ PieceFields s_rows[2], s_ins[2];        // by parity of the round
   __shared__ uint32_t s_skip[2][32];                 // bit j: row j of the round's insertion is deferred
-  __shared__ uint32_t s_max, s_vmin[2], s_bmin[2], s_flags, s_arrived;
-  __shared__ uint4 s_runs[16];
+  __shared__ uint32_t s_max, s_vmin[2], s_bmin[2], s_wild, s_flags, s_arrived;
+  __shared__ uint2 s_runs[16];
   const uint32_t t = blockIdx.x;
   const uint32_t tid = threadIdx.x, lane = tid & 63u;
   const uint32_t H = g.H, N = g.N, n_requests = a.n_requests;
@@ -796,6 +802,7 @@ k_run_requests(QueueKernelArgs ka) {
   if (tid == 0) {
     s_max = read_max_bits(g, t);
     s_vmin[0] = s_vmin[1] = s_bmin[0] = s_bmin[1] = kNoMin;
+    s_wild = 0;
     s_flags = 0;
     s_arrived = 0;
   }
@@ -846,6 +853,7 @@ k_run_requests(QueueKernelArgs ka) {
   tv.N = N;
   tv.s_max = &s_max;
   tv.s_arrived = &s_arrived;
+  tv.s_wild = &s_wild;
   tv.s_runs = s_runs;
   tv.apart = apart;
   tv.team = team;
@@ -863,6 +871,7 @@ k_run_requests(QueueKernelArgs ka) {
   uint32_t up_i = 0;
   RowItem ip;
   uint4 iv;
+  uint32_t sampled = 0;                    // sampling requests so far
   uint32_t sample_n = 0, before_smp = 3;   // the sampling request of the round before: its batch (0: none) and place
   auto inserted_by = [&](const per_request& q) -> uint32_t {   // the row of the insertion that this lane places (>= n: none)
     const uint32_t j = WAVE ? lane - (64u - q.n) : tid;
@@ -967,6 +976,7 @@ k_run_requests(QueueKernelArgs ka) {
         up.i = w.idx ? up_i : node;
         up.size = size;
         up.v = up_v;
+        up.batch = sampled;
       }
       InsertWork in{};
       in.on = do_ins;
@@ -1021,6 +1031,7 @@ k_run_requests(QueueKernelArgs ka) {
     sample_n = smp ? wave_value(smp->n) : 0u;
     before_smp = cur.smp;
     if (smp) {
+      ++sampled;
       // ---- weights relative to the whole tree: its smallest positive leaf
       if (a.buffer_norm && smp->out_weight && in_rows) {
         uint32_t m = kNoMin;
@@ -1030,6 +1041,7 @@ k_run_requests(QueueKernelArgs ka) {
       }
       // ---- sampling
       if (in_team && (WAVE || (tid & ~63u) < sample_n)) {
+        if constexpr (!WAVE) note_wild(u_i, sampled, &s_wild);
         walk_tree<LOGK, MEM>(tv, tid, sample_n, u_i, node, val);
         if (node == 0xFFFFFFFFu) {
           if (tid == 0) flags |= 4u;
@@ -1091,17 +1103,22 @@ static hipError_t launch_run_steps_k(const Geom& g, const Tuning& tn, StreamArgs
   // always the largest workgroup, also for small batches: measured faster than a workgroup of the batch's
   // size (the tree copy and the row movers use all lanes)
   const bool wave = a.B <= 64 && a.n_insert <= 64, mem = ka.a.leaves_in_memory != 0;
-#define PER_RUN(W, M)                                                                                   \
+#define PER_RUN(W, M, A)                                                                                \
   do {                                                                                                  \
-    hipError_t e = grant_lds<&k_run_steps<LOGK, W, M>>(tn, bytes);                                      \
+    hipError_t e = grant_lds<&k_run_steps<LOGK, W, M, A>>(tn, bytes);                                   \
     if (e != hipSuccess) return e;                                                                      \
-    PER_LAUNCH(KID_RUN_STEPS, (k_run_steps<LOGK, W, M>), dim3(g.T), dim3(1024), bytes, s, ka);          \
+    PER_LAUNCH(KID_RUN_STEPS, (k_run_steps<LOGK, W, M, A>), dim3(g.T), dim3(1024), bytes, s, ka);       \
+  } while (0)
+#define PER_RUN_WHERE(W, A)                                                                             \
+  do {                                                                                                  \
+    if (mem) PER_RUN(W, true, A); else PER_RUN(W, false, A);                                            \
   } while (0)
   if (wave) {
-    if (mem) PER_RUN(true, true); else PER_RUN(true, false);
+    if (a.ahead) PER_RUN_WHERE(true, true); else PER_RUN_WHERE(true, false);
   } else {
-    if (mem) PER_RUN(false, true); else PER_RUN(false, false);
+    if (a.ahead) PER_RUN_WHERE(false, true); else PER_RUN_WHERE(false, false);
   }
+#undef PER_RUN_WHERE
 #undef PER_RUN
   return hipGetLastError();
 }
