@@ -531,7 +531,7 @@ __device__ __forceinline__ void walk_tree(const TreeView<MEM>& tv, uint32_t i, u
 // The order that memory needs: the stored rows of an insertion are read by the gather of the same step at the earliest
 // (its lanes wait for their stores before the barrier that ends the sampling), and overwrite what the gather of the
 // step before has read (all of whose loads have arrived at the barrier in front of the insertion's stores).
-// 100 steps on 10 000 leaves at K = 16 (32 samples, 4 new rows of 41 bytes): 266 us; 1001 us as one phase after the
+// 100 steps on 10 000 leaves at K = 16 (32 samples, 4 new rows of 41 bytes): 268 us; 1001 us as one phase after the
 // other by the whole workgroup with a full barrier between them.
 // AHEAD: no step reads what a step returns.
 template <int LOGK, bool WAVE, bool MEM, bool AHEAD>
@@ -750,7 +750,7 @@ k_run_steps(StreamKernelArgs ka) {
 // Fetching ahead is only right where a request reads nothing that one just before it writes (an update whose index
 // array is the sampled one, say).  The host has checked that (QueueArgs::ahead); where it does not hold, every
 // request is a round of its own with an empty one behind it, which brings all results to memory.
-// 20 times (insert 16 rows, sample 512, update them) on 30 000 leaves at K = 16: 191 us; 353 us one request after the
+// 20 times (insert 16 rows, sample 512, update them) on 30 000 leaves at K = 16: 193 us; 353 us one request after the
 // other by the whole workgroup with a full barrier between their phases.
 struct QueueKernelArgs {            // one kernel argument (Geom first: see fill_level_table)
   Geom g;
