@@ -97,7 +97,8 @@ int per_destroy(per_t* p);
  * call started).  Ancestors are re-summed.  n <= N.
  *   d_field_src : HOST array of n_fields DEVICE pointers, each [T][n][field_bytes[f]];
  *                 may be NULL (or hold NULLs) to leave payload columns untouched.
- *   d_out_idx   : [T][n] slots written, or NULL.
+ *   d_out_idx   : [T][n] slots written, or NULL.  They may go to memory that d_field_src or d_prio are read from
+ *                 (a small kernel behind the insertion stores them then).
  * An invalid explicit priority skips the leaf write (row is still stored) and sets
  * PER_FLAG_BAD_PRIORITY. */
 int per_insert(per_t* p, uint32_t n, const void* const* d_field_src, const float* d_prio,

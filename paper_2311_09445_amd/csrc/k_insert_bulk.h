@@ -368,3 +368,16 @@ hipError_t launch_insert_bulk(const Geom& g, const Tuning& tn, const FieldTable*
   PER_DISPATCH_LOGK(g.logK, CALL)
 #undef CALL
 }
+
+// The slots of an insertion by themselves, for calls that return them where they are read from: behind the insertion.
+__global__ void __launch_bounds__(256)
+k_write_slots(uint32_t n, uint32_t cursor, uint32_t N, uint32_t* __restrict__ out_idx) {
+  const uint32_t j = blockIdx.x * 256u + threadIdx.x;
+  if (j >= n) return;
+  const uint64_t slot = (uint64_t)cursor + j;
+  out_idx[(size_t)blockIdx.y * n + j] = (uint32_t)(slot >= N ? slot - N : slot);
+}
+hipError_t launch_write_slots(const Geom& g, const Tuning& tn, uint32_t n, uint32_t cursor, uint32_t* out_idx, hipStream_t s) {
+  PER_LAUNCH(KID_WRITE_SLOTS, k_write_slots, dim3((uint32_t)(((uint64_t)n + 255) / 256), g.T), dim3(256), 0, s, n, cursor, g.N, out_idx);
+  return hipGetLastError();
+}

@@ -366,6 +366,22 @@ int per_destroy(per_t* p) {
   return PER_OK;
 }
 
+// true when byte ranges [a, a+na) and [b, b+nb) share a byte (null ranges share nothing)
+static bool ranges_overlap(const void* a, size_t na, const void* b, size_t nb) {
+  if (!a || !b) return false;
+  const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
+  return x < y + nb && y < x + na;
+}
+
+// Do the slots that an insertion of n rows per tree returns go to memory that it reads rows or priorities from?
+static bool slots_over_inputs(const per_t* p, uint32_t n, const void* const* d_field_src, const float* d_prio, const uint32_t* d_out_idx) {
+  const size_t rows = (size_t)p->g.T * n;
+  bool over = ranges_overlap(d_out_idx, rows * 4, d_prio, rows * 4);
+  for (uint32_t f = 0; d_field_src && f < p->cfg.n_fields; ++f)
+    over = over || ranges_overlap(d_out_idx, rows * 4, d_field_src[f], rows * p->cfg.field_bytes[f]);
+  return over;
+}
+
 static int insert_impl(per_t* p, uint32_t n, const void* const* d_field_src, const float* d_prio, uint32_t* d_out_idx,
                        uint32_t n_protect, const uint32_t* d_protect, void* stream) {
   if (!p) return PER_EINVAL;
@@ -382,6 +398,9 @@ static int insert_impl(per_t* p, uint32_t n, const void* const* d_field_src, con
   const bool has_rows = fill_fields(p, const_cast<void* const*>(reinterpret_cast<const void* const*>(d_field_src)), &ft);
   const bool one_workgroup = insert_fits_one_workgroup(p->g, has_rows ? &ft : nullptr, n);
   if (n_protect && !one_workgroup) return PER_ERANGE;   // the protected form exists for small inserts only
+  // (rows, priorities and slots are the work of workgroups that run side by side: slots that go over what is read come last)
+  uint32_t* slots_last = !n_protect && slots_over_inputs(p, n, d_field_src, d_prio, d_out_idx) ? d_out_idx : nullptr;
+  if (slots_last) d_out_idx = nullptr;
   // The one-workgroup kernel serves protected insertions, and the smallest ones on trees whose top is not left to its next
   // reader (it goes up to the root with its nodes in registers; 4 rows on 4096 leaves at K = 2: 6.0 us against 7.1 by the
   // kernel of large insertions, 16 rows: 6.5 against 6.7, 64 rows: 7.1 against 6.7).  Everywhere else the other one is
@@ -391,10 +410,11 @@ static int insert_impl(per_t* p, uint32_t n, const void* const* d_field_src, con
     hipError_t e1 = launch_insert_small(p->g, p->tn, has_rows ? &ft : nullptr, n, cursor, d_prio, d_out_idx, p->stale_hb,
                                         n_protect ? d_protect : nullptr, n_protect, tracks_min(p), s);
     if (e1 != hipSuccess) return PER_EHIP;   // nothing was enqueued: the mirrors stay
+    if (slots_last) e1 = launch_write_slots(p->g, p->tn, n, cursor, slots_last, s);
     p->stale_hb = 0;
     p->cursor = (p->cursor + n) % N;
     p->size = p->size + n > N ? N : p->size + n;
-    return PER_OK;
+    return hip_rc(e1);
   }
   // one kernel for rows, leaves and the heights of the touched subtrees; the heights above are left stale, or re-summed
   const uint32_t hb = lazy_top_height(p->g, p->tn);
@@ -402,6 +422,7 @@ static int insert_impl(per_t* p, uint32_t n, const void* const* d_field_src, con
   const bool track = tracks_min(p);
   if (!track) p->min_stale = true;
   if (e == hipSuccess) e = launch_insert_bulk(p->g, p->tn, has_rows ? &ft : nullptr, n, cursor, d_prio, d_out_idx, track, s);
+  if (e == hipSuccess && slots_last) e = launch_write_slots(p->g, p->tn, n, cursor, slots_last, s);
   if (hb) p->stale_hb = hb;
   // the mirrors advance even if a later launch failed: rows already enqueued have been placed
   p->cursor = (p->cursor + n) % N;
@@ -445,13 +466,6 @@ static int check_update_args(per_t* p, uint32_t B, const uint32_t* d_idx, const 
   if (!d_idx || !d_prio || misaligned(d_idx, 4) || misaligned(d_prio, 4)) return PER_EINVAL;
   if ((uint64_t)B * 16 > 0x7FFFFFFFull) return PER_ERANGE;
   return PER_OK;
-}
-
-// true when byte ranges [a, a+na) and [b, b+nb) share a byte (null ranges share nothing)
-static bool ranges_overlap(const void* a, size_t na, const void* b, size_t nb) {
-  if (!a || !b) return false;
-  const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
-  return x < y + nb && y < x + na;
 }
 
 static int sample_impl(per_t* p, uint32_t B, float beta, const float* d_u, uint32_t* d_out_idx, float* d_out_weight,
@@ -633,7 +647,7 @@ int per_insert_step(per_t* p, uint32_t n, const void* const* d_field_src, const 
   InsertRide ride{};
   const bool has_rows = fill_fields(p, const_cast<void* const*>(reinterpret_cast<const void* const*>(d_field_src)), &ride.rows);
   if (!has_rows) ride.rows = FieldTable{};
-  bool carried = p->tn.insert_ride && p->weight_norm == PER_NORM_BATCH &&
+  bool carried = p->tn.insert_ride && p->weight_norm == PER_NORM_BATCH && !slots_over_inputs(p, n, d_field_src, d_ins_prio, d_ins_out_idx) &&
                  sample_can_carry_insert(p->g, p->tn, B, has_rows ? &ride.rows : nullptr, n, (uint32_t)p->cursor);
   for (const void* o : outs) {
     carried = carried && !ranges_overlap(d_ins_prio, n_ins, o, n_out);

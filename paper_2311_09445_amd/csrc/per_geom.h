@@ -217,7 +217,7 @@ struct InsertRide : InsertRideHead {
 enum KernelId {
   KID_FILL, KID_SAMPLE, KID_WEIGHTS, KID_GATHER, KID_FINISH, KID_INSERT_BULK, KID_RESUM_DENSE,
   KID_RESUM_TAIL, KID_UPDATE_CLAIM, KID_UPDATE_TREE, KID_TREE_FINISH, KID_UPDATE_DELTA, KID_GET_PRIORITY,
-  KID_INSERT_SMALL, KID_RUN_STEPS, KID_RUN_REQUESTS, KID_MIN_REBUILD, KID_MIN_REDUCE, KID_STEP, KID_STEP_TABLES, KID_STEP_EPILOGUE, KID_COUNT
+  KID_INSERT_SMALL, KID_RUN_STEPS, KID_RUN_REQUESTS, KID_MIN_REBUILD, KID_MIN_REDUCE, KID_STEP, KID_STEP_TABLES, KID_STEP_EPILOGUE, KID_WRITE_SLOTS, KID_COUNT
 };
 const char* kernel_name(int kid);
 
@@ -269,6 +269,7 @@ hipError_t launch_gather(const Geom& g, const Tuning& tn, const FieldTable& ft, 
                          hipStream_t s);
 hipError_t launch_insert_bulk(const Geom& g, const Tuning& tn, const FieldTable* rows, uint32_t n, uint32_t cursor, const float* prio,
                               uint32_t* out_idx, bool track_min, hipStream_t s);
+hipError_t launch_write_slots(const Geom& g, const Tuning& tn, uint32_t n, uint32_t cursor, uint32_t* out_idx, hipStream_t s);
 bool insert_fits_one_workgroup(const Geom& g, const FieldTable* ft, uint32_t n);
 hipError_t launch_insert_small(const Geom& g, const Tuning& tn, const FieldTable* ft, uint32_t n, uint32_t cursor,
                                const float* prio, uint32_t* out_idx, uint32_t stale_hb, const uint32_t* protect,

@@ -1426,6 +1426,39 @@ def test_insertions_of_many_rows(K, N, T, fb, sizes, norm):
     m.compare_status()
 
 
+@pytest.mark.parametrize("K,N,T,fb,n", [(16, 70001, 1, (4,), 5), (2, 3000, 1, (4, 8), 9), (16, 70001, 2, (4,), 60000), (8, 70001, 1, (16, 4), 33000),
+                                        (32, 200001, 1, (160, 4), 150000), (64, 30001, 8, (4, 128), 16)])
+@pytest.mark.parametrize("in_step", [False, True])
+def test_insertion_returns_slots_where_its_rows_lie(K, N, T, fb, n, in_step):
+    """The slots of an insertion go to the memory that a field of its rows (or its priorities) is read from: rows and
+    priorities are read first."""
+    log(f"slots over rows K={K} N={N} T={T} fb={fb} n={n} in_step={in_step}")
+    rng = np.random.default_rng(n)
+    m = Mirror(K, N, T, fb)
+    m.insert(N, prio=wl._draw_priorities("exponential_1", rng, (T, N)))
+    m.update(m.sample(wl.uniform01(rng, (T, 64)), 0.5)[1], np.ones((T, 64), np.float32))
+    for over in ("rows", "priorities"):
+        rows = [rng.integers(0, 256, (T, n, b)).astype(np.uint8) for b in fb]
+        prio = (rng.random((T, n)) * 4).astype(np.float32)
+        d_rows, d_prio = [dev(r) for r in rows], dev(prio)
+        out = d_rows[fb.index(4)].view(-1).view(torch.int32).view(T, n) if over == "rows" else d_prio.view(torch.int32)
+        slots = m.cpu.insert(n, rows, prio)
+        if in_step:
+            u, up = wl.uniform01(rng, (T, 64)), (rng.random((T, 64)) * 2).astype(np.float32)
+            gi, _, _ = m.gpu.step(dev(u), 0.5, dev(up), insert=(n, d_rows, d_prio, out))
+            ci, _, _ = m.cpu.sample(u, 0.5, True)
+            assert np.array_equal(idx_to_host(gi), ci), "sampled indices"
+            m.cpu.update(ci, up)
+        else:
+            m.gpu.insert(n, d_rows, d_prio, out)
+        assert np.array_equal(idx_to_host(out), slots), "slots"
+        got = m.gpu.gather(idx_to_dev(slots))
+        for f, r in enumerate(rows):
+            assert np.array_equal(got[f].cpu().numpy(), r), f"rows of field {f} ({over})"
+        m.compare_tree()
+    m.compare_status()
+
+
 @pytest.mark.parametrize("K,N", [(K, (2048 if K == 2 else 64) * K + extra) for K in (2, 4, 8, 16, 32, 64) for extra in (0, 1)] +
                          [(2, 4096 * 128 + 1), (2, 4096 * 512 + 1), (4, 4096 * 256 + 1), (8, 4096 * 512 + 1)])
 def test_subtrees_of_the_tree_pass(K, N):
