@@ -28,6 +28,25 @@ struct StreamKernelArgs {           // one kernel argument, so that both parts s
   StreamArgs a;
 };
 
+// The copy of the tree is held as levels of wide groups.  Every stored height of a narrow tree (K = 2, 4) costs the walk
+// and the pass over the ancestors a trip through LDS of its own, whatever its fanout, and a node is nothing but the
+// pairwise sum of what lies under it: the copy keeps every fourth height of a K = 2 tree and every second of a K = 4
+// one, a level then has sixteen children like the heights of a K = 16 tree, with the same sums in the same order.  The
+// heights between two levels are worked out once, when the tree goes back to memory.  (K = 2, 4096 leaves: three levels
+// for twelve heights; 50 steps of 64 samples and 4 new rows on it 231 -> 124 us, with what walk_tree and sum_top save.)
+template <int LOGK>
+struct Wide {
+  static constexpr int LOGR = LOGK <= 2 ? 4 : LOGK;   // log2 of a level's children
+  static constexpr int R = 1 << LOGR;
+  static constexpr int LH = LOGR / LOGK;              // heights a level spans
+};
+// Height of level v (level V, the root's, may span fewer heights than the others).
+template <int LOGK>
+__device__ __forceinline__ uint32_t level_height(uint32_t v, uint32_t H) {
+  const uint32_t h = v * (uint32_t)Wide<LOGK>::LH;
+  return h < H ? h : H;
+}
+
 // Sum of the 4*N children behind g4 in the balanced pairwise order, by a single lane.
 template <int N, typename P>
 __device__ __forceinline__ float sum_chunks(P grp) {
@@ -38,59 +57,90 @@ __device__ __forceinline__ float sum_chunks(P grp) {
     return sum_chunks<N / 2>(grp) + sum_chunks<N / 2>(grp + 2 * N);
   }
 }
-template <int LOGK, typename P>
-__device__ __forceinline__ float lane_group_sum(P grp) {
-  if constexpr (LOGK == 1) {
-    const Floats2 c = load_floats2(grp);
-    return c.x + c.y;
-  } else {
-    return sum_chunks<(1 << LOGK) / 4>(grp);
-  }
-}
 
 // One tree in the LDS of its workgroup.
 struct LdsTree {
-  float* tree;              // heights 0 .. H back to back, zero padding included (height 0 left out when leaves_mem is set)
+  float* tree;              // levels 0 .. V back to back (level 0 left out when leaves_mem is set), each padded with zeros to
+                            // whole groups and, below the root's children, with one group more: what the nodes beyond the
+                            // next level's last have for children
   float* leaves_mem;        // null, or the tree's leaves in memory (zero padded to whole groups)
-  const uint32_t* off;      // off[h]: where height h starts (floats); off[H + 1]: all floats
+  const uint32_t *off, *n;  // off[v]: where level v starts (floats), off[V + 1]: all floats; n[v]: its real nodes
   uint32_t* max_bits;       // running maximum priority (fp32 bits)
-  uint32_t H, N;
+  uint32_t H, V;
 };
 
-// Loads every height of tree t into LDS (lanes 64 .. 64 + H + 1 have filled s_off, lane 0 the maximum).  The heights
-// are arrays of their own in memory and lie back to back in LDS; the copy runs over the LDS floats as one range, eight
-// per lane in flight and all loads of a round before its first store, so that a tree of a dozen heights is not a dozen
-// trips to memory one after the other.
+// Loads every level of tree t into LDS.  The heights are arrays of their own in memory (zero padded to 64 floats) and the
+// levels lie back to back in LDS; the copy runs over the LDS floats as one range, four 16-byte pieces per lane in flight
+// and all loads of a round before its first store.
+template <int LOGK>
 __device__ __forceinline__ void lds_tree_load(const LevelTable& tab, const LdsTree& lt) {
-  constexpr int R = 8;
-  const uint32_t h_first = lt.leaves_mem ? 1u : 0u;
-  const uint32_t begin = lt.off[h_first], end = lt.off[lt.H + 1];
-  for (uint32_t base = begin; base < end; base += (uint32_t)R * blockDim.x) {
-    float v[R];
-    uint32_t h = h_first;   // (the height of this lane's element: found anew per round, then it only grows)
+  constexpr int R = 4;
+  const uint32_t v_first = lt.leaves_mem ? 1u : 0u;
+  const uint32_t begin = lt.off[v_first], end = lt.off[lt.V + 1];
+  for (uint32_t base = begin; base < end; base += 4u * R * blockDim.x) {
+    Floats4 x[R];
+    uint32_t v = v_first;   // (the level of this lane's piece: found anew per round, then it only grows)
 #pragma unroll
     for (int k = 0; k < R; ++k) {
-      const uint32_t e = base + (uint32_t)k * blockDim.x + threadIdx.x;
-      v[k] = 0.0f;
+      const uint32_t e = base + 4u * ((uint32_t)k * blockDim.x + threadIdx.x);
       if (e < end) {
-        while (h < lt.H && e >= lt.off[h + 1]) ++h;
-        v[k] = tab.lvl[h][e - lt.off[h]];
+        while (v < lt.V && e >= lt.off[v + 1]) ++v;
+        const uint32_t i = e - lt.off[v];
+        x[k] = Floats4{0.0f, 0.0f, 0.0f, 0.0f};
+        if (i < lt.n[v]) x[k] = load_floats4(as_global(static_cast<const float*>(tab.lvl[level_height<LOGK>(v, lt.H)])) + i);
       }
     }
 #pragma unroll
     for (int k = 0; k < R; ++k) {
-      const uint32_t e = base + (uint32_t)k * blockDim.x + threadIdx.x;
-      if (e < end) lt.tree[e] = v[k];
+      const uint32_t e = base + 4u * ((uint32_t)k * blockDim.x + threadIdx.x);
+      if (e < end) *reinterpret_cast<Floats4*>(lt.tree + e) = x[k];
+    }
+  }
+}
+// The heights between level v and the next one, from a group of sixteen at level v: a lane per group.  (Nodes beyond a
+// height's last are zero, as its padding is.)
+template <int LOGK, typename P>
+__device__ __forceinline__ void store_between(P grp, uint32_t p, uint32_t h0, const LevelTable& tab, uint32_t H) {
+  float x[16];
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+    const Floats4 q = load_floats4(grp + 4 * c);
+    x[4 * c] = q.x, x[4 * c + 1] = q.y, x[4 * c + 2] = q.z, x[4 * c + 3] = q.w;
+  }
+#pragma unroll
+  for (int d = 1; d < 4; ++d) {   // x: the sums of blocks of 2^d
+#pragma unroll
+    for (int i = 0; i < (16 >> d); ++i) x[i] = x[2 * i] + x[2 * i + 1];
+    const uint32_t h = h0 + (uint32_t)(d / LOGK);
+    if (d % LOGK == 0 && h <= H) {
+      GlobalPtr<float> at = as_global(tab.lvl[h]) + (size_t)p * (16 >> d);
+#pragma unroll
+      for (int i = 0; i < (16 >> d); i += 2) *(GlobalPtr<Floats2>)(at + i) = Floats2{x[i], x[i + 1]};
     }
   }
 }
 // ... and back to memory, with the running maximum and the flags the lanes have collected.
+template <int LOGK>
 __device__ __forceinline__ void lds_tree_store(const Geom& g, uint32_t t, const LevelTable& tab, const LdsTree& lt,
                                                uint32_t flags, uint32_t* s_flags) {
-  for (uint32_t h = lt.leaves_mem ? 1u : 0u; h <= lt.H; ++h) {
-    float* lvl = tab.lvl[h];
-    const float* src = lt.tree + lt.off[h];
-    for (uint32_t e = threadIdx.x; e < tab.n[h]; e += blockDim.x) lvl[e] = src[e];
+  constexpr uint32_t LH = Wide<LOGK>::LH, R = Wide<LOGK>::R;
+  const uint32_t V = lt.V, H = lt.H;
+  // (a root less than a whole level above its children is stored by the pass below: the level's sum of it has zeros added)
+  const uint32_t end = V * LH == H ? lt.off[V + 1] : lt.off[V];
+  uint32_t v = lt.leaves_mem ? 1u : 0u;
+  for (uint32_t e = lt.off[v] + 4u * threadIdx.x; e < end; e += 4u * blockDim.x) {
+    while (v < V && e >= lt.off[v + 1]) ++v;
+    const uint32_t i = e - lt.off[v];
+    if (i < lt.n[v]) *(GlobalPtr<Floats4>)(as_global(tab.lvl[level_height<LOGK>(v, H)]) + i) = load_floats4(lt.tree + e);
+  }
+  if constexpr (LH > 1) {
+    for (uint32_t w = 0; w < V; ++w) {
+      const uint32_t groups = tab.n[level_height<LOGK>(w + 1, H)];
+      for (uint32_t p = threadIdx.x; p < groups; p += blockDim.x) {
+        if (w == 0 && lt.leaves_mem) store_between<LOGK>(as_global(static_cast<const float*>(lt.leaves_mem)) + (size_t)p * R, p, 0, tab, H);
+        else store_between<LOGK>(static_cast<const float*>(lt.tree) + lt.off[w] + (size_t)p * R, p, w * LH, tab, H);
+      }
+    }
   }
   if (threadIdx.x == 0) g.max_v[t] = __uint_as_float(*lt.max_bits);
   if (flags) atomicOr(s_flags, flags);
@@ -281,12 +331,14 @@ __device__ __forceinline__ void wave_order() {
 // The tree work of one round, as the lanes of the team see it.  MEM: the leaves are in memory.  (A compile-time choice:
 // one pointer for both places would make flat accesses, and the wait for one of those is a wait for every load and
 // store the wave has under way; a branch at every access costs the registers of both sides.)
+constexpr uint32_t kTopNodes = 128;   // a level of at most this many nodes is summed by one wave, with all levels above it
 template <bool MEM>
 struct TreeView {
   float* tree;               // the LDS copy
-  float* leaves;             // MEM: the leaves (else they are in the copy, height 0 at offset 0)
-  uint32_t off_reg, n_reg;   // lane h of every wave: off[h], real nodes of height h (read from there: an LDS trip less per height)
-  uint32_t H, N;
+  float* leaves;             // MEM: the leaves (else they are in the copy, level 0 at offset 0)
+  uint32_t off_reg, n_reg;   // lane v of every wave: off[v], real nodes of level v (read from there: an LDS trip less per level)
+  uint32_t V, N;
+  uint32_t vt;               // the lowest level above the leaves of at most kTopNodes nodes
   uint32_t* s_max;           // running maximum (WAVE: the team keeps its own copy)
   uint32_t* s_arrived;       // team waves that have come to one of its barriers, over all barriers (LDS)
   bool apart;                // there are waves outside the team
@@ -294,7 +346,7 @@ struct TreeView {
   uint32_t* s_wild;          // the latest sampling with a uniform outside [0, 1) (0: none)
   uint2* s_runs;             // [16] of every team wave: the leaf its elements begin with, what is known of them (see change_tree)
   uint32_t met;              // what s_arrived has to reach at the team's next barrier, less a team's waves
-  __device__ __forceinline__ uint32_t off(uint32_t h) const { return (uint32_t)__builtin_amdgcn_readlane((int)off_reg, (int)h); }
+  __device__ __forceinline__ uint32_t off(uint32_t v) const { return (uint32_t)__builtin_amdgcn_readlane((int)off_reg, (int)v); }
   __device__ __forceinline__ void set_leaf(uint32_t i, float v) const {
     if constexpr (MEM) as_global(leaves)[i] = v;
     else tree[i] = v;
@@ -303,7 +355,7 @@ struct TreeView {
     if constexpr (MEM) return as_global(leaves)[i];
     else return tree[i];
   }
-  __device__ __forceinline__ uint32_t n(uint32_t h) const { return (uint32_t)__builtin_amdgcn_readlane((int)n_reg, (int)h); }
+  __device__ __forceinline__ uint32_t n(uint32_t v) const { return (uint32_t)__builtin_amdgcn_readlane((int)n_reg, (int)v); }
   // Barrier of the team between phases that hand leaves or sums to other waves of it.  The hardware's barrier would hold
   // the team until the row waves come by; the team's waves count themselves in LDS instead (all of them are resident, and
   // each comes to every barrier, so the wait ends).
@@ -320,13 +372,66 @@ struct TreeView {
     asm volatile("" ::: "memory");
   }
 };
+// Sum of the children of node `parent` of level v, by a single lane.
 template <int LOGK, bool MEM>
-__device__ __forceinline__ float child_group_sum(const TreeView<MEM>& v, uint32_t h, uint32_t parent) {
-  constexpr int K = Fan<LOGK>::K;
+__device__ __forceinline__ float child_group_sum(const TreeView<MEM>& tv, uint32_t v, uint32_t parent) {
+  constexpr int R = Wide<LOGK>::R;
   if constexpr (MEM) {
-    if (h == 1) return lane_group_sum<LOGK>(as_global(v.leaves) + (size_t)parent * K);
+    if (v == 1) return sum_chunks<R / 4>(as_global(static_cast<const float*>(tv.leaves)) + (size_t)parent * R);
   }
-  return lane_group_sum<LOGK>(v.tree + v.off(h - 1) + (size_t)parent * K);
+  return sum_chunks<R / 4>(static_cast<const float*>(tv.tree) + tv.off(v - 1) + (size_t)parent * R);
+}
+
+// x of the lane whose number differs in bit STEP, where the lanes of a block of 2^STEP all hold the same value (see
+// butterfly_move; from sixteen lanes on two halves of a register pair trade rows).
+template <int STEP>
+__device__ __forceinline__ float add_other_half(float x) {
+  if constexpr (STEP <= 3) {
+    return x + __int_as_float(butterfly_move<STEP>(__float_as_int(x)));
+  } else {
+    const unsigned b = __float_as_uint(x);
+    auto p = [&] {
+      if constexpr (STEP == 4) return __builtin_amdgcn_permlane16_swap(b, b, false, false);
+      else return __builtin_amdgcn_permlane32_swap(b, b, false, false);
+    }();
+    return __uint_as_float(p[0]) + __uint_as_float(p[1]);
+  }
+}
+// The sums over blocks of 2, 4, .. 64 lanes of x, the nodes of level vt from node `base` on; those that are nodes of a
+// level below the root are stored.  Returns the sum of all.
+template <int LOGR, int STEP, bool MEM>
+__device__ __forceinline__ float sums_above(const TreeView<MEM>& tv, float x, uint32_t base) {
+  if constexpr (STEP < 6) {
+    x = add_other_half<STEP>(x);
+    constexpr uint32_t done = STEP + 1;
+    if constexpr (done % LOGR == 0) {
+      const uint32_t lane = threadIdx.x & 63u, v = tv.vt + done / LOGR, node = (base + lane) >> done;
+      if (v < tv.V && (lane & ((1u << done) - 1u)) == 0 && node < tv.n(v)) tv.tree[tv.off(v) + node] = x;
+    }
+    return sums_above<LOGR, STEP + 1>(tv, x, base);
+  } else {
+    return x;
+  }
+}
+// The levels from vt up, recomputed whole by one wave: a lane or two per node of level vt, and above it no trips through
+// LDS, only sums of neighbouring lanes (a height of sixteen children was a trip and a chain of 450 cycles, whatever its
+// few nodes).  Returns the root.
+template <int LOGK, bool MEM>
+__device__ __forceinline__ float sum_top(const TreeView<MEM>& tv) {
+  constexpr int LOGR = Wide<LOGK>::LOGR;
+  const uint32_t lane = threadIdx.x & 63u, n = tv.n(tv.vt), at = tv.off(tv.vt);
+  const bool two = n > 64u;
+  float x = 0.0f, y = 0.0f;
+  if (lane < n) x = child_group_sum<LOGK, MEM>(tv, tv.vt, lane);
+  if (two && lane + 64u < n) y = child_group_sum<LOGK, MEM>(tv, tv.vt, lane + 64u);
+  if (lane < n) tv.tree[at + lane] = x;
+  x = sums_above<LOGR, 0>(tv, x, 0u);
+  if (two) {
+    if (lane + 64u < n) tv.tree[at + 64u + lane] = y;
+    x = x + sums_above<LOGR, 0>(tv, y, 64u);
+  }
+  if (tv.vt < tv.V && lane == 0) tv.tree[tv.off(tv.V)] = x;
+  return x;
 }
 
 // An update of n elements (lane tid < n of the team: leaf ui gets uv) and then an insertion (lanes with `inserts`: row at
@@ -342,9 +447,11 @@ struct InsertWork {
   uint32_t n, slot;
   float v;
 };
+// (WAVE: total is the root; else it is read from the copy)
 template <int LOGK, bool WAVE, bool MEM>
 __device__ __forceinline__ void change_tree(TreeView<MEM>& tv, const UpdateWork& u, const InsertWork& ins, uint32_t& max_bits,
-                                            uint32_t& flags) {
+                                            uint32_t& flags, float& total) {
+  constexpr int LOGR = Wide<LOGK>::LOGR;
   const uint32_t tid = threadIdx.x;
   bool valid = false, placed = false;
   if (u.on) {
@@ -446,38 +553,33 @@ __device__ __forceinline__ void change_tree(TreeView<MEM>& tv, const UpdateWork&
       for (int pass = 0; pass < (together ? 1 : 2); ++pass) {
         const bool act = together ? valid || placed : pass == 0 ? valid : placed;
         const uint32_t leaf = together ? (placed ? ins.slot : u.i) : pass == 0 ? u.i : ins.slot;
-        for (uint32_t h = 1; h <= tv.H; ++h) {
+        for (uint32_t v = 1; v < tv.vt; ++v) {
           wave_order();
           if (act) {
-            const uint32_t parent = leaf >> (h * LOGK);
-            tv.tree[tv.off(h) + parent] = child_group_sum<LOGK, MEM>(tv, h, parent);
+            const uint32_t parent = leaf >> (v * LOGR);
+            tv.tree[tv.off(v) + parent] = child_group_sum<LOGK, MEM>(tv, v, parent);
           }
         }
       }
       wave_order();
+      total = sum_top<LOGK, MEM>(tv);
+      wave_order();
     } else {
-      // A height of no more nodes than there are elements is recomputed whole (fewer lanes than elements); from the
-      // first height of at most 64 nodes on one wave goes up to the root without barriers.
+      // A level of no more nodes than there are elements is recomputed whole (fewer lanes than elements).
       const uint32_t elements = (u.on ? u.n : 0u) + (ins.on ? ins.n : 0u);
-      for (uint32_t h = 1; h <= tv.H; ++h) {
+      for (uint32_t v = 1; v < tv.vt; ++v) {
         tv.sync();
-        const uint32_t nodes = tv.n(h);
-        if (nodes <= 64u) {
-          if (tid < 64u)
-            for (; h <= tv.H; ++h) {
-              if (tid < tv.n(h)) tv.tree[tv.off(h) + tid] = child_group_sum<LOGK, MEM>(tv, h, tid);
-              wave_order();
-            }
-          break;
-        }
+        const uint32_t nodes = tv.n(v);
         if (nodes <= elements) {
-          for (uint32_t j = tid; j < nodes; j += tv.team) tv.tree[tv.off(h) + j] = child_group_sum<LOGK, MEM>(tv, h, j);
+          for (uint32_t j = tid; j < nodes; j += tv.team) tv.tree[tv.off(v) + j] = child_group_sum<LOGK, MEM>(tv, v, j);
           continue;
         }
-        const uint32_t pu = u.i >> (h * LOGK), pi = ins.slot >> (h * LOGK);
-        if (valid) tv.tree[tv.off(h) + pu] = child_group_sum<LOGK, MEM>(tv, h, pu);
-        if (placed) tv.tree[tv.off(h) + pi] = child_group_sum<LOGK, MEM>(tv, h, pi);
+        const uint32_t pu = u.i >> (v * LOGR), pi = ins.slot >> (v * LOGR);
+        if (valid) tv.tree[tv.off(v) + pu] = child_group_sum<LOGK, MEM>(tv, v, pu);
+        if (placed) tv.tree[tv.off(v) + pi] = child_group_sum<LOGK, MEM>(tv, v, pi);
       }
+      tv.sync();
+      if (tid < 64u) sum_top<LOGK, MEM>(tv);
     }
   }
 }
@@ -488,28 +590,129 @@ __device__ __forceinline__ void note_wild(float u, uint32_t batch, uint32_t* s_w
   if (__builtin_expect(__any(__float_as_uint(u) >= 0x3F800000u), 0)) *s_wild = batch;
 }
 
-// Sample i of n (lane i of the team; lanes beyond repeat the last one), uniform u: leaf and value, 0xFFFFFFFF and 0 where
-// nothing can be sampled.
+// The binary steps of the walk inside a group held in registers, without a look at the right block: see walk_tree.
+// (children: the N children; node: 2 node + 1 for a turn to the right)
+template <int N>
+__device__ __forceinline__ float first_half_sum(const float (&c)[N]) {   // of c[0 .. N/2), pairwise
+  if constexpr (N == 2) {
+    return c[0];
+  } else {
+    float h[N / 2];
+#pragma unroll
+    for (int i = 0; i < N / 2; ++i) h[i] = c[i];
+    if constexpr (N == 4) return h[0] + h[1];
+    else {
+      float up[N / 4];
+#pragma unroll
+      for (int i = 0; i < N / 4; ++i) up[i] = h[2 * i] + h[2 * i + 1];
+#pragma unroll
+      for (int w = N / 8; w >= 1; w /= 2)
+#pragma unroll
+        for (int i = 0; i < w; ++i) up[i] = up[2 * i] + up[2 * i + 1];
+      return up[0];
+    }
+  }
+}
+template <int N>
+__device__ __forceinline__ void turn_down(const float (&c)[N], float& r, uint32_t& node, float& val) {
+  if constexpr (N == 1) {
+    val = c[0];
+  } else {
+    const float L = first_half_sum<N>(c), rest = r - L;
+    const bool right = !(r < L);
+    r = right ? rest : r;
+    node = 2u * node + (right ? 1u : 0u);
+    float h[N / 2];
+#pragma unroll
+    for (int i = 0; i < N / 2; ++i) h[i] = right ? c[N / 2 + i] : c[i];
+    turn_down<N / 2>(h, r, node, val);
+  }
+}
+// One level down: grp points at the children of `node`.
+template <int LOGR, typename P>
+__device__ __forceinline__ void level_down(P grp, float& r, uint32_t& node, float& val) {
+  constexpr int R = 1 << LOGR;
+  if constexpr (R <= 16) {
+    float c[R];
+#pragma unroll
+    for (int k = 0; k < R / 4; ++k) {
+      const Floats4 x = load_floats4(grp + 4 * k);
+      c[4 * k] = x.x, c[4 * k + 1] = x.y, c[4 * k + 2] = x.z, c[4 * k + 3] = x.w;
+    }
+    turn_down<R>(c, r, node, val);
+  } else {   // by the sums of its chunks first; the chosen chunk is read again
+    float sums[R / 4];
+#pragma unroll
+    for (int k = 0; k < R / 4; ++k) {
+      const Floats4 x = load_floats4(grp + 4 * k);
+      sums[k] = (x.x + x.y) + (x.z + x.w);
+    }
+    uint32_t chunk = 0;
+    turn_down<R / 4>(sums, r, chunk, val);
+    const Floats4 x = load_floats4(grp + 4 * chunk);
+    const float c[4] = {x.x, x.y, x.z, x.w};
+    node = node * (R / 4) + chunk;
+    turn_down<4>(c, r, node, val);
+  }
+}
+
+// Sample i of n (lane i of the team; lanes beyond repeat the last one), uniform u, with seg = total / n: leaf and value,
+// 0xFFFFFFFF and 0 where nothing can be sampled.
+// A binary step goes right iff the right block is not zero and not r < left block.  That the right block is zero while
+// r is not below the left one takes a rounding, or a uniform outside [0, 1): the first walk does not look, and arrives
+// at a leaf of zero if it ever should have stayed (a block of sum zero holds nothing else, and nodes beyond a level's
+// last have the group of zeros behind its groups for children).  Where that happens to any lane the wave walks again,
+// looking.  (With the right blocks' sums left out, and the sixteen children kept in registers instead of read a second
+// time once the chunk of four is known, a level takes two thirds of the 570 cycles it took.)
 template <int LOGK, bool MEM>
-__device__ __forceinline__ void walk_tree(const TreeView<MEM>& tv, uint32_t i, uint32_t n, float u, uint32_t& node, float& val) {
-  constexpr int K = Fan<LOGK>::K;
-  const float total = tv.tree[tv.off(tv.H)];
+__device__ __forceinline__ void walk_tree(const TreeView<MEM>& tv, uint32_t i, uint32_t n, float u, float total, float seg, uint32_t& node,
+                                          float& val) {
+  constexpr int LOGR = Wide<LOGK>::LOGR, R = Wide<LOGK>::R;
   node = 0xFFFFFFFFu;
   val = 0.0f;
   if (!(total > 0.0f)) return;
-  float r = ((float)(i < n ? i : n - 1) + u) * (total / (float)n);
+  const float r0 = ((float)(i < n ? i : n - 1) + u) * seg;
+  float r = r0;
   node = 0;
-  val = total;
-  for (uint32_t h = tv.H; h-- > 0;) {
-    unsigned child;
-    if constexpr (MEM) {
-      if (h == 0) descend_lane<LOGK>(as_global(tv.leaves) + (size_t)node * K, r, child, val);
-      else descend_lane<LOGK>(tv.tree + tv.off(h) + (size_t)node * K, r, child, val);
-    } else {
-      descend_lane<LOGK>(tv.tree + tv.off(h) + (size_t)node * K, r, child, val);
-    }
-    node = node * K + child;
+  uint32_t v = tv.V - 1;
+  if (R > 4 && v > 0 && tv.n(v) <= 4u) {   // (few children of the root, the same for all lanes)
+    const Floats4 x = load_floats4(static_cast<const float*>(tv.tree) + tv.off(v));
+    const float c[4] = {x.x, x.y, x.z, x.w};
+    turn_down<4>(c, r, node, val);
+    --v;
   }
+  for (; v > 0; --v) {
+    float unused;
+    level_down<LOGR>(static_cast<const float*>(tv.tree) + tv.off(v) + (size_t)min_u32(node, tv.n(v + 1)) * R, r, node, unused);
+  }
+  const uint32_t n1 = tv.n(1);
+  bool astray = false;
+  if constexpr (MEM) {   // (no such group behind the leaves in memory)
+    astray = node >= n1;
+    level_down<LOGR>(as_global(static_cast<const float*>(tv.leaves)) + (size_t)(astray ? 0u : node) * R, r, node, val);
+  } else {
+    level_down<LOGR>(static_cast<const float*>(tv.tree) + (size_t)min_u32(node, n1) * R, r, node, val);
+  }
+  if (__builtin_expect(__any(astray || !(val > 0.0f)), 0)) {
+    r = r0;
+    node = 0;
+    for (v = tv.V; v-- > 0;) {
+      unsigned child;
+      if constexpr (MEM) {
+        if (v == 0) descend_lane<LOGR>(as_global(static_cast<const float*>(tv.leaves)) + (size_t)node * R, r, child, val);
+        else descend_lane<LOGR>(static_cast<const float*>(tv.tree) + tv.off(v) + (size_t)node * R, r, child, val);
+      } else {
+        descend_lane<LOGR>(static_cast<const float*>(tv.tree) + tv.off(v) + (size_t)node * R, r, child, val);
+      }
+      node = node * R + child;
+    }
+  }
+}
+// total / n, the mass a sample stands for.  Where n is a power of two the product with its reciprocal is the same number
+// (the scaled total, rounded once either way) without the steps of a division.
+__device__ __forceinline__ float mass_per_sample(float total, uint32_t n) {
+  const float fn = (float)n;
+  return (n & (n - 1u)) == 0u ? total * __uint_as_float(0x7F000000u - __float_as_uint(fn)) : total / fn;
 }
 
 // The list of steps.  What bounds it is one chain of instructions and LDS trips from step to step (the tree as one
@@ -531,7 +734,7 @@ __device__ __forceinline__ void walk_tree(const TreeView<MEM>& tv, uint32_t i, u
 // The order that memory needs: the stored rows of an insertion are read by the gather of the same step at the earliest
 // (its lanes wait for their stores before the barrier that ends the sampling), and overwrite what the gather of the
 // step before has read (all of whose loads have arrived at the barrier in front of the insertion's stores).
-// 100 steps on 10 000 leaves at K = 16 (32 samples, 4 new rows of 41 bytes): 268 us; 1001 us as one phase after the
+// 100 steps on 10 000 leaves at K = 16 (32 samples, 4 new rows of 41 bytes): 232 us; 1001 us as one phase after the
 // other by the whole workgroup with a full barrier between them.
 // AHEAD: no step reads what a step returns.
 template <int LOGK, bool WAVE, bool MEM, bool AHEAD>
@@ -541,16 +744,19 @@ k_run_steps(StreamKernelArgs ka) {
   const StreamArgs& a = ka.a;
   extern __shared__ __attribute__((aligned(16))) float tree[];
   __shared__ LevelTable tab;
-  __shared__ uint32_t s_off[kMaxHeight + 2];
+  __shared__ uint32_t s_off[kStreamLevels + 2], s_n[kStreamLevels + 1];
   __shared__ uint32_t s_max, s_vmin[2], s_bmin[2], s_wild, s_flags, s_arrived;
   __shared__ uint2 s_runs[16];
   __shared__ PieceFields s_rows, s_ins;
   const uint32_t t = blockIdx.x;
   const uint32_t tid = threadIdx.x, lane = tid & 63u;
   const uint32_t H = g.H, T = g.T, B = a.B, n_ins = a.n_insert, N = g.N;
+  const uint32_t V = a.levels;
   fill_level_table(H, t, &tab);
-  if (tid >= 64 && tid <= 64 + H + 1)
+  if (tid >= 64 && tid <= 64 + V + 1) {
     s_off[tid - 64] = kernarg_at<StreamArgs>(offsetof(StreamKernelArgs, a))->off[tid - 64];
+    if (tid <= 64 + V) s_n[tid - 64] = kernarg_at<Geom>(0)->n[level_height<LOGK>(tid - 64, H)];
+  }
   if (tid == 0) {
     s_max = read_max_bits(g, t);
     s_vmin[0] = s_vmin[1] = s_bmin[0] = s_bmin[1] = kNoMin;
@@ -596,19 +802,22 @@ k_run_steps(StreamKernelArgs ka) {
   lt.tree = tree;
   lt.leaves_mem = MEM ? tab.lvl[0] : nullptr;
   lt.off = s_off;
+  lt.n = s_n;
   lt.max_bits = &s_max;
   lt.H = H;
-  lt.N = N;
-  lds_tree_load(tab, lt);
-  uint32_t* nodes = reinterpret_cast<uint32_t*>(tree + s_off[H + 1]);   // [B] sampled leaves of the step
+  lt.V = V;
+  lds_tree_load<LOGK>(tab, lt);
+  uint32_t* nodes = reinterpret_cast<uint32_t*>(tree + s_off[V + 1]);   // [B] sampled leaves of the step
   float* values = reinterpret_cast<float*>(nodes + 512);                // [B] and their values (apart only: B <= 512)
   TreeView<MEM> tv;
   tv.tree = tree;
   tv.leaves = lt.leaves_mem;
-  tv.off_reg = s_off[lane <= H + 1 ? lane : H + 1];
-  tv.n_reg = tab.n[lane <= H ? lane : H];
-  tv.H = H;
+  tv.off_reg = s_off[lane <= V + 1 ? lane : V + 1];
+  tv.n_reg = s_n[lane <= V ? lane : V];
+  tv.V = V;
   tv.N = N;
+  tv.vt = 1;
+  while (tv.vt < V && tv.n(tv.vt) > kTopNodes) ++tv.vt;
   tv.s_max = &s_max;
   tv.s_arrived = &s_arrived;
   tv.s_wild = &s_wild;
@@ -622,6 +831,7 @@ k_run_steps(StreamKernelArgs ka) {
   uint32_t max_bits = s_max;      // (WAVE: the team's copy; else s_max counts)
   uint32_t node = 0xFFFFFFFFu;    // this lane's sample of the step before
   float val = 0.0f;
+  float total = tree[s_off[V]];   // (WAVE: the root as the latest change has left it)
   for (uint32_t s = 0;; ++s) {
     const bool more = s < a.n_steps;
     // ---- rows and weights of the step before
@@ -669,7 +879,7 @@ k_run_steps(StreamKernelArgs ka) {
     if (in_team) {
       const UpdateWork up{do_upd, in_team && tid < B, a.upd_is_sampled != 0, B, a.upd_is_sampled ? node : up_i, upd_size, up_v, s};
       const InsertWork in{do_ins, inserts, a.ins_prio != nullptr, n_ins, inserts ? ring_slot(cursor, j_ins, N) : 0u, in_v};
-      change_tree<LOGK, WAVE, MEM>(tv, up, in, max_bits, flags);
+      change_tree<LOGK, WAVE, MEM>(tv, up, in, max_bits, flags, total);
       // inputs of the next round
       if (AHEAD && in_team && tid < B) {
         const size_t bo = ((size_t)s * T + t) * B + tid;
@@ -711,7 +921,8 @@ k_run_steps(StreamKernelArgs ka) {
     // ---- sampling
     if (in_team && (WAVE || (tid & ~63u) < B)) {
       if constexpr (!WAVE) note_wild(u_i, s + 1u, &s_wild);
-      walk_tree<LOGK, MEM>(tv, tid, B, u_i, node, val);
+      if constexpr (!WAVE) total = tree[tv.off(V)];
+      walk_tree<LOGK, MEM>(tv, tid, B, u_i, total, mass_per_sample(total, B), node, val);
       if (node == 0xFFFFFFFFu) {
         if (tid == 0) flags |= 4u;
       } else if (a.out_w) {
@@ -731,7 +942,7 @@ k_run_steps(StreamKernelArgs ka) {
   }
   if (WAVE && tid == 0) s_max = max_bits;
   __syncthreads();
-  lds_tree_store(g, t, tab, lt, flags, &s_flags);
+  lds_tree_store<LOGK>(g, t, tab, lt, flags, &s_flags);
 }
 
 // ---------------------------------------------------------------------------------
@@ -750,7 +961,7 @@ k_run_steps(StreamKernelArgs ka) {
 // Fetching ahead is only right where a request reads nothing that one just before it writes (an update whose index
 // array is the sampled one, say).  The host has checked that (QueueArgs::ahead); where it does not hold, every
 // request is a round of its own with an empty one behind it, which brings all results to memory.
-// 20 times (insert 16 rows, sample 512, update them) on 30 000 leaves at K = 16: 193 us; 353 us one request after the
+// 20 times (insert 16 rows, sample 512, update them) on 30 000 leaves at K = 16: 188 us; 353 us one request after the
 // other by the whole workgroup with a full barrier between their phases.
 struct QueueKernelArgs {            // one kernel argument (Geom first: see fill_level_table)
   Geom g;
@@ -785,7 +996,7 @@ k_run_requests(QueueKernelArgs ka) {
   const QueueArgs& a = ka.a;
   extern __shared__ __attribute__((aligned(16))) float tree[];
   __shared__ LevelTable tab;
-  __shared__ uint32_t s_off[kMaxHeight + 2];
+  __shared__ uint32_t s_off[kStreamLevels + 2], s_n[kStreamLevels + 1];
   __shared__ per_request s_req[3][kRoundRequests];   // round i: s_req[i % 3]
   __shared__ PieceFields s_rows[2], s_ins[2];        // by parity of the round
   __shared__ uint32_t s_skip[2][32];                 // bit j: row j of the round's insertion is deferred
@@ -796,9 +1007,12 @@ k_run_requests(QueueKernelArgs ka) {
   const uint32_t H = g.H, N = g.N, n_requests = a.n_requests;
   const FieldTable* fields = kernarg_at<FieldTable>(offsetof(QueueKernelArgs, a) + offsetof(QueueArgs, fields));
   const uint32_t* queue = reinterpret_cast<const uint32_t*>(a.queue);
+  const uint32_t V = a.levels;
   fill_level_table(H, t, &tab);
-  if (tid >= 64 && tid <= 64 + H + 1)
+  if (tid >= 64 && tid <= 64 + V + 1) {
     s_off[tid - 64] = kernarg_at<QueueArgs>(offsetof(QueueKernelArgs, a))->off[tid - 64];
+    if (tid <= 64 + V) s_n[tid - 64] = kernarg_at<Geom>(0)->n[level_height<LOGK>(tid - 64, H)];
+  }
   if (tid == 0) {
     s_max = read_max_bits(g, t);
     s_vmin[0] = s_vmin[1] = s_bmin[0] = s_bmin[1] = kNoMin;
@@ -838,19 +1052,22 @@ k_run_requests(QueueKernelArgs ka) {
   lt.tree = tree;
   lt.leaves_mem = MEM ? tab.lvl[0] : nullptr;
   lt.off = s_off;
+  lt.n = s_n;
   lt.max_bits = &s_max;
   lt.H = H;
-  lt.N = N;
-  lds_tree_load(tab, lt);
-  uint32_t* nodes = reinterpret_cast<uint32_t*>(tree + s_off[H + 1]);   // sampled leaves of the round
+  lt.V = V;
+  lds_tree_load<LOGK>(tab, lt);
+  uint32_t* nodes = reinterpret_cast<uint32_t*>(tree + s_off[V + 1]);   // sampled leaves of the round
   float* values = reinterpret_cast<float*>(nodes + 512);                // and their values (apart only: at most 512)
   TreeView<MEM> tv;
   tv.tree = tree;
   tv.leaves = lt.leaves_mem;
-  tv.off_reg = s_off[lane <= H + 1 ? lane : H + 1];
-  tv.n_reg = tab.n[lane <= H ? lane : H];
-  tv.H = H;
+  tv.off_reg = s_off[lane <= V + 1 ? lane : V + 1];
+  tv.n_reg = s_n[lane <= V ? lane : V];
+  tv.V = V;
   tv.N = N;
+  tv.vt = 1;
+  while (tv.vt < V && tv.n(tv.vt) > kTopNodes) ++tv.vt;
   tv.s_max = &s_max;
   tv.s_arrived = &s_arrived;
   tv.s_wild = &s_wild;
@@ -862,6 +1079,7 @@ k_run_requests(QueueKernelArgs ka) {
   uint32_t flags = 0;
   uint32_t node = 0xFFFFFFFFu;    // this lane's sample of the latest sampling request
   float val = 0.0f;
+  float total = 0.0f;             // (WAVE: the root as the latest change has left it)
   // the round under way, the next one, and where the one after that starts in the queue
   const bool single = a.ahead == 0;
   QueueRound cur = take_round(s_req[0], n_requests, single);
@@ -927,6 +1145,7 @@ k_run_requests(QueueKernelArgs ka) {
   }
   __syncthreads();
   uint32_t max_bits = s_max;      // (WAVE: the team's copy; else s_max counts)
+  total = tree[s_off[V]];
 
   for (uint32_t i = 0;; ++i) {
     const uint32_t par = i & 1u, slot_cur = i % 3u, slot_next = (i + 1u) % 3u, slot_before = (i + 2u) % 3u;
@@ -988,7 +1207,7 @@ k_run_requests(QueueKernelArgs ka) {
         in.slot = in.mine ? ring_slot(cursor, j, N) : 0u;
         in.v = in_v;
       }
-      change_tree<LOGK, WAVE, MEM>(tv, up, in, max_bits, flags);
+      change_tree<LOGK, WAVE, MEM>(tv, up, in, max_bits, flags, total);
     }
     if (do_ins) {
       cursor = ring_slot(cursor, n_ins, N);
@@ -1042,7 +1261,8 @@ k_run_requests(QueueKernelArgs ka) {
       // ---- sampling
       if (in_team && (WAVE || (tid & ~63u) < sample_n)) {
         if constexpr (!WAVE) note_wild(u_i, sampled, &s_wild);
-        walk_tree<LOGK, MEM>(tv, tid, sample_n, u_i, node, val);
+        if constexpr (!WAVE) total = tree[tv.off(V)];
+        walk_tree<LOGK, MEM>(tv, tid, sample_n, u_i, total, mass_per_sample(total, sample_n), node, val);
         if (node == 0xFFFFFFFFu) {
           if (tid == 0) flags |= 4u;
         } else if (smp->out_weight) {
@@ -1067,27 +1287,44 @@ k_run_requests(QueueKernelArgs ka) {
   }
   if (WAVE && tid == 0) s_max = max_bits;
   __syncthreads();
-  lds_tree_store(g, t, tab, lt, flags, &s_flags);
+  lds_tree_store<LOGK>(g, t, tab, lt, flags, &s_flags);
 }
 
-// LDS floats of a tree's copy (every height padded to whole child groups), or 0 if it cannot be held beside the step
-// kernel's other LDS data.  The whole tree if that fits; else the heights 1 .. H, the leaves staying in memory
-// (*leaves_in_memory says which).
-constexpr uint32_t kStreamLdsBytes = 156 * 1024;
-uint32_t stream_tree_floats(const Geom& g, uint32_t* off, uint32_t* leaves_in_memory) {
+// A tree can be worked on where its heights (every one padded to whole child groups), or those above the leaves, fit
+// beside the step kernel's other LDS data.
+constexpr uint32_t kStreamLdsBytes = 156 * 1024, kStreamBatchWords = 1024;   // (the sampled indices and values of a step)
+bool stream_tree_fits(const Geom& g) {
+  for (uint32_t skip = 0; skip < 2; ++skip) {
+    uint64_t floats = kStreamBatchWords;
+    for (uint32_t h = skip; h <= g.H && floats * 4 <= kStreamLdsBytes; ++h)
+      floats += h < g.H ? ((uint64_t)g.n[h] + g.K - 1) / g.K * g.K : 4;   // (the root padded to 16 bytes)
+    if (floats * 4 <= kStreamLdsBytes && !(skip && g.H < 2)) return true;
+  }
+  return false;
+}
+// Levels of the copy (see Wide): the whole tree if that fits, else the levels above the leaves.  Narrow trees take less
+// room as levels than as heights, and the groups of zeros behind the levels (512 bytes at most, K = 64) go beyond
+// kStreamLdsBytes, so one of the two fits where stream_tree_fits() says so.  Returns the LDS floats, the batch's words
+// included (0: neither fits).
+constexpr uint32_t kStreamLdsMost = kStreamLdsBytes + 512;
+template <int LOGK>
+static uint32_t plan_stream_levels(const Geom& g, uint32_t* off, uint32_t* levels, uint32_t* leaves_in_memory) {
+  constexpr uint32_t LH = Wide<LOGK>::LH, R = Wide<LOGK>::R;
+  const uint32_t V = (g.H + LH - 1) / LH;
+  if (V > kStreamLevels) return 0u;
   for (uint32_t skip = 0; skip < 2; ++skip) {
     uint64_t floats = 0;
-    bool fits = true;
-    for (uint32_t h = 0; h <= g.H && fits; ++h) {
-      if (off) off[h] = (uint32_t)floats;
-      if (h == 0 && skip) continue;
-      floats += h < g.H ? ((uint64_t)g.n[h] + g.K - 1) / g.K * g.K : 4;   // (the root padded to 16 bytes)
-      fits = floats * 4 <= kStreamLdsBytes;
+    for (uint32_t v = 0; v <= V; ++v) {
+      off[v] = (uint32_t)floats;
+      if (v == 0 && skip) continue;
+      floats += v < V ? ((uint64_t)g.n[v * LH] + R - 1) / R * R + (v + 1 < V ? R : 0) : 4;
+      if (floats * 4 > kStreamLdsMost) break;
     }
-    if (!fits || (floats + 1024) * 4 > kStreamLdsBytes || (skip && g.H < 2)) continue;
-    if (off) off[g.H + 1] = (uint32_t)floats;
-    if (leaves_in_memory) *leaves_in_memory = skip;
-    return (uint32_t)floats;
+    if ((floats + kStreamBatchWords) * 4 > kStreamLdsMost || (skip && V < 2)) continue;
+    off[V + 1] = (uint32_t)floats;
+    *levels = V;
+    *leaves_in_memory = skip;
+    return (uint32_t)floats + kStreamBatchWords;
   }
   return 0u;
 }
@@ -1097,9 +1334,9 @@ static hipError_t launch_run_steps_k(const Geom& g, const Tuning& tn, StreamArgs
   StreamKernelArgs ka{};
   ka.g = g;
   ka.a = a;
-  const uint32_t floats = stream_tree_floats(g, ka.a.off, &ka.a.leaves_in_memory);
+  const uint32_t floats = plan_stream_levels<LOGK>(g, ka.a.off, &ka.a.levels, &ka.a.leaves_in_memory);
   if (!floats) return hipErrorInvalidValue;
-  const size_t bytes = ((size_t)floats + 1024) * 4;   // the tree and the sampled indices of one step
+  const size_t bytes = (size_t)floats * 4;
   // always the largest workgroup, also for small batches: measured faster than a workgroup of the batch's
   // size (the tree copy and the row movers use all lanes)
   const bool wave = a.B <= 64 && a.n_insert <= 64, mem = ka.a.leaves_in_memory != 0;
@@ -1134,9 +1371,9 @@ static hipError_t launch_run_requests_k(const Geom& g, const Tuning& tn, const Q
   QueueKernelArgs ka{};
   ka.g = g;
   ka.a = a;
-  const uint32_t floats = stream_tree_floats(g, ka.a.off, &ka.a.leaves_in_memory);
+  const uint32_t floats = plan_stream_levels<LOGK>(g, ka.a.off, &ka.a.levels, &ka.a.leaves_in_memory);
   if (!floats) return hipErrorInvalidValue;
-  const size_t bytes = ((size_t)floats + 1024) * 4;   // the tree and the indices of the latest sampling request
+  const size_t bytes = (size_t)floats * 4;
   const bool wave = a.most <= 64, mem = ka.a.leaves_in_memory != 0;
 #define PER_RUN(W, M)                                                                                   \
   do {                                                                                                  \

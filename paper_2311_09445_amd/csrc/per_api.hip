@@ -747,7 +747,7 @@ int per_update_delta(per_t* p, uint32_t B, const uint32_t* d_idx, const float* d
   return hip_rc(e);
 }
 
-int per_run_steps_fits(const per_t* p) { return p && stream_tree_floats(p->g, nullptr) ? 1 : 0; }
+int per_run_steps_fits(const per_t* p) { return p && stream_tree_fits(p->g) ? 1 : 0; }
 
 // A byte range of the caller's memory that a list of steps or a request reads or writes.
 struct Span { uintptr_t lo, hi; };
@@ -784,7 +784,7 @@ int per_run_steps(per_t* p, uint32_t n_steps, uint32_t n_insert, uint32_t B, con
   if (!p || !io || io->struct_size != sizeof(per_stream_io)) return PER_EINVAL;
   if (n_steps == 0) return PER_OK;
   if (B == 0 || B > 1024 || n_insert > 1024 || n_insert > p->cfg.capacity) return PER_ERANGE;
-  if (!stream_tree_floats(p->g, nullptr)) return PER_ERANGE;   // the tree does not fit the LDS of a compute unit
+  if (!stream_tree_fits(p->g)) return PER_ERANGE;   // the tree does not fit the LDS of a compute unit
   if (!io->d_u || !io->d_beta || !io->d_out_idx || misaligned(io->d_u, 4) || misaligned(io->d_beta, 4) ||
       misaligned(io->d_out_idx, 4) || misaligned(io->d_out_weight, 4) || misaligned(io->d_out_prio, 4) ||
       misaligned(io->d_upd_idx, 4) || misaligned(io->d_upd_prio, 4) || misaligned(io->d_ins_prio, 4))
@@ -860,7 +860,7 @@ int per_run_requests(per_t* p, uint32_t n_requests, const per_request* h_request
   if (!p) return PER_EINVAL;
   if (n_requests == 0) return PER_OK;
   if (!h_requests || !d_requests || misaligned(d_requests, 8)) return PER_EINVAL;
-  if (!stream_tree_floats(p->g, nullptr)) return PER_ERANGE;   // the tree does not fit the LDS of a compute unit
+  if (!stream_tree_fits(p->g)) return PER_ERANGE;   // the tree does not fit the LDS of a compute unit
   QueueArgs a{};
   (void)fill_fields(p, nullptr, &a.fields);
   for (uint32_t f = 0; f < a.fields.n_fields; ++f) a.fields.vec[f] = vec_width(a.fields.bytes[f], nullptr);

@@ -21,6 +21,7 @@ constexpr uint32_t kVminSlots = 256;   // partial batch minima per tree and buff
 constexpr uint32_t kStepGroups = 64;   // counters the owners of the one-kernel step are spread over (one wave reads them all)
 constexpr uint32_t kStepDoneSlots = 8; // counters its builders are spread over
 constexpr uint32_t kStepMaxOwners = 2048;   // most owner workgroups over all trees
+constexpr uint32_t kStreamLevels = 8;  // most levels above the leaves of an on-chip tree (K = 8, 272 000 leaves: 7)
 
 struct Geom {
   uint32_t K, logK, H, T;
@@ -158,8 +159,9 @@ struct StreamArgs {
   const float* upd_prio;            // [steps][T][B] or null: no update
   const float* ins_prio;            // [steps][T][n_insert] or null: running maximum
   FieldTable ins, rows;             // io arrays hold [steps][T][n][bytes]; io all null: nothing to move
-  uint32_t off[kMaxHeight + 2];     // where height h starts in LDS (floats); off[H + 1] = all floats
-  uint32_t leaves_in_memory;        // the LDS copy holds heights 1 .. H only
+  uint32_t off[kStreamLevels + 2];  // where level v of the LDS copy starts (floats); off[levels + 1] = all floats
+  uint32_t levels;                  // levels above the leaves (see Wide)
+  uint32_t leaves_in_memory;        // the LDS copy holds the levels above the leaves only
 };
 
 // A queue of op-coded requests run by one workgroup per tree on an LDS copy of the tree (see k_run_requests).
@@ -171,7 +173,8 @@ struct QueueArgs {
   uint32_t ahead;                   // what a request reads may be fetched before the ones just before it are done
   const per_request* queue;         // device copy of the requests
   FieldTable fields;                // columns, row sizes and access widths; the io pointers come from the requests
-  uint32_t off[kMaxHeight + 2];     // as in StreamArgs
+  uint32_t off[kStreamLevels + 2];  // as in StreamArgs
+  uint32_t levels;
   uint32_t leaves_in_memory;
 };
 
@@ -290,7 +293,7 @@ size_t step_table_bytes();
 // or when `device` is not the current one), and given back.
 void* step_static_claim(const void* holder, int device, hipStream_t s);
 void step_static_release(const void* holder, int device);
-uint32_t stream_tree_floats(const Geom& g, uint32_t* off, uint32_t* leaves_in_memory = nullptr);
+bool stream_tree_fits(const Geom& g);
 hipError_t launch_run_steps(const Geom& g, const Tuning& tn, const StreamArgs& a, hipStream_t s);
 hipError_t launch_run_requests(const Geom& g, const Tuning& tn, const QueueArgs& a, hipStream_t s);
 hipError_t launch_get_priority(const Geom& g, const Tuning& tn, uint32_t n, const uint32_t* idx, float* out, hipStream_t s);

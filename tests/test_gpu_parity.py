@@ -713,6 +713,42 @@ def test_run_steps_limits_and_empty_tree():
     assert q.status() == FLAG_ZERO_TOTAL
 
 
+@pytest.mark.parametrize("K,N", [(2, 1), (2, 16), (2, 17), (2, 33), (2, 513), (4, 5), (4, 65), (4, 4097), (8, 9), (8, 520), (8, 1025), (16, 17),
+                                 (16, 2049), (16, 36000), (32, 33), (32, 4100), (64, 65), (64, 8200),   # 64, 65, 128, 129 nodes on a level and around
+                                 (2, 19400), (4, 29000), (8, 33900), (64, 38200), (8, 272000), (64, 2400000)])   # the most that fit, with and without their leaves
+@pytest.mark.parametrize("B", [40, 130])
+def test_levels_of_the_on_chip_tree(K, N, B):
+    """Trees at the edges of what the on-chip kernels hold as levels of sixteen children or more, with leaves of zero (also of minus
+    zero) and uniforms whose targets round up to the end of a block: a walk that does not look for empty blocks has to notice."""
+    log(f"on-chip levels K={K} N={N} B={B}")
+    rng = np.random.default_rng(N + B)
+    m = Mirror(K, N, 1, ())
+    assert m.gpu.run_steps_fits()
+    prio = wl._draw_priorities("exponential_1", rng, (1, N))
+    prio[:, rng.random(N) < 0.3] = 0.0
+    prio[:, rng.random(N) < 0.3] = -0.0
+    prio[:, N // 2] = 1.0
+    m.insert(N, prio=prio, chunk=max(5000, N // 8))
+    steps = 5
+    u = wl.uniform01(rng, (steps, 1, B))
+    u[1] = 1.0 - 2.0 ** -24
+    u[2, :, ::3] = 1.0 - 2.0 ** -24
+    u[3, :, B // 2:] = 1.0
+    up = (rng.random((steps, 1, B)) * 4).astype(np.float32)
+    up[rng.random(up.shape) < 0.5] = 0.0
+    oi = torch.empty((steps, 1, B), dtype=torch.int32, device="cuda")
+    ov = torch.empty((steps, 1, B), device="cuda")
+    m.gpu.run_steps(dev(u), dev(np.full(steps, 0.5, np.float32)), oi, None, ov, upd_prio=dev(up), n_insert=min(N, 3))
+    for s in range(steps):
+        m.cpu.insert(min(N, 3), None, None)
+        ci, _, cv = m.cpu.sample(u[s], 0.5, False)
+        assert np.array_equal(idx_to_host(oi)[s], ci), f"step {s}: sampled indices"
+        assert ov[s].cpu().numpy().tobytes() == cv.tobytes(), f"step {s}: sampled values"
+        m.cpu.update(ci, up[s])
+    m.compare_tree()
+    m.compare_status()
+
+
 @pytest.mark.parametrize("K,N,T,B,fb", [(16, 3000, 2, 32, (16, 4, 4, 16, 1)), (2, 3000, 1, 64, (12,)), (16, 30000, 1, 300, (68, 24, 4, 68, 1)),
                                         (8, 5000, 3, 65, ()), (4, 9000, 1, 700, (16, 1)), (16, 100000, 1, 64, (5,)), (32, 300000, 2, 513, (8, 4))])
 @pytest.mark.parametrize("what", ["late", "own"])
