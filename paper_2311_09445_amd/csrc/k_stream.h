@@ -153,170 +153,287 @@ __device__ __forceinline__ void lds_tree_store(const Geom& g, uint32_t t, const 
 // wave: an item.  A wave then works with one access width and one field's constants (with the pieces of all fields
 // shared out lane by lane, every lane paid for a chain of selects over the fields, a division, and the loads and
 // stores of every width that occurs in its wave).
+constexpr int kWidths = 5;         // access widths: 16, 8, 4, 2 and 1 byte
+constexpr uint32_t kLeastMovers = 6;   // waves that share a list's items, at least (see fill_piece_fields)
 struct PieceFields {               // what the waves ask of one list of fields, in LDS
   uint8_t* io[kMaxFields];         // the caller's array: the rows of this tree (in step 0)
   uint8_t* col[kMaxFields];        // the field in row 0 of this tree
-  uint64_t step[kMaxFields];       // bytes of the caller's array per step
-  uint32_t bytes[kMaxFields], vec[kMaxFields];
-  uint32_t pieces[kMaxFields];     // pieces of this field
+  uint64_t step_rows;              // rows of the caller's arrays per step
+  uint32_t bytes[kMaxFields], width[kMaxFields];
   uint32_t recip[kMaxFields];      // floor(2^32 / pieces per row) + 1
-  uint32_t end[kMaxFields];        // items of this field and all before it
-  __device__ __forceinline__ uint32_t items() const { return (uint32_t)__builtin_amdgcn_readfirstlane((int)end[kMaxFields - 1]); }
-};
-// Called by one wave: n rows per tree; field f's array is `io` for tree 0 (null: not asked for), `step` bytes from step to step.
-__device__ __forceinline__ void fill_piece_fields(const FieldTable* ft, uint8_t* io, uint32_t t, uint32_t n, uint64_t step_rows,
-                                                  PieceFields* pf) {
-  const uint32_t f = threadIdx.x & 63u;
-  if (f < (uint32_t)kMaxFields) {
-    const bool on = f < ft->n_fields && io && n;
-    const uint32_t E = on ? ft->bytes[f] : 1u, v = on ? ft->vec[f] : 1u, epr = row_elements(E, v);
-    pf->io[f] = on ? io + (uint64_t)t * n * E : nullptr;
-    pf->col[f] = ft->col[f] + (uint64_t)t * ft->col_stride[f];
-    pf->step[f] = step_rows * E;
-    pf->bytes[f] = E;
-    pf->vec[f] = v;
-    pf->pieces[f] = on ? n * epr : 0u;
-    pf->recip[f] = epr > 1 ? 0xFFFFFFFFu / epr + 1u : 0u;
-    uint32_t end = on ? (n * epr + 63u) / 64u : 0u;
-#pragma unroll
-    for (int d = 1; d < kMaxFields; d <<= 1) {
-      const uint32_t before = (uint32_t)__shfl_up((int)end, d);
-      if (f >= (uint32_t)d) end += before;
-    }
-    pf->end[f] = end;
-  }
-}
-struct RowItem {        // this lane's piece of an item
-  bool on;
-  uint32_t f, w, row;   // field and access width (the same for the wave), row of the batch
-  uint8_t* stored;      // the piece in row 0 of the tree's payload
-  uint8_t* dense;       // the piece in the caller's array (step 0)
+  uint32_t first[kMaxFields], end[kMaxFields];   // its items, all items ordered by width
+  uint32_t items, n, asked;        // all items; rows; bit f: field f is asked for
 };
 __device__ __forceinline__ uint32_t wave_value(uint32_t x) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)x); }   // (the same in all lanes)
-// Item i < pf.items(): fields one after the other.
+__device__ __forceinline__ uint64_t wave_value64(uint64_t x) {
+  return (uint64_t)wave_value((uint32_t)(x >> 32)) << 32 | wave_value((uint32_t)x);
+}
+__device__ __forceinline__ uint8_t* wave_pointer(uint8_t* p) { return reinterpret_cast<uint8_t*>(wave_value64(reinterpret_cast<uint64_t>(p))); }
+// Row waves that gather the rows of n samples (the others of `rws` weigh them, if there are enough).
+__device__ __forceinline__ uint32_t gathering_waves(uint32_t n, uint32_t rws) {
+  const uint32_t weigh = (n + 63u) / 64u;
+  return rws >= weigh + kLeastMovers ? rws - weigh : rws;
+}
+// Called by one wave: n rows per tree; field f's array is `io` for tree 0 (null: not asked for), `step_rows` rows from step to
+// step; `waves` >= kLeastMovers waves take the items, each a run of them and of one access width, so that what a wave does
+// with its items is straight code: the runs are as short as that allows.  share (null: not asked for): items of wave i.
+__device__ __forceinline__ void fill_piece_fields(const FieldTable* ft, uint8_t* io, uint32_t t, uint32_t n, uint64_t step_rows,
+                                                  uint32_t waves, PieceFields* pf, uint2* share) {
+  const uint32_t lane = threadIdx.x & 63u, f = lane;
+  const bool on = f < (uint32_t)kMaxFields && f < ft->n_fields && io && n;
+  const uint32_t E = on ? ft->bytes[f] : 1u, v = on ? ft->vec[f] : 1u, epr = row_elements(E, v);
+  const uint32_t w = moves_wide(E, v) ? 16u : v, kind = 4u - (uint32_t)__builtin_ctz(w);   // 0: 16 bytes .. 4: one
+  const uint32_t items = on ? (n * epr + 63u) / 64u : 0u;
+  // items per width and in front of this field
+  uint32_t of_kind[kWidths] = {}, before = 0;
+#pragma unroll
+  for (uint32_t g = 0; g < (uint32_t)kMaxFields; ++g) {
+    const uint32_t its = (uint32_t)__builtin_amdgcn_readlane((int)items, (int)g), kd = (uint32_t)__builtin_amdgcn_readlane((int)kind, (int)g);
+#pragma unroll
+    for (int c = 0; c < kWidths; ++c) of_kind[c] += kd == (uint32_t)c ? its : 0u;
+    before += kd < kind || (kd == kind && g < f) ? its : 0u;
+  }
+  uint32_t total = 0;
+#pragma unroll
+  for (int c = 0; c < kWidths; ++c) total += of_kind[c];
+  if (f < (uint32_t)kMaxFields) {
+    pf->io[f] = on ? io + (uint64_t)t * n * E : nullptr;
+    pf->col[f] = on ? ft->col[f] + (uint64_t)t * ft->col_stride[f] : nullptr;
+    pf->bytes[f] = E;
+    pf->width[f] = w;
+    pf->recip[f] = epr > 1 ? 0xFFFFFFFFu / epr + 1u : 0u;
+    pf->first[f] = before;
+    pf->end[f] = before + items;
+  }
+  const uint32_t asked = (uint32_t)__ballot(on);
+  if (f == 0) {
+    pf->items = total;
+    pf->step_rows = step_rows;
+    pf->n = n;
+    pf->asked = asked;
+  }
+  if (!share) return;
+  // the shortest runs with which there are waves enough: lane i tries one length.  (A run of all items
+  // always does, with a wave per width: the last lane tries no less.)
+  const uint32_t least = (total + waves - 1) / waves, len = least + lane * (total / 64u + 1u);
+  uint32_t needed = 0;
+#pragma unroll
+  for (int c = 0; c < kWidths; ++c) needed += len ? (of_kind[c] + len - 1) / len : 0u;
+  const unsigned long long enough = __ballot(needed <= waves);
+  const uint32_t run = (uint32_t)__builtin_amdgcn_readlane((int)len, enough ? (int)__builtin_ctzll(enough) : 63);
+  if (lane < 16u) {
+    uint32_t a = 0, b = 0, start = 0, wave0 = 0;
+#pragma unroll
+    for (int c = 0; c < kWidths; ++c) {
+      const uint32_t takes = run ? (of_kind[c] + run - 1) / run : 0u;
+      if (lane >= wave0 && lane < wave0 + takes) {
+        a = start + (lane - wave0) * run;
+        b = a + run < start + of_kind[c] ? a + run : start + of_kind[c];
+      }
+      start += of_kind[c];
+      wave0 += takes;
+    }
+    share[lane] = make_uint2(a, b);
+  }
+}
+struct RowItem {         // this lane's piece of an item
+  uint32_t row;          // row of the batch, 0xFFFFFFFF: no piece
+  uint32_t f, w;         // field and access width (the same for the wave; w = 0: no item)
+  uint8_t* stored;       // the piece in row 0 of the tree's payload
+  uint8_t* io;           // the caller's array (the same for the wave)
+  uint32_t out;          // offset of the piece in it
+  uint64_t step;         // bytes of that array per step (the same for the wave)
+};
+// Item i < pf.items of a list (in step 0).
 __device__ __forceinline__ RowItem find_item(const PieceFields& pf, uint32_t i) {
   uint32_t f = 0;
 #pragma unroll
-  for (uint32_t k = 0; k + 1 < (uint32_t)kMaxFields; ++k) f += i >= pf.end[k] ? 1u : 0u;
+  for (uint32_t k = 1; k < (uint32_t)kMaxFields; ++k) f = i >= pf.first[k] && i < pf.end[k] ? k : f;
   f = wave_value(f);
-  const uint32_t E = wave_value(pf.bytes[f]), v = wave_value(pf.vec[f]);
-  const uint32_t el = (i - (f ? wave_value(pf.end[f - 1]) : 0u)) * 64u + (threadIdx.x & 63u);
-  const bool wide = moves_wide(E, v);
-  const uint32_t epr = row_elements(E, v), w = wide ? 16u : v;
+  const uint32_t E = wave_value(pf.bytes[f]), w = wave_value(pf.width[f]), epr = (E + w - 1) / w;
+  const uint32_t el = (i - wave_value(pf.first[f])) * 64u + (threadIdx.x & 63u);
+  // (at most 1024 rows: the reciprocal is exact for less than 2048 pieces per row)
+  const uint32_t row = epr == 1 ? el : epr < 2048u ? __umulhi(el, wave_value(pf.recip[f])) : el / epr;
+  const uint32_t k = el - row * epr, at = k * w + w > E ? E - w : k * w;   // (wide pieces: the last one ends with the field)
   RowItem p;
-  p.on = el < pf.pieces[f];
+  p.row = row < wave_value(pf.n) ? row : 0xFFFFFFFFu;
   p.f = f;
   p.w = w;
-  // (at most 1024 rows: the reciprocal is exact for less than 2048 pieces per row)
-  p.row = epr == 1 ? el : epr < 2048u ? __umulhi(el, wave_value(pf.recip[f])) : el / epr;
-  const uint32_t k = el - p.row * epr;
-  const uint32_t at = wide && 16u * k + 16u > E ? E - 16u : k * w;
   p.stored = pf.col[f] + at;
-  p.dense = pf.io[f] + (uint64_t)p.row * E + at;
+  p.io = wave_pointer(pf.io[f]);
+  p.out = p.row == 0xFFFFFFFFu ? 0u : row * E + at;   // (at most 1024 rows of at most 1 MiB)
+  p.step = wave_value64(pf.step_rows) * E;
   return p;
 }
 typedef uint32_t Words4 __attribute__((ext_vector_type(4), aligned(4)));   // (16-byte pieces of some fields lie on 4-byte boundaries)
 typedef uint32_t Words2 __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ uint4 load_piece(const uint8_t* src, uint32_t w) {
-  uint4 v;   // (what a narrow piece leaves of it stays undefined: setting it would make the wave wait for loads under way)
-  switch (w) {
-    case 16: { const Words4 x = *(GlobalPtr<const Words4>)src; v = make_uint4(x.x, x.y, x.z, x.w); } break;
-    case 8: { const Words2 x = *(GlobalPtr<const Words2>)src; v.x = x.x; v.y = x.y; } break;
-    case 4: v.x = *(GlobalPtr<const uint32_t>)src; break;
-    case 2: v.x = *(GlobalPtr<const uint16_t>)src; break;
-    default: v.x = *(GlobalPtr<const uint8_t>)src; break;
+// (One test per width and no else between them: a switch on a value of the wave becomes a dozen branches.  What a narrow
+// piece leaves of v stays undefined: setting it would make the wave wait for loads under way.)
+__device__ __forceinline__ uint4 load_piece(const uint8_t* p, uint32_t w) {
+  GlobalPtr<const uint8_t> src = as_global(p);
+  uint4 v;
+  if (w == 16u) {
+    const Words4 x = *(GlobalPtr<const Words4>)src;
+    v = make_uint4(x.x, x.y, x.z, x.w);
   }
+  if (w == 8u) {
+    const Words2 x = *(GlobalPtr<const Words2>)src;
+    v.x = x.x, v.y = x.y;
+  }
+  if (w == 4u) v.x = *(GlobalPtr<const uint32_t>)src;
+  if (w == 2u) v.x = *(GlobalPtr<const uint16_t>)src;
+  if (w == 1u) v.x = *(GlobalPtr<const uint8_t>)src;
   return v;
 }
-__device__ __forceinline__ void store_piece(uint8_t* dst, uint32_t w, const uint4& v) {
-  switch (w) {
-    case 16: { const Words4 x = {v.x, v.y, v.z, v.w}; *(GlobalPtr<Words4>)dst = x; } break;
-    case 8: { const Words2 x = {v.x, v.y}; *(GlobalPtr<Words2>)dst = x; } break;
-    case 4: *(GlobalPtr<uint32_t>)dst = v.x; break;
-    case 2: *(GlobalPtr<uint16_t>)dst = (uint16_t)v.x; break;
-    default: *(GlobalPtr<uint8_t>)dst = (uint8_t)v.x; break;
+__device__ __forceinline__ void store_piece(uint8_t* p, uint32_t w, const uint4& v) {
+  GlobalPtr<uint8_t> dst = as_global(p);
+  if (w == 16u) {
+    const Words4 x = {v.x, v.y, v.z, v.w};
+    *(GlobalPtr<Words4>)dst = x;
   }
+  if (w == 8u) {
+    const Words2 x = {v.x, v.y};
+    *(GlobalPtr<Words2>)dst = x;
+  }
+  if (w == 4u) *(GlobalPtr<uint32_t>)dst = v.x;
+  if (w == 2u) *(GlobalPtr<uint16_t>)dst = (uint16_t)v.x;
+  if (w == 1u) *(GlobalPtr<uint8_t>)dst = (uint8_t)v.x;
 }
 __device__ __forceinline__ uint32_t ring_slot(uint32_t cursor, uint32_t j, uint32_t N) {
-  const uint64_t s = (uint64_t)cursor + j;
-  return (uint32_t)(s >= N ? s - N : s);
+  const uint32_t s = cursor + j;   // (N <= 2^31, j < N)
+  return s >= N ? s - N : s;
 }
-// Items i .. end of one field of a gather (nodes: the batch's slots; one beyond the tree gives zeros and a flag), four at a
-// time: the loads of all, then the stores of all.
-template <typename V>
-__device__ __forceinline__ void gather_span(uint32_t i, uint32_t end, uint32_t pieces, uint32_t epr, uint32_t recip, uint32_t E,
-                                            uint32_t row_stride, const uint8_t* col, uint8_t* io, const uint32_t* nodes, uint32_t N,
-                                            uint32_t& flags) {
-  constexpr int U = 4;
-#pragma unroll 1
-  for (; i < end; i += U) {
-    V v[U];
-    uint32_t slot[U], el[U], at[U];
+// The pieces of a gather that a wave has under way: M items of its share.  Where a piece lies in its row and where it goes
+// is known before the rows are; prepared in time, what is left between the batch and its loads is a look at the batch's
+// slots.  All loads are on their way before the first store, and all of a wave's items have one access width: the code
+// for a width is straight.  (Several waves share a SIMD, and what they issue is what bounds large batches.)
+constexpr int kInFlight = 6;   // (of a wave that does nothing else)
+template <int M>
+struct GatherItems {
+  uint32_t count = 0, w = 0;   // items, their access width
+  uint32_t on = 0;             // bit k: this lane has a piece of item k
+  uint32_t row[M], slot[M], out[M];
+  const uint8_t* stored[M];
+  uint32_t field[M];
+  uint8_t* io[M];              // the caller's array in the current step
+  uint64_t step[M];
+  uint4 v[M];
+  // items first .. last - 1 (at most M) of a list, in step `at`
+  __device__ __forceinline__ void prepare(const PieceFields& pf, uint32_t first, uint32_t last, uint64_t at) {
+    count = first < last ? (last - first < (uint32_t)M ? last - first : (uint32_t)M) : 0u;
+    on = 0;
 #pragma unroll
-    for (int k = 0; k < U; ++k) {   // (beyond the end: the first piece again, so that no load stands in a branch)
-      el[k] = (i + k) * 64u + (threadIdx.x & 63u);
-      if (i + k >= end || el[k] >= pieces) el[k] = 0xFFFFFFFFu;
-      const uint32_t e = el[k] == 0xFFFFFFFFu ? 0u : el[k];
-      const uint32_t row = epr == 1 ? e : epr < 2048u ? __umulhi(e, recip) : e / epr, within = (e - row * epr) * (uint32_t)sizeof(V);
-      at[k] = within + (uint32_t)sizeof(V) > E ? E - (uint32_t)sizeof(V) : within;   // (wide pieces: the last one ends with the field)
-      slot[k] = nodes[row];
-      el[k] = el[k] == 0xFFFFFFFFu ? el[k] : row;
-    }
-#pragma unroll
-    for (int k = 0; k < U; ++k) v[k] = *(GlobalPtr<const V>)(col + (uint64_t)(slot[k] < N ? slot[k] : 0u) * row_stride + at[k]);
-#pragma unroll
-    for (int k = 0; k < U; ++k)
-      if (el[k] != 0xFFFFFFFFu) {
-        if (!(slot[k] < N)) {
-          v[k] = V{};
-          flags |= 1u;
-        }
-        *(GlobalPtr<V>)(io + (uint64_t)el[k] * E + at[k]) = v[k];
+    for (int k = 0; k < M; ++k) {   // (beyond the last: the first one again, without lanes: no load stands in a branch)
+      asm volatile("" ::: "memory");   // (one item after the other: all at once they take more registers than there are)
+      if (first + k < last) {
+        const RowItem p = find_item(pf, first + k);
+        w = p.w;
+        on |= p.row != 0xFFFFFFFFu ? 1u << k : 0u;
+        row[k] = p.row != 0xFFFFFFFFu ? p.row : 0u;
+        out[k] = p.out;
+        stored[k] = p.stored;
+        field[k] = p.f;
+        io[k] = p.io + at * p.step;
+        step[k] = p.step;
+      } else {
+        row[k] = row[0];
+        out[k] = 0;
+        stored[k] = stored[0];
+        field[k] = 0;
+        io[k] = nullptr;
+        step[k] = 0;
       }
-  }
-}
-// This wave's share (number `part` of `parts`) of a gather: a run of items, so that it has to do with few fields.  `step`:
-// which step's part of the caller's arrays.  (Looped and not unrolled over the items: the code a round goes through has
-// to stay within the instruction cache.)
-__device__ __forceinline__ void gather_rows(const PieceFields& pf, uint32_t part, uint32_t parts, const uint32_t* nodes, uint32_t N,
-                                            uint32_t row_stride, uint64_t step, uint32_t& flags) {
-  const uint32_t items = pf.items(), per = (items + parts - 1) / parts;
-  uint32_t i = part * per;
-  const uint32_t last = i + per < items ? i + per : items;
-#pragma unroll 1
-  while (i < last) {
-    uint32_t f = 0;
-#pragma unroll
-    for (uint32_t k = 0; k + 1 < (uint32_t)kMaxFields; ++k) f += i >= pf.end[k] ? 1u : 0u;
-    f = wave_value(f);
-    const uint32_t E = wave_value(pf.bytes[f]), v = wave_value(pf.vec[f]), first = f ? wave_value(pf.end[f - 1]) : 0u;
-    const uint32_t fend = wave_value(pf.end[f]), pieces = wave_value(pf.pieces[f]), recip = wave_value(pf.recip[f]);
-    const uint32_t end = fend < last ? fend : last, epr = row_elements(E, v);
-    const uint8_t* col = pf.col[f];
-    uint8_t* io = pf.io[f] + step * pf.step[f];
-    switch (moves_wide(E, v) ? 16u : v) {
-      case 16: gather_span<Words4>(i - first, end - first, pieces, epr, recip, E, row_stride, col, io, nodes, N, flags); break;
-      case 8: gather_span<Words2>(i - first, end - first, pieces, epr, recip, E, row_stride, col, io, nodes, N, flags); break;
-      case 4: gather_span<uint32_t>(i - first, end - first, pieces, epr, recip, E, row_stride, col, io, nodes, N, flags); break;
-      case 2: gather_span<uint16_t>(i - first, end - first, pieces, epr, recip, E, row_stride, col, io, nodes, N, flags); break;
-      default: gather_span<uint8_t>(i - first, end - first, pieces, epr, recip, E, row_stride, col, io, nodes, N, flags); break;
     }
-    i = end;
+  }
+  // the same items of another list with rows, fields and waves alike
+  __device__ __forceinline__ void move_to(const PieceFields& pf) {
+#pragma unroll
+    for (int k = 0; k < M; ++k)
+      if (k < (int)count) io[k] = wave_pointer(pf.io[field[k]]);
+  }
+  template <int C, typename V>
+  __device__ __forceinline__ void load_as(uint32_t N, uint32_t row_stride) {
+#pragma unroll
+    for (int k = 0; k < C; ++k) {
+      const V x = *(GlobalPtr<const V>)as_global(stored[k] + (uint64_t)(slot[k] < N ? slot[k] : 0u) * row_stride);
+      if constexpr (sizeof(V) == 16) v[k] = make_uint4(x.x, x.y, x.z, x.w);
+      else if constexpr (sizeof(V) == 8) v[k].x = x.x, v[k].y = x.y;
+      else v[k].x = x;
+    }
+  }
+  template <int C>
+  __device__ __forceinline__ void load_some(const uint32_t* nodes, uint32_t N, uint32_t row_stride) {
+#pragma unroll
+    for (int k = 0; k < C; ++k) slot[k] = nodes[row[k]];
+    if (w == 16u) load_as<C, Words4>(N, row_stride);
+    if (w == 8u) load_as<C, Words2>(N, row_stride);
+    if (w == 4u) load_as<C, uint32_t>(N, row_stride);
+    if (w == 2u) load_as<C, uint16_t>(N, row_stride);
+    if (w == 1u) load_as<C, uint8_t>(N, row_stride);
+  }
+  // (nodes: the batch's slots)
+  __device__ __forceinline__ void load(const uint32_t* nodes, uint32_t N, uint32_t row_stride) {
+    if (count == 0) return;
+    if (M > 2 && count > 2) load_some<M>(nodes, N, row_stride);
+    else load_some<M < 2 ? M : 2>(nodes, N, row_stride);
+  }
+  template <int C, typename V>
+  __device__ __forceinline__ void store_as() {
+#pragma unroll
+    for (int k = 0; k < C; ++k) {
+      if ((on >> k) & 1u) {
+        GlobalPtr<V> dst = (GlobalPtr<V>)as_global(io[k] + out[k]);
+        if constexpr (sizeof(V) == 16) *dst = V{v[k].x, v[k].y, v[k].z, v[k].w};
+        else if constexpr (sizeof(V) == 8) *dst = V{v[k].x, v[k].y};
+        else *dst = (V)v[k].x;
+      }
+      io[k] += step[k];
+    }
+  }
+  // (a batch of an empty tree gives zeros and a flag; the caller's arrays move on to the next step)
+  __device__ __forceinline__ void store(uint32_t N, uint32_t& flags) {
+    if (count == 0) return;
+    if (__builtin_expect(wave_value(slot[0]) >= N, 0)) {
+#pragma unroll
+      for (int k = 0; k < M; ++k) v[k] = make_uint4(0, 0, 0, 0);
+      if (on) flags |= 1u;
+    }
+    if (M > 2 && count > 2) store_some<M>();
+    else store_some<M < 2 ? M : 2>();
+  }
+  template <int C>
+  __device__ __forceinline__ void store_some() {
+    if (w == 16u) store_as<C, Words4>();
+    if (w == 8u) store_as<C, Words2>();
+    if (w == 4u) store_as<C, uint32_t>();
+    if (w == 2u) store_as<C, uint16_t>();
+    if (w == 1u) store_as<C, uint8_t>();
+  }
+};
+// Items first .. last of a list at once, from beginning to end, M at a time.
+template <int M>
+__device__ __forceinline__ void gather_rest(const PieceFields& pf, uint32_t first, uint32_t last, const uint32_t* nodes, uint32_t N,
+                                            uint32_t row_stride, uint64_t step, uint32_t& flags) {
+#pragma unroll 1
+  for (; first < last; first += M) {
+    GatherItems<M> it;
+    it.prepare(pf, first, last, step);
+    it.load(nodes, N, row_stride);
+    it.store(N, flags);
   }
 }
 // The rows of an insertion at ring slot `cursor`, items first, first + every, ..; row j is left out where bit j of skip is set.
 __device__ __forceinline__ void place_row_piece(const RowItem& p, uint32_t cursor, uint32_t N, uint32_t row_stride, const uint32_t* skip,
                                                 const uint4& v) {
-  if (skip && ((skip[p.row >> 5] >> (p.row & 31u)) & 1u)) return;
+  if (p.row == 0xFFFFFFFFu || (skip && ((skip[p.row >> 5] >> (p.row & 31u)) & 1u))) return;
   store_piece(p.stored + (uint64_t)ring_slot(cursor, p.row, N) * row_stride, p.w, v);
 }
-__device__ __forceinline__ void insert_rows(const PieceFields& pf, uint32_t first, uint32_t every, uint32_t cursor, uint32_t N,
+__device__ __forceinline__ void insert_rows(const PieceFields& pf, uint32_t items, uint32_t first, uint32_t every, uint32_t cursor, uint32_t N,
                                             uint32_t row_stride, uint64_t step, const uint32_t* skip) {
-  const uint32_t items = pf.items();
 #pragma unroll 1
   for (uint32_t e = first; e < items; e += every) {
     const RowItem p = find_item(pf, e);
-    if (p.on) place_row_piece(p, cursor, N, row_stride, skip, load_piece(p.dense + step * pf.step[p.f], p.w));
+    if (p.row != 0xFFFFFFFFu) place_row_piece(p, cursor, N, row_stride, skip, load_piece(p.io + step * p.step + p.out, p.w));
   }
 }
 // Waits until this wave's loads have arrived and its stores have been acknowledged.
@@ -339,12 +456,12 @@ struct TreeView {
   uint32_t off_reg, n_reg;   // lane v of every wave: off[v], real nodes of level v (read from there: an LDS trip less per level)
   uint32_t V, N;
   uint32_t vt;               // the lowest level above the leaves of at most kTopNodes nodes
-  uint32_t* s_max;           // running maximum (WAVE: the team keeps its own copy)
+  uint32_t* s_max;           // running maximum (a team of one wave keeps its own)
   uint32_t* s_arrived;       // team waves that have come to one of its barriers, over all barriers (LDS)
   bool apart;                // there are waves outside the team
   uint32_t team;             // lanes of the team
   uint32_t* s_wild;          // the latest sampling with a uniform outside [0, 1) (0: none)
-  uint2* s_runs;             // [16] of every team wave: the leaf its elements begin with, what is known of them (see change_tree)
+  const uint32_t* nodes;     // the leaves sampled last (LDS)
   uint32_t met;              // what s_arrived has to reach at the team's next barrier, less a team's waves
   __device__ __forceinline__ uint32_t off(uint32_t v) const { return (uint32_t)__builtin_amdgcn_readlane((int)off_reg, (int)v); }
   __device__ __forceinline__ void set_leaf(uint32_t i, float v) const {
@@ -358,9 +475,10 @@ struct TreeView {
   __device__ __forceinline__ uint32_t n(uint32_t v) const { return (uint32_t)__builtin_amdgcn_readlane((int)n_reg, (int)v); }
   // Barrier of the team between phases that hand leaves or sums to other waves of it.  The hardware's barrier would hold
   // the team until the row waves come by; the team's waves count themselves in LDS instead (all of them are resident, and
-  // each comes to every barrier, so the wait ends).
+  // each comes to every barrier, so the wait ends).  Leaves stored to memory are not waited for: the waves of a workgroup
+  // share a compute unit, whose memory accesses pass its first-level cache in the order they are issued (which is why a
+  // fence of workgroup scope waits for none either).
   __device__ __forceinline__ void sync() {
-    if constexpr (MEM) wait_memory();
     if (!apart) {
       lds_barrier();
       return;
@@ -434,122 +552,84 @@ __device__ __forceinline__ float sum_top(const TreeView<MEM>& tv) {
   return x;
 }
 
-// An update of n elements (lane tid < n of the team: leaf ui gets uv) and then an insertion (lanes with `inserts`: row at
-// ring slot `slot`, value in_v or the running maximum), and the ancestors of both in one pass.  Called by the team.
+// An update (lane tid < n of the team: leaf i gets v) and then an insertion (lanes with `mine`: row at ring slot `slot`, its
+// value or the running maximum), and the ancestors of both in one pass.  Called by the team.
 struct UpdateWork {
-  bool on, mine, sorted;     // sorted: the indices are those of a sampled batch
-  uint32_t n, i, size;
+  bool on, mine, sorted;     // mine: this lane has an element; sorted: the indices are those of the batch sampled last
+  bool counted;              // several waves: the running maximum has the elements' values already (see note_update)
+  uint32_t n, i, size;       // n: elements (0: no update)
   float v;
-  uint32_t batch;            // sorted, !WAVE: the number of that sampling (from 1 on)
+  const float* prio;         // sorted, several waves: the values of all elements
+  uint32_t batch;            // likewise: the number of that sampling (from 1 on)
 };
 struct InsertWork {
   bool on, mine, given;      // given: the value is `v`, else the running maximum
-  uint32_t n, slot;
+  bool whole;                // every row is placed: no deferred ones, no values that may not be valid
+  uint32_t n, first, slot;   // first: ring slot of row 0
   float v;
 };
-// (WAVE: total is the root; else it is read from the copy)
-template <int LOGK, bool WAVE, bool MEM>
-__device__ __forceinline__ void change_tree(TreeView<MEM>& tv, const UpdateWork& u, const InsertWork& ins, uint32_t& max_bits,
-                                            uint32_t& flags, float& total) {
+// The same as valid_priority(v), in one instruction: plus or minus zero, positive and finite.
+__device__ __forceinline__ bool priority_class(float v) { return __builtin_isfpclass(v, 0x20 | 0x40 | 0x80 | 0x100); }
+__device__ __forceinline__ bool check_element(const UpdateWork& u, uint32_t& flags) {
+  if (!u.mine) return false;
+  if (!(u.i < u.size)) flags |= 1u;
+  else if (!priority_class(u.v)) flags |= 2u;
+  else return true;
+  return false;
+}
+
+// By a team of one wave.  lane_max: the lanes' share of the running maximum (the greatest of them is it).  Returns the root.
+// (Sampled leaves come in order from uniforms in [0, 1): the targets do not decrease then, and the walk keeps their order.
+// Elements of one leaf are neighbours and the last of them wins.  One look at the leaves and values says whether that is
+// so; where it is not, and for indices that were not sampled, markers decide.  The code of a step that has neither an
+// update nor an insertion left out runs without a branch up to the sums: at an instruction every five cycles a branch
+// around three of them is no gain.)
+template <int LOGK, bool MEM>
+__device__ __forceinline__ float change_by_wave(TreeView<MEM>& tv, const UpdateWork& u, const InsertWork& ins, float& lane_max,
+                                                uint32_t& flags, float total) {
   constexpr int LOGR = Wide<LOGK>::LOGR;
   const uint32_t tid = threadIdx.x;
-  bool valid = false, placed = false;
-  if (u.on) {
-    if (u.mine) {
-      if (!(u.i < u.size)) flags |= 1u;
-      else if (!valid_priority(u.v)) flags |= 2u;
-      else valid = true;
-    }
-    const uint32_t mx = valid && u.v > 0.0f ? __float_as_uint(u.v) : 0u;
-    bool won = valid;
+  const uint32_t next = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)u.i, 0x130 /* wave_shl:1: from the lane above */, 0xF, 0xF, true);
+  const bool last = not_before_here(tid) + 1u >= u.n;   // (worked out here each time: as a mask kept over the steps it costs more, scalar registers are short)
+  bool valid = u.mine, won = u.mine && (last || next != u.i);
+  const bool plain = u.sorted && __all(!u.mine || (u.i < u.size && priority_class(u.v) && (last || next >= u.i)));
+  if (__builtin_expect(!plain, 0)) {   // (out of the way: the code of a round is fetched line by line as it goes)
+    valid = check_element(u, flags);
     const uint32_t mark = 0x80000001u + tid;
-    // Sampled leaves come in order from uniforms in [0, 1): the targets do not decrease then, and the walk keeps their order.
-    // Uniforms outside may return leaves in any order; the markers decide there.  (One wave looks at its leaves; several
-    // go by whether a uniform was out of range, in which case the sampling has left its number in *tv.s_wild.)
-    bool in_order = u.sorted;
-    if (WAVE && in_order) {
-      // (elements of one leaf are neighbours, and the last of them wins)
-      const uint32_t next = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)u.i, 0x130 /* wave_shl:1: from the lane above */, 0xF, 0xF, true);
-      const bool last = not_before_here(tid) + 1u >= u.n;   // (worked out here each time: as a mask kept over the steps it costs more, scalar registers are short)
-      in_order = __all(!u.mine || (valid && (last || next >= u.i)));
-      if (in_order) won = valid && (last || next != u.i);
-    } else if (!WAVE && in_order) {
-      // The last valid element of every run of equal leaves wins.  Within a wave that is read off two masks: where runs
-      // begin, and which elements are valid.  A run that reaches the end of its wave may go on in the next ones: each
-      // wave leaves the leaf it begins with and whether that first run has a valid element (1) and is all there is (2).
-      const unsigned lane = tid & 63u;
-      const uint32_t wild = *tv.s_wild;   // (read here, looked at behind the barrier, which hides the trip)
-      const uint32_t below = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)u.i, 0x138 /* wave_shr:1: from the lane below */, 0xF, 0xF, true);
-      const unsigned long long begins = __ballot(u.mine && (lane == 0 || below != u.i)), good = __ballot(valid);
-      const unsigned long long later = lane == 63u ? 0ull : begins >> (lane + 1u);
-      const unsigned run_end = later ? lane + 1u + (unsigned)__builtin_ctzll(later) : 64u;   // first lane behind this lane's run
-      const unsigned long long behind = lane == 63u ? 0ull : (good >> (lane + 1u)) & (run_end == 64u && lane == 0 ? ~0ull : (1ull << (run_end - lane - 1u)) - 1ull);
-      const unsigned long long first_run = begins & ~1ull ? (1ull << __builtin_ctzll(begins & ~1ull)) - 1ull : ~0ull;
-      if (lane == 0) tv.s_runs[tid >> 6] = make_uint2(u.mine ? u.i : 0xFFFFFFFFu, ((good & first_run) ? 1u : 0u) | ((begins & ~1ull) ? 0u : 2u));
-      won = valid && !behind;
-      const uint32_t m = wave_max_u32(mx);
-      if (lane == 0 && m) atomicMax(tv.s_max, m);
-      tv.sync();
-      in_order = wave_value(wild) != u.batch;
-      if (in_order && won && run_end == 64u)
-        for (uint32_t w = (tid >> 6) + 1u; w < (tv.team >> 6); ++w) {
-          const uint2 r = tv.s_runs[w];
-          if (r.x != u.i) break;
-          if (r.y & 1u) won = false;
-          if (!(r.y & 2u) || !won) break;
-        }
-    }
-    if (__builtin_expect(!in_order, 0)) {   // (out of the way: the code of a round is fetched line by line as it goes)
-      if constexpr (MEM) {   // (markers in memory: atomics there, and a read that passes by the first-level cache)
-        GlobalPtr<uint32_t> bits = (GlobalPtr<uint32_t>)tv.leaves;
-        if (valid) __hip_atomic_fetch_max(&bits[u.i], mark, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if constexpr (WAVE) wait_memory(); else tv.sync();
-        won = valid && __hip_atomic_load(&bits[u.i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == mark;
-        if constexpr (WAVE) wait_memory(); else tv.sync();
-      } else {
-        uint32_t* bits = reinterpret_cast<uint32_t*>(tv.tree);
-        if (valid) atomicMax(&bits[u.i], mark);
-        if constexpr (WAVE) wave_order(); else tv.sync();
-        won = valid && bits[u.i] == mark;
-        if constexpr (WAVE) wave_order(); else tv.sync();
-      }
-    }
-    if (won) tv.set_leaf(u.i, u.v);
-    if constexpr (WAVE) {
-      const uint32_t m = wave_max_u32(mx);
-      max_bits = m > max_bits ? m : max_bits;
-      wave_order();
+    if constexpr (MEM) {   // (markers in memory: atomics there, and a read that passes by the first-level cache)
+      GlobalPtr<uint32_t> bits = (GlobalPtr<uint32_t>)tv.leaves;
+      wait_memory();
+      if (valid) __hip_atomic_fetch_max(&bits[u.i], mark, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      wait_memory();
+      won = valid && __hip_atomic_load(&bits[u.i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == mark;
+      wait_memory();
     } else {
-      if (!u.sorted && mx) atomicMax(tv.s_max, mx);
-      if (ins.on || !u.sorted) tv.sync();   // (the insertion comes behind the update)
+      uint32_t* bits = reinterpret_cast<uint32_t*>(tv.tree);
+      if (valid) atomicMax(&bits[u.i], mark);
+      wave_order();
+      won = valid && bits[u.i] == mark;
+      wave_order();
     }
   }
+  if (won) tv.set_leaf(u.i, u.v);
+  if (valid && u.v > lane_max) lane_max = u.v;
+  wave_order();
+  bool placed = ins.mine;
   if (ins.on) {
-    uint32_t mx = 0;
-    if (ins.mine) {
-      float v = __uint_as_float(WAVE ? max_bits : *tv.s_max);
-      placed = true;
-      if (ins.given) {
-        v = ins.v;
-        placed = valid_priority(v);
-        if (!placed) flags |= 2u;
-        mx = placed && v > 0.0f ? __float_as_uint(v) : 0u;
-      }
-      if (placed) tv.set_leaf(ins.slot, v);
-    }
+    float v = ins.v;
     if (ins.given) {
-      if constexpr (WAVE) {
-        const uint32_t m = wave_max_u32(mx);
-        max_bits = m > max_bits ? m : max_bits;
-      } else if (mx) {
-        atomicMax(tv.s_max, mx);
-      }
+      placed = ins.mine && priority_class(v);
+      if (ins.mine && !placed) flags |= 2u;
+      if (placed && v > lane_max) lane_max = v;
+    } else {
+      v = __uint_as_float(wave_max_u32(__float_as_uint(lane_max)));
     }
+    if (placed) tv.set_leaf(ins.slot, v);
   }
   // the ancestors (elements that share a parent store the same sum)
-  if (u.on || ins.on) {
-    if constexpr (WAVE) {
-      const bool together = !u.on || !ins.on || u.n + ins.n <= 64u;   // (no lane has both)
+  if (u.n + (ins.on ? ins.n : 0u)) {
+    const bool together = !ins.on || u.n + ins.n <= 64u;   // (no lane has both)
+    if (tv.vt > 1) {
       for (int pass = 0; pass < (together ? 1 : 2); ++pass) {
         const bool act = together ? valid || placed : pass == 0 ? valid : placed;
         const uint32_t leaf = together ? (placed ? ins.slot : u.i) : pass == 0 ? u.i : ins.slot;
@@ -561,27 +641,113 @@ __device__ __forceinline__ void change_tree(TreeView<MEM>& tv, const UpdateWork&
           }
         }
       }
-      wave_order();
-      total = sum_top<LOGK, MEM>(tv);
-      wave_order();
-    } else {
-      // A level of no more nodes than there are elements is recomputed whole (fewer lanes than elements).
-      const uint32_t elements = (u.on ? u.n : 0u) + (ins.on ? ins.n : 0u);
-      for (uint32_t v = 1; v < tv.vt; ++v) {
-        tv.sync();
-        const uint32_t nodes = tv.n(v);
-        if (nodes <= elements) {
-          for (uint32_t j = tid; j < nodes; j += tv.team) tv.tree[tv.off(v) + j] = child_group_sum<LOGK, MEM>(tv, v, j);
-          continue;
-        }
-        const uint32_t pu = u.i >> (v * LOGR), pi = ins.slot >> (v * LOGR);
-        if (valid) tv.tree[tv.off(v) + pu] = child_group_sum<LOGK, MEM>(tv, v, pu);
-        if (placed) tv.tree[tv.off(v) + pi] = child_group_sum<LOGK, MEM>(tv, v, pi);
-      }
-      tv.sync();
-      if (tid < 64u) sum_top<LOGK, MEM>(tv);
     }
+    wave_order();
+    total = sum_top<LOGK, MEM>(tv);
+    wave_order();
   }
+  return total;
+}
+
+// By a team of several waves.
+template <int LOGK, bool MEM>
+__device__ __forceinline__ void change_by_team(TreeView<MEM>& tv, const UpdateWork& u, const InsertWork& ins, uint32_t& flags) {
+  constexpr int LOGR = Wide<LOGK>::LOGR;
+  const uint32_t tid = threadIdx.x;
+  bool valid = false, placed = false;
+  if (u.on) {
+    valid = check_element(u, flags);
+    const uint32_t mark = 0x80000001u + tid;
+    bool won = valid, in_order = u.sorted;
+    if (in_order) {
+      // The last valid element of every run of equal leaves wins (the leaves are in order where no uniform was out of
+      // range, else the sampling has left its number in *tv.s_wild).  Within a wave that is read off two masks: where runs
+      // begin, and which elements are valid.  A run that reaches the end of its wave may go on in the next one; its last
+      // lane then looks at the elements behind it, seldom more than one (their leaves are still in LDS as they were sampled).
+      const unsigned lane = tid & 63u;
+      const uint32_t wild = *tv.s_wild, behind_wave = (tid | 63u) + 1u;
+      const uint32_t next_leaf = behind_wave < u.n ? tv.nodes[behind_wave] : 0xFFFFFFFFu;
+      const uint32_t below = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)u.i, 0x138 /* wave_shr:1: from the lane below */, 0xF, 0xF, true);
+      const unsigned long long begins = __ballot(u.mine && (lane == 0 || below != u.i)), good = __ballot(valid);
+      const unsigned long long later = lane == 63u ? 0ull : begins >> (lane + 1u);
+      const unsigned run_end = later ? lane + 1u + (unsigned)__builtin_ctzll(later) : 64u;   // first lane behind this lane's run
+      const unsigned long long behind = lane == 63u ? 0ull : (good >> (lane + 1u)) & (run_end == 64u && lane == 0 ? ~0ull : (1ull << (run_end - lane - 1u)) - 1ull);
+      won = valid && !behind;
+      in_order = wave_value(wild) != u.batch;
+      if (in_order && won && run_end == 64u && next_leaf == u.i)
+        for (uint32_t j = behind_wave; won && j < u.n && tv.nodes[j] == u.i; ++j) won = !priority_class(as_global(u.prio)[j]);
+    }
+    if (__builtin_expect(!in_order, 0)) {
+      if constexpr (MEM) {
+        GlobalPtr<uint32_t> bits = (GlobalPtr<uint32_t>)tv.leaves;
+        wait_memory();
+        tv.sync();
+        if (valid) __hip_atomic_fetch_max(&bits[u.i], mark, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        wait_memory();
+        tv.sync();
+        won = valid && __hip_atomic_load(&bits[u.i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == mark;
+        wait_memory();
+        tv.sync();
+      } else {
+        uint32_t* bits = reinterpret_cast<uint32_t*>(tv.tree);
+        if (valid) atomicMax(&bits[u.i], mark);
+        tv.sync();
+        won = valid && bits[u.i] == mark;
+        tv.sync();
+      }
+    }
+    // The insertion comes behind the update.  Where it fills its stretch of the ring whole, the update leaves the leaves
+    // there alone, and no barrier of the team is needed between the two.
+    const bool leave = ins.on && ins.whole;
+    const uint32_t at = u.i >= ins.first ? u.i - ins.first : u.i + (tv.N - ins.first);
+    if (won && !(leave && at < ins.n)) tv.set_leaf(u.i, u.v);
+    if (!u.counted) {
+      const uint32_t m = wave_max_u32(valid && u.v > 0.0f ? __float_as_uint(u.v) : 0u);
+      if ((tid & 63u) == 0 && m) atomicMax(tv.s_max, m);
+    }
+    if (ins.on && !(leave && (u.counted || ins.given))) tv.sync();
+  }
+  if (ins.on) {
+    uint32_t mx = 0;
+    if (ins.mine) {
+      float v = __uint_as_float(*tv.s_max);
+      placed = true;
+      if (ins.given) {
+        v = ins.v;
+        placed = priority_class(v);
+        if (!placed) flags |= 2u;
+        mx = placed && v > 0.0f ? __float_as_uint(v) : 0u;
+      }
+      if (placed) tv.set_leaf(ins.slot, v);
+    }
+    if (ins.given && mx) atomicMax(tv.s_max, mx);
+  }
+  // the ancestors (elements that share a parent store the same sum)
+  if (u.on || ins.on) {
+    // A level of no more nodes than there are elements is recomputed whole (fewer lanes than elements).
+    const uint32_t elements = (u.on ? u.n : 0u) + (ins.on ? ins.n : 0u);
+    for (uint32_t v = 1; v < tv.vt; ++v) {
+      tv.sync();
+      const uint32_t nodes = tv.n(v);
+      if (nodes <= elements) {
+        for (uint32_t j = tid; j < nodes; j += tv.team) tv.tree[tv.off(v) + j] = child_group_sum<LOGK, MEM>(tv, v, j);
+        continue;
+      }
+      const uint32_t pu = u.i >> (v * LOGR), pi = ins.slot >> (v * LOGR);
+      if (valid) tv.tree[tv.off(v) + pu] = child_group_sum<LOGK, MEM>(tv, v, pu);
+      if (placed) tv.tree[tv.off(v) + pi] = child_group_sum<LOGK, MEM>(tv, v, pi);
+    }
+    tv.sync();
+    if (tid < 64u) sum_top<LOGK, MEM>(tv);
+  }
+}
+
+// The values of the update that comes next raise the running maximum as soon as its elements are known: an insertion
+// behind that update finds it raised, without a barrier between the two.  (Only where nothing reads the maximum before the
+// update.)  Called by whole waves of a team of several.
+__device__ __forceinline__ void note_update(bool mine, uint32_t i, uint32_t size, float v, uint32_t* s_max) {
+  const uint32_t m = wave_max_u32(mine && i < size && valid_priority(v) && v > 0.0f ? __float_as_uint(v) : 0u);
+  if ((threadIdx.x & 63u) == 0 && m) atomicMax(s_max, m);
 }
 
 // Waves of the team with a uniform outside [0, 1) (or -0, which does no harm) leave the number of the sampling.  Lanes without
@@ -662,15 +828,19 @@ __device__ __forceinline__ void level_down(P grp, float& r, uint32_t& node, floa
 // r is not below the left one takes a rounding, or a uniform outside [0, 1): the first walk does not look, and arrives
 // at a leaf of zero if it ever should have stayed (a block of sum zero holds nothing else, and nodes beyond a level's
 // last have the group of zeros behind its groups for children).  Where that happens to any lane the wave walks again,
-// looking.  (With the right blocks' sums left out, and the sixteen children kept in registers instead of read a second
+// looking.  `call` is called once, behind the few nodes below the root or before the walk's last level (or where there is no
+// walk).  (With the right blocks' sums left out, and the sixteen children kept in registers instead of read a second
 // time once the chunk of four is known, a level takes two thirds of the 570 cycles it took.)
-template <int LOGK, bool MEM>
+template <int LOGK, bool MEM, bool CALL_LAST, typename F>
 __device__ __forceinline__ void walk_tree(const TreeView<MEM>& tv, uint32_t i, uint32_t n, float u, float total, float seg, uint32_t& node,
-                                          float& val) {
+                                          float& val, F&& call) {
   constexpr int LOGR = Wide<LOGK>::LOGR, R = Wide<LOGK>::R;
   node = 0xFFFFFFFFu;
   val = 0.0f;
-  if (!(total > 0.0f)) return;
+  if (!(total > 0.0f)) {
+    call();
+    return;
+  }
   const float r0 = ((float)(i < n ? i : n - 1) + u) * seg;
   float r = r0;
   node = 0;
@@ -681,10 +851,12 @@ __device__ __forceinline__ void walk_tree(const TreeView<MEM>& tv, uint32_t i, u
     turn_down<4>(c, r, node, val);
     --v;
   }
+  if constexpr (!CALL_LAST) call();
   for (; v > 0; --v) {
     float unused;
     level_down<LOGR>(static_cast<const float*>(tv.tree) + tv.off(v) + (size_t)min_u32(node, tv.n(v + 1)) * R, r, node, unused);
   }
+  if constexpr (CALL_LAST) call();
   const uint32_t n1 = tv.n(1);
   bool astray = false;
   if constexpr (MEM) {   // (no such group behind the leaves in memory)
@@ -715,11 +887,40 @@ __device__ __forceinline__ float mass_per_sample(float total, uint32_t n) {
   return (n & (n - 1u)) == 0u ? total * __uint_as_float(0x7F000000u - __float_as_uint(fn)) : total / fn;
 }
 
+// Smallest of the n <= 512 values in LDS (as bits, which order like positive values), by every calling wave for itself.  Called by
+// whole waves.
+__device__ __forceinline__ uint32_t smallest_value(const float* values, uint32_t n) {
+  const uint32_t lane = threadIdx.x & 63u;
+  uint32_t m = 0xFFFFFFFFu;
+  if (n <= 64u) {
+    if (lane < n) m = __float_as_uint(values[lane]);
+  } else {
+#pragma unroll
+    for (uint32_t k = 0; k < 2; ++k) {
+      const uint32_t e = 4u * (k * 64u + lane);
+      const Floats4 x = load_floats4(values + e);
+      if (e < n) m = min_u32(m, __float_as_uint(x.x));
+      if (e + 1u < n) m = min_u32(m, __float_as_uint(x.y));
+      if (e + 2u < n) m = min_u32(m, __float_as_uint(x.z));
+      if (e + 3u < n) m = min_u32(m, __float_as_uint(x.w));
+    }
+  }
+  return wave_min_u32(m);
+}
+
+// Who does the tree work: the first wave, the first few, or every wave, which then moves the rows as well.
+enum TeamForm { TEAM_ONE_WAVE, TEAM_WAVES, TEAM_ALL };
+static TeamForm team_form(uint32_t samples, uint32_t inserted) {
+  const uint32_t most = samples > inserted ? samples : inserted;
+  return most <= 64 ? TEAM_ONE_WAVE : most <= 512 ? TEAM_WAVES : TEAM_ALL;
+}
+
 // The list of steps.  What bounds it is one chain of instructions and LDS trips from step to step (the tree as one
 // step leaves it is what the next samples from), so everything that is not tree work is taken off that chain:
 //  - The waves split: the first ones (the team, a lane per sample and per inserted row) do the tree work, the others
-//    move the rows and turn values into weights, one step behind.  Batches of more than 512 leave no waves over; the
-//    team then does both in turn.
+//    move the rows and turn values into weights, one step behind, each in a loop of its own.  (As one loop that asks
+//    every wave at every turn what it is, the bookkeeping was a quarter of a step.)  Batches of more than 512 leave no
+//    waves over; the team then does both in turn.
 //  - Inputs are fetched a step ahead.  That is only right where no step reads what a step returns; the host has checked
 //    it (StreamArgs::ahead).  Where it does not hold, a step's results are stored and waited for before its update and
 //    the inputs of the step behind it are fetched (a build of its own: as a branch it costs the other lists 2 to 5 %, 50
@@ -732,22 +933,24 @@ __device__ __forceinline__ float mass_per_sample(float total, uint32_t n) {
 //  - Barriers wait for LDS only.  A __syncthreads() also waits for every store of the wave to be acknowledged from
 //    memory, a microsecond at each phase that writes results or rows.
 // The order that memory needs: the stored rows of an insertion are read by the gather of the same step at the earliest
-// (its lanes wait for their stores before the barrier that ends the sampling), and overwrite what the gather of the
-// step before has read (all of whose loads have arrived at the barrier in front of the insertion's stores).
-// 100 steps on 10 000 leaves at K = 16 (32 samples, 4 new rows of 41 bytes): 232 us; 1001 us as one phase after the
+// (its loads are issued behind the barrier that ends the sampling), and overwrite what the gather of the step before has
+// read (whose loads are issued in front of the barrier before the insertion's stores); the accesses of a workgroup's waves
+// keep that order (see TreeView::sync).
+// 100 steps on 10 000 leaves at K = 16 (32 samples, 4 new rows of 41 bytes): 172 us; 1001 us as one phase after the
 // other by the whole workgroup with a full barrier between them.
 // AHEAD: no step reads what a step returns.
-template <int LOGK, bool WAVE, bool MEM, bool AHEAD>
+template <int LOGK, TeamForm FORM, bool MEM, bool AHEAD>
 __global__ void __launch_bounds__(1024)
 k_run_steps(StreamKernelArgs ka) {
+  constexpr bool WAVE = FORM == TEAM_ONE_WAVE, apart = FORM != TEAM_ALL;
   const Geom& g = ka.g;
   const StreamArgs& a = ka.a;
   extern __shared__ __attribute__((aligned(16))) float tree[];
   __shared__ LevelTable tab;
   __shared__ uint32_t s_off[kStreamLevels + 2], s_n[kStreamLevels + 1];
   __shared__ uint32_t s_max, s_vmin[2], s_bmin[2], s_wild, s_flags, s_arrived;
-  __shared__ uint2 s_runs[16];
   __shared__ PieceFields s_rows, s_ins;
+  __shared__ uint2 s_share[16];
   const uint32_t t = blockIdx.x;
   const uint32_t tid = threadIdx.x, lane = tid & 63u;
   const uint32_t H = g.H, T = g.T, B = a.B, n_ins = a.n_insert, N = g.N;
@@ -766,9 +969,8 @@ k_run_steps(StreamKernelArgs ka) {
   }
   // lanes of the team, of the rows, of the weights
   const uint32_t wanted = WAVE ? 64u : ((B > n_ins ? B : n_ins) + 63u) / 64u * 64u;
-  const bool apart = wanted <= 512u;
   const uint32_t team = apart ? wanted : 1024u;   // (not apart: every wave comes to the team's barriers)
-  const bool in_team = tid < team, in_rows = !apart || tid >= team;
+  const bool in_team = tid < team;
   const uint32_t rn = apart ? 1024u - team : 1024u, rl = apart ? tid - team : tid;
   const uint32_t rw = wave_value(rl >> 6), rws = rn >> 6;   // number of this wave among the row waves, and how many there are
   const uint32_t w0 = apart ? 1024u - (B + 63u) / 64u * 64u : 0u;
@@ -778,16 +980,10 @@ k_run_steps(StreamKernelArgs ka) {
     const bool rows = tid < 192;
     const FieldTable* ft = kernarg_at<FieldTable>(offsetof(StreamKernelArgs, a) + (rows ? offsetof(StreamArgs, rows) : offsetof(StreamArgs, ins)));
     const uint32_t n = rows ? B : n_ins;
-    fill_piece_fields(ft, lane < (uint32_t)kMaxFields ? ft->io[lane] : nullptr, t, n, (uint64_t)T * n, rows ? &s_rows : &s_ins);
+    fill_piece_fields(ft, lane < (uint32_t)kMaxFields ? ft->io[lane] : nullptr, t, n, (uint64_t)T * n, rows ? gathering_waves(B, rws) : rws, rows ? &s_rows : &s_ins,
+                      rows ? s_share : nullptr);
   }
   __syncthreads();
-  const uint32_t insert_items = in_rows ? s_ins.items() : 0u;
-  RowItem ip;
-  uint4 iv;
-  if (rw < insert_items) {   // (the first item of an insertion is fetched a step ahead)
-    ip = find_item(s_ins, rw);
-    if (ip.on) iv = load_piece(ip.dense, ip.w);
-  }
   // inputs of the team: the uniform of the step to sample, value (and index) of the update to apply, inserted priority
   float u_i = 0.0f, u_next = 0.0f, up_v = 0.0f, in_v = 0.0f;
   [[maybe_unused]] float beta_i = 0.0f;
@@ -821,126 +1017,205 @@ k_run_steps(StreamKernelArgs ka) {
   tv.s_max = &s_max;
   tv.s_arrived = &s_arrived;
   tv.s_wild = &s_wild;
-  tv.s_runs = s_runs;
+  tv.nodes = nodes;
   tv.apart = apart;
   tv.team = team;
   tv.met = 0;
-  uint32_t cursor = a.cursor, size = a.size, upd_size = 0;
-  uint32_t flags = 0;
   __syncthreads();
-  uint32_t max_bits = s_max;      // (WAVE: the team's copy; else s_max counts)
-  uint32_t node = 0xFFFFFFFFu;    // this lane's sample of the step before
-  float val = 0.0f;
-  float total = tree[s_off[V]];   // (WAVE: the root as the latest change has left it)
-  for (uint32_t s = 0;; ++s) {
-    const bool more = s < a.n_steps;
-    // ---- rows and weights of the step before
-    float w_out = 0.0f, v_out = 0.0f;
-    uint32_t n_out = 0;
-    if (s) {
-      if (in_rows) gather_rows(s_rows, rw, rws, nodes, N, a.rows.row_stride, s - 1, flags);
-      if (weigher) {
-        n_out = nodes[tid - w0];
-        v_out = apart ? values[tid - w0] : val;
-        if (a.out_w) {
-          const uint32_t vmin = s_vmin[(s - 1) & 1u];
-          const uint32_t least = a.buffer_norm ? s_bmin[(s - 1) & 1u] : vmin;
-          w_out = vmin == kNoMin ? 0.0f : importance_weight(v_out, __uint_as_float(least), AHEAD ? a.beta[s - 1] : beta_i);
-        }
+  uint32_t flags = 0;
+  float lane_max = __uint_as_float(s_max);   // (WAVE: the lanes' share of it; else s_max counts)
+
+  auto work = [&](auto does_tree, auto does_rows) {
+    constexpr bool TREE = decltype(does_tree)::value, ROWS = decltype(does_rows)::value;
+    const bool gives = a.upd_prio != nullptr, own = a.upd_is_sampled != 0;
+    const size_t batch = (size_t)T * B;              // samples of a step, over all trees
+    size_t at = (size_t)t * B + tid;                 // this lane's sample in the inputs of step s
+    uint32_t cursor = a.cursor, size = a.size, upd_size = 0;
+    uint32_t node = 0xFFFFFFFFu;                     // this lane's sample of the step before
+    float val = 0.0f;
+    float total = tree[s_off[V]];                    // (WAVE: the root as the latest change has left it)
+    // this wave's share of the rows, the same in every step: the first item of the insertion, fetched a step ahead, and the
+    // first few of the gather (a team that moves rows as well has no registers for those)
+    RowItem ip{};
+    ip.row = 0xFFFFFFFFu;
+    uint4 iv;
+    uint32_t more_first = 0, more_last = 0, insert_items = 0;   // the items of the gather beyond the first few; items of the insertion
+    GatherItems<kInFlight> items;
+    if constexpr (ROWS) {
+      insert_items = wave_value(s_ins.items);
+      if (rw < insert_items) {
+        ip = find_item(s_ins, rw);
+        if (ip.row != 0xFFFFFFFFu) iv = load_piece(ip.io + ip.out, ip.w);
+      }
+      more_first = wave_value(s_share[rw].x);
+      more_last = wave_value(s_share[rw].y);
+      if constexpr (!TREE) {
+        items.prepare(s_rows, more_first, more_last, 0);
+        more_first += kInFlight;
       }
     }
-    auto store_results = [&]() {   // of the step before
-      if (!weigher) return;
-      const size_t o = ((size_t)(s - 1) * T + t) * B + (tid - w0);
-      a.out_idx[o] = n_out;
-      if (a.out_prio) a.out_prio[o] = v_out;
-      if (a.out_w) a.out_w[o] = w_out;
-    };
-    if (!AHEAD && s) {
-      store_results();
-      wait_memory();
+    for (uint32_t s = 0;; ++s) {
+      const bool more = s < a.n_steps;
+      // ---- rows and weights of the step before
+      float w_out = 0.0f, v_out = 0.0f;
+      uint32_t n_out = 0;
+      if (ROWS && s) {
+        if (more_first < more_last) gather_rest<TREE ? 4 : 2>(s_rows, more_first, more_last, nodes, N, a.rows.row_stride, s - 1, flags);
+        if constexpr (!TREE) items.load(nodes, N, a.rows.row_stride);
+        uint32_t least = 0;
+        if (a.out_w && tid >= w0) {   // (whole waves)
+          if (a.buffer_norm) least = s_bmin[(s - 1) & 1u];
+          else if (TREE) least = s_vmin[(s - 1) & 1u];
+          else least = smallest_value(values, B);
+        }
+        if (weigher) {
+          n_out = nodes[tid - w0];
+          v_out = TREE ? val : values[tid - w0];
+          if (a.out_w) {
+            w_out = n_out == 0xFFFFFFFFu ? 0.0f : importance_weight(v_out, __uint_as_float(least), AHEAD ? a.beta[s - 1] : beta_i);
+          }
+        }
+      }
+      auto store_results = [&]() {   // of the step before
+        if (!ROWS || !s) return;
+        if constexpr (!TREE) items.store(N, flags);
+        if (!weigher) return;
+        const size_t o = ((size_t)(s - 1) * T + t) * B + (tid - w0);
+        a.out_idx[o] = n_out;
+        if (a.out_prio) a.out_prio[o] = v_out;
+        if (a.out_w) a.out_w[o] = w_out;
+      };
+      // (One wave of tree work comes late to the next barrier, and soon to the one behind it; several are early at the first
+      // and walk longer behind it.)
+      constexpr bool stores_first = WAVE || !AHEAD;
+      if (stores_first) store_results();
+      if (!AHEAD && s) {
+        wait_memory();
+        lds_barrier();
+        if (TREE && tid < B) {
+          if (gives) {
+            up_v = a.upd_prio[at - batch];
+            if (!own) up_i = a.upd_idx[at - batch];
+          }
+          if (more) u_i = a.u[at];
+        }
+        if (more) {
+          ip.io += ip.step;
+          if (ROWS && ip.row != 0xFFFFFFFFu) iv = load_piece(ip.io + ip.out, ip.w);
+          if (TREE && inserts && a.ins_prio) in_v = a.ins_prio[((size_t)s * T + t) * n_ins + j_ins];
+          beta_i = a.beta[s];
+        }
+      }
+      const bool do_upd = s > 0 && gives, do_ins = more && n_ins > 0;
+      const uint32_t first = cursor;
+      // (where this step's first piece of the insertion goes, and the next step's: nothing but the store is left to do behind
+      // the barrier, which is what the team waits for at the next one)
+      uint8_t* place = nullptr;
+      uint4 next_iv;
+      if (ROWS && do_ins && ip.w) {
+        if (AHEAD) ip.io += ip.step;
+        if (ip.row != 0xFFFFFFFFu) {
+          place = ip.stored + (uint64_t)ring_slot(first, ip.row, N) * a.ins.row_stride;
+          if (AHEAD && s + 1 < a.n_steps) next_iv = load_piece(ip.io + ip.out, ip.w);
+        }
+      }
+      // ---- the tree: update of the step before, insertion of this one
+      if constexpr (TREE) {
+        UpdateWork up;
+        up.on = do_upd;
+        up.mine = do_upd && tid < B;
+        up.sorted = own;
+        up.counted = AHEAD;
+        up.n = do_upd ? B : 0u;
+        up.i = own ? node : up_i;
+        up.size = upd_size;
+        up.v = up_v;
+        up.prio = a.upd_prio + (at - batch - tid);
+        up.batch = s;
+        InsertWork in;
+        in.on = do_ins;
+        in.mine = do_ins && inserts;
+        in.given = a.ins_prio != nullptr;
+        in.whole = !in.given;
+        in.n = n_ins;
+        in.first = first;
+        in.slot = inserts ? ring_slot(first, j_ins, N) : 0u;
+        in.v = in_v;
+        if constexpr (WAVE) total = change_by_wave<LOGK, MEM>(tv, up, in, lane_max, flags, total);
+        else change_by_team<LOGK, MEM>(tv, up, in, flags);
+        // inputs of the next round
+        if (AHEAD && tid < B) {
+          if (more && gives) {
+            up_v = a.upd_prio[at];
+            if (!own) up_i = a.upd_idx[at];
+          }
+          if (s + 1 < a.n_steps) u_next = a.u[at + batch];   // (here and not behind the walk: the next wait would be for it)
+        }
+        if (AHEAD && inserts && s + 1 < a.n_steps && a.ins_prio) in_v = a.ins_prio[((size_t)(s + 1) * T + t) * n_ins + j_ins];
+      }
+      if (do_ins) {
+        cursor = ring_slot(cursor, n_ins, N);
+        size = size + n_ins > N ? N : size + n_ins;
+      }
+      upd_size = size;
+      // ---- the rows of the step before have been asked for; the tree is whole.  (A team of one wave has no use for this
+      // barrier itself: it passes it as late as the walk allows, where the row waves have long come.)
+      const bool late = WAVE && TREE && more && !a.buffer_norm;
+      if (!late) lds_barrier();
+      if constexpr (ROWS) {
+        if (do_ins) {
+          if (place) store_piece(place, ip.w, iv);
+          if (AHEAD) iv = next_iv;
+          if (rw + rws < insert_items) insert_rows(s_ins, insert_items, rw + rws, rws, first, N, a.ins.row_stride, s, nullptr);
+        }
+        if (!stores_first) store_results();
+      }
+      if (!more) break;
+      if constexpr (ROWS) {
+        // (read by the weights of step s - 1, before the barrier)
+        if ((TREE || a.buffer_norm) && rl == 0) s_vmin[(s + 1) & 1u] = s_bmin[(s + 1) & 1u] = kNoMin;
+        // ---- weights relative to the whole tree: its smallest positive leaf
+        if (a.buffer_norm && a.out_w) {
+          uint32_t m = kNoMin;
+          for (uint32_t e = rl; e < N; e += rn) m = min_u32(m, positive_bits(tv.leaf(e)));
+          m = wave_min_u32(m);
+          if (lane == 0 && m != kNoMin) atomicMin(&s_bmin[s & 1u], m);
+        }
+      }
+      // ---- sampling
+      if constexpr (TREE) {
+        if (WAVE || (tid & ~63u) < B) {
+          if constexpr (!WAVE) {
+            note_wild(u_i, s + 1u, &s_wild);
+            total = tree[tv.off(V)];
+          }
+          walk_tree<LOGK, MEM, true>(tv, tid, B, u_i, total, mass_per_sample(total, B), node, val, [&] {
+            if (late) lds_barrier();
+          });
+          if (node == 0xFFFFFFFFu && tid == 0) flags |= 4u;
+          if (ROWS && a.out_w) {
+            const uint32_t m = wave_min_u32(tid < B ? __float_as_uint(val) : kNoMin);
+            if (lane == 0) atomicMin(&s_vmin[s & 1u], m);
+          }
+          if (tid < B) {
+            nodes[tid] = node;
+            if (!ROWS) values[tid] = val;
+          }
+          if (AHEAD) u_i = u_next;
+        }
+        if (!WAVE && AHEAD && gives) note_update(tid < B, own ? node : up_i, upd_size, up_v, &s_max);
+        at += batch;
+      }
       lds_barrier();
-      if (in_team && tid < B) {
-        const size_t bo = ((size_t)(s - 1) * T + t) * B + tid;
-        if (a.upd_prio) {
-          up_v = a.upd_prio[bo];
-          if (!a.upd_is_sampled) up_i = a.upd_idx[bo];
-        }
-        if (more) u_i = a.u[bo + (size_t)T * B];
-      }
-      if (more) {
-        if (rw < insert_items && ip.on) iv = load_piece(ip.dense + (uint64_t)s * s_ins.step[ip.f], ip.w);
-        if (inserts && a.ins_prio) in_v = a.ins_prio[((size_t)s * T + t) * n_ins + j_ins];
-        if constexpr (!AHEAD) beta_i = a.beta[s];
-      }
     }
-    // ---- the tree: update of the step before, insertion of this one
-    const bool do_upd = s > 0 && a.upd_prio != nullptr, do_ins = more && n_ins > 0;
-    if (in_team) {
-      const UpdateWork up{do_upd, in_team && tid < B, a.upd_is_sampled != 0, B, a.upd_is_sampled ? node : up_i, upd_size, up_v, s};
-      const InsertWork in{do_ins, inserts, a.ins_prio != nullptr, n_ins, inserts ? ring_slot(cursor, j_ins, N) : 0u, in_v};
-      change_tree<LOGK, WAVE, MEM>(tv, up, in, max_bits, flags, total);
-      // inputs of the next round
-      if (AHEAD && in_team && tid < B) {
-        const size_t bo = ((size_t)s * T + t) * B + tid;
-        if (more && a.upd_prio) {
-          up_v = a.upd_prio[bo];
-          if (!a.upd_is_sampled) up_i = a.upd_idx[bo];
-        }
-        if (s + 1 < a.n_steps) u_next = a.u[bo + (size_t)T * B];   // (here and not behind the walk: the next wait would be for it)
-      }
-    }
-    if (do_ins) {
-      cursor = ring_slot(cursor, n_ins, N);
-      size = size + n_ins > N ? N : size + n_ins;
-    }
-    upd_size = size;
-    // ---- the rows of the step before have been read; the tree is whole
-    if (WAVE && MEM && a.buffer_norm) wait_memory();   // (!WAVE: the team has waited for its leaves)
-    lds_barrier();
-    if (do_ins && in_rows) {
-      const uint32_t first = cursor >= n_ins ? cursor - n_ins : cursor + (N - n_ins);
-      if (rw < insert_items && ip.on) place_row_piece(ip, first, N, a.ins.row_stride, nullptr, iv);
-      insert_rows(s_ins, rw + rws, rws, first, N, a.ins.row_stride, s, nullptr);
-      wait_memory();
-    }
-    if (AHEAD && s) store_results();
-    if (!more) break;
-    if (AHEAD && s + 1 < a.n_steps && n_ins) {
-      if (rw < insert_items && ip.on) iv = load_piece(ip.dense + (uint64_t)(s + 1) * s_ins.step[ip.f], ip.w);
-      if (inserts && a.ins_prio) in_v = a.ins_prio[((size_t)(s + 1) * T + t) * n_ins + j_ins];
-    }
-    if (tid == 0) s_vmin[(s + 1) & 1u] = s_bmin[(s + 1) & 1u] = kNoMin;   // (read by the weights of step s - 1, before the barrier)
-    // ---- weights relative to the whole tree: its smallest positive leaf
-    if (a.buffer_norm && a.out_w && in_rows) {
-      uint32_t m = kNoMin;
-      for (uint32_t e = rl; e < N; e += rn) m = min_u32(m, positive_bits(tv.leaf(e)));
-      m = wave_min_u32(m);
-      if (lane == 0 && m != kNoMin) atomicMin(&s_bmin[s & 1u], m);
-    }
-    // ---- sampling
-    if (in_team && (WAVE || (tid & ~63u) < B)) {
-      if constexpr (!WAVE) note_wild(u_i, s + 1u, &s_wild);
-      if constexpr (!WAVE) total = tree[tv.off(V)];
-      walk_tree<LOGK, MEM>(tv, tid, B, u_i, total, mass_per_sample(total, B), node, val);
-      if (node == 0xFFFFFFFFu) {
-        if (tid == 0) flags |= 4u;
-      } else if (a.out_w) {
-        const uint32_t m = wave_min_u32(tid < B ? __float_as_uint(val) : kNoMin);
-        if (lane == 0) {
-          if constexpr (WAVE) s_vmin[s & 1u] = m;
-          else atomicMin(&s_vmin[s & 1u], m);
-        }
-      }
-      if (tid < B) {
-        nodes[tid] = node;
-        if (apart) values[tid] = val;
-      }
-      if constexpr (AHEAD) u_i = u_next;
-    }
-    lds_barrier();
+  };
+  if constexpr (!apart) work(std::true_type{}, std::true_type{});
+  else if (in_team) work(std::true_type{}, std::false_type{});
+  else work(std::false_type{}, std::true_type{});
+  if (WAVE && in_team) {
+    const uint32_t m = wave_max_u32(__float_as_uint(lane_max));
+    if (tid == 0) s_max = m;
   }
-  if (WAVE && tid == 0) s_max = max_bits;
   __syncthreads();
   lds_tree_store<LOGK>(g, t, tab, lt, flags, &s_flags);
 }
@@ -955,59 +1230,98 @@ k_run_steps(StreamKernelArgs ka) {
 //
 // The requests are taken in rounds of at most one update, then one insertion, then one sampling request: what a step
 // of k_run_steps does between two of its samplings, with parts left out where the queue has something else.  A round
-// runs as a step does there (see above): its tree changes in one pass over the ancestors, rows and weights of the
-// sampling request before it beside them, and what it reads fetched in the round before.  The requests themselves come
-// in two rounds ahead (three at a time: a round takes no more).
+// runs as a step does there (see above): tree work and row work in loops of their own, and what a round reads fetched in
+// the round before.  One wave decodes: it fetches the requests three rounds ahead (three at a time: a round takes no more) and
+// lays out the rounds two ahead, each as one run of words that a wave takes in with two loads, a word per lane; the fields
+// of a round are then read from its lanes.  (With every wave at the requests' fields, one LDS trip each, rounds of 64 samples
+// on 4096 leaves at K = 16 took 4.0 us where they take 2.2.)
 // Fetching ahead is only right where a request reads nothing that one just before it writes (an update whose index
 // array is the sampled one, say).  The host has checked that (QueueArgs::ahead); where it does not hold, every
 // request is a round of its own with an empty one behind it, which brings all results to memory.
-// 20 times (insert 16 rows, sample 512, update them) on 30 000 leaves at K = 16: 188 us; 353 us one request after the
+// 20 times (insert 16 rows, sample 512, update them) on 30 000 leaves at K = 16: 171 us; 353 us one request after the
 // other by the whole workgroup with a full barrier between their phases.
 struct QueueKernelArgs {            // one kernel argument (Geom first: see fill_level_table)
   Geom g;
   QueueArgs a;
 };
 constexpr uint32_t kRoundRequests = 3, kRequestWords = sizeof(per_request) / 4;
-struct QueueRound {                 // what a round takes: places of its requests among the three fetched for it (3: none)
-  uint32_t upd, ins, smp, used;
+// A round as words in LDS: its sampling request, its insertion, its update (the count of one it has not is 0), and whether the
+// queue goes on up to it.
+constexpr uint32_t kRoundSample = 0, kRoundInsert = kRequestWords, kRoundUpdate = 2 * kRequestWords, kRoundMore = 3 * kRequestWords;
+constexpr uint32_t kRoundWords = kRoundMore + 2;
+static_assert(sizeof(per_request) % 8 == 0 && kRoundWords <= 128 && kRoundUpdate >= 64 && kRoundInsert + 16 <= 64, "two words per lane");
+#define PER_REQUEST_WORD(field) (offsetof(per_request, field) / 4)
+struct Round {                      // the same, in the lanes of a wave
+  uint32_t lo, hi;
+  template <uint32_t AT>
+  __device__ __forceinline__ uint32_t word() const {
+    return (uint32_t)__builtin_amdgcn_readlane((int)(AT < 64 ? lo : hi), (int)(AT & 63u));
+  }
+  template <uint32_t AT, typename T>
+  __device__ __forceinline__ T* pointer() const { return reinterpret_cast<T*>((uint64_t)word<AT + 1>() << 32 | word<AT>()); }
+  __device__ __forceinline__ void read(const uint32_t* words) {
+    const uint32_t lane = threadIdx.x & 63u;
+    lo = words[lane];
+    hi = words[64u + lane < kRoundWords ? 64u + lane : 64u];
+  }
+  __device__ __forceinline__ uint32_t samples() const { return word<kRoundSample + PER_REQUEST_WORD(n)>(); }
+  __device__ __forceinline__ uint32_t inserts() const { return word<kRoundInsert + PER_REQUEST_WORD(n)>(); }
+  __device__ __forceinline__ uint32_t updates() const { return word<kRoundUpdate + PER_REQUEST_WORD(n)>(); }
+  __device__ __forceinline__ bool more() const { return word<kRoundMore>() != 0; }
 };
-// The round that starts with the `left` requests of q (at most three are looked at).
-__device__ __forceinline__ QueueRound take_round(const per_request* q, uint32_t left, bool single) {
-  QueueRound r{3, 3, 3, 0};
-  uint32_t stage = 0;   // 1: past the update, 2: past the insertion, 3: past the sampling
+// Lays out the round that starts with the `left` requests in the lanes of one wave (word w of them in lane w of x or, from 64
+// on, of y).  Returns how many it takes.
+__device__ __forceinline__ uint32_t lay_out_round(uint32_t x, uint32_t y, uint32_t left, bool single, bool gap, uint32_t* words) {
+  const uint32_t lane = threadIdx.x & 63u;
+  uint32_t upd = 3, ins = 3, smp = 3, used = 0, stage = 0;   // places of its requests; stage 1: past the update, 2: past the insertion, 3: past the sampling
 #pragma unroll
   for (uint32_t k = 0; k < kRoundRequests; ++k) {
-    const uint32_t op = k < left ? (uint32_t)__builtin_amdgcn_readfirstlane((int)q[k].op) : 0u;
+    const uint32_t at = k * kRequestWords;
+    const uint32_t op = k < left && !gap ? (uint32_t)__builtin_amdgcn_readlane((int)(at < 64 ? x : y), (int)(at & 63u)) : 0u;
     const bool u = op == PER_OP_UPDATE && stage < 1, i = op == PER_OP_INSERT && stage < 2, s = op == PER_OP_SAMPLE && stage < 3;
-    if (r.used == k && (u || i || s) && !(single && k)) {
-      if (u) r.upd = k, stage = 1;
-      if (i) r.ins = k, stage = 2;
-      if (s) r.smp = k, stage = 3;
-      r.used = k + 1;
+    if (used == k && (u || i || s) && !(single && k)) {
+      if (u) upd = k, stage = 1;
+      if (i) ins = k, stage = 2;
+      if (s) smp = k, stage = 3;
+      used = k + 1;
     }
   }
-  if (r.used == 0 && left) r.used = 1;   // (an unknown operation is passed over: the kernel ends whatever the queue holds)
-  return r;
+  if (used == 0 && left && !gap) used = 1;   // (an unknown operation is passed over: the kernel ends whatever the queue holds)
+  auto put = [&](uint32_t w, uint32_t value) {
+    const uint32_t k = w < kRequestWords ? 0u : w < 2u * kRequestWords ? 1u : 2u;
+    const uint32_t part = k == smp ? kRoundSample : k == ins ? kRoundInsert : k == upd ? kRoundUpdate : 0xFFFFFFFFu;
+    if (w < kRoundRequests * kRequestWords && part != 0xFFFFFFFFu) words[part + (w - k * kRequestWords)] = value;
+  };
+  put(lane, x);
+  put(lane + 64u, y);
+  if (lane == 0) {
+    if (smp == 3) words[kRoundSample + PER_REQUEST_WORD(n)] = 0;
+    if (ins == 3) words[kRoundInsert + PER_REQUEST_WORD(n)] = 0;
+    if (upd == 3) words[kRoundUpdate + PER_REQUEST_WORD(n)] = 0;
+    words[kRoundMore] = left != 0 ? 1u : 0u;
+  }
+  return used;
 }
-template <int LOGK, bool WAVE, bool MEM>
+template <int LOGK, TeamForm FORM, bool MEM>
 __global__ void __launch_bounds__(1024)
 k_run_requests(QueueKernelArgs ka) {
+  constexpr bool WAVE = FORM == TEAM_ONE_WAVE, apart = FORM != TEAM_ALL;
   const Geom& g = ka.g;
   const QueueArgs& a = ka.a;
   extern __shared__ __attribute__((aligned(16))) float tree[];
   __shared__ LevelTable tab;
   __shared__ uint32_t s_off[kStreamLevels + 2], s_n[kStreamLevels + 1];
-  __shared__ per_request s_req[3][kRoundRequests];   // round i: s_req[i % 3]
+  __shared__ uint32_t s_round[3][kRoundWords];       // round i: s_round[i % 3]
   __shared__ PieceFields s_rows[2], s_ins[2];        // by parity of the round
+  __shared__ uint2 s_share[2][16];
   __shared__ uint32_t s_skip[2][32];                 // bit j: row j of the round's insertion is deferred
   __shared__ uint32_t s_max, s_vmin[2], s_bmin[2], s_wild, s_flags, s_arrived;
-  __shared__ uint2 s_runs[16];
   const uint32_t t = blockIdx.x;
   const uint32_t tid = threadIdx.x, lane = tid & 63u;
-  const uint32_t H = g.H, N = g.N, n_requests = a.n_requests;
+  const uint32_t H = g.H, N = g.N, n_requests = a.n_requests, V = a.levels;
   const FieldTable* fields = kernarg_at<FieldTable>(offsetof(QueueKernelArgs, a) + offsetof(QueueArgs, fields));
   const uint32_t* queue = reinterpret_cast<const uint32_t*>(a.queue);
-  const uint32_t V = a.levels;
+  const bool single = a.ahead == 0;
   fill_level_table(H, t, &tab);
   if (tid >= 64 && tid <= 64 + V + 1) {
     s_off[tid - 64] = kernarg_at<QueueArgs>(offsetof(QueueKernelArgs, a))->off[tid - 64];
@@ -1020,31 +1334,32 @@ k_run_requests(QueueKernelArgs ka) {
     s_flags = 0;
     s_arrived = 0;
   }
-  // words of the three requests from `at` on, two per lane of one wave
-  const bool fetcher = tid >= 960;
-  constexpr uint32_t kFetch = kRoundRequests * kRequestWords;
-  static_assert(kFetch <= 128, "two words per lane");
-  auto fetch = [&](uint32_t at, uint32_t& x, uint32_t& y) {
-    const uint64_t w0 = (uint64_t)at * kRequestWords, all = (uint64_t)n_requests * kRequestWords;
-    x = y = 0;
-    if (w0 + lane < all) x = queue[w0 + lane];
-    if (lane + 64u < kFetch && w0 + lane + 64u < all) y = queue[w0 + lane + 64u];
+  if (tid < 64) s_skip[tid >> 5][tid & 31u] = 0;
+  // the decoding wave: requests of the round to lay out next in its lanes, where they start in the queue
+  const bool decodes = tid >= 896 && tid < 960;
+  uint32_t pos = 0, req_x = 0, req_y = 0, rounds = 0;
+  bool gap = false;
+  auto fetch = [&] {
+    const uint64_t w0 = (uint64_t)(pos < n_requests ? pos : n_requests) * kRequestWords, all = (uint64_t)n_requests * kRequestWords;
+    req_x = req_y = 0;
+    if (w0 + lane < all) req_x = queue[w0 + lane];
+    if (lane + 64u < kRoundRequests * kRequestWords && w0 + lane + 64u < all) req_y = queue[w0 + lane + 64u];
   };
-  auto park = [&](uint32_t slot, uint32_t x, uint32_t y) {
-    uint32_t* dst = reinterpret_cast<uint32_t*>(&s_req[slot][0]);
-    dst[lane] = x;
-    if (lane + 64u < kFetch) dst[lane + 64u] = y;
+  auto decode = [&] {   // (single: a round with nothing in it behind every request)
+    const uint32_t used = lay_out_round(req_x, req_y, pos < n_requests ? n_requests - pos : 0u, single, gap, s_round[rounds % 3u]);
+    gap = single && used != 0;
+    pos += used;
+    ++rounds;
+    fetch();
   };
-  if (fetcher) {
-    uint32_t x, y;
-    fetch(0, x, y);
-    park(0, x, y);
+  if (decodes) {
+    fetch();
+    decode();
+    decode();
   }
   // lanes of the team, of the rows (the weights: see k_run_steps)
-  const uint32_t wanted = WAVE ? 64u : (a.most + 63u) / 64u * 64u;
-  const bool apart = wanted <= 512u;
-  const uint32_t team = apart ? wanted : 1024u;   // (not apart: every wave comes to the team's barriers)
-  const bool in_team = tid < team, in_rows = !apart || tid >= team;
+  const uint32_t team = WAVE ? 64u : apart ? (a.most + 63u) / 64u * 64u : 1024u;
+  const bool in_team = tid < team;
   const uint32_t rn = apart ? 1024u - team : 1024u, rl = apart ? tid - team : tid;
   const uint32_t rw = wave_value(rl >> 6), rws = rn >> 6;   // number of this wave among the row waves, and how many there are
   __syncthreads();
@@ -1071,221 +1386,288 @@ k_run_requests(QueueKernelArgs ka) {
   tv.s_max = &s_max;
   tv.s_arrived = &s_arrived;
   tv.s_wild = &s_wild;
-  tv.s_runs = s_runs;
+  tv.nodes = nodes;
   tv.apart = apart;
   tv.team = team;
   tv.met = 0;
-  uint32_t cursor = a.cursor, size = a.size;
+  // The table of one request's fields, by one wave (words: the request's part of its round).  Where the one before it asked
+  // for the same fields of as many rows, only the caller's arrays change.
+  auto fill_fields = [&](const uint32_t* words, PieceFields* pf, uint2* share) {
+    const uint32_t n = wave_value(words[PER_REQUEST_WORD(n)]);
+    uint8_t* io = nullptr;
+    if (n && lane < fields->n_fields) {
+      const uint32_t* w = words + PER_REQUEST_WORD(field) + 2u * lane;
+      io = reinterpret_cast<uint8_t*>((uint64_t)w[1] << 32 | w[0]);
+    }
+    const uint32_t asked = (uint32_t)__ballot(io != nullptr);
+    if (pf->n == n && pf->asked == asked) {
+      if (io) pf->io[lane] = io + (uint64_t)t * n * pf->bytes[lane];
+    } else {
+      fill_piece_fields(fields, io, t, n, 0, share ? gathering_waves(n, rws) : rws, pf, share);
+    }
+  };
+  if (tid >= 832 && tid < 896) {
+    if (lane < 2u) s_rows[lane].n = s_ins[lane].n = 0xFFFFFFFFu;   // (no list yet)
+    wave_order();
+    fill_fields(s_round[0] + kRoundInsert, &s_ins[0], nullptr);
+  }
+  __syncthreads();
   uint32_t flags = 0;
-  uint32_t node = 0xFFFFFFFFu;    // this lane's sample of the latest sampling request
-  float val = 0.0f;
-  float total = 0.0f;             // (WAVE: the root as the latest change has left it)
-  // the round under way, the next one, and where the one after that starts in the queue
-  const bool single = a.ahead == 0;
-  QueueRound cur = take_round(s_req[0], n_requests, single);
-  uint32_t pos = cur.used, pos_cur = 0;
-  // what the rounds read: uniform; value and index of the update; inserted priority; rows
-  float u_i = 0.0f, u_next = 0.0f, up_v = 0.0f, in_v = 0.0f;
-  uint32_t up_i = 0;
-  RowItem ip;
-  uint4 iv;
-  uint32_t sampled = 0;                    // sampling requests so far
-  uint32_t sample_n = 0, before_smp = 3;   // the sampling request of the round before: its batch (0: none) and place
-  auto inserted_by = [&](const per_request& q) -> uint32_t {   // the row of the insertion that this lane places (>= n: none)
-    const uint32_t j = WAVE ? lane - (64u - q.n) : tid;
-    return in_team && (!WAVE || lane >= 64u - q.n) ? j : 0xFFFFFFFFu;
-  };
-  auto fill_fields = [&](const per_request* q, PieceFields* pf) {
-    fill_piece_fields(fields, q && lane < (uint32_t)kMaxFields ? static_cast<uint8_t*>(q->field[lane]) : nullptr, t, q ? q->n : 0u, 0, pf);
-  };
-  // fetches what round r (its requests in q, its insertion at ring slot `at`) reads
-  auto fetch_inputs = [&](const QueueRound& r, const per_request* q, uint32_t parity, uint32_t at) {
-    if (r.smp < 3) {
-      const per_request& w = q[r.smp];
-      if (in_team && tid < w.n) u_next = as_global(w.u)[(size_t)t * w.n + tid];
-    }
-    if (r.upd < 3) {
-      const per_request& w = q[r.upd];
-      if (in_team && tid < w.n) {
-        up_v = as_global(w.prio)[(size_t)t * w.n + tid];
-        if (w.idx) up_i = as_global(w.idx)[(size_t)t * w.n + tid];
+  float lane_max = __uint_as_float(s_max);   // (WAVE: the lanes' share of it; else s_max counts)
+
+  auto work = [&](auto does_tree, auto does_rows) {
+    constexpr bool TREE = decltype(does_tree)::value, ROWS = decltype(does_rows)::value;
+    uint32_t cursor = a.cursor, size = a.size;
+    uint32_t node = 0xFFFFFFFFu;             // this lane's sample of the latest sampling request
+    float val = 0.0f;
+    float total = tree[s_off[V]];            // (WAVE: the root as the latest change has left it)
+    uint32_t sampled = 0;                    // sampling requests so far
+    Round cur, before, next;                 // this round, the one before it and the one behind it
+    cur.read(s_round[0]);
+    before = cur;
+    uint32_t n_before = 0;                   // samples of the round before
+    // what the rounds read: uniform; value and index of the update; inserted priority; rows
+    float u_i = 0.0f, u_next = 0.0f, up_v = 0.0f, in_v = 0.0f;
+    uint32_t up_i = 0;
+    RowItem ip{};
+    ip.row = 0xFFFFFFFFu;
+    uint4 iv;
+    GatherItems<kInFlight> items;
+    uint32_t listed_n = 0xFFFFFFFFu, listed = 0;   // the list that `items` is of: its rows, the fields asked for
+    uint2 share = make_uint2(0, 0);
+    auto inserted_by = [&](uint32_t n) -> uint32_t {   // the row of the insertion that this lane places (>= n: none)
+      const uint32_t j = WAVE ? lane - (64u - n) : tid;
+      return !WAVE || lane >= 64u - n ? j : 0xFFFFFFFFu;
+    };
+    // fetches what the tree work of round r reads
+    auto fetch_inputs = [&](const Round& r) {
+      if (const uint32_t n = r.samples())
+        if (tid < n) u_next = as_global(r.pointer<kRoundSample + PER_REQUEST_WORD(u), const float>())[(size_t)t * n + tid];
+      if (const uint32_t n = r.updates()) {
+        const uint32_t* idx = r.pointer<kRoundUpdate + PER_REQUEST_WORD(idx), const uint32_t>();
+        if (tid < n) {
+          up_v = as_global(r.pointer<kRoundUpdate + PER_REQUEST_WORD(prio), const float>())[(size_t)t * n + tid];
+          if (idx) up_i = as_global(idx)[(size_t)t * n + tid];
+        }
       }
-    }
-    if (r.ins < 3) {
-      const per_request& w = q[r.ins];
-      const uint32_t j = inserted_by(w);
-      if (j < w.n && w.prio) in_v = as_global(w.prio)[(size_t)t * w.n + j];
-      if (w.protect && in_rows) {   // collision-free insertion: rows aimed at a protected slot are deferred (see k_insert_small)
-        const uint32_t* protect = w.protect + (size_t)t * w.n_protect;
-        for (uint32_t k = rl; k < w.n_protect; k += rn) {
+      if (const uint32_t n = r.inserts()) {
+        const float* prio = r.pointer<kRoundInsert + PER_REQUEST_WORD(prio), const float>();
+        const uint32_t j = inserted_by(n);
+        if (prio && j < n) in_v = as_global(prio)[(size_t)t * n + j];
+      }
+    };
+    // and its row work: the first item of the insertion (the others come when it is their turn); its deferred rows, those
+    // aimed at a protected slot (`at`: the insertion's ring slot; see k_insert_small)
+    auto fetch_rows = [&](const Round& r, uint32_t parity, uint32_t at) {
+      const uint32_t n = r.inserts();
+      if (n == 0) return;
+      if (const uint32_t* protect = r.pointer<kRoundInsert + PER_REQUEST_WORD(protect), const uint32_t>()) {
+        const uint32_t np = r.word<kRoundInsert + PER_REQUEST_WORD(n_protect)>();
+        protect += (size_t)t * np;
+        for (uint32_t k = rl; k < np; k += rn) {
           const uint32_t i = as_global(protect)[k];
           if (i < N) {
             const uint32_t p = i >= at ? i - at : i + (N - at);   // position in the ring window
-            if (p < w.n) atomicOr(&s_skip[parity][p >> 5], 1u << (p & 31u));
+            if (p < n) atomicOr(&s_skip[parity][p >> 5], 1u << (p & 31u));
           }
         }
       }
-      if (in_rows && rw < s_ins[parity].items()) {   // (the first item of the insertion; the others come when it is their turn)
+      if (rw < wave_value(s_ins[parity].items)) {
         ip = find_item(s_ins[parity], rw);
-        if (ip.on) iv = load_piece(ip.dense, ip.w);
+        if (ip.row != 0xFFFFFFFFu) iv = load_piece(ip.io + ip.out, ip.w);
       }
-    }
-  };
-  {   // round 0, and the requests of round 1
-    if (tid >= 896 && tid < 960) fill_fields(cur.ins < 3 ? &s_req[0][cur.ins] : nullptr, &s_ins[0]);
-    if (fetcher) {
-      uint32_t x, y;
-      fetch(single ? 0u : pos, x, y);   // (single: round 1 is empty)
-      park(1, x, y);
-    }
-    if (tid < 64) s_skip[tid >> 5][tid & 31u] = 0;
-    __syncthreads();
-    fetch_inputs(cur, s_req[0], 0, cursor);
+    };
+    if constexpr (TREE) fetch_inputs(cur);
+    if constexpr (ROWS) fetch_rows(cur, 0, cursor);
     u_i = u_next;
-  }
-  __syncthreads();
-  uint32_t max_bits = s_max;      // (WAVE: the team's copy; else s_max counts)
-  total = tree[s_off[V]];
+    lds_barrier();   // (deferred rows of round 0)
 
-  for (uint32_t i = 0;; ++i) {
-    const uint32_t par = i & 1u, slot_cur = i % 3u, slot_next = (i + 1u) % 3u, slot_before = (i + 2u) % 3u;
-    const per_request* q = s_req[slot_cur];
-    const bool more = pos_cur < n_requests;
-    // (single: a round with nothing in it behind every request)
-    const bool gap = single && cur.used != 0;
-    const QueueRound next = gap ? QueueRound{3, 3, 3, 0} : take_round(s_req[slot_next], n_requests - (pos < n_requests ? pos : n_requests), single);
-    // ---- rows and weights of the round before
-    const uint32_t w0 = apart ? 1024u - (sample_n + 63u) / 64u * 64u : 0u;
-    const bool weigher = sample_n && tid >= w0 && tid - w0 < sample_n;
-    float w_out = 0.0f, v_out = 0.0f;
-    uint32_t n_out = 0;
-    uint32_t* out_idx = nullptr;
-    float *out_w = nullptr, *out_prio = nullptr;
-    if (sample_n && in_rows) gather_rows(s_rows[par ^ 1u], rw, rws, nodes, N, a.fields.row_stride, 0, flags);
-    if (weigher) {
-      const per_request& w = s_req[slot_before][before_smp];
-      n_out = nodes[tid - w0];
-      v_out = apart ? values[tid - w0] : val;
-      const size_t o = (size_t)t * sample_n + (tid - w0);
-      out_idx = w.idx + o;
-      if (w.out_prio) out_prio = w.out_prio + o;
-      if (w.out_weight) {
-        out_w = w.out_weight + o;
-        const uint32_t vmin = s_vmin[par ^ 1u];
-        const uint32_t least = a.buffer_norm ? s_bmin[par ^ 1u] : vmin;
-        w_out = vmin == kNoMin ? 0.0f : importance_weight(v_out, __uint_as_float(least), w.beta);
+    uint32_t slot = 0;
+    for (uint32_t i = 0;; ++i) {
+      const uint32_t par = i & 1u, slot_next = slot == 2u ? 0u : slot + 1u;
+      const bool more = cur.more();
+      const uint32_t n_upd = cur.updates(), n_ins = cur.inserts(), n_smp = cur.samples();
+      next.read(s_round[slot_next]);
+      // ---- rows and weights of the round before
+      const uint32_t w0 = apart ? 1024u - (n_before + 63u) / 64u * 64u : 0u;
+      const bool weigher = ROWS && n_before && tid >= w0 && tid - w0 < n_before;
+      float w_out = 0.0f, v_out = 0.0f;
+      uint32_t n_out = 0;
+      if (ROWS && n_before) {
+        const uint32_t rest = share.x + (TREE ? 0u : (uint32_t)kInFlight);
+        if (rest < share.y) gather_rest<TREE ? 4 : 2>(s_rows[par ^ 1u], rest, share.y, nodes, N, a.fields.row_stride, 0, flags);
+        if constexpr (!TREE) items.load(nodes, N, a.fields.row_stride);
+        const bool weigh = before.pointer<kRoundSample + PER_REQUEST_WORD(out_weight), float>() != nullptr;
+        uint32_t least = 0;
+        if (weigh && tid >= w0) {   // (whole waves)
+          if (a.buffer_norm) least = s_bmin[par ^ 1u];
+          else if (TREE) least = s_vmin[par ^ 1u];
+          else least = smallest_value(values, n_before);
+        }
+        if (weigher) {
+          n_out = nodes[tid - w0];
+          v_out = TREE ? val : values[tid - w0];
+          if (weigh) w_out = n_out == 0xFFFFFFFFu ? 0.0f : importance_weight(v_out, __uint_as_float(least), __uint_as_float(before.word<kRoundSample + PER_REQUEST_WORD(beta)>()));
+        }
       }
-    }
-    // ---- the requests of the round after the next one are asked for
-    const uint32_t pos_after = pos + next.used;
-    uint32_t req_x = 0, req_y = 0;
-    if (fetcher) fetch(single && next.used ? 0u : pos_after < n_requests ? pos_after : n_requests, req_x, req_y);
-    // ---- the tree: update, insertion
-    const bool do_upd = cur.upd < 3, do_ins = cur.ins < 3;
-    const uint32_t n_ins = do_ins ? wave_value(q[cur.ins].n) : 0u;
-    const uint32_t cursor0 = cursor;
-    if (in_team) {
-      UpdateWork up{};
-      up.on = do_upd;
-      if (do_upd) {
-        const per_request& w = q[cur.upd];
-        up.n = wave_value(w.n);
-        up.mine = in_team && tid < up.n;
-        up.sorted = w.idx == nullptr;
-        up.i = w.idx ? up_i : node;
+      auto store_results = [&] {   // of the round before
+        if (!ROWS || !n_before) return;
+        if constexpr (!TREE) items.store(N, flags);
+        if (!weigher) return;
+        const size_t o = (size_t)t * n_before + (tid - w0);
+        float* out_prio = before.pointer<kRoundSample + PER_REQUEST_WORD(out_prio), float>();
+        float* out_w = before.pointer<kRoundSample + PER_REQUEST_WORD(out_weight), float>();
+        as_global(before.pointer<kRoundSample + PER_REQUEST_WORD(idx), uint32_t>())[o] = n_out;
+        if (out_prio) as_global(out_prio)[o] = v_out;
+        if (out_w) as_global(out_w)[o] = w_out;
+      };
+      constexpr bool stores_first = WAVE;
+      if (stores_first) store_results();
+      // ---- the round behind the next one is laid out; the fields of the next round's insertion and of this round's sample
+      if constexpr (ROWS) {
+        if (decodes) decode();
+        if (tid >= 832 && tid < 896) {
+          fill_fields(s_round[slot_next] + kRoundInsert, &s_ins[par ^ 1u], nullptr);
+          if (n_smp) fill_fields(s_round[slot] + kRoundSample, &s_rows[par], s_share[par]);   // (the round before's is the other one)
+          if (lane < 32u) s_skip[par ^ 1u][lane] = 0;
+        }
+      }
+      // ---- the tree: update, insertion
+      const uint32_t first = cursor;
+      uint8_t* place = nullptr;
+      uint32_t insert_items = 0;
+      if (ROWS && n_ins) {
+        insert_items = wave_value(s_ins[par].items);
+        if (rw < insert_items && ip.row != 0xFFFFFFFFu && !((s_skip[par][ip.row >> 5] >> (ip.row & 31u)) & 1u))
+          place = ip.stored + (uint64_t)ring_slot(first, ip.row, N) * a.fields.row_stride;
+      }
+      if constexpr (TREE) {
+        UpdateWork up{};
+        up.on = n_upd != 0;
+        up.n = n_upd;
+        up.mine = tid < n_upd;
+        up.sorted = cur.pointer<kRoundUpdate + PER_REQUEST_WORD(idx), uint32_t>() == nullptr;
+        up.counted = !single;
+        up.i = up.sorted ? node : up_i;
         up.size = size;
         up.v = up_v;
+        up.prio = cur.pointer<kRoundUpdate + PER_REQUEST_WORD(prio), const float>() + (size_t)t * n_upd;
         up.batch = sampled;
+        InsertWork in{};
+        in.on = n_ins != 0;
+        if (n_ins) {
+          const uint32_t j = inserted_by(n_ins);
+          const bool guarded = cur.pointer<kRoundInsert + PER_REQUEST_WORD(protect), const uint32_t>() != nullptr;
+          in.n = n_ins;
+          in.mine = j < n_ins && !(guarded && ((s_skip[par][(j & 1023u) >> 5] >> (j & 31u)) & 1u));
+          in.given = cur.pointer<kRoundInsert + PER_REQUEST_WORD(prio), const float>() != nullptr;
+          in.whole = !in.given && !guarded;
+          in.first = first;
+          in.slot = in.mine ? ring_slot(first, j, N) : 0u;
+          in.v = in_v;
+        }
+        if constexpr (WAVE) total = change_by_wave<LOGK, MEM>(tv, up, in, lane_max, flags, total);
+        else change_by_team<LOGK, MEM>(tv, up, in, flags);
+        if (!single && more) fetch_inputs(next);
       }
-      InsertWork in{};
-      in.on = do_ins;
-      if (do_ins) {
-        const uint32_t j = inserted_by(q[cur.ins]);
-        in.n = n_ins;
-        in.mine = j < n_ins && !((s_skip[par][(j & 1023u) >> 5] >> (j & 31u)) & 1u);
-        in.given = q[cur.ins].prio != nullptr;
-        in.slot = in.mine ? ring_slot(cursor, j, N) : 0u;
-        in.v = in_v;
+      if (n_ins) {
+        cursor = ring_slot(cursor, n_ins, N);
+        size = size + n_ins > N ? N : size + n_ins;
       }
-      change_tree<LOGK, WAVE, MEM>(tv, up, in, max_bits, flags, total);
-    }
-    if (do_ins) {
-      cursor = ring_slot(cursor, n_ins, N);
-      size = size + n_ins > N ? N : size + n_ins;
-    }
-    // ---- tables of the next round's insertion and of this round's sample; the next round's deferred rows, none so far
-    if (tid >= 896 && tid < 960) {
-      fill_fields(next.ins < 3 ? &s_req[slot_next][next.ins] : nullptr, &s_ins[par ^ 1u]);
-      // (s_rows of the round before is still in use: this round's is the other one)
-      fill_fields(cur.smp < 3 ? &q[cur.smp] : nullptr, &s_rows[par]);
-      if (lane < 32) s_skip[par ^ 1u][lane] = 0;
-    }
-    // ---- the rows of the round before have been read; the tree is whole
-    if (WAVE && MEM) wait_memory();   // (!WAVE: the team has waited for its leaves)
-    lds_barrier();
-    if (do_ins && in_rows) {
-      auto deferred = [&](uint32_t row) -> bool { return ((s_skip[par][row >> 5] >> (row & 31u)) & 1u) != 0; };
-      if (rw < s_ins[par].items() && ip.on) place_row_piece(ip, cursor0, N, a.fields.row_stride, s_skip[par], iv);
-      insert_rows(s_ins[par], rw + rws, rws, cursor0, N, a.fields.row_stride, 0, s_skip[par]);
-      if (q[cur.ins].idx) {
-        uint32_t* slots = q[cur.ins].idx + (size_t)t * n_ins;
-        for (uint32_t j = rl; j < n_ins; j += rn) as_global(slots)[j] = deferred(j) ? 0xFFFFFFFFu : ring_slot(cursor0, j, N);
-      }
-      wait_memory();
-    }
-    if (weigher) {
-      *as_global(out_idx) = n_out;
-      if (out_prio) *as_global(out_prio) = v_out;
-      if (out_w) *as_global(out_w) = w_out;
-    }
-    if (!more) break;
-    if (single) {   // (what this round has stored is there before the next one's inputs are read)
-      wait_memory();
-      lds_barrier();
-    }
-    fetch_inputs(next, s_req[slot_next], par ^ 1u, cursor);
-    if (tid == 0) s_vmin[par ^ 1u] = s_bmin[par ^ 1u] = kNoMin;   // (read by the weights of the round before, in front of the barrier)
-    if (fetcher) park(slot_before, req_x, req_y);                 // (likewise)
-    const per_request* smp = cur.smp < 3 ? &q[cur.smp] : nullptr;
-    sample_n = smp ? wave_value(smp->n) : 0u;
-    before_smp = cur.smp;
-    if (smp) {
-      ++sampled;
-      // ---- weights relative to the whole tree: its smallest positive leaf
-      if (a.buffer_norm && smp->out_weight && in_rows) {
-        uint32_t m = kNoMin;
-        for (uint32_t e = rl; e < N; e += rn) m = min_u32(m, positive_bits(tv.leaf(e)));
-        m = wave_min_u32(m);
-        if (lane == 0 && m != kNoMin) atomicMin(&s_bmin[par], m);
-      }
-      // ---- sampling
-      if (in_team && (WAVE || (tid & ~63u) < sample_n)) {
-        if constexpr (!WAVE) note_wild(u_i, sampled, &s_wild);
-        if constexpr (!WAVE) total = tree[tv.off(V)];
-        walk_tree<LOGK, MEM>(tv, tid, sample_n, u_i, total, mass_per_sample(total, sample_n), node, val);
-        if (node == 0xFFFFFFFFu) {
-          if (tid == 0) flags |= 4u;
-        } else if (smp->out_weight) {
-          const uint32_t m = wave_min_u32(tid < sample_n ? __float_as_uint(val) : kNoMin);
-          if (lane == 0) {
-            if constexpr (WAVE) s_vmin[par] = m;
-            else atomicMin(&s_vmin[par], m);
+      // ---- the rows of the round before have been asked for; the tree is whole (see k_run_steps)
+      const bool late = WAVE && TREE && n_smp && !a.buffer_norm && !single;
+      if (!late) lds_barrier();
+      if constexpr (ROWS) {
+        if (n_ins) {
+          const bool guarded = cur.pointer<kRoundInsert + PER_REQUEST_WORD(protect), const uint32_t>() != nullptr;
+          if (place) store_piece(place, ip.w, iv);
+          if (rw + rws < insert_items)
+            insert_rows(s_ins[par], insert_items, rw + rws, rws, first, N, a.fields.row_stride, 0, guarded ? s_skip[par] : nullptr);
+          if (uint32_t* slots = cur.pointer<kRoundInsert + PER_REQUEST_WORD(idx), uint32_t>()) {
+            slots += (size_t)t * n_ins;
+            for (uint32_t j = rl; j < n_ins; j += rn)
+              as_global(slots)[j] = (s_skip[par][j >> 5] >> (j & 31u)) & 1u ? 0xFFFFFFFFu : ring_slot(first, j, N);
           }
         }
-        if (tid < sample_n) {
-          nodes[tid] = node;
-          if (apart) values[tid] = val;
+        if (!stores_first) store_results();
+      }
+      if (!more) break;
+      if (single) {   // (what this round has stored is there before the next one's inputs are read)
+        wait_memory();
+        lds_barrier();
+        if constexpr (TREE) fetch_inputs(next);
+      }
+      if constexpr (ROWS) {
+        fetch_rows(next, par ^ 1u, cursor);
+        // (read by the weights of the round before, in front of the barrier)
+        if ((TREE || a.buffer_norm) && rl == 0) s_vmin[par ^ 1u] = s_bmin[par ^ 1u] = kNoMin;
+        if (n_smp) {
+          const PieceFields& pf = s_rows[par];
+          share = s_share[par][rw];
+          share.x = wave_value(share.x);
+          share.y = wave_value(share.y);
+          if constexpr (!TREE) {
+            const uint32_t asked = wave_value(pf.asked);
+            if (listed_n == n_smp && listed == asked) {
+              items.move_to(pf);
+            } else {
+              items.prepare(pf, share.x, share.y, 0);
+              listed_n = n_smp;
+              listed = asked;
+            }
+          }
+          // ---- weights relative to the whole tree: its smallest positive leaf
+          if (a.buffer_norm && cur.pointer<kRoundSample + PER_REQUEST_WORD(out_weight), float>()) {
+            uint32_t m = kNoMin;
+            for (uint32_t e = rl; e < N; e += rn) m = min_u32(m, positive_bits(tv.leaf(e)));
+            m = wave_min_u32(m);
+            if (lane == 0 && m != kNoMin) atomicMin(&s_bmin[par], m);
+          }
         }
       }
+      // ---- sampling
+      if (n_smp) ++sampled;
+      if constexpr (TREE) {
+        if (n_smp && (WAVE || (tid & ~63u) < n_smp)) {
+          if constexpr (!WAVE) {
+            note_wild(u_i, sampled, &s_wild);
+            total = tree[tv.off(V)];
+          }
+          walk_tree<LOGK, MEM, false>(tv, tid, n_smp, u_i, total, mass_per_sample(total, n_smp), node, val, [&] {
+            if (late) lds_barrier();
+          });
+          if (node == 0xFFFFFFFFu && tid == 0) flags |= 4u;
+          if (ROWS && cur.pointer<kRoundSample + PER_REQUEST_WORD(out_weight), float>()) {
+            const uint32_t m = wave_min_u32(tid < n_smp ? __float_as_uint(val) : kNoMin);
+            if (lane == 0) atomicMin(&s_vmin[par], m);
+          }
+          if (tid < n_smp) {
+            nodes[tid] = node;
+            if (!ROWS) values[tid] = val;
+          }
+        }
+        u_i = u_next;
+        if (!WAVE && !single) {
+          if (const uint32_t n = next.updates()) {
+            const bool own = next.pointer<kRoundUpdate + PER_REQUEST_WORD(idx), uint32_t>() == nullptr;
+            note_update(tid < n, own ? node : up_i, size, up_v, &s_max);
+          }
+        }
+      }
+      before = cur;
+      n_before = n_smp;
+      cur = next;
+      slot = slot_next;
+      lds_barrier();
     }
-    u_i = u_next;
-    if (in_rows) wait_memory();   // (the next sampling request may return its results in the same arrays)
-    pos_cur = pos;
-    pos = pos_after;
-    cur = next;
-    lds_barrier();
+  };
+  if constexpr (!apart) work(std::true_type{}, std::true_type{});
+  else if (in_team) work(std::true_type{}, std::false_type{});
+  else work(std::false_type{}, std::true_type{});
+  if (WAVE && in_team) {
+    const uint32_t m = wave_max_u32(__float_as_uint(lane_max));
+    if (tid == 0) s_max = m;
   }
-  if (WAVE && tid == 0) s_max = max_bits;
   __syncthreads();
   lds_tree_store<LOGK>(g, t, tab, lt, flags, &s_flags);
 }
@@ -1339,22 +1721,26 @@ static hipError_t launch_run_steps_k(const Geom& g, const Tuning& tn, StreamArgs
   const size_t bytes = (size_t)floats * 4;
   // always the largest workgroup, also for small batches: measured faster than a workgroup of the batch's
   // size (the tree copy and the row movers use all lanes)
-  const bool wave = a.B <= 64 && a.n_insert <= 64, mem = ka.a.leaves_in_memory != 0;
-#define PER_RUN(W, M, A)                                                                                \
+  const TeamForm form = team_form(a.B, a.n_insert);
+  const bool mem = ka.a.leaves_in_memory != 0;
+#define PER_RUN(F, M, A)                                                                                \
   do {                                                                                                  \
-    hipError_t e = grant_lds<&k_run_steps<LOGK, W, M, A>>(tn, bytes);                                   \
+    hipError_t e = grant_lds<&k_run_steps<LOGK, F, M, A>>(tn, bytes);                                   \
     if (e != hipSuccess) return e;                                                                      \
-    PER_LAUNCH(KID_RUN_STEPS, (k_run_steps<LOGK, W, M, A>), dim3(g.T), dim3(1024), bytes, s, ka);       \
+    PER_LAUNCH(KID_RUN_STEPS, (k_run_steps<LOGK, F, M, A>), dim3(g.T), dim3(1024), bytes, s, ka);       \
   } while (0)
-#define PER_RUN_WHERE(W, A)                                                                             \
+#define PER_RUN_WHERE(F, A)                                                                             \
   do {                                                                                                  \
-    if (mem) PER_RUN(W, true, A); else PER_RUN(W, false, A);                                            \
+    if (mem) PER_RUN(F, true, A); else PER_RUN(F, false, A);                                            \
   } while (0)
-  if (wave) {
-    if (a.ahead) PER_RUN_WHERE(true, true); else PER_RUN_WHERE(true, false);
-  } else {
-    if (a.ahead) PER_RUN_WHERE(false, true); else PER_RUN_WHERE(false, false);
-  }
+#define PER_RUN_WHEN(F)                                                                                 \
+  do {                                                                                                  \
+    if (a.ahead) PER_RUN_WHERE(F, true); else PER_RUN_WHERE(F, false);                                  \
+  } while (0)
+  if (form == TEAM_ONE_WAVE) PER_RUN_WHEN(TEAM_ONE_WAVE);
+  else if (form == TEAM_WAVES) PER_RUN_WHEN(TEAM_WAVES);
+  else PER_RUN_WHEN(TEAM_ALL);
+#undef PER_RUN_WHEN
 #undef PER_RUN_WHERE
 #undef PER_RUN
   return hipGetLastError();
@@ -1374,18 +1760,22 @@ static hipError_t launch_run_requests_k(const Geom& g, const Tuning& tn, const Q
   const uint32_t floats = plan_stream_levels<LOGK>(g, ka.a.off, &ka.a.levels, &ka.a.leaves_in_memory);
   if (!floats) return hipErrorInvalidValue;
   const size_t bytes = (size_t)floats * 4;
-  const bool wave = a.most <= 64, mem = ka.a.leaves_in_memory != 0;
-#define PER_RUN(W, M)                                                                                   \
+  const TeamForm form = team_form(a.most, 0);
+  const bool mem = ka.a.leaves_in_memory != 0;
+#define PER_RUN(F, M)                                                                                   \
   do {                                                                                                  \
-    hipError_t e = grant_lds<&k_run_requests<LOGK, W, M>>(tn, bytes);                                   \
+    hipError_t e = grant_lds<&k_run_requests<LOGK, F, M>>(tn, bytes);                                   \
     if (e != hipSuccess) return e;                                                                      \
-    PER_LAUNCH(KID_RUN_REQUESTS, (k_run_requests<LOGK, W, M>), dim3(g.T), dim3(1024), bytes, s, ka);    \
+    PER_LAUNCH(KID_RUN_REQUESTS, (k_run_requests<LOGK, F, M>), dim3(g.T), dim3(1024), bytes, s, ka);    \
   } while (0)
-  if (wave) {
-    if (mem) PER_RUN(true, true); else PER_RUN(true, false);
-  } else {
-    if (mem) PER_RUN(false, true); else PER_RUN(false, false);
-  }
+#define PER_RUN_WHERE(F)                                                                                \
+  do {                                                                                                  \
+    if (mem) PER_RUN(F, true); else PER_RUN(F, false);                                                  \
+  } while (0)
+  if (form == TEAM_ONE_WAVE) PER_RUN_WHERE(TEAM_ONE_WAVE);
+  else if (form == TEAM_WAVES) PER_RUN_WHERE(TEAM_WAVES);
+  else PER_RUN_WHERE(TEAM_ALL);
+#undef PER_RUN_WHERE
 #undef PER_RUN
   return hipGetLastError();
 }
