@@ -157,12 +157,13 @@ constexpr int kWidths = 5;         // access widths: 16, 8, 4, 2 and 1 byte
 constexpr uint32_t kLeastMovers = 6;   // waves that share a list's items, at least (see fill_piece_fields)
 struct PieceFields {               // what the waves ask of one list of fields, in LDS
   uint8_t* io[kMaxFields];         // the caller's array: the rows of this tree (in step 0)
-  uint8_t* col[kMaxFields];        // the field in row 0 of this tree
+  uint8_t* base;                   // row 0 of this tree's payload
+  uint32_t off[kMaxFields];        // where in a stored row the field lies
   uint64_t step_rows;              // rows of the caller's arrays per step
   uint32_t bytes[kMaxFields], width[kMaxFields];
   uint32_t recip[kMaxFields];      // floor(2^32 / pieces per row) + 1
   uint32_t first[kMaxFields], end[kMaxFields];   // its items, all items ordered by width
-  uint32_t items, n, asked;        // all items; rows; bit f: field f is asked for
+  uint32_t items, n;               // all items; rows
 };
 __device__ __forceinline__ uint32_t wave_value(uint32_t x) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)x); }   // (the same in all lanes)
 __device__ __forceinline__ uint64_t wave_value64(uint64_t x) {
@@ -174,13 +175,13 @@ __device__ __forceinline__ uint32_t gathering_waves(uint32_t n, uint32_t rws) {
   const uint32_t weigh = (n + 63u) / 64u;
   return rws >= weigh + kLeastMovers ? rws - weigh : rws;
 }
-// Called by one wave: n rows per tree; field f's array is `io` for tree 0 (null: not asked for), `step_rows` rows from step to
+// Called by one wave: n rows per tree; field f is `asked` for, and its array is `io` for tree 0, `step_rows` rows from step to
 // step; `waves` >= kLeastMovers waves take the items, each a run of them and of one access width, so that what a wave does
 // with its items is straight code: the runs are as short as that allows.  share (null: not asked for): items of wave i.
-__device__ __forceinline__ void fill_piece_fields(const FieldTable* ft, uint8_t* io, uint32_t t, uint32_t n, uint64_t step_rows,
+__device__ __forceinline__ void fill_piece_fields(const FieldTable* ft, bool asked, uint8_t* io, uint32_t t, uint32_t n, uint64_t step_rows,
                                                   uint32_t waves, PieceFields* pf, uint2* share) {
   const uint32_t lane = threadIdx.x & 63u, f = lane;
-  const bool on = f < (uint32_t)kMaxFields && f < ft->n_fields && io && n;
+  const bool on = f < (uint32_t)kMaxFields && f < ft->n_fields && asked && n;
   const uint32_t E = on ? ft->bytes[f] : 1u, v = on ? ft->vec[f] : 1u, epr = row_elements(E, v);
   const uint32_t w = moves_wide(E, v) ? 16u : v, kind = 4u - (uint32_t)__builtin_ctz(w);   // 0: 16 bytes .. 4: one
   const uint32_t items = on ? (n * epr + 63u) / 64u : 0u;
@@ -198,19 +199,18 @@ __device__ __forceinline__ void fill_piece_fields(const FieldTable* ft, uint8_t*
   for (int c = 0; c < kWidths; ++c) total += of_kind[c];
   if (f < (uint32_t)kMaxFields) {
     pf->io[f] = on ? io + (uint64_t)t * n * E : nullptr;
-    pf->col[f] = on ? ft->col[f] + (uint64_t)t * ft->col_stride[f] : nullptr;
+    pf->off[f] = on ? (uint32_t)(ft->col[f] - ft->col[0]) : 0u;   // (the fields of a row lie in the order of their numbers)
     pf->bytes[f] = E;
     pf->width[f] = w;
     pf->recip[f] = epr > 1 ? 0xFFFFFFFFu / epr + 1u : 0u;
     pf->first[f] = before;
     pf->end[f] = before + items;
   }
-  const uint32_t asked = (uint32_t)__ballot(on);
   if (f == 0) {
+    pf->base = ft->n_fields ? ft->col[0] + (uint64_t)t * ft->col_stride[0] : nullptr;
     pf->items = total;
     pf->step_rows = step_rows;
     pf->n = n;
-    pf->asked = asked;
   }
   if (!share) return;
   // the shortest runs with which there are waves enough: lane i tries one length.  (A run of all items
@@ -239,7 +239,7 @@ __device__ __forceinline__ void fill_piece_fields(const FieldTable* ft, uint8_t*
 struct RowItem {         // this lane's piece of an item
   uint32_t row;          // row of the batch, 0xFFFFFFFF: no piece
   uint32_t f, w;         // field and access width (the same for the wave; w = 0: no item)
-  uint8_t* stored;       // the piece in row 0 of the tree's payload
+  uint32_t at;           // offset of the piece in the stored row
   uint8_t* io;           // the caller's array (the same for the wave)
   uint32_t out;          // offset of the piece in it
   uint64_t step;         // bytes of that array per step (the same for the wave)
@@ -259,7 +259,7 @@ __device__ __forceinline__ RowItem find_item(const PieceFields& pf, uint32_t i) 
   p.row = row < wave_value(pf.n) ? row : 0xFFFFFFFFu;
   p.f = f;
   p.w = w;
-  p.stored = pf.col[f] + at;
+  p.at = wave_value(pf.off[f]) + at;
   p.io = wave_pointer(pf.io[f]);
   p.out = p.row == 0xFFFFFFFFu ? 0u : row * E + at;   // (at most 1024 rows of at most 1 MiB)
   p.step = wave_value64(pf.step_rows) * E;
@@ -312,16 +312,16 @@ template <int M>
 struct GatherItems {
   uint32_t count = 0, w = 0;   // items, their access width
   uint32_t on = 0;             // bit k: this lane has a piece of item k
-  uint32_t row[M], slot[M], out[M];
-  const uint8_t* stored[M];
+  uint32_t row[M], slot[M], at[M], out[M];
+  const uint8_t* base;         // row 0 of the tree's payload
   uint32_t field[M];
-  uint8_t* io[M];              // the caller's array in the current step
-  uint64_t step[M];
   uint4 v[M];
-  // items first .. last - 1 (at most M) of a list, in step `at`
-  __device__ __forceinline__ void prepare(const PieceFields& pf, uint32_t first, uint32_t last, uint64_t at) {
+  // items first .. last - 1 (at most M) of a list; `take` is called with every item's number here and the item
+  template <typename F>
+  __device__ __forceinline__ void prepare(const PieceFields& pf, uint32_t first, uint32_t last, F&& take) {
     count = first < last ? (last - first < (uint32_t)M ? last - first : (uint32_t)M) : 0u;
     on = 0;
+    base = wave_pointer(pf.base);
 #pragma unroll
     for (int k = 0; k < M; ++k) {   // (beyond the last: the first one again, without lanes: no load stands in a branch)
       asm volatile("" ::: "memory");   // (one item after the other: all at once they take more registers than there are)
@@ -331,31 +331,22 @@ struct GatherItems {
         on |= p.row != 0xFFFFFFFFu ? 1u << k : 0u;
         row[k] = p.row != 0xFFFFFFFFu ? p.row : 0u;
         out[k] = p.out;
-        stored[k] = p.stored;
+        at[k] = p.at;
         field[k] = p.f;
-        io[k] = p.io + at * p.step;
-        step[k] = p.step;
+        take(k, p);
       } else {
         row[k] = row[0];
         out[k] = 0;
-        stored[k] = stored[0];
+        at[k] = at[0];
         field[k] = 0;
-        io[k] = nullptr;
-        step[k] = 0;
       }
     }
-  }
-  // the same items of another list with rows, fields and waves alike
-  __device__ __forceinline__ void move_to(const PieceFields& pf) {
-#pragma unroll
-    for (int k = 0; k < M; ++k)
-      if (k < (int)count) io[k] = wave_pointer(pf.io[field[k]]);
   }
   template <int C, typename V>
   __device__ __forceinline__ void load_as(uint32_t N, uint32_t row_stride) {
 #pragma unroll
     for (int k = 0; k < C; ++k) {
-      const V x = *(GlobalPtr<const V>)as_global(stored[k] + (uint64_t)(slot[k] < N ? slot[k] : 0u) * row_stride);
+      const V x = *(GlobalPtr<const V>)as_global(base + (uint64_t)(slot[k] < N ? slot[k] : 0u) * row_stride + at[k]);
       if constexpr (sizeof(V) == 16) v[k] = make_uint4(x.x, x.y, x.z, x.w);
       else if constexpr (sizeof(V) == 8) v[k].x = x.x, v[k].y = x.y;
       else v[k].x = x;
@@ -377,63 +368,66 @@ struct GatherItems {
     if (M > 2 && count > 2) load_some<M>(nodes, N, row_stride);
     else load_some<M < 2 ? M : 2>(nodes, N, row_stride);
   }
-  template <int C, typename V>
-  __device__ __forceinline__ void store_as() {
+  template <int C, typename V, typename F>
+  __device__ __forceinline__ void store_as(F&& array_of) {
 #pragma unroll
     for (int k = 0; k < C; ++k) {
       if ((on >> k) & 1u) {
-        GlobalPtr<V> dst = (GlobalPtr<V>)as_global(io[k] + out[k]);
+        GlobalPtr<V> dst = (GlobalPtr<V>)as_global(array_of(k) + out[k]);
         if constexpr (sizeof(V) == 16) *dst = V{v[k].x, v[k].y, v[k].z, v[k].w};
         else if constexpr (sizeof(V) == 8) *dst = V{v[k].x, v[k].y};
         else *dst = (V)v[k].x;
       }
-      io[k] += step[k];
     }
   }
-  // (a batch of an empty tree gives zeros and a flag; the caller's arrays move on to the next step)
-  __device__ __forceinline__ void store(uint32_t N, uint32_t& flags) {
+  // (array_of(k): the caller's array for item k; a batch of an empty tree gives zeros and a flag)
+  template <typename F>
+  __device__ __forceinline__ void store(uint32_t N, uint32_t& flags, F&& array_of) {
     if (count == 0) return;
     if (__builtin_expect(wave_value(slot[0]) >= N, 0)) {
 #pragma unroll
       for (int k = 0; k < M; ++k) v[k] = make_uint4(0, 0, 0, 0);
       if (on) flags |= 1u;
     }
-    if (M > 2 && count > 2) store_some<M>();
-    else store_some<M < 2 ? M : 2>();
+    if (M > 2 && count > 2) store_some<M>(array_of);
+    else store_some<M < 2 ? M : 2>(array_of);
   }
-  template <int C>
-  __device__ __forceinline__ void store_some() {
-    if (w == 16u) store_as<C, Words4>();
-    if (w == 8u) store_as<C, Words2>();
-    if (w == 4u) store_as<C, uint32_t>();
-    if (w == 2u) store_as<C, uint16_t>();
-    if (w == 1u) store_as<C, uint8_t>();
+  template <int C, typename F>
+  __device__ __forceinline__ void store_some(F&& array_of) {
+    if (w == 16u) store_as<C, Words4>(array_of);
+    if (w == 8u) store_as<C, Words2>(array_of);
+    if (w == 4u) store_as<C, uint32_t>(array_of);
+    if (w == 2u) store_as<C, uint16_t>(array_of);
+    if (w == 1u) store_as<C, uint8_t>(array_of);
   }
 };
-// Items first .. last of a list at once, from beginning to end, M at a time.
-template <int M>
+// Items first .. last of a list at once, from beginning to end, M at a time.  (array_of: the caller's array of a field, null:
+// as the list has it)
+template <int M, typename F>
 __device__ __forceinline__ void gather_rest(const PieceFields& pf, uint32_t first, uint32_t last, const uint32_t* nodes, uint32_t N,
-                                            uint32_t row_stride, uint64_t step, uint32_t& flags) {
+                                            uint32_t row_stride, uint64_t step, uint32_t& flags, F&& array_of) {
 #pragma unroll 1
   for (; first < last; first += M) {
     GatherItems<M> it;
-    it.prepare(pf, first, last, step);
+    uint8_t* io[M];
+    it.prepare(pf, first, last, [&](int k, const RowItem& p) { io[k] = array_of(p) + step * p.step; });
     it.load(nodes, N, row_stride);
-    it.store(N, flags);
+    it.store(N, flags, [&](int k) { return io[k]; });
   }
 }
 // The rows of an insertion at ring slot `cursor`, items first, first + every, ..; row j is left out where bit j of skip is set.
-__device__ __forceinline__ void place_row_piece(const RowItem& p, uint32_t cursor, uint32_t N, uint32_t row_stride, const uint32_t* skip,
+__device__ __forceinline__ void place_row_piece(const RowItem& p, uint8_t* base, uint32_t cursor, uint32_t N, uint32_t row_stride, const uint32_t* skip,
                                                 const uint4& v) {
   if (p.row == 0xFFFFFFFFu || (skip && ((skip[p.row >> 5] >> (p.row & 31u)) & 1u))) return;
-  store_piece(p.stored + (uint64_t)ring_slot(cursor, p.row, N) * row_stride, p.w, v);
+  store_piece(base + (uint64_t)ring_slot(cursor, p.row, N) * row_stride + p.at, p.w, v);
 }
+template <typename F>
 __device__ __forceinline__ void insert_rows(const PieceFields& pf, uint32_t items, uint32_t first, uint32_t every, uint32_t cursor, uint32_t N,
-                                            uint32_t row_stride, uint64_t step, const uint32_t* skip) {
+                                            uint32_t row_stride, uint64_t step, const uint32_t* skip, F&& array_of) {
 #pragma unroll 1
   for (uint32_t e = first; e < items; e += every) {
     const RowItem p = find_item(pf, e);
-    if (p.row != 0xFFFFFFFFu) place_row_piece(p, cursor, N, row_stride, skip, load_piece(p.io + step * p.step + p.out, p.w));
+    if (p.row != 0xFFFFFFFFu) place_row_piece(p, wave_pointer(pf.base), cursor, N, row_stride, skip, load_piece(array_of(p) + step * p.step + p.out, p.w));
   }
 }
 // Waits until this wave's loads have arrived and its stores have been acknowledged.
@@ -980,7 +974,8 @@ k_run_steps(StreamKernelArgs ka) {
     const bool rows = tid < 192;
     const FieldTable* ft = kernarg_at<FieldTable>(offsetof(StreamKernelArgs, a) + (rows ? offsetof(StreamArgs, rows) : offsetof(StreamArgs, ins)));
     const uint32_t n = rows ? B : n_ins;
-    fill_piece_fields(ft, lane < (uint32_t)kMaxFields ? ft->io[lane] : nullptr, t, n, (uint64_t)T * n, rows ? gathering_waves(B, rws) : rws, rows ? &s_rows : &s_ins,
+    uint8_t* io = lane < (uint32_t)kMaxFields ? ft->io[lane] : nullptr;
+    fill_piece_fields(ft, io != nullptr, io, t, n, (uint64_t)T * n, rows ? gathering_waves(B, rws) : rws, rows ? &s_rows : &s_ins,
                       rows ? s_share : nullptr);
   }
   __syncthreads();
@@ -1025,6 +1020,7 @@ k_run_steps(StreamKernelArgs ka) {
   uint32_t flags = 0;
   float lane_max = __uint_as_float(s_max);   // (WAVE: the lanes' share of it; else s_max counts)
 
+  auto list_array = [](const RowItem& p) { return p.io; };
   auto work = [&](auto does_tree, auto does_rows) {
     constexpr bool TREE = decltype(does_tree)::value, ROWS = decltype(does_rows)::value;
     const bool gives = a.upd_prio != nullptr, own = a.upd_is_sampled != 0;
@@ -1039,10 +1035,14 @@ k_run_steps(StreamKernelArgs ka) {
     RowItem ip{};
     ip.row = 0xFFFFFFFFu;
     uint4 iv;
+    uint8_t* payload = nullptr;                      // row 0 of this tree
     uint32_t more_first = 0, more_last = 0, insert_items = 0;   // the items of the gather beyond the first few; items of the insertion
     GatherItems<kInFlight> items;
+    uint8_t* io[kInFlight];                          // the caller's arrays for those, in the step before s
+    uint64_t io_step[kInFlight];
     if constexpr (ROWS) {
       insert_items = wave_value(s_ins.items);
+      payload = wave_pointer(s_ins.base);
       if (rw < insert_items) {
         ip = find_item(s_ins, rw);
         if (ip.row != 0xFFFFFFFFu) iv = load_piece(ip.io + ip.out, ip.w);
@@ -1050,7 +1050,10 @@ k_run_steps(StreamKernelArgs ka) {
       more_first = wave_value(s_share[rw].x);
       more_last = wave_value(s_share[rw].y);
       if constexpr (!TREE) {
-        items.prepare(s_rows, more_first, more_last, 0);
+        items.prepare(s_rows, more_first, more_last, [&](int k, const RowItem& p) {
+          io[k] = p.io;
+          io_step[k] = p.step;
+        });
         more_first += kInFlight;
       }
     }
@@ -1060,7 +1063,7 @@ k_run_steps(StreamKernelArgs ka) {
       float w_out = 0.0f, v_out = 0.0f;
       uint32_t n_out = 0;
       if (ROWS && s) {
-        if (more_first < more_last) gather_rest<TREE ? 4 : 2>(s_rows, more_first, more_last, nodes, N, a.rows.row_stride, s - 1, flags);
+        if (more_first < more_last) gather_rest<TREE ? 4 : 2>(s_rows, more_first, more_last, nodes, N, a.rows.row_stride, s - 1, flags, list_array);
         if constexpr (!TREE) items.load(nodes, N, a.rows.row_stride);
         uint32_t least = 0;
         if (a.out_w && tid >= w0) {   // (whole waves)
@@ -1078,7 +1081,11 @@ k_run_steps(StreamKernelArgs ka) {
       }
       auto store_results = [&]() {   // of the step before
         if (!ROWS || !s) return;
-        if constexpr (!TREE) items.store(N, flags);
+        if constexpr (!TREE) {
+          items.store(N, flags, [&](int k) { return io[k]; });
+#pragma unroll
+          for (int k = 0; k < kInFlight; ++k) io[k] += io_step[k];
+        }
         if (!weigher) return;
         const size_t o = ((size_t)(s - 1) * T + t) * B + (tid - w0);
         a.out_idx[o] = n_out;
@@ -1115,7 +1122,7 @@ k_run_steps(StreamKernelArgs ka) {
       if (ROWS && do_ins && ip.w) {
         if (AHEAD) ip.io += ip.step;
         if (ip.row != 0xFFFFFFFFu) {
-          place = ip.stored + (uint64_t)ring_slot(first, ip.row, N) * a.ins.row_stride;
+          place = payload + (uint64_t)ring_slot(first, ip.row, N) * a.ins.row_stride + ip.at;
           if (AHEAD && s + 1 < a.n_steps) next_iv = load_piece(ip.io + ip.out, ip.w);
         }
       }
@@ -1166,7 +1173,7 @@ k_run_steps(StreamKernelArgs ka) {
         if (do_ins) {
           if (place) store_piece(place, ip.w, iv);
           if (AHEAD) iv = next_iv;
-          if (rw + rws < insert_items) insert_rows(s_ins, insert_items, rw + rws, rws, first, N, a.ins.row_stride, s, nullptr);
+          if (rw + rws < insert_items) insert_rows(s_ins, insert_items, rw + rws, rws, first, N, a.ins.row_stride, s, nullptr, list_array);
         }
         if (!stores_first) store_results();
       }
@@ -1234,22 +1241,24 @@ k_run_steps(StreamKernelArgs ka) {
 // the round before.  One wave decodes: it fetches the requests three rounds ahead (three at a time: a round takes no more) and
 // lays out the rounds two ahead, each as one run of words that a wave takes in with two loads, a word per lane; the fields
 // of a round are then read from its lanes.  (With every wave at the requests' fields, one LDS trip each, rounds of 64 samples
-// on 4096 leaves at K = 16 took 4.0 us where they take 2.2.)
+// on 4096 leaves at K = 16 took 4.0 us where they take 2.0.)  The lists of fields in LDS are made anew only where a request
+// asks for other fields or another number of rows than the one before it: making them for every request, and finding
+// every wave's items in them, held the round of 512 at 8.5 us where it takes 7.1.
 // Fetching ahead is only right where a request reads nothing that one just before it writes (an update whose index
 // array is the sampled one, say).  The host has checked that (QueueArgs::ahead); where it does not hold, every
 // request is a round of its own with an empty one behind it, which brings all results to memory.
-// 20 times (insert 16 rows, sample 512, update them) on 30 000 leaves at K = 16: 171 us; 353 us one request after the
+// 20 times (insert 16 rows, sample 512, update them) on 30 000 leaves at K = 16: 143 us; 353 us one request after the
 // other by the whole workgroup with a full barrier between their phases.
 struct QueueKernelArgs {            // one kernel argument (Geom first: see fill_level_table)
   Geom g;
   QueueArgs a;
 };
 constexpr uint32_t kRoundRequests = 3, kRequestWords = sizeof(per_request) / 4;
-// A round as words in LDS: its sampling request, its insertion, its update (the count of one it has not is 0), and whether the
-// queue goes on up to it.
-constexpr uint32_t kRoundSample = 0, kRoundInsert = kRequestWords, kRoundUpdate = 2 * kRequestWords, kRoundMore = 3 * kRequestWords;
-constexpr uint32_t kRoundWords = kRoundMore + 2;
-static_assert(sizeof(per_request) % 8 == 0 && kRoundWords <= 128 && kRoundUpdate >= 64 && kRoundInsert + 16 <= 64, "two words per lane");
+// A round as words in LDS: its sampling request, the head of its update, its insertion (the count of one it has not is 0), and
+// whether the queue goes on up to it.
+constexpr uint32_t kRoundSample = 0, kRoundUpdate = kRequestWords, kRoundInsert = 64, kRoundMore = kRoundInsert + kRequestWords;
+constexpr uint32_t kRoundWords = kRoundMore + 2, kRoundUpdateWords = kRoundInsert - kRoundUpdate;
+static_assert(kRoundWords <= 128 && offsetof(per_request, out_weight) / 4 <= kRoundUpdateWords, "two words per lane, and an update's words among them");
 #define PER_REQUEST_WORD(field) (offsetof(per_request, field) / 4)
 struct Round {                      // the same, in the lanes of a wave
   uint32_t lo, hi;
@@ -1268,6 +1277,18 @@ struct Round {                      // the same, in the lanes of a wave
   __device__ __forceinline__ uint32_t inserts() const { return word<kRoundInsert + PER_REQUEST_WORD(n)>(); }
   __device__ __forceinline__ uint32_t updates() const { return word<kRoundUpdate + PER_REQUEST_WORD(n)>(); }
   __device__ __forceinline__ bool more() const { return word<kRoundMore>() != 0; }
+  // the caller's array of field f, and which fields have one (bit 2f), in the sampling request or the insertion
+  template <uint32_t PART>
+  __device__ __forceinline__ uint8_t* array(uint32_t f) const {
+    static_assert(PART == kRoundSample || PART == kRoundInsert, "");
+    const int at = (int)((PART & 63u) + PER_REQUEST_WORD(field) + 2u * f), x = (int)(PART < 64 ? lo : hi);
+    return reinterpret_cast<uint8_t*>((uint64_t)(uint32_t)__builtin_amdgcn_readlane(x, at + 1) << 32 | (uint32_t)__builtin_amdgcn_readlane(x, at));
+  }
+  template <uint32_t PART>
+  __device__ __forceinline__ uint32_t asked() const {
+    const unsigned long long set = __ballot((PART < 64 ? lo : hi) != 0u);
+    return (uint32_t)((set | set >> 1) >> ((PART & 63u) + PER_REQUEST_WORD(field))) & 0x5555u;
+  }
 };
 // Lays out the round that starts with the `left` requests in the lanes of one wave (word w of them in lane w of x or, from 64
 // on, of y).  Returns how many it takes.
@@ -1289,8 +1310,8 @@ __device__ __forceinline__ uint32_t lay_out_round(uint32_t x, uint32_t y, uint32
   if (used == 0 && left && !gap) used = 1;   // (an unknown operation is passed over: the kernel ends whatever the queue holds)
   auto put = [&](uint32_t w, uint32_t value) {
     const uint32_t k = w < kRequestWords ? 0u : w < 2u * kRequestWords ? 1u : 2u;
-    const uint32_t part = k == smp ? kRoundSample : k == ins ? kRoundInsert : k == upd ? kRoundUpdate : 0xFFFFFFFFu;
-    if (w < kRoundRequests * kRequestWords && part != 0xFFFFFFFFu) words[part + (w - k * kRequestWords)] = value;
+    const uint32_t part = k == smp ? kRoundSample : k == ins ? kRoundInsert : k == upd ? kRoundUpdate : 0xFFFFFFFFu, j = w - k * kRequestWords;
+    if (w < kRoundRequests * kRequestWords && part != 0xFFFFFFFFu && (k != upd || j < kRoundUpdateWords)) words[part + j] = value;
   };
   put(lane, x);
   put(lane + 64u, y);
@@ -1390,27 +1411,20 @@ k_run_requests(QueueKernelArgs ka) {
   tv.apart = apart;
   tv.team = team;
   tv.met = 0;
-  // The table of one request's fields, by one wave (words: the request's part of its round).  Where the one before it asked
-  // for the same fields of as many rows, only the caller's arrays change.
+  // The list of one request's fields, by one wave (words: the request's part of its round), with this tree's place in the
+  // caller's arrays for an array.  Only where it asks for other fields, or for another number of rows, than the one before
+  // it: where the arrays are the waves know from the round.
   auto fill_fields = [&](const uint32_t* words, PieceFields* pf, uint2* share) {
     const uint32_t n = wave_value(words[PER_REQUEST_WORD(n)]);
-    uint8_t* io = nullptr;
-    if (n && lane < fields->n_fields) {
+    bool asked = false;
+    if (n && lane < (uint32_t)kMaxFields) {
       const uint32_t* w = words + PER_REQUEST_WORD(field) + 2u * lane;
-      io = reinterpret_cast<uint8_t*>((uint64_t)w[1] << 32 | w[0]);
+      asked = (w[0] | w[1]) != 0;
     }
-    const uint32_t asked = (uint32_t)__ballot(io != nullptr);
-    if (pf->n == n && pf->asked == asked) {
-      if (io) pf->io[lane] = io + (uint64_t)t * n * pf->bytes[lane];
-    } else {
-      fill_piece_fields(fields, io, t, n, 0, share ? gathering_waves(n, rws) : rws, pf, share);
-    }
+    fill_piece_fields(fields, asked, nullptr, t, n, 0, share ? gathering_waves(n, rws) : rws, pf, share);
   };
-  if (tid >= 832 && tid < 896) {
-    if (lane < 2u) s_rows[lane].n = s_ins[lane].n = 0xFFFFFFFFu;   // (no list yet)
-    wave_order();
-    fill_fields(s_round[0] + kRoundInsert, &s_ins[0], nullptr);
-  }
+  const bool lists = tid >= 832 && tid < 896;   // (the wave that does)
+  if (lists) fill_fields(s_round[0] + kRoundInsert, &s_ins[0], nullptr);
   __syncthreads();
   uint32_t flags = 0;
   float lane_max = __uint_as_float(s_max);   // (WAVE: the lanes' share of it; else s_max counts)
@@ -1433,7 +1447,13 @@ k_run_requests(QueueKernelArgs ka) {
     ip.row = 0xFFFFFFFFu;
     uint4 iv;
     GatherItems<kInFlight> items;
-    uint32_t listed_n = 0xFFFFFFFFu, listed = 0;   // the list that `items` is of: its rows, the fields asked for
+    auto list_of = [](uint32_t n, uint32_t asked) { return n ? n << 16 | asked : 0u; };
+    // The lists that `items` and `share`, and `ip` and `insert_items`, are of: rows << 16 | fields asked for; and, of the wave
+    // that fills them, those in LDS by parity.
+    uint32_t sample_list = 0, insert_list = 0, insert_items = 0;
+    uint8_t* payload = nullptr;   // row 0 of this tree
+    uint32_t in_lds_sample = 0, in_lds_sample_other = 0;   // (this round's and the other one's; of insertions the next round's)
+    uint32_t in_lds_insert = 0, in_lds_insert_other = list_of(cur.inserts(), cur.asked<kRoundInsert>());
     uint2 share = make_uint2(0, 0);
     auto inserted_by = [&](uint32_t n) -> uint32_t {   // the row of the insertion that this lane places (>= n: none)
       const uint32_t j = WAVE ? lane - (64u - n) : tid;
@@ -1472,9 +1492,18 @@ k_run_requests(QueueKernelArgs ka) {
           }
         }
       }
-      if (rw < wave_value(s_ins[parity].items)) {
-        ip = find_item(s_ins[parity], rw);
-        if (ip.row != 0xFFFFFFFFu) iv = load_piece(ip.io + ip.out, ip.w);
+      const uint32_t list = list_of(n, r.asked<kRoundInsert>());
+      if (list != insert_list) {
+        insert_list = list;
+        insert_items = wave_value(s_ins[parity].items);
+        payload = wave_pointer(s_ins[parity].base);
+        ip.w = 0;
+        ip.row = 0xFFFFFFFFu;
+        if (rw < insert_items) ip = find_item(s_ins[parity], rw);
+      }
+      if (ip.w) {
+        const uint8_t* from = r.array<kRoundInsert>(ip.f) + reinterpret_cast<uintptr_t>(ip.io);
+        if (ip.row != 0xFFFFFFFFu) iv = load_piece(from + ip.out, ip.w);
       }
     };
     if constexpr (TREE) fetch_inputs(cur);
@@ -1494,8 +1523,10 @@ k_run_requests(QueueKernelArgs ka) {
       float w_out = 0.0f, v_out = 0.0f;
       uint32_t n_out = 0;
       if (ROWS && n_before) {
-        const uint32_t rest = share.x + (TREE ? 0u : (uint32_t)kInFlight);
-        if (rest < share.y) gather_rest<TREE ? 4 : 2>(s_rows[par ^ 1u], rest, share.y, nodes, N, a.fields.row_stride, 0, flags);
+        const uint32_t rest = share.x + items.count;
+        if (rest < share.y)
+          gather_rest<TREE ? 4 : 2>(s_rows[par ^ 1u], rest, share.y, nodes, N, a.fields.row_stride, 0, flags,
+                                    [&](const RowItem& p) { return before.array<kRoundSample>(p.f) + reinterpret_cast<uintptr_t>(p.io); });
         if constexpr (!TREE) items.load(nodes, N, a.fields.row_stride);
         const bool weigh = before.pointer<kRoundSample + PER_REQUEST_WORD(out_weight), float>() != nullptr;
         uint32_t least = 0;
@@ -1512,7 +1543,7 @@ k_run_requests(QueueKernelArgs ka) {
       }
       auto store_results = [&] {   // of the round before
         if (!ROWS || !n_before) return;
-        if constexpr (!TREE) items.store(N, flags);
+        if constexpr (!TREE) items.store(N, flags, [&](int k) { return before.array<kRoundSample>(items.field[k]); });
         if (!weigher) return;
         const size_t o = (size_t)t * n_before + (tid - w0);
         float* out_prio = before.pointer<kRoundSample + PER_REQUEST_WORD(out_prio), float>();
@@ -1526,20 +1557,30 @@ k_run_requests(QueueKernelArgs ka) {
       // ---- the round behind the next one is laid out; the fields of the next round's insertion and of this round's sample
       if constexpr (ROWS) {
         if (decodes) decode();
-        if (tid >= 832 && tid < 896) {
-          fill_fields(s_round[slot_next] + kRoundInsert, &s_ins[par ^ 1u], nullptr);
-          if (n_smp) fill_fields(s_round[slot] + kRoundSample, &s_rows[par], s_share[par]);   // (the round before's is the other one)
+        if (lists) {
+          const uint32_t ins = list_of(next.inserts(), next.asked<kRoundInsert>()), smp = list_of(n_smp, cur.asked<kRoundSample>());
+          if (ins && in_lds_insert != ins) {
+            fill_fields(s_round[slot_next] + kRoundInsert, &s_ins[par ^ 1u], nullptr);
+            in_lds_insert = ins;
+          }
+          if (smp && in_lds_sample != smp) {   // (the round before's is the other one)
+            fill_fields(s_round[slot] + kRoundSample, &s_rows[par], s_share[par]);
+            in_lds_sample = smp;
+          }
+          const uint32_t other_sample = in_lds_sample_other, other_insert = in_lds_insert_other;
+          in_lds_sample_other = in_lds_sample;
+          in_lds_insert_other = in_lds_insert;
+          in_lds_sample = other_sample;
+          in_lds_insert = other_insert;
           if (lane < 32u) s_skip[par ^ 1u][lane] = 0;
         }
       }
       // ---- the tree: update, insertion
       const uint32_t first = cursor;
       uint8_t* place = nullptr;
-      uint32_t insert_items = 0;
       if (ROWS && n_ins) {
-        insert_items = wave_value(s_ins[par].items);
-        if (rw < insert_items && ip.row != 0xFFFFFFFFu && !((s_skip[par][ip.row >> 5] >> (ip.row & 31u)) & 1u))
-          place = ip.stored + (uint64_t)ring_slot(first, ip.row, N) * a.fields.row_stride;
+        if (ip.w && ip.row != 0xFFFFFFFFu && !((s_skip[par][ip.row >> 5] >> (ip.row & 31u)) & 1u))
+          place = payload + (uint64_t)ring_slot(first, ip.row, N) * a.fields.row_stride + ip.at;
       }
       if constexpr (TREE) {
         UpdateWork up{};
@@ -1582,7 +1623,8 @@ k_run_requests(QueueKernelArgs ka) {
           const bool guarded = cur.pointer<kRoundInsert + PER_REQUEST_WORD(protect), const uint32_t>() != nullptr;
           if (place) store_piece(place, ip.w, iv);
           if (rw + rws < insert_items)
-            insert_rows(s_ins[par], insert_items, rw + rws, rws, first, N, a.fields.row_stride, 0, guarded ? s_skip[par] : nullptr);
+            insert_rows(s_ins[par], insert_items, rw + rws, rws, first, N, a.fields.row_stride, 0, guarded ? s_skip[par] : nullptr,
+                        [&](const RowItem& p) { return cur.array<kRoundInsert>(p.f) + reinterpret_cast<uintptr_t>(p.io); });
           if (uint32_t* slots = cur.pointer<kRoundInsert + PER_REQUEST_WORD(idx), uint32_t>()) {
             slots += (size_t)t * n_ins;
             for (uint32_t j = rl; j < n_ins; j += rn)
@@ -1602,18 +1644,20 @@ k_run_requests(QueueKernelArgs ka) {
         // (read by the weights of the round before, in front of the barrier)
         if ((TREE || a.buffer_norm) && rl == 0) s_vmin[par ^ 1u] = s_bmin[par ^ 1u] = kNoMin;
         if (n_smp) {
-          const PieceFields& pf = s_rows[par];
-          share = s_share[par][rw];
-          share.x = wave_value(share.x);
-          share.y = wave_value(share.y);
-          if constexpr (!TREE) {
-            const uint32_t asked = wave_value(pf.asked);
-            if (listed_n == n_smp && listed == asked) {
-              items.move_to(pf);
-            } else {
-              items.prepare(pf, share.x, share.y, 0);
-              listed_n = n_smp;
-              listed = asked;
+          const uint32_t list = list_of(n_smp, cur.asked<kRoundSample>());
+          if (list != sample_list) {
+            sample_list = list;
+            share.x = wave_value(s_share[par][rw].x);
+            share.y = wave_value(s_share[par][rw].y);
+            if constexpr (!TREE) {
+              // (this tree's place in the caller's arrays goes into the offsets of the pieces; where it is too far for those
+              // the items are taken as those beyond the first few)
+              bool far = false;
+              items.prepare(s_rows[par], share.x, share.y, [&](int k, const RowItem& p) {
+                far = far || reinterpret_cast<uintptr_t>(p.io) > 0x7FFFFFFFull;
+                items.out[k] += (uint32_t)reinterpret_cast<uintptr_t>(p.io);
+              });
+              if (far) items.count = 0;
             }
           }
           // ---- weights relative to the whole tree: its smallest positive leaf
