@@ -1356,8 +1356,14 @@ k_run_requests(QueueKernelArgs ka) {
     s_arrived = 0;
   }
   if (tid < 64) s_skip[tid >> 5][tid & 31u] = 0;
-  // the decoding wave: requests of the round to lay out next in its lanes, where they start in the queue
-  const bool decodes = tid >= 896 && tid < 960;
+  // lanes of the team, of the rows (the weights: see k_run_steps)
+  const uint32_t team = WAVE ? 64u : apart ? (a.most + 63u) / 64u * 64u : 1024u;
+  const bool in_team = tid < team;
+  const uint32_t rn = apart ? 1024u - team : 1024u, rl = apart ? tid - team : tid;
+  const uint32_t rw = wave_value(rl >> 6), rws = rn >> 6;   // number of this wave among the row waves, and how many there are
+  // the decoding wave (one that weighs nothing, as long as there are such): requests of the round to lay out next in its
+  // lanes, where they start in the queue
+  const bool decodes = !(apart && in_team) && rw == 0;
   uint32_t pos = 0, req_x = 0, req_y = 0, rounds = 0;
   bool gap = false;
   auto fetch = [&] {
@@ -1378,11 +1384,6 @@ k_run_requests(QueueKernelArgs ka) {
     decode();
     decode();
   }
-  // lanes of the team, of the rows (the weights: see k_run_steps)
-  const uint32_t team = WAVE ? 64u : apart ? (a.most + 63u) / 64u * 64u : 1024u;
-  const bool in_team = tid < team;
-  const uint32_t rn = apart ? 1024u - team : 1024u, rl = apart ? tid - team : tid;
-  const uint32_t rw = wave_value(rl >> 6), rws = rn >> 6;   // number of this wave among the row waves, and how many there are
   __syncthreads();
   LdsTree lt;
   lt.tree = tree;
@@ -1423,7 +1424,7 @@ k_run_requests(QueueKernelArgs ka) {
     }
     fill_piece_fields(fields, asked, nullptr, t, n, 0, share ? gathering_waves(n, rws) : rws, pf, share);
   };
-  const bool lists = tid >= 832 && tid < 896;   // (the wave that does)
+  const bool lists = !(apart && in_team) && rw == 1;   // (the wave that does)
   if (lists) fill_fields(s_round[0] + kRoundInsert, &s_ins[0], nullptr);
   __syncthreads();
   uint32_t flags = 0;
