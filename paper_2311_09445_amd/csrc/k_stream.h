@@ -69,33 +69,46 @@ struct LdsTree {
   uint32_t H, V;
 };
 
-// Loads every level of tree t into LDS.  The heights are arrays of their own in memory (zero padded to 64 floats) and the
-// levels lie back to back in LDS; the copy runs over the LDS floats as one range, four 16-byte pieces per lane in flight
-// and all loads of a round before its first store.
+// Loads every level of tree t into LDS, by lanes 0 .. lanes - 1.  The heights are arrays of their own in memory (zero padded
+// to 64 floats) and the levels lie back to back in LDS.  The lowest level is most of it: it goes in 16-byte pieces, eight
+// per lane under way at once, behind the first piece that the lane has of the levels above.  Called by waves that have
+// nothing else to do: the lists of fields and the first requests are made meanwhile.
 template <int LOGK>
-__device__ __forceinline__ void lds_tree_load(const LevelTable& tab, const LdsTree& lt) {
-  constexpr int R = 4;
-  const uint32_t v_first = lt.leaves_mem ? 1u : 0u;
-  const uint32_t begin = lt.off[v_first], end = lt.off[lt.V + 1];
-  for (uint32_t base = begin; base < end; base += 4u * R * blockDim.x) {
+__device__ __forceinline__ void lds_tree_load(const LevelTable& tab, const LdsTree& lt, uint32_t lane, uint32_t lanes) {
+  constexpr int R = 8;
+  typedef GlobalPtr<const float> Source;
+  const uint32_t v0 = lt.leaves_mem ? 1u : 0u, V = lt.V;
+  auto above = [&](uint32_t e) {   // the piece at LDS float e, of a level above v0
+    uint32_t v = v0 + 1u;
+    while (v < V && e >= lt.off[v + 1]) ++v;
+    const uint32_t i = e - lt.off[v];
+    Floats4 x = {0.0f, 0.0f, 0.0f, 0.0f};
+    if (i < lt.n[v]) x = load_floats4(as_global(static_cast<const float*>(tab.lvl[level_height<LOGK>(v, lt.H)])) + i);
+    return x;
+  };
+  const uint32_t end = lt.off[V + 1], first = lt.off[v0 + 1], n0 = lt.n[v0];
+  Floats4 top;
+  const uint32_t top_at = first + 4u * lane;
+  if (top_at < end) top = above(top_at);
+  Source src = as_global(static_cast<const float*>(tab.lvl[level_height<LOGK>(v0, lt.H)]));
+  float* dst = lt.tree + lt.off[v0];
+  const uint32_t room = first - lt.off[v0];
+  for (uint32_t base = 0; base < room; base += 4u * R * lanes) {
     Floats4 x[R];
-    uint32_t v = v_first;   // (the level of this lane's piece: found anew per round, then it only grows)
 #pragma unroll
     for (int k = 0; k < R; ++k) {
-      const uint32_t e = base + 4u * ((uint32_t)k * blockDim.x + threadIdx.x);
-      if (e < end) {
-        while (v < lt.V && e >= lt.off[v + 1]) ++v;
-        const uint32_t i = e - lt.off[v];
-        x[k] = Floats4{0.0f, 0.0f, 0.0f, 0.0f};
-        if (i < lt.n[v]) x[k] = load_floats4(as_global(static_cast<const float*>(tab.lvl[level_height<LOGK>(v, lt.H)])) + i);
-      }
+      const uint32_t e = base + 4u * ((uint32_t)k * lanes + lane);
+      x[k] = Floats4{0.0f, 0.0f, 0.0f, 0.0f};
+      if (e < n0) x[k] = load_floats4(src + e);
     }
 #pragma unroll
     for (int k = 0; k < R; ++k) {
-      const uint32_t e = base + 4u * ((uint32_t)k * blockDim.x + threadIdx.x);
-      if (e < end) *reinterpret_cast<Floats4*>(lt.tree + e) = x[k];
+      const uint32_t e = base + 4u * ((uint32_t)k * lanes + lane);
+      if (e < room) *reinterpret_cast<Floats4*>(dst + e) = x[k];
     }
   }
+  if (top_at < end) *reinterpret_cast<Floats4*>(lt.tree + top_at) = top;
+  for (uint32_t e = top_at + 4u * lanes; e < end; e += 4u * lanes) *reinterpret_cast<Floats4*>(lt.tree + e) = above(e);
 }
 // The heights between level v and the next one, from a group of sixteen at level v: a lane per group.  (Nodes beyond a
 // height's last are zero, as its padding is.)
@@ -127,8 +140,26 @@ __device__ __forceinline__ void lds_tree_store(const Geom& g, uint32_t t, const 
   const uint32_t V = lt.V, H = lt.H;
   // (a root less than a whole level above its children is stored by the pass below: the level's sum of it has zeros added)
   const uint32_t end = V * LH == H ? lt.off[V + 1] : lt.off[V];
-  uint32_t v = lt.leaves_mem ? 1u : 0u;
-  for (uint32_t e = lt.off[v] + 4u * threadIdx.x; e < end; e += 4u * blockDim.x) {
+  const uint32_t v0 = lt.leaves_mem ? 1u : 0u, n0 = lt.n[v0];
+  {   // the lowest level, then those above it
+    constexpr int U = 4;
+    GlobalPtr<float> dst = as_global(tab.lvl[level_height<LOGK>(v0, H)]);
+    const float* src = lt.tree + lt.off[v0];
+    for (uint32_t base = 4u * threadIdx.x; base < n0; base += 4u * U * blockDim.x) {
+      Floats4 x[U];
+#pragma unroll
+      for (int k = 0; k < U; ++k) {
+        const uint32_t e = base + 4u * (uint32_t)k * blockDim.x;
+        x[k] = load_floats4(src + (e < n0 ? e : 0u));
+      }
+#pragma unroll
+      for (int k = 0; k < U; ++k) {
+        const uint32_t e = base + 4u * (uint32_t)k * blockDim.x;
+        if (e < n0) *(GlobalPtr<Floats4>)(dst + e) = x[k];
+      }
+    }
+  }
+  for (uint32_t e = lt.off[v0 + 1] + 4u * threadIdx.x, v = v0 + 1u; e < end; e += 4u * blockDim.x) {
     while (v < V && e >= lt.off[v + 1]) ++v;
     const uint32_t i = e - lt.off[v];
     if (i < lt.n[v]) *(GlobalPtr<Floats4>)(as_global(tab.lvl[level_height<LOGK>(v, H)]) + i) = load_floats4(lt.tree + e);
@@ -930,7 +961,7 @@ static TeamForm team_form(uint32_t samples, uint32_t inserted) {
 // (its loads are issued behind the barrier that ends the sampling), and overwrite what the gather of the step before has
 // read (whose loads are issued in front of the barrier before the insertion's stores); the accesses of a workgroup's waves
 // keep that order (see TreeView::sync).
-// 100 steps on 10 000 leaves at K = 16 (32 samples, 4 new rows of 41 bytes): 172 us; 1001 us as one phase after the
+// 100 steps on 10 000 leaves at K = 16 (32 samples, 4 new rows of 41 bytes): 167 us; 1001 us as one phase after the
 // other by the whole workgroup with a full barrier between them.
 // AHEAD: no step reads what a step returns.
 template <int LOGK, TeamForm FORM, bool MEM, bool AHEAD>
@@ -969,15 +1000,6 @@ k_run_steps(StreamKernelArgs ka) {
   const uint32_t rw = wave_value(rl >> 6), rws = rn >> 6;   // number of this wave among the row waves, and how many there are
   const uint32_t w0 = apart ? 1024u - (B + 63u) / 64u * 64u : 0u;
   const bool weigher = tid >= w0 && tid - w0 < B;
-  // (the field tables from the argument segment by vector loads, a lane per field)
-  if (tid >= 128 && tid < 256) {
-    const bool rows = tid < 192;
-    const FieldTable* ft = kernarg_at<FieldTable>(offsetof(StreamKernelArgs, a) + (rows ? offsetof(StreamArgs, rows) : offsetof(StreamArgs, ins)));
-    const uint32_t n = rows ? B : n_ins;
-    uint8_t* io = lane < (uint32_t)kMaxFields ? ft->io[lane] : nullptr;
-    fill_piece_fields(ft, io != nullptr, io, t, n, (uint64_t)T * n, rows ? gathering_waves(B, rws) : rws, rows ? &s_rows : &s_ins,
-                      rows ? s_share : nullptr);
-  }
   __syncthreads();
   // inputs of the team: the uniform of the step to sample, value (and index) of the update to apply, inserted priority
   float u_i = 0.0f, u_next = 0.0f, up_v = 0.0f, in_v = 0.0f;
@@ -988,7 +1010,6 @@ k_run_steps(StreamKernelArgs ka) {
   if (in_team && tid < B) u_i = a.u[(size_t)t * B + tid];
   if (inserts && a.ins_prio) in_v = a.ins_prio[(size_t)t * n_ins + j_ins];
   if constexpr (!AHEAD) beta_i = a.beta[0];
-  __syncthreads();
   LdsTree lt;
   lt.tree = tree;
   lt.leaves_mem = MEM ? tab.lvl[0] : nullptr;
@@ -997,7 +1018,17 @@ k_run_steps(StreamKernelArgs ka) {
   lt.max_bits = &s_max;
   lt.H = H;
   lt.V = V;
-  lds_tree_load<LOGK>(tab, lt);
+  // (the lists from the argument segment by vector loads, a lane per field, two waves beside the others' copy of the tree)
+  if (tid >= 896) {
+    const bool rows = tid < 960;
+    const FieldTable* ft = kernarg_at<FieldTable>(offsetof(StreamKernelArgs, a) + (rows ? offsetof(StreamArgs, rows) : offsetof(StreamArgs, ins)));
+    const uint32_t n = rows ? B : n_ins;
+    uint8_t* io = lane < (uint32_t)kMaxFields ? ft->io[lane] : nullptr;
+    fill_piece_fields(ft, io != nullptr, io, t, n, (uint64_t)T * n, rows ? gathering_waves(B, rws) : rws, rows ? &s_rows : &s_ins,
+                      rows ? s_share : nullptr);
+  } else {
+    lds_tree_load<LOGK>(tab, lt, tid, 896u);
+  }
   uint32_t* nodes = reinterpret_cast<uint32_t*>(tree + s_off[V + 1]);   // [B] sampled leaves of the step
   float* values = reinterpret_cast<float*>(nodes + 512);                // [B] and their values (apart only: B <= 512)
   TreeView<MEM> tv;
@@ -1243,11 +1274,11 @@ k_run_steps(StreamKernelArgs ka) {
 // of a round are then read from its lanes.  (With every wave at the requests' fields, one LDS trip each, rounds of 64 samples
 // on 4096 leaves at K = 16 took 4.0 us where they take 2.0.)  The lists of fields in LDS are made anew only where a request
 // asks for other fields or another number of rows than the one before it: making them for every request, and finding
-// every wave's items in them, held the round of 512 at 8.5 us where it takes 7.1.
+// every wave's items in them, held the round of 512 at 8.5 us where it takes 6.7.
 // Fetching ahead is only right where a request reads nothing that one just before it writes (an update whose index
 // array is the sampled one, say).  The host has checked that (QueueArgs::ahead); where it does not hold, every
 // request is a round of its own with an empty one behind it, which brings all results to memory.
-// 20 times (insert 16 rows, sample 512, update them) on 30 000 leaves at K = 16: 143 us; 353 us one request after the
+// 20 times (insert 16 rows, sample 512, update them) on 30 000 leaves at K = 16: 134 us; 353 us one request after the
 // other by the whole workgroup with a full barrier between their phases.
 struct QueueKernelArgs {            // one kernel argument (Geom first: see fill_level_table)
   Geom g;
@@ -1379,11 +1410,7 @@ k_run_requests(QueueKernelArgs ka) {
     ++rounds;
     fetch();
   };
-  if (decodes) {
-    fetch();
-    decode();
-    decode();
-  }
+  if (decodes) fetch();
   __syncthreads();
   LdsTree lt;
   lt.tree = tree;
@@ -1393,7 +1420,14 @@ k_run_requests(QueueKernelArgs ka) {
   lt.max_bits = &s_max;
   lt.H = H;
   lt.V = V;
-  lds_tree_load<LOGK>(tab, lt);
+  // (the first two rounds are laid out beside the others' copy of the tree)
+  const uint32_t at_work = apart ? team : 0u;   // first lane of the decoding wave
+  if (decodes) {
+    decode();
+    decode();
+  } else {
+    lds_tree_load<LOGK>(tab, lt, tid < at_work ? tid : tid - 64u, 960u);
+  }
   uint32_t* nodes = reinterpret_cast<uint32_t*>(tree + s_off[V + 1]);   // sampled leaves of the round
   float* values = reinterpret_cast<float*>(nodes + 512);                // and their values (apart only: at most 512)
   TreeView<MEM> tv;
@@ -1425,6 +1459,7 @@ k_run_requests(QueueKernelArgs ka) {
     fill_piece_fields(fields, asked, nullptr, t, n, 0, share ? gathering_waves(n, rws) : rws, pf, share);
   };
   const bool lists = !(apart && in_team) && rw == 1;   // (the wave that does)
+  __syncthreads();
   if (lists) fill_fields(s_round[0] + kRoundInsert, &s_ins[0], nullptr);
   __syncthreads();
   uint32_t flags = 0;
