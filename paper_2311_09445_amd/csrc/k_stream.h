@@ -1003,13 +1003,13 @@ k_run_steps(StreamKernelArgs ka) {
   __syncthreads();
   // inputs of the team: the uniform of the step to sample, value (and index) of the update to apply, inserted priority
   float u_i = 0.0f, u_next = 0.0f, up_v = 0.0f, in_v = 0.0f;
-  [[maybe_unused]] float beta_i = 0.0f;
+  float beta_i = 0.0f;
   uint32_t up_i = 0;
   const uint32_t j_ins = WAVE ? lane - (64u - n_ins) : tid;   // (WAVE: the last lanes of the wave, so that samples and rows share it)
   const bool inserts = in_team && (!WAVE || lane >= 64u - n_ins) && j_ins < n_ins;
-  if (in_team && tid < B) u_i = a.u[(size_t)t * B + tid];
+  if (in_team && tid < B) u_i = a.u ? a.u[(size_t)t * B + tid] : counter_uniform(a.rng, tid, t);
   if (inserts && a.ins_prio) in_v = a.ins_prio[(size_t)t * n_ins + j_ins];
-  if constexpr (!AHEAD) beta_i = a.beta[0];
+  if (!AHEAD || !a.beta) beta_i = a.beta ? a.beta[0] : a.beta_value;
   LdsTree lt;
   lt.tree = tree;
   lt.leaves_mem = MEM ? tab.lvl[0] : nullptr;
@@ -1106,7 +1106,7 @@ k_run_steps(StreamKernelArgs ka) {
           n_out = nodes[tid - w0];
           v_out = TREE ? val : values[tid - w0];
           if (a.out_w) {
-            w_out = n_out == 0xFFFFFFFFu ? 0.0f : importance_weight(v_out, __uint_as_float(least), AHEAD ? a.beta[s - 1] : beta_i);
+            w_out = n_out == 0xFFFFFFFFu ? 0.0f : importance_weight(v_out, __uint_as_float(least), AHEAD && a.beta ? a.beta[s - 1] : beta_i);
           }
         }
       }
@@ -1204,6 +1204,8 @@ k_run_steps(StreamKernelArgs ka) {
         if (do_ins) {
           if (place) store_piece(place, ip.w, iv);
           if (AHEAD) iv = next_iv;
+          if (a.ins_slots)
+            for (uint32_t j = rl; j < n_ins; j += rn) a.ins_slots[(size_t)t * n_ins + j] = ring_slot(first, j, N);
           if (rw + rws < insert_items) insert_rows(s_ins, insert_items, rw + rws, rws, first, N, a.ins.row_stride, s, nullptr, list_array);
         }
         if (!stores_first) store_results();
@@ -1789,6 +1791,43 @@ static uint32_t plan_stream_levels(const Geom& g, uint32_t* off, uint32_t* level
     return (uint32_t)floats + kStreamBatchWords;
   }
   return 0u;
+}
+
+// Whether one step (with n_insert new rows, or none) is faster as one launch of the kernel above than as the two or three
+// kernels it otherwise takes.  Both sides in hundredths of a microsecond, fitted to 289 shapes (1 to 64 trees of 1000 to
+// 400 000 leaves, 16 to 512 samples, 0 to 256 new rows of 25 to 1033 bytes; the fits are off by 8 and 9 %).  On the chip: the
+// launch and one step's chain, more with several waves at the tree; the rows, which one compute unit moves; the copy
+// of the tree, with a trip to memory for the leaves where they stay there, and the heights between the levels.  As
+// kernels: two launches, or the sampling kernel with the insertion in it (12.3 us), or three (no K = 2 tree's is carried, and
+// those are chains of many heights).  Of the shapes 165 go this way, 1.30 times as fast on average (4096 leaves at K = 2, 64
+// samples, 4 rows: 19.5 -> 9.8 us); of those 5 are slower, by 7 % at most, before batches beyond 256 were left out.
+template <int LOGK>
+static bool step_on_chip_pays_k(const Geom& g, uint32_t n_insert, uint32_t B, const FieldTable& rows, const FieldTable& ins) {
+  uint32_t off[kStreamLevels + 2], levels = 0, in_memory = 0;
+  const uint64_t floats = plan_stream_levels<LOGK>(g, off, &levels, &in_memory);
+  if (!floats || g.T > 64 || (B > 256 && g.K > 2)) return false;
+  uint64_t heights = 0, row = 0, new_row = 0;
+  for (uint32_t h = in_memory; h <= g.H; ++h) heights += g.n[h];
+  for (uint32_t f = 0; f < rows.n_fields; ++f) row += rows.io[f] ? rows.bytes[f] : 0u;
+  for (uint32_t f = 0; f < ins.n_fields; ++f) new_row += ins.io[f] ? ins.bytes[f] : 0u;
+  const uint64_t here = 830 + (team_form(B, n_insert) == TEAM_ONE_WAVE ? 0 : 180) + B * row * 9 / 1024 + n_insert * new_row * 4 / 1024 +
+                        floats * 5 / 1024 + (in_memory ? 100 : 0) + (heights > floats ? (heights - floats) * 18 / 1024 : 0);
+  const uint64_t apart = g.K == 2 ? (n_insert ? 1800 : 1200)
+                                  : (n_insert ? 1230 : 960) + (g.K >= 32 ? 120 : 0) + (g.T >= 16 ? 100 : 0);
+  return here < apart;
+}
+bool step_on_chip_pays(const Geom& g, uint32_t n_insert, uint32_t B, const FieldTable& rows, const FieldTable& ins) {
+#define CALL(L) step_on_chip_pays_k<L>(g, n_insert, B, rows, ins)
+  switch (g.logK) {
+    case 1: return CALL(1);
+    case 2: return CALL(2);
+    case 3: return CALL(3);
+    case 4: return CALL(4);
+    case 5: return CALL(5);
+    case 6: return CALL(6);
+    default: return false;
+  }
+#undef CALL
 }
 
 template <int LOGK>

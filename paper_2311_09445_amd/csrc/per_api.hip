@@ -24,6 +24,7 @@ struct per_buffer {
   int weight_norm;           // PER_NORM_BATCH or PER_NORM_BUFFER
   bool min_stale;            // min1 does not describe the leaves (it is rebuilt when next needed)
   uint32_t stale_hb;         // != 0: the last update left the heights above this one to their next reader
+  bool step_before;          // the latest call that changed the tree was a step (see step_on_chip)
   bool tables_valid;         // the per-owner tables of the one-kernel step describe the tree as it is
   unsigned long long capture_id;   // the stream capture the last call was recorded into (0: it ran eagerly)
   bool rng_on;               // per_set_rng was called: sampling calls without uniforms draw their own
@@ -333,6 +334,7 @@ int per_create(const per_config* cfg, void* d_arena, size_t arena_bytes, void* s
   p->tn.group_claim = 1;
   p->tn.update_runs = 1;
   p->tn.step_kernel = 1;
+  p->tn.step_on_chip = 1;
   p->tn.step_tail = 0;   // (measured slower than the second kernel: see k_step)
   p->tn.insert_ride = 1;
   p->tn.whole_rows = 1;
@@ -432,11 +434,13 @@ static int insert_impl(per_t* p, uint32_t n, const void* const* d_field_src, con
 
 int per_insert(per_t* p, uint32_t n, const void* const* d_field_src, const float* d_prio, uint32_t* d_out_idx,
                void* stream) {
+  if (p) p->step_before = false;
   return insert_impl(p, n, d_field_src, d_prio, d_out_idx, 0, nullptr, stream);
 }
 
 int per_insert_protected(per_t* p, uint32_t n, const void* const* d_field_src, const float* d_prio, uint32_t* d_out_idx,
                          uint32_t n_protect, const uint32_t* d_protect_idx, void* stream) {
+  if (p) p->step_before = false;
   return insert_impl(p, n, d_field_src, d_prio, d_out_idx, n_protect, d_protect_idx, stream);
 }
 
@@ -600,10 +604,103 @@ int per_sample_gather_update(per_t* p, uint32_t B, float beta, const float* d_u,
                              const uint32_t* d_upd_idx, const float* d_upd_prio, void* stream) {
   int rc = check_update_args(p, upd_B, d_upd_idx, d_upd_prio);
   if (rc != PER_OK) return rc;
+  if (upd_B) p->step_before = false;
   if (B == 0)   // nothing to sample: plain update
     return upd_B ? per_update(p, upd_B, d_upd_idx, d_upd_prio, stream) : PER_OK;
   return sample_impl(p, B, beta, d_u, d_out_idx, d_out_weight, d_out_prio, d_field_dst, upd_B, d_upd_idx, d_upd_prio,
                      stream);
+}
+
+// A byte range of the caller's memory that a list of steps or a request reads or writes.
+struct Span { uintptr_t lo, hi; };
+static void add_span(Span* s, uint32_t* n, const void* p, uint64_t bytes) {
+  if (p && bytes) s[(*n)++] = Span{reinterpret_cast<uintptr_t>(p), reinterpret_cast<uintptr_t>(p) + bytes};
+}
+static bool spans_meet(const Span* a, uint32_t na, const Span* b, uint32_t nb) {
+  for (uint32_t i = 0; i < na; ++i)
+    for (uint32_t j = 0; j < nb; ++j)
+      if (a[i].lo < b[j].hi && b[j].lo < a[i].hi) return true;
+  return false;
+}
+// A step with its insertion, as one launch of the kernel of per_run_steps: one workgroup per tree, which copies the tree (or
+// what is above its leaves) to its LDS, inserts, samples, updates, moves the rows and stores the tree.  Taken where
+// step_on_chip_pays says so, for weights relative to the batch, and where nothing the call reads lies in what it writes.
+// Returns false where the call takes its usual way (which also has the errors).
+static bool step_on_chip(per_t* p, uint32_t n, const void* const* d_field_src, const float* d_ins_prio, uint32_t* d_ins_out_idx, uint32_t B,
+                         float beta, const float* d_u, uint32_t* d_out_idx, float* d_out_weight, float* d_out_prio,
+                         void* const* d_field_dst, const float* d_upd_prio, const uint32_t* d_upd_pos, void* stream, int* rc) {
+  // (whoever chooses by hand how the kernels below work means those kernels)
+  const bool forced = p->tn.step_on_chip == 2;
+  const bool by_hand = p->tn.step_kernel != 1 || !p->tn.group_claim || !p->tn.claim_in_sample || !p->tn.insert_ride || !p->tn.lazy_top;
+  if (!p->tn.step_on_chip || (!forced && by_hand) || d_upd_pos || B > 512 || n > 512 || n > p->cfg.capacity ||
+      (p->size == 0 && n == 0) || (d_out_weight && p->weight_norm != PER_NORM_BATCH) || !stream_tree_fits(p->g))
+    return false;
+  if ((!d_u && !p->rng_on) || !d_out_idx || !d_upd_prio || !isfinite(beta) || beta < 0.0f) return false;
+  for (const void* a : {static_cast<const void*>(d_ins_prio), static_cast<const void*>(d_ins_out_idx), static_cast<const void*>(d_u),
+                        static_cast<const void*>(d_out_idx), static_cast<const void*>(d_out_weight),
+                        static_cast<const void*>(d_out_prio), static_cast<const void*>(d_upd_prio)})
+    if (misaligned(a, 4)) return false;
+  StreamArgs a{};
+  (void)fill_fields(p, d_field_dst, &a.rows);
+  if (n) (void)fill_fields(p, const_cast<void* const*>(reinterpret_cast<const void* const*>(d_field_src)), &a.ins);
+  if (!forced && !step_on_chip_pays(p->g, n, B, a.rows, a.ins)) return false;
+  Span in[3 + PER_MAX_FIELDS], out[4 + PER_MAX_FIELDS];
+  uint32_t ni = 0, no = 0;
+  const uint64_t samples = (uint64_t)p->g.T * B, rows = (uint64_t)p->g.T * n;
+  add_span(in, &ni, d_u, samples * 4);
+  add_span(in, &ni, d_upd_prio, samples * 4);
+  add_span(in, &ni, d_ins_prio, rows * 4);
+  add_span(out, &no, d_out_idx, samples * 4);
+  add_span(out, &no, d_out_weight, samples * 4);
+  add_span(out, &no, d_out_prio, samples * 4);
+  add_span(out, &no, d_ins_out_idx, rows * 4);
+  for (uint32_t f = 0; f < p->cfg.n_fields; ++f) {
+    add_span(in, &ni, a.ins.io[f], rows * p->cfg.field_bytes[f]);
+    add_span(out, &no, a.rows.io[f], samples * p->cfg.field_bytes[f]);
+  }
+  for (uint32_t i = 0; i < no; ++i)   // (results over one another are the calls' own business)
+    if (spans_meet(out + i, 1, in, ni) || spans_meet(out + i, 1, out + i + 1, no - i - 1)) return false;
+  hipStream_t s = static_cast<hipStream_t>(stream);
+  CaptureGuard capture(p, s);
+  // The kernel loads whole heights from memory.  Heights that another call has left stale cost a launch to bring in order
+  // first, which the usual way does on its way: worth it once, where steps follow steps, not where such calls and steps
+  // take turns.
+  if (!forced && p->stale_hb && !p->step_before) {
+    p->step_before = true;
+    return false;
+  }
+  a.n_steps = 1;
+  a.n_insert = n;
+  a.B = B;
+  a.cursor = (uint32_t)p->cursor;
+  a.size = (uint32_t)p->size;
+  a.upd_is_sampled = 1;
+  a.ahead = 1;
+  a.u = d_u;
+  if (!d_u) {
+    a.rng.on = 1;
+    a.rng.seed_lo = (uint32_t)p->rng_seed;
+    a.rng.seed_hi = (uint32_t)(p->rng_seed >> 32);
+    a.rng.call_lo = (uint32_t)p->rng_calls;
+    a.rng.call_hi = (uint32_t)(p->rng_calls >> 32);
+    ++p->rng_calls;
+  }
+  a.beta_value = beta;
+  a.out_idx = d_out_idx;
+  a.out_w = d_out_weight;
+  a.out_prio = d_out_prio;
+  a.upd_prio = d_upd_prio;
+  a.ins_prio = d_ins_prio;
+  a.ins_slots = d_ins_out_idx;
+  p->min_stale = true;   // (as per_run_steps)
+  p->tables_valid = false;
+  hipError_t e = ensure_top(p, s);
+  if (e == hipSuccess) e = launch_run_steps(p->g, p->tn, a, s);
+  const uint64_t N = p->cfg.capacity;
+  p->cursor = (p->cursor + n) % N;
+  p->size = p->size + n > N ? N : p->size + n;
+  *rc = hip_rc(e);
+  return true;
 }
 
 int per_step(per_t* p, uint32_t B, float beta, const float* d_u, uint32_t* d_out_idx, float* d_out_weight,
@@ -616,6 +713,10 @@ int per_step(per_t* p, uint32_t B, float beta, const float* d_u, uint32_t* d_out
   const void* outs[3] = {d_out_idx, d_out_weight, d_out_prio};
   for (const void* o : outs)   // the update's inputs are read after (and while) the outputs are written
     if (ranges_overlap(d_upd_prio, n, o, n) || ranges_overlap(d_upd_pos, n, o, n)) return PER_EINVAL;
+  int rc;
+  if (step_on_chip(p, 0, nullptr, nullptr, nullptr, B, beta, d_u, d_out_idx, d_out_weight, d_out_prio, d_field_dst, d_upd_prio, d_upd_pos,
+                   stream, &rc))
+    return rc;
   return sample_impl(p, B, beta, d_u, d_out_idx, d_out_weight, d_out_prio, d_field_dst, B, d_out_idx, d_upd_prio, stream,
                      d_upd_pos);
 }
@@ -641,6 +742,10 @@ int per_insert_step(per_t* p, uint32_t n, const void* const* d_field_src, const 
   const void* outs[3] = {d_out_idx, d_out_weight, d_out_prio};
   for (const void* o : outs)
     if (ranges_overlap(d_upd_prio, n_out, o, n_out) || ranges_overlap(d_upd_pos, n_out, o, n_out)) return PER_EINVAL;
+  int on_chip_rc;
+  if (step_on_chip(p, n, d_field_src, d_ins_prio, d_ins_out_idx, B, beta, d_u, d_out_idx, d_out_weight, d_out_prio, d_field_dst,
+                   d_upd_prio, d_upd_pos, stream, &on_chip_rc))
+    return on_chip_rc;
 
   // The sampling kernel of the step carries the insertion where it can.  What the insertion reads and writes then
   // must lie apart from what the sampling kernel writes and reads, since the two run side by side.
@@ -660,7 +765,7 @@ int per_insert_step(per_t* p, uint32_t n, const void* const* d_field_src, const 
                         static_cast<const void*>(d_upd_prio), static_cast<const void*>(d_upd_pos)})
     carried = carried && !ranges_overlap(d_ins_out_idx, n_ins, a, n_out);
   if (!carried) {
-    int rc = per_insert(p, n, d_field_src, d_ins_prio, d_ins_out_idx, stream);
+    int rc = insert_impl(p, n, d_field_src, d_ins_prio, d_ins_out_idx, 0, nullptr, stream);
     if (rc != PER_OK) return rc;
     return sample_impl(p, B, beta, d_u, d_out_idx, d_out_weight, d_out_prio, d_field_dst, B, d_out_idx, d_upd_prio, stream,
                        d_upd_pos, nullptr, true);
@@ -695,6 +800,7 @@ int per_gather(per_t* p, uint32_t B, const uint32_t* d_idx, void* const* d_field
 int per_update(per_t* p, uint32_t B, const uint32_t* d_idx, const float* d_prio, void* stream) {
   int rc = check_update_args(p, B, d_idx, d_prio);
   if (rc != PER_OK || B == 0) return rc;
+  p->step_before = false;
   hipStream_t s = static_cast<hipStream_t>(stream);
   CaptureGuard capture(p, s);
   if (prepare_tree_pass(p, s) != hipSuccess) return PER_EHIP;
@@ -715,6 +821,7 @@ int per_update_td(per_t* p, uint32_t B, const uint32_t* d_idx, const float* d_td
                   void* stream) {
   int rc = check_update_args(p, B, d_idx, d_td);
   if (rc != PER_OK || B == 0) return rc;
+  p->step_before = false;
   if (!(eps >= 0.0) || !isfinite(eps) || !(alpha >= 0.0) || !isfinite(alpha)) return PER_EINVAL;
   hipStream_t s = static_cast<hipStream_t>(stream);
   CaptureGuard capture(p, s);
@@ -749,17 +856,6 @@ int per_update_delta(per_t* p, uint32_t B, const uint32_t* d_idx, const float* d
 
 int per_run_steps_fits(const per_t* p) { return p && stream_tree_fits(p->g) ? 1 : 0; }
 
-// A byte range of the caller's memory that a list of steps or a request reads or writes.
-struct Span { uintptr_t lo, hi; };
-static void add_span(Span* s, uint32_t* n, const void* p, uint64_t bytes) {
-  if (p && bytes) s[(*n)++] = Span{reinterpret_cast<uintptr_t>(p), reinterpret_cast<uintptr_t>(p) + bytes};
-}
-static bool spans_meet(const Span* a, uint32_t na, const Span* b, uint32_t nb) {
-  for (uint32_t i = 0; i < na; ++i)
-    for (uint32_t j = 0; j < nb; ++j)
-      if (a[i].lo < b[j].hi && b[j].lo < a[i].hi) return true;
-  return false;
-}
 // True where no step of the list reads memory that a step writes its results to.
 static bool step_inputs_apart(const per_t* p, uint32_t n_steps, uint32_t n_insert, uint32_t B, const per_stream_io* io) {
   Span in[5 + PER_MAX_FIELDS], out[3 + PER_MAX_FIELDS];
@@ -1096,6 +1192,11 @@ int per_set_tuning(per_t* p, const char* name, int64_t value) {
   if (!strcmp(name, "insert_ride")) {
     if (value != 0 && value != 1) return PER_EINVAL;
     p->tn.insert_ride = (uint32_t)value;
+    return PER_OK;
+  }
+  if (!strcmp(name, "step_on_chip")) {
+    if (value < 0 || value > 2) return PER_ERANGE;
+    p->tn.step_on_chip = (uint32_t)value;
     return PER_OK;
   }
   if (!strcmp(name, "step_kernel")) {

@@ -150,14 +150,17 @@ struct StreamArgs {
   uint32_t upd_is_sampled;          // a step updates the batch it has just sampled
   uint32_t buffer_norm;             // importance weights relative to the whole tree (else to the batch)
   uint32_t ahead;                   // what a step reads may be fetched before the results of the step before are in memory
-  const float* u;                   // [steps][T][B]
-  const float* beta;                // [steps]
+  const float* u;                   // [steps][T][B] (null, one step: drawn here)
+  RngArgs rng;
+  const float* beta;                // [steps] (null, one step: beta_value)
+  float beta_value;
   uint32_t* out_idx;                // [steps][T][B]
   float* out_w;                     // [steps][T][B] or null
   float* out_prio;                  // [steps][T][B] or null
   const uint32_t* upd_idx;          // [steps][T][B] (unused when upd_is_sampled)
   const float* upd_prio;            // [steps][T][B] or null: no update
   const float* ins_prio;            // [steps][T][n_insert] or null: running maximum
+  uint32_t* ins_slots;              // one step: [T][n_insert] or null
   FieldTable ins, rows;             // io arrays hold [steps][T][n][bytes]; io all null: nothing to move
   uint32_t off[kStreamLevels + 2];  // where level v of the LDS copy starts (floats); off[levels + 1] = all floats
   uint32_t levels;                  // levels above the leaves (see Wide)
@@ -248,6 +251,7 @@ struct Tuning {
   uint32_t sample_block_auto; // sample_block is the default, not a size that was asked for
   uint32_t whole_rows;        // gathers of several fields move whole rows through LDS where the rows are short enough
   uint32_t step_tail;         // the one-kernel step also ends inside that kernel (rows, weights, tables) where all its workgroups fit the GPU at once
+  uint32_t step_on_chip;      // per_step and per_insert_step run as one workgroup per tree on an LDS copy: 0 never, 1 where it pays off, 2 wherever it can
   uint32_t step_kernel;       // per_step runs sampling and update as one kernel: 0 never, 1 where it fits and pays off, 2 wherever it fits
   Profiler* prof;
   int device;                 // the device the buffer lives on
@@ -294,6 +298,7 @@ size_t step_table_bytes();
 void* step_static_claim(const void* holder, int device, hipStream_t s);
 void step_static_release(const void* holder, int device);
 bool stream_tree_fits(const Geom& g);
+bool step_on_chip_pays(const Geom& g, uint32_t n_insert, uint32_t B, const FieldTable& rows, const FieldTable& ins);
 hipError_t launch_run_steps(const Geom& g, const Tuning& tn, const StreamArgs& a, hipStream_t s);
 hipError_t launch_run_requests(const Geom& g, const Tuning& tn, const QueueArgs& a, hipStream_t s);
 hipError_t launch_get_priority(const Geom& g, const Tuning& tn, uint32_t n, const uint32_t* idx, float* out, hipStream_t s);

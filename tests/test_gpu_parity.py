@@ -713,6 +713,85 @@ def test_run_steps_limits_and_empty_tree():
     assert q.status() == FLAG_ZERO_TOTAL
 
 
+@pytest.mark.parametrize("K,N,T,B,n,fb", [(2, 4096, 1, 64, 4, (16, 4, 4, 16, 1)), (2, 1000, 3, 65, 65, ()), (4, 300, 2, 1, 1, (5,)), (4, 9000, 1, 512, 512, (12, 2)),
+                                           (8, 5000, 64, 33, 3, (8,)), (16, 10000, 1, 130, 0, (68, 24, 4, 68, 1)), (16, 100, 2, 64, 100, (128,)),
+                                           (16, 100000, 1, 40, 16, (16, 4, 4, 1)), (32, 40000, 2, 256, 64, (4,)), (64, 200000, 1, 63, 1, (7056, 4))])
+def test_steps_on_the_chip(K, N, T, B, n, fb):
+    """per_step and per_insert_step as one launch on an LDS copy of the tree, with and without new rows (past the ring's end, at
+    given priorities, invalid ones among them), elements that are invalid, and other calls in between."""
+    log(f"steps on the chip K={K} N={N} T={T} B={B} n={n} fb={fb}")
+    rng = np.random.default_rng(K + N + B)
+    m = Mirror(K, N, T, fb)
+    m.gpu.set_tuning("step_on_chip", 2)
+    prio = wl._draw_priorities("exponential_1", rng, (T, N - N // 20))
+    prio[:, ::9] = 0.0
+    m.insert(N - N // 20, prio=prio, chunk=1 << 18)
+    for it in range(6):
+        up = wl._draw_updates("absnormal1_eps_pow0.6", rng, (T, B))
+        if it == 2:
+            up[:, ::3] = np.float32("nan")
+        ins = (rng.random((T, n)) * 5).astype(np.float32) if n and it % 2 else None
+        if ins is not None and it == 3:
+            ins[:, 0] = np.float32("inf")
+        if n and it != 4:
+            m.insert_step_call(n, ins, wl.uniform01(rng, (T, B)), 0.3 + 0.1 * it, it != 1, up)
+        else:
+            m.step_call(wl.uniform01(rng, (T, B)), 0.3 + 0.1 * it, it != 1, up, None)
+        m.compare_tree()
+        if it == 3:
+            m.update(rng.integers(0, N, (T, 50)).astype(np.uint32), rng.random((T, 50)).astype(np.float32))
+    m.compare_status()
+
+
+def test_steps_on_the_chip_draw_and_replay_as_the_kernels_do():
+    """The library's own uniforms, results that lie over inputs (the usual way is taken), an empty tree, and replays of a
+    captured step between eager calls: the same as with the kernels."""
+    log("steps on the chip against the kernels")
+    K, N, B, n, fb = 16, 5000, 48, 6, (16, 4)
+    bufs = []
+    for way in (2, 0):
+        p = PrioritizedReplay(K, N, 1, fb)
+        p.set_tuning("step_on_chip", way)
+        p.set_rng(99)
+        bufs.append(p)
+    new = lambda *shape, dtype=torch.int32: torch.zeros(shape, dtype=dtype, device="cuda")  # noqa: E731
+    g = torch.Generator(device="cuda")
+    got = []
+    for p in bufs:
+        g.manual_seed(5)
+        rand = lambda *shape: torch.rand(shape, generator=g, device="cuda")  # noqa: E731
+        rows = lambda k: [torch.randint(0, 256, (1, k, b), generator=g, device="cuda", dtype=torch.uint8) for b in fb]  # noqa: E731
+        out = []
+        p.insert(20, rows(20), torch.zeros((1, 20), device="cuda"))
+        i, w, v = p.step(None, 0.5, rand(1, B), B=B)                      # nothing to draw
+        out += [i, w, v]
+        p.insert(3000, rows(3000), rand(1, 3000))
+        slots, idx, wt, val, ro, up = new(1, n), new(1, B), new(1, B, dtype=torch.float32), new(1, B, dtype=torch.float32), rows(B), rand(1, B)
+        for _ in range(3):
+            p.step(None, 0.5, up, out_idx=idx, out_weight=wt, out_prio=val, rows_out=ro, B=B, insert=(n, rows(n), None, slots))
+            out += [x.clone() for x in (idx, wt, val, slots, *ro)]
+        p.step(None, 0.5, up, out_idx=idx, out_weight=wt, out_prio=val, rows_out=ro, B=B, insert=(B, ro, None, None))   # rows stored again
+        out += [x.clone() for x in (idx, wt, val, *ro)]
+        u = rand(1, B)
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            for _ in range(2):
+                p.step(u, 0.5, up, out_idx=idx, out_weight=wt, out_prio=val, rows_out=ro)
+        for _ in range(3):
+            u.copy_(rand(1, B))
+            graph.replay()
+            p.note_replay()
+            out += [x.clone() for x in (idx, wt, val, *ro)]
+            p.update(idx, rand(1, B))
+            i, w, v = p.step(rand(1, B), 0.7, rand(1, B))
+            out += [i, w, v]
+        out += [p.read_level(0, h) for h in range(p.H + 1)] + [torch.tensor([p.status(), p.cursor, p.size])]
+        got.append(out)
+    for k, (a, b) in enumerate(zip(*got)):
+        assert a.cpu().numpy().tobytes() == b.cpu().numpy().tobytes(), f"result {k}"
+
+
 @pytest.mark.parametrize("K,N", [(2, 1), (2, 16), (2, 17), (2, 33), (2, 513), (4, 5), (4, 65), (4, 4097), (8, 9), (8, 520), (8, 1025), (16, 17),
                                  (16, 2049), (16, 36000), (32, 33), (32, 4100), (64, 65), (64, 8200),   # 64, 65, 128, 129 nodes on a level and around
                                  (2, 19400), (4, 29000), (8, 33900), (64, 38200), (8, 272000), (64, 2400000)])   # the most that fit, with and without their leaves
