@@ -264,7 +264,7 @@ __device__ __forceinline__ void descend_chunk(P grp, const float (&s)[(1 << LOGK
 // grp points at the K children (LDS or global).  Returns the chosen child, its value and the
 // residual.  The chosen chunk is read a second time instead of keeping all K children live.
 template <int LOGK, typename P>
-__device__ __forceinline__ void descend_lane(P grp, float& r, unsigned& child, float& val) {
+__device__ __forceinline__ void descend_looking(P grp, float& r, unsigned& child, float& val) {
   if constexpr (LOGK == 1) {
     const Floats2 c = load_floats2(grp);
     const bool right = (c.y != 0.0f) && !(r < c.x);
@@ -280,6 +280,85 @@ __device__ __forceinline__ void descend_lane(P grp, float& r, unsigned& child, f
       s[c] = (x.x + x.y) + (x.z + x.w);
     }
     descend_chunk<LOGK>(grp, s, r, child, val);
+  }
+}
+
+// The same binary steps on a group held in registers, without a look at the right block.  That the right block is zero
+// while r is not below the left one takes a rounding, or a uniform outside [0, 1); a walk that does not look then ends at a
+// child of zero, because a block whose sum is zero holds nothing else, and whoever walks so has to check that.  (c: the N
+// children; node: 2 node + 1 for a turn to the right.)
+template <int N>
+__device__ __forceinline__ float first_half_sum(const float (&c)[N]) {   // of c[0 .. N/2), pairwise
+  if constexpr (N == 2) {
+    return c[0];
+  } else {
+    float h[N / 2];
+#pragma unroll
+    for (int i = 0; i < N / 2; ++i) h[i] = c[i];
+    if constexpr (N == 4) return h[0] + h[1];
+    else {
+      float up[N / 4];
+#pragma unroll
+      for (int i = 0; i < N / 4; ++i) up[i] = h[2 * i] + h[2 * i + 1];
+#pragma unroll
+      for (int w = N / 8; w >= 1; w /= 2)
+#pragma unroll
+        for (int i = 0; i < w; ++i) up[i] = up[2 * i] + up[2 * i + 1];
+      return up[0];
+    }
+  }
+}
+template <int N>
+__device__ __forceinline__ void turn_down(const float (&c)[N], float& r, uint32_t& node, float& val) {
+  if constexpr (N == 1) {
+    val = c[0];
+  } else {
+    const float L = first_half_sum<N>(c), rest = r - L;
+    const bool right = !(r < L);
+    r = right ? rest : r;
+    node = 2u * node + (right ? 1u : 0u);
+    float h[N / 2];
+#pragma unroll
+    for (int i = 0; i < N / 2; ++i) h[i] = right ? c[N / 2 + i] : c[i];
+    turn_down<N / 2>(h, r, node, val);
+  }
+}
+// The child chosen in the group behind grp, its value and the residual, as descend_looking() gives them, by a walk that does
+// not look first: half the right blocks' sums need not be built, and up to sixteen children stay in registers where the
+// chosen chunk was read a second time.  Lanes that arrive at a zero make the wave walk again, looking.
+template <int LOGK, typename P>
+__device__ __forceinline__ void descend_lane(P grp, float& r, unsigned& child, float& val) {
+  constexpr int K = 1 << LOGK;
+  const float r0 = r;
+  uint32_t at = 0;
+  if constexpr (LOGK == 1) {
+    const Floats2 x = load_floats2(grp);
+    const float c[2] = {x.x, x.y};
+    turn_down<2>(c, r, at, val);
+  } else if constexpr (LOGK <= 4) {
+    float c[K];
+#pragma unroll
+    for (int k = 0; k < K / 4; ++k) {
+      const Floats4 x = load_floats4(grp + 4 * k);
+      c[4 * k] = x.x, c[4 * k + 1] = x.y, c[4 * k + 2] = x.z, c[4 * k + 3] = x.w;
+    }
+    turn_down<K>(c, r, at, val);
+  } else {
+    float sums[K / 4];
+#pragma unroll
+    for (int k = 0; k < K / 4; ++k) {
+      const Floats4 x = load_floats4(grp + 4 * k);
+      sums[k] = (x.x + x.y) + (x.z + x.w);
+    }
+    turn_down<K / 4>(sums, r, at, val);
+    const Floats4 x = load_floats4(grp + 4 * at);
+    const float c[4] = {x.x, x.y, x.z, x.w};
+    turn_down<4>(c, r, at, val);
+  }
+  child = at;
+  if (__builtin_expect(__any(!(val > 0.0f)), 0)) {
+    r = r0;
+    descend_looking<LOGK>(grp, r, child, val);
   }
 }
 

@@ -159,7 +159,17 @@ __device__ __forceinline__ void descend_row(const float* row, float& r, unsigned
       s[c + 3] = x.w;
     }
   }
-  descend_chunk<LOGK>(row, s, r, child, val);
+  const float r0 = r;
+  uint32_t at = 0;
+  turn_down<Row::C>(s, r, at, val);
+  const Floats4 x = load_floats4(row + 4 * at);
+  const float c[4] = {x.x, x.y, x.z, x.w};
+  turn_down<4>(c, r, at, val);
+  child = at;
+  if (__builtin_expect(__any(!(val > 0.0f)), 0)) {   // (see descend_lane)
+    r = r0;
+    descend_chunk<LOGK>(row, s, r, child, val);
+  }
 }
 
 // stale < 0: the tree in memory is whole.  stale >= 0: the last update left the root and the

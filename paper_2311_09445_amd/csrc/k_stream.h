@@ -781,44 +781,6 @@ __device__ __forceinline__ void note_wild(float u, uint32_t batch, uint32_t* s_w
   if (__builtin_expect(__any(__float_as_uint(u) >= 0x3F800000u), 0)) *s_wild = batch;
 }
 
-// The binary steps of the walk inside a group held in registers, without a look at the right block: see walk_tree.
-// (children: the N children; node: 2 node + 1 for a turn to the right)
-template <int N>
-__device__ __forceinline__ float first_half_sum(const float (&c)[N]) {   // of c[0 .. N/2), pairwise
-  if constexpr (N == 2) {
-    return c[0];
-  } else {
-    float h[N / 2];
-#pragma unroll
-    for (int i = 0; i < N / 2; ++i) h[i] = c[i];
-    if constexpr (N == 4) return h[0] + h[1];
-    else {
-      float up[N / 4];
-#pragma unroll
-      for (int i = 0; i < N / 4; ++i) up[i] = h[2 * i] + h[2 * i + 1];
-#pragma unroll
-      for (int w = N / 8; w >= 1; w /= 2)
-#pragma unroll
-        for (int i = 0; i < w; ++i) up[i] = up[2 * i] + up[2 * i + 1];
-      return up[0];
-    }
-  }
-}
-template <int N>
-__device__ __forceinline__ void turn_down(const float (&c)[N], float& r, uint32_t& node, float& val) {
-  if constexpr (N == 1) {
-    val = c[0];
-  } else {
-    const float L = first_half_sum<N>(c), rest = r - L;
-    const bool right = !(r < L);
-    r = right ? rest : r;
-    node = 2u * node + (right ? 1u : 0u);
-    float h[N / 2];
-#pragma unroll
-    for (int i = 0; i < N / 2; ++i) h[i] = right ? c[N / 2 + i] : c[i];
-    turn_down<N / 2>(h, r, node, val);
-  }
-}
 // One level down: grp points at the children of `node`.
 template <int LOGR, typename P>
 __device__ __forceinline__ void level_down(P grp, float& r, uint32_t& node, float& val) {
@@ -896,10 +858,10 @@ __device__ __forceinline__ void walk_tree(const TreeView<MEM>& tv, uint32_t i, u
     for (v = tv.V; v-- > 0;) {
       unsigned child;
       if constexpr (MEM) {
-        if (v == 0) descend_lane<LOGR>(as_global(static_cast<const float*>(tv.leaves)) + (size_t)node * R, r, child, val);
-        else descend_lane<LOGR>(static_cast<const float*>(tv.tree) + tv.off(v) + (size_t)node * R, r, child, val);
+        if (v == 0) descend_looking<LOGR>(as_global(static_cast<const float*>(tv.leaves)) + (size_t)node * R, r, child, val);
+        else descend_looking<LOGR>(static_cast<const float*>(tv.tree) + tv.off(v) + (size_t)node * R, r, child, val);
       } else {
-        descend_lane<LOGR>(static_cast<const float*>(tv.tree) + tv.off(v) + (size_t)node * R, r, child, val);
+        descend_looking<LOGR>(static_cast<const float*>(tv.tree) + tv.off(v) + (size_t)node * R, r, child, val);
       }
       node = node * R + child;
     }
