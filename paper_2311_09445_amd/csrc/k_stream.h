@@ -339,11 +339,14 @@ __device__ __forceinline__ uint32_t ring_slot(uint32_t cursor, uint32_t j, uint3
 // slots.  All loads are on their way before the first store, and all of a wave's items have one access width: the code
 // for a width is straight.  (Several waves share a SIMD, and what they issue is what bounds large batches.)
 constexpr int kInFlight = 6;   // (of a wave that does nothing else)
-template <int M>
+template <int M, bool PACKED = false>
 struct GatherItems {
   uint32_t count = 0, w = 0;   // items, their access width
   uint32_t on = 0;             // bit k: this lane has a piece of item k
-  uint32_t row[M], slot[M], at[M], out[M];
+  // (PACKED: a batch of at most 512 rows, whose number goes into the bits above the 23 of an offset in a stored row, 8 fields of at
+  // most 1 MiB.  For the queue, whose waves have no register to spare: what they spill they read back between loads and
+  // stores, each time with a wait for all they have under way.  The list of steps, which spills nothing, loses 1 % by it.)
+  uint32_t row[M], slot[M], at[PACKED ? 1 : M], out[M];
   const uint8_t* base;         // row 0 of the tree's payload
   uint32_t field[M];
   uint4 v[M];
@@ -362,13 +365,14 @@ struct GatherItems {
         on |= p.row != 0xFFFFFFFFu ? 1u << k : 0u;
         row[k] = p.row != 0xFFFFFFFFu ? p.row : 0u;
         out[k] = p.out;
-        at[k] = p.at;
+        if constexpr (PACKED) row[k] = row[k] << 23 | p.at;
+        else at[k] = p.at;
         field[k] = p.f;
         take(k, p);
       } else {
         row[k] = row[0];
         out[k] = 0;
-        at[k] = at[0];
+        if constexpr (!PACKED) at[k] = at[0];
         field[k] = 0;
       }
     }
@@ -377,7 +381,7 @@ struct GatherItems {
   __device__ __forceinline__ void load_as(uint32_t N, uint32_t row_stride) {
 #pragma unroll
     for (int k = 0; k < C; ++k) {
-      const V x = *(GlobalPtr<const V>)as_global(base + (uint64_t)(slot[k] < N ? slot[k] : 0u) * row_stride + at[k]);
+      const V x = *(GlobalPtr<const V>)as_global(base + (uint64_t)(slot[k] < N ? slot[k] : 0u) * row_stride + (PACKED ? row[k] & 0x7FFFFFu : at[PACKED ? 0 : k]));
       if constexpr (sizeof(V) == 16) v[k] = make_uint4(x.x, x.y, x.z, x.w);
       else if constexpr (sizeof(V) == 8) v[k].x = x.x, v[k].y = x.y;
       else v[k].x = x;
@@ -386,7 +390,7 @@ struct GatherItems {
   template <int C>
   __device__ __forceinline__ void load_some(const uint32_t* nodes, uint32_t N, uint32_t row_stride) {
 #pragma unroll
-    for (int k = 0; k < C; ++k) slot[k] = nodes[row[k]];
+    for (int k = 0; k < C; ++k) slot[k] = nodes[PACKED ? row[k] >> 23 : row[k]];
     if (w == 16u) load_as<C, Words4>(N, row_stride);
     if (w == 8u) load_as<C, Words2>(N, row_stride);
     if (w == 4u) load_as<C, uint32_t>(N, row_stride);
@@ -886,10 +890,11 @@ __device__ __forceinline__ uint32_t smallest_value(const float* values, uint32_t
     for (uint32_t k = 0; k < 2; ++k) {
       const uint32_t e = 4u * (k * 64u + lane);
       const Floats4 x = load_floats4(values + e);
-      if (e < n) m = min_u32(m, __float_as_uint(x.x));
-      if (e + 1u < n) m = min_u32(m, __float_as_uint(x.y));
-      if (e + 2u < n) m = min_u32(m, __float_as_uint(x.z));
-      if (e + 3u < n) m = min_u32(m, __float_as_uint(x.w));
+      const int left = (int)n - (int)e;   // (one number and four constants: e + 1 .. e + 3 were kept over the rounds, spilled)
+      if (left > 0) m = min_u32(m, __float_as_uint(x.x));
+      if (left > 1) m = min_u32(m, __float_as_uint(x.y));
+      if (left > 2) m = min_u32(m, __float_as_uint(x.z));
+      if (left > 3) m = min_u32(m, __float_as_uint(x.w));
     }
   }
   return wave_min_u32(m);
@@ -1238,12 +1243,13 @@ k_run_steps(StreamKernelArgs ka) {
 // of a round are then read from its lanes.  (With every wave at the requests' fields, one LDS trip each, rounds of 64 samples
 // on 4096 leaves at K = 16 took 4.0 us where they take 2.0.)  The lists of fields in LDS are made anew only where a request
 // asks for other fields or another number of rows than the one before it: making them for every request, and finding
-// every wave's items in them, held the round of 512 at 8.5 us where it takes 6.7.
+// every wave's items in them, held the round of 512 at 8.5 us, 6.7 without.
 // Fetching ahead is only right where a request reads nothing that one just before it writes (an update whose index
 // array is the sampled one, say).  The host has checked that (QueueArgs::ahead); where it does not hold, every
 // request is a round of its own with an empty one behind it, which brings all results to memory.
-// 20 times (insert 16 rows, sample 512, update them) on 30 000 leaves at K = 16: 134 us; 353 us one request after the
-// other by the whole workgroup with a full barrier between their phases.
+// 20 times (insert 16 rows, sample 512, update them) on 30 000 leaves at K = 16: 112 us; 353 us one request after the
+// other by the whole workgroup with a full barrier between their phases.  The row waves are at work throughout, the team
+// waits for them at both barriers, a third of the round: 40 gathers of 64 rows each take the memory pipe 100 cycles.
 struct QueueKernelArgs {            // one kernel argument (Geom first: see fill_level_table)
   Geom g;
   QueueArgs a;
@@ -1446,7 +1452,7 @@ k_run_requests(QueueKernelArgs ka) {
     RowItem ip{};
     ip.row = 0xFFFFFFFFu;
     uint4 iv;
-    GatherItems<kInFlight> items;
+    GatherItems<kInFlight, !WAVE> items;
     auto list_of = [](uint32_t n, uint32_t asked) { return n ? n << 16 | asked : 0u; };
     // The lists that `items` and `share`, and `ip` and `insert_items`, are of: rows << 16 | fields asked for; and, of the wave
     // that fills them, those in LDS by parity.

@@ -1801,6 +1801,29 @@ def test_run_requests_in_rounds(K, N, T, fb, sizes, dependent):
     assert m.gpu.cursor == m.cpu.trees[0].cursor and m.gpu.size == m.cpu.trees[0].size
 
 
+@pytest.mark.parametrize("B", [65, 70])
+@pytest.mark.parametrize("b", [4096, 1 << 20])
+def test_run_requests_moves_the_longest_rows(B, b):
+    """Rows of eight fields of the longest size there is, and a batch of several waves: where a piece lies in its row takes all the
+    bits that the row movers keep for it."""
+    from paper_2311_09445_amd.per import OP_SAMPLE
+    log(f"on-chip queue, rows of 8 x {b} bytes B={B}")
+    N = 70
+    p = PrioritizedReplay(16, N, 1, (b,) * 8)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(b + B)
+    stored = [torch.randint(0, 256, (1, N, b), generator=g, device="cuda", dtype=torch.uint8) for _ in range(8)]
+    p.insert(N, stored, torch.rand((1, N), generator=g, device="cuda"))
+    u, idx = torch.rand((1, B), generator=g, device="cuda"), torch.zeros((1, B), dtype=torch.int32, device="cuda")
+    got = [torch.zeros((1, B, b), dtype=torch.uint8, device="cuda") if f in (0, 7) else None for f in range(8)]
+    keep = p.run_requests([{"op": OP_SAMPLE, "u": u, "beta": 0.5, "idx": idx, "rows": got}])
+    want = p.sample(u, 0.5)[0]
+    assert torch.equal(idx, want)
+    for f in (0, 7):
+        assert torch.equal(got[f][0], stored[f][0][idx[0].long()]), f"field {f}"
+    del keep
+
+
 def test_run_requests_argument_checks():
     from paper_2311_09445_amd.per import OP_SAMPLE, OP_UPDATE
     big = PrioritizedReplay(16, 1 << 20)
