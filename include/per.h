@@ -421,6 +421,11 @@ uint64_t per_rng_calls(const per_t* p);
  *                  weights in a second, where the tree fits that kernel and the batch is large enough for it
  *                  to pay off (long runs of samples per subtree, few trees); 2: wherever the tree fits (tests);
  *                  0: always the separate kernels
+ *   "step_on_chip" : how per_step and per_insert_step run small batches on trees that fit the LDS of a compute unit, or
+ *                  whose heights above the leaves do (per_run_steps_fits).  1 (default): as one launch, one workgroup per
+ *                  tree, where that is the faster way; 2: wherever it can be (tests); 0: never.  (Whoever sets
+ *                  "step_kernel", "group_claim", "claim_in_sample", "insert_ride" or "lazy_top" from their defaults gets
+ *                  the kernels that those choose.)
  *   "claim_in_sample" : 1 (default) lets per_sample_gather_update run the first phase of its update
  *                  inside the sampling kernel (two kernels per step) whenever the update batch is the
  *                  sampled batch itself or lies apart from the sampling outputs; 0: always three kernels */

@@ -1248,8 +1248,8 @@ k_run_steps(StreamKernelArgs ka) {
 // array is the sampled one, say).  The host has checked that (QueueArgs::ahead); where it does not hold, every
 // request is a round of its own with an empty one behind it, which brings all results to memory.
 // 20 times (insert 16 rows, sample 512, update them) on 30 000 leaves at K = 16: 112 us; 353 us one request after the
-// other by the whole workgroup with a full barrier between their phases.  The row waves are at work throughout, the team
-// waits for them at both barriers, a third of the round: 40 gathers of 64 rows each take the memory pipe 100 cycles.
+// other by the whole workgroup with a full barrier between their phases.  The row waves are at work throughout, and the
+// team waits for them at both barriers, a third of the round.
 struct QueueKernelArgs {            // one kernel argument (Geom first: see fill_level_table)
   Geom g;
   QueueArgs a;

@@ -1801,27 +1801,32 @@ def test_run_requests_in_rounds(K, N, T, fb, sizes, dependent):
     assert m.gpu.cursor == m.cpu.trees[0].cursor and m.gpu.size == m.cpu.trees[0].size
 
 
-@pytest.mark.parametrize("B", [65, 70])
-@pytest.mark.parametrize("b", [4096, 1 << 20])
-def test_run_requests_moves_the_longest_rows(B, b):
-    """Rows of eight fields of the longest size there is, and a batch of several waves: where a piece lies in its row takes all the
-    bits that the row movers keep for it."""
+@pytest.mark.parametrize("fb,B", [((1 << 20,) * 8, 65), ((4096,) * 8, 70), ((8, 2, 6, 3, 1, 4, 20, 5), 40), ((8, 2, 6, 3, 1, 4, 20, 5), 130), ((1, 1, 2, 24, 12, 7), 513)])
+def test_on_chip_row_pieces(fb, B):
+    """Rows of the longest fields there are, where a piece's place in its row takes all the bits that are kept for it, and of fields of
+    every access width at many places of the 16 bytes that a narrow piece comes with; from a queue and from a list of steps."""
     from paper_2311_09445_amd.per import OP_SAMPLE
-    log(f"on-chip queue, rows of 8 x {b} bytes B={B}")
+    log(f"on-chip row pieces fb={fb} B={B}")
     N = 70
-    p = PrioritizedReplay(16, N, 1, (b,) * 8)
+    p = PrioritizedReplay(16, N, 1, fb)
     g = torch.Generator(device="cuda")
-    g.manual_seed(b + B)
-    stored = [torch.randint(0, 256, (1, N, b), generator=g, device="cuda", dtype=torch.uint8) for _ in range(8)]
+    g.manual_seed(sum(fb) + B)
+    stored = [torch.randint(0, 256, (1, N, b), generator=g, device="cuda", dtype=torch.uint8) for b in fb]
     p.insert(N, stored, torch.rand((1, N), generator=g, device="cuda"))
-    u, idx = torch.rand((1, B), generator=g, device="cuda"), torch.zeros((1, B), dtype=torch.int32, device="cuda")
-    got = [torch.zeros((1, B, b), dtype=torch.uint8, device="cuda") if f in (0, 7) else None for f in range(8)]
-    keep = p.run_requests([{"op": OP_SAMPLE, "u": u, "beta": 0.5, "idx": idx, "rows": got}])
+    asked = [f for f in range(len(fb)) if fb[f] <= 4096 or f in (0, 7)]
+    u = torch.rand((1, B), generator=g, device="cuda")
     want = p.sample(u, 0.5)[0]
-    assert torch.equal(idx, want)
-    for f in (0, 7):
-        assert torch.equal(got[f][0], stored[f][0][idx[0].long()]), f"field {f}"
-    del keep
+    for form in ("queue", "steps"):
+        idx = torch.zeros((1, B), dtype=torch.int32, device="cuda")
+        got = [torch.zeros((1, B, b), dtype=torch.uint8, device="cuda") if f in asked else None for f, b in enumerate(fb)]
+        if form == "queue":
+            keep = p.run_requests([{"op": OP_SAMPLE, "u": u, "beta": 0.5, "idx": idx, "rows": got}])
+        else:
+            keep = p.run_steps(u[None], torch.full((1,), 0.5, device="cuda"), idx[None], None, None, [x if x is None else x[None] for x in got])
+        assert torch.equal(idx, want), form
+        for f in asked:
+            assert torch.equal(got[f][0], stored[f][0][idx[0].long()]), f"{form}: field {f}"
+        del keep
 
 
 def test_run_requests_argument_checks():
