@@ -185,7 +185,20 @@ __device__ __forceinline__ void lds_tree_store(const Geom& g, uint32_t t, const 
 // shared out lane by lane, every lane paid for a chain of selects over the fields, a division, and the loads and
 // stores of every width that occurs in its wave).
 constexpr int kWidths = 5;         // access widths: 16, 8, 4, 2 and 1 byte
-constexpr uint32_t kLeastMovers = 6;   // waves that share a list's items, at least (see fill_piece_fields)
+constexpr uint32_t kInFlight = 6;   // items that a wave which does nothing else has under way at once
+constexpr uint32_t kLeastMovers = 6;   // row waves that are left to gather where the others weigh the samples, at least
+// How the items of a gather are shared out among the row waves.
+enum GatherShares {
+  SHARES_NONE,   // (an insertion)
+  SHARES_RUNS,   // every wave has a run of at most kInFlight items of one access width: straight code, and all under way at once
+  SHARES_EVEN,   // more than that, or a team that does the rows as well: equally many to every wave, see gather_spans
+  SHARES_ANY     // runs where that works, else evenly (a queue, whose requests differ: the first few of a wave's items are kept all the same)
+};
+// Waves that gather in runs where n samples are weighed as well: those that do not weigh, if there are enough.
+__host__ __device__ __forceinline__ uint32_t run_waves(uint32_t n, uint32_t rws) {
+  const uint32_t weigh = (n + 63u) / 64u;
+  return rws >= weigh + kLeastMovers ? rws - weigh : rws;
+}
 struct PieceFields {               // what the waves ask of one list of fields, in LDS
   uint8_t* io[kMaxFields];         // the caller's array: the rows of this tree (in step 0)
   uint8_t* base;                   // row 0 of this tree's payload
@@ -201,16 +214,11 @@ __device__ __forceinline__ uint64_t wave_value64(uint64_t x) {
   return (uint64_t)wave_value((uint32_t)(x >> 32)) << 32 | wave_value((uint32_t)x);
 }
 __device__ __forceinline__ uint8_t* wave_pointer(uint8_t* p) { return reinterpret_cast<uint8_t*>(wave_value64(reinterpret_cast<uint64_t>(p))); }
-// Row waves that gather the rows of n samples (the others of `rws` weigh them, if there are enough).
-__device__ __forceinline__ uint32_t gathering_waves(uint32_t n, uint32_t rws) {
-  const uint32_t weigh = (n + 63u) / 64u;
-  return rws >= weigh + kLeastMovers ? rws - weigh : rws;
-}
 // Called by one wave: n rows per tree; field f is `asked` for, and its array is `io` for tree 0, `step_rows` rows from step to
-// step; `waves` >= kLeastMovers waves take the items, each a run of them and of one access width, so that what a wave does
-// with its items is straight code: the runs are as short as that allows.  share (null: not asked for): items of wave i.
+// step; the `rws` row waves share the items out.  share: items of wave i.  (Host: gathers_in_runs() says whether runs work.)
+template <GatherShares SHARES>
 __device__ __forceinline__ void fill_piece_fields(const FieldTable* ft, bool asked, uint8_t* io, uint32_t t, uint32_t n, uint64_t step_rows,
-                                                  uint32_t waves, PieceFields* pf, uint2* share) {
+                                                  uint32_t rws, PieceFields* pf, uint2* share) {
   const uint32_t lane = threadIdx.x & 63u, f = lane;
   const bool on = f < (uint32_t)kMaxFields && f < ft->n_fields && asked && n;
   const uint32_t E = on ? ft->bytes[f] : 1u, v = on ? ft->vec[f] : 1u, epr = row_elements(E, v);
@@ -243,29 +251,50 @@ __device__ __forceinline__ void fill_piece_fields(const FieldTable* ft, bool ask
     pf->step_rows = step_rows;
     pf->n = n;
   }
-  if (!share) return;
-  // the shortest runs with which there are waves enough: lane i tries one length.  (A run of all items
-  // always does, with a wave per width: the last lane tries no less.)
-  const uint32_t least = (total + waves - 1) / waves, len = least + lane * (total / 64u + 1u);
-  uint32_t needed = 0;
+  if constexpr (SHARES == SHARES_NONE) return;
+  uint32_t run = 0, waves = rws;
+  if constexpr (SHARES == SHARES_RUNS || SHARES == SHARES_ANY) {
+    // the shortest runs with which there are waves enough: lane i tries runs of i + 1 (at most 16 * 6 items count here, for which
+    // the product with the reciprocal is the quotient)
+    waves = run_waves(n, rws);
+    const uint32_t len = lane + 1u, recip = (0x10000u + lane) / len;
+    uint32_t needed = 0;
 #pragma unroll
-  for (int c = 0; c < kWidths; ++c) needed += len ? (of_kind[c] + len - 1) / len : 0u;
-  const unsigned long long enough = __ballot(needed <= waves);
-  const uint32_t run = (uint32_t)__builtin_amdgcn_readlane((int)len, enough ? (int)__builtin_ctzll(enough) : 63);
+    for (int c = 0; c < kWidths; ++c) needed += (min_u32(of_kind[c], 1023u) + lane) * recip >> 16;
+    const unsigned long long enough = __ballot(needed <= waves && lane < kInFlight);
+    run = enough ? 1u + (uint32_t)__builtin_ctzll(enough) : 0u;
+  }
   if (lane < 16u) {
-    uint32_t a = 0, b = 0, start = 0, wave0 = 0;
+    uint32_t a = 0, b = 0;
+    if (SHARES == SHARES_RUNS || (SHARES == SHARES_ANY && run)) {
+      const uint32_t recip = 0xFFFFu / run + 1u;   // (as above)
+      uint32_t start = 0, wave0 = 0;
 #pragma unroll
-    for (int c = 0; c < kWidths; ++c) {
-      const uint32_t takes = run ? (of_kind[c] + run - 1) / run : 0u;
-      if (lane >= wave0 && lane < wave0 + takes) {
-        a = start + (lane - wave0) * run;
-        b = a + run < start + of_kind[c] ? a + run : start + of_kind[c];
+      for (int c = 0; c < kWidths; ++c) {
+        const uint32_t takes = (of_kind[c] + run - 1u) * recip >> 16;
+        if (lane >= wave0 && lane < wave0 + takes) {
+          a = start + (lane - wave0) * run;
+          b = a + run < start + of_kind[c] ? a + run : start + of_kind[c];
+        }
+        start += of_kind[c];
+        wave0 += takes;
       }
-      start += of_kind[c];
-      wave0 += takes;
+    } else {
+      const uint32_t each = (total + rws - 1) / rws;
+      if (lane < rws && lane * each < total) {
+        a = lane * each;
+        b = a + each < total ? a + each : total;
+      }
     }
     share[lane] = make_uint2(a, b);
   }
+}
+// el / epr, for el < 2^31 (at most 1024 rows of at most 2^20 pieces, and less than a few items beyond them) and recip = floor(2^32 /
+// epr) + 1: recip is less than 1 / epr of itself too large, the quotient less than a half, so it comes out right or one too
+// large.  (epr = 1: recip = 0, and no branch for it: there is one such quotient per piece.)
+__device__ __forceinline__ uint32_t row_of_piece(uint32_t el, uint32_t epr, uint32_t recip) {
+  const uint32_t row = __umulhi(el, recip) | (epr == 1 ? el : 0u);
+  return row * epr > el ? row - 1u : row;
 }
 struct RowItem {         // this lane's piece of an item
   uint32_t row;          // row of the batch, 0xFFFFFFFF: no piece
@@ -275,16 +304,19 @@ struct RowItem {         // this lane's piece of an item
   uint32_t out;          // offset of the piece in it
   uint64_t step;         // bytes of that array per step (the same for the wave)
 };
-// Item i < pf.items of a list (in step 0).
-__device__ __forceinline__ RowItem find_item(const PieceFields& pf, uint32_t i) {
+// The field of item i < pf.items of a list.
+__device__ __forceinline__ uint32_t field_of_item(const PieceFields& pf, uint32_t i) {
   uint32_t f = 0;
 #pragma unroll
   for (uint32_t k = 1; k < (uint32_t)kMaxFields; ++k) f = i >= pf.first[k] && i < pf.end[k] ? k : f;
-  f = wave_value(f);
+  return wave_value(f);
+}
+// Item i < pf.items of a list (in step 0).
+__device__ __forceinline__ RowItem find_item(const PieceFields& pf, uint32_t i) {
+  const uint32_t f = field_of_item(pf, i);
   const uint32_t E = wave_value(pf.bytes[f]), w = wave_value(pf.width[f]), epr = (E + w - 1) / w;
   const uint32_t el = (i - wave_value(pf.first[f])) * 64u + (threadIdx.x & 63u);
-  // (at most 1024 rows: the reciprocal is exact for less than 2048 pieces per row)
-  const uint32_t row = epr == 1 ? el : epr < 2048u ? __umulhi(el, wave_value(pf.recip[f])) : el / epr;
+  const uint32_t row = row_of_piece(el, epr, wave_value(pf.recip[f]));
   const uint32_t k = el - row * epr, at = k * w + w > E ? E - w : k * w;   // (wide pieces: the last one ends with the field)
   RowItem p;
   p.row = row < wave_value(pf.n) ? row : 0xFFFFFFFFu;
@@ -338,7 +370,6 @@ __device__ __forceinline__ uint32_t ring_slot(uint32_t cursor, uint32_t j, uint3
 // is known before the rows are; prepared in time, what is left between the batch and its loads is a look at the batch's
 // slots.  All loads are on their way before the first store, and all of a wave's items have one access width: the code
 // for a width is straight.  (Several waves share a SIMD, and what they issue is what bounds large batches.)
-constexpr int kInFlight = 6;   // (of a wave that does nothing else)
 template <int M, bool PACKED = false>
 struct GatherItems {
   uint32_t count = 0, w = 0;   // items, their access width
@@ -350,9 +381,20 @@ struct GatherItems {
   const uint8_t* base;         // row 0 of the tree's payload
   uint32_t field[M];
   uint4 v[M];
-  // items first .. last - 1 (at most M) of a list; `take` is called with every item's number here and the item
+  // the items of one access width that items first .. last - 1 of a list begin with (at most M); `take` is called with every
+  // item's number here and the item
   template <typename F>
   __device__ __forceinline__ void prepare(const PieceFields& pf, uint32_t first, uint32_t last, F&& take) {
+    if constexpr (PACKED) {   // (the queue: others may be behind them, see SHARES_ANY)
+      if (first < last) {
+        const uint32_t width = wave_value(pf.width[field_of_item(pf, first)]);
+        uint32_t end = first;
+#pragma unroll
+        for (uint32_t f = 0; f < (uint32_t)kMaxFields; ++f) end = pf.width[f] == width && pf.end[f] > end ? pf.end[f] : end;
+        end = wave_value(end);   // (all items are ordered by width)
+        last = last < end ? last : end;
+      }
+    }
     count = first < last ? (last - first < (uint32_t)M ? last - first : (uint32_t)M) : 0u;
     on = 0;
     base = wave_pointer(pf.base);
@@ -436,18 +478,66 @@ struct GatherItems {
     if (w == 1u) store_as<C, uint8_t>(array_of);
   }
 };
-// Items first .. last of a list at once, from beginning to end, M at a time.  (array_of: the caller's array of a field, null:
-// as the list has it)
-template <int M, typename F>
-__device__ __forceinline__ void gather_rest(const PieceFields& pf, uint32_t first, uint32_t last, const uint32_t* nodes, uint32_t N,
-                                            uint32_t row_stride, uint64_t step, uint32_t& flags, F&& array_of) {
+// Items i .. end - 1 of one field of a gather (counted within the field), U at a time: the loads of all, then the stores
+// of all.  (nodes: the batch's slots; one beyond the tree gives zeros and a flag)
+template <int U, typename V>
+__device__ __forceinline__ void gather_span(uint32_t i, uint32_t end, uint32_t n, uint32_t epr, uint32_t recip, uint32_t E, uint32_t row_stride,
+                                            const uint8_t* col, uint8_t* io, const uint32_t* nodes, uint32_t N, uint32_t& flags) {
+  typedef std::conditional_t<(sizeof(V) < 4), uint32_t, V> Kept;   // (as bytes the compiler packs them and takes them apart again)
 #pragma unroll 1
-  for (; first < last; first += M) {
-    GatherItems<M> it;
-    uint8_t* io[M];
-    it.prepare(pf, first, last, [&](int k, const RowItem& p) { io[k] = array_of(p) + step * p.step; });
-    it.load(nodes, N, row_stride);
-    it.store(N, flags, [&](int k) { return io[k]; });
+  for (; i < end; i += U) {
+    Kept v[U];
+    uint32_t slot[U], row[U], at[U];
+#pragma unroll
+    for (int k = 0; k < U; ++k) {   // (beyond the end: the first piece again, so that no load stands in a branch)
+      asm volatile("" ::: "memory");   // (one after the other, as in prepare)
+      const uint32_t el = (i + k) * 64u + (threadIdx.x & 63u);
+      uint32_t r = row_of_piece(el, epr, recip);
+      const bool on = i + k < end && r < n;
+      const uint32_t within = on ? (el - r * epr) * (uint32_t)sizeof(V) : 0u;
+      r = on ? r : 0u;
+      at[k] = within + (uint32_t)sizeof(V) > E ? E - (uint32_t)sizeof(V) : within;   // (wide pieces: the last one ends with the field)
+      slot[k] = nodes[r];
+      row[k] = on ? r : 0xFFFFFFFFu;
+    }
+#pragma unroll
+    for (int k = 0; k < U; ++k) v[k] = *(GlobalPtr<const V>)as_global(col + (uint64_t)(slot[k] < N ? slot[k] : 0u) * row_stride + at[k]);
+#pragma unroll
+    for (int k = 0; k < U; ++k)
+      if (row[k] != 0xFFFFFFFFu) {
+        if (!(slot[k] < N)) {
+          v[k] = Kept{};
+          flags |= 1u;
+        }
+        *(GlobalPtr<V>)as_global(io + (row[k] * E + at[k])) = (V)v[k];   // (at most 1024 rows of at most 1 MiB)
+      }
+  }
+}
+// Items first .. last - 1 of a list, from beginning to end, a field at a time: what a field asks for is looked up once and the
+// code for its access width is straight.  What bounds it is the trip to memory per U items, and what the items' places
+// cost to work out.  Item by item, two at a time, with every lookup anew, a step on 10 000 leaves at K = 16 took 125 us with
+// 512 rows of one 165-byte field (1320 items), 15.5 with 512 rows of 165 bytes in five fields, 11.0 with 513 of 41 bytes;
+// so it takes 30.7, 8.2 and 6.9.  (U = 8 where the registers allow it: 64 rows' worth of 16-byte pieces for each of eight waves
+// is one trip then, 6.6 -> 6.1 us a step on 100 000 leaves; looped and not unrolled over the items: the code a round goes
+// through has to stay within the instruction cache.)  array_of(f, io): the caller's array of field f, io: as the list has it.
+template <int U, typename F>
+__device__ __forceinline__ void gather_spans(const PieceFields& pf, uint32_t first, uint32_t last, const uint32_t* nodes, uint32_t N,
+                                            uint32_t row_stride, uint64_t step, uint32_t& flags, F&& array_of) {
+  const uint32_t n = wave_value(pf.n);
+  const uint8_t* base = wave_pointer(pf.base);
+#pragma unroll 1
+  while (first < last) {
+    const uint32_t f = field_of_item(pf, first);
+    const uint32_t E = wave_value(pf.bytes[f]), w = wave_value(pf.width[f]), recip = wave_value(pf.recip[f]), epr = (E + w - 1) / w;
+    const uint32_t f0 = wave_value(pf.first[f]), fend = wave_value(pf.end[f]), end = fend < last ? fend : last;
+    const uint8_t* col = base + wave_value(pf.off[f]);
+    uint8_t* io = array_of(f, wave_pointer(pf.io[f])) + step * (wave_value64(pf.step_rows) * E);
+    if (w == 16u) gather_span<U, Words4>(first - f0, end - f0, n, epr, recip, E, row_stride, col, io, nodes, N, flags);
+    if (w == 8u) gather_span<U, Words2>(first - f0, end - f0, n, epr, recip, E, row_stride, col, io, nodes, N, flags);
+    if (w == 4u) gather_span<U, uint32_t>(first - f0, end - f0, n, epr, recip, E, row_stride, col, io, nodes, N, flags);
+    if (w == 2u) gather_span<U, uint16_t>(first - f0, end - f0, n, epr, recip, E, row_stride, col, io, nodes, N, flags);
+    if (w == 1u) gather_span<U, uint8_t>(first - f0, end - f0, n, epr, recip, E, row_stride, col, io, nodes, N, flags);
+    first = end;
   }
 }
 // The rows of an insertion at ring slot `cursor`, items first, first + every, ..; row j is left out where bit j of skip is set.
@@ -901,7 +991,8 @@ __device__ __forceinline__ uint32_t smallest_value(const float* values, uint32_t
 }
 
 // Who does the tree work: the first wave, the first few, or every wave, which then moves the rows as well.
-enum TeamForm { TEAM_ONE_WAVE, TEAM_WAVES, TEAM_ALL };
+// (TEAM_WAVES_SPANS, of a list: where a step's gather is more than its row waves have under way at once)
+enum TeamForm { TEAM_ONE_WAVE, TEAM_WAVES, TEAM_WAVES_SPANS, TEAM_ALL };
 static TeamForm team_form(uint32_t samples, uint32_t inserted) {
   const uint32_t most = samples > inserted ? samples : inserted;
   return most <= 64 ? TEAM_ONE_WAVE : most <= 512 ? TEAM_WAVES : TEAM_ALL;
@@ -934,7 +1025,7 @@ static TeamForm team_form(uint32_t samples, uint32_t inserted) {
 template <int LOGK, TeamForm FORM, bool MEM, bool AHEAD>
 __global__ void __launch_bounds__(1024)
 k_run_steps(StreamKernelArgs ka) {
-  constexpr bool WAVE = FORM == TEAM_ONE_WAVE, apart = FORM != TEAM_ALL;
+  constexpr bool WAVE = FORM == TEAM_ONE_WAVE, apart = FORM != TEAM_ALL, SPANS = FORM == TEAM_WAVES_SPANS || FORM == TEAM_ALL;
   const Geom& g = ka.g;
   const StreamArgs& a = ka.a;
   extern __shared__ __attribute__((aligned(16))) float tree[];
@@ -991,8 +1082,8 @@ k_run_steps(StreamKernelArgs ka) {
     const FieldTable* ft = kernarg_at<FieldTable>(offsetof(StreamKernelArgs, a) + (rows ? offsetof(StreamArgs, rows) : offsetof(StreamArgs, ins)));
     const uint32_t n = rows ? B : n_ins;
     uint8_t* io = lane < (uint32_t)kMaxFields ? ft->io[lane] : nullptr;
-    fill_piece_fields(ft, io != nullptr, io, t, n, (uint64_t)T * n, rows ? gathering_waves(B, rws) : rws, rows ? &s_rows : &s_ins,
-                      rows ? s_share : nullptr);
+    if (rows) fill_piece_fields<SPANS ? SHARES_EVEN : SHARES_RUNS>(ft, io != nullptr, io, t, n, (uint64_t)T * n, rws, &s_rows, s_share);
+    else fill_piece_fields<SHARES_NONE>(ft, io != nullptr, io, t, n, (uint64_t)T * n, rws, &s_ins, nullptr);
   } else {
     lds_tree_load<LOGK>(tab, lt, tid, 896u);
   }
@@ -1029,12 +1120,13 @@ k_run_steps(StreamKernelArgs ka) {
     float val = 0.0f;
     float total = tree[s_off[V]];                    // (WAVE: the root as the latest change has left it)
     // this wave's share of the rows, the same in every step: the first item of the insertion, fetched a step ahead, and the
-    // first few of the gather (a team that moves rows as well has no registers for those)
+    // items of the gather (SPANS: their numbers; what is kept over the steps for the others takes the registers that the spans
+    // have their loads in)
     RowItem ip{};
     ip.row = 0xFFFFFFFFu;
     uint4 iv;
     uint8_t* payload = nullptr;                      // row 0 of this tree
-    uint32_t more_first = 0, more_last = 0, insert_items = 0;   // the items of the gather beyond the first few; items of the insertion
+    uint32_t gather_first = 0, gather_last = 0, insert_items = 0;   // items of the insertion
     GatherItems<kInFlight> items;
     uint8_t* io[kInFlight];                          // the caller's arrays for those, in the step before s
     uint64_t io_step[kInFlight];
@@ -1045,15 +1137,13 @@ k_run_steps(StreamKernelArgs ka) {
         ip = find_item(s_ins, rw);
         if (ip.row != 0xFFFFFFFFu) iv = load_piece(ip.io + ip.out, ip.w);
       }
-      more_first = wave_value(s_share[rw].x);
-      more_last = wave_value(s_share[rw].y);
-      if constexpr (!TREE) {
-        items.prepare(s_rows, more_first, more_last, [&](int k, const RowItem& p) {
+      gather_first = wave_value(s_share[rw].x);
+      gather_last = wave_value(s_share[rw].y);
+      if constexpr (!SPANS)
+        items.prepare(s_rows, gather_first, gather_last, [&](int k, const RowItem& p) {
           io[k] = p.io;
           io_step[k] = p.step;
         });
-        more_first += kInFlight;
-      }
     }
     for (uint32_t s = 0;; ++s) {
       const bool more = s < a.n_steps;
@@ -1061,8 +1151,8 @@ k_run_steps(StreamKernelArgs ka) {
       float w_out = 0.0f, v_out = 0.0f;
       uint32_t n_out = 0;
       if (ROWS && s) {
-        if (more_first < more_last) gather_rest<TREE ? 4 : 2>(s_rows, more_first, more_last, nodes, N, a.rows.row_stride, s - 1, flags, list_array);
-        if constexpr (!TREE) items.load(nodes, N, a.rows.row_stride);
+        if constexpr (SPANS) gather_spans<apart ? 8 : 4>(s_rows, gather_first, gather_last, nodes, N, a.rows.row_stride, s - 1, flags, [](uint32_t, uint8_t* at) { return at; });
+        else items.load(nodes, N, a.rows.row_stride);
         uint32_t least = 0;
         if (a.out_w && tid >= w0) {   // (whole waves)
           if (a.buffer_norm) least = s_bmin[(s - 1) & 1u];
@@ -1079,7 +1169,7 @@ k_run_steps(StreamKernelArgs ka) {
       }
       auto store_results = [&]() {   // of the step before
         if (!ROWS || !s) return;
-        if constexpr (!TREE) {
+        if constexpr (!SPANS) {
           items.store(N, flags, [&](int k) { return io[k]; });
 #pragma unroll
           for (int k = 0; k < kInFlight; ++k) io[k] += io_step[k];
@@ -1426,7 +1516,8 @@ k_run_requests(QueueKernelArgs ka) {
       const uint32_t* w = words + PER_REQUEST_WORD(field) + 2u * lane;
       asked = (w[0] | w[1]) != 0;
     }
-    fill_piece_fields(fields, asked, nullptr, t, n, 0, share ? gathering_waves(n, rws) : rws, pf, share);
+    if (share) fill_piece_fields<apart ? SHARES_ANY : SHARES_EVEN>(fields, asked, nullptr, t, n, 0, rws, pf, share);
+    else fill_piece_fields<SHARES_NONE>(fields, asked, nullptr, t, n, 0, rws, pf, nullptr);
   };
   const bool lists = !(apart && in_team) && rw == 1;   // (the wave that does)
   __syncthreads();
@@ -1452,7 +1543,7 @@ k_run_requests(QueueKernelArgs ka) {
     RowItem ip{};
     ip.row = 0xFFFFFFFFu;
     uint4 iv;
-    GatherItems<kInFlight, !WAVE> items;
+    GatherItems<kInFlight, true> items;
     auto list_of = [](uint32_t n, uint32_t asked) { return n ? n << 16 | asked : 0u; };
     // The lists that `items` and `share`, and `ip` and `insert_items`, are of: rows << 16 | fields asked for; and, of the wave
     // that fills them, those in LDS by parity.
@@ -1530,9 +1621,9 @@ k_run_requests(QueueKernelArgs ka) {
       uint32_t n_out = 0;
       if (ROWS && n_before) {
         const uint32_t rest = share.x + items.count;
-        if (rest < share.y)
-          gather_rest<TREE ? 4 : 2>(s_rows[par ^ 1u], rest, share.y, nodes, N, a.fields.row_stride, 0, flags,
-                                    [&](const RowItem& p) { return before.array<kRoundSample>(p.f) + reinterpret_cast<uintptr_t>(p.io); });
+        if (__builtin_expect(rest < share.y, TREE))
+          gather_spans<4>(s_rows[par ^ 1u], rest, share.y, nodes, N, a.fields.row_stride, 0, flags,
+                          [&](uint32_t f, uint8_t* io) { return before.array<kRoundSample>(f) + reinterpret_cast<uintptr_t>(io); });
         if constexpr (!TREE) items.load(nodes, N, a.fields.row_stride);
         const bool weigh = before.pointer<kRoundSample + PER_REQUEST_WORD(out_weight), float>() != nullptr;
         uint32_t least = 0;
@@ -1657,7 +1748,7 @@ k_run_requests(QueueKernelArgs ka) {
             share.y = wave_value(s_share[par][rw].y);
             if constexpr (!TREE) {
               // (this tree's place in the caller's arrays goes into the offsets of the pieces; where it is too far for those
-              // the items are taken as those beyond the first few)
+              // the items are taken like those beyond the first few)
               bool far = false;
               items.prepare(s_rows[par], share.x, share.y, [&](int k, const RowItem& p) {
                 far = far || reinterpret_cast<uintptr_t>(p.io) > 0x7FFFFFFFull;
@@ -1798,6 +1889,24 @@ bool step_on_chip_pays(const Geom& g, uint32_t n_insert, uint32_t B, const Field
 #undef CALL
 }
 
+// Waves of the team (where it is not all of them).
+static uint32_t team_waves(uint32_t samples, uint32_t inserted) { return ((samples > inserted ? samples : inserted) + 63u) / 64u; }
+// Whether a gather of n rows can be shared out in runs among rws row waves (see fill_piece_fields).
+static bool gathers_in_runs(const FieldTable& ft, uint32_t n, uint32_t rws) {
+  uint64_t of_kind[kWidths] = {};
+  for (uint32_t f = 0; f < ft.n_fields; ++f) {
+    if (!ft.io[f]) continue;
+    const uint32_t w = moves_wide(ft.bytes[f], ft.vec[f]) ? 16u : ft.vec[f];
+    of_kind[4 - __builtin_ctz(w)] += ((uint64_t)n * row_elements(ft.bytes[f], ft.vec[f]) + 63u) / 64u;
+  }
+  for (uint32_t len = 1; len <= kInFlight; ++len) {
+    uint64_t needed = 0;
+    for (int c = 0; c < kWidths; ++c) needed += (of_kind[c] + len - 1) / len;
+    if (needed <= run_waves(n, rws)) return true;
+  }
+  return false;
+}
+
 template <int LOGK>
 static hipError_t launch_run_steps_k(const Geom& g, const Tuning& tn, StreamArgs a, hipStream_t s) {
   StreamKernelArgs ka{};
@@ -1808,7 +1917,8 @@ static hipError_t launch_run_steps_k(const Geom& g, const Tuning& tn, StreamArgs
   const size_t bytes = (size_t)floats * 4;
   // always the largest workgroup, also for small batches: measured faster than a workgroup of the batch's
   // size (the tree copy and the row movers use all lanes)
-  const TeamForm form = team_form(a.B, a.n_insert);
+  TeamForm form = team_form(a.B, a.n_insert);
+  if (form != TEAM_ALL && !gathers_in_runs(a.rows, a.B, 16u - team_waves(a.B, a.n_insert))) form = TEAM_WAVES_SPANS;
   const bool mem = ka.a.leaves_in_memory != 0;
 #define PER_RUN(F, M, A)                                                                                \
   do {                                                                                                  \
@@ -1826,6 +1936,7 @@ static hipError_t launch_run_steps_k(const Geom& g, const Tuning& tn, StreamArgs
   } while (0)
   if (form == TEAM_ONE_WAVE) PER_RUN_WHEN(TEAM_ONE_WAVE);
   else if (form == TEAM_WAVES) PER_RUN_WHEN(TEAM_WAVES);
+  else if (form == TEAM_WAVES_SPANS) PER_RUN_WHEN(TEAM_WAVES_SPANS);
   else PER_RUN_WHEN(TEAM_ALL);
 #undef PER_RUN_WHEN
 #undef PER_RUN_WHERE

@@ -1829,6 +1829,46 @@ def test_on_chip_row_pieces(fb, B):
         del keep
 
 
+@pytest.mark.parametrize("fb,B", [((165,), 64), ((165,), 130), ((165,), 512), ((165,), 513), ((165,), 1024), ((68, 24, 4, 68, 1), 256), ((68, 24, 4, 68, 1), 400),
+                                  ((68, 24, 4, 68, 1), 1024), ((16, 4, 4, 16, 1), 512), ((128,), 512), ((8, 2, 6, 3, 1, 4, 20, 5), 512), ((4099, 6, 1), 33),
+                                  ((4099, 2050, 12), 300), ((24, 8, 40, 16), 384), ((24, 8, 40, 16), 385), ((1,), 1), ((16,) * 8, 384), ((16,) * 8, 385)])
+def test_on_chip_rows_of_all_shares(fb, B):
+    """Gathers of as many pieces as the row waves have under way at once, and of more: shared out by width or evenly, fields of every
+    width, more pieces in a row than a reciprocal of 32 bits is exact for; two trees, and an empty tree's zeros."""
+    from paper_2311_09445_amd.per import OP_SAMPLE, OP_UPDATE
+    log(f"on-chip row shares fb={fb} B={B}")
+    N, T, steps = 90, 2, 3
+    p, q, empty = (PrioritizedReplay(16, N, T, fb) for _ in range(3))
+    g = torch.Generator(device="cuda")
+    g.manual_seed(sum(fb) + B)
+    stored = [torch.randint(0, 256, (T, N, b), generator=g, device="cuda", dtype=torch.uint8) for b in fb]
+    prio = torch.rand((T, N), generator=g, device="cuda")
+    for x, v in ((p, prio), (q, prio), (empty, torch.zeros_like(prio))):
+        x.insert(N, stored, v)
+    u, up = (torch.rand((steps, T, B), generator=g, device="cuda") for _ in range(2))
+    outs = lambda: (torch.zeros((steps, T, B), dtype=torch.int32, device="cuda"),   # noqa: E731
+                    [torch.full((steps, T, B, b), 7, dtype=torch.uint8, device="cuda") for b in fb])
+    idx, rows = outs()
+    p.run_steps(u, torch.full((steps,), 0.5, device="cuda"), idx, None, None, rows, upd_prio=up)
+    idx_q, rows_q = outs()
+    queue = []
+    for s in range(steps):
+        queue += [{"op": OP_SAMPLE, "u": u[s], "beta": 0.5, "idx": idx_q[s], "rows": [r[s] for r in rows_q]}, {"op": OP_UPDATE, "prio": up[s]}]
+    keep = q.run_requests(queue)
+    assert torch.equal(idx, idx_q)
+    for f in range(len(fb)):
+        for s in range(steps):
+            for t in range(T):
+                want = stored[f][t][idx[s, t].long()]
+                assert torch.equal(rows[f][s, t], want), f"list, field {f}, step {s}, tree {t}"
+                assert torch.equal(rows_q[f][s, t], want), f"queue, field {f}, step {s}, tree {t}"
+    idx, rows = outs()
+    empty.run_steps(u, torch.full((steps,), 0.5, device="cuda"), idx, None, None, rows)
+    assert bool((idx == -1).all()) and all(not bool(r.any()) for r in rows)
+    assert empty.status() == FLAG_ZERO_TOTAL | FLAG_BAD_INDEX
+    del keep
+
+
 def test_run_requests_argument_checks():
     from paper_2311_09445_amd.per import OP_SAMPLE, OP_UPDATE
     big = PrioritizedReplay(16, 1 << 20)
