@@ -1852,31 +1852,69 @@ static uint32_t plan_stream_levels(const Geom& g, uint32_t* off, uint32_t* level
   return 0u;
 }
 
+// Waves of the team (where it is not all of them).
+static uint32_t team_waves(uint32_t samples, uint32_t inserted) { return ((samples > inserted ? samples : inserted) + 63u) / 64u; }
+// Items that n rows are moved in, of every access width (see fill_piece_fields); returns all of them.
+static uint64_t items_by_width(const FieldTable& ft, uint32_t n, uint64_t (&of_kind)[kWidths]) {
+  uint64_t total = 0;
+  for (uint64_t& k : of_kind) k = 0;
+  for (uint32_t f = 0; f < ft.n_fields; ++f) {
+    if (!ft.io[f]) continue;
+    const uint32_t w = moves_wide(ft.bytes[f], ft.vec[f]) ? 16u : ft.vec[f];
+    const uint64_t items = ((uint64_t)n * row_elements(ft.bytes[f], ft.vec[f]) + 63u) / 64u;
+    of_kind[4 - __builtin_ctz(w)] += items;
+    total += items;
+  }
+  return total;
+}
+// Whether a gather of n rows can be shared out in runs among rws row waves (see fill_piece_fields).
+static bool gathers_in_runs(const FieldTable& ft, uint32_t n, uint32_t rws) {
+  uint64_t of_kind[kWidths];
+  (void)items_by_width(ft, n, of_kind);
+  for (uint32_t len = 1; len <= kInFlight; ++len) {
+    uint64_t needed = 0;
+    for (int c = 0; c < kWidths; ++c) needed += (of_kind[c] + len - 1) / len;
+    if (needed <= run_waves(n, rws)) return true;
+  }
+  return false;
+}
+
 // Whether one step (with n_insert new rows, or none) is faster as one launch of the kernel above than as the two or three
-// kernels it otherwise takes.  Both sides in hundredths of a microsecond, fitted to 289 shapes (1 to 64 trees of 1000 to
-// 400 000 leaves, 16 to 512 samples, 0 to 256 new rows of 25 to 1033 bytes; the fits are off by 8 and 9 %).  On the chip: the
-// launch and one step's chain, more with several waves at the tree; the rows, which one compute unit moves; the copy
-// of the tree, with a trip to memory for the leaves where they stay there, and the heights between the levels.  As
-// kernels: two launches, or the sampling kernel with the insertion in it (12.3 us), or three (no K = 2 tree's is carried, and
-// those are chains of many heights).  Of the shapes 165 go this way, 1.30 times as fast on average (4096 leaves at K = 2, 64
-// samples, 4 rows: 19.5 -> 9.8 us); of those 5 are slower, by 7 % at most, before batches beyond 256 were left out.
+// kernels it otherwise takes.  Both sides in hundredths of a microsecond, fitted to 639 shapes (1 to 64 trees of 300 to
+// 400 000 leaves, 16 to 512 samples, 0 to 400 new rows of 0 to 1033 bytes in fields of every access width; the fits are off
+// by 7 and 10 %).  On the chip: the launch and one step's chain, more with several waves at the tree; the rows, which one
+// compute unit moves, by the pieces that every row wave has (in runs each piece is the rest of a trip to memory, evenly
+// shared ones go eight to a trip; a new row's pieces one to a trip); the copy of the tree, the trips to leaves in memory
+// and the heights between the levels.  As kernels: two launches, with the insertion in the sampling kernel where that can
+// carry it, else three; K = 2 trees are chains of many heights.  Of the shapes 413 go this way, 1.37 times as fast on
+// average (4096 leaves at K = 2, 64 samples, 4 rows of 41 bytes: 19.1 -> 9.0 us); 8 of those are slower by 2 % or more, by 15 %
+// at most (the 3 % below: without them 11, for 16 shapes more).  By the bytes of a row alone, 45 were, and by up to 4.5 times:
+// 256 samples of a 165-byte field on 4096 leaves at K = 2 71 us against 22.  Batches beyond 256 at K > 2 are left out: what
+// there is to gain is less than the fits are off by.
 template <int LOGK>
-static bool step_on_chip_pays_k(const Geom& g, uint32_t n_insert, uint32_t B, const FieldTable& rows, const FieldTable& ins) {
+static bool step_on_chip_pays_k(const Geom& g, const Tuning& tn, uint32_t n_insert, uint32_t B, const FieldTable& rows, const FieldTable& ins) {
   uint32_t off[kStreamLevels + 2], levels = 0, in_memory = 0;
   const uint64_t floats = plan_stream_levels<LOGK>(g, off, &levels, &in_memory);
   if (!floats || g.T > 64 || (B > 256 && g.K > 2)) return false;
-  uint64_t heights = 0, row = 0, new_row = 0;
+  uint64_t heights = 0, row = 0, of_kind[kWidths];
   for (uint32_t h = in_memory; h <= g.H; ++h) heights += g.n[h];
   for (uint32_t f = 0; f < rows.n_fields; ++f) row += rows.io[f] ? rows.bytes[f] : 0u;
-  for (uint32_t f = 0; f < ins.n_fields; ++f) new_row += ins.io[f] ? ins.bytes[f] : 0u;
-  const uint64_t here = 830 + (team_form(B, n_insert) == TEAM_ONE_WAVE ? 0 : 180) + B * row * 9 / 1024 + n_insert * new_row * 4 / 1024 +
-                        floats * 5 / 1024 + (in_memory ? 100 : 0) + (heights > floats ? (heights - floats) * 18 / 1024 : 0);
-  const uint64_t apart = g.K == 2 ? (n_insert ? 1800 : 1200)
-                                  : (n_insert ? 1230 : 960) + (g.K >= 32 ? 120 : 0) + (g.T >= 16 ? 100 : 0);
-  return here < apart;
+  const uint32_t rws = 16u - team_waves(B, n_insert);
+  const uint64_t gathered = items_by_width(rows, B, of_kind), placed = items_by_width(ins, n_insert, of_kind);
+  int64_t here = 700 + (team_form(B, n_insert) == TEAM_ONE_WAVE ? 0 : 138) + (n_insert ? 55 : 0) + (g.T >= 16 ? 71 : 0) + (g.K == 64 ? 37 * B / 64 : 0);
+  here += gathers_in_runs(rows, B, rws) ? 80 * gathered / rws : 136 + 19 * gathered / rws;
+  here += (placed > rws ? 81 * (placed - rws) / rws : 0) + floats * 4 / 1024 + (in_memory ? 58 + 63 * B / 64 : 0);
+  here += heights > floats ? (heights - floats) * 13 / 1024 : 0;
+  bool has_rows = false;
+  for (uint32_t f = 0; f < ins.n_fields; ++f) has_rows = has_rows || ins.io[f];
+  // (asked as for a ring at its start: the way does not change in the one step whose rows go round its end)
+  const bool carried = n_insert && sample_can_carry_insert(g, tn, B, has_rows ? &ins : nullptr, n_insert, 0);
+  int64_t apart = 938 + (!n_insert ? 0 : carried ? 273 : 374 + (g.K <= 4 ? 141 : 0)) + (g.K == 2 ? 106 * (int64_t)g.H - 815 : 0);
+  apart += (g.K == 4 ? 87 : 0) + (g.K >= 32 ? 55 : 0) + (g.T >= 16 ? 105 : 0) + (int64_t)(176 * g.T * B * row >> 20);
+  return here * 103 < apart * 100;
 }
-bool step_on_chip_pays(const Geom& g, uint32_t n_insert, uint32_t B, const FieldTable& rows, const FieldTable& ins) {
-#define CALL(L) step_on_chip_pays_k<L>(g, n_insert, B, rows, ins)
+bool step_on_chip_pays(const Geom& g, const Tuning& tn, uint32_t n_insert, uint32_t B, const FieldTable& rows, const FieldTable& ins) {
+#define CALL(L) step_on_chip_pays_k<L>(g, tn, n_insert, B, rows, ins)
   switch (g.logK) {
     case 1: return CALL(1);
     case 2: return CALL(2);
@@ -1887,24 +1925,6 @@ bool step_on_chip_pays(const Geom& g, uint32_t n_insert, uint32_t B, const Field
     default: return false;
   }
 #undef CALL
-}
-
-// Waves of the team (where it is not all of them).
-static uint32_t team_waves(uint32_t samples, uint32_t inserted) { return ((samples > inserted ? samples : inserted) + 63u) / 64u; }
-// Whether a gather of n rows can be shared out in runs among rws row waves (see fill_piece_fields).
-static bool gathers_in_runs(const FieldTable& ft, uint32_t n, uint32_t rws) {
-  uint64_t of_kind[kWidths] = {};
-  for (uint32_t f = 0; f < ft.n_fields; ++f) {
-    if (!ft.io[f]) continue;
-    const uint32_t w = moves_wide(ft.bytes[f], ft.vec[f]) ? 16u : ft.vec[f];
-    of_kind[4 - __builtin_ctz(w)] += ((uint64_t)n * row_elements(ft.bytes[f], ft.vec[f]) + 63u) / 64u;
-  }
-  for (uint32_t len = 1; len <= kInFlight; ++len) {
-    uint64_t needed = 0;
-    for (int c = 0; c < kWidths; ++c) needed += (of_kind[c] + len - 1) / len;
-    if (needed <= run_waves(n, rws)) return true;
-  }
-  return false;
 }
 
 template <int LOGK>

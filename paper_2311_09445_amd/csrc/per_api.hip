@@ -643,7 +643,7 @@ static bool step_on_chip(per_t* p, uint32_t n, const void* const* d_field_src, c
   StreamArgs a{};
   (void)fill_fields(p, d_field_dst, &a.rows);
   if (n) (void)fill_fields(p, const_cast<void* const*>(reinterpret_cast<const void* const*>(d_field_src)), &a.ins);
-  if (!forced && !step_on_chip_pays(p->g, n, B, a.rows, a.ins)) return false;
+  if (!forced && !step_on_chip_pays(p->g, p->tn, n, B, a.rows, a.ins)) return false;
   Span in[3 + PER_MAX_FIELDS], out[4 + PER_MAX_FIELDS];
   uint32_t ni = 0, no = 0;
   const uint64_t samples = (uint64_t)p->g.T * B, rows = (uint64_t)p->g.T * n;

@@ -298,7 +298,7 @@ size_t step_table_bytes();
 void* step_static_claim(const void* holder, int device, hipStream_t s);
 void step_static_release(const void* holder, int device);
 bool stream_tree_fits(const Geom& g);
-bool step_on_chip_pays(const Geom& g, uint32_t n_insert, uint32_t B, const FieldTable& rows, const FieldTable& ins);
+bool step_on_chip_pays(const Geom& g, const Tuning& tn, uint32_t n_insert, uint32_t B, const FieldTable& rows, const FieldTable& ins);
 hipError_t launch_run_steps(const Geom& g, const Tuning& tn, const StreamArgs& a, hipStream_t s);
 hipError_t launch_run_requests(const Geom& g, const Tuning& tn, const QueueArgs& a, hipStream_t s);
 hipError_t launch_get_priority(const Geom& g, const Tuning& tn, uint32_t n, const uint32_t* idx, float* out, hipStream_t s);

@@ -743,6 +743,34 @@ def test_steps_on_the_chip(K, N, T, B, n, fb):
     m.compare_status()
 
 
+# (whether one launch on an LDS copy is the way a step goes by default: shapes well on either side of the rule's line)
+STEP_WAYS = [(2, 4096, 1, 64, 4, (16, 4, 4, 16, 1), True), (16, 10000, 1, 32, 0, (), True), (16, 900, 1, 64, 4, (16, 4, 4, 16, 1), True),
+             (4, 9000, 1, 40, 16, (12,), True), (64, 5000, 1, 32, 4, (16,), True), (16, 10000, 1, 300, 4, (16,), False),
+             (2, 4096, 1, 256, 64, (165,), False), (16, 10000, 1, 128, 64, (63,), False), (8, 5000, 64, 64, 0, (1033,), False), (16, 10000, 65, 32, 4, (), False)]
+
+
+@pytest.mark.parametrize("K,N,T,B,n,fb,chip", STEP_WAYS)
+def test_way_that_a_step_goes(claim_form, K, N, T, B, n, fb, chip):
+    """Steps by the default rule: which kernels they launch, and their results; narrow fields go by the pieces they are moved in."""
+    if claim_form != "group":
+        pytest.skip("the rule stands aside where the kernels are chosen by hand")
+    log(f"way of a step K={K} N={N} T={T} B={B} n={n} fb={fb}")
+    rng = np.random.default_rng(K + N + B)
+    m = Mirror(K, N, T, fb)
+    m.insert(N, prio=wl._draw_priorities("exponential_1", rng, (T, N)))
+    step = lambda: (m.insert_step_call(n, None, wl.uniform01(rng, (T, B)), 0.4, True, wl._draw_updates("absnormal1_eps_pow0.6", rng, (T, B)))  # noqa: E731
+                    if n else m.step_call(wl.uniform01(rng, (T, B)), 0.4, True, wl._draw_updates("absnormal1_eps_pow0.6", rng, (T, B)), None))
+    step()   # (the first may find the tree's top stale)
+    m.gpu.profile(True)
+    step()
+    step()
+    launched = kernel_launches(m)
+    m.gpu.profile(False)
+    assert (launched.get("k_run_steps") == 2 and len(launched) <= 2) if chip else "k_run_steps" not in launched, launched
+    m.compare_tree()
+    m.compare_status()
+
+
 def test_steps_on_the_chip_draw_and_replay_as_the_kernels_do():
     """The library's own uniforms, results that lie over inputs (the usual way is taken), an empty tree, and replays of a
     captured step between eager calls: the same as with the kernels."""
