@@ -210,7 +210,10 @@ int per_update_td(per_t* p, uint32_t B, const uint32_t* d_idx /*[T][B]*/, const 
  * exact pairwise sum of its children; per_update restores that for the paths it touches.
  * Duplicated indices add up.  The running maximum priority is not touched (the call never sees a
  * priority).  Valid means d_idx < size and d_delta finite; other elements are skipped and flagged
- * (BAD_INDEX, BAD_PRIORITY).  The caller keeps leaves non-negative. */
+ * (BAD_INDEX, BAD_PRIORITY).  The caller keeps leaves non-negative.
+ * per_run_steps and per_run_requests work on exact sums: on a tree that holds such changes they begin with per_rebuild.  (A
+ * graph of them, or of steps on a tree of their size, captured before the buffer's first per_update_delta does not: it takes
+ * the nodes as they are and puts some of them in order on the way.) */
 int per_update_delta(per_t* p, uint32_t B, const uint32_t* d_idx /*[T][B]*/, const float* d_delta /*[T][B]*/,
                      void* stream);
 

@@ -10,6 +10,14 @@
 
 using namespace per;
 
+// Is every node the pairwise sum of its children?  The on-chip kernels take it for granted: their copy leaves out the heights
+// between its levels, and a walk that does not look for empty blocks relies on a node of zero holding nothing else.
+enum NodeSums {
+  SUMS_WHOLE,
+  SUMS_UNKNOWN,   // a restored arena: put in order (per_rebuild) before the first on-chip launch
+  SUMS_ROUNDED    // per_update_delta has added to the nodes: likewise for a list or a queue; a step takes the other kernels
+};
+
 struct per_buffer {
   per_config cfg;
   Geom g;
@@ -24,6 +32,9 @@ struct per_buffer {
   int weight_norm;           // PER_NORM_BATCH or PER_NORM_BUFFER
   bool min_stale;            // min1 does not describe the leaves (it is rebuilt when next needed)
   uint32_t stale_hb;         // != 0: the last update left the heights above this one to their next reader
+  NodeSums sums;
+  NodeSums sums_eager;       // as the calls outside captures have left it
+  bool delta_captured;       // a graph may add changes to the nodes whenever it is replayed
   bool step_before;          // the latest call that changed the tree was a step (see step_on_chip)
   bool tables_valid;         // the per-owner tables of the one-kernel step describe the tree as it is
   unsigned long long capture_id;   // the stream capture the last call was recorded into (0: it ran eagerly)
@@ -199,7 +210,21 @@ void forget_device_notes(per_t* p) {
   if (hb) p->stale_hb = hb;
   p->min_stale = true;
   p->tables_valid = false;
+  p->sums = p->delta_captured ? SUMS_ROUNDED : p->sums_eager;
 }
+// Every height from the leaves up.
+hipError_t rebuild_heights(per_t* p, hipStream_t s) {
+  p->tables_valid = false;
+  hipError_t e = launch_resum_ranges(p->g, p->tn, Range2{0, p->g.N, 0, 0}, s);
+  if (e == hipSuccess) {
+    p->stale_hb = 0;
+    p->sums = SUMS_WHOLE;
+    if (!p->capture_id) p->sums_eager = SUMS_WHOLE;
+  }
+  return e;
+}
+// Before an on-chip launch, which loads whole heights from memory: the topmost heights are current, and sums of their children.
+hipError_t ensure_sums(per_t* p, hipStream_t s) { return p->sums == SUMS_WHOLE ? ensure_top(p, s) : rebuild_heights(p, s); }
 // Before a tree pass: the heights it does not rewrite in full (up to its workgroup roots) must not be stale below
 // those roots.
 hipError_t prepare_tree_pass(per_t* p, hipStream_t s) {
@@ -343,6 +368,8 @@ int per_create(const per_config* cfg, void* d_arena, size_t arena_bytes, void* s
   p->tn.prof = &p->prof;
   p->claims_left = false;
   p->tables_valid = false;
+  p->sums = p->sums_eager = SUMS_WHOLE;
+  p->delta_captured = false;
   p->capture_id = 0;
   p->weight_norm = PER_NORM_BATCH;
   p->min_stale = true;
@@ -662,6 +689,7 @@ static bool step_on_chip(per_t* p, uint32_t n, const void* const* d_field_src, c
     if (spans_meet(out + i, 1, in, ni) || spans_meet(out + i, 1, out + i + 1, no - i - 1)) return false;
   hipStream_t s = static_cast<hipStream_t>(stream);
   CaptureGuard capture(p, s);
+  if (p->sums == SUMS_ROUNDED) return false;   // (the draws and sums of the other kernels, which go by every stored node)
   // The kernel loads whole heights from memory.  Heights that another call has left stale cost a launch to bring in order
   // first, which the usual way does on its way: worth it once, where steps follow steps, not where such calls and steps
   // take turns.
@@ -694,7 +722,7 @@ static bool step_on_chip(per_t* p, uint32_t n, const void* const* d_field_src, c
   a.ins_slots = d_ins_out_idx;
   p->min_stale = true;   // (as per_run_steps)
   p->tables_valid = false;
-  hipError_t e = ensure_top(p, s);
+  hipError_t e = ensure_sums(p, s);
   if (e == hipSuccess) e = launch_run_steps(p->g, p->tn, a, s);
   const uint64_t N = p->cfg.capacity;
   p->cursor = (p->cursor + n) % N;
@@ -848,6 +876,9 @@ int per_update_delta(per_t* p, uint32_t B, const uint32_t* d_idx, const float* d
   hipStream_t s = static_cast<hipStream_t>(stream);
   CaptureGuard capture(p, s);
   p->min_stale = true;               // (changes added by atomics: min1 cannot follow them)
+  p->sums = SUMS_ROUNDED;
+  if (p->capture_id) p->delta_captured = true;
+  else p->sums_eager = SUMS_ROUNDED;
   p->tables_valid = false;
   hipError_t e = ensure_top(p, s);   // changes are added to whole nodes: the top heights must be current
   if (e == hipSuccess) e = launch_update_delta(p->g, p->tn, B, (uint32_t)p->size, d_idx, d_delta, s);
@@ -910,7 +941,7 @@ int per_run_steps(per_t* p, uint32_t n_steps, uint32_t n_insert, uint32_t B, con
   a.ins_prio = io->d_ins_prio;
   if (n_insert) (void)fill_fields(p, const_cast<void* const*>(reinterpret_cast<const void* const*>(io->d_ins_rows)), &a.ins);
   (void)fill_fields(p, io->d_rows_out, &a.rows);
-  hipError_t e = ensure_top(p, s);   // the kernel loads whole heights from memory
+  hipError_t e = ensure_sums(p, s);
   if (e == hipSuccess) e = launch_run_steps(p->g, p->tn, a, s);
   const uint64_t N = p->cfg.capacity, added = (uint64_t)n_steps * n_insert;
   p->cursor = (p->cursor + added) % N;
@@ -999,7 +1030,7 @@ int per_run_requests(per_t* p, uint32_t n_requests, const per_request* h_request
   a.cursor = (uint32_t)p->cursor;
   a.size = (uint32_t)p->size;
   a.queue = d_requests;
-  hipError_t e = ensure_top(p, s);   // the kernel loads whole heights from memory
+  hipError_t e = ensure_sums(p, s);
   if (e == hipSuccess) e = launch_run_requests(p->g, p->tn, a, s);
   p->cursor = cursor;
   p->size = size;
@@ -1010,12 +1041,7 @@ int per_rebuild(per_t* p, void* stream) {
   if (!p) return PER_EINVAL;
   hipStream_t s = static_cast<hipStream_t>(stream);
   CaptureGuard capture(p, s);
-  p->tables_valid = false;
-  // all leaves count as touched: every height is recomputed in full, bottom-up
-  hipError_t e = launch_resum_ranges(p->g, p->tn, Range2{0, p->g.N, 0, 0}, s);
-  if (e != hipSuccess) return PER_EHIP;
-  p->stale_hb = 0;
-  return PER_OK;
+  return hip_rc(rebuild_heights(p, s));   // all leaves count as touched: every height is recomputed in full, bottom-up
 }
 
 int per_get_priority(per_t* p, uint32_t n, const uint32_t* d_idx, float* d_out, void* stream) {
@@ -1080,6 +1106,8 @@ int per_set_ring(per_t* p, uint64_t cursor, uint64_t size) {
   p->cursor = cursor;
   p->size = size;
   p->stale_hb = lazy_top_height(p->g, p->tn);   // a saved arena may predate the rebuild of its top heights
+  if (p->sums_eager == SUMS_WHOLE) p->sums_eager = SUMS_UNKNOWN;
+  if (p->sums == SUMS_WHOLE) p->sums = SUMS_UNKNOWN;
   p->min_stale = true;
   p->tables_valid = false;
   return PER_OK;

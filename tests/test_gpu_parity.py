@@ -856,6 +856,89 @@ def test_levels_of_the_on_chip_tree(K, N, B):
     m.compare_status()
 
 
+def add_changes(p, rng, n):
+    """n calls of one change each (whose result does not depend on an order), large ones added and taken back: inner nodes that are the
+    sums of their children only up to what those leave behind."""
+    for _ in range(n // 2):
+        i = np.array([[int(rng.integers(0, p.size))] for _ in range(p.T)], np.uint32)
+        d = np.array([[float(rng.integers(1, 9)) * 10.0 ** int(rng.integers(0, 6))] for _ in range(p.T)], np.float32)
+        p.update_delta(idx_to_dev(i), dev(d))
+        p.update_delta(idx_to_dev(i), dev(-d))
+
+
+@pytest.mark.parametrize("K,N,T", [(2, 3000, 1), (4, 20000, 2), (16, 9000, 1), (2, 30000, 1), (64, 4000, 1)])
+def test_on_chip_calls_after_changes_added(claim_form, K, N, T):
+    """Trees that hold changes of per_update_delta: a step is the separate kernels', also as a graph replayed; a list and a queue are
+    those on the same tree put in order, and so is a step on a restored arena."""
+    from paper_2311_09445_amd.per import OP_SAMPLE, OP_UPDATE
+    log(f"on-chip after changes added K={K} N={N} T={T}")
+    rng = np.random.default_rng(K + N)
+    B, steps = 60, 4
+    prio = dev(wl._draw_priorities("exponential_1", rng, (T, N)))
+
+    def made(**tuning):
+        p = PrioritizedReplay(K, N, T, (4,))
+        for name, value in tuning.items():
+            p.set_tuning(name, value)
+        p.insert(N, None, prio)
+        return p
+
+    levels = lambda p: [p.read_level(t, h).cpu().numpy().tobytes() for t in range(T) for h in range(p.H + 1)]   # noqa: E731
+    u, up = (torch.from_numpy(rng.random((steps, T, B)).astype(np.float32)).cuda() for _ in range(2))
+    seed = int(rng.integers(1 << 30))
+    off = {"step_on_chip": 0}
+    results = []
+    for tuning in ({}, off):                                  # a step, then as a graph with further changes between its replays
+        p, r, out = made(**tuning), np.random.default_rng(seed), []
+        add_changes(p, r, 60)
+        for s in range(steps):
+            out += [x.cpu().numpy().tobytes() for x in p.step(u[s], 0.5, up[s])]
+        out += levels(p)
+        got = [torch.empty((T, B), dtype=d, device="cuda") for d in (torch.int32, torch.float32, torch.float32)]
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            p.step(u[0], 0.5, up[0], out_idx=got[0], out_weight=got[1], out_prio=got[2])
+        for s in range(3):
+            add_changes(p, r, 20)
+            graph.replay()
+            p.note_replay()
+            out += [x.cpu().numpy().tobytes() for x in got] + levels(p)
+        results.append(out)
+    assert results[0] == results[1]
+    changed = made()
+    add_changes(changed, np.random.default_rng(seed), 60)
+    loose = levels(changed)
+    changed.rebuild()
+    assert levels(changed) != loose                           # (the changes have left something behind)
+    for form in ("steps", "queue", "restored"):
+        results = []
+        for whole in (False, True):
+            p = made(**(off if form == "restored" and whole else {}))
+            add_changes(p, np.random.default_rng(seed), 60)
+            if whole:
+                p.rebuild()
+            idx = torch.empty((steps, T, B), dtype=torch.int32, device="cuda")
+            if form == "steps":
+                p.run_steps(u, torch.full((steps,), 0.5, device="cuda"), idx, upd_prio=up)
+            elif form == "queue":
+                keep = p.run_requests([q for s in range(steps) for q in ({"op": OP_SAMPLE, "u": u[s], "beta": 0.5, "idx": idx[s]},
+                                                                         {"op": OP_UPDATE, "prio": up[s]})])
+            else:
+                if not whole:                                 # (the arena's nodes as the changes have left them)
+                    fresh = PrioritizedReplay(K, N, T, (4,))
+                    fresh.set_tuning("step_on_chip", 2)
+                    fresh.arena.copy_(p.arena)
+                    fresh.set_ring(p.cursor, p.size)
+                    p = fresh
+                for s in range(steps):
+                    p.step(u[s], 0.5, up[s], out_idx=idx[s])
+            results.append([idx.cpu().numpy().tobytes()] + levels(p))
+        assert results[0] == results[1], form
+        keep = None
+    del keep
+
+
 @pytest.mark.parametrize("K,N,T,B,fb", [(16, 3000, 2, 32, (16, 4, 4, 16, 1)), (2, 3000, 1, 64, (12,)), (16, 30000, 1, 300, (68, 24, 4, 68, 1)),
                                         (8, 5000, 3, 65, ()), (4, 9000, 1, 700, (16, 1)), (16, 100000, 1, 64, (5,)), (32, 300000, 2, 513, (8, 4))])
 @pytest.mark.parametrize("what", ["late", "own"])
