@@ -35,7 +35,7 @@ struct per_buffer {
   NodeSums sums;
   NodeSums sums_eager;       // as the calls outside captures have left it
   bool delta_captured;       // a graph may add changes to the nodes whenever it is replayed
-  bool step_before;          // the latest call that changed the tree was a step (see step_on_chip)
+  bool step_before;          // the latest call that changed the tree was a step that could have been one launch (see step_on_chip)
   bool tables_valid;         // the per-owner tables of the one-kernel step describe the tree as it is
   unsigned long long capture_id;   // the stream capture the last call was recorded into (0: it ran eagerly)
   bool rng_on;               // per_set_rng was called: sampling calls without uniforms draw their own
@@ -461,13 +461,13 @@ static int insert_impl(per_t* p, uint32_t n, const void* const* d_field_src, con
 
 int per_insert(per_t* p, uint32_t n, const void* const* d_field_src, const float* d_prio, uint32_t* d_out_idx,
                void* stream) {
-  if (p) p->step_before = false;
+  if (p && n) p->step_before = false;
   return insert_impl(p, n, d_field_src, d_prio, d_out_idx, 0, nullptr, stream);
 }
 
 int per_insert_protected(per_t* p, uint32_t n, const void* const* d_field_src, const float* d_prio, uint32_t* d_out_idx,
                          uint32_t n_protect, const uint32_t* d_protect_idx, void* stream) {
-  if (p) p->step_before = false;
+  if (p && n) p->step_before = false;
   return insert_impl(p, n, d_field_src, d_prio, d_out_idx, n_protect, d_protect_idx, stream);
 }
 
@@ -656,6 +656,8 @@ static bool spans_meet(const Span* a, uint32_t na, const Span* b, uint32_t nb) {
 static bool step_on_chip(per_t* p, uint32_t n, const void* const* d_field_src, const float* d_ins_prio, uint32_t* d_ins_out_idx, uint32_t B,
                          float beta, const float* d_u, uint32_t* d_out_idx, float* d_out_weight, float* d_out_prio,
                          void* const* d_field_dst, const float* d_upd_prio, const uint32_t* d_upd_pos, void* stream, int* rc) {
+  const bool after_step = p->step_before;
+  p->step_before = false;
   // (whoever chooses by hand how the kernels below work means those kernels)
   const bool forced = p->tn.step_on_chip == 2;
   const bool by_hand = p->tn.step_kernel != 1 || !p->tn.group_claim || !p->tn.claim_in_sample || !p->tn.insert_ride || !p->tn.lazy_top;
@@ -691,12 +693,10 @@ static bool step_on_chip(per_t* p, uint32_t n, const void* const* d_field_src, c
   CaptureGuard capture(p, s);
   if (p->sums == SUMS_ROUNDED) return false;   // (the draws and sums of the other kernels, which go by every stored node)
   // The kernel loads whole heights from memory.  Heights that another call has left stale cost a launch to bring in order
-  // first, which the usual way does on its way: worth it once, where steps follow steps, not where such calls and steps
-  // take turns.
-  if (!forced && p->stale_hb && !p->step_before) {
-    p->step_before = true;
-    return false;
-  }
+  // first, which the usual way does on its way: worth it once, where steps follow steps, not where such calls (steps that go
+  // the usual way for another reason among them) and steps take turns.
+  p->step_before = true;
+  if (!forced && p->stale_hb && !after_step) return false;
   a.n_steps = 1;
   a.n_insert = n;
   a.B = B;
@@ -849,8 +849,8 @@ int per_update_td(per_t* p, uint32_t B, const uint32_t* d_idx, const float* d_td
                   void* stream) {
   int rc = check_update_args(p, B, d_idx, d_td);
   if (rc != PER_OK || B == 0) return rc;
-  p->step_before = false;
   if (!(eps >= 0.0) || !isfinite(eps) || !(alpha >= 0.0) || !isfinite(alpha)) return PER_EINVAL;
+  p->step_before = false;
   hipStream_t s = static_cast<hipStream_t>(stream);
   CaptureGuard capture(p, s);
   if (prepare_tree_pass(p, s) != hipSuccess) return PER_EHIP;

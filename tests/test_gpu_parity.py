@@ -771,6 +771,42 @@ def test_way_that_a_step_goes(claim_form, K, N, T, B, n, fb, chip):
     m.compare_status()
 
 
+@pytest.mark.parametrize("between", ["nothing", "update", "insert", "position map", "no chip size"])
+def test_steps_and_calls_that_leave_the_top_stale(claim_form, between):
+    """A step behind a call that has left the tree's top to its next reader goes by the kernels, the next ones as one launch; where
+    such calls and steps take turns all steps go by the kernels, and no launch brings the top in order before them."""
+    if claim_form != "group":
+        pytest.skip("the rule stands aside where the kernels are chosen by hand")
+    log(f"steps and stale tops: {between}")
+    rng = np.random.default_rng(3)
+    K, N, B = 16, 10000, 32
+    m = Mirror(K, N, 1, ())
+    m.insert(N, prio=wl._draw_priorities("exponential_1", rng, (1, N)))
+
+    def step(pos=None, size=B):
+        m.step_call(wl.uniform01(rng, (1, size)), 0.4, True, wl._draw_updates("absnormal1_eps_pow0.6", rng, (1, size)), pos)
+
+    calls = {"nothing": lambda: None,
+             "update": lambda: m.update(rng.integers(0, N, (1, 50)).astype(np.uint32), rng.random((1, 50)).astype(np.float32)),
+             "insert": lambda: m.insert(8, prio=rng.random((1, 8)).astype(np.float32)),
+             "position map": lambda: step(rng.integers(0, B, (1, B)).astype(np.uint32)), "no chip size": lambda: step(size=300)}
+    for _ in range(2):
+        calls[between]()
+        step()
+    m.gpu.profile(True)
+    for _ in range(4):
+        calls[between]()
+        step()
+    launched = kernel_launches(m)
+    assert launched.get("k_run_steps", 0) == (4 if between == "nothing" else 0) and "k_resum_tail" not in launched, launched
+    step()
+    step()
+    assert kernel_launches(m)["k_run_steps"] == launched.get("k_run_steps", 0) + 2
+    m.gpu.profile(False)
+    m.compare_tree()
+    m.compare_status()
+
+
 def test_steps_on_the_chip_draw_and_replay_as_the_kernels_do():
     """The library's own uniforms, results that lie over inputs (the usual way is taken), an empty tree, and replays of a
     captured step between eager calls: the same as with the kernels."""
