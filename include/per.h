@@ -345,10 +345,10 @@ int per_set_ring(per_t* p, uint64_t cursor, uint64_t size);
  * Here the companion structure is the smallest positive leaf under every height-1 node, renewed by
  * per_update, the fused step and insertions for the nodes they touch while this mode is on, rebuilt
  * from the leaves after calls that cannot (the one-kernel form of per_step, per_update_delta, per_run_steps,
- * per_run_requests, per_set_ring), and reduced to one value per tree by extra workgroups of every sampling
- * kernel whose call returns weights (by a kernel of its own in front of the one-kernel form of per_step and for
- * per_min_priority).  per_run_steps and per_run_requests sweep the leaves (their LDS copy,
- * or memory) instead.  The mode applies to the calls made after it is set.
+ * per_run_requests, per_set_ring; a step goes as one on-chip launch only where it is not current anyway), and reduced
+ * to one value per tree by extra workgroups of every sampling kernel whose call returns weights (by a kernel of its own
+ * in front of the one-kernel form of per_step and for per_min_priority).  per_run_steps and per_run_requests sweep the
+ * leaves (their LDS copy, or memory) instead.  The mode applies to the calls made after it is set.
  * per_min_priority: d_out[t] = smallest positive leaf of tree t (+infinity if there is none). */
 #define PER_NORM_BATCH  0
 #define PER_NORM_BUFFER 1

@@ -691,6 +691,7 @@ static bool step_on_chip(per_t* p, uint32_t n, const void* const* d_field_src, c
     if (spans_meet(out + i, 1, in, ni) || spans_meet(out + i, 1, out + i + 1, no - i - 1)) return false;
   hipStream_t s = static_cast<hipStream_t>(stream);
   CaptureGuard capture(p, s);
+  if (!forced && tracks_min(p)) return false;   // (the kernels keep the tree's minimum; made anew it is a pass over all leaves)
   if (p->sums == SUMS_ROUNDED) return false;   // (the draws and sums of the other kernels, which go by every stored node)
   // The kernel loads whole heights from memory.  Heights that another call has left stale cost a launch to bring in order
   // first, which the usual way does on its way: worth it once, where steps follow steps, not where such calls (steps that go

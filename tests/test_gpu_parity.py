@@ -807,6 +807,31 @@ def test_steps_and_calls_that_leave_the_top_stale(claim_form, between):
     m.compare_status()
 
 
+def test_steps_without_weights_keep_the_tree_s_minimum(claim_form):
+    """Weights relative to the buffer, asked for by samples but not by the steps between them: the steps keep the minimum that the
+    samples use, where one launch on an LDS copy would leave it to be made anew from all leaves."""
+    if claim_form != "group":
+        pytest.skip("the rule stands aside where the kernels are chosen by hand")
+    rng = np.random.default_rng(8)
+    K, N, B = 16, 10000, 32
+    p, q = (PrioritizedReplay(K, N, 1, ()) for _ in range(2))
+    q.set_tuning("step_on_chip", 0)
+    prio, u, up = (dev(rng.random((1, n)).astype(np.float32)) for n in (N, B, B))
+    got = []
+    for x in (p, q):
+        x.set_weight_norm("buffer")
+        x.insert(N, None, prio)
+        x.sample(u, 0.5)
+        x.profile(True)
+        out = []
+        for _ in range(3):
+            out += [y.cpu().numpy().tobytes() for y in x.step(u, 0.5, up, want_weights=False) + x.sample(u, 0.5) if y is not None]
+        assert x.profile_read().get("k_min_rebuild", (0, 0))[1] == 0
+        x.profile(False)
+        got.append(out)
+    assert got[0] == got[1]
+
+
 def test_steps_on_the_chip_draw_and_replay_as_the_kernels_do():
     """The library's own uniforms, results that lie over inputs (the usual way is taken), an empty tree, and replays of a
     captured step between eager calls: the same as with the kernels."""
