@@ -192,7 +192,7 @@ enum GatherShares {
   SHARES_NONE,   // (an insertion)
   SHARES_RUNS,   // every wave has a run of at most kInFlight items of one access width: straight code, and all under way at once
   SHARES_EVEN,   // more than that, or a team that does the rows as well: equally many to every wave, see gather_spans
-  SHARES_ANY     // runs where that works, else evenly (a queue, whose requests differ: the first few of a wave's items are kept all the same)
+  SHARES_ANY     // runs where that works, else evenly (a queue, whose requests differ)
 };
 // Waves that gather in runs where n samples are weighed as well: those that do not weigh, if there are enough.
 __host__ __device__ __forceinline__ uint32_t run_waves(uint32_t n, uint32_t rws) {
@@ -208,6 +208,7 @@ struct PieceFields {               // what the waves ask of one list of fields, 
   uint32_t recip[kMaxFields];      // floor(2^32 / pieces per row) + 1
   uint32_t first[kMaxFields], end[kMaxFields];   // its items, all items ordered by width
   uint32_t items, n;               // all items; rows
+  uint32_t runs;                   // SHARES_ANY: the length of the runs, 0: shared out evenly
 };
 __device__ __forceinline__ uint32_t wave_value(uint32_t x) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)x); }   // (the same in all lanes)
 __device__ __forceinline__ uint64_t wave_value64(uint64_t x) {
@@ -263,6 +264,7 @@ __device__ __forceinline__ void fill_piece_fields(const FieldTable* ft, bool ask
     for (int c = 0; c < kWidths; ++c) needed += (min_u32(of_kind[c], 1023u) + lane) * recip >> 16;
     const unsigned long long enough = __ballot(needed <= waves && lane < kInFlight);
     run = enough ? 1u + (uint32_t)__builtin_ctzll(enough) : 0u;
+    if (SHARES == SHARES_ANY && f == 0) pf->runs = run;
   }
   if (lane < 16u) {
     uint32_t a = 0, b = 0;
@@ -381,11 +383,11 @@ struct GatherItems {
   const uint8_t* base;         // row 0 of the tree's payload
   uint32_t field[M];
   uint4 v[M];
-  // the items of one access width that items first .. last - 1 of a list begin with (at most M); `take` is called with every
-  // item's number here and the item
-  template <typename F>
+  // items first .. last - 1 (at most M) of a list, of one access width; MIXED: those of one width that they begin with.  `take`
+  // is called with every item's number here and the item
+  template <bool MIXED = false, typename F>
   __device__ __forceinline__ void prepare(const PieceFields& pf, uint32_t first, uint32_t last, F&& take) {
-    if constexpr (PACKED) {   // (the queue: others may be behind them, see SHARES_ANY)
+    if constexpr (MIXED) {
       if (first < last) {
         const uint32_t width = wave_value(pf.width[field_of_item(pf, first)]);
         uint32_t end = first;
@@ -1750,7 +1752,10 @@ k_run_requests(QueueKernelArgs ka) {
               // (this tree's place in the caller's arrays goes into the offsets of the pieces; where it is too far for those
               // the items are taken like those beyond the first few)
               bool far = false;
-              items.prepare(s_rows[par], share.x, share.y, [&](int k, const RowItem& p) {
+              // (a wave's evenly shared items: the first few are kept all the same, but for a team of one wave, whose build
+              // has no registers for that)
+              const bool none = WAVE && wave_value(s_rows[par].runs) == 0;
+              items.template prepare<!WAVE>(s_rows[par], share.x, none ? share.x : share.y, [&](int k, const RowItem& p) {
                 far = far || reinterpret_cast<uintptr_t>(p.io) > 0x7FFFFFFFull;
                 items.out[k] += (uint32_t)reinterpret_cast<uintptr_t>(p.io);
               });
