@@ -516,8 +516,8 @@ __device__ __forceinline__ void gather_span(uint32_t i, uint32_t end, uint32_t n
   }
 }
 // Items first .. last - 1 of a list, from beginning to end, a field at a time: what a field asks for is looked up once and the
-// code for its access width is straight.  What bounds it is the trip to memory per U items, and what the items' places
-// cost to work out.  Item by item, two at a time, with every lookup anew, a step on 10 000 leaves at K = 16 took 125 us with
+// code for its access width is straight.  What bounds it is the trip to memory per U items, and what it costs to work out
+// the items' places.  Item by item, two at a time, with every lookup anew, a step on 10 000 leaves at K = 16 took 125 us with
 // 512 rows of one 165-byte field (1320 items), 15.5 with 512 rows of 165 bytes in five fields, 11.0 with 513 of 41 bytes;
 // so it takes 30.7, 8.2 and 6.9.  (U = 8 where the registers allow it: 64 rows' worth of 16-byte pieces for each of eight waves
 // is one trip then, 6.6 -> 6.1 us a step on 100 000 leaves; looped and not unrolled over the items: the code a round goes
@@ -993,7 +993,9 @@ __device__ __forceinline__ uint32_t smallest_value(const float* values, uint32_t
 }
 
 // Who does the tree work: the first wave, the first few, or every wave, which then moves the rows as well.
-// (TEAM_WAVES_SPANS, of a list: where a step's gather is more than its row waves have under way at once)
+// (TEAM_WAVES_SPANS, of a list: where a step's gather is more than its row waves have under way at once.  Only as long as every
+// step is fetched ahead: else, with all results waited for in between, every wave at the rows is the faster way, 256 rows of
+// 165 bytes in five fields on 10 000 leaves at K = 16 6.0 us a step, 7.7 by the waves that are not the team's.)
 enum TeamForm { TEAM_ONE_WAVE, TEAM_WAVES, TEAM_WAVES_SPANS, TEAM_ALL };
 static TeamForm team_form(uint32_t samples, uint32_t inserted) {
   const uint32_t most = samples > inserted ? samples : inserted;
@@ -1943,7 +1945,7 @@ static hipError_t launch_run_steps_k(const Geom& g, const Tuning& tn, StreamArgs
   // always the largest workgroup, also for small batches: measured faster than a workgroup of the batch's
   // size (the tree copy and the row movers use all lanes)
   TeamForm form = team_form(a.B, a.n_insert);
-  if (form != TEAM_ALL && !gathers_in_runs(a.rows, a.B, 16u - team_waves(a.B, a.n_insert))) form = TEAM_WAVES_SPANS;
+  if (form != TEAM_ALL && !gathers_in_runs(a.rows, a.B, 16u - team_waves(a.B, a.n_insert))) form = a.ahead ? TEAM_WAVES_SPANS : TEAM_ALL;
   const bool mem = ka.a.leaves_in_memory != 0;
 #define PER_RUN(F, M, A)                                                                                \
   do {                                                                                                  \
@@ -1961,7 +1963,7 @@ static hipError_t launch_run_steps_k(const Geom& g, const Tuning& tn, StreamArgs
   } while (0)
   if (form == TEAM_ONE_WAVE) PER_RUN_WHEN(TEAM_ONE_WAVE);
   else if (form == TEAM_WAVES) PER_RUN_WHEN(TEAM_WAVES);
-  else if (form == TEAM_WAVES_SPANS) PER_RUN_WHEN(TEAM_WAVES_SPANS);
+  else if (form == TEAM_WAVES_SPANS) PER_RUN_WHERE(TEAM_WAVES_SPANS, true);
   else PER_RUN_WHEN(TEAM_ALL);
 #undef PER_RUN_WHEN
 #undef PER_RUN_WHERE
