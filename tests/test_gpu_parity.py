@@ -832,6 +832,68 @@ def test_steps_without_weights_keep_the_tree_s_minimum(claim_form):
     assert got[0] == got[1]
 
 
+def test_steps_that_cannot_be_one_launch():
+    """Where one launch on an LDS copy is asked for wherever it can be: it is taken, and not for position maps, weights relative to the
+    buffer, arrays that lie over one another, or more samples or rows than it takes."""
+    K, N, B, n = 16, 9000, 40, 5
+    p = PrioritizedReplay(K, N, 1, (8,))
+    p.set_tuning("step_on_chip", 2)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(2)
+    rand = lambda k: torch.rand((1, k), generator=g, device="cuda")   # noqa: E731
+    rows = lambda k: torch.randint(0, 256, (1, k, 8), generator=g, device="cuda", dtype=torch.uint8)   # noqa: E731
+    p.insert(N, [rows(N)], rand(N))
+    out, pos = rows(B), torch.arange(B, device="cuda", dtype=torch.int32)[None].contiguous()
+    slots = torch.zeros((1, n), dtype=torch.int32, device="cuda")
+    u = rand(B)
+    weights = torch.zeros((1, B), device="cuda")
+    calls = [("plain", True, lambda: p.step(u, 0.5, rand(B), rows_out=[out])),
+             ("new rows", True, lambda: p.step(u, 0.5, rand(B), rows_out=[out], insert=(n, [rows(n)], None, slots))),
+             ("most", True, lambda: p.step(rand(512), 0.5, rand(512), insert=(512, None, rand(512), None))),
+             ("position map", False, lambda: p.step(u, 0.5, rand(B), pos, rows_out=[out])),
+             ("more samples", False, lambda: p.step(rand(513), 0.5, rand(513))),
+             ("more rows", False, lambda: p.step(u, 0.5, rand(B), insert=(513, [rows(513)], None, None))),
+             ("rows stored again", False, lambda: p.step(u, 0.5, rand(B), rows_out=[out], insert=(B, [out], None, None))),
+             ("slots over uniforms", False, lambda: p.step(u, 0.5, rand(B), insert=(n, [rows(n)], None, u.view(torch.int32)[:, :n]))),
+             ("weights over uniforms", False, lambda: p.step(weights, 0.5, rand(B), out_weight=weights))]
+    p.profile(True)
+    before = 0
+    for what, chip, call in calls:
+        call()
+        now = int(p.profile_read().get("k_run_steps", (0, 0))[1])
+        assert (now == before + 1) == chip and now - before <= 1, what
+        before = now
+    p.set_weight_norm("buffer")
+    p.step(u, 0.5, rand(B))
+    assert int(p.profile_read()["k_run_steps"][1]) == before, "weights relative to the buffer"
+    p.profile(False)
+
+
+@pytest.mark.parametrize("K,N,T,B,fb", [(16, 5000, 1, 64, (16, 5)), (8, 9000, 2, 40, (12,)), (4, 3000, 1, 130, ()), (32, 70001, 1, 300, (4, 4))])
+def test_carried_insertions_on_small_trees(K, N, T, B, fb):
+    """Steps with new rows by the kernels, on trees that by default go as one launch: the sampling kernel carries the insertion, past the
+    ring's end it is made on its own."""
+    log(f"carried insertions K={K} N={N} T={T} B={B}")
+    rng = np.random.default_rng(K + N)
+    m = Mirror(K, N, T, fb)
+    m.gpu.set_tuning("step_on_chip", 0)
+    m.gpu.set_tuning("step_kernel", 0)
+    m.insert(N - 40, prio=wl._draw_priorities("pareto_1.5", rng, (T, N - 40)))
+    m.gpu.profile(True)
+    for it, n in enumerate((4, 1, K, 16, 30, 9)):
+        before = kernel_launches(m)
+        ins = (rng.random((T, n)) * 9).astype(np.float32) if it % 2 else None
+        m.insert_step_call(n, ins, wl.uniform01(rng, (T, B)), 0.4, it != 1, wl._draw_updates("absnormal1_eps_pow0.6", rng, (T, B)))
+        after = kernel_launches(m)
+        own = {k for k, v in after.items() if v != before.get(k, 0)}
+        assert "k_run_steps" not in own
+        if n <= 4:
+            assert not any(k.startswith("k_insert") for k in own), own
+        m.compare_tree()
+    m.gpu.profile(False)
+    m.compare_status()
+
+
 def test_steps_on_the_chip_draw_and_replay_as_the_kernels_do():
     """The library's own uniforms, results that lie over inputs (the usual way is taken), an empty tree, and replays of a
     captured step between eager calls: the same as with the kernels."""
