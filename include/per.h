@@ -165,7 +165,10 @@ int per_sample_gather_update(per_t* p, uint32_t B, float beta, const float* d_u,
  * with the same results (last writer in order of j where several elements meet on a leaf).  A position
  * >= B makes its element invalid (PER_FLAG_BAD_INDEX), as does a sample that found nothing
  * (PER_FLAG_ZERO_TOTAL).  d_upd_prio and d_upd_pos are [T][B] and must not overlap the outputs
- * (PER_EINVAL).  d_field_dst and d_out_weight may be NULL. */
+ * (PER_EINVAL).  d_field_dst and d_out_weight may be NULL.
+ * A step without a position map, of at most 512 samples and new rows on a tree that per_run_steps takes, goes as one launch
+ * of that call's kernel where that is the faster way (tuning "step_on_chip"); see per_set_weight_norm and
+ * per_update_delta for where it does not. */
 int per_step(per_t* p, uint32_t B, float beta, const float* d_u, uint32_t* d_out_idx, float* d_out_weight,
              float* d_out_prio, void* const* d_field_dst, const float* d_upd_prio, const uint32_t* d_upd_pos,
              void* stream);
@@ -179,8 +182,9 @@ int per_step(per_t* p, uint32_t B, float beta, const float* d_u, uint32_t* d_out
  * insertion leaves it, extra workgroups move the rows and the first of them stores the new nodes; the step then
  * takes two kernel launches, insertion included.  For that the
  * insertion's arrays (d_field_src[f], d_ins_prio, d_ins_out_idx) must not overlap the step's outputs and
- * d_ins_out_idx none of the step's inputs either; otherwise, and for any other shape, the two calls are made one
- * after the other.  Arguments, flags and errors as for the two calls; an argument error of the step is
+ * d_ins_out_idx none of the step's inputs either.  Small steps go as one launch, insertion included, as with per_step
+ * (for that no array that is read may lie over one that is written, and no two that are written over one another);
+ * otherwise, and for any other shape, the two calls are made one after the other.  Arguments, flags and errors as for the two calls; an argument error of the step is
  * reported before the insertion is enqueued. */
 int per_insert_step(per_t* p, uint32_t n, const void* const* d_field_src, const float* d_ins_prio,
                     uint32_t* d_ins_out_idx, uint32_t B, float beta, const float* d_u, uint32_t* d_out_idx,

@@ -6,17 +6,19 @@
 // ---------------------------------------------------------------------------------
 // The paper keeps the sum tree of its Replay Manager in on-chip memory and lets one kernel, started
 // once, work through a stream of requests (Section V-A, "RM on FPGA": buffers of 10K to 100K entries,
-// autorun kernels that need no launch per request).  The counterpart here: when all heights of a
-// tree fit the LDS of one compute unit, one workgroup per tree loads the tree once, runs a whole
+// autorun kernels that need no launch per request).  The counterpart here: when a tree
+// fits the LDS of one compute unit, one workgroup per tree loads the tree once, runs a whole
 // list of steps (insert -> sample -> gather -> update, the order of the separate calls) against
 // the LDS copy, and stores the tree back at the end.  Every tree access of a step is then an LDS
 // access; only rows, inputs and outputs travel to memory.  Results are those of the separate calls.
 //
-// A tree whose leaves do not fit beside the rest (MEM) keeps heights 1 .. H in LDS and its leaves in memory: the
+// A tree whose leaves do not fit beside the rest (MEM) keeps what is above them in LDS and its leaves in memory: the
 // paper's 100K-entry buffers at small fanouts are of that size.  The workgroup is still the only one that
 // touches the tree while the kernel runs, so its own leaf stores, made visible to its other waves by a
 // barrier, are all the coherence that takes; every operation then costs a trip or two to memory for the leaf
 // groups it reads (sampling: the last level of the walk; insert and update: the groups whose sums change).
+// Of narrow trees the copy holds some heights only (see Wide).  Every node is taken for the sum of its children, which
+// the host sees to before the launch.
 //
 // Update inside one workgroup: a valid element raises the leaf (reinterpreted as an integer) to
 // a marker above every valid priority pattern, 0x80000001 + its position, by an LDS atomic max; the
@@ -1023,7 +1025,7 @@ static TeamForm team_form(uint32_t samples, uint32_t inserted) {
 // (its loads are issued behind the barrier that ends the sampling), and overwrite what the gather of the step before has
 // read (whose loads are issued in front of the barrier before the insertion's stores); the accesses of a workgroup's waves
 // keep that order (see TreeView::sync).
-// 100 steps on 10 000 leaves at K = 16 (32 samples, 4 new rows of 41 bytes): 167 us; 1001 us as one phase after the
+// 100 steps on 10 000 leaves at K = 16 (32 samples, 4 new rows of 41 bytes): 169 us; 1001 us as one phase after the
 // other by the whole workgroup with a full barrier between them.
 // AHEAD: no step reads what a step returns.
 template <int LOGK, TeamForm FORM, bool MEM, bool AHEAD>
@@ -1341,7 +1343,7 @@ k_run_steps(StreamKernelArgs ka) {
 // Fetching ahead is only right where a request reads nothing that one just before it writes (an update whose index
 // array is the sampled one, say).  The host has checked that (QueueArgs::ahead); where it does not hold, every
 // request is a round of its own with an empty one behind it, which brings all results to memory.
-// 20 times (insert 16 rows, sample 512, update them) on 30 000 leaves at K = 16: 112 us; 353 us one request after the
+// 20 times (insert 16 rows, sample 512, update them) on 30 000 leaves at K = 16: 110 us; 353 us one request after the
 // other by the whole workgroup with a full barrier between their phases.  The row waves are at work throughout, and the
 // team waits for them at both barriers, a third of the round.
 struct QueueKernelArgs {            // one kernel argument (Geom first: see fill_level_table)
