@@ -2103,6 +2103,39 @@ def test_on_chip_rows_of_all_shares(fb, B):
     del keep
 
 
+@pytest.mark.parametrize("K,N,B,fb", [(16, 900, 64, (165,)), (2, 900, 130, (165,)), (16, 60000, 64, (165,)), (32, 3000, 256, (68, 24, 4, 68, 1)), (4, 2000, 512, (63, 5))])
+def test_lists_that_read_their_results_with_long_gathers(K, N, B, fb):
+    """Steps that update the batch of the step before, with more pieces per batch than the row waves have under way at once: few samples
+    and many, by the build in which every wave does both; against the separate calls."""
+    log(f"dependent lists with long gathers K={K} N={N} B={B} fb={fb}")
+    steps, n = 5, 7
+    p, q = PrioritizedReplay(K, N, 1, fb), PrioritizedReplay(K, N, 1, fb)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(K + B)
+    rand = lambda *shape: torch.rand(shape, generator=g, device="cuda")   # noqa: E731
+    data = lambda *lead: [torch.randint(0, 256, (*lead, b), generator=g, device="cuda", dtype=torch.uint8) for b in fb]   # noqa: E731
+    first, prio, new = data(1, N), rand(1, N), data(steps, 1, n)
+    for x in (p, q):
+        x.insert(N, first, prio)
+    u, up = rand(steps, 1, B), rand(steps, 1, B)
+    idx = torch.zeros((steps + 1, 1, B), dtype=torch.int32, device="cuda")
+    weight, value = torch.zeros((steps, 1, B), device="cuda"), torch.zeros((steps, 1, B), device="cuda")
+    rows = data(steps, 1, B)
+    p.run_steps(u, torch.full((steps,), 0.5, device="cuda"), idx[1:], weight, value, rows, upd_prio=up, upd_idx=idx[:-1], n_insert=n, ins_rows=new)
+    before = torch.zeros((1, B), dtype=torch.int32, device="cuda")
+    for s in range(steps):
+        q.insert(n, [r[s] for r in new])
+        got = [torch.empty((1, B, b), dtype=torch.uint8, device="cuda") for b in fb]
+        i, w, v = q.sample(u[s], 0.5, rows_out=got)
+        assert torch.equal(i, idx[s + 1]) and torch.equal(v, value[s]), f"step {s}"
+        np.testing.assert_allclose(weight[s].cpu().numpy(), w.cpu().numpy(), rtol=1e-6)
+        assert all(torch.equal(a, b[s]) for a, b in zip(got, rows)), f"rows of step {s}"
+        q.update(before, up[s])
+        before = i
+    for h in range(p.H + 1):
+        assert torch.equal(p.read_level(0, h), q.read_level(0, h)), f"height {h}"
+
+
 def test_run_requests_argument_checks():
     from paper_2311_09445_amd.per import OP_SAMPLE, OP_UPDATE
     big = PrioritizedReplay(16, 1 << 20)
