@@ -211,7 +211,8 @@ int per_update_td(per_t* p, uint32_t B, const uint32_t* d_idx /*[T][B]*/, const 
  * "priority retrievals followed by priority updates": retrieve the old values, form
  * delta = new - old, apply.  Changes to the same node meet in no fixed order (hardware float
  * atomics), so a node equals the sequential result only up to fp32 rounding, no longer the
- * exact pairwise sum of its children; per_update restores that for the paths it touches.
+ * exact pairwise sum of its children; per_update restores that for the paths it touches.  (Until then a target that
+ * falls on such a rounding error may be drawn from a subtree whose leaves are zero.)
  * Duplicated indices add up.  The running maximum priority is not touched (the call never sees a
  * priority).  Valid means d_idx < size and d_delta finite; other elements are skipped and flagged
  * (BAD_INDEX, BAD_PRIORITY).  The caller keeps leaves non-negative.

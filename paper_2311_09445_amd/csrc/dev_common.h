@@ -285,8 +285,10 @@ __device__ __forceinline__ void descend_looking(P grp, float& r, unsigned& child
 
 // The same binary steps on a group held in registers, without a look at the right block.  That the right block is zero
 // while r is not below the left one takes a rounding, or a uniform outside [0, 1); a walk that does not look then ends at a
-// child of zero, because a block whose sum is zero holds nothing else, and whoever walks so has to check that.  (c: the N
-// children; node: 2 node + 1 for a turn to the right.)
+// child of zero, because a block whose sum is zero holds nothing else, and whoever walks so has to check that.  (Nodes that
+// changes added and taken back have left a rounding error above or below zero can cancel to a block of exactly zero; a walk
+// that looks passes by that block, but ends as well in any whose errors do not cancel.  c: the N children; node: 2 node + 1
+// for a turn to the right.)
 template <int N>
 __device__ __forceinline__ float first_half_sum(const float (&c)[N]) {   // of c[0 .. N/2), pairwise
   if constexpr (N == 2) {
