@@ -25,9 +25,21 @@
 // element that finds its own marker afterwards is the last writer and stores its value; then
 // every valid element recomputes its ancestors height by height (elements that share a parent
 // store the same sum).
-struct StreamKernelArgs {           // one kernel argument, so that both parts sit at known offsets of the segment
+// The list of a batch's row pieces (see PieceFields), laid out by the host: worked out by a wave of the kernel, it was what the
+// first step waited for (divisions and shares: 1.1 us behind the copy of the tree).
+struct PieceList {
+  uint8_t* io[kMaxFields];         // as in PieceFields, of tree 0
+  uint8_t* base;
+  uint64_t base_stride;            // bytes between the payloads of two trees
+  uint64_t step_rows;
+  uint32_t off[kMaxFields], bytes[kMaxFields], width[kMaxFields], recip[kMaxFields], first[kMaxFields], end[kMaxFields];
+  uint32_t items, n;
+};
+struct StreamKernelArgs {           // one kernel argument, so that its parts sit at known offsets of the segment
   Geom g;
   StreamArgs a;
+  PieceList rows, ins;
+  uint2 share[16];                  // items of the gather of every row wave
 };
 
 // The copy of the tree is held as levels of wide groups.  Every stored height of a narrow tree (K = 2, 4) costs the walk
@@ -47,6 +59,12 @@ template <int LOGK>
 __device__ __forceinline__ uint32_t level_height(uint32_t v, uint32_t H) {
   const uint32_t h = v * (uint32_t)Wide<LOGK>::LH;
   return h < H ? h : H;
+}
+
+__device__ __forceinline__ uint32_t wave_value(uint32_t x) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)x); }   // (the same in all lanes)
+__device__ __forceinline__ uint32_t ring_slot(uint32_t cursor, uint32_t j, uint32_t N) {
+  const uint32_t s = cursor + j;   // (N <= 2^31, j < N)
+  return s >= N ? s - N : s;
 }
 
 // Sum of the 4*N children behind g4 in the balanced pairwise order, by a single lane.
@@ -73,25 +91,28 @@ struct LdsTree {
 
 // Loads every level of tree t into LDS, by lanes 0 .. lanes - 1.  The heights are arrays of their own in memory (zero padded
 // to 64 floats) and the levels lie back to back in LDS.  The lowest level is most of it: it goes in 16-byte pieces, eight
-// per lane under way at once, behind the first piece that the lane has of the levels above.  Called by waves that have
-// nothing else to do: the lists of fields and the first requests are made meanwhile.
+// per lane under way at once, and with the first eight the first piece that the lane has of the levels above.  Called by waves that have
+// nothing else to do: the first requests of a queue are laid out meanwhile.
 template <int LOGK>
 __device__ __forceinline__ void lds_tree_load(const LevelTable& tab, const LdsTree& lt, uint32_t lane, uint32_t lanes) {
   constexpr int R = 8;
   typedef GlobalPtr<const float> Source;
   const uint32_t v0 = lt.leaves_mem ? 1u : 0u, V = lt.V;
+  // (all offsets in the lanes of the wave: a piece's level is then found without a trip to LDS per level)
+  const uint32_t off_reg = lt.off[min_u32(threadIdx.x & 63u, V + 1u)];
+  auto off = [&](uint32_t v) { return (uint32_t)__builtin_amdgcn_readlane((int)off_reg, (int)v); };
   auto above = [&](uint32_t e) {   // the piece at LDS float e, of a level above v0
     uint32_t v = v0 + 1u;
-    while (v < V && e >= lt.off[v + 1]) ++v;
+#pragma unroll 1
+    for (uint32_t w = v0 + 2u; w <= V; ++w) v += e >= off(w) ? 1u : 0u;   // (the same for the wave: w)
     const uint32_t i = e - lt.off[v];
     Floats4 x = {0.0f, 0.0f, 0.0f, 0.0f};
     if (i < lt.n[v]) x = load_floats4(as_global(static_cast<const float*>(tab.lvl[level_height<LOGK>(v, lt.H)])) + i);
     return x;
   };
-  const uint32_t end = lt.off[V + 1], first = lt.off[v0 + 1], n0 = lt.n[v0];
+  const uint32_t end = off(V + 1), first = off(v0 + 1), n0 = lt.n[v0];
   Floats4 top;
-  const uint32_t top_at = first + 4u * lane;
-  if (top_at < end) top = above(top_at);
+  const uint32_t top_at = first + 4u * (lanes - 1u - lane);   // (the last waves first: the first have their own inputs to ask for)
   Source src = as_global(static_cast<const float*>(tab.lvl[level_height<LOGK>(v0, lt.H)]));
   float* dst = lt.tree + lt.off[v0];
   const uint32_t room = first - lt.off[v0];
@@ -103,6 +124,7 @@ __device__ __forceinline__ void lds_tree_load(const LevelTable& tab, const LdsTr
       x[k] = Floats4{0.0f, 0.0f, 0.0f, 0.0f};
       if (e < n0) x[k] = load_floats4(src + e);
     }
+    if (base == 0 && top_at < end) top = above(top_at);   // (which level it is of is found while those are on their way)
 #pragma unroll
     for (int k = 0; k < R; ++k) {
       const uint32_t e = base + 4u * ((uint32_t)k * lanes + lane);
@@ -134,10 +156,17 @@ __device__ __forceinline__ void store_between(P grp, uint32_t p, uint32_t h0, co
     }
   }
 }
-// ... and back to memory, with the running maximum and the flags the lanes have collected.
+// What the lanes of a wave have found goes into the tree's sticky flags.  Called by whole waves.
+__device__ __forceinline__ void report_flags(const Geom& g, uint32_t t, uint32_t flags) {
+  if (!__any(flags != 0)) return;
+  uint32_t all = 0;
+#pragma unroll
+  for (uint32_t bit = 1; bit <= 4; bit <<= 1) all |= __any((flags & bit) != 0) ? bit : 0u;
+  if ((threadIdx.x & 63u) == 0) atomicOr(&g.status[t], all);
+}
+// ... and back to memory, with the running maximum.
 template <int LOGK>
-__device__ __forceinline__ void lds_tree_store(const Geom& g, uint32_t t, const LevelTable& tab, const LdsTree& lt,
-                                               uint32_t flags, uint32_t* s_flags) {
+__device__ __forceinline__ void lds_tree_store(const Geom& g, uint32_t t, const LevelTable& tab, const LdsTree& lt) {
   constexpr uint32_t LH = Wide<LOGK>::LH, R = Wide<LOGK>::R;
   const uint32_t V = lt.V, H = lt.H;
   // (a root less than a whole level above its children is stored by the pass below: the level's sum of it has zeros added)
@@ -176,9 +205,52 @@ __device__ __forceinline__ void lds_tree_store(const Geom& g, uint32_t t, const 
     }
   }
   if (threadIdx.x == 0) g.max_v[t] = __uint_as_float(*lt.max_bits);
-  if (flags) atomicOr(s_flags, flags);
-  __syncthreads();
-  if (threadIdx.x == 0 && *s_flags) atomicOr(&g.status[t], *s_flags);
+}
+// Of a list of one step only what it has changed goes back: the leaves of the updated batch (`nodes` in LDS, null: no update)
+// and of the insertion, and their ancestors (elements that share one store the same value).  A wave takes 64 elements at one
+// level at a time, from the count of what is taken in LDS: waves that have no rows begin as soon as the team has made the tree
+// whole (*s_whole), and none waits for the others' results.  (Stored whole, with a barrier in front and behind, a step of 64 samples and 4 rows on
+// 4096 leaves at K = 2 spent 1.8 us on it; all of the paths by the team's one wave, 2.0.)
+template <int LOGK, bool MEM>
+__device__ __forceinline__ void store_paths(const LevelTable& tab, const LdsTree& lt, const uint32_t* nodes, uint32_t updated, uint32_t cursor,
+                                            uint32_t inserted, uint32_t N, uint32_t* s_taken, const uint32_t* s_whole) {
+  constexpr uint32_t LH = Wide<LOGK>::LH, LOGR = Wide<LOGK>::LOGR, R = Wide<LOGK>::R;
+  const uint32_t lane = threadIdx.x & 63u, n = nodes ? updated : 0u, elements = n + inserted;
+  const uint32_t levels = lt.V + (MEM ? 0u : 1u), rounds = (elements + 63u) / 64u;
+  for (;;) {
+    uint32_t item = 0;
+    if (lane == 0) item = atomicAdd(s_taken, 1u);
+    item = wave_value(item);
+    if (item >= rounds * levels) return;
+    uint32_t round = 0;   // (few rounds)
+    while (item >= levels) item -= levels, ++round;
+    const uint32_t e = round * 64u + lane, v = lt.V - item;   // (the level with the heights between first)
+    uint32_t leaf = 0xFFFFFFFFu;
+    if (e < n) leaf = nodes[e];
+    else if (e < elements) leaf = ring_slot(cursor, e - n, N);
+    const bool some = leaf < N;   // (else nothing could be sampled, or no element)
+    while (wave_value(*(const volatile uint32_t*)s_whole) == 0u) __builtin_amdgcn_s_sleep(1);   // (the team waits for nobody)
+    asm volatile("" ::: "memory");
+    const uint32_t node = leaf >> (v * LOGR);
+    if constexpr (LH > 1) {   // the heights between level v - 1 and this one: the blocks of two, four, eight children that hold the leaf
+      const uint32_t h0 = (v - 1) * LH, child = (leaf >> ((v - 1) * LOGR)) & (R - 1u);
+      auto between = [&](auto grp) {
+        const Floats4 a = load_floats4(grp + (child & ~7u)), b = load_floats4(grp + (child & ~7u) + 4);
+        const bool upper = (child & 4u) != 0;
+        const Floats4 x = upper ? b : a;
+        const float sa = (a.x + a.y) + (a.z + a.w), sb = (b.x + b.y) + (b.z + b.w);
+        constexpr uint32_t d4 = 2 / LOGK;   // heights up to the blocks of four
+        if (LOGK == 1 && h0 + 1 <= lt.H) as_global(tab.lvl[h0 + 1])[leaf >> (h0 + 1)] = (child & 2u) ? x.z + x.w : x.x + x.y;
+        if (h0 + d4 <= lt.H) as_global(tab.lvl[h0 + d4])[leaf >> ((h0 + d4) * LOGK)] = upper ? sb : sa;
+        if (LOGK == 1 && h0 + 3 <= lt.H) as_global(tab.lvl[h0 + 3])[leaf >> (h0 + 3)] = sa + sb;
+      };
+      if (v && some) {
+        if (MEM && v == 1) between(as_global(static_cast<const float*>(lt.leaves_mem)) + (size_t)node * R);
+        else between(static_cast<const float*>(lt.tree) + lt.off[v - 1] + (size_t)node * R);
+      }
+    }
+    if (some && v * LH <= lt.H) as_global(tab.lvl[v * LH])[node] = lt.tree[lt.off[v] + node];
+  }
 }
 
 // ---- rows of the stream kernels
@@ -192,9 +264,9 @@ constexpr uint32_t kLeastMovers = 6;   // row waves that are left to gather wher
 // How the items of a gather are shared out among the row waves.
 enum GatherShares {
   SHARES_NONE,   // (an insertion)
-  SHARES_RUNS,   // every wave has a run of at most kInFlight items of one access width: straight code, and all under way at once
-  SHARES_EVEN,   // more than that, or a team that does the rows as well: equally many to every wave, see gather_spans
-  SHARES_ANY     // runs where that works, else evenly (a queue, whose requests differ)
+  SHARES_EVEN,   // equally many to every wave, see gather_spans
+  SHARES_ANY     // where that works, every wave has a run of at most kInFlight items of one access width (straight code, and all
+                 // under way at once), else evenly
 };
 // Waves that gather in runs where n samples are weighed as well: those that do not weigh, if there are enough.
 __host__ __device__ __forceinline__ uint32_t run_waves(uint32_t n, uint32_t rws) {
@@ -212,16 +284,15 @@ struct PieceFields {               // what the waves ask of one list of fields, 
   uint32_t items, n;               // all items; rows
   uint32_t runs;                   // SHARES_ANY: the length of the runs, 0: shared out evenly
 };
-__device__ __forceinline__ uint32_t wave_value(uint32_t x) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)x); }   // (the same in all lanes)
 __device__ __forceinline__ uint64_t wave_value64(uint64_t x) {
   return (uint64_t)wave_value((uint32_t)(x >> 32)) << 32 | wave_value((uint32_t)x);
 }
 __device__ __forceinline__ uint8_t* wave_pointer(uint8_t* p) { return reinterpret_cast<uint8_t*>(wave_value64(reinterpret_cast<uint64_t>(p))); }
-// Called by one wave: n rows per tree; field f is `asked` for, and its array is `io` for tree 0, `step_rows` rows from step to
-// step; the `rws` row waves share the items out.  share: items of wave i.  (Host: gathers_in_runs() says whether runs work.)
+// The list of a request, by one wave: n rows per tree; field f is `asked` for (where its array is the round says); the `rws`
+// row waves share the items out.  share: items of wave i.  (A list of steps has its lists from the host: plan_pieces.)
 template <GatherShares SHARES>
-__device__ __forceinline__ void fill_piece_fields(const FieldTable* ft, bool asked, uint8_t* io, uint32_t t, uint32_t n, uint64_t step_rows,
-                                                  uint32_t rws, PieceFields* pf, uint2* share) {
+__device__ __forceinline__ void fill_piece_fields(const FieldTable* ft, bool asked, uint32_t t, uint32_t n, uint32_t rws, PieceFields* pf,
+                                                  uint2* share) {
   const uint32_t lane = threadIdx.x & 63u, f = lane;
   const bool on = f < (uint32_t)kMaxFields && f < ft->n_fields && asked && n;
   const uint32_t E = on ? ft->bytes[f] : 1u, v = on ? ft->vec[f] : 1u, epr = row_elements(E, v);
@@ -240,7 +311,7 @@ __device__ __forceinline__ void fill_piece_fields(const FieldTable* ft, bool ask
 #pragma unroll
   for (int c = 0; c < kWidths; ++c) total += of_kind[c];
   if (f < (uint32_t)kMaxFields) {
-    pf->io[f] = on ? io + (uint64_t)t * n * E : nullptr;
+    pf->io[f] = on ? reinterpret_cast<uint8_t*>(0) + (uint64_t)t * n * E : nullptr;
     pf->off[f] = on ? (uint32_t)(ft->col[f] - ft->col[0]) : 0u;   // (the fields of a row lie in the order of their numbers)
     pf->bytes[f] = E;
     pf->width[f] = w;
@@ -251,12 +322,12 @@ __device__ __forceinline__ void fill_piece_fields(const FieldTable* ft, bool ask
   if (f == 0) {
     pf->base = ft->n_fields ? ft->col[0] + (uint64_t)t * ft->col_stride[0] : nullptr;
     pf->items = total;
-    pf->step_rows = step_rows;
+    pf->step_rows = 0;
     pf->n = n;
   }
   if constexpr (SHARES == SHARES_NONE) return;
   uint32_t run = 0, waves = rws;
-  if constexpr (SHARES == SHARES_RUNS || SHARES == SHARES_ANY) {
+  if constexpr (SHARES == SHARES_ANY) {
     // the shortest runs with which there are waves enough: lane i tries runs of i + 1 (at most 16 * 6 items count here, for which
     // the product with the reciprocal is the quotient)
     waves = run_waves(n, rws);
@@ -266,11 +337,11 @@ __device__ __forceinline__ void fill_piece_fields(const FieldTable* ft, bool ask
     for (int c = 0; c < kWidths; ++c) needed += (min_u32(of_kind[c], 1023u) + lane) * recip >> 16;
     const unsigned long long enough = __ballot(needed <= waves && lane < kInFlight);
     run = enough ? 1u + (uint32_t)__builtin_ctzll(enough) : 0u;
-    if (SHARES == SHARES_ANY && f == 0) pf->runs = run;
+    if (f == 0) pf->runs = run;
   }
   if (lane < 16u) {
     uint32_t a = 0, b = 0;
-    if (SHARES == SHARES_RUNS || (SHARES == SHARES_ANY && run)) {
+    if (SHARES == SHARES_ANY && run) {
       const uint32_t recip = 0xFFFFu / run + 1u;   // (as above)
       uint32_t start = 0, wave0 = 0;
 #pragma unroll
@@ -293,6 +364,45 @@ __device__ __forceinline__ void fill_piece_fields(const FieldTable* ft, bool ask
     share[lane] = make_uint2(a, b);
   }
 }
+// The same from a list that the host has laid out, by one wave: read when the kernel starts, put into LDS behind the first
+// barrier, for which the other waves then need not wait.
+struct PieceCopy {
+  uint8_t *io, *base;
+  uint64_t step_rows;
+  uint32_t off, bytes, width, recip, first, end, items, n;
+  __device__ __forceinline__ void read(const PieceList* pl, uint32_t t) {
+    const uint32_t f = min_u32(threadIdx.x & 63u, (uint32_t)kMaxFields - 1u);
+    n = pl->n;
+    items = pl->items;
+    step_rows = pl->step_rows;
+    base = pl->base + (uint64_t)t * pl->base_stride;
+    off = pl->off[f];
+    bytes = pl->bytes[f];
+    width = pl->width[f];
+    recip = pl->recip[f];
+    first = pl->first[f];
+    end = pl->end[f];
+    io = pl->io[f];
+  }
+  __device__ __forceinline__ void put(uint32_t t, PieceFields* pf) const {
+    const uint32_t f = threadIdx.x & 63u;
+    if (f < (uint32_t)kMaxFields) {
+      pf->io[f] = io + (uint64_t)t * n * bytes;
+      pf->off[f] = off;
+      pf->bytes[f] = bytes;
+      pf->width[f] = width;
+      pf->recip[f] = recip;
+      pf->first[f] = first;
+      pf->end[f] = end;
+    }
+    if (f == 0) {
+      pf->base = base;
+      pf->items = items;
+      pf->step_rows = step_rows;
+      pf->n = n;
+    }
+  }
+};
 // el / epr, for el < 2^31 (at most 1024 rows of at most 2^20 pieces, and less than a few items beyond them) and recip = floor(2^32 /
 // epr) + 1: recip is less than 1 / epr of itself too large, the quotient less than a half, so it comes out right or one too
 // large.  (epr = 1: recip = 0, and no branch for it: there is one such quotient per piece.)
@@ -365,10 +475,6 @@ __device__ __forceinline__ void store_piece(uint8_t* p, uint32_t w, const uint4&
   if (w == 4u) *(GlobalPtr<uint32_t>)dst = v.x;
   if (w == 2u) *(GlobalPtr<uint16_t>)dst = (uint16_t)v.x;
   if (w == 1u) *(GlobalPtr<uint8_t>)dst = (uint8_t)v.x;
-}
-__device__ __forceinline__ uint32_t ring_slot(uint32_t cursor, uint32_t j, uint32_t N) {
-  const uint32_t s = cursor + j;   // (N <= 2^31, j < N)
-  return s >= N ? s - N : s;
 }
 // The pieces of a gather that a wave has under way: M items of its share.  Where a piece lies in its row and where it goes
 // is known before the rows are; prepared in time, what is left between the batch and its loads is a look at the batch's
@@ -1037,24 +1143,37 @@ k_run_steps(StreamKernelArgs ka) {
   extern __shared__ __attribute__((aligned(16))) float tree[];
   __shared__ LevelTable tab;
   __shared__ uint32_t s_off[kStreamLevels + 2], s_n[kStreamLevels + 1];
-  __shared__ uint32_t s_max, s_vmin[2], s_bmin[2], s_wild, s_flags, s_arrived;
+  __shared__ uint32_t s_max, s_vmin[2], s_bmin[2], s_wild, s_arrived, s_whole, s_taken;
   __shared__ PieceFields s_rows, s_ins;
   __shared__ uint2 s_share[16];
   const uint32_t t = blockIdx.x;
   const uint32_t tid = threadIdx.x, lane = tid & 63u;
   const uint32_t H = g.H, T = g.T, B = a.B, n_ins = a.n_insert, N = g.N;
   const uint32_t V = a.levels;
-  fill_level_table(H, t, &tab);
-  if (tid >= 64 && tid <= 64 + V + 1) {
-    s_off[tid - 64] = kernarg_at<StreamArgs>(offsetof(StreamKernelArgs, a))->off[tid - 64];
-    if (tid <= 64 + V) s_n[tid - 64] = kernarg_at<Geom>(0)->n[level_height<LOGK>(tid - 64, H)];
+  // the tables from the argument segment by vector loads, as many entries as there can be, so that none waits for another
+  // argument first; the lists a lane per field, by two waves
+  const StreamArgs* as = kernarg_at<StreamArgs>(offsetof(StreamKernelArgs, a));
+  if (tid <= (uint32_t)kMaxHeight) {
+    const Geom* gk = kernarg_at<Geom>(0);
+    tab.lvl[tid] = gk->level[tid] + (size_t)t * gk->stride[tid];
+    tab.n[tid] = gk->n[tid];
   }
+  if (tid >= 64 && tid < 64 + kStreamLevels + 2) s_off[tid - 64] = as->off[tid - 64];
+  if (tid >= 128 && tid < 128 + kStreamLevels + 1) s_n[tid - 128] = as->nodes[tid - 128];
+  PieceCopy list;
+  uint2 share = make_uint2(0, 0);
+  const bool lists = tid >= 384 && tid < 512;
+  if (lists) {
+    list.read(kernarg_at<PieceList>(tid < 448 ? offsetof(StreamKernelArgs, rows) : offsetof(StreamKernelArgs, ins)), t);
+    share = kernarg_at<uint2>(offsetof(StreamKernelArgs, share))[lane & 15u];
+  }
+  uint32_t max_seen = 0;
   if (tid == 0) {
-    s_max = read_max_bits(g, t);
+    max_seen = read_max_bits(g, t);   // (on its way while the tree is asked for)
     s_vmin[0] = s_vmin[1] = s_bmin[0] = s_bmin[1] = kNoMin;
     s_wild = 0;
-    s_flags = 0;
     s_arrived = 0;
+    s_whole = s_taken = 0;
   }
   // lanes of the team, of the rows, of the weights
   const uint32_t wanted = WAVE ? 64u : ((B > n_ins ? B : n_ins) + 63u) / 64u * 64u;
@@ -1065,6 +1184,10 @@ k_run_steps(StreamKernelArgs ka) {
   const uint32_t w0 = apart ? 1024u - (B + 63u) / 64u * 64u : 0u;
   const bool weigher = tid >= w0 && tid - w0 < B;
   __syncthreads();
+  if (lists) {
+    list.put(t, tid < 448 ? &s_rows : &s_ins);
+    if (tid < 400) s_share[lane] = share;
+  }
   // inputs of the team: the uniform of the step to sample, value (and index) of the update to apply, inserted priority
   float u_i = 0.0f, u_next = 0.0f, up_v = 0.0f, in_v = 0.0f;
   float beta_i = 0.0f;
@@ -1082,17 +1205,8 @@ k_run_steps(StreamKernelArgs ka) {
   lt.max_bits = &s_max;
   lt.H = H;
   lt.V = V;
-  // (the lists from the argument segment by vector loads, a lane per field, two waves beside the others' copy of the tree)
-  if (tid >= 896) {
-    const bool rows = tid < 960;
-    const FieldTable* ft = kernarg_at<FieldTable>(offsetof(StreamKernelArgs, a) + (rows ? offsetof(StreamArgs, rows) : offsetof(StreamArgs, ins)));
-    const uint32_t n = rows ? B : n_ins;
-    uint8_t* io = lane < (uint32_t)kMaxFields ? ft->io[lane] : nullptr;
-    if (rows) fill_piece_fields<SPANS ? SHARES_EVEN : SHARES_RUNS>(ft, io != nullptr, io, t, n, (uint64_t)T * n, rws, &s_rows, s_share);
-    else fill_piece_fields<SHARES_NONE>(ft, io != nullptr, io, t, n, (uint64_t)T * n, rws, &s_ins, nullptr);
-  } else {
-    lds_tree_load<LOGK>(tab, lt, tid, 896u);
-  }
+  lds_tree_load<LOGK>(tab, lt, tid, 1024u);
+  if (tid == 0) s_max = max_seen;
   uint32_t* nodes = reinterpret_cast<uint32_t*>(tree + s_off[V + 1]);   // [B] sampled leaves of the step
   float* values = reinterpret_cast<float*>(nodes + 512);                // [B] and their values (apart only: B <= 512)
   TreeView<MEM> tv;
@@ -1115,6 +1229,7 @@ k_run_steps(StreamKernelArgs ka) {
   uint32_t flags = 0;
   float lane_max = __uint_as_float(s_max);   // (WAVE: the lanes' share of it; else s_max counts)
 
+  const bool brief = apart && a.n_steps == 1 && (a.upd_is_sampled || !a.upd_prio);   // (see store_paths)
   auto list_array = [](const RowItem& p) { return p.io; };
   auto work = [&](auto does_tree, auto does_rows) {
     constexpr bool TREE = decltype(does_tree)::value, ROWS = decltype(does_rows)::value;
@@ -1157,8 +1272,8 @@ k_run_steps(StreamKernelArgs ka) {
       float w_out = 0.0f, v_out = 0.0f;
       uint32_t n_out = 0;
       if (ROWS && s) {
-        if constexpr (SPANS) gather_spans<apart ? 8 : 4>(s_rows, gather_first, gather_last, nodes, N, a.rows.row_stride, s - 1, flags, [](uint32_t, uint8_t* at) { return at; });
-        else items.load(nodes, N, a.rows.row_stride);
+        if constexpr (SPANS) gather_spans<apart ? 8 : 4>(s_rows, gather_first, gather_last, nodes, N, a.rows_stride, s - 1, flags, [](uint32_t, uint8_t* at) { return at; });
+        else items.load(nodes, N, a.rows_stride);
         uint32_t least = 0;
         if (a.out_w && tid >= w0) {   // (whole waves)
           if (a.buffer_norm) least = s_bmin[(s - 1) & 1u];
@@ -1216,7 +1331,7 @@ k_run_steps(StreamKernelArgs ka) {
       if (ROWS && do_ins && ip.w) {
         if (AHEAD) ip.io += ip.step;
         if (ip.row != 0xFFFFFFFFu) {
-          place = payload + (uint64_t)ring_slot(first, ip.row, N) * a.ins.row_stride + ip.at;
+          place = payload + (uint64_t)ring_slot(first, ip.row, N) * a.ins_stride + ip.at;
           if (AHEAD && s + 1 < a.n_steps) next_iv = load_piece(ip.io + ip.out, ip.w);
         }
       }
@@ -1259,6 +1374,15 @@ k_run_steps(StreamKernelArgs ka) {
         size = size + n_ins > N ? N : size + n_ins;
       }
       upd_size = size;
+      if (!more) {
+        if (ROWS && !stores_first) store_results();
+        if (TREE && brief) {
+          if constexpr (!WAVE) tv.sync();
+          asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+          if (tid == 0) *(volatile uint32_t*)&s_whole = 1u;
+        }
+        break;
+      }
       // ---- the rows of the step before have been asked for; the tree is whole.  (A team of one wave has no use for this
       // barrier itself: it passes it as late as the walk allows, where the row waves have long come.)
       const bool late = WAVE && TREE && more && !a.buffer_norm;
@@ -1269,11 +1393,10 @@ k_run_steps(StreamKernelArgs ka) {
           if (AHEAD) iv = next_iv;
           if (a.ins_slots)
             for (uint32_t j = rl; j < n_ins; j += rn) a.ins_slots[(size_t)t * n_ins + j] = ring_slot(first, j, N);
-          if (rw + rws < insert_items) insert_rows(s_ins, insert_items, rw + rws, rws, first, N, a.ins.row_stride, s, nullptr, list_array);
+          if (rw + rws < insert_items) insert_rows(s_ins, insert_items, rw + rws, rws, first, N, a.ins_stride, s, nullptr, list_array);
         }
         if (!stores_first) store_results();
       }
-      if (!more) break;
       if constexpr (ROWS) {
         // (read by the weights of step s - 1, before the barrier)
         if ((TREE || a.buffer_norm) && rl == 0) s_vmin[(s + 1) & 1u] = s_bmin[(s + 1) & 1u] = kNoMin;
@@ -1319,8 +1442,15 @@ k_run_steps(StreamKernelArgs ka) {
     const uint32_t m = wave_max_u32(__float_as_uint(lane_max));
     if (tid == 0) s_max = m;
   }
+  report_flags(g, t, flags);
+  if (brief) {
+    if (tid == 0) g.max_v[t] = __uint_as_float(s_max);
+    if (a.out_w && tid >= w0) return;   // (the weights are what takes longest)
+    store_paths<LOGK, MEM>(tab, lt, a.upd_prio ? nodes : nullptr, B, a.cursor, n_ins, N, &s_taken, &s_whole);
+    return;
+  }
   __syncthreads();
-  lds_tree_store<LOGK>(g, t, tab, lt, flags, &s_flags);
+  lds_tree_store<LOGK>(g, t, tab, lt);
 }
 
 // ---------------------------------------------------------------------------------
@@ -1433,7 +1563,7 @@ k_run_requests(QueueKernelArgs ka) {
   __shared__ PieceFields s_rows[2], s_ins[2];        // by parity of the round
   __shared__ uint2 s_share[2][16];
   __shared__ uint32_t s_skip[2][32];                 // bit j: row j of the round's insertion is deferred
-  __shared__ uint32_t s_max, s_vmin[2], s_bmin[2], s_wild, s_flags, s_arrived;
+  __shared__ uint32_t s_max, s_vmin[2], s_bmin[2], s_wild, s_arrived;
   const uint32_t t = blockIdx.x;
   const uint32_t tid = threadIdx.x, lane = tid & 63u;
   const uint32_t H = g.H, N = g.N, n_requests = a.n_requests, V = a.levels;
@@ -1449,7 +1579,6 @@ k_run_requests(QueueKernelArgs ka) {
     s_max = read_max_bits(g, t);
     s_vmin[0] = s_vmin[1] = s_bmin[0] = s_bmin[1] = kNoMin;
     s_wild = 0;
-    s_flags = 0;
     s_arrived = 0;
   }
   if (tid < 64) s_skip[tid >> 5][tid & 31u] = 0;
@@ -1522,8 +1651,8 @@ k_run_requests(QueueKernelArgs ka) {
       const uint32_t* w = words + PER_REQUEST_WORD(field) + 2u * lane;
       asked = (w[0] | w[1]) != 0;
     }
-    if (share) fill_piece_fields<apart ? SHARES_ANY : SHARES_EVEN>(fields, asked, nullptr, t, n, 0, rws, pf, share);
-    else fill_piece_fields<SHARES_NONE>(fields, asked, nullptr, t, n, 0, rws, pf, nullptr);
+    if (share) fill_piece_fields<apart ? SHARES_ANY : SHARES_EVEN>(fields, asked, t, n, rws, pf, share);
+    else fill_piece_fields<SHARES_NONE>(fields, asked, t, n, rws, pf, nullptr);
   };
   const bool lists = !(apart && in_team) && rw == 1;   // (the wave that does)
   __syncthreads();
@@ -1818,8 +1947,9 @@ k_run_requests(QueueKernelArgs ka) {
     const uint32_t m = wave_max_u32(__float_as_uint(lane_max));
     if (tid == 0) s_max = m;
   }
+  report_flags(g, t, flags);
   __syncthreads();
-  lds_tree_store<LOGK>(g, t, tab, lt, flags, &s_flags);
+  lds_tree_store<LOGK>(g, t, tab, lt);
 }
 
 // A tree can be worked on where its heights (every one padded to whole child groups), or those above the leaves, fit
@@ -1876,16 +2006,64 @@ static uint64_t items_by_width(const FieldTable& ft, uint32_t n, uint64_t (&of_k
   }
   return total;
 }
-// Whether a gather of n rows can be shared out in runs among rws row waves (see fill_piece_fields).
-static bool gathers_in_runs(const FieldTable& ft, uint32_t n, uint32_t rws) {
-  uint64_t of_kind[kWidths];
-  (void)items_by_width(ft, n, of_kind);
+// Length of the runs in which a gather of n rows can be shared out among rws row waves (0: it cannot): every wave has at most
+// that many items, of one access width, and not more than it can have under way at once.
+static uint32_t gather_run(const uint64_t (&of_kind)[kWidths], uint32_t n, uint32_t rws) {
   for (uint32_t len = 1; len <= kInFlight; ++len) {
     uint64_t needed = 0;
     for (int c = 0; c < kWidths; ++c) needed += (of_kind[c] + len - 1) / len;
-    if (needed <= run_waves(n, rws)) return true;
+    if (needed <= run_waves(n, rws)) return len;
   }
-  return false;
+  return 0;
+}
+static bool gathers_in_runs(const FieldTable& ft, uint32_t n, uint32_t rws) {
+  uint64_t of_kind[kWidths];
+  (void)items_by_width(ft, n, of_kind);
+  return gather_run(of_kind, n, rws) != 0;
+}
+// The list of n rows' pieces for the kernel (the items ordered by access width, and those of one width by field).
+static void plan_pieces(const FieldTable& ft, uint32_t n, uint32_t trees, PieceList* pl) {
+  uint64_t of_kind[kWidths];
+  pl->items = (uint32_t)items_by_width(ft, n, of_kind);
+  pl->n = n;
+  pl->step_rows = (uint64_t)trees * n;
+  pl->base = ft.n_fields ? ft.col[0] : nullptr;
+  pl->base_stride = ft.n_fields ? ft.col_stride[0] : 0;
+  uint32_t at = 0;
+  for (uint32_t f = 0; f < (uint32_t)kMaxFields; ++f) pl->bytes[f] = pl->width[f] = 1;
+  for (uint32_t w = 16; w; w /= 2) {
+    for (uint32_t f = 0; f < ft.n_fields; ++f) {
+      const uint32_t E = ft.bytes[f], epr = row_elements(E, ft.vec[f]);
+      if (!n || !ft.io[f] || (moves_wide(E, ft.vec[f]) ? 16u : ft.vec[f]) != w) continue;
+      pl->io[f] = ft.io[f];
+      pl->off[f] = (uint32_t)(ft.col[f] - ft.col[0]);   // (the fields of a row lie in the order of their numbers)
+      pl->bytes[f] = E;
+      pl->width[f] = w;
+      pl->recip[f] = epr > 1 ? 0xFFFFFFFFu / epr + 1u : 0u;
+      pl->first[f] = at;
+      at += (uint32_t)(((uint64_t)n * epr + 63u) / 64u);
+      pl->end[f] = at;
+    }
+  }
+}
+// Which of a gather's items every one of the rws row waves has: runs, or equally many (`even`).
+static void plan_shares(const FieldTable& ft, uint32_t n, uint32_t rws, bool even, uint2 (&share)[16]) {
+  uint64_t of_kind[kWidths];
+  const uint64_t total = items_by_width(ft, n, of_kind);
+  const uint32_t run = even ? 0u : gather_run(of_kind, n, rws);
+  uint32_t wave = 0;
+  if (run) {
+    uint32_t start = 0;
+    for (int c = 0; c < kWidths; ++c) {
+      const uint32_t end = start + (uint32_t)of_kind[c];
+      for (; start < end; start += run) share[wave++] = make_uint2(start, start + run < end ? start + run : end);
+      start = end;
+    }
+  } else {
+    const uint64_t each = (total + rws - 1) / rws;
+    for (uint64_t first = 0; first < total; first += each)
+      share[wave++] = make_uint2((uint32_t)first, (uint32_t)(first + each < total ? first + each : total));
+  }
 }
 
 // Whether one step (with n_insert new rows, or none) is faster as one launch of the kernel above than as the two or three
@@ -1937,7 +2115,7 @@ bool step_on_chip_pays(const Geom& g, const Tuning& tn, uint32_t n_insert, uint3
 }
 
 template <int LOGK>
-static hipError_t launch_run_steps_k(const Geom& g, const Tuning& tn, StreamArgs a, hipStream_t s) {
+static hipError_t launch_run_steps_k(const Geom& g, const Tuning& tn, const StreamCall& a, hipStream_t s) {
   StreamKernelArgs ka{};
   ka.g = g;
   ka.a = a;
@@ -1948,6 +2126,12 @@ static hipError_t launch_run_steps_k(const Geom& g, const Tuning& tn, StreamArgs
   // size (the tree copy and the row movers use all lanes)
   TeamForm form = team_form(a.B, a.n_insert);
   if (form != TEAM_ALL && !gathers_in_runs(a.rows, a.B, 16u - team_waves(a.B, a.n_insert))) form = a.ahead ? TEAM_WAVES_SPANS : TEAM_ALL;
+  for (uint32_t v = 0; v <= ka.a.levels; ++v) ka.a.nodes[v] = g.n[v * Wide<LOGK>::LH < g.H ? v * Wide<LOGK>::LH : g.H];
+  plan_pieces(a.rows, a.B, g.T, &ka.rows);
+  plan_pieces(a.ins, a.n_insert, g.T, &ka.ins);
+  plan_shares(a.rows, a.B, form == TEAM_ALL ? 16u : 16u - team_waves(a.B, a.n_insert), form == TEAM_ALL || form == TEAM_WAVES_SPANS, ka.share);
+  ka.a.rows_stride = a.rows.row_stride;
+  ka.a.ins_stride = a.ins.row_stride;
   const bool mem = ka.a.leaves_in_memory != 0;
 #define PER_RUN(F, M, A)                                                                                \
   do {                                                                                                  \
@@ -1973,7 +2157,7 @@ static hipError_t launch_run_steps_k(const Geom& g, const Tuning& tn, StreamArgs
   return hipGetLastError();
 }
 
-hipError_t launch_run_steps(const Geom& g, const Tuning& tn, const StreamArgs& a, hipStream_t s) {
+hipError_t launch_run_steps(const Geom& g, const Tuning& tn, const StreamCall& a, hipStream_t s) {
 #define CALL(L) launch_run_steps_k<L>(g, tn, a, s)
   PER_DISPATCH_LOGK(g.logK, CALL)
 #undef CALL

@@ -669,7 +669,7 @@ static bool step_on_chip(per_t* p, uint32_t n, const void* const* d_field_src, c
                         static_cast<const void*>(d_out_idx), static_cast<const void*>(d_out_weight),
                         static_cast<const void*>(d_out_prio), static_cast<const void*>(d_upd_prio)})
     if (misaligned(a, 4)) return false;
-  StreamArgs a{};
+  StreamCall a{};
   (void)fill_fields(p, d_field_dst, &a.rows);
   if (n) (void)fill_fields(p, const_cast<void* const*>(reinterpret_cast<const void* const*>(d_field_src)), &a.ins);
   if (!forced && !step_on_chip_pays(p->g, p->tn, n, B, a.rows, a.ins)) return false;
@@ -921,7 +921,7 @@ int per_run_steps(per_t* p, uint32_t n_steps, uint32_t n_insert, uint32_t B, con
   if (p->size == 0 && n_insert == 0) return PER_EEMPTY;
   hipStream_t s = static_cast<hipStream_t>(stream);
   CaptureGuard capture(p, s);
-  StreamArgs a{};
+  StreamCall a{};
   a.n_steps = n_steps;
   a.n_insert = n_insert;
   a.B = B;

@@ -161,10 +161,15 @@ struct StreamArgs {
   const float* upd_prio;            // [steps][T][B] or null: no update
   const float* ins_prio;            // [steps][T][n_insert] or null: running maximum
   uint32_t* ins_slots;              // one step: [T][n_insert] or null
-  FieldTable ins, rows;             // io arrays hold [steps][T][n][bytes]; io all null: nothing to move
+  // planned by the launcher
+  uint32_t rows_stride, ins_stride; // bytes between stored rows (of the gather's and of the insertion's fields)
   uint32_t off[kStreamLevels + 2];  // where level v of the LDS copy starts (floats); off[levels + 1] = all floats
+  uint32_t nodes[kStreamLevels + 1];// real nodes of every level
   uint32_t levels;                  // levels above the leaves (see Wide)
   uint32_t leaves_in_memory;        // the LDS copy holds the levels above the leaves only
+};
+struct StreamCall : StreamArgs {    // with the fields, of which the kernel has its own lists
+  FieldTable ins, rows;             // io arrays hold [steps][T][n][bytes]; io all null: nothing to move
 };
 
 // A queue of op-coded requests run by one workgroup per tree on an LDS copy of the tree (see k_run_requests).
@@ -299,7 +304,7 @@ void* step_static_claim(const void* holder, int device, hipStream_t s);
 void step_static_release(const void* holder, int device);
 bool stream_tree_fits(const Geom& g);
 bool step_on_chip_pays(const Geom& g, const Tuning& tn, uint32_t n_insert, uint32_t B, const FieldTable& rows, const FieldTable& ins);
-hipError_t launch_run_steps(const Geom& g, const Tuning& tn, const StreamArgs& a, hipStream_t s);
+hipError_t launch_run_steps(const Geom& g, const Tuning& tn, const StreamCall& a, hipStream_t s);
 hipError_t launch_run_requests(const Geom& g, const Tuning& tn, const QueueArgs& a, hipStream_t s);
 hipError_t launch_get_priority(const Geom& g, const Tuning& tn, uint32_t n, const uint32_t* idx, float* out, hipStream_t s);
 hipError_t launch_read_scalars(const Geom& g, int which, uint32_t weight_mode, float* out, hipStream_t s);

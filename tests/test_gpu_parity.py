@@ -743,6 +743,40 @@ def test_steps_on_the_chip(K, N, T, B, n, fb):
     m.compare_status()
 
 
+# A step by itself stores the paths of what it has changed.  Heights that a level's groups do not fill (K = 2: every remainder by
+# four, K = 4: by two), leaves in memory, one element and a full wave of them, and more paths than there are waves.
+PATHS = [(2, 33, 1, 1, 0), (2, 70, 2, 64, 1), (2, 150, 1, 65, 3), (2, 300, 1, 20, 60), (2, 37_500, 1, 40, 30), (4, 60, 1, 10, 5), (4, 1025, 2, 64, 64),
+         (4, 70_001, 1, 70, 100), (8, 513, 1, 512, 40), (16, 17, 3, 16, 17), (16, 200_003, 2, 130, 9), (32, 33_001, 1, 512, 512), (64, 65, 1, 3, 2)]
+
+
+@pytest.mark.parametrize("K,N,T,B,n", PATHS)
+def test_step_on_the_chip_stores_what_it_has_changed(K, N, T, B, n):
+    """Single steps against the oracle, every stored node after every one: with and without new rows (past the ring's end, given
+    priorities that are not valid among them), with no element that is valid, and on a tree without mass."""
+    log(f"paths of a step on the chip K={K} N={N} T={T} B={B} n={n}")
+    rng = np.random.default_rng(K * N + B)
+    m = Mirror(K, N, T, (5,))
+    m.gpu.set_tuning("step_on_chip", 2)
+    m.insert(N - N // 8, prio=np.zeros((T, N - N // 8), np.float32), chunk=1 << 18)
+    up = lambda: wl._draw_updates("absnormal1_eps_pow0.6", rng, (T, B))  # noqa: E731
+    m.step_call(wl.uniform01(rng, (T, B)), 0.4, True, up(), None)   # nothing to draw
+    m.compare_tree()
+    m.update(rng.integers(0, N - N // 8, (T, 400)).astype(np.uint32), rng.random((T, 400)).astype(np.float32))
+    for it in range(4):
+        u, v = wl.uniform01(rng, (T, B)), up()
+        if it == 1:
+            v[:] = np.float32("nan")
+        if n:
+            ins = (rng.random((T, n)) * 5).astype(np.float32) if it % 2 else None
+            if ins is not None:
+                ins[:, ::2] = np.float32("-1")
+            m.insert_step_call(n, ins, u, 0.4, True, v)
+        else:
+            m.step_call(u, 0.4, True, v, None)
+        m.compare_tree()
+    m.compare_status()
+
+
 # (whether one launch on an LDS copy is the way a step goes by default: shapes well on either side of the rule's line)
 STEP_WAYS = [(2, 4096, 1, 64, 4, (16, 4, 4, 16, 1), True), (16, 10000, 1, 32, 0, (), True), (16, 900, 1, 64, 4, (16, 4, 4, 16, 1), True),
              (4, 9000, 1, 40, 16, (12,), True), (64, 5000, 1, 32, 4, (16,), True), (16, 10000, 1, 300, 4, (16,), False),
