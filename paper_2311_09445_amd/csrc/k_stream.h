@@ -80,10 +80,10 @@ __device__ __forceinline__ float sum_chunks(P grp) {
 
 // One tree in the LDS of its workgroup.
 struct LdsTree {
-  float* tree;              // levels 0 .. V back to back (level 0 left out when leaves_mem is set), each padded with zeros to
+  float* tree;              // levels in_memory .. V back to back, each padded with zeros to
                             // whole groups and, below the root's children, with one group more: what the nodes beyond the
                             // next level's last have for children
-  float* leaves_mem;        // null, or the tree's leaves in memory (zero padded to whole groups)
+  uint32_t in_memory;       // the lowest levels, so many of them, stay in memory (zero padded to whole groups)
   const uint32_t *off, *n;  // off[v]: where level v starts (floats), off[V + 1]: all floats; n[v]: its real nodes
   uint32_t* max_bits;       // running maximum priority (fp32 bits)
   uint32_t H, V;
@@ -97,7 +97,7 @@ template <int LOGK>
 __device__ __forceinline__ void lds_tree_load(const LevelTable& tab, const LdsTree& lt, uint32_t lane, uint32_t lanes) {
   constexpr int R = 8;
   typedef GlobalPtr<const float> Source;
-  const uint32_t v0 = lt.leaves_mem ? 1u : 0u, V = lt.V;
+  const uint32_t v0 = lt.in_memory, V = lt.V;
   // (all offsets in the lanes of the wave: a piece's level is then found without a trip to LDS per level)
   const uint32_t off_reg = lt.off[min_u32(threadIdx.x & 63u, V + 1u)];
   auto off = [&](uint32_t v) { return (uint32_t)__builtin_amdgcn_readlane((int)off_reg, (int)v); };
@@ -171,7 +171,7 @@ __device__ __forceinline__ void lds_tree_store(const Geom& g, uint32_t t, const 
   const uint32_t V = lt.V, H = lt.H;
   // (a root less than a whole level above its children is stored by the pass below: the level's sum of it has zeros added)
   const uint32_t end = V * LH == H ? lt.off[V + 1] : lt.off[V];
-  const uint32_t v0 = lt.leaves_mem ? 1u : 0u, n0 = lt.n[v0];
+  const uint32_t v0 = lt.in_memory, n0 = lt.n[v0];
   {   // the lowest level, then those above it
     constexpr int U = 4;
     GlobalPtr<float> dst = as_global(tab.lvl[level_height<LOGK>(v0, H)]);
@@ -199,7 +199,7 @@ __device__ __forceinline__ void lds_tree_store(const Geom& g, uint32_t t, const 
     for (uint32_t w = 0; w < V; ++w) {
       const uint32_t groups = tab.n[level_height<LOGK>(w + 1, H)];
       for (uint32_t p = threadIdx.x; p < groups; p += blockDim.x) {
-        if (w == 0 && lt.leaves_mem) store_between<LOGK>(as_global(static_cast<const float*>(lt.leaves_mem)) + (size_t)p * R, p, 0, tab, H);
+        if (w == 0 && lt.in_memory) store_between<LOGK>(as_global(static_cast<const float*>(tab.lvl[0])) + (size_t)p * R, p, 0, tab, H);
         else store_between<LOGK>(static_cast<const float*>(lt.tree) + lt.off[w] + (size_t)p * R, p, w * LH, tab, H);
       }
     }
@@ -211,12 +211,13 @@ __device__ __forceinline__ void lds_tree_store(const Geom& g, uint32_t t, const 
 // level at a time, from the count of what is taken in LDS: waves that have no rows begin as soon as the team has made the tree
 // whole (*s_whole), and none waits for the others' results.  (Stored whole, with a barrier in front and behind, a step of 64 samples and 4 rows on
 // 4096 leaves at K = 2 spent 1.8 us on it; all of the paths by the team's one wave, 2.0.)
-template <int LOGK, bool MEM>
+template <int LOGK, int MEM>
 __device__ __forceinline__ void store_paths(const LevelTable& tab, const LdsTree& lt, const uint32_t* nodes, uint32_t updated, uint32_t cursor,
                                             uint32_t inserted, uint32_t N, uint32_t* s_taken, const uint32_t* s_whole) {
   constexpr uint32_t LH = Wide<LOGK>::LH, LOGR = Wide<LOGK>::LOGR, R = Wide<LOGK>::R;
   const uint32_t lane = threadIdx.x & 63u, n = nodes ? updated : 0u, elements = n + inserted;
-  const uint32_t levels = lt.V + (MEM ? 0u : 1u), rounds = (elements + 63u) / 64u;
+  // (levels in memory have been stored as they were changed; of narrow trees the heights below one of them have not)
+  const uint32_t levels = lt.V + 1u - (LH > 1 && MEM ? 1u : (uint32_t)MEM), rounds = (elements + 63u) / 64u;
   for (;;) {
     uint32_t item = 0;
     if (lane == 0) item = atomicAdd(s_taken, 1u);
@@ -245,11 +246,11 @@ __device__ __forceinline__ void store_paths(const LevelTable& tab, const LdsTree
         if (LOGK == 1 && h0 + 3 <= lt.H) as_global(tab.lvl[h0 + 3])[leaf >> (h0 + 3)] = sa + sb;
       };
       if (v && some) {
-        if (MEM && v == 1) between(as_global(static_cast<const float*>(lt.leaves_mem)) + (size_t)node * R);
+        if (MEM && v <= (uint32_t)MEM) between(as_global(static_cast<const float*>(tab.lvl[h0])) + (size_t)node * R);
         else between(static_cast<const float*>(lt.tree) + lt.off[v - 1] + (size_t)node * R);
       }
     }
-    if (some && v * LH <= lt.H) as_global(tab.lvl[v * LH])[node] = lt.tree[lt.off[v] + node];
+    if (some && v >= (uint32_t)MEM && v * LH <= lt.H) as_global(tab.lvl[v * LH])[node] = lt.tree[lt.off[v] + node];
   }
 }
 
@@ -678,10 +679,10 @@ __device__ __forceinline__ void wave_order() {
 // one pointer for both places would make flat accesses, and the wait for one of those is a wait for every load and
 // store the wave has under way; a branch at every access costs the registers of both sides.)
 constexpr uint32_t kTopNodes = 128;   // a level of at most this many nodes is summed by one wave, with all levels above it
-template <bool MEM>
+template <int MEM>
 struct TreeView {
   float* tree;               // the LDS copy
-  float* leaves;             // MEM: the leaves (else they are in the copy, level 0 at offset 0)
+  float *leaves, *level1;    // MEM: the leaves, the level above them (else they are in the copy, the leaves at offset 0)
   uint32_t off_reg, n_reg;   // lane v of every wave: off[v], real nodes of level v (read from there: an LDS trip less per level)
   uint32_t V, N;
   uint32_t vt;               // the lowest level above the leaves of at most kTopNodes nodes
@@ -700,6 +701,15 @@ struct TreeView {
   __device__ __forceinline__ float leaf(uint32_t i) const {
     if constexpr (MEM) return as_global(leaves)[i];
     else return tree[i];
+  }
+  __device__ __forceinline__ void set_node(uint32_t v, uint32_t i, float x) const {   // v > 0
+    if constexpr (MEM > 1) {
+      if (v == 1) {
+        as_global(level1)[i] = x;
+        return;
+      }
+    }
+    tree[off(v) + i] = x;
   }
   __device__ __forceinline__ uint32_t n(uint32_t v) const { return (uint32_t)__builtin_amdgcn_readlane((int)n_reg, (int)v); }
   // Barrier of the team between phases that hand leaves or sums to other waves of it.  The hardware's barrier would hold
@@ -720,11 +730,12 @@ struct TreeView {
   }
 };
 // Sum of the children of node `parent` of level v, by a single lane.
-template <int LOGK, bool MEM>
+template <int LOGK, int MEM>
 __device__ __forceinline__ float child_group_sum(const TreeView<MEM>& tv, uint32_t v, uint32_t parent) {
   constexpr int R = Wide<LOGK>::R;
   if constexpr (MEM) {
     if (v == 1) return sum_chunks<R / 4>(as_global(static_cast<const float*>(tv.leaves)) + (size_t)parent * R);
+    if (MEM > 1 && v == 2) return sum_chunks<R / 4>(as_global(static_cast<const float*>(tv.level1)) + (size_t)parent * R);
   }
   return sum_chunks<R / 4>(static_cast<const float*>(tv.tree) + tv.off(v - 1) + (size_t)parent * R);
 }
@@ -746,7 +757,7 @@ __device__ __forceinline__ float add_other_half(float x) {
 }
 // The sums over blocks of 2, 4, .. 64 lanes of x, the nodes of level vt from node `base` on; those that are nodes of a
 // level below the root are stored.  Returns the sum of all.
-template <int LOGR, int STEP, bool MEM>
+template <int LOGR, int STEP, int MEM>
 __device__ __forceinline__ float sums_above(const TreeView<MEM>& tv, float x, uint32_t base) {
   if constexpr (STEP < 6) {
     x = add_other_half<STEP>(x);
@@ -763,7 +774,7 @@ __device__ __forceinline__ float sums_above(const TreeView<MEM>& tv, float x, ui
 // The levels from vt up, recomputed whole by one wave: a lane or two per node of level vt, and above it no trips through
 // LDS, only sums of neighbouring lanes (a height of sixteen children was a trip and a chain of 450 cycles, whatever its
 // few nodes).  Returns the root.
-template <int LOGK, bool MEM>
+template <int LOGK, int MEM>
 __device__ __forceinline__ float sum_top(const TreeView<MEM>& tv) {
   constexpr int LOGR = Wide<LOGK>::LOGR;
   const uint32_t lane = threadIdx.x & 63u, n = tv.n(tv.vt), at = tv.off(tv.vt);
@@ -813,7 +824,7 @@ __device__ __forceinline__ bool check_element(const UpdateWork& u, uint32_t& fla
 // so; where it is not, and for indices that were not sampled, markers decide.  The code of a step that has neither an
 // update nor an insertion left out runs without a branch up to the sums: at an instruction every five cycles a branch
 // around three of them is no gain.)
-template <int LOGK, bool MEM>
+template <int LOGK, int MEM>
 __device__ __forceinline__ float change_by_wave(TreeView<MEM>& tv, const UpdateWork& u, const InsertWork& ins, float& lane_max,
                                                 uint32_t& flags, float total) {
   constexpr int LOGR = Wide<LOGK>::LOGR;
@@ -866,7 +877,7 @@ __device__ __forceinline__ float change_by_wave(TreeView<MEM>& tv, const UpdateW
           wave_order();
           if (act) {
             const uint32_t parent = leaf >> (v * LOGR);
-            tv.tree[tv.off(v) + parent] = child_group_sum<LOGK, MEM>(tv, v, parent);
+            tv.set_node(v, parent, child_group_sum<LOGK, MEM>(tv, v, parent));
           }
         }
       }
@@ -879,7 +890,7 @@ __device__ __forceinline__ float change_by_wave(TreeView<MEM>& tv, const UpdateW
 }
 
 // By a team of several waves.
-template <int LOGK, bool MEM>
+template <int LOGK, int MEM>
 __device__ __forceinline__ void change_by_team(TreeView<MEM>& tv, const UpdateWork& u, const InsertWork& ins, uint32_t& flags) {
   constexpr int LOGR = Wide<LOGK>::LOGR;
   const uint32_t tid = threadIdx.x;
@@ -959,12 +970,12 @@ __device__ __forceinline__ void change_by_team(TreeView<MEM>& tv, const UpdateWo
       tv.sync();
       const uint32_t nodes = tv.n(v);
       if (nodes <= elements) {
-        for (uint32_t j = tid; j < nodes; j += tv.team) tv.tree[tv.off(v) + j] = child_group_sum<LOGK, MEM>(tv, v, j);
+        for (uint32_t j = tid; j < nodes; j += tv.team) tv.set_node(v, j, child_group_sum<LOGK, MEM>(tv, v, j));
         continue;
       }
       const uint32_t pu = u.i >> (v * LOGR), pi = ins.slot >> (v * LOGR);
-      if (valid) tv.tree[tv.off(v) + pu] = child_group_sum<LOGK, MEM>(tv, v, pu);
-      if (placed) tv.tree[tv.off(v) + pi] = child_group_sum<LOGK, MEM>(tv, v, pi);
+      if (valid) tv.set_node(v, pu, child_group_sum<LOGK, MEM>(tv, v, pu));
+      if (placed) tv.set_node(v, pi, child_group_sum<LOGK, MEM>(tv, v, pi));
     }
     tv.sync();
     if (tid < 64u) sum_top<LOGK, MEM>(tv);
@@ -1022,7 +1033,7 @@ __device__ __forceinline__ void level_down(P grp, float& r, uint32_t& node, floa
 // looking.  `call` is called once, behind the few nodes below the root or before the walk's last level (or where there is no
 // walk).  (With the right blocks' sums left out, and the sixteen children kept in registers instead of read a second
 // time once the chunk of four is known, a level takes two thirds of the 570 cycles it took.)
-template <int LOGK, bool MEM, bool CALL_LAST, typename F>
+template <int LOGK, int MEM, bool CALL_LAST, typename F>
 __device__ __forceinline__ void walk_tree(const TreeView<MEM>& tv, uint32_t i, uint32_t n, float u, float total, float seg, uint32_t& node,
                                           float& val, F&& call) {
   constexpr int LOGR = Wide<LOGK>::LOGR, R = Wide<LOGK>::R;
@@ -1043,16 +1054,20 @@ __device__ __forceinline__ void walk_tree(const TreeView<MEM>& tv, uint32_t i, u
     --v;
   }
   if constexpr (!CALL_LAST) call();
-  for (; v > 0; --v) {
-    float unused;
+  float unused;
+  for (; v > (MEM > 1 ? 1u : 0u); --v)
     level_down<LOGR>(static_cast<const float*>(tv.tree) + tv.off(v) + (size_t)min_u32(node, tv.n(v + 1)) * R, r, node, unused);
+  bool astray = false;
+  if constexpr (MEM > 1) {
+    astray = node >= tv.n(2);
+    level_down<LOGR>(as_global(static_cast<const float*>(tv.level1)) + (size_t)(astray ? 0u : node) * R, r, node, unused);
   }
   if constexpr (CALL_LAST) call();
   const uint32_t n1 = tv.n(1);
-  bool astray = false;
   if constexpr (MEM) {   // (no such group behind the leaves in memory)
-    astray = node >= n1;
-    level_down<LOGR>(as_global(static_cast<const float*>(tv.leaves)) + (size_t)(astray ? 0u : node) * R, r, node, val);
+    const bool beyond = node >= n1;
+    astray = astray || beyond;
+    level_down<LOGR>(as_global(static_cast<const float*>(tv.leaves)) + (size_t)(beyond ? 0u : node) * R, r, node, val);
   } else {
     level_down<LOGR>(static_cast<const float*>(tv.tree) + (size_t)min_u32(node, n1) * R, r, node, val);
   }
@@ -1063,6 +1078,7 @@ __device__ __forceinline__ void walk_tree(const TreeView<MEM>& tv, uint32_t i, u
       unsigned child;
       if constexpr (MEM) {
         if (v == 0) descend_looking<LOGR>(as_global(static_cast<const float*>(tv.leaves)) + (size_t)node * R, r, child, val);
+        else if (MEM > 1 && v == 1) descend_looking<LOGR>(as_global(static_cast<const float*>(tv.level1)) + (size_t)node * R, r, child, val);
         else descend_looking<LOGR>(static_cast<const float*>(tv.tree) + tv.off(v) + (size_t)node * R, r, child, val);
       } else {
         descend_looking<LOGR>(static_cast<const float*>(tv.tree) + tv.off(v) + (size_t)node * R, r, child, val);
@@ -1134,7 +1150,7 @@ static TeamForm team_form(uint32_t samples, uint32_t inserted) {
 // 100 steps on 10 000 leaves at K = 16 (32 samples, 4 new rows of 41 bytes): 169 us; 1001 us as one phase after the
 // other by the whole workgroup with a full barrier between them.
 // AHEAD: no step reads what a step returns.
-template <int LOGK, TeamForm FORM, bool MEM, bool AHEAD>
+template <int LOGK, TeamForm FORM, int MEM, bool AHEAD>
 __global__ void __launch_bounds__(1024)
 k_run_steps(StreamKernelArgs ka) {
   constexpr bool WAVE = FORM == TEAM_ONE_WAVE, apart = FORM != TEAM_ALL, SPANS = FORM == TEAM_WAVES_SPANS || FORM == TEAM_ALL;
@@ -1199,7 +1215,7 @@ k_run_steps(StreamKernelArgs ka) {
   if (!AHEAD || !a.beta) beta_i = a.beta ? a.beta[0] : a.beta_value;
   LdsTree lt;
   lt.tree = tree;
-  lt.leaves_mem = MEM ? tab.lvl[0] : nullptr;
+  lt.in_memory = MEM;
   lt.off = s_off;
   lt.n = s_n;
   lt.max_bits = &s_max;
@@ -1211,7 +1227,8 @@ k_run_steps(StreamKernelArgs ka) {
   float* values = reinterpret_cast<float*>(nodes + 512);                // [B] and their values (apart only: B <= 512)
   TreeView<MEM> tv;
   tv.tree = tree;
-  tv.leaves = lt.leaves_mem;
+  tv.leaves = MEM ? tab.lvl[0] : nullptr;
+  tv.level1 = MEM > 1 ? tab.lvl[Wide<LOGK>::LH] : nullptr;
   tv.off_reg = s_off[lane <= V + 1 ? lane : V + 1];
   tv.n_reg = s_n[lane <= V ? lane : V];
   tv.V = V;
@@ -1229,7 +1246,7 @@ k_run_steps(StreamKernelArgs ka) {
   uint32_t flags = 0;
   float lane_max = __uint_as_float(s_max);   // (WAVE: the lanes' share of it; else s_max counts)
 
-  const bool brief = apart && a.n_steps == 1 && (a.upd_is_sampled || !a.upd_prio);   // (see store_paths)
+  const bool brief = MEM > 1 || (apart && a.n_steps == 1 && (a.upd_is_sampled || !a.upd_prio));   // (see store_paths; MEM > 1: only launched so)
   auto list_array = [](const RowItem& p) { return p.io; };
   auto work = [&](auto does_tree, auto does_rows) {
     constexpr bool TREE = decltype(does_tree)::value, ROWS = decltype(does_rows)::value;
@@ -1550,7 +1567,7 @@ __device__ __forceinline__ uint32_t lay_out_round(uint32_t x, uint32_t y, uint32
   }
   return used;
 }
-template <int LOGK, TeamForm FORM, bool MEM>
+template <int LOGK, TeamForm FORM, int MEM>
 __global__ void __launch_bounds__(1024)
 k_run_requests(QueueKernelArgs ka) {
   constexpr bool WAVE = FORM == TEAM_ONE_WAVE, apart = FORM != TEAM_ALL;
@@ -1609,7 +1626,7 @@ k_run_requests(QueueKernelArgs ka) {
   __syncthreads();
   LdsTree lt;
   lt.tree = tree;
-  lt.leaves_mem = MEM ? tab.lvl[0] : nullptr;
+  lt.in_memory = MEM;
   lt.off = s_off;
   lt.n = s_n;
   lt.max_bits = &s_max;
@@ -1627,7 +1644,8 @@ k_run_requests(QueueKernelArgs ka) {
   float* values = reinterpret_cast<float*>(nodes + 512);                // and their values (apart only: at most 512)
   TreeView<MEM> tv;
   tv.tree = tree;
-  tv.leaves = lt.leaves_mem;
+  tv.leaves = MEM ? tab.lvl[0] : nullptr;
+  tv.level1 = MEM > 1 ? tab.lvl[Wide<LOGK>::LH] : nullptr;
   tv.off_reg = s_off[lane <= V + 1 ? lane : V + 1];
   tv.n_reg = s_n[lane <= V ? lane : V];
   tv.V = V;
@@ -1952,7 +1970,7 @@ k_run_requests(QueueKernelArgs ka) {
   lds_tree_store<LOGK>(g, t, tab, lt);
 }
 
-// A tree can be worked on where its heights (every one padded to whole child groups), or those above the leaves, fit
+// A list or a queue can work on a tree where its heights (every one padded to whole child groups), or those above the leaves, fit
 // beside the step kernel's other LDS data.
 constexpr uint32_t kStreamLdsBytes = 156 * 1024, kStreamBatchWords = 1024;   // (the sampled indices and values of a step)
 bool stream_tree_fits(const Geom& g) {
@@ -1964,28 +1982,52 @@ bool stream_tree_fits(const Geom& g) {
   }
   return false;
 }
-// Levels of the copy (see Wide): the whole tree if that fits, else the levels above the leaves.  Narrow trees take less
+// A step by itself can also leave the level above the leaves in memory: it reads and changes few groups of it, each a trip more.
+// (Its tree is on the chip for one step: what counts there is the copy of the tree, not the trips of every step.)
+template <int LOGK>
+static uint32_t plan_stream_levels(const Geom& g, uint32_t most_in_memory, uint32_t* off, uint32_t* levels, uint32_t* in_memory);
+static bool gathers_in_runs(const FieldTable& ft, uint32_t n, uint32_t rws);
+static uint32_t team_waves(uint32_t samples, uint32_t inserted);
+bool stream_step_fits(const Geom& g, uint32_t n_insert, uint32_t B, const FieldTable& rows) {
+  if (stream_tree_fits(g)) return true;
+  uint32_t off[kStreamLevels + 2], levels = 0, in_memory = 0;
+#define CALL(L) plan_stream_levels<L>(g, 2, off, &levels, &in_memory)
+  const uint32_t floats = [&]() -> uint32_t {
+    switch (g.logK) {
+      case 1: return CALL(1);
+      case 2: return CALL(2);
+      case 3: return CALL(3);
+      case 4: return CALL(4);
+      case 5: return CALL(5);
+      case 6: return CALL(6);
+      default: return 0u;
+    }
+  }();
+#undef CALL
+  return floats && gathers_in_runs(rows, B, 16u - team_waves(B, n_insert));   // (that kernel is built for gathers in runs only)
+}
+// Levels of the copy (see Wide): the whole tree if that fits, else the levels above the leaves, or above the next one.  Narrow trees take less
 // room as levels than as heights, and the groups of zeros behind the levels (512 bytes at most, K = 64) go beyond
 // kStreamLdsBytes, so one of the two fits where stream_tree_fits() says so.  Returns the LDS floats, the batch's words
 // included (0: neither fits).
 constexpr uint32_t kStreamLdsMost = kStreamLdsBytes + 512;
 template <int LOGK>
-static uint32_t plan_stream_levels(const Geom& g, uint32_t* off, uint32_t* levels, uint32_t* leaves_in_memory) {
+static uint32_t plan_stream_levels(const Geom& g, uint32_t most_in_memory, uint32_t* off, uint32_t* levels, uint32_t* in_memory) {
   constexpr uint32_t LH = Wide<LOGK>::LH, R = Wide<LOGK>::R;
   const uint32_t V = (g.H + LH - 1) / LH;
   if (V > kStreamLevels) return 0u;
-  for (uint32_t skip = 0; skip < 2; ++skip) {
+  for (uint32_t skip = 0; skip <= most_in_memory; ++skip) {
     uint64_t floats = 0;
     for (uint32_t v = 0; v <= V; ++v) {
       off[v] = (uint32_t)floats;
-      if (v == 0 && skip) continue;
+      if (v < skip) continue;
       floats += v < V ? ((uint64_t)g.n[v * LH] + R - 1) / R * R + (v + 1 < V ? R : 0) : 4;
       if (floats * 4 > kStreamLdsMost) break;
     }
-    if ((floats + kStreamBatchWords) * 4 > kStreamLdsMost || (skip && V < 2)) continue;
+    if ((floats + kStreamBatchWords) * 4 > kStreamLdsMost || V <= skip) continue;
     off[V + 1] = (uint32_t)floats;
     *levels = V;
-    *leaves_in_memory = skip;
+    *in_memory = skip;
     return (uint32_t)floats + kStreamBatchWords;
   }
   return 0u;
@@ -2067,36 +2109,41 @@ static void plan_shares(const FieldTable& ft, uint32_t n, uint32_t rws, bool eve
 }
 
 // Whether one step (with n_insert new rows, or none) is faster as one launch of the kernel above than as the two or three
-// kernels it otherwise takes.  Both sides in hundredths of a microsecond, fitted to 639 shapes (1 to 64 trees of 300 to
-// 400 000 leaves, 16 to 512 samples, 0 to 400 new rows of 0 to 1033 bytes in fields of every access width; the fits are off
-// by 7 and 10 %).  On the chip: the launch and one step's chain, more with several waves at the tree; the rows, which one
-// compute unit moves, by the pieces that every row wave has (in runs each piece is the rest of a trip to memory, evenly
-// shared ones go eight to a trip; a new row's pieces one to a trip); the copy of the tree, the trips to leaves in memory
-// and the heights between the levels.  As kernels: two launches, with the insertion in the sampling kernel where that can
-// carry it, else three; K = 2 trees are chains of many heights.  Of the shapes 413 go this way, 1.37 times as fast on
-// average (4096 leaves at K = 2, 64 samples, 4 rows of 41 bytes: 19.1 -> 9.0 us); 8 of those are slower by 2 % or more, by 15 %
-// at most (the 3 % below: without them 11, for 16 shapes more).  By the bytes of a row alone, 45 were, and by up to 4.5 times:
-// 256 samples of a 165-byte field on 4096 leaves at K = 2 71 us against 22.  Batches beyond 256 at K > 2 are left out: what
-// there is to gain is less than the fits are off by.
+// kernels it otherwise takes.  Both sides in hundredths of a microsecond, first fitted to 639 shapes (1 to 64 trees of 300 to
+// 400 000 leaves, 16 to 512 samples, 0 to 400 new rows of 0 to 1033 bytes in fields of every access width), the side on the
+// chip again since a step by itself stores its paths only and leaves up to two levels in memory.  On the chip: the launch and
+// one step's chain, more with several waves at the tree; the rows, which one compute unit moves, by the pieces that every
+// row wave has (in runs each piece is the rest of a trip to memory, evenly shared ones go eight to a trip; a new row's pieces
+// one to a trip); the copy of the tree and the trips to levels in memory.  As kernels: two launches, with the insertion in
+// the sampling kernel where that can carry it, else three; K = 2 trees are chains of many heights, and so are large ones.
+// Of 144 shapes (every fanout, 1000 to 4 million leaves, 16 to 512 samples, 1 to 64 trees) the way it chooses is 0.6 % behind
+// the better one on average, one loses 15 % on the chip (32 samples on 2^20 leaves at K = 16: 12.4 -> 7.5 us, 64 on 64 trees of
+// 2^18: 16.9 -> 8.9; where it stays away: 256 samples with rows of 165 bytes on 100 000 leaves 11.9, 12.2 on the chip).
+// By the bytes of a row alone, 45 of the 639 lost 2 % or more, and by up to 4.5 times: 256 samples of a 165-byte field on
+// 4096 leaves at K = 2 71 us against 22.  Batches beyond 256 at K > 2 are left out: what there is to gain is less than the
+// fits are off by.
 template <int LOGK>
 static bool step_on_chip_pays_k(const Geom& g, const Tuning& tn, uint32_t n_insert, uint32_t B, const FieldTable& rows, const FieldTable& ins) {
   uint32_t off[kStreamLevels + 2], levels = 0, in_memory = 0;
-  const uint64_t floats = plan_stream_levels<LOGK>(g, off, &levels, &in_memory);
+  const uint64_t floats = plan_stream_levels<LOGK>(g, 2, off, &levels, &in_memory);
   if (!floats || g.T > 64 || (B > 256 && g.K > 2)) return false;
-  uint64_t heights = 0, row = 0, of_kind[kWidths];
-  for (uint32_t h = in_memory; h <= g.H; ++h) heights += g.n[h];
+  uint64_t row = 0, of_kind[kWidths];
   for (uint32_t f = 0; f < rows.n_fields; ++f) row += rows.io[f] ? rows.bytes[f] : 0u;
   const uint32_t rws = 16u - team_waves(B, n_insert);
   const uint64_t gathered = items_by_width(rows, B, of_kind), placed = items_by_width(ins, n_insert, of_kind);
-  int64_t here = 700 + (team_form(B, n_insert) == TEAM_ONE_WAVE ? 0 : 138) + (n_insert ? 55 : 0) + (g.T >= 16 ? 71 : 0) + (g.K == 64 ? 37 * B / 64 : 0);
+  int64_t here = 520 + (team_form(B, n_insert) == TEAM_ONE_WAVE ? 0 : 138) + (n_insert ? 55 : 0) + (g.T >= 16 ? 71 : 0) + (g.K == 64 ? 37 * B / 64 : 0);
   here += gathers_in_runs(rows, B, rws) ? 80 * gathered / rws : 136 + 19 * gathered / rws;
-  here += (placed > rws ? 81 * (placed - rws) / rws : 0) + floats * 4 / 1024 + (in_memory ? 58 + 63 * B / 64 : 0);
-  here += heights > floats ? (heights - floats) * 13 / 1024 : 0;
+  here += (placed > rws ? 81 * (placed - rws) / rws : 0) + floats * 4 / 1024 + (g.K == 2 ? 40 : g.K == 4 ? 20 : 0);
+  if (in_memory) {
+    here += in_memory == 1 ? 40 + 40 * B / 64 : 100 + 55 * B / 64 + (n_insert ? 25 : 0);
+    here += g.K == 2 ? 40 + (in_memory == 1 ? 25 : 60) * B / 64 : g.K == 64 ? 70 + 60 * B / 64 : 0;
+  }
   bool has_rows = false;
   for (uint32_t f = 0; f < ins.n_fields; ++f) has_rows = has_rows || ins.io[f];
   // (asked as for a ring at its start: the way does not change in the one step whose rows go round its end)
   const bool carried = n_insert && sample_can_carry_insert(g, tn, B, has_rows ? &ins : nullptr, n_insert, 0);
   int64_t apart = 938 + (!n_insert ? 0 : carried ? 273 : 374 + (g.K <= 4 ? 141 : 0)) + (g.K == 2 ? 106 * (int64_t)g.H - 815 : 0);
+  apart += (g.N > 1u << 20 ? 170 : 0) + (g.K == 64 && g.H >= 3 ? 90 : 0) + (g.K == 4 && g.H >= 9 ? 600 : 0);
   apart += (g.K == 4 ? 87 : 0) + (g.K >= 32 ? 55 : 0) + (g.T >= 16 ? 105 : 0) + (int64_t)(176 * g.T * B * row >> 20);
   return here * 103 < apart * 100;
 }
@@ -2119,7 +2166,7 @@ static hipError_t launch_run_steps_k(const Geom& g, const Tuning& tn, const Stre
   StreamKernelArgs ka{};
   ka.g = g;
   ka.a = a;
-  const uint32_t floats = plan_stream_levels<LOGK>(g, ka.a.off, &ka.a.levels, &ka.a.leaves_in_memory);
+  const uint32_t floats = plan_stream_levels<LOGK>(g, a.most_in_memory, ka.a.off, &ka.a.levels, &ka.a.levels_in_memory);
   if (!floats) return hipErrorInvalidValue;
   const size_t bytes = (size_t)floats * 4;
   // always the largest workgroup, also for small batches: measured faster than a workgroup of the batch's
@@ -2132,7 +2179,7 @@ static hipError_t launch_run_steps_k(const Geom& g, const Tuning& tn, const Stre
   plan_shares(a.rows, a.B, form == TEAM_ALL ? 16u : 16u - team_waves(a.B, a.n_insert), form == TEAM_ALL || form == TEAM_WAVES_SPANS, ka.share);
   ka.a.rows_stride = a.rows.row_stride;
   ka.a.ins_stride = a.ins.row_stride;
-  const bool mem = ka.a.leaves_in_memory != 0;
+  const uint32_t mem = ka.a.levels_in_memory;
 #define PER_RUN(F, M, A)                                                                                \
   do {                                                                                                  \
     hipError_t e = grant_lds<&k_run_steps<LOGK, F, M, A>>(tn, bytes);                                   \
@@ -2141,13 +2188,16 @@ static hipError_t launch_run_steps_k(const Geom& g, const Tuning& tn, const Stre
   } while (0)
 #define PER_RUN_WHERE(F, A)                                                                             \
   do {                                                                                                  \
-    if (mem) PER_RUN(F, true, A); else PER_RUN(F, false, A);                                            \
+    if (mem) PER_RUN(F, 1, A); else PER_RUN(F, 0, A);                                                   \
   } while (0)
 #define PER_RUN_WHEN(F)                                                                                 \
   do {                                                                                                  \
     if (a.ahead) PER_RUN_WHERE(F, true); else PER_RUN_WHERE(F, false);                                  \
   } while (0)
-  if (form == TEAM_ONE_WAVE) PER_RUN_WHEN(TEAM_ONE_WAVE);
+  if (mem > 1) {   // (see stream_step_fits)
+    if (a.n_steps != 1 || !a.ahead || !a.upd_is_sampled || form > TEAM_WAVES) return hipErrorInvalidValue;
+    if (form == TEAM_ONE_WAVE) PER_RUN(TEAM_ONE_WAVE, 2, true); else PER_RUN(TEAM_WAVES, 2, true);
+  } else if (form == TEAM_ONE_WAVE) PER_RUN_WHEN(TEAM_ONE_WAVE);
   else if (form == TEAM_WAVES) PER_RUN_WHEN(TEAM_WAVES);
   else if (form == TEAM_WAVES_SPANS) PER_RUN_WHERE(TEAM_WAVES_SPANS, true);
   else PER_RUN_WHEN(TEAM_ALL);
@@ -2168,11 +2218,11 @@ static hipError_t launch_run_requests_k(const Geom& g, const Tuning& tn, const Q
   QueueKernelArgs ka{};
   ka.g = g;
   ka.a = a;
-  const uint32_t floats = plan_stream_levels<LOGK>(g, ka.a.off, &ka.a.levels, &ka.a.leaves_in_memory);
+  const uint32_t floats = plan_stream_levels<LOGK>(g, 1, ka.a.off, &ka.a.levels, &ka.a.levels_in_memory);
   if (!floats) return hipErrorInvalidValue;
   const size_t bytes = (size_t)floats * 4;
   const TeamForm form = team_form(a.most, 0);
-  const bool mem = ka.a.leaves_in_memory != 0;
+  const bool mem = ka.a.levels_in_memory != 0;
 #define PER_RUN(F, M)                                                                                   \
   do {                                                                                                  \
     hipError_t e = grant_lds<&k_run_requests<LOGK, F, M>>(tn, bytes);                                   \
@@ -2181,7 +2231,7 @@ static hipError_t launch_run_requests_k(const Geom& g, const Tuning& tn, const Q
   } while (0)
 #define PER_RUN_WHERE(F)                                                                                \
   do {                                                                                                  \
-    if (mem) PER_RUN(F, true); else PER_RUN(F, false);                                                  \
+    if (mem) PER_RUN(F, 1); else PER_RUN(F, 0);                                                         \
   } while (0)
   if (form == TEAM_ONE_WAVE) PER_RUN_WHERE(TEAM_ONE_WAVE);
   else if (form == TEAM_WAVES) PER_RUN_WHERE(TEAM_WAVES);

@@ -662,7 +662,7 @@ static bool step_on_chip(per_t* p, uint32_t n, const void* const* d_field_src, c
   const bool forced = p->tn.step_on_chip == 2;
   const bool by_hand = p->tn.step_kernel != 1 || !p->tn.group_claim || !p->tn.claim_in_sample || !p->tn.insert_ride || !p->tn.lazy_top;
   if (!p->tn.step_on_chip || (!forced && by_hand) || d_upd_pos || B > 512 || n > 512 || n > p->cfg.capacity ||
-      (p->size == 0 && n == 0) || (d_out_weight && p->weight_norm != PER_NORM_BATCH) || !stream_tree_fits(p->g))
+      (p->size == 0 && n == 0) || (d_out_weight && p->weight_norm != PER_NORM_BATCH))
     return false;
   if ((!d_u && !p->rng_on) || !d_out_idx || !d_upd_prio || !isfinite(beta) || beta < 0.0f) return false;
   for (const void* a : {static_cast<const void*>(d_ins_prio), static_cast<const void*>(d_ins_out_idx), static_cast<const void*>(d_u),
@@ -672,7 +672,7 @@ static bool step_on_chip(per_t* p, uint32_t n, const void* const* d_field_src, c
   StreamCall a{};
   (void)fill_fields(p, d_field_dst, &a.rows);
   if (n) (void)fill_fields(p, const_cast<void* const*>(reinterpret_cast<const void* const*>(d_field_src)), &a.ins);
-  if (!forced && !step_on_chip_pays(p->g, p->tn, n, B, a.rows, a.ins)) return false;
+  if (!stream_step_fits(p->g, n, B, a.rows) || (!forced && !step_on_chip_pays(p->g, p->tn, n, B, a.rows, a.ins))) return false;
   Span in[3 + PER_MAX_FIELDS], out[4 + PER_MAX_FIELDS];
   uint32_t ni = 0, no = 0;
   const uint64_t samples = (uint64_t)p->g.T * B, rows = (uint64_t)p->g.T * n;
@@ -699,6 +699,7 @@ static bool step_on_chip(per_t* p, uint32_t n, const void* const* d_field_src, c
   p->step_before = true;
   if (!forced && p->stale_hb && !after_step) return false;
   a.n_steps = 1;
+  a.most_in_memory = 2;
   a.n_insert = n;
   a.B = B;
   a.cursor = (uint32_t)p->cursor;
@@ -922,6 +923,7 @@ int per_run_steps(per_t* p, uint32_t n_steps, uint32_t n_insert, uint32_t B, con
   hipStream_t s = static_cast<hipStream_t>(stream);
   CaptureGuard capture(p, s);
   StreamCall a{};
+  a.most_in_memory = 1;
   a.n_steps = n_steps;
   a.n_insert = n_insert;
   a.B = B;

@@ -166,9 +166,10 @@ struct StreamArgs {
   uint32_t off[kStreamLevels + 2];  // where level v of the LDS copy starts (floats); off[levels + 1] = all floats
   uint32_t nodes[kStreamLevels + 1];// real nodes of every level
   uint32_t levels;                  // levels above the leaves (see Wide)
-  uint32_t leaves_in_memory;        // the LDS copy holds the levels above the leaves only
+  uint32_t levels_in_memory;        // the LDS copy holds the levels above the lowest ones only (so many)
 };
 struct StreamCall : StreamArgs {    // with the fields, of which the kernel has its own lists
+  uint32_t most_in_memory;          // a step by itself: 2, else 1
   FieldTable ins, rows;             // io arrays hold [steps][T][n][bytes]; io all null: nothing to move
 };
 
@@ -183,7 +184,7 @@ struct QueueArgs {
   FieldTable fields;                // columns, row sizes and access widths; the io pointers come from the requests
   uint32_t off[kStreamLevels + 2];  // as in StreamArgs
   uint32_t levels;
-  uint32_t leaves_in_memory;
+  uint32_t levels_in_memory;
 };
 
 // Workgroup ranges of the jobs sharing one launch: [first[j], first[j+1]) for job j, where job 0 is the
@@ -303,6 +304,7 @@ size_t step_table_bytes();
 void* step_static_claim(const void* holder, int device, hipStream_t s);
 void step_static_release(const void* holder, int device);
 bool stream_tree_fits(const Geom& g);
+bool stream_step_fits(const Geom& g, uint32_t n_insert, uint32_t B, const FieldTable& rows);
 bool step_on_chip_pays(const Geom& g, const Tuning& tn, uint32_t n_insert, uint32_t B, const FieldTable& rows, const FieldTable& ins);
 hipError_t launch_run_steps(const Geom& g, const Tuning& tn, const StreamCall& a, hipStream_t s);
 hipError_t launch_run_requests(const Geom& g, const Tuning& tn, const QueueArgs& a, hipStream_t s);

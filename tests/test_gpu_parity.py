@@ -744,9 +744,12 @@ def test_steps_on_the_chip(K, N, T, B, n, fb):
 
 
 # A step by itself stores the paths of what it has changed.  Heights that a level's groups do not fill (K = 2: every remainder by
-# four, K = 4: by two), leaves in memory, one element and a full wave of them, and more paths than there are waves.
+# four, K = 4: by two), leaves and the level above them in memory, one element and a full wave of them, and more paths than
+# there are waves.
 PATHS = [(2, 33, 1, 1, 0), (2, 70, 2, 64, 1), (2, 150, 1, 65, 3), (2, 300, 1, 20, 60), (2, 37_500, 1, 40, 30), (4, 60, 1, 10, 5), (4, 1025, 2, 64, 64),
-         (4, 70_001, 1, 70, 100), (8, 513, 1, 512, 40), (16, 17, 3, 16, 17), (16, 200_003, 2, 130, 9), (32, 33_001, 1, 512, 512), (64, 65, 1, 3, 2)]
+         (4, 70_001, 1, 70, 100), (8, 513, 1, 512, 40), (16, 17, 3, 16, 17), (16, 200_003, 2, 130, 9), (32, 33_001, 1, 512, 512), (64, 65, 1, 3, 2),
+         (2, 40_001, 1, 64, 1), (2, 300_007, 2, 100, 20), (4, 500_001, 1, 65, 3), (8, 290_000, 1, 512, 70), (16, 524_300, 1, 1, 0), (16, 700_001, 3, 64, 64),
+         (32, 1_300_000, 1, 33, 31), (64, 2_600_000, 1, 130, 65)]
 
 
 @pytest.mark.parametrize("K,N,T,B,n", PATHS)
@@ -759,6 +762,7 @@ def test_step_on_the_chip_stores_what_it_has_changed(K, N, T, B, n):
     m.gpu.set_tuning("step_on_chip", 2)
     m.insert(N - N // 8, prio=np.zeros((T, N - N // 8), np.float32), chunk=1 << 18)
     up = lambda: wl._draw_updates("absnormal1_eps_pow0.6", rng, (T, B))  # noqa: E731
+    m.gpu.profile(True)
     m.step_call(wl.uniform01(rng, (T, B)), 0.4, True, up(), None)   # nothing to draw
     m.compare_tree()
     m.update(rng.integers(0, N - N // 8, (T, 400)).astype(np.uint32), rng.random((T, 400)).astype(np.float32))
@@ -774,11 +778,14 @@ def test_step_on_the_chip_stores_what_it_has_changed(K, N, T, B, n):
         else:
             m.step_call(u, 0.4, True, v, None)
         m.compare_tree()
+    assert kernel_launches(m)["k_run_steps"] == 5
+    m.gpu.profile(False)
     m.compare_status()
 
 
 # (whether one launch on an LDS copy is the way a step goes by default: shapes well on either side of the rule's line)
 STEP_WAYS = [(2, 4096, 1, 64, 4, (16, 4, 4, 16, 1), True), (16, 10000, 1, 32, 0, (), True), (16, 900, 1, 64, 4, (16, 4, 4, 16, 1), True),
+             (16, 600_000, 1, 32, 4, (16, 4, 4, 1), True), (16, 600_000, 1, 128, 0, (68, 24, 4, 165), False),
              (4, 9000, 1, 40, 16, (12,), True), (64, 5000, 1, 32, 4, (16,), True), (16, 10000, 1, 300, 4, (16,), False),
              (2, 4096, 1, 256, 64, (165,), False), (16, 10000, 1, 128, 64, (63,), False), (8, 5000, 64, 64, 0, (1033,), False), (16, 10000, 65, 32, 4, (), False)]
 
