@@ -12,9 +12,10 @@
 // the LDS copy, and stores the tree back at the end.  Every tree access of a step is then an LDS
 // access; only rows, inputs and outputs travel to memory.  Results are those of the separate calls.
 //
-// A tree whose leaves do not fit beside the rest (MEM) keeps what is above them in LDS and its leaves in memory: the
-// paper's 100K-entry buffers at small fanouts are of that size.  The workgroup is still the only one that
-// touches the tree while the kernel runs, so its own leaf stores, made visible to its other waves by a
+// A tree whose leaves do not fit beside the rest (MEM: levels in memory) keeps what is above them in LDS and its leaves in
+// memory: the paper's 100K-entry buffers at small fanouts are of that size.  A list of one step, which has few groups to read
+// and no further steps to pay for them, also leaves the level above the leaves there.  The workgroup is still the only one that
+// touches the tree while the kernel runs, so its own stores, made visible to its other waves by a
 // barrier, are all the coherence that takes; every operation then costs a trip or two to memory for the leaf
 // groups it reads (sampling: the last level of the walk; insert and update: the groups whose sums change).
 // Of narrow trees the copy holds some heights only (see Wide).  Every node is taken for the sum of its children, which
@@ -76,6 +77,20 @@ __device__ __forceinline__ float sum_chunks(P grp) {
   } else {
     return sum_chunks<N / 2>(grp) + sum_chunks<N / 2>(grp + 2 * N);
   }
+}
+
+// The tables of heights and levels from the argument segment by vector loads (Geom first), as many entries as there can be, so
+// that none waits for another argument first.
+template <typename Args>
+__device__ __forceinline__ void fill_stream_tables(uint32_t t, const Args* a, LevelTable* tab, uint32_t* off, uint32_t* n) {
+  const uint32_t tid = threadIdx.x;
+  if (tid <= (uint32_t)kMaxHeight) {
+    const Geom* gk = kernarg_at<Geom>(0);
+    tab->lvl[tid] = gk->level[tid] + (size_t)t * gk->stride[tid];
+    tab->n[tid] = gk->n[tid];
+  }
+  if (tid >= 64 && tid < 64 + kStreamLevels + 2) off[tid - 64] = a->off[tid - 64];
+  if (tid >= 128 && tid < 128 + kStreamLevels + 1) n[tid - 128] = a->nodes[tid - 128];
 }
 
 // One tree in the LDS of its workgroup.
@@ -1166,16 +1181,8 @@ k_run_steps(StreamKernelArgs ka) {
   const uint32_t tid = threadIdx.x, lane = tid & 63u;
   const uint32_t H = g.H, T = g.T, B = a.B, n_ins = a.n_insert, N = g.N;
   const uint32_t V = a.levels;
-  // the tables from the argument segment by vector loads, as many entries as there can be, so that none waits for another
-  // argument first; the lists a lane per field, by two waves
-  const StreamArgs* as = kernarg_at<StreamArgs>(offsetof(StreamKernelArgs, a));
-  if (tid <= (uint32_t)kMaxHeight) {
-    const Geom* gk = kernarg_at<Geom>(0);
-    tab.lvl[tid] = gk->level[tid] + (size_t)t * gk->stride[tid];
-    tab.n[tid] = gk->n[tid];
-  }
-  if (tid >= 64 && tid < 64 + kStreamLevels + 2) s_off[tid - 64] = as->off[tid - 64];
-  if (tid >= 128 && tid < 128 + kStreamLevels + 1) s_n[tid - 128] = as->nodes[tid - 128];
+  fill_stream_tables(t, kernarg_at<StreamArgs>(offsetof(StreamKernelArgs, a)), &tab, s_off, s_n);
+  // (the lists a lane per field, by two waves)
   PieceCopy list;
   uint2 share = make_uint2(0, 0);
   const bool lists = tid >= 384 && tid < 512;
@@ -1587,13 +1594,10 @@ k_run_requests(QueueKernelArgs ka) {
   const FieldTable* fields = kernarg_at<FieldTable>(offsetof(QueueKernelArgs, a) + offsetof(QueueArgs, fields));
   const uint32_t* queue = reinterpret_cast<const uint32_t*>(a.queue);
   const bool single = a.ahead == 0;
-  fill_level_table(H, t, &tab);
-  if (tid >= 64 && tid <= 64 + V + 1) {
-    s_off[tid - 64] = kernarg_at<QueueArgs>(offsetof(QueueKernelArgs, a))->off[tid - 64];
-    if (tid <= 64 + V) s_n[tid - 64] = kernarg_at<Geom>(0)->n[level_height<LOGK>(tid - 64, H)];
-  }
+  fill_stream_tables(t, kernarg_at<QueueArgs>(offsetof(QueueKernelArgs, a)), &tab, s_off, s_n);   // (see k_run_steps)
+  uint32_t max_seen = 0;
   if (tid == 0) {
-    s_max = read_max_bits(g, t);
+    max_seen = read_max_bits(g, t);
     s_vmin[0] = s_vmin[1] = s_bmin[0] = s_bmin[1] = kNoMin;
     s_wild = 0;
     s_arrived = 0;
@@ -1632,14 +1636,30 @@ k_run_requests(QueueKernelArgs ka) {
   lt.max_bits = &s_max;
   lt.H = H;
   lt.V = V;
-  // (the first two rounds are laid out beside the others' copy of the tree)
+  // The list of one request's fields, by one wave (words: the request's part of its round), with this tree's place in the
+  // caller's arrays for an array.  Only where it asks for other fields, or for another number of rows, than the one before
+  // it: where the arrays are the waves know from the round.
+  auto fill_fields = [&](const uint32_t* words, PieceFields* pf, uint2* share) {
+    const uint32_t n = wave_value(words[PER_REQUEST_WORD(n)]);
+    bool asked = false;
+    if (n && lane < (uint32_t)kMaxFields) {
+      const uint32_t* w = words + PER_REQUEST_WORD(field) + 2u * lane;
+      asked = (w[0] | w[1]) != 0;
+    }
+    if (share) fill_piece_fields<apart ? SHARES_ANY : SHARES_EVEN>(fields, asked, t, n, rws, pf, share);
+    else fill_piece_fields<SHARES_NONE>(fields, asked, t, n, rws, pf, nullptr);
+  };
+  // (the first two rounds are laid out, and the fields of the first insertion, beside the others' copy of the tree)
   const uint32_t at_work = apart ? team : 0u;   // first lane of the decoding wave
   if (decodes) {
     decode();
     decode();
+    wave_order();
+    fill_fields(s_round[0] + kRoundInsert, &s_ins[0], nullptr);
   } else {
     lds_tree_load<LOGK>(tab, lt, tid < at_work ? tid : tid - 64u, 960u);
   }
+  if (tid == 0) s_max = max_seen;
   uint32_t* nodes = reinterpret_cast<uint32_t*>(tree + s_off[V + 1]);   // sampled leaves of the round
   float* values = reinterpret_cast<float*>(nodes + 512);                // and their values (apart only: at most 512)
   TreeView<MEM> tv;
@@ -1659,22 +1679,7 @@ k_run_requests(QueueKernelArgs ka) {
   tv.apart = apart;
   tv.team = team;
   tv.met = 0;
-  // The list of one request's fields, by one wave (words: the request's part of its round), with this tree's place in the
-  // caller's arrays for an array.  Only where it asks for other fields, or for another number of rows, than the one before
-  // it: where the arrays are the waves know from the round.
-  auto fill_fields = [&](const uint32_t* words, PieceFields* pf, uint2* share) {
-    const uint32_t n = wave_value(words[PER_REQUEST_WORD(n)]);
-    bool asked = false;
-    if (n && lane < (uint32_t)kMaxFields) {
-      const uint32_t* w = words + PER_REQUEST_WORD(field) + 2u * lane;
-      asked = (w[0] | w[1]) != 0;
-    }
-    if (share) fill_piece_fields<apart ? SHARES_ANY : SHARES_EVEN>(fields, asked, t, n, rws, pf, share);
-    else fill_piece_fields<SHARES_NONE>(fields, asked, t, n, rws, pf, nullptr);
-  };
-  const bool lists = !(apart && in_team) && rw == 1;   // (the wave that does)
-  __syncthreads();
-  if (lists) fill_fields(s_round[0] + kRoundInsert, &s_ins[0], nullptr);
+  const bool lists = !(apart && in_team) && rw == 1;   // (the wave that fills the lists of fields from then on)
   __syncthreads();
   uint32_t flags = 0;
   float lane_max = __uint_as_float(s_max);   // (WAVE: the lanes' share of it; else s_max counts)
@@ -2033,6 +2038,12 @@ static uint32_t plan_stream_levels(const Geom& g, uint32_t most_in_memory, uint3
   return 0u;
 }
 
+// Real nodes of every level.
+template <int LOGK>
+static void level_nodes(const Geom& g, uint32_t levels, uint32_t* nodes) {
+  for (uint32_t v = 0; v <= levels; ++v) nodes[v] = g.n[v * Wide<LOGK>::LH < g.H ? v * Wide<LOGK>::LH : g.H];
+}
+
 // Waves of the team (where it is not all of them).
 static uint32_t team_waves(uint32_t samples, uint32_t inserted) { return ((samples > inserted ? samples : inserted) + 63u) / 64u; }
 // Items that n rows are moved in, of every access width (see fill_piece_fields); returns all of them.
@@ -2173,7 +2184,7 @@ static hipError_t launch_run_steps_k(const Geom& g, const Tuning& tn, const Stre
   // size (the tree copy and the row movers use all lanes)
   TeamForm form = team_form(a.B, a.n_insert);
   if (form != TEAM_ALL && !gathers_in_runs(a.rows, a.B, 16u - team_waves(a.B, a.n_insert))) form = a.ahead ? TEAM_WAVES_SPANS : TEAM_ALL;
-  for (uint32_t v = 0; v <= ka.a.levels; ++v) ka.a.nodes[v] = g.n[v * Wide<LOGK>::LH < g.H ? v * Wide<LOGK>::LH : g.H];
+  level_nodes<LOGK>(g, ka.a.levels, ka.a.nodes);
   plan_pieces(a.rows, a.B, g.T, &ka.rows);
   plan_pieces(a.ins, a.n_insert, g.T, &ka.ins);
   plan_shares(a.rows, a.B, form == TEAM_ALL ? 16u : 16u - team_waves(a.B, a.n_insert), form == TEAM_ALL || form == TEAM_WAVES_SPANS, ka.share);
@@ -2220,6 +2231,7 @@ static hipError_t launch_run_requests_k(const Geom& g, const Tuning& tn, const Q
   ka.a = a;
   const uint32_t floats = plan_stream_levels<LOGK>(g, 1, ka.a.off, &ka.a.levels, &ka.a.levels_in_memory);
   if (!floats) return hipErrorInvalidValue;
+  level_nodes<LOGK>(g, ka.a.levels, ka.a.nodes);
   const size_t bytes = (size_t)floats * 4;
   const TeamForm form = team_form(a.most, 0);
   const bool mem = ka.a.levels_in_memory != 0;

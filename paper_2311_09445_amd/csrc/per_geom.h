@@ -183,6 +183,7 @@ struct QueueArgs {
   const per_request* queue;         // device copy of the requests
   FieldTable fields;                // columns, row sizes and access widths; the io pointers come from the requests
   uint32_t off[kStreamLevels + 2];  // as in StreamArgs
+  uint32_t nodes[kStreamLevels + 1];
   uint32_t levels;
   uint32_t levels_in_memory;
 };
