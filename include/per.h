@@ -166,9 +166,9 @@ int per_sample_gather_update(per_t* p, uint32_t B, float beta, const float* d_u,
  * >= B makes its element invalid (PER_FLAG_BAD_INDEX), as does a sample that found nothing
  * (PER_FLAG_ZERO_TOTAL).  d_upd_prio and d_upd_pos are [T][B] and must not overlap the outputs
  * (PER_EINVAL).  d_field_dst and d_out_weight may be NULL.
- * A step without a position map, of at most 512 samples and new rows on a tree that per_run_steps takes, goes as one launch
- * of that call's kernel where that is the faster way (tuning "step_on_chip"); see per_set_weight_norm and
- * per_update_delta for where it does not. */
+ * A step without a position map, of at most 512 samples and new rows on a tree that per_run_steps takes, or whose heights
+ * above the leaves and the level over them fit, goes as one launch of that call's kernel where that is the faster way
+ * (tuning "step_on_chip"); see per_set_weight_norm and per_update_delta for where it does not. */
 int per_step(per_t* p, uint32_t B, float beta, const float* d_u, uint32_t* d_out_idx, float* d_out_weight,
              float* d_out_prio, void* const* d_field_dst, const float* d_upd_prio, const uint32_t* d_upd_pos,
              void* stream);
@@ -430,8 +430,8 @@ uint64_t per_rng_calls(const per_t* p);
  *                  to pay off (long runs of samples per subtree, few trees); 2: wherever the tree fits (tests);
  *                  0: always the separate kernels
  *   "step_on_chip" : how per_step and per_insert_step run small batches on trees that fit the LDS of a compute unit, or
- *                  whose heights above the leaves do (per_run_steps_fits).  1 (default): as one launch, one workgroup per
- *                  tree, where that is the faster way; 2: wherever it can be (tests); 0: never.  (Whoever sets
+ *                  whose heights above the leaves do (per_run_steps_fits), or those above the level over the leaves.
+ *                  1 (default): as one launch, one workgroup per tree, where that is the faster way; 2: wherever it can be (tests); 0: never.  (Whoever sets
  *                  "step_kernel", "group_claim", "claim_in_sample", "insert_ride" or "lazy_top" from their defaults gets
  *                  the kernels that those choose.)
  *   "claim_in_sample" : 1 (default) lets per_sample_gather_update run the first phase of its update

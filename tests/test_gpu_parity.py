@@ -755,7 +755,7 @@ PATHS = [(2, 33, 1, 1, 0), (2, 70, 2, 64, 1), (2, 150, 1, 65, 3), (2, 300, 1, 20
 @pytest.mark.parametrize("K,N,T,B,n", PATHS)
 def test_step_on_the_chip_stores_what_it_has_changed(K, N, T, B, n):
     """Single steps against the oracle, every stored node after every one: with and without new rows (past the ring's end, given
-    priorities that are not valid among them), with no element that is valid, and on a tree without mass."""
+    priorities that are not valid among them), with no element that is valid, with uniforms out of range, and on a tree without mass."""
     log(f"paths of a step on the chip K={K} N={N} T={T} B={B} n={n}")
     rng = np.random.default_rng(K * N + B)
     m = Mirror(K, N, T, (5,))
@@ -770,6 +770,8 @@ def test_step_on_the_chip_stores_what_it_has_changed(K, N, T, B, n):
         u, v = wl.uniform01(rng, (T, B)), up()
         if it == 1:
             v[:] = np.float32("nan")
+        if it == 3:   # walks that leave their way
+            u[:, ::5] = (rng.random((T, len(range(0, B, 5)))) * 3 * B - B).astype(np.float32)
         if n:
             ins = (rng.random((T, n)) * 5).astype(np.float32) if it % 2 else None
             if ins is not None:
