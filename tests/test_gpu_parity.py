@@ -785,6 +785,28 @@ def test_step_on_the_chip_stores_what_it_has_changed(K, N, T, B, n):
     m.compare_status()
 
 
+@pytest.mark.parametrize("width,B", [(128, 32767), (128, 32768), (48, 87381), (48, 87382), (16, 262145), (7056, 595)])
+def test_gathers_on_either_side_of_streaming_stores(claim_form, width, B):
+    """Fields of 16-byte elements whose gathered rows come to just below 4 MiB, and to it: sampled with their rows, and gathered
+    again by the indices drawn, against the rows as they were put in."""
+    if claim_form != "group":
+        pytest.skip("no claims in these calls")
+    log(f"streamed rows width={width} B={B}")
+    N = 5003
+    g = torch.Generator(device="cuda")
+    g.manual_seed(width + B)
+    rows = torch.randint(0, 256, (1, N, width), generator=g, device="cuda", dtype=torch.uint8)
+    p = PrioritizedReplay(16, N, 1, (width,))
+    p.insert(N, [rows], torch.rand((1, N), generator=g, device="cuda"))
+    out, idx = torch.zeros((1, B, width), dtype=torch.uint8, device="cuda"), torch.zeros((1, B), dtype=torch.int32, device="cuda")
+    p.sample(torch.rand((1, B), generator=g, device="cuda"), 0.4, out_idx=idx, rows_out=[out])
+    assert torch.equal(out[0], rows[0][idx[0].long()])
+    again = idx.flip(1).contiguous()
+    got = p.gather(again)
+    assert torch.equal(got[0][0], rows[0][again[0].long()])
+    assert p.status() == 0
+
+
 # (whether one launch on an LDS copy is the way a step goes by default: shapes well on either side of the rule's line)
 STEP_WAYS = [(2, 4096, 1, 64, 4, (16, 4, 4, 16, 1), True), (16, 10000, 1, 32, 0, (), True), (16, 900, 1, 64, 4, (16, 4, 4, 16, 1), True),
              (16, 600_000, 1, 32, 4, (16, 4, 4, 1), True), (16, 600_000, 1, 128, 0, (68, 24, 4, 165), False),
