@@ -57,9 +57,11 @@ struct RowMove {                 // what the elements of one field and tree have
   bool streams;                  // a long gather of 16-byte elements (see store_streaming)
 };
 // Gathered rows of a long batch leave by stores that do not stay in the second-level caches: there they push out what the
-// kernels around them read again, the tree's lower heights and the batch's indices and values.  From 4 MiB a tree on (2^20
-// rows of 128 bytes, sampled and updated on 2^24 leaves: 141.2 -> 131.4 us; 65 536: 23.5 -> 22.5 a step; 4096: no difference).
-constexpr uint64_t kStreamedBytes = 4u << 20;
+// kernels around them read again, the tree's lower heights and the batch's indices and values.  From 32 MiB a tree on, which is
+// what those caches hold together (2^20 rows of 128 bytes, sampled and updated on 2^24 leaves: 141.2 -> 131.4 us).  8 MiB, 65 536
+// such rows, still fit: steps one after the other 20.9 us, 21.65 with streaming stores (with other work between every eight
+// steps 23.5 and 22.7).
+constexpr uint64_t kStreamedBytes = 32u << 20;
 __device__ __forceinline__ void store_streaming(uint4* p, const uint4& x) {
   typedef uint32_t Quad __attribute__((ext_vector_type(4)));
   asm volatile("");   // (without these the compiler makes one ordinary store of the two in the branches)

@@ -785,9 +785,9 @@ def test_step_on_the_chip_stores_what_it_has_changed(K, N, T, B, n):
     m.compare_status()
 
 
-@pytest.mark.parametrize("width,B", [(128, 32767), (128, 32768), (48, 87381), (48, 87382), (16, 262145), (7056, 595)])
+@pytest.mark.parametrize("width,B", [(128, 262143), (128, 262144), (48, 699050), (48, 699051), (16, 2097153), (7056, 4756)])
 def test_gathers_on_either_side_of_streaming_stores(claim_form, width, B):
-    """Fields of 16-byte elements whose gathered rows come to just below 4 MiB, and to it: sampled with their rows, and gathered
+    """Fields of 16-byte elements whose gathered rows come to just below 32 MiB, and to it: sampled with their rows, and gathered
     again by the indices drawn, against the rows as they were put in."""
     if claim_form != "group":
         pytest.skip("no claims in these calls")
