@@ -54,20 +54,7 @@ struct RowMove {                 // what the elements of one field and tree have
   const uint32_t* idx;           // the tree's indices (gather)
   uint64_t total, stride;        // elements of the job; elements between two of a lane's
   uint32_t RS, epr, cursor, N;
-  bool streams;                  // a long gather of 16-byte elements (see store_streaming)
 };
-// Gathered rows of a long batch leave by stores that do not stay in the second-level caches: there they push out what the
-// kernels around them read again, the tree's lower heights and the batch's indices and values.  From 32 MiB a tree on, which is
-// what those caches hold together (2^20 rows of 128 bytes, sampled and updated on 2^24 leaves: 141.2 -> 131.4 us).  8 MiB, 65 536
-// such rows, still fit: steps one after the other 20.9 us, 21.65 with streaming stores (with other work between every eight
-// steps 23.5 and 22.7).
-constexpr uint64_t kStreamedBytes = 32u << 20;
-__device__ __forceinline__ void store_streaming(uint4* p, const uint4& x) {
-  typedef uint32_t Quad __attribute__((ext_vector_type(4)));
-  asm volatile("");   // (without these the compiler makes one ordinary store of the two in the branches)
-  __builtin_nontemporal_store(Quad{x.x, x.y, x.z, x.w}, reinterpret_cast<Quad*>(p));
-  asm volatile("");
-}
 
 // Element K of the sweep that starts at e0 (clamped to e0 beyond the end, so that loads need no branch).
 template <int K>
@@ -121,10 +108,7 @@ __device__ __forceinline__ void sweep_store(const RowMove& m, uint64_t e0, Regs<
     bool live;
     const uint64_t e = sweep_elem<K>(m, e0, live);
     if (live) {
-      if constexpr (GATHER && sizeof(V) == 16) {
-        if (m.streams) store_streaming(reinterpret_cast<V*>(m.io) + e, reg<K>(v));
-        else *(reinterpret_cast<V*>(m.io) + e) = reg<K>(v);
-      } else if constexpr (GATHER) *(reinterpret_cast<V*>(m.io) + e) = (V)reg<K>(v);
+      if constexpr (GATHER) *(reinterpret_cast<V*>(m.io) + e) = (V)reg<K>(v);
       else *(reinterpret_cast<V*>(m.col + (uint64_t)reg<K>(at) * m.RS) + (uint32_t)(e % m.epr)) = (V)reg<K>(v);
     }
     sweep_store<V, GATHER, K + 1, U>(m, e0, at, v);
@@ -149,7 +133,6 @@ __device__ __forceinline__ void move_rows(const FieldTable& ft, uint32_t f, uint
   m.stride = (uint64_t)job_blocks * blockDim.x;
   m.cursor = cursor;
   m.N = N;
-  m.streams = (uint64_t)B * E >= kStreamedBytes;
   bool bad = false;
   for (uint64_t e0 = (uint64_t)job_block * blockDim.x + threadIdx.x; e0 < m.total; e0 += U * m.stride) {
     Regs<uint32_t, U> at;

@@ -785,13 +785,12 @@ def test_step_on_the_chip_stores_what_it_has_changed(K, N, T, B, n):
     m.compare_status()
 
 
+@pytest.mark.parametrize("claim_form", ["group"], indirect=True)   # (no claims in these calls)
 @pytest.mark.parametrize("width,B", [(128, 262143), (128, 262144), (48, 699050), (48, 699051), (16, 2097153), (7056, 4756)])
-def test_gathers_on_either_side_of_streaming_stores(claim_form, width, B):
-    """Fields of 16-byte elements whose gathered rows come to just below 32 MiB, and to it: sampled with their rows, and gathered
+def test_long_gathers_of_wide_elements(width, B):
+    """Fields of 16-byte elements whose gathered rows come to 32 MiB and just below: sampled with their rows, and gathered
     again by the indices drawn, against the rows as they were put in."""
-    if claim_form != "group":
-        pytest.skip("no claims in these calls")
-    log(f"streamed rows width={width} B={B}")
+    log(f"long gathers width={width} B={B}")
     N = 5003
     g = torch.Generator(device="cuda")
     g.manual_seed(width + B)
