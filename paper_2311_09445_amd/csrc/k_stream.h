@@ -2120,19 +2120,21 @@ static void plan_shares(const FieldTable& ft, uint32_t n, uint32_t rws, bool eve
 }
 
 // Whether one step (with n_insert new rows, or none) is faster as one launch of the kernel above than as the two or three
-// kernels it otherwise takes.  Both sides in hundredths of a microsecond, first fitted to 639 shapes (1 to 64 trees of 300 to
-// 400 000 leaves, 16 to 512 samples, 0 to 400 new rows of 0 to 1033 bytes in fields of every access width), the side on the
-// chip again since a step by itself stores its paths only and leaves up to two levels in memory.  On the chip: the launch and
-// one step's chain, more with several waves at the tree; the rows, which one compute unit moves, by the pieces that every
-// row wave has (in runs each piece is the rest of a trip to memory, evenly shared ones go eight to a trip; a new row's pieces
-// one to a trip); the copy of the tree and the trips to levels in memory.  As kernels: two launches, with the insertion in
-// the sampling kernel where that can carry it, else three; K = 2 trees are chains of many heights, and so are large ones.
-// Of 144 shapes (every fanout, 1000 to 4 million leaves, 16 to 512 samples, 1 to 64 trees) the way it chooses is 0.6 % behind
-// the better one on average, one loses 15 % on the chip (32 samples on 2^20 leaves at K = 16: 12.4 -> 7.5 us, 64 on 64 trees of
-// 2^18: 16.9 -> 8.9; where it stays away: 256 samples with rows of 165 bytes on 100 000 leaves 11.9, 12.2 on the chip).
-// By the bytes of a row alone, 45 of the 639 lost 2 % or more, and by up to 4.5 times: 256 samples of a 165-byte field on
-// 4096 leaves at K = 2 71 us against 22.  Batches beyond 256 at K > 2 are left out: what there is to gain is less than the
-// fits are off by.
+// kernels it otherwise takes.  Both sides in hundredths of a microsecond, fitted to measured shapes (every fanout, 300 to 4
+// million leaves, 1 to 64 trees, 16 to 512 samples, 0 to 512 new rows of 0 to 1033 bytes in fields of every access width).  On the
+// chip: the launch and one step's chain, more with several waves at the tree; the rows, which one compute unit moves, by the
+// pieces that every row wave has (in runs each piece is the rest of a trip to memory, evenly shared ones go eight to a trip; a
+// new row's pieces one to a trip); the copy of the tree and the trips to levels in memory.  As kernels: two launches, with the
+// insertion in the sampling kernel where that can carry it, else three; K = 2 trees are chains of many heights, and so are large
+// ones.  (32 samples on 2^20 leaves at K = 16: 12.4 us as kernels, 7.5 on the chip; 64 on each of 64 trees of 2^18: 16.9 and 8.9;
+// where it stays away: 256 samples with rows of 165 bytes on 4096 leaves at K = 2, 22 and 71.)
+// Where rows are shared evenly, pieces of one byte among them, the two fits are off by up to 15 %, and the chip has to be ahead
+// by a tenth, not by 3 % (35 samples with rows of 1033 bytes on each of 64 trees of 1074 leaves at K = 4: 13.2 us as kernels, 15.6 on the
+// chip; 63 of 165 bytes on 2416 leaves at K = 64: 9.2 and 10.0).
+// Of 580 shapes that the constants were not fitted to (profiles/step_ways.txt) 501 go on the chip, one of them 2.4 % slower for it;
+// the way taken is 0.8 % behind the better one on average.
+// Batches beyond 256 at K > 2 are left out, though several trees of a few thousand leaves would gain (410 samples on each of 4 trees
+// of 27 915 leaves at K = 32: 16.8 and 13.1): of 71 such shapes that the fits would take, three lose 6 to 13 %.
 template <int LOGK>
 static bool step_on_chip_pays_k(const Geom& g, const Tuning& tn, uint32_t n_insert, uint32_t B, const FieldTable& rows, const FieldTable& ins) {
   uint32_t off[kStreamLevels + 2], levels = 0, in_memory = 0;
@@ -2143,7 +2145,8 @@ static bool step_on_chip_pays_k(const Geom& g, const Tuning& tn, uint32_t n_inse
   const uint32_t rws = 16u - team_waves(B, n_insert);
   const uint64_t gathered = items_by_width(rows, B, of_kind), placed = items_by_width(ins, n_insert, of_kind);
   int64_t here = 520 + (team_form(B, n_insert) == TEAM_ONE_WAVE ? 0 : 138) + (n_insert ? 55 : 0) + (g.T >= 16 ? 71 : 0) + (g.K == 64 ? 37 * B / 64 : 0);
-  here += gathers_in_runs(rows, B, rws) ? 80 * gathered / rws : 136 + 19 * gathered / rws;
+  const bool runs = gathers_in_runs(rows, B, rws);
+  here += runs ? 80 * gathered / rws : 136 + 19 * gathered / rws;
   here += (placed > rws ? 81 * (placed - rws) / rws : 0) + floats * 4 / 1024 + (g.K == 2 ? 40 : g.K == 4 ? 20 : 0);
   if (in_memory) {
     here += in_memory == 1 ? 40 + 40 * B / 64 : 100 + 55 * B / 64 + (n_insert ? 25 : 0);
@@ -2156,7 +2159,7 @@ static bool step_on_chip_pays_k(const Geom& g, const Tuning& tn, uint32_t n_inse
   int64_t apart = 938 + (!n_insert ? 0 : carried ? 273 : 374 + (g.K <= 4 ? 141 : 0)) + (g.K == 2 ? 106 * (int64_t)g.H - 815 : 0);
   apart += (g.N > 1u << 20 ? 170 : 0) + (g.K == 64 && g.H >= 3 ? 90 : 0) + (g.K == 4 && g.H >= 9 ? 600 : 0);
   apart += (g.K == 4 ? 87 : 0) + (g.K >= 32 ? 55 : 0) + (g.T >= 16 ? 105 : 0) + (int64_t)(176 * g.T * B * row >> 20);
-  return here * 103 < apart * 100;
+  return here * (runs ? 103 : 110) < apart * 100;
 }
 bool step_on_chip_pays(const Geom& g, const Tuning& tn, uint32_t n_insert, uint32_t B, const FieldTable& rows, const FieldTable& ins) {
 #define CALL(L) step_on_chip_pays_k<L>(g, tn, n_insert, B, rows, ins)

@@ -810,14 +810,14 @@ def test_long_gathers_of_wide_elements(width, B):
 STEP_WAYS = [(2, 4096, 1, 64, 4, (16, 4, 4, 16, 1), True), (16, 10000, 1, 32, 0, (), True), (16, 900, 1, 64, 4, (16, 4, 4, 16, 1), True),
              (16, 600_000, 1, 32, 4, (16, 4, 4, 1), True), (16, 600_000, 1, 128, 0, (68, 24, 4, 165), False),
              (4, 9000, 1, 40, 16, (12,), True), (64, 5000, 1, 32, 4, (16,), True), (16, 10000, 1, 300, 4, (16,), False),
-             (2, 4096, 1, 256, 64, (165,), False), (16, 10000, 1, 128, 64, (63,), False), (8, 5000, 64, 64, 0, (1033,), False), (16, 10000, 65, 32, 4, (), False)]
+             (2, 4096, 1, 256, 64, (165,), False), (16, 10000, 1, 128, 64, (63,), False), (8, 5000, 64, 64, 0, (1033,), False), (16, 10000, 65, 32, 4, (), False),
+             (4, 1074, 64, 35, 0, (1033,), False), (64, 2416, 1, 63, 0, (165,), False), (4, 5468, 64, 101, 1, (63,), True)]
 
 
+@pytest.mark.parametrize("claim_form", ["group"], indirect=True)   # (the rule stands aside where the kernels are chosen by hand)
 @pytest.mark.parametrize("K,N,T,B,n,fb,chip", STEP_WAYS)
-def test_way_that_a_step_goes(claim_form, K, N, T, B, n, fb, chip):
+def test_way_that_a_step_goes(K, N, T, B, n, fb, chip):
     """Steps by the default rule: which kernels they launch, and their results; narrow fields go by the pieces they are moved in."""
-    if claim_form != "group":
-        pytest.skip("the rule stands aside where the kernels are chosen by hand")
     log(f"way of a step K={K} N={N} T={T} B={B} n={n} fb={fb}")
     rng = np.random.default_rng(K + N + B)
     m = Mirror(K, N, T, fb)
