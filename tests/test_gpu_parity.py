@@ -697,6 +697,48 @@ def test_run_steps_equals_the_separate_calls(K, N, T, B, n_ins, fb, explicit, ow
         m.compare_tree()
 
 
+# (teams of one wave, of several, of several with more pieces of rows than they have under way at once, of all waves)
+@pytest.mark.parametrize("K,N,T,B,n,fb", [(2, 150, 1, 64, 5, (5,)), (4, 5000, 2, 40, 0, (16, 4)), (16, 3000, 1, 130, 9, (12,)), (2, 37_500, 1, 33, 31, ()),
+                                          (8, 200_001, 1, 512, 4, (4, 1)), (16, 100_000, 2, 64, 64, (16,)), (16, 30_000, 1, 300, 16, (68, 24, 4, 68, 1)),
+                                          (32, 40_000, 1, 700, 3, (8,))])
+@pytest.mark.parametrize("what", ["apart", "weights", "no update", "other batch"])
+def test_lists_of_one_step(K, N, T, B, n, fb, what):
+    """per_run_steps of a single step, several times, every stored node after each: with an update of its own batch by given priorities,
+    by the weights the step itself returns (through their array, so that the step waits for its results), without an update,
+    and with one of other indices."""
+    log(f"lists of one step K={K} N={N} T={T} B={B} n={n} fb={fb} {what}")
+    rng = np.random.default_rng(N + B)
+    m = Mirror(K, N, T, fb)
+    filled = N - 3 * n // 2
+    m.insert(filled, prio=wl._draw_priorities("exponential_1", rng, (T, filled)), chunk=max(5000, N // 8))
+    for it in range(4):
+        u, up = wl.uniform01(rng, (1, T, B)), (rng.random((1, T, B)) * 4).astype(np.float32)
+        if it == 2:
+            up[:, :, ::3] = np.float32("nan")
+            u[:, :, ::5] = (rng.random((1, T, len(range(0, B, 5)))) * 3 * B - B).astype(np.float32)
+        ui = rng.integers(0, filled, (1, T, B)).astype(np.uint32)
+        counters = m.counter + np.arange(n)
+        rows = [np.stack([wl.row_bytes(t, counters, f, b) for t in range(T)]) for f, b in enumerate(fb)] if n and fb else None
+        ins = (rng.random((1, T, n)) * 6).astype(np.float32) if n and it % 2 else None
+        oi, ow, ov = (torch.empty((1, T, B), dtype=d, device="cuda") for d in (torch.int32, torch.float32, torch.float32))
+        ro = [torch.empty((1, T, B, b), dtype=torch.uint8, device="cuda") for b in fb] if fb else None
+        m.gpu.run_steps(dev(u), torch.full((1,), 0.5, device="cuda"), oi, ow, ov, ro,
+                        upd_prio={"no update": None, "weights": ow}.get(what, dev(up)), upd_idx=idx_to_dev(ui) if what == "other batch" else None,
+                        n_insert=n, ins_rows=[dev(r) for r in rows] if rows else None, ins_prio=None if ins is None else dev(ins))
+        if n:
+            m.cpu.insert(n, rows, None if ins is None else ins[0])
+            m.counter += n
+        ci, cw, cv = m.cpu.sample(u[0], 0.5, True)
+        assert np.array_equal(idx_to_host(oi)[0], ci) and ov[0].cpu().numpy().tobytes() == cv.tobytes()
+        np.testing.assert_allclose(ow[0].cpu().numpy(), cw, rtol=1e-6, atol=0)
+        for f, want in enumerate(m.cpu.gather(ci)):
+            assert np.array_equal(ro[f][0].cpu().numpy(), want), f"rows of field {f}"
+        if what != "no update":
+            m.cpu.update(ui[0] if what == "other batch" else ci, ow[0].cpu().numpy() if what == "weights" else up[0])
+        m.compare_tree()
+    m.compare_status()
+
+
 def test_run_steps_limits_and_empty_tree():
     p = PrioritizedReplay(16, 1 << 20)
     assert not p.run_steps_fits()
@@ -743,29 +785,53 @@ def test_steps_on_the_chip(K, N, T, B, n, fb):
     m.compare_status()
 
 
+def levels_in_memory(K, N):
+    """How many of the lowest levels of a tree a single on-chip step leaves in memory (None: no such step).  The copy holds levels
+    of sixteen children at K = 2 and 4, padded to whole groups and with one group of zeros more below the root's children,
+    and 1024 words of the batch, in 156.5 KiB; it has at most eight levels above the leaves."""
+    n = [N]
+    while n[-1] > 1:
+        n.append(-(-n[-1] // K))
+    heights, group = {2: (4, 16), 4: (2, 16)}.get(K, (1, K))
+    levels = -(-(len(n) - 1) // heights)
+    for left in range(3):
+        words = 1024 + sum(4 if v == levels else -(-n[v * heights] // group) * group + (group if v + 1 < levels else 0) for v in range(left, levels + 1))
+        if words * 4 <= 156 * 1024 + 512 and levels > left and levels <= 8:
+            return left
+    return None
+
+
 # A step by itself stores the paths of what it has changed.  Heights that a level's groups do not fill (K = 2: every remainder by
-# four, K = 4: by two), leaves and the level above them in memory, one element and a full wave of them, and more paths than
-# there are waves.
-PATHS = [(2, 33, 1, 1, 0), (2, 70, 2, 64, 1), (2, 150, 1, 65, 3), (2, 300, 1, 20, 60), (2, 37_500, 1, 40, 30), (4, 60, 1, 10, 5), (4, 1025, 2, 64, 64),
-         (4, 70_001, 1, 70, 100), (8, 513, 1, 512, 40), (16, 17, 3, 16, 17), (16, 200_003, 2, 130, 9), (32, 33_001, 1, 512, 512), (64, 65, 1, 3, 2),
-         (2, 40_001, 1, 64, 1), (2, 300_007, 2, 100, 20), (4, 500_001, 1, 65, 3), (8, 290_000, 1, 512, 70), (16, 524_300, 1, 1, 0), (16, 700_001, 3, 64, 64),
-         (32, 1_300_000, 1, 33, 31), (64, 2_600_000, 1, 130, 65)]
+# four, K = 4: by two), one element and a full wave of them, more paths than there are waves, teams of one wave and of several; the
+# whole tree on the chip, its leaves in memory, the level above them too (of as many levels as there can be at K = 8).
+PATHS = [(2, 33, 1, 1, 0, 0), (2, 70, 2, 64, 1, 0), (2, 150, 1, 65, 3, 0), (2, 300, 1, 20, 60, 0), (2, 37_500, 1, 40, 30, 1), (4, 60, 1, 10, 5, 0),
+         (4, 1025, 2, 64, 64, 0), (4, 70_001, 1, 70, 100, 1), (8, 513, 1, 512, 40, 0), (16, 17, 3, 16, 17, 0), (16, 200_003, 2, 130, 9, 1),
+         (32, 33_001, 1, 512, 512, 0), (64, 65, 1, 3, 2, 0),
+         (2, 40_001, 1, 64, 1, 1), (2, 300_007, 2, 100, 20, 1), (4, 500_001, 1, 65, 3, 1), (8, 290_000, 1, 512, 70, 2), (16, 524_300, 1, 1, 0, 1),
+         (16, 700_001, 3, 64, 64, 2), (32, 1_300_000, 1, 33, 31, 2), (64, 2_600_000, 1, 130, 65, 2),
+         (2, 600_001, 1, 64, 4, 2), (2, 1_100_000, 1, 130, 20, 2), (2, 2_200_001, 1, 33, 31, 2), (4, 600_001, 2, 128, 9, 2), (4, 1_100_003, 1, 60, 4, 2),
+         (8, 2_150_000, 1, 64, 40, 2), (8, 2_170_001, 1, 200, 0, 2)]
 
 
-@pytest.mark.parametrize("K,N,T,B,n", PATHS)
-def test_step_on_the_chip_stores_what_it_has_changed(K, N, T, B, n):
-    """Single steps against the oracle, every stored node after every one: with and without new rows (past the ring's end, given
-    priorities that are not valid among them), with no element that is valid, with uniforms out of range, and on a tree without mass."""
-    log(f"paths of a step on the chip K={K} N={N} T={T} B={B} n={n}")
+@pytest.mark.parametrize("K,N,T,B,n,left", PATHS)
+def test_step_on_the_chip_stores_what_it_has_changed(K, N, T, B, n, left):
+    """Single steps against the oracle, every stored node after every one: with and without new rows (given priorities that are not
+    valid among them; of four insertions of more than one row one goes past the ring's end, half of it on either side), with no element
+    that is valid, with uniforms out of range, and on a tree without mass."""
+    log(f"paths of a step on the chip K={K} N={N} T={T} B={B} n={n}, {left} levels in memory")
+    assert levels_in_memory(K, N) == left
     rng = np.random.default_rng(K * N + B)
     m = Mirror(K, N, T, (5,))
+    assert left == 2 or K < 8 or m.gpu.run_steps_fits()   # (lists leave at most the leaves in memory)
+    assert left < 2 or not m.gpu.run_steps_fits()
     m.gpu.set_tuning("step_on_chip", 2)
-    m.insert(N - N // 8, prio=np.zeros((T, N - N // 8), np.float32), chunk=1 << 18)
+    filled = N - min(N // 8, 3 * n // 2 if n > 1 else N)
+    m.insert(filled, prio=np.zeros((T, filled), np.float32), chunk=1 << 18)
     up = lambda: wl._draw_updates("absnormal1_eps_pow0.6", rng, (T, B))  # noqa: E731
     m.gpu.profile(True)
     m.step_call(wl.uniform01(rng, (T, B)), 0.4, True, up(), None)   # nothing to draw
     m.compare_tree()
-    m.update(rng.integers(0, N - N // 8, (T, 400)).astype(np.uint32), rng.random((T, 400)).astype(np.float32))
+    m.update(rng.integers(0, filled, (T, 400)).astype(np.uint32), rng.random((T, 400)).astype(np.float32))
     for it in range(4):
         u, v = wl.uniform01(rng, (T, B)), up()
         if it == 1:
@@ -958,13 +1024,16 @@ def test_carried_insertions_on_small_trees(K, N, T, B, fb):
     m.compare_status()
 
 
-def test_steps_on_the_chip_draw_and_replay_as_the_kernels_do():
+@pytest.mark.parametrize("K,N", [(16, 5000), (16, 700_001), (2, 1_100_000)])
+def test_steps_on_the_chip_draw_and_replay_as_the_kernels_do(K, N):
     """The library's own uniforms, results that lie over inputs (the usual way is taken), an empty tree, and replays of a
-    captured step between eager calls: the same as with the kernels."""
-    log("steps on the chip against the kernels")
-    K, N, B, n, fb = 16, 5000, 48, 6, (16, 4)
+    captured step between eager calls: the same as with the kernels, wherever it fits and by the default rule.  The whole tree on
+    the chip, and all but two levels of it."""
+    log(f"steps on the chip against the kernels K={K} N={N}")
+    B, n, fb, many = 48, 6, (16, 4), min(N * 3 // 5, 400_000)
+    assert levels_in_memory(K, N) == (0 if N < 10_000 else 2)
     bufs = []
-    for way in (2, 0):
+    for way in (2, 0, 1):
         p = PrioritizedReplay(K, N, 1, fb)
         p.set_tuning("step_on_chip", way)
         p.set_rng(99)
@@ -980,7 +1049,7 @@ def test_steps_on_the_chip_draw_and_replay_as_the_kernels_do():
         p.insert(20, rows(20), torch.zeros((1, 20), device="cuda"))
         i, w, v = p.step(None, 0.5, rand(1, B), B=B)                      # nothing to draw
         out += [i, w, v]
-        p.insert(3000, rows(3000), rand(1, 3000))
+        p.insert(many, rows(many), rand(1, many))
         slots, idx, wt, val, ro, up = new(1, n), new(1, B), new(1, B, dtype=torch.float32), new(1, B, dtype=torch.float32), rows(B), rand(1, B)
         for _ in range(3):
             p.step(None, 0.5, up, out_idx=idx, out_weight=wt, out_prio=val, rows_out=ro, B=B, insert=(n, rows(n), None, slots))
@@ -1003,8 +1072,9 @@ def test_steps_on_the_chip_draw_and_replay_as_the_kernels_do():
             out += [i, w, v]
         out += [p.read_level(0, h) for h in range(p.H + 1)] + [torch.tensor([p.status(), p.cursor, p.size])]
         got.append(out)
-    for k, (a, b) in enumerate(zip(*got)):
-        assert a.cpu().numpy().tobytes() == b.cpu().numpy().tobytes(), f"result {k}"
+    for k, (a, *others) in enumerate(zip(*got)):
+        for b in others:
+            assert a.cpu().numpy().tobytes() == b.cpu().numpy().tobytes(), f"result {k}"
 
 
 @pytest.mark.parametrize("K,N", [(2, 1), (2, 16), (2, 17), (2, 33), (2, 513), (4, 5), (4, 65), (4, 4097), (8, 9), (8, 520), (8, 1025), (16, 17),
