@@ -81,16 +81,15 @@ __device__ __forceinline__ float sum_chunks(P grp) {
 
 // The tables of heights and levels from the argument segment by vector loads (Geom first), as many entries as there can be, so
 // that none waits for another argument first.
-template <typename Args>
-__device__ __forceinline__ void fill_stream_tables(uint32_t t, const Args* a, LevelTable* tab, uint32_t* off, uint32_t* n) {
+__device__ __forceinline__ void fill_stream_tables(uint32_t t, const StreamPlan* plan, LevelTable* tab, uint32_t* off, uint32_t* n) {
   const uint32_t tid = threadIdx.x;
   if (tid <= (uint32_t)kMaxHeight) {
     const Geom* gk = kernarg_at<Geom>(0);
     tab->lvl[tid] = gk->level[tid] + (size_t)t * gk->stride[tid];
     tab->n[tid] = gk->n[tid];
   }
-  if (tid >= 64 && tid < 64 + kStreamLevels + 2) off[tid - 64] = a->off[tid - 64];
-  if (tid >= 128 && tid < 128 + kStreamLevels + 1) n[tid - 128] = a->nodes[tid - 128];
+  if (tid >= 64 && tid < 64 + kStreamLevels + 2) off[tid - 64] = plan->off[tid - 64];
+  if (tid >= 128 && tid < 128 + kStreamLevels + 1) n[tid - 128] = plan->nodes[tid - 128];
 }
 
 // One tree in the LDS of its workgroup.
@@ -274,7 +273,6 @@ __device__ __forceinline__ void store_paths(const LevelTable& tab, const LdsTree
 // wave: an item.  A wave then works with one access width and one field's constants (with the pieces of all fields
 // shared out lane by lane, every lane paid for a chain of selects over the fields, a division, and the loads and
 // stores of every width that occurs in its wave).
-constexpr int kWidths = 5;         // access widths: 16, 8, 4, 2 and 1 byte
 constexpr uint32_t kInFlight = 6;   // items that a wave which does nothing else has under way at once
 constexpr uint32_t kLeastMovers = 6;   // row waves that are left to gather where the others weigh the samples, at least
 // How the items of a gather are shared out among the row waves.
@@ -1180,8 +1178,8 @@ k_run_steps(StreamKernelArgs ka) {
   const uint32_t t = blockIdx.x;
   const uint32_t tid = threadIdx.x, lane = tid & 63u;
   const uint32_t H = g.H, T = g.T, B = a.B, n_ins = a.n_insert, N = g.N;
-  const uint32_t V = a.levels;
-  fill_stream_tables(t, kernarg_at<StreamArgs>(offsetof(StreamKernelArgs, a)), &tab, s_off, s_n);
+  const uint32_t V = a.plan.levels;
+  fill_stream_tables(t, kernarg_at<StreamPlan>(offsetof(StreamKernelArgs, a) + offsetof(StreamArgs, plan)), &tab, s_off, s_n);
   // (the lists a lane per field, by two waves)
   PieceCopy list;
   uint2 share = make_uint2(0, 0);
@@ -1590,11 +1588,11 @@ k_run_requests(QueueKernelArgs ka) {
   __shared__ uint32_t s_max, s_vmin[2], s_bmin[2], s_wild, s_arrived;
   const uint32_t t = blockIdx.x;
   const uint32_t tid = threadIdx.x, lane = tid & 63u;
-  const uint32_t H = g.H, N = g.N, n_requests = a.n_requests, V = a.levels;
+  const uint32_t H = g.H, N = g.N, n_requests = a.n_requests, V = a.plan.levels;
   const FieldTable* fields = kernarg_at<FieldTable>(offsetof(QueueKernelArgs, a) + offsetof(QueueArgs, fields));
   const uint32_t* queue = reinterpret_cast<const uint32_t*>(a.queue);
   const bool single = a.ahead == 0;
-  fill_stream_tables(t, kernarg_at<QueueArgs>(offsetof(QueueKernelArgs, a)), &tab, s_off, s_n);   // (see k_run_steps)
+  fill_stream_tables(t, kernarg_at<StreamPlan>(offsetof(QueueKernelArgs, a) + offsetof(QueueArgs, plan)), &tab, s_off, s_n);   // (see k_run_steps)
   uint32_t max_seen = 0;
   if (tid == 0) {
     max_seen = read_max_bits(g, t);
@@ -1978,7 +1976,7 @@ k_run_requests(QueueKernelArgs ka) {
 // A list or a queue can work on a tree where its heights (every one padded to whole child groups), or those above the leaves, fit
 // beside the step kernel's other LDS data.
 constexpr uint32_t kStreamLdsBytes = 156 * 1024, kStreamBatchWords = 1024;   // (the sampled indices and values of a step)
-bool stream_tree_fits(const Geom& g) {
+static bool stream_tree_fits(const Geom& g) {
   for (uint32_t skip = 0; skip < 2; ++skip) {
     uint64_t floats = kStreamBatchWords;
     for (uint32_t h = skip; h <= g.H && floats * 4 <= kStreamLdsBytes; ++h)
@@ -1987,97 +1985,83 @@ bool stream_tree_fits(const Geom& g) {
   }
   return false;
 }
-// A step by itself can also leave the level above the leaves in memory: it reads and changes few groups of it, each a trip more.
-// (Its tree is on the chip for one step: what counts there is the copy of the tree, not the trips of every step.)
-template <int LOGK>
-static uint32_t plan_stream_levels(const Geom& g, uint32_t most_in_memory, uint32_t* off, uint32_t* levels, uint32_t* in_memory);
-static bool gathers_in_runs(const FieldTable& ft, uint32_t n, uint32_t rws);
-static uint32_t team_waves(uint32_t samples, uint32_t inserted);
-bool stream_step_fits(const Geom& g, uint32_t n_insert, uint32_t B, const FieldTable& rows) {
-  if (stream_tree_fits(g)) return true;
-  uint32_t off[kStreamLevels + 2], levels = 0, in_memory = 0;
-#define CALL(L) plan_stream_levels<L>(g, 2, off, &levels, &in_memory)
-  const uint32_t floats = [&]() -> uint32_t {
-    switch (g.logK) {
-      case 1: return CALL(1);
-      case 2: return CALL(2);
-      case 3: return CALL(3);
-      case 4: return CALL(4);
-      case 5: return CALL(5);
-      case 6: return CALL(6);
-      default: return 0u;
-    }
-  }();
-#undef CALL
-  return floats && gathers_in_runs(rows, B, 16u - team_waves(B, n_insert));   // (that kernel is built for gathers in runs only)
-}
 // Levels of the copy (see Wide): the whole tree if that fits, else the levels above the leaves, or above the next one.  Narrow trees take less
 // room as levels than as heights, and the groups of zeros behind the levels (512 bytes at most, K = 64) go beyond
-// kStreamLdsBytes, so one of the two fits where stream_tree_fits() says so.  Returns the LDS floats, the batch's words
-// included (0: neither fits).
+// kStreamLdsBytes, so one of the first two fits where stream_tree_fits() says so.
 constexpr uint32_t kStreamLdsMost = kStreamLdsBytes + 512;
 template <int LOGK>
-static uint32_t plan_stream_levels(const Geom& g, uint32_t most_in_memory, uint32_t* off, uint32_t* levels, uint32_t* in_memory) {
+static StreamPlan plan_stream_levels(const Geom& g, uint32_t most_in_memory) {
   constexpr uint32_t LH = Wide<LOGK>::LH, R = Wide<LOGK>::R;
+  StreamPlan p{};
   const uint32_t V = (g.H + LH - 1) / LH;
-  if (V > kStreamLevels) return 0u;
-  for (uint32_t skip = 0; skip <= most_in_memory; ++skip) {
+  if (V > kStreamLevels) return p;
+  for (uint32_t skip = 0; skip <= most_in_memory && skip < V; ++skip) {
     uint64_t floats = 0;
     for (uint32_t v = 0; v <= V; ++v) {
-      off[v] = (uint32_t)floats;
+      p.off[v] = (uint32_t)floats;
       if (v < skip) continue;
       floats += v < V ? ((uint64_t)g.n[v * LH] + R - 1) / R * R + (v + 1 < V ? R : 0) : 4;
       if (floats * 4 > kStreamLdsMost) break;
     }
-    if ((floats + kStreamBatchWords) * 4 > kStreamLdsMost || V <= skip) continue;
-    off[V + 1] = (uint32_t)floats;
-    *levels = V;
-    *in_memory = skip;
-    return (uint32_t)floats + kStreamBatchWords;
+    if ((floats + kStreamBatchWords) * 4 > kStreamLdsMost) continue;
+    p.off[V + 1] = (uint32_t)floats;
+    for (uint32_t v = 0; v <= V; ++v) p.nodes[v] = g.n[v * LH < g.H ? v * LH : g.H];
+    p.levels = V;
+    p.levels_in_memory = skip;
+    p.floats = (uint32_t)floats + kStreamBatchWords;
+    return p;
   }
-  return 0u;
+  return p;
 }
-
-// Real nodes of every level.
-template <int LOGK>
-static void level_nodes(const Geom& g, uint32_t levels, uint32_t* nodes) {
-  for (uint32_t v = 0; v <= levels; ++v) nodes[v] = g.n[v * Wide<LOGK>::LH < g.H ? v * Wide<LOGK>::LH : g.H];
+static StreamPlan plan_stream(const Geom& g, uint32_t most_in_memory) {
+  switch (g.logK) {
+    case 1: return plan_stream_levels<1>(g, most_in_memory);
+    case 2: return plan_stream_levels<2>(g, most_in_memory);
+    case 3: return plan_stream_levels<3>(g, most_in_memory);
+    case 4: return plan_stream_levels<4>(g, most_in_memory);
+    case 5: return plan_stream_levels<5>(g, most_in_memory);
+    case 6: return plan_stream_levels<6>(g, most_in_memory);
+    default: return StreamPlan{};
+  }
 }
+StreamPlan stream_list_plan(const Geom& g) { return stream_tree_fits(g) ? plan_stream(g, 1) : StreamPlan{}; }
+// A step by itself can also leave the level above the leaves in memory: it reads and changes few groups of it, each a trip more.
+// (Its tree is on the chip for one step: what counts there is the copy of the tree, not the trips of every step.)
+StreamPlan stream_step_plan(const Geom& g) { return plan_stream(g, 2); }
 
 // Waves of the team (where it is not all of them).
 static uint32_t team_waves(uint32_t samples, uint32_t inserted) { return ((samples > inserted ? samples : inserted) + 63u) / 64u; }
-// Items that n rows are moved in, of every access width (see fill_piece_fields); returns all of them.
-static uint64_t items_by_width(const FieldTable& ft, uint32_t n, uint64_t (&of_kind)[kWidths]) {
-  uint64_t total = 0;
-  for (uint64_t& k : of_kind) k = 0;
+// Items that n rows are moved in (see fill_piece_fields).
+static RowItems row_items(const FieldTable& ft, uint32_t n) {
+  RowItems it{};
   for (uint32_t f = 0; f < ft.n_fields; ++f) {
     if (!ft.io[f]) continue;
     const uint32_t w = moves_wide(ft.bytes[f], ft.vec[f]) ? 16u : ft.vec[f];
     const uint64_t items = ((uint64_t)n * row_elements(ft.bytes[f], ft.vec[f]) + 63u) / 64u;
-    of_kind[4 - __builtin_ctz(w)] += items;
-    total += items;
+    it.of_width[4 - __builtin_ctz(w)] += items;
+    it.all += items;
   }
-  return total;
+  return it;
 }
 // Length of the runs in which a gather of n rows can be shared out among rws row waves (0: it cannot): every wave has at most
 // that many items, of one access width, and not more than it can have under way at once.
-static uint32_t gather_run(const uint64_t (&of_kind)[kWidths], uint32_t n, uint32_t rws) {
+static uint32_t gather_run(const RowItems& it, uint32_t n, uint32_t rws) {
   for (uint32_t len = 1; len <= kInFlight; ++len) {
     uint64_t needed = 0;
-    for (int c = 0; c < kWidths; ++c) needed += (of_kind[c] + len - 1) / len;
+    for (const uint64_t of_this : it.of_width) needed += (of_this + len - 1) / len;
     if (needed <= run_waves(n, rws)) return len;
   }
   return 0;
 }
-static bool gathers_in_runs(const FieldTable& ft, uint32_t n, uint32_t rws) {
-  uint64_t of_kind[kWidths];
-  (void)items_by_width(ft, n, of_kind);
-  return gather_run(of_kind, n, rws) != 0;
+void plan_stream_rows(StreamCall* a) {
+  a->gathered = row_items(a->rows, a->B);
+  a->placed = row_items(a->ins, a->n_insert);
+  const uint32_t team = team_waves(a->B, a->n_insert);
+  a->run = team < 16u ? gather_run(a->gathered, a->B, 16u - team) : 0u;
 }
 // The list of n rows' pieces for the kernel (the items ordered by access width, and those of one width by field).
-static void plan_pieces(const FieldTable& ft, uint32_t n, uint32_t trees, PieceList* pl) {
-  uint64_t of_kind[kWidths];
-  pl->items = (uint32_t)items_by_width(ft, n, of_kind);
+static void plan_pieces(const FieldTable& ft, const RowItems& it, uint32_t n, uint32_t trees, PieceList* pl) {
+  pl->items = (uint32_t)it.all;
   pl->n = n;
   pl->step_rows = (uint64_t)trees * n;
   pl->base = ft.n_fields ? ft.col[0] : nullptr;
@@ -2099,23 +2083,20 @@ static void plan_pieces(const FieldTable& ft, uint32_t n, uint32_t trees, PieceL
     }
   }
 }
-// Which of a gather's items every one of the rws row waves has: runs, or equally many (`even`).
-static void plan_shares(const FieldTable& ft, uint32_t n, uint32_t rws, bool even, uint2 (&share)[16]) {
-  uint64_t of_kind[kWidths];
-  const uint64_t total = items_by_width(ft, n, of_kind);
-  const uint32_t run = even ? 0u : gather_run(of_kind, n, rws);
+// Which of a gather's items every one of the rws row waves has: runs of that length, or (run 0) equally many.
+static void plan_shares(const RowItems& it, uint32_t run, uint32_t rws, uint2 (&share)[16]) {
   uint32_t wave = 0;
   if (run) {
     uint32_t start = 0;
-    for (int c = 0; c < kWidths; ++c) {
-      const uint32_t end = start + (uint32_t)of_kind[c];
+    for (const uint64_t of_this : it.of_width) {
+      const uint32_t end = start + (uint32_t)of_this;
       for (; start < end; start += run) share[wave++] = make_uint2(start, start + run < end ? start + run : end);
       start = end;
     }
   } else {
-    const uint64_t each = (total + rws - 1) / rws;
-    for (uint64_t first = 0; first < total; first += each)
-      share[wave++] = make_uint2((uint32_t)first, (uint32_t)(first + each < total ? first + each : total));
+    const uint64_t each = (it.all + rws - 1) / rws;
+    for (uint64_t first = 0; first < it.all; first += each)
+      share[wave++] = make_uint2((uint32_t)first, (uint32_t)(first + each < it.all ? first + each : it.all));
   }
 }
 
@@ -2135,44 +2116,28 @@ static void plan_shares(const FieldTable& ft, uint32_t n, uint32_t rws, bool eve
 // the way taken is 0.8 % behind the better one on average.
 // Batches beyond 256 at K > 2 are left out, though several trees of a few thousand leaves would gain (410 samples on each of 4 trees
 // of 27 915 leaves at K = 32: 16.8 and 13.1): of 71 such shapes that the fits would take, three lose 6 to 13 %.
-template <int LOGK>
-static bool step_on_chip_pays_k(const Geom& g, const Tuning& tn, uint32_t n_insert, uint32_t B, const FieldTable& rows, const FieldTable& ins) {
-  uint32_t off[kStreamLevels + 2], levels = 0, in_memory = 0;
-  const uint64_t floats = plan_stream_levels<LOGK>(g, 2, off, &levels, &in_memory);
-  if (!floats || g.T > 64 || (B > 256 && g.K > 2)) return false;
-  uint64_t row = 0, of_kind[kWidths];
-  for (uint32_t f = 0; f < rows.n_fields; ++f) row += rows.io[f] ? rows.bytes[f] : 0u;
+bool step_on_chip_pays(const Geom& g, const Tuning& tn, const StreamCall& a) {
+  const uint32_t B = a.B, n_insert = a.n_insert, floats = a.plan.floats, in_memory = a.plan.levels_in_memory;
+  if (g.T > 64 || (B > 256 && g.K > 2)) return false;
+  uint64_t row = 0;
+  for (uint32_t f = 0; f < a.rows.n_fields; ++f) row += a.rows.io[f] ? a.rows.bytes[f] : 0u;
   const uint32_t rws = 16u - team_waves(B, n_insert);
-  const uint64_t gathered = items_by_width(rows, B, of_kind), placed = items_by_width(ins, n_insert, of_kind);
+  const uint64_t gathered = a.gathered.all, placed = a.placed.all;
   int64_t here = 520 + (team_form(B, n_insert) == TEAM_ONE_WAVE ? 0 : 138) + (n_insert ? 55 : 0) + (g.T >= 16 ? 71 : 0) + (g.K == 64 ? 37 * B / 64 : 0);
-  const bool runs = gathers_in_runs(rows, B, rws);
-  here += runs ? 80 * gathered / rws : 136 + 19 * gathered / rws;
+  here += a.run ? 80 * gathered / rws : 136 + 19 * gathered / rws;
   here += (placed > rws ? 81 * (placed - rws) / rws : 0) + floats * 4 / 1024 + (g.K == 2 ? 40 : g.K == 4 ? 20 : 0);
   if (in_memory) {
     here += in_memory == 1 ? 40 + 40 * B / 64 : 100 + 55 * B / 64 + (n_insert ? 25 : 0);
     here += g.K == 2 ? 40 + (in_memory == 1 ? 25 : 60) * B / 64 : g.K == 64 ? 70 + 60 * B / 64 : 0;
   }
   bool has_rows = false;
-  for (uint32_t f = 0; f < ins.n_fields; ++f) has_rows = has_rows || ins.io[f];
+  for (uint32_t f = 0; f < a.ins.n_fields; ++f) has_rows = has_rows || a.ins.io[f];
   // (asked as for a ring at its start: the way does not change in the one step whose rows go round its end)
-  const bool carried = n_insert && sample_can_carry_insert(g, tn, B, has_rows ? &ins : nullptr, n_insert, 0);
+  const bool carried = n_insert && sample_can_carry_insert(g, tn, B, has_rows ? &a.ins : nullptr, n_insert, 0);
   int64_t apart = 938 + (!n_insert ? 0 : carried ? 273 : 374 + (g.K <= 4 ? 141 : 0)) + (g.K == 2 ? 106 * (int64_t)g.H - 815 : 0);
   apart += (g.N > 1u << 20 ? 170 : 0) + (g.K == 64 && g.H >= 3 ? 90 : 0) + (g.K == 4 && g.H >= 9 ? 600 : 0);
   apart += (g.K == 4 ? 87 : 0) + (g.K >= 32 ? 55 : 0) + (g.T >= 16 ? 105 : 0) + (int64_t)(176 * g.T * B * row >> 20);
-  return here * (runs ? 103 : 110) < apart * 100;
-}
-bool step_on_chip_pays(const Geom& g, const Tuning& tn, uint32_t n_insert, uint32_t B, const FieldTable& rows, const FieldTable& ins) {
-#define CALL(L) step_on_chip_pays_k<L>(g, tn, n_insert, B, rows, ins)
-  switch (g.logK) {
-    case 1: return CALL(1);
-    case 2: return CALL(2);
-    case 3: return CALL(3);
-    case 4: return CALL(4);
-    case 5: return CALL(5);
-    case 6: return CALL(6);
-    default: return false;
-  }
-#undef CALL
+  return here * (a.run ? 103 : 110) < apart * 100;
 }
 
 template <int LOGK>
@@ -2180,20 +2145,18 @@ static hipError_t launch_run_steps_k(const Geom& g, const Tuning& tn, const Stre
   StreamKernelArgs ka{};
   ka.g = g;
   ka.a = a;
-  const uint32_t floats = plan_stream_levels<LOGK>(g, a.most_in_memory, ka.a.off, &ka.a.levels, &ka.a.levels_in_memory);
-  if (!floats) return hipErrorInvalidValue;
-  const size_t bytes = (size_t)floats * 4;
+  if (!a.plan.floats) return hipErrorInvalidValue;
+  const size_t bytes = (size_t)a.plan.floats * 4;
   // always the largest workgroup, also for small batches: measured faster than a workgroup of the batch's
   // size (the tree copy and the row movers use all lanes)
   TeamForm form = team_form(a.B, a.n_insert);
-  if (form != TEAM_ALL && !gathers_in_runs(a.rows, a.B, 16u - team_waves(a.B, a.n_insert))) form = a.ahead ? TEAM_WAVES_SPANS : TEAM_ALL;
-  level_nodes<LOGK>(g, ka.a.levels, ka.a.nodes);
-  plan_pieces(a.rows, a.B, g.T, &ka.rows);
-  plan_pieces(a.ins, a.n_insert, g.T, &ka.ins);
-  plan_shares(a.rows, a.B, form == TEAM_ALL ? 16u : 16u - team_waves(a.B, a.n_insert), form == TEAM_ALL || form == TEAM_WAVES_SPANS, ka.share);
+  if (form != TEAM_ALL && !a.run) form = a.ahead ? TEAM_WAVES_SPANS : TEAM_ALL;
+  plan_pieces(a.rows, a.gathered, a.B, g.T, &ka.rows);
+  plan_pieces(a.ins, a.placed, a.n_insert, g.T, &ka.ins);
+  plan_shares(a.gathered, form == TEAM_ONE_WAVE || form == TEAM_WAVES ? a.run : 0u, form == TEAM_ALL ? 16u : 16u - team_waves(a.B, a.n_insert), ka.share);
   ka.a.rows_stride = a.rows.row_stride;
   ka.a.ins_stride = a.ins.row_stride;
-  const uint32_t mem = ka.a.levels_in_memory;
+  const uint32_t mem = a.plan.levels_in_memory;
 #define PER_RUN(F, M, A)                                                                                \
   do {                                                                                                  \
     hipError_t e = grant_lds<&k_run_steps<LOGK, F, M, A>>(tn, bytes);                                   \
@@ -2208,7 +2171,7 @@ static hipError_t launch_run_steps_k(const Geom& g, const Tuning& tn, const Stre
   do {                                                                                                  \
     if (a.ahead) PER_RUN_WHERE(F, true); else PER_RUN_WHERE(F, false);                                  \
   } while (0)
-  if (mem > 1) {   // (see stream_step_fits)
+  if (mem > 1) {   // (built for single steps whose gathers go in runs only)
     if (a.n_steps != 1 || !a.ahead || !a.upd_is_sampled || form > TEAM_WAVES) return hipErrorInvalidValue;
     if (form == TEAM_ONE_WAVE) PER_RUN(TEAM_ONE_WAVE, 2, true); else PER_RUN(TEAM_WAVES, 2, true);
   } else if (form == TEAM_ONE_WAVE) PER_RUN_WHEN(TEAM_ONE_WAVE);
@@ -2232,12 +2195,10 @@ static hipError_t launch_run_requests_k(const Geom& g, const Tuning& tn, const Q
   QueueKernelArgs ka{};
   ka.g = g;
   ka.a = a;
-  const uint32_t floats = plan_stream_levels<LOGK>(g, 1, ka.a.off, &ka.a.levels, &ka.a.levels_in_memory);
-  if (!floats) return hipErrorInvalidValue;
-  level_nodes<LOGK>(g, ka.a.levels, ka.a.nodes);
-  const size_t bytes = (size_t)floats * 4;
+  if (!a.plan.floats) return hipErrorInvalidValue;
+  const size_t bytes = (size_t)a.plan.floats * 4;
   const TeamForm form = team_form(a.most, 0);
-  const bool mem = ka.a.levels_in_memory != 0;
+  const bool mem = a.plan.levels_in_memory != 0;
 #define PER_RUN(F, M)                                                                                   \
   do {                                                                                                  \
     hipError_t e = grant_lds<&k_run_requests<LOGK, F, M>>(tn, bytes);                                   \

@@ -40,6 +40,7 @@ struct per_buffer {
   unsigned long long capture_id;   // the stream capture the last call was recorded into (0: it ran eagerly)
   bool rng_on;               // per_set_rng was called: sampling calls without uniforms draw their own
   uint64_t rng_seed, rng_calls;   // key of the generator; number of sampling calls that drew from it
+  StreamPlan list_plan, step_plan;   // what the on-chip kernels hold of a tree: lists and queues, a step by itself
   int device;
   uint8_t* arena_tab;        // where the arena keeps the tables of the one-kernel step (they may sit in the kernels' static array instead)
   uint32_t* static_scratch;   // this device's copy of the static array of per_min_priority_static (null: its address could not be had)
@@ -341,6 +342,8 @@ int per_create(const per_config* cfg, void* d_arena, size_t arena_bytes, void* s
   g.step_tab = p->arena_tab;
   g.step_tab_static = 0;
   g.step_ho = step_owner_height(g);
+  p->list_plan = stream_list_plan(g);
+  p->step_plan = stream_step_plan(g);
   g.min1 = reinterpret_cast<uint32_t*>(p->arena + L.min1_off);
   g.min1_stride = L.min1_stride;
   for (uint32_t f = 0; f < cfg->n_fields; ++f) {
@@ -669,10 +672,17 @@ static bool step_on_chip(per_t* p, uint32_t n, const void* const* d_field_src, c
                         static_cast<const void*>(d_out_idx), static_cast<const void*>(d_out_weight),
                         static_cast<const void*>(d_out_prio), static_cast<const void*>(d_upd_prio)})
     if (misaligned(a, 4)) return false;
+  if (!p->step_plan.floats) return false;
   StreamCall a{};
+  a.plan = p->step_plan;
+  a.n_steps = 1;
+  a.n_insert = n;
+  a.B = B;
   (void)fill_fields(p, d_field_dst, &a.rows);
   if (n) (void)fill_fields(p, const_cast<void* const*>(reinterpret_cast<const void* const*>(d_field_src)), &a.ins);
-  if (!stream_step_fits(p->g, n, B, a.rows) || (!forced && !step_on_chip_pays(p->g, p->tn, n, B, a.rows, a.ins))) return false;
+  plan_stream_rows(&a);
+  // (on trees that lists do not take, by gathers in runs only)
+  if ((!p->list_plan.floats && !a.run) || (!forced && !step_on_chip_pays(p->g, p->tn, a))) return false;
   Span in[3 + PER_MAX_FIELDS], out[4 + PER_MAX_FIELDS];
   uint32_t ni = 0, no = 0;
   const uint64_t samples = (uint64_t)p->g.T * B, rows = (uint64_t)p->g.T * n;
@@ -698,10 +708,6 @@ static bool step_on_chip(per_t* p, uint32_t n, const void* const* d_field_src, c
   // the usual way for another reason among them) and steps take turns.
   p->step_before = true;
   if (!forced && p->stale_hb && !after_step) return false;
-  a.n_steps = 1;
-  a.most_in_memory = 2;
-  a.n_insert = n;
-  a.B = B;
   a.cursor = (uint32_t)p->cursor;
   a.size = (uint32_t)p->size;
   a.upd_is_sampled = 1;
@@ -887,7 +893,7 @@ int per_update_delta(per_t* p, uint32_t B, const uint32_t* d_idx, const float* d
   return hip_rc(e);
 }
 
-int per_run_steps_fits(const per_t* p) { return p && stream_tree_fits(p->g) ? 1 : 0; }
+int per_run_steps_fits(const per_t* p) { return p && p->list_plan.floats ? 1 : 0; }
 
 // True where no step of the list reads memory that a step writes its results to.
 static bool step_inputs_apart(const per_t* p, uint32_t n_steps, uint32_t n_insert, uint32_t B, const per_stream_io* io) {
@@ -913,7 +919,7 @@ int per_run_steps(per_t* p, uint32_t n_steps, uint32_t n_insert, uint32_t B, con
   if (!p || !io || io->struct_size != sizeof(per_stream_io)) return PER_EINVAL;
   if (n_steps == 0) return PER_OK;
   if (B == 0 || B > 1024 || n_insert > 1024 || n_insert > p->cfg.capacity) return PER_ERANGE;
-  if (!stream_tree_fits(p->g)) return PER_ERANGE;   // the tree does not fit the LDS of a compute unit
+  if (!p->list_plan.floats) return PER_ERANGE;   // the tree does not fit the LDS of a compute unit
   if (!io->d_u || !io->d_beta || !io->d_out_idx || misaligned(io->d_u, 4) || misaligned(io->d_beta, 4) ||
       misaligned(io->d_out_idx, 4) || misaligned(io->d_out_weight, 4) || misaligned(io->d_out_prio, 4) ||
       misaligned(io->d_upd_idx, 4) || misaligned(io->d_upd_prio, 4) || misaligned(io->d_ins_prio, 4))
@@ -923,7 +929,7 @@ int per_run_steps(per_t* p, uint32_t n_steps, uint32_t n_insert, uint32_t B, con
   hipStream_t s = static_cast<hipStream_t>(stream);
   CaptureGuard capture(p, s);
   StreamCall a{};
-  a.most_in_memory = 1;
+  a.plan = p->list_plan;
   a.n_steps = n_steps;
   a.n_insert = n_insert;
   a.B = B;
@@ -944,6 +950,7 @@ int per_run_steps(per_t* p, uint32_t n_steps, uint32_t n_insert, uint32_t B, con
   a.ins_prio = io->d_ins_prio;
   if (n_insert) (void)fill_fields(p, const_cast<void* const*>(reinterpret_cast<const void* const*>(io->d_ins_rows)), &a.ins);
   (void)fill_fields(p, io->d_rows_out, &a.rows);
+  plan_stream_rows(&a);
   hipError_t e = ensure_sums(p, s);
   if (e == hipSuccess) e = launch_run_steps(p->g, p->tn, a, s);
   const uint64_t N = p->cfg.capacity, added = (uint64_t)n_steps * n_insert;
@@ -990,7 +997,7 @@ int per_run_requests(per_t* p, uint32_t n_requests, const per_request* h_request
   if (!p) return PER_EINVAL;
   if (n_requests == 0) return PER_OK;
   if (!h_requests || !d_requests || misaligned(d_requests, 8)) return PER_EINVAL;
-  if (!stream_tree_fits(p->g)) return PER_ERANGE;   // the tree does not fit the LDS of a compute unit
+  if (!p->list_plan.floats) return PER_ERANGE;   // the tree does not fit the LDS of a compute unit
   QueueArgs a{};
   (void)fill_fields(p, nullptr, &a.fields);
   for (uint32_t f = 0; f < a.fields.n_fields; ++f) a.fields.vec[f] = vec_width(a.fields.bytes[f], nullptr);
@@ -1033,6 +1040,7 @@ int per_run_requests(per_t* p, uint32_t n_requests, const per_request* h_request
   a.cursor = (uint32_t)p->cursor;
   a.size = (uint32_t)p->size;
   a.queue = d_requests;
+  a.plan = p->list_plan;
   hipError_t e = ensure_sums(p, s);
   if (e == hipSuccess) e = launch_run_requests(p->g, p->tn, a, s);
   p->cursor = cursor;

@@ -21,7 +21,8 @@ constexpr uint32_t kVminSlots = 256;   // partial batch minima per tree and buff
 constexpr uint32_t kStepGroups = 64;   // counters the owners of the one-kernel step are spread over (one wave reads them all)
 constexpr uint32_t kStepDoneSlots = 8; // counters its builders are spread over
 constexpr uint32_t kStepMaxOwners = 2048;   // most owner workgroups over all trees
-constexpr uint32_t kStreamLevels = 8;  // most levels above the leaves of an on-chip tree (K = 8, 272 000 leaves: 7)
+constexpr uint32_t kStreamLevels = 8;  // most levels above the leaves of an on-chip tree (K = 8, from 2 097 153 leaves on, for a single step: 8)
+constexpr int kWidths = 5;             // access widths of rows: 16, 8, 4, 2 and 1 byte
 
 struct Geom {
   uint32_t K, logK, H, T;
@@ -143,6 +144,19 @@ struct FinishArgs {
   ClaimArgs claim;
 };
 
+// What of a tree an on-chip kernel holds in LDS, and where: follows from the geometry, and is worked out once, with the buffer.
+struct StreamPlan {
+  uint32_t floats;                  // of LDS, the words of a batch among them (0: the tree does not fit)
+  uint32_t off[kStreamLevels + 2];  // where level v of the LDS copy starts (floats); off[levels + 1] = all floats
+  uint32_t nodes[kStreamLevels + 1];// real nodes of every level
+  uint32_t levels;                  // levels above the leaves (see Wide)
+  uint32_t levels_in_memory;        // the LDS copy holds the levels above the lowest ones only (so many)
+};
+// What the rows of a step move in: items of 64 pieces, by the pieces' access width.
+struct RowItems {
+  uint64_t of_width[kWidths], all;
+};
+
 // A list of steps run by one workgroup per tree on an LDS copy of the tree (see k_run_steps).
 struct StreamArgs {
   uint32_t n_steps, n_insert, B;
@@ -163,14 +177,13 @@ struct StreamArgs {
   uint32_t* ins_slots;              // one step: [T][n_insert] or null
   // planned by the launcher
   uint32_t rows_stride, ins_stride; // bytes between stored rows (of the gather's and of the insertion's fields)
-  uint32_t off[kStreamLevels + 2];  // where level v of the LDS copy starts (floats); off[levels + 1] = all floats
-  uint32_t nodes[kStreamLevels + 1];// real nodes of every level
-  uint32_t levels;                  // levels above the leaves (see Wide)
-  uint32_t levels_in_memory;        // the LDS copy holds the levels above the lowest ones only (so many)
+  StreamPlan plan;
 };
 struct StreamCall : StreamArgs {    // with the fields, of which the kernel has its own lists
-  uint32_t most_in_memory;          // a step by itself: 2, else 1
   FieldTable ins, rows;             // io arrays hold [steps][T][n][bytes]; io all null: nothing to move
+  // worked out by plan_stream_rows
+  RowItems placed, gathered;
+  uint32_t run;                     // length of the runs that the gather is shared out in (0: it cannot be, see gather_run)
 };
 
 // A queue of op-coded requests run by one workgroup per tree on an LDS copy of the tree (see k_run_requests).
@@ -182,10 +195,7 @@ struct QueueArgs {
   uint32_t ahead;                   // what a request reads may be fetched before the ones just before it are done
   const per_request* queue;         // device copy of the requests
   FieldTable fields;                // columns, row sizes and access widths; the io pointers come from the requests
-  uint32_t off[kStreamLevels + 2];  // as in StreamArgs
-  uint32_t nodes[kStreamLevels + 1];
-  uint32_t levels;
-  uint32_t levels_in_memory;
+  StreamPlan plan;
 };
 
 // Workgroup ranges of the jobs sharing one launch: [first[j], first[j+1]) for job j, where job 0 is the
@@ -304,9 +314,10 @@ size_t step_table_bytes();
 // or when `device` is not the current one), and given back.
 void* step_static_claim(const void* holder, int device, hipStream_t s);
 void step_static_release(const void* holder, int device);
-bool stream_tree_fits(const Geom& g);
-bool stream_step_fits(const Geom& g, uint32_t n_insert, uint32_t B, const FieldTable& rows);
-bool step_on_chip_pays(const Geom& g, const Tuning& tn, uint32_t n_insert, uint32_t B, const FieldTable& rows, const FieldTable& ins);
+StreamPlan stream_list_plan(const Geom& g);   // for lists and queues
+StreamPlan stream_step_plan(const Geom& g);   // for a step by itself
+void plan_stream_rows(StreamCall* a);         // (needs n_insert, B, ins, rows)
+bool step_on_chip_pays(const Geom& g, const Tuning& tn, const StreamCall& a);
 hipError_t launch_run_steps(const Geom& g, const Tuning& tn, const StreamCall& a, hipStream_t s);
 hipError_t launch_run_requests(const Geom& g, const Tuning& tn, const QueueArgs& a, hipStream_t s);
 hipError_t launch_get_priority(const Geom& g, const Tuning& tn, uint32_t n, const uint32_t* idx, float* out, hipStream_t s);
