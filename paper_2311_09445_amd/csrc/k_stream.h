@@ -13,9 +13,10 @@
 // access; only rows, inputs and outputs travel to memory.  Results are those of the separate calls.
 //
 // A tree whose leaves do not fit beside the rest (MEM: levels in memory) keeps what is above them in LDS and its leaves in
-// memory: the paper's 100K-entry buffers at small fanouts are of that size.  A list of one step, which has few groups to read
-// and no further steps to pay for them, also leaves the level above the leaves there.  The workgroup is still the only one that
-// touches the tree while the kernel runs, so its own stores, made visible to its other waves by a
+// memory: the paper's 100K-entry buffers at small fanouts are of that size.  per_step and per_insert_step, which come here with one
+// step, few groups to read and no further steps to pay for them, also leave the level above the leaves there.  A list of one step that
+// updates the batch it draws, or none, stores only the paths of what it has changed (see store_paths).  The workgroup is still the only one
+// that touches the tree while the kernel runs, so its own stores, made visible to its other waves by a
 // barrier, are all the coherence that takes; every operation then costs a trip or two to memory for the leaf
 // groups it reads (sampling: the last level of the walk; insert and update: the groups whose sums change).
 // Of narrow trees the copy holds some heights only (see Wide).  Every node is taken for the sum of its children, which
@@ -1160,7 +1161,7 @@ static TeamForm team_form(uint32_t samples, uint32_t inserted) {
 // (its loads are issued behind the barrier that ends the sampling), and overwrite what the gather of the step before has
 // read (whose loads are issued in front of the barrier before the insertion's stores); the accesses of a workgroup's waves
 // keep that order (see TreeView::sync).
-// 100 steps on 10 000 leaves at K = 16 (32 samples, 4 new rows of 41 bytes): 169 us; 1001 us as one phase after the
+// 100 steps on 10 000 leaves at K = 16 (32 samples, 4 new rows of 41 bytes): 166 us; 1001 us as one phase after the
 // other by the whole workgroup with a full barrier between them.
 // AHEAD: no step reads what a step returns.
 template <int LOGK, TeamForm FORM, int MEM, bool AHEAD>
@@ -1498,7 +1499,7 @@ k_run_steps(StreamKernelArgs ka) {
 // 20 times (insert 16 rows, sample 512, update them) on 30 000 leaves at K = 16: 110 us; 353 us one request after the
 // other by the whole workgroup with a full barrier between their phases.  The row waves are at work throughout, and the
 // team waits for them at both barriers, a third of the round.
-struct QueueKernelArgs {            // one kernel argument (Geom first: see fill_level_table)
+struct QueueKernelArgs {            // one kernel argument (Geom first: see fill_stream_tables)
   Geom g;
   QueueArgs a;
 };
@@ -1985,8 +1986,8 @@ static bool stream_tree_fits(const Geom& g) {
   }
   return false;
 }
-// Levels of the copy (see Wide): the whole tree if that fits, else the levels above the leaves, or above the next one.  Narrow trees take less
-// room as levels than as heights, and the groups of zeros behind the levels (512 bytes at most, K = 64) go beyond
+// Levels of the copy (see Wide): the whole tree if that fits, else the levels above the leaves, or above the next one.  Narrow trees take
+// less room as levels than as heights, and the groups of zeros behind the levels (512 bytes at most, K = 64) go beyond
 // kStreamLdsBytes, so one of the first two fits where stream_tree_fits() says so.
 constexpr uint32_t kStreamLdsMost = kStreamLdsBytes + 512;
 template <int LOGK>

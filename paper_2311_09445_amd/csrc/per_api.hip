@@ -652,9 +652,10 @@ static bool spans_meet(const Span* a, uint32_t na, const Span* b, uint32_t nb) {
       if (a[i].lo < b[j].hi && b[j].lo < a[i].hi) return true;
   return false;
 }
-// A step with its insertion, as one launch of the kernel of per_run_steps: one workgroup per tree, which copies the tree (or
-// what is above its leaves) to its LDS, inserts, samples, updates, moves the rows and stores the tree.  Taken where
-// step_on_chip_pays says so, for weights relative to the batch, and where nothing the call reads lies in what it writes.
+// A step with its insertion, as one launch of the kernel of per_run_steps: one workgroup per tree, which copies the tree (or what
+// is above its leaves, or above the level over them) to its LDS, inserts, samples, updates, moves the rows and stores the paths of
+// what it has changed.  Taken where step_on_chip_pays says so, for weights relative to the batch, and where nothing the call reads
+// lies in what it writes.
 // Returns false where the call takes its usual way (which also has the errors).
 static bool step_on_chip(per_t* p, uint32_t n, const void* const* d_field_src, const float* d_ins_prio, uint32_t* d_ins_out_idx, uint32_t B,
                          float beta, const float* d_u, uint32_t* d_out_idx, float* d_out_weight, float* d_out_prio,
