@@ -102,21 +102,25 @@ __device__ __forceinline__ void sweep_load(const RowMove& m, uint64_t e0, Regs<u
     sweep_load<V, GATHER, K + 1, U>(m, e0, at, v, bad);
   }
 }
-template <typename V, bool GATHER, int K, int U>
+typedef uint32_t Quad __attribute__((ext_vector_type(4)));
+template <typename V, bool GATHER, bool STREAMS, int K, int U>
 __device__ __forceinline__ void sweep_store(const RowMove& m, uint64_t e0, Regs<uint32_t, U>& at, Regs<Held<V>, U>& v) {
   if constexpr (K < U) {
     bool live;
     const uint64_t e = sweep_elem<K>(m, e0, live);
     if (live) {
-      if constexpr (GATHER) *(reinterpret_cast<V*>(m.io) + e) = (V)reg<K>(v);
+      if constexpr (GATHER && STREAMS && sizeof(V) == 16) {
+        const uint4 x = reg<K>(v);
+        __builtin_nontemporal_store(Quad{x.x, x.y, x.z, x.w}, reinterpret_cast<Quad*>(m.io) + e);
+      } else if constexpr (GATHER) *(reinterpret_cast<V*>(m.io) + e) = (V)reg<K>(v);
       else *(reinterpret_cast<V*>(m.col + (uint64_t)reg<K>(at) * m.RS) + (uint32_t)(e % m.epr)) = (V)reg<K>(v);
     }
-    sweep_store<V, GATHER, K + 1, U>(m, e0, at, v);
+    sweep_store<V, GATHER, STREAMS, K + 1, U>(m, e0, at, v);
   }
 }
 
 // (row0, nrows: only the rows [row0, row0 + nrows) of the B rows per tree; gathers only)
-template <typename V, bool GATHER>
+template <typename V, bool GATHER, bool STREAMS>
 __device__ __forceinline__ void move_rows(const FieldTable& ft, uint32_t f, uint32_t t, uint32_t B,
                                           const uint32_t* __restrict__ idx, uint32_t cursor, uint32_t N,
                                           uint32_t* status, uint32_t job_block, uint32_t job_blocks, uint32_t row0 = 0,
@@ -139,7 +143,7 @@ __device__ __forceinline__ void move_rows(const FieldTable& ft, uint32_t f, uint
     Regs<Held<V>, U> v;
     sweep_where<V, GATHER, 0, U>(m, e0, at);
     sweep_load<V, GATHER, 0, U>(m, e0, at, v, bad);
-    sweep_store<V, GATHER, 0, U>(m, e0, at, v);
+    sweep_store<V, GATHER, STREAMS, 0, U>(m, e0, at, v);
   }
   if (bad) atomicOr(&status[t], 1u);
 }
@@ -353,14 +357,15 @@ __device__ __forceinline__ uint32_t job_field(const JobRanges& jr, uint32_t b) {
 // Moves the rows of one payload field; the workgroup is number job_block of job_blocks on that field.
 // WIDE: the kernel was built with the 16-byte moves on 4-byte boundaries (see Wide16); the launchers pick
 // that build only when a field of the call moves that way, so that calls without one run the smaller code.
-template <bool GATHER, bool WIDE>
+// STREAMS: likewise for rows that are stored past the caches (see gather_streams).
+template <bool GATHER, bool WIDE, bool STREAMS = false>
 __device__ __forceinline__ void rows_job(const FieldTable& ft, uint32_t f, uint32_t t, uint32_t B,
                                          const uint32_t* __restrict__ idx, uint32_t cursor, uint32_t N,
                                          uint32_t* status, uint32_t job_block, uint32_t job_blocks, uint32_t row0 = 0,
                                          uint32_t nrows = 0xFFFFFFFFu) {
   switch (ft.vec[f]) {
-    case 16: move_rows<uint4, GATHER>(ft, f, t, B, idx, cursor, N, status, job_block, job_blocks, row0, nrows); break;
-    case 8: move_rows<uint2, GATHER>(ft, f, t, B, idx, cursor, N, status, job_block, job_blocks, row0, nrows); break;
+    case 16: move_rows<uint4, GATHER, STREAMS>(ft, f, t, B, idx, cursor, N, status, job_block, job_blocks, row0, nrows); break;
+    case 8: move_rows<uint2, GATHER, STREAMS>(ft, f, t, B, idx, cursor, N, status, job_block, job_blocks, row0, nrows); break;
     case 4:
       if constexpr (WIDE) {
         if (moves_wide(ft.bytes[f], 4)) {
@@ -368,10 +373,10 @@ __device__ __forceinline__ void rows_job(const FieldTable& ft, uint32_t f, uint3
           break;
         }
       }
-      move_rows<uint32_t, GATHER>(ft, f, t, B, idx, cursor, N, status, job_block, job_blocks, row0, nrows);
+      move_rows<uint32_t, GATHER, STREAMS>(ft, f, t, B, idx, cursor, N, status, job_block, job_blocks, row0, nrows);
       break;
-    case 2: move_rows<uint16_t, GATHER>(ft, f, t, B, idx, cursor, N, status, job_block, job_blocks, row0, nrows); break;
-    default: move_rows<uint8_t, GATHER>(ft, f, t, B, idx, cursor, N, status, job_block, job_blocks, row0, nrows); break;
+    case 2: move_rows<uint16_t, GATHER, STREAMS>(ft, f, t, B, idx, cursor, N, status, job_block, job_blocks, row0, nrows); break;
+    default: move_rows<uint8_t, GATHER, STREAMS>(ft, f, t, B, idx, cursor, N, status, job_block, job_blocks, row0, nrows); break;
   }
 }
 
@@ -471,7 +476,7 @@ __device__ __forceinline__ void ride_rows(const InsertRide& ride, uint32_t t, ui
 // asked for), then the claim phase of a priority update (if one is fused in), then one job per
 // payload field of the sampled rows, or a single job over whole rows (move_whole_rows) in the first
 // asked-for field's range.  The small jobs come first, so their latency hides behind the row traffic.
-template <bool WIDE>
+template <bool WIDE, bool STREAMS>
 __global__ void k_finish(FieldTable ft, JobRanges jr, Geom g, FinishArgs a) {
   const uint32_t t = blockIdx.y;
   const uint32_t b = blockIdx.x;
@@ -488,11 +493,11 @@ __global__ void k_finish(FieldTable ft, JobRanges jr, Geom g, FinishArgs a) {
     extern __shared__ __attribute__((aligned(16))) uint8_t stage[];
     move_whole_rows(ft, jr, t, a.B, a.idx, g.N, g.status, b - jr.first[2 + f], jr.first[3 + f] - jr.first[2 + f], stage);
   } else if (f < (uint32_t)kMaxFields)
-    rows_job<true, WIDE>(ft, f, t, a.B, a.idx, 0, g.N, g.status, b - jr.first[2 + f], jr.first[3 + f] - jr.first[2 + f]);
+    rows_job<true, WIDE, STREAMS>(ft, f, t, a.B, a.idx, 0, g.N, g.status, b - jr.first[2 + f], jr.first[3 + f] - jr.first[2 + f]);
 }
 
 // Stand-alone gather: one job per payload field, or one over whole rows.
-template <bool WIDE>
+template <bool WIDE, bool STREAMS>
 __global__ void k_rows(FieldTable ft, JobRanges jr, uint32_t B, const uint32_t* __restrict__ idx, uint32_t N, uint32_t* status) {
   const uint32_t t = blockIdx.y;
   const uint32_t b = blockIdx.x;
@@ -503,7 +508,7 @@ __global__ void k_rows(FieldTable ft, JobRanges jr, uint32_t B, const uint32_t* 
     return;
   }
   if (f < (uint32_t)kMaxFields)
-    rows_job<true, WIDE>(ft, f, t, B, idx, 0, N, status, b - jr.first[2 + f], jr.first[3 + f] - jr.first[2 + f]);
+    rows_job<true, WIDE, STREAMS>(ft, f, t, B, idx, 0, N, status, b - jr.first[2 + f], jr.first[3 + f] - jr.first[2 + f]);
 }
 
 // Workgroups per job: weights, claim, then each field with a destination.  A field gets the workgroups one
@@ -587,6 +592,25 @@ static bool any_field_moves_wide(const FieldTable* ft) {
   return false;
 }
 
+// Whether a gather stores its 16-byte elements past the caches: where the rows of the launch come to 192 MiB, over all fields and
+// trees.  The 256 MB behind the second-level caches then do not keep them for their reader beside what was read, and storing
+// them there pushes out what the calls around read again.  `sample` with rows and `update` of 2^24 leaves (rows of 128 bytes, K = 32) at
+// 192 MiB: 186.3 -> 172.7 us, with a kernel between that reads the rows 241.1 both, where it copies them 257.1 -> 258.5; at 256 MiB 234.4 ->
+// 223.3, 305.8 -> 304.4, 325.9 -> 327.  Over five layouts, six kinds of work between the calls, one buffer and three in turn, no time
+// grew by more than 2.4 % from 192 MiB on; at 160 MiB by up to 7 %, at 128 MiB (132.4 -> 120.1 us where nothing reads the rows) by up to
+// 13 %: their reader waits for memory.  (The second kernels of fused steps store all rows the ordinary way.)
+constexpr uint64_t kStreamedBytes = 192u << 20;
+static bool gather_streams(const FieldTable& ft, uint32_t B, uint32_t trees, const JobRanges& jr) {
+  uint64_t row = 0;
+  bool any = false;
+  for (uint32_t f = 0; f < ft.n_fields; ++f) {
+    if (!ft.io[f]) continue;
+    row += ft.bytes[f];
+    any = any || ft.vec[f] == 16;
+  }
+  return any && !jr.whole_rows && row * B * trees >= kStreamedBytes;
+}
+
 hipError_t launch_gather(const Geom& g, const Tuning& tn, const FieldTable& ft, uint32_t B, const uint32_t* idx,
                          hipStream_t s) {
   const uint32_t block = tn.gather_block;
@@ -594,11 +618,11 @@ hipError_t launch_gather(const Geom& g, const Tuning& tn, const FieldTable& ft, 
   const uint32_t gx = jr.first[2 + kMaxFields];
   if (gx == 0) return hipSuccess;
   const size_t lds = whole_rows_lds(jr);
-  if (!jr.whole_rows && any_field_moves_wide(&ft)) {
-    PER_LAUNCH(KID_GATHER, k_rows<true>, dim3(gx, g.T), dim3(block), lds, s, ft, jr, B, idx, g.N, g.status);
-  } else {
-    PER_LAUNCH(KID_GATHER, k_rows<false>, dim3(gx, g.T), dim3(block), lds, s, ft, jr, B, idx, g.N, g.status);
-  }
+#define PER_ROWS(WD, ST) PER_LAUNCH(KID_GATHER, (k_rows<WD, ST>), dim3(gx, g.T), dim3(block), lds, s, ft, jr, B, idx, g.N, g.status)
+  if (gather_streams(ft, B, g.T, jr)) PER_ROWS(true, true);
+  else if (!jr.whole_rows && any_field_moves_wide(&ft)) PER_ROWS(true, false);
+  else PER_ROWS(false, false);
+#undef PER_ROWS
   return hipGetLastError();
 }
 
@@ -611,10 +635,10 @@ static hipError_t launch_finish(const Geom& g, const Tuning& tn, const FieldTabl
   const JobRanges jr = job_ranges(rows ? &ft : nullptr, a.B, block, a.w ? a.B : 0u, a.has_claim ? a.claim.B : 0u, g.T,
                                   tn.whole_rows);
   const size_t lds = whole_rows_lds(jr);
-  if (!jr.whole_rows && any_field_moves_wide(rows ? &ft : nullptr)) {
-    PER_LAUNCH(KID_FINISH, k_finish<true>, dim3(jr.first[2 + kMaxFields], g.T), dim3(block), lds, s, ft, jr, g, a);
-  } else {
-    PER_LAUNCH(KID_FINISH, k_finish<false>, dim3(jr.first[2 + kMaxFields], g.T), dim3(block), lds, s, ft, jr, g, a);
-  }
+#define PER_FINISH(WD, ST) PER_LAUNCH(KID_FINISH, (k_finish<WD, ST>), dim3(jr.first[2 + kMaxFields], g.T), dim3(block), lds, s, ft, jr, g, a)
+  if (rows && gather_streams(ft, a.B, g.T, jr)) PER_FINISH(true, true);
+  else if (!jr.whole_rows && any_field_moves_wide(rows ? &ft : nullptr)) PER_FINISH(true, false);
+  else PER_FINISH(false, false);
+#undef PER_FINISH
   return hipGetLastError();
 }

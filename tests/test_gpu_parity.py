@@ -852,24 +852,34 @@ def test_step_on_the_chip_stores_what_it_has_changed(K, N, T, B, n, left):
 
 
 @pytest.mark.parametrize("claim_form", ["group"], indirect=True)   # (no claims in these calls)
-@pytest.mark.parametrize("width,B", [(128, 262143), (128, 262144), (48, 699050), (48, 699051), (16, 2097153), (7056, 4756)])
-def test_long_gathers_of_wide_elements(width, B):
-    """Fields of 16-byte elements whose gathered rows come to 32 MiB and just below: sampled with their rows, and gathered
+@pytest.mark.parametrize("fb,T,B", [((128,), 1, 262144), ((48,), 1, 699051), ((7056,), 1, 4756), ((128,), 1, 1572863), ((128,), 1, 1572864), ((128,), 3, 524288),
+                                    ((16,), 1, 12582913), ((7056,), 1, 28534), ((7056, 16), 2, 14234), ((7056, 16), 2, 14235), ((16, 7076, 3, 8), 1, 28346),
+                                    ((64, 64), 1, 1572864)])
+def test_long_gathers_of_wide_elements(fb, T, B):
+    """Rows that come to 32 MiB, to just below 192 MiB and to it, over all fields and trees (from there on 16-byte elements are stored past
+    the caches; fields of other elements beside them, and rows gathered whole, are not): sampled with their rows, and gathered
     again by the indices drawn, against the rows as they were put in."""
-    log(f"long gathers width={width} B={B}")
+    log(f"long gathers fields={fb} T={T} B={B}")
     N = 5003
     g = torch.Generator(device="cuda")
-    g.manual_seed(width + B)
-    rows = torch.randint(0, 256, (1, N, width), generator=g, device="cuda", dtype=torch.uint8)
-    p = PrioritizedReplay(16, N, 1, (width,))
-    p.insert(N, [rows], torch.rand((1, N), generator=g, device="cuda"))
-    out, idx = torch.zeros((1, B, width), dtype=torch.uint8, device="cuda"), torch.zeros((1, B), dtype=torch.int32, device="cuda")
-    p.sample(torch.rand((1, B), generator=g, device="cuda"), 0.4, out_idx=idx, rows_out=[out])
-    assert torch.equal(out[0], rows[0][idx[0].long()])
+    g.manual_seed(fb[0] + B)
+    rows = [torch.randint(0, 256, (T, N, b), generator=g, device="cuda", dtype=torch.uint8) for b in fb]
+    p = PrioritizedReplay(16, N, T, fb)
+    p.insert(N, rows, torch.rand((T, N), generator=g, device="cuda"))
+    out, idx = [torch.zeros((T, B, b), dtype=torch.uint8, device="cuda") for b in fb], torch.zeros((T, B), dtype=torch.int32, device="cuda")
+    u = torch.rand((T, B), generator=g, device="cuda")
+    same = lambda got, want: all(torch.equal(x[t], r[t][want[t].long()]) for x, r in zip(got, rows) for t in range(T))  # noqa: E731
+    p.sample(u, 0.4, out_idx=idx, rows_out=out)
+    assert same(out, idx)
     again = idx.flip(1).contiguous()
-    got = p.gather(again)
-    assert torch.equal(got[0][0], rows[0][again[0].long()])
-    assert p.status() == 0
+    again[0, 5] = N                              # no such row: zeros, and a flag
+    out = p.gather(again)
+    assert all(int(x[0, 5].max()) == 0 for x in out)
+    again[0, 5] = 0
+    for x, r in zip(out, rows):
+        x[0, 5] = r[0, 0]
+    assert same(out, again)
+    assert p.status() == FLAG_BAD_INDEX
 
 
 # (whether one launch on an LDS copy is the way a step goes by default: shapes well on either side of the rule's line)
