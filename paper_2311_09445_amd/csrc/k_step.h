@@ -1086,12 +1086,12 @@ k_step_epilogue(Geom g, StepShape sh, uint32_t table_blocks, uint32_t B, float b
   if (i < B) w[o] = nothing_sampled ? 0.0f : importance_weight(v, __uint_as_float(m), beta);
 }
 
-// The owner height of a tree for k_step, or 0 when the kernel does not fit it: the lowest height, not below the
-// tree pass's own workgroup roots, with at most 2048 nodes over all trees, whose subtrees (heights 1 .. ho-1)
+// The owner height of a tree for k_step, or 0 when the kernel does not fit it: the lowest height, not below
+// subtree_height, with at most 2048 nodes over all trees, whose subtrees (heights 1 .. ho-1)
 // and the heights from it to the root are small enough for LDS.
 uint32_t step_owner_height(const Geom& g) {
   if (g.logK < 3) return 0;
-  for (uint32_t ho = tree_pass_height(g) < 2 ? 2 : tree_pass_height(g); ho + 1 <= g.H; ++ho) {
+  for (uint32_t ho = subtree_height(g) < 2 ? 2 : subtree_height(g); ho + 1 <= g.H; ++ho) {
     if ((uint64_t)g.n[ho] * g.T > kStepMaxOwners || g.n[ho] > kLazyTopNodes) continue;
     if (g.H - ho > (uint32_t)kStepTop || ho - 1 > (uint32_t)kStepSub) return 0;
     uint64_t sub = 0;

@@ -636,14 +636,12 @@ k_tree_finish(Geom g, SubLevels sl, uint32_t chain, uint32_t tree_blocks, FieldT
   PER_FLUSH();
 }
 
-// Height of the workgroup roots of the tree pass: the lowest whose subtrees hold 64 height-1 nodes (so that dirty words
-// are never shared between workgroups), or the root of a tree of no more of them.  The pass works through a subtree's
-// claimed nodes a few at a time, a trip to memory each, and what lies above is left to the next sampling call, which has
-// the top of the tree in LDS anyway.  (A tree of up to 2048 height-1 nodes as one subtree: 512 elements on 100 000 leaves
+// Lowest height whose subtrees hold 64 height-1 nodes, or the root of a tree of no more of them; the owners of the
+// one-kernel step are never lower.  (A tree of up to 2048 height-1 nodes as one subtree: 512 elements on 100 000 leaves
 // at K = 64 took 11.3 us, 3.7 so; a step of 1024 on 30 000 at K = 16, insertion of 16 rows now carried by the sampling,
 // 21.5 and 12.3; 64 such trees 40.9 and 32.5.)  Not at K = 2, where the many heights to rebuild cost the sampling as much
 // as the pass gains: a step of 64 on 4096 leaves 13.5 us as one subtree, 14.7 as 32.
-static uint32_t tree_pass_height(const Geom& g) {
+static uint32_t subtree_height(const Geom& g) {
   if (g.n[1] <= (g.logK == 1 ? 2048u : 64u)) return g.H;
   uint32_t hb = 1;
   while (hb < g.H && (1ull << ((hb - 1) * g.logK)) < 64) ++hb;
@@ -652,6 +650,28 @@ static uint32_t tree_pass_height(const Geom& g) {
   const uint32_t most = g.logK == 1 ? kMaxPassHeight<1> : g.logK == 2 ? kMaxPassHeight<2> : g.logK == 3 ? kMaxPassHeight<3> : hb;
   while (hb < g.H && hb < most && g.n[hb] > kLazyTopNodes) ++hb;
   return hb;
+}
+
+// Height of the workgroup roots of the tree pass.  The pass works through a subtree's claimed nodes a few at a time, a trip
+// to memory each, and what lies above is left to the next sampling call, which has the top of the tree in LDS anyway: many
+// small subtrees are faster until their roots are too many for every sampling workgroup to rebuild the top from, or for
+// the device to hold the workgroups.  subtree_height() gives 1024 nodes to a subtree at K = 32 and 256 at K = 16, which
+// leaves trees of few leaves to a handful of workgroups; height 2 gives 32 and 16 (a group entry and a dirty word belong to
+// one subtree still).  us per call, subtree_height() and height 2:
+//  - K = 32, up to 1024 roots: 512 temporal-difference errors on 30 000 leaves 23.6 and 15.1; a step of 512 there 17.3 and
+//    11.7, on 64 such trees 35.8 and 23.0 with 1000 each; 2^20 leaves: `sample` and `update` of 2^18 73.5 and 48.6, 40 000
+//    rows inserted 26.3 and 18.5, a step of 64 9.5 and 9.4, the earlier-batch form of 64 10.3 and 10.4.  With 2048
+//    roots (2^21 leaves) that form takes 11.1 and 13.2, with 4096 11.1 and 17.0.
+//  - K = 16, up to 16 roots, 64 on several trees: a step of 1000 on 4096 leaves 16.1 and 12.5, on 64 trees of 16 384 29.4
+//    and 24.6; with more roots nothing is gained (50 000 leaves, 300 samples: 11.5 and 11.6).
+//  - no more than 4096 over all trees: 64 trees of 32 768 leaves at K = 16, 300 samples: 17.0 and 20.2; 16 of 2^19 at K =
+//    32, 1024 samples: 19.4 and 20.9.
+constexpr uint64_t kMostSmallSubtrees = 4096;
+static uint32_t tree_pass_height(const Geom& g) {
+  const uint32_t hb = subtree_height(g);
+  if (hb <= 2 || (g.logK != 4 && g.logK != 5) || g.n[1] <= 64u) return hb;
+  const uint32_t most = g.logK == 5 ? 1024u : g.T >= 4 ? 64u : 16u;
+  return g.n[2] <= most && (uint64_t)g.n[2] * g.T <= kMostSmallSubtrees ? 2u : hb;
 }
 
 // Heights above this one may be left stale by an update (0: never).

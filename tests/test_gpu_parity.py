@@ -1971,6 +1971,31 @@ def test_subtrees_of_the_tree_pass(K, N):
     m.compare_status()
 
 
+@pytest.mark.parametrize("K,N,T", [(32, 2049, 1), (32, 1 << 20, 1), (32, (1 << 20) + 1, 1), (32, 1 << 16, 64), (32, (1 << 16) + 1, 64), (16, 4096, 1), (16, 4097, 1),
+                                   (16, 1025, 3), (16, 16384, 4), (16, 16385, 4), (16, 1 << 14, 64)])
+def test_small_subtrees_of_the_tree_pass(K, N, T):
+    """Subtrees of K height-1 nodes and the trees of one leaf or node more that do not have them: insertions of a few rows and
+    of many, up to the ring's end, steps, sparse and dense updates."""
+    log(f"small subtrees K={K} N={N} T={T}")
+    rng = np.random.default_rng(N + T)
+    B = 150 if T > 4 else 500
+    m = Mirror(K, N, T, ())
+    m.insert(N, prio=wl._draw_priorities("lognormal_0_1", rng, (T, N)))
+    new = lambda n: wl._draw_updates("absnormal1_eps_pow0.6", rng, (T, n))  # noqa: E731
+    for r in range(3):
+        m.insert([3, K * K + 5, N // 2 + 1][r], prio=None if r else (rng.random((T, 3)) * 4).astype(np.float32))
+        gi, ci = m.sample(wl.uniform01(rng, (T, B)), 0.5)
+        m.update(ci, new(B))
+        m.insert_step_call(4, None, wl.uniform01(rng, (T, B)), 0.5, True, new(B))
+        if T == 1:
+            m.sample_gather_update(wl.uniform01(rng, (T, B)), 0.5, True, new(B // 2), tail=B // 2)
+        dense = np.sort(rng.integers(0, N, (T, min(N, 40000))), axis=1).astype(np.uint32)
+        m.update(dense, new(dense.shape[1]))
+        if r != 1:
+            m.compare_tree()
+    m.compare_status()
+
+
 @pytest.mark.parametrize("N", [(1 << 23) + 1, (1 << 24) + 1])
 @pytest.mark.parametrize("norm", ["batch", "buffer"])
 def test_largest_subtrees_of_the_tree_pass(N, norm, claim_form):
