@@ -72,15 +72,24 @@ __device__ __forceinline__ void stage_group_per_lane(const float* __restrict__ l
 // chunk computes once for all lanes of the group, and the number of its node:
 //   [K children][K / 4 chunk sums][node] pad
 // rows an odd number of 16-byte units apart, so that lanes on different rows read different banks.
+// A wave has fewer rows than lanes (ROWS, about 5 KB) and takes its groups in rounds of as many: a sample in sixteen leaves
+// or more, as large batches have it, seldom needs a second round, and the waves wait for memory two thirds of their time
+// (counters: 63 % at three waves per SIMD with 64 rows each, 11 KB at K = 32), which more of them fill.  In workgroups of four
+// waves, so that no more of them copy the top than before: 2^20 samples on 2^24 leaves 28.2 -> 24 us at K = 32 (33 in
+// workgroups of two), with the `update` behind them 172 -> 148 at K = 64, 142 -> 138 at K = 16, 166 -> 159 at K = 8.
 template <int LOGK>
 struct StageRow {
   static constexpr int K = 1 << LOGK, C = K / 4;
   static constexpr int UNITS = (K + C + 1 + 3) / 4;
   static constexpr int FLOATS = 4 * (UNITS | 1);
   static constexpr int SUMS = K, NODE = K + C;
+  static constexpr int ROWS = LOGK <= 3 ? 64 : LOGK == 4 ? 48 : LOGK == 5 ? 32 : 24;   // staged at a time
+  static constexpr int FETCHES = (ROWS * C + 63) / 64;                                 // 16-byte loads of a lane for them
 };
-static uint32_t stage_row_floats(uint32_t logK) {
-  return logK == 3 ? StageRow<3>::FLOATS : logK == 4 ? StageRow<4>::FLOATS : logK == 5 ? StageRow<5>::FLOATS : logK == 6 ? StageRow<6>::FLOATS : 0u;
+template <int LOGK>
+constexpr uint32_t kStageFloats = StageRow<LOGK>::ROWS * StageRow<LOGK>::FLOATS;   // per wave
+static uint32_t stage_floats(uint32_t logK) {
+  return logK == 3 ? kStageFloats<3> : logK == 4 ? kStageFloats<4> : logK == 5 ? kStageFloats<5> : logK == 6 ? kStageFloats<6> : 0u;
 }
 // Chunk (IT*64 + lane) of the wave's `chunks` 16-byte chunks, for IT = 0 .. C-1: first the numbers of all their nodes,
 // then every fetch, then the LDS stores.  Written as recursions over IT (not loops over arrays of registers) so that each
@@ -123,23 +132,6 @@ __device__ __forceinline__ void order_within_wave() {
   __builtin_amdgcn_wave_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
-// Returns this lane's row.
-template <int LOGK>
-__device__ __forceinline__ const float* stage_groups(const float* __restrict__ lvl, uint32_t node, unsigned lane, float* stage) {
-  using Row = StageRow<LOGK>;
-  const uint32_t below = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)node, 0x138 /* wave_shr:1: from the lane below */, 0xF, 0xF, true);
-  const bool first = lane == 0 || below != node;
-  const unsigned long long firsts = __ballot(first);
-  const uint32_t rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(firsts >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)firsts, 0u)) + (first ? 1u : 0u) - 1u;
-  float* row = stage + (size_t)rank * Row::FLOATS;
-  if (first) row[Row::NODE] = __uint_as_float(node);
-  order_within_wave();
-  NodeNumbers<Row::C> nodes;
-  read_nodes<LOGK, 0>(stage, lane, nodes);
-  stage_chunks<LOGK, 0>(lvl, (uint32_t)__popcll(firsts) * Row::C, lane, stage, nodes);
-  order_within_wave();
-  return row;
-}
 // descend_lane on a staged row: the walk over the chunks from their sums, then the chosen chunk.
 template <int LOGK>
 __device__ __forceinline__ void descend_row(const float* row, float& r, unsigned& child, float& val) {
@@ -169,6 +161,30 @@ __device__ __forceinline__ void descend_row(const float* row, float& r, unsigned
   if (__builtin_expect(__any(!(val > 0.0f)), 0)) {   // (see descend_lane)
     r = r0;
     descend_chunk<LOGK>(row, s, r, child, val);
+  }
+}
+
+// One height of the walk: the wave's distinct groups are staged, at most ROWS of them at a time, and every lane walks the row
+// of its group.
+template <int LOGK>
+__device__ __forceinline__ void descend_staged(const float* __restrict__ lvl, uint32_t node, unsigned lane, float* stage, float& r, unsigned& child, float& val) {
+  using Row = StageRow<LOGK>;
+  const uint32_t below = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)node, 0x138 /* wave_shr:1: from the lane below */, 0xF, 0xF, true);
+  const bool first = lane == 0 || below != node;
+  const unsigned long long firsts = __ballot(first);
+  const uint32_t rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(firsts >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)firsts, 0u)) + (first ? 1u : 0u) - 1u;
+  const uint32_t groups = (uint32_t)__popcll(firsts);
+  for (uint32_t base = 0; base < groups; base += Row::ROWS) {   // (one round where samples lie densely)
+    const bool mine = rank - base < (uint32_t)Row::ROWS;        // (ranks below base wrap)
+    float* row = stage + (size_t)(mine ? rank - base : 0u) * Row::FLOATS;
+    if (mine && first) row[Row::NODE] = __uint_as_float(node);
+    order_within_wave();
+    NodeNumbers<Row::FETCHES> nodes;
+    read_nodes<LOGK, 0>(stage, lane, nodes);
+    stage_chunks<LOGK, 0>(lvl, min_u32(groups - base, (uint32_t)Row::ROWS) * Row::C, lane, stage, nodes);
+    order_within_wave();
+    if (mine) descend_row<LOGK>(row, r, child, val);
+    order_within_wave();
   }
 }
 
@@ -213,6 +229,7 @@ k_sample(Geom g, TopCopy tc, uint32_t B, uint32_t size, float beta, const float*
   constexpr int K = Fan<LOGK>::K;
   constexpr int LPS = Fan<LOGK>::LPS;
   constexpr int ROW = LOOP && LOGK >= 3 ? StageRow<LOGK>::FLOATS : K + 4;   // staging row, floats
+  constexpr int ROWS = LOOP && LOGK >= 3 ? StageRow<LOGK>::ROWS : 64;       // of a wave
   using Vec = typename std::conditional<LOGK == 1, float2, float4>::type;
   constexpr int VF = sizeof(Vec) / 4;
   // (lines 1, 3, 6, 7, 10, 11 of the geometry hold what this kernel does not read on trees of few heights: the upper
@@ -290,7 +307,7 @@ k_sample(Geom g, TopCopy tc, uint32_t B, uint32_t size, float beta, const float*
   for (int i = 0; i < kTopSlots; ++i) off[i + 1] = off[i] + (i < nslots ? tc.cnt[i] : 0u);
   const uint32_t top_floats = off[kTopSlots];
   // the carried insertion's LDS: behind the top copy and the waves' staging rows
-  float* rl = lds + top_floats + (LOGK >= 3 ? (size_t)(blockDim.x >> 6) * 64 * ROW : (size_t)0);
+  float* rl = lds + top_floats + (LOGK >= 3 ? (size_t)(blockDim.x >> 6) * ROWS * ROW : (size_t)0);
   // Everything it reads is fetched in the trip of the top copy: the loads are issued here, into registers, and
   // parked in LDS once the top copy's own loads are under way (a store to LDS waits for its data).  Lane i takes
   // element i of each height's run of child groups.  A staged leaf that the insertion rewrites is replaced as it
@@ -516,7 +533,7 @@ k_sample(Geom g, TopCopy tc, uint32_t B, uint32_t size, float beta, const float*
   }
 
   PER_MARK(3);
-  float* stage = lds + top_floats + (size_t)wave * 64 * ROW;
+  float* stage = lds + top_floats + (size_t)wave * ROWS * ROW;
   const int l0 = (int)H - 1 - nslots;     // highest height read from memory
   // the pointer of the next level is fetched while the current one is processed
   const float* lvl_next = l0 >= 0 ? g.level[l0] + (size_t)t * g.stride[l0] : nullptr;
@@ -537,8 +554,7 @@ k_sample(Geom g, TopCopy tc, uint32_t B, uint32_t size, float beta, const float*
       if (RIDE && patched) descend_lane<LOGK>(patched, r, child, val);
       else descend_lane<LOGK>(lvl + (size_t)node * K, r, child, val);
     } else if constexpr (LOOP) {
-      descend_row<LOGK>(stage_groups<LOGK>(lvl, node, lane, stage), r, child, val);
-      __builtin_amdgcn_wave_barrier();
+      descend_staged<LOGK>(lvl, node, lane, stage, r, child, val);
     } else {
       stage_group_per_lane<LOGK, 0>(lvl, node, lane, stage);
       order_within_wave();
@@ -654,6 +670,30 @@ template <int LOGK>
 static hipError_t launch_tree_finish_k(const Geom& g, const Tuning& tn, const ClaimArgs& c, const FieldTable* rows,
                                        const FinishArgs& a, hipStream_t s);
 
+// Waves of a sampling workgroup (carried: rows of the insertion that the launch carries, or 0).  Every workgroup copies the
+// top of the tree and, behind an update, rebuilds it from the roots of the tree pass's subtrees.  One wave needs no barriers
+// for that and leaves the samples to the most compute units; with more than 256 roots the copy wants more lanes, beyond 1024
+// fewer workgroups that make it.  One and two waves (us per step, K = 16): 2^18 leaves, 4096 samples, 4 new rows 13.7 and
+// 13.0, 8192 and none 12.6 and 12.1; 2^20 leaves, earlier-batch form of 8192 11.1 and 10.8, 2^22 (1024 roots) 13.3 and
+// 13.9; K = 32, 2^22 leaves, 8192: 13.6 and 13.2.  Two and four: 2^20 leaves at K = 8 (2048 roots), earlier-batch form of
+// 8192, 13.0 and 12.5.  (Fewer than 48 roots: 0.93 to 1.02 times; K = 8 the same, K = 64 0.97 to 1.01.)
+// Every workgroup works a carried insertion out for itself, a run of child groups of which must fit its lanes: that is the
+// least it may have (up to two waves, up to eight on many trees).  On 64 trees it is better worked out by few workgroups of
+// eight waves unless the trees are small (1000 samples, 4 rows each, eight waves and two: 2^18 leaves at K = 16 26.7 and 27.5,
+// 4096 27.3 and 26.2; 48 trees of 2^18 18.7 and 18.4, 8 of 4096 17.9 and 13.5).
+static uint32_t sample_waves(const Geom& g, const Tuning& tn, uint32_t carried) {
+  const uint32_t hb = lazy_top_height(g, tn);
+  uint32_t waves = 2;
+  if (hb && g.n[hb] > 1024u && g.logK == 3) waves = 4;
+  if (hb >= 3 && (g.logK == 4 || g.logK == 5) && g.n[hb] > 48u && g.n[hb] <= 256u) waves = 1;
+  if (!carried) return waves;
+  if (g.T >= 64u && g.N > 8192u) return 8;
+  const uint32_t lanes = ((carried - 1) / g.K + 2) * g.K, most = g.T >= 8u ? 8u : 2u;
+  const uint32_t least = (lanes + 63u) / 64u < most ? (lanes + 63u) / 64u : most;
+  return waves > least ? waves : least;
+}
+constexpr uint32_t kLoopWaves = 4;   // (of the kernel that loops over blocks: see StageRow)
+
 // Workgroup size and top copy of a sampling launch for batch B (stale_hb: the height the stale top is rebuilt
 // from, or 0).  The copy: at most kTopSlots of the topmost heights (below the root), within the LDS budget, and
 // only while a height is small next to what the workgroup's samples would fetch from it one by one.
@@ -661,11 +701,11 @@ struct SampleShape {
   TopCopy tc;
   uint32_t waves, wave_bytes, top_bytes;
 };
-static SampleShape sample_shape(const Geom& g, const Tuning& tn, uint32_t B, uint32_t stale_hb, bool weights_behind, bool carries_insert = false, bool loop = false) {
+static SampleShape sample_shape(const Geom& g, const Tuning& tn, uint32_t B, uint32_t stale_hb, bool weights_behind, uint32_t carried = 0, bool loop = false) {
   constexpr uint32_t kLdsCap = 128 * 1024;
   SampleShape sh{};
   const uint32_t K = g.K;
-  sh.wave_bytes = g.logK < 3 ? 0u : 64u * (loop ? stage_row_floats(g.logK) : K + 4u) * 4u;   // staging per wave
+  sh.wave_bytes = g.logK < 3 ? 0u : (loop ? stage_floats(g.logK) : 64u * (K + 4u)) * 4u;   // staging per wave
   // workgroup size: the configured size, or the whole batch in one workgroup when it is small and no kernel comes behind
   // that could finish the weights (where one does, several workgroups are faster from the third wave on: a step of 1024
   // samples on 2^20 leaves at K = 4 takes 20.8 us with one and 16.3 with eight, of 512 at K = 16 12.8 and 11.7);
@@ -674,10 +714,7 @@ static SampleShape sample_shape(const Geom& g, const Tuning& tn, uint32_t B, uin
   if (max_waves > 16) max_waves = 16;
   if (max_waves < 1) max_waves = 1;
   uint32_t waves = tn.sample_block / 64;
-  // Every sampling workgroup of a launch that carries an insertion works that insertion out for itself: on many trees
-  // fewer, larger workgroups pay (64 trees, 1024 samples and 16 rows each: 29.3 -> 28.5 us per step with 512 lanes;
-  // on one tree the small ones stay ahead).  Only when the size was not asked for.
-  if (carries_insert && tn.sample_block_auto && g.T >= 8 && waves < 8) waves = 8;
+  if (tn.sample_block_auto) waves = loop ? kLoopWaves : sample_waves(g, tn, carried);
   const uint32_t need = (B + 63) / 64;
   if (need <= (weights_behind ? waves : max_waves)) waves = need;
   if (waves > max_waves) waves = max_waves;
@@ -759,7 +796,7 @@ bool sample_can_carry_insert(const Geom& g, const Tuning& tn, uint32_t B, const 
       if (ft->io[f]) bytes += (uint64_t)n * ft->bytes[f];
   if (bytes > 256 * 1024) return false;
   // the top copy must reach down to the height the top is rebuilt from
-  const SampleShape sh = sample_shape(g, tn, B, hb, true, true);
+  const SampleShape sh = sample_shape(g, tn, B, hb, true, n);
   if (sh.tc.nslots == 0 || g.H - sh.tc.nslots > hb) return false;
   // the runs of the patch must fit the workgroup, and the patch its share of the LDS
   InsertRide rd{};
@@ -778,11 +815,11 @@ static hipError_t launch_sample_k(const Geom& g, const Tuning& tn, uint32_t B, u
                                   const float* u, const RngArgs& rng, uint32_t* out_idx, float* out_w,
                                   float* out_prio, uint32_t weight_mode, uint32_t stale_hb, const FieldTable* rows,
                                   const ClaimArgs* claim, int claim_mode, const InsertRide* ride, hipStream_t s) {
-  SampleShape sh = sample_shape(g, tn, B, stale_hb, rows || claim, ride != nullptr);
+  SampleShape sh = sample_shape(g, tn, B, stale_hb, rows || claim, ride ? ride->n : 0u);
   // No more workgroups than the device holds at once (their staging rows fill its LDS): they take further blocks of
   // samples in turn, with the top of the tree in place and the next uniforms under way, where workgroups of a second
   // round would begin with their arguments and the top of the tree again, two of the five trips to memory of a block.
-  // (2^20 samples on 2^24 leaves at K = 32: 59 us with a workgroup per block, 27 so, with the rows of stage_groups.)
+  // (2^20 samples on 2^24 leaves at K = 32: 59 us with a workgroup per block, 24 so, with the rows of descend_staged.)
   const uint64_t units = compute_units(tn.device);
   auto held = [&]() -> uint64_t {   // workgroups the device holds
     uint64_t bytes = (uint64_t)sh.top_bytes + (uint64_t)sh.waves * sh.wave_bytes, by_waves = 32 / sh.waves;
@@ -791,7 +828,7 @@ static hipError_t launch_sample_k(const Geom& g, const Tuning& tn, uint32_t B, u
     return (units ? units : 256) * (n < 1 ? 1 : n);
   };
   const bool loop = !ride && (uint64_t)((B + sh.waves * 64 - 1) / (sh.waves * 64)) * g.T > held();
-  if (loop) sh = sample_shape(g, tn, B, stale_hb, rows || claim, false, true);
+  if (loop) sh = sample_shape(g, tn, B, stale_hb, rows || claim, 0, true);
   const TopCopy& tc = sh.tc;
   const uint32_t waves = sh.waves;
   const uint32_t block = waves * 64;
@@ -800,6 +837,15 @@ static hipError_t launch_sample_k(const Geom& g, const Tuning& tn, uint32_t B, u
   if (loop) {
     gx = (uint32_t)(held() / g.T < 2 ? 2 : held() / g.T);   // (at least two: one workgroup alone finishes the weights of the block it holds)
     if (gx > blocks) gx = blocks;
+    // Where the leaves stay in the second-level caches (32 MiB), no more workgroups than it takes for all to have as many blocks
+    // as the busiest: `sample` and `update` of 2^19 on 3 million leaves at K = 32 87.6 -> 83.5 us, on 2^20 at K = 16
+    // 67.2 -> 63.5.  On 2^24 leaves at K = 32 the workgroups without a last block leave more of the memory to the
+    // others: 78.2 so, 80.2 with as many blocks each.
+    if ((uint64_t)g.N * g.T * 4u <= 32u << 20 && gx > 2) {
+      const uint32_t rounds = (blocks + gx - 1) / gx;
+      gx = (blocks + rounds - 1) / rounds;
+      if (gx < 2) gx = 2;
+    }
   }
   uint32_t parts = 0;
   if (weight_mode & kWeightMinHere) {

@@ -1832,6 +1832,24 @@ def test_sampling_workgroups_take_blocks_in_turn(K, N, T, B):
     m.compare_status()
 
 
+@pytest.mark.parametrize("claim_form", ["group"], indirect=True)   # (no claims in these calls)
+@pytest.mark.parametrize("K,N,T,B", [(8, 1 << 20, 1, 33000), (16, 700_001, 1, 33021), (16, 1 << 22, 1, 40001), (32, 1 << 20, 2, 20001), (32, 1 << 22, 1, 33000),
+                                     (64, 300_001, 1, 40000), (64, 1 << 22, 1, 33000)])
+def test_samples_of_more_groups_than_a_wave_stages(claim_form, K, N, T, B):
+    """The looping sampling kernel where 64 samples lie in about as many child groups as a wave has staging rows, in more, and,
+    with uniforms that leave their range, in no order."""
+    log(f"staged in rounds K={K} N={N} T={T} B={B}")
+    rng = np.random.default_rng(B + N)
+    m = Mirror(K, N, T, ())
+    m.gpu.set_tuning("sample_min_lds", 100_000)   # (one workgroup per compute unit)
+    m.insert(N, prio=wl._draw_priorities("exponential_1", rng, (T, N)))
+    u = wl.uniform01(rng, (T, B))
+    m.sample(u, 0.4)
+    u[:, ::3] = (rng.random(u[:, ::3].shape) * 40000 - 20000).astype(np.float32)
+    m.sample(u, 0.4)
+    m.compare_status()
+
+
 @pytest.mark.parametrize("K,N,T", [(2, 5000, 1), (4, 4097, 2), (8, 9000, 1), (16, 70001, 2), (32, 200003, 1), (64, 70001, 2)])
 @pytest.mark.parametrize("norm", ["batch", "buffer"])
 def test_updates_claimed_in_runs(K, N, T, norm):
