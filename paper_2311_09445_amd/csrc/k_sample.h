@@ -701,7 +701,8 @@ struct SampleShape {
   TopCopy tc;
   uint32_t waves, wave_bytes, top_bytes;
 };
-static SampleShape sample_shape(const Geom& g, const Tuning& tn, uint32_t B, uint32_t stale_hb, bool weights_behind, uint32_t carried = 0, bool loop = false) {
+static SampleShape sample_shape(const Geom& g, const Tuning& tn, uint32_t B, uint32_t stale_hb, bool weights_behind, uint32_t carried = 0, bool loop = false,
+                                bool wide = false) {
   constexpr uint32_t kLdsCap = 128 * 1024;
   SampleShape sh{};
   const uint32_t K = g.K;
@@ -714,7 +715,7 @@ static SampleShape sample_shape(const Geom& g, const Tuning& tn, uint32_t B, uin
   if (max_waves > 16) max_waves = 16;
   if (max_waves < 1) max_waves = 1;
   uint32_t waves = tn.sample_block / 64;
-  if (tn.sample_block_auto) waves = loop ? kLoopWaves : sample_waves(g, tn, carried);
+  if (tn.sample_block_auto) waves = loop ? kLoopWaves : wide ? 2u : sample_waves(g, tn, carried);
   const uint32_t need = (B + 63) / 64;
   if (need <= (weights_behind ? waves : max_waves)) waves = need;
   if (waves > max_waves) waves = max_waves;
@@ -810,12 +811,12 @@ bool sample_can_carry_insert(const Geom& g, const Tuning& tn, uint32_t B, const 
 // kernel, the tree pass then shares the second kernel with the weights and row jobs; CLAIM_FINISH: in
 // the second kernel, the tree pass is a third).  ride: an insertion carried by the sampling kernel (the caller
 // has checked sample_can_carry_insert and passes the lazily rebuilt height as stale_hb).
-template <int LOGK>
-static hipError_t launch_sample_k(const Geom& g, const Tuning& tn, uint32_t B, uint32_t size, float beta,
+template <int TREE, int LOGK>
+static hipError_t launch_sample_walk(const Geom& tree, const Geom& g, const Tuning& tn, uint32_t B, uint32_t size, float beta,
                                   const float* u, const RngArgs& rng, uint32_t* out_idx, float* out_w,
                                   float* out_prio, uint32_t weight_mode, uint32_t stale_hb, const FieldTable* rows,
                                   const ClaimArgs* claim, int claim_mode, const InsertRide* ride, hipStream_t s) {
-  SampleShape sh = sample_shape(g, tn, B, stale_hb, rows || claim, ride ? ride->n : 0u);
+  SampleShape sh = sample_shape(g, tn, B, stale_hb, rows || claim, ride ? ride->n : 0u, false, TREE != LOGK);
   // No more workgroups than the device holds at once (their staging rows fill its LDS): they take further blocks of
   // samples in turn, with the top of the tree in place and the next uniforms under way, where workgroups of a second
   // round would begin with their arguments and the top of the tree again, two of the five trips to memory of a block.
@@ -828,7 +829,7 @@ static hipError_t launch_sample_k(const Geom& g, const Tuning& tn, uint32_t B, u
     return (units ? units : 256) * (n < 1 ? 1 : n);
   };
   const bool loop = !ride && (uint64_t)((B + sh.waves * 64 - 1) / (sh.waves * 64)) * g.T > held();
-  if (loop) sh = sample_shape(g, tn, B, stale_hb, rows || claim, 0, true);
+  if (loop) sh = sample_shape(g, tn, B, stale_hb, rows || claim, 0, true, TREE != LOGK);
   const TopCopy& tc = sh.tc;
   const uint32_t waves = sh.waves;
   const uint32_t block = waves * 64;
@@ -925,26 +926,72 @@ static hipError_t launch_sample_k(const Geom& g, const Tuning& tn, uint32_t B, u
       c2.fold_max = ride ? 1u : 0u;   // the tree pass folds what this kernel has left in max_pend
     }
     if (claim_here) {   // second kernel: tree pass beside the weights and the rows
-      if (rows || finish_weights) return launch_tree_finish_k<LOGK>(g, tn, c2, rows, a, s);
-      return launch_tree_k<LOGK>(g, tn, c2, s);
+      if (rows || finish_weights) return launch_tree_finish_k<TREE>(tree, tn, c2, rows, a, s);
+      return launch_tree_k<TREE>(tree, tn, c2, s);
     }
     // second kernel: rows, weights and the claim phase; the tree pass follows
     a.has_claim = claim ? 1u : 0u;
     if (claim) a.claim = c2;
-    e = launch_finish(g, tn, rows, a, s);
+    e = launch_finish(tree, tn, rows, a, s);
     if (e != hipSuccess || !claim) return e;
-    return launch_tree_k<LOGK>(g, tn, c2, s);
+    return launch_tree_k<TREE>(tree, tn, c2, s);
   }
   if (!finish_weights) return e;
-  PER_LAUNCH(KID_WEIGHTS, k_weights, dim3((B + 255) / 256, g.T), dim3(256), 0, s, g, B, size, beta, out_w, weight_mode);
+  PER_LAUNCH(KID_WEIGHTS, k_weights, dim3((B + 255) / 256, g.T), dim3(256), 0, s, tree, B, size, beta, out_w, weight_mode);
   return hipGetLastError();
+}
+
+// A tree of fanout 2 or 4 as one of fanout 16: every fourth or second height of it.  Where every node is the sum of its children
+// a group of sixteen holds the heights in between, the same sums in the same order; the arrays of all heights are a multiple of
+// 64 floats apart, zeros beyond the nodes, so its last group is whole.
+static Geom of_sixteen(const Geom& g) {
+  Geom w = g;
+  const uint32_t step = 4u / g.logK;
+  w.logK = 4;
+  w.K = 16;
+  w.H = (g.H + step - 1) / step;
+  for (uint32_t h = 0; h <= w.H; ++h) {
+    const uint32_t of = h * step < g.H ? h * step : g.H;
+    w.n[h] = g.n[of];
+    w.stride[h] = g.stride[of];
+    w.level[h] = g.level[of];
+  }
+  return w;
+}
+
+// whole_sums: every node is the sum of its children.  A walk in a tree of fanout 2 or 4 then goes by sixteens: a trip to memory and a
+// group of its lane in LDS for four (two) heights, where each of them was a trip of its own: 256 samples on 2^20 leaves 9.4 -> 5.9 us
+// at K = 2, 4096 7.0 -> 6.4 at K = 4; whole steps, with the faster k_resum_top in front, 512 samples on 607 642 leaves at K = 2 22.9 ->
+// 14.5, 2193 on 1 055 898 at K = 4 17.5 -> 15.0; over 90 drawn steps of both fanouts none took longer by more than the runs differ.
+// Not where the sampling kernel rebuilds a stale top of such a tree or carries an insertion, nor where it folds the tree's
+// minimum (by the real height 1).
+template <int LOGK>
+static hipError_t launch_sample_k(const Geom& g, const Tuning& tn, uint32_t B, uint32_t size, float beta,
+                                  const float* u, const RngArgs& rng, uint32_t* out_idx, float* out_w,
+                                  float* out_prio, uint32_t weight_mode, uint32_t stale_hb, const FieldTable* rows,
+                                  const ClaimArgs* claim, int claim_mode, const InsertRide* ride, bool whole_sums, hipStream_t s) {
+  if constexpr (LOGK <= 2) {
+    bool wide = whole_sums && !ride && !(weight_mode & kWeightMinHere) && g.H * LOGK > 4u;
+    if (wide && stale_hb) {
+      const SampleShape sh = sample_shape(g, tn, B, stale_hb, rows || claim);
+      wide = !sh.tc.nslots || g.H - sh.tc.nslots > stale_hb;
+      if (wide) {
+        const hipError_t e = launch_resum_top_k<LOGK>(g, tn, stale_hb, s);
+        if (e != hipSuccess) return e;
+      }
+    }
+    if (wide)
+      return launch_sample_walk<LOGK, 4>(g, of_sixteen(g), tn, B, size, beta, u, rng, out_idx, out_w, out_prio, weight_mode, 0, rows, claim, claim_mode,
+                                         nullptr, s);
+  }
+  return launch_sample_walk<LOGK, LOGK>(g, g, tn, B, size, beta, u, rng, out_idx, out_w, out_prio, weight_mode, stale_hb, rows, claim, claim_mode, ride, s);
 }
 
 hipError_t launch_sample(const Geom& g, const Tuning& tn, uint32_t B, uint32_t size, float beta, const float* u,
                          const RngArgs& rng, uint32_t* out_idx, float* out_w, float* out_prio, uint32_t weight_mode,
                          uint32_t stale_hb, const FieldTable* rows, const ClaimArgs* claim, int claim_mode,
-                         hipStream_t s, const InsertRide* ride) {
-#define CALL(L) launch_sample_k<L>(g, tn, B, size, beta, u, rng, out_idx, out_w, out_prio, weight_mode, stale_hb, rows, claim, claim_mode, ride, s)
+                         hipStream_t s, const InsertRide* ride, bool whole_sums) {
+#define CALL(L) launch_sample_k<L>(g, tn, B, size, beta, u, rng, out_idx, out_w, out_prio, weight_mode, stale_hb, rows, claim, claim_mode, ride, whole_sums, s)
   PER_DISPATCH_LOGK(g.logK, CALL)
 #undef CALL
 }

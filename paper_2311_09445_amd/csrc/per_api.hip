@@ -612,7 +612,7 @@ static int sample_impl(per_t* p, uint32_t B, float beta, const float* d_u, uint3
   p->stale_hb = 0;   // the sampling kernel rebuilds and stores the stale heights
   hipError_t e = launch_sample(p->g, p->tn, B, (uint32_t)p->size, beta, d_u, rng, d_out_idx, d_out_weight, d_out_prio,
                                weight_mode, stale, fused ? &ft : nullptr, upd_B ? &claim : nullptr,
-                               claim_mode, s, ride);
+                               claim_mode, s, ride, p->sums == SUMS_WHOLE && !p->capture_id);   // (a graph may run behind changes added later)
   if (e == hipSuccess && upd_B) p->stale_hb = lazy_top_height(p->g, p->tn);   // the tree pass ran
   if (e != hipSuccess && upd_B) p->claims_left = true;   // (the claim phase may have run without its tree pass)
   return hip_rc(e);

@@ -285,7 +285,7 @@ hipError_t launch_sample(const Geom& g, const Tuning& tn, uint32_t B, uint32_t s
                          const RngArgs& rng,
                          uint32_t* out_idx, float* out_w, float* out_prio, uint32_t weight_mode, uint32_t stale_hb,
                          const FieldTable* rows, const ClaimArgs* claim, int claim_mode, hipStream_t s,
-                         const InsertRide* ride = nullptr);
+                         const InsertRide* ride, bool whole_sums);   // (whole_sums: every node is the sum of its children)
 // True when the sampling kernel of a call with batch B can carry an insertion of n rows at ring slot cursor (ft: their
 // fields, or null).
 bool sample_can_carry_insert(const Geom& g, const Tuning& tn, uint32_t B, const FieldTable* ft, uint32_t n, uint32_t cursor);

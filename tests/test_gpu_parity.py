@@ -1832,6 +1832,55 @@ def test_sampling_workgroups_take_blocks_in_turn(K, N, T, B):
     m.compare_status()
 
 
+@pytest.mark.parametrize("K,N,T,B", [(2, 17, 3, 40), (2, 33, 1, 64), (2, 4097, 2, 300), (2, 65537, 1, 700), (2, 70001, 3, 130), (2, 1 << 19, 1, 3000),
+                                     (2, (1 << 20) + 1, 1, 40000), (4, 17, 2, 30), (4, 257, 3, 65), (4, 1025, 1, 500), (4, 70001, 2, 900),
+                                     (4, 262145, 1, 4000), (4, 1 << 20, 1, 40000)])
+def test_walks_by_sixteens(K, N, T, B):
+    """Sampling from trees of fanout 2 and 4 by every fourth or second height: groups cut short by the last node, one-sided ones,
+    uniforms that leave their range, leaves of zero, a top left stale, weights by the batch and by the whole buffer; behind
+    changes added, which leave nodes that are not the sums of their children, and in a buffer restored from a copy."""
+    log(f"walks by sixteens K={K} N={N} T={T} B={B}")
+    rng = np.random.default_rng(N + B)
+    m = Mirror(K, N, T, ())
+    prio = wl._draw_priorities("lognormal_0_1", rng, (T, N))
+    prio[:, rng.random(N) < 0.4] = 0.0
+    prio[:, N - 1] = 0.25
+    m.insert(N, prio=prio)
+    new = lambda n: wl._draw_updates("absnormal1_eps_pow0.6", rng, (T, n))  # noqa: E731
+
+    def walks():
+        u = wl.uniform01(rng, (T, B))
+        m.sample(u, 0.4)
+        u[:, ::3] = (rng.random(u[:, ::3].shape) * (3 * B) - B).astype(np.float32)
+        m.sample(u, 0.4)
+
+    for r in range(2):
+        walks()
+        m.update(rng.integers(0, N, (T, B)).astype(np.uint32), new(B))   # (the top is stale behind it)
+        walks()
+        m.sample_gather_update(wl.uniform01(rng, (T, B)), 0.5, True, new(B), alias=True)
+        m.insert(min(N, 5))
+        walks()
+        m.update(np.arange(0, N, 2, dtype=np.uint32)[None].repeat(T, 0), np.zeros((T, (N + 1) // 2), np.float32))   # every other leaf zero
+        m.compare_tree()
+        walks()
+    fresh = PrioritizedReplay(K, N, T, ())
+    fresh.arena.copy_(m.gpu.arena)
+    fresh.set_ring(m.gpu.cursor, m.gpu.size)
+    m.gpu = fresh
+    walks()
+    m.set_weight_norm("buffer")
+    walks()
+    m.set_weight_norm("batch")
+    for i in range(4):   # one change per call: the same bits in any order
+        idx, delta = rng.integers(0, N, (T, 1)).astype(np.uint32), rng.random((T, 1)).astype(np.float32)
+        m.gpu.update_delta(idx_to_dev(idx), dev(delta))
+        m.cpu.update_delta(idx, delta)
+        m.compare_tree()
+        if K == 2:   # (at K = 4 a walk goes by the pairwise sums of four children, which do not add up to a node that changes have rounded)
+            walks()
+
+
 @pytest.mark.parametrize("claim_form", ["group"], indirect=True)   # (no claims in these calls)
 @pytest.mark.parametrize("K,N,T,B", [(8, 1 << 20, 1, 33000), (16, 700_001, 1, 33021), (16, 1 << 22, 1, 40001), (32, 1 << 20, 2, 20001), (32, 1 << 22, 1, 33000),
                                      (64, 300_001, 1, 40000), (64, 1 << 22, 1, 33000)])
