@@ -77,20 +77,30 @@ __device__ __forceinline__ void stage_group_per_lane(const float* __restrict__ l
 // (counters: 63 % at three waves per SIMD with 64 rows each, 11 KB at K = 32), which more of them fill.  In workgroups of four
 // waves, so that no more of them copy the top than before: 2^20 samples on 2^24 leaves 28.2 -> 24 us at K = 32 (33 in
 // workgroups of two), with the `update` behind them 172 -> 148 at K = 64, 142 -> 138 at K = 16, 166 -> 159 at K = 8.
-template <int LOGK>
+template <int LOGK, bool FEW = true>
 struct StageRow {
   static constexpr int K = 1 << LOGK, C = K / 4;
   static constexpr int UNITS = (K + C + 1 + 3) / 4;
   static constexpr int FLOATS = 4 * (UNITS | 1);
   static constexpr int SUMS = K, NODE = K + C;
-  static constexpr int ROWS = LOGK <= 3 ? 64 : LOGK == 4 ? 48 : LOGK == 5 ? 32 : 24;   // staged at a time
-  static constexpr int FETCHES = (ROWS * C + 63) / 64;                                 // 16-byte loads of a lane for them
+  static constexpr int ROWS = !FEW || LOGK <= 3 ? 64 : LOGK == 4 ? 48 : LOGK == 5 ? 32 : 24;   // staged at a time
+  static constexpr int FETCHES = (ROWS * C + 63) / 64;                                         // 16-byte loads of a lane for them
 };
 template <int LOGK>
-constexpr uint32_t kStageFloats = StageRow<LOGK>::ROWS * StageRow<LOGK>::FLOATS;   // per wave
-static uint32_t stage_floats(uint32_t logK) {
-  return logK == 3 ? kStageFloats<3> : logK == 4 ? kStageFloats<4> : logK == 5 ? kStageFloats<5> : logK == 6 ? kStageFloats<6> : 0u;
+static uint32_t stage_floats_k(bool few) {   // per wave
+  return few ? StageRow<LOGK, true>::ROWS * StageRow<LOGK, true>::FLOATS : StageRow<LOGK, false>::ROWS * StageRow<LOGK, false>::FLOATS;
 }
+static uint32_t stage_floats(uint32_t logK, bool few) {
+  return logK == 3 ? stage_floats_k<3>(few) : logK == 4 ? stage_floats_k<4>(few) : logK == 5 ? stage_floats_k<5>(few) : logK == 6 ? stage_floats_k<6>(few) : 0u;
+}
+// Few rows: where 64 samples, spread evenly over the leaves, lie in no more groups than seven eighths of them.  (K = 32, `sample` and
+// `update`: 2^18 samples on 2^24 leaves 51.9 us with 64 rows, 53.7 with 32; 2^20 samples 141 and 138.)
+static bool few_rows(const Geom& g, uint32_t B) {
+  const double groups = 64.0 * (double)g.N / ((double)B * (double)g.K);
+  const int rows = g.logK == 4 ? StageRow<4>::ROWS : g.logK == 5 ? StageRow<5>::ROWS : g.logK == 6 ? StageRow<6>::ROWS : 64;
+  return g.logK <= 3 || groups * (1.0 - exp(-64.0 / groups)) <= 0.875 * rows;
+}
+enum SampleLoop { LOOP_NONE, LOOP_FEW_ROWS, LOOP_ALL_ROWS };   // (see k_sample)
 // Chunk (IT*64 + lane) of the wave's `chunks` 16-byte chunks, for IT = 0 .. C-1: first the numbers of all their nodes,
 // then every fetch, then the LDS stores.  Written as recursions over IT (not loops over arrays of registers) so that each
 // phase is under way as a whole before the next one waits, without the compiler having to promote an array.
@@ -166,9 +176,9 @@ __device__ __forceinline__ void descend_row(const float* row, float& r, unsigned
 
 // One height of the walk: the wave's distinct groups are staged, at most ROWS of them at a time, and every lane walks the row
 // of its group.
-template <int LOGK>
+template <int LOGK, bool FEW>
 __device__ __forceinline__ void descend_staged(const float* __restrict__ lvl, uint32_t node, unsigned lane, float* stage, float& r, unsigned& child, float& val) {
-  using Row = StageRow<LOGK>;
+  using Row = StageRow<LOGK, FEW>;
   const uint32_t below = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)node, 0x138 /* wave_shr:1: from the lane below */, 0xF, 0xF, true);
   const bool first = lane == 0 || below != node;
   const unsigned long long firsts = __ballot(first);
@@ -220,7 +230,7 @@ template <bool RIDE> using RideParam = typename std::conditional<RIDE, InsertRid
 __device__ __forceinline__ void ride_rows(const InsertRide& ride, uint32_t t, uint32_t N, uint32_t part, uint32_t parts);   // (k_rows.h)
 
 // LOOP: fewer sampling workgroups than blocks of samples; each takes blocks in turn.
-template <int LOGK, bool RIDE, bool LOOP>
+template <int LOGK, bool RIDE, int LOOP>
 __global__ void __launch_bounds__(1024)
 k_sample(Geom g, TopCopy tc, uint32_t B, uint32_t size, float beta, const float* __restrict__ u,
          uint32_t* __restrict__ out_idx, float* __restrict__ out_prio, float* __restrict__ out_w,
@@ -229,7 +239,7 @@ k_sample(Geom g, TopCopy tc, uint32_t B, uint32_t size, float beta, const float*
   constexpr int K = Fan<LOGK>::K;
   constexpr int LPS = Fan<LOGK>::LPS;
   constexpr int ROW = LOOP && LOGK >= 3 ? StageRow<LOGK>::FLOATS : K + 4;   // staging row, floats
-  constexpr int ROWS = LOOP && LOGK >= 3 ? StageRow<LOGK>::ROWS : 64;       // of a wave
+  constexpr int ROWS = LOOP && LOGK >= 3 ? StageRow<LOGK, LOOP == LOOP_FEW_ROWS>::ROWS : 64;   // of a wave
   using Vec = typename std::conditional<LOGK == 1, float2, float4>::type;
   constexpr int VF = sizeof(Vec) / 4;
   // (lines 1, 3, 6, 7, 10, 11 of the geometry hold what this kernel does not read on trees of few heights: the upper
@@ -553,8 +563,8 @@ k_sample(Geom g, TopCopy tc, uint32_t B, uint32_t size, float beta, const float*
     if constexpr (LOGK <= 2) {
       if (RIDE && patched) descend_lane<LOGK>(patched, r, child, val);
       else descend_lane<LOGK>(lvl + (size_t)node * K, r, child, val);
-    } else if constexpr (LOOP) {
-      descend_staged<LOGK>(lvl, node, lane, stage, r, child, val);
+    } else if constexpr (LOOP != LOOP_NONE) {
+      descend_staged<LOGK, LOOP == LOOP_FEW_ROWS>(lvl, node, lane, stage, r, child, val);
     } else {
       stage_group_per_lane<LOGK, 0>(lvl, node, lane, stage);
       order_within_wave();
@@ -676,23 +686,24 @@ static hipError_t launch_tree_finish_k(const Geom& g, const Tuning& tn, const Cl
 // fewer workgroups that make it.  One and two waves (us per step, K = 16): 2^18 leaves, 4096 samples, 4 new rows 13.7 and
 // 13.0, 8192 and none 12.6 and 12.1; 2^20 leaves, earlier-batch form of 8192 11.1 and 10.8, 2^22 (1024 roots) 13.3 and
 // 13.9; K = 32, 2^22 leaves, 8192: 13.6 and 13.2.  Two and four: 2^20 leaves at K = 8 (2048 roots), earlier-batch form of
-// 8192, 13.0 and 12.5.  (Fewer than 48 roots: 0.93 to 1.02 times; K = 8 the same, K = 64 0.97 to 1.01.)
+// 8192, 13.0 and 12.5.  (Fewer than 48 roots: 0.93 to 1.02 times; K = 8 the same, K = 64 0.97 to 1.01; 131 072 samples on 2^23
+// leaves at K = 32 35.3 and 36.0.)
 // Every workgroup works a carried insertion out for itself, a run of child groups of which must fit its lanes: that is the
 // least it may have (up to two waves, up to eight on many trees).  On 64 trees it is better worked out by few workgroups of
 // eight waves unless the trees are small (1000 samples, 4 rows each, eight waves and two: 2^18 leaves at K = 16 26.7 and 27.5,
 // 4096 27.3 and 26.2; 48 trees of 2^18 18.7 and 18.4, 8 of 4096 17.9 and 13.5).
-static uint32_t sample_waves(const Geom& g, const Tuning& tn, uint32_t carried) {
+static uint32_t sample_waves(const Geom& g, const Tuning& tn, uint32_t B, uint32_t carried) {
   const uint32_t hb = lazy_top_height(g, tn);
   uint32_t waves = 2;
   if (hb && g.n[hb] > 1024u && g.logK == 3) waves = 4;
-  if (hb >= 3 && (g.logK == 4 || g.logK == 5) && g.n[hb] > 48u && g.n[hb] <= 256u) waves = 1;
+  if (hb >= 3 && (g.logK == 4 || g.logK == 5) && g.n[hb] > 48u && g.n[hb] <= 256u && (uint64_t)B * g.T <= 16384u) waves = 1;
   if (!carried) return waves;
   if (g.T >= 64u && g.N > 8192u) return 8;
   const uint32_t lanes = ((carried - 1) / g.K + 2) * g.K, most = g.T >= 8u ? 8u : 2u;
   const uint32_t least = (lanes + 63u) / 64u < most ? (lanes + 63u) / 64u : most;
   return waves > least ? waves : least;
 }
-constexpr uint32_t kLoopWaves = 4;   // (of the kernel that loops over blocks: see StageRow)
+constexpr uint32_t kLoopWaves = 4;   // (of the kernel that loops over blocks with few rows: see StageRow)
 
 // Workgroup size and top copy of a sampling launch for batch B (stale_hb: the height the stale top is rebuilt
 // from, or 0).  The copy: at most kTopSlots of the topmost heights (below the root), within the LDS budget, and
@@ -701,12 +712,12 @@ struct SampleShape {
   TopCopy tc;
   uint32_t waves, wave_bytes, top_bytes;
 };
-static SampleShape sample_shape(const Geom& g, const Tuning& tn, uint32_t B, uint32_t stale_hb, bool weights_behind, uint32_t carried = 0, bool loop = false,
-                                bool wide = false) {
+static SampleShape sample_shape(const Geom& g, const Tuning& tn, uint32_t B, uint32_t stale_hb, bool weights_behind, uint32_t carried = 0,
+                                SampleLoop loop = LOOP_NONE, bool wide = false) {
   constexpr uint32_t kLdsCap = 128 * 1024;
   SampleShape sh{};
   const uint32_t K = g.K;
-  sh.wave_bytes = g.logK < 3 ? 0u : (loop ? stage_floats(g.logK) : 64u * (K + 4u)) * 4u;   // staging per wave
+  sh.wave_bytes = g.logK < 3 ? 0u : (loop ? stage_floats(g.logK, loop == LOOP_FEW_ROWS) : 64u * (K + 4u)) * 4u;   // staging per wave
   // workgroup size: the configured size, or the whole batch in one workgroup when it is small and no kernel comes behind
   // that could finish the weights (where one does, several workgroups are faster from the third wave on: a step of 1024
   // samples on 2^20 leaves at K = 4 takes 20.8 us with one and 16.3 with eight, of 512 at K = 16 12.8 and 11.7);
@@ -715,7 +726,7 @@ static SampleShape sample_shape(const Geom& g, const Tuning& tn, uint32_t B, uin
   if (max_waves > 16) max_waves = 16;
   if (max_waves < 1) max_waves = 1;
   uint32_t waves = tn.sample_block / 64;
-  if (tn.sample_block_auto) waves = loop ? kLoopWaves : wide ? 2u : sample_waves(g, tn, carried);
+  if (tn.sample_block_auto) waves = loop == LOOP_FEW_ROWS ? kLoopWaves : loop || wide ? 2u : sample_waves(g, tn, B, carried);
   const uint32_t need = (B + 63) / 64;
   if (need <= (weights_behind ? waves : max_waves)) waves = need;
   if (waves > max_waves) waves = max_waves;
@@ -816,7 +827,7 @@ static hipError_t launch_sample_walk(const Geom& tree, const Geom& g, const Tuni
                                   const float* u, const RngArgs& rng, uint32_t* out_idx, float* out_w,
                                   float* out_prio, uint32_t weight_mode, uint32_t stale_hb, const FieldTable* rows,
                                   const ClaimArgs* claim, int claim_mode, const InsertRide* ride, hipStream_t s) {
-  SampleShape sh = sample_shape(g, tn, B, stale_hb, rows || claim, ride ? ride->n : 0u, false, TREE != LOGK);
+  SampleShape sh = sample_shape(g, tn, B, stale_hb, rows || claim, ride ? ride->n : 0u, LOOP_NONE, TREE != LOGK);
   // No more workgroups than the device holds at once (their staging rows fill its LDS): they take further blocks of
   // samples in turn, with the top of the tree in place and the next uniforms under way, where workgroups of a second
   // round would begin with their arguments and the top of the tree again, two of the five trips to memory of a block.
@@ -828,8 +839,10 @@ static hipError_t launch_sample_walk(const Geom& tree, const Geom& g, const Tuni
     const uint64_t by_lds = bytes ? (160 * 1024) / bytes : by_waves, n = by_lds < by_waves ? by_lds : by_waves;
     return (units ? units : 256) * (n < 1 ? 1 : n);
   };
-  const bool loop = !ride && (uint64_t)((B + sh.waves * 64 - 1) / (sh.waves * 64)) * g.T > held();
-  if (loop) sh = sample_shape(g, tn, B, stale_hb, rows || claim, 0, true, TREE != LOGK);
+  const SampleLoop loop = ride || (uint64_t)((B + sh.waves * 64 - 1) / (sh.waves * 64)) * g.T <= held() ? LOOP_NONE
+                          : few_rows(g, B)                                                              ? LOOP_FEW_ROWS
+                                                                                                        : LOOP_ALL_ROWS;
+  if (loop) sh = sample_shape(g, tn, B, stale_hb, rows || claim, 0, loop, TREE != LOGK);
   const TopCopy& tc = sh.tc;
   const uint32_t waves = sh.waves;
   const uint32_t block = waves * 64;
@@ -892,9 +905,9 @@ static hipError_t launch_sample_walk(const Geom& tree, const Geom& g, const Tuni
     if (claim_blocks > 4096) claim_blocks = 4096;   // the claim job strides
   }
   if (ride) {
-    e = grant_lds<&k_sample<LOGK, true, false>>(tn, bytes);
+    e = grant_lds<&k_sample<LOGK, true, LOOP_NONE>>(tn, bytes);
     if (e != hipSuccess) return e;
-    PER_LAUNCH(KID_SAMPLE, (k_sample<LOGK, true, false>), dim3(gx + claim_blocks + rd.movers, g.T), dim3(block), bytes, s, g, tc, B,
+    PER_LAUNCH(KID_SAMPLE, (k_sample<LOGK, true, LOOP_NONE>), dim3(gx + claim_blocks + rd.movers, g.T), dim3(block), bytes, s, g, tc, B,
                size, beta, u, out_idx, out_prio, out_w, weight_mode, stale, claim_blocks, claim_here ? *claim : ClaimArgs{},
                claim_here ? claim_mode : (int)CLAIM_NONE, rng, rd);
   } else {
@@ -906,7 +919,9 @@ static hipError_t launch_sample_walk(const Geom& tree, const Geom& g, const Tuni
                beta, u, out_idx, out_prio, out_w, weight_mode, stale, claim_blocks, claim_here ? *claim : ClaimArgs{},         \
                claim_here ? claim_mode : (int)CLAIM_NONE, rng, NoRide{});                                                      \
   } while (0)
-    if (loop) PER_SAMPLE(true); else PER_SAMPLE(false);
+    if (loop == LOOP_NONE) PER_SAMPLE(LOOP_NONE);
+    else if (LOGK <= 3 || loop == LOOP_FEW_ROWS) PER_SAMPLE(LOOP_FEW_ROWS);
+    else if constexpr (LOGK > 3) PER_SAMPLE(LOOP_ALL_ROWS);
 #undef PER_SAMPLE
   }
   e = hipGetLastError();
