@@ -320,7 +320,7 @@ template <int LOGK>
 static hipError_t launch_insert_bulk_k(const Geom& g, const Tuning& tn, const FieldTable* rows, uint32_t n, uint32_t cursor,
                                        const float* prio, uint32_t* out_idx, bool track_min, hipStream_t s) {
   SubLevels sl;
-  sub_levels<LOGK>(g, &sl);
+  sub_levels<LOGK>(g, tree_pass_height(g), &sl);
   const uint32_t hb = sl.hb, sh = hb * LOGK;
   BulkInsert a{};
   a.n = n;

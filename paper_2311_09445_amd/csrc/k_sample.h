@@ -678,7 +678,7 @@ template <int LOGK>
 static hipError_t launch_tree_k(const Geom& g, const Tuning& tn, const ClaimArgs& c, hipStream_t s);
 template <int LOGK>
 static hipError_t launch_tree_finish_k(const Geom& g, const Tuning& tn, const ClaimArgs& c, const FieldTable* rows,
-                                       const FinishArgs& a, hipStream_t s);
+                                       const FinishArgs& a, bool earlier, hipStream_t s);
 
 // Waves of a sampling workgroup (carried: rows of the insertion that the launch carries, or 0).  Every workgroup copies the
 // top of the tree and, behind an update, rebuilds it from the roots of the tree pass's subtrees.  One wave needs no barriers
@@ -941,7 +941,7 @@ static hipError_t launch_sample_walk(const Geom& tree, const Geom& g, const Tuni
       c2.fold_max = ride ? 1u : 0u;   // the tree pass folds what this kernel has left in max_pend
     }
     if (claim_here) {   // second kernel: tree pass beside the weights and the rows
-      if (rows || finish_weights) return launch_tree_finish_k<TREE>(tree, tn, c2, rows, a, s);
+      if (rows || finish_weights) return launch_tree_finish_k<TREE>(tree, tn, c2, rows, a, claim_mode == CLAIM_BLOCKS, s);
       return launch_tree_k<TREE>(tree, tn, c2, s);
     }
     // second kernel: rows, weights and the claim phase; the tree pass follows

@@ -689,10 +689,10 @@ static size_t tree_lds_bytes(const SubLevels& sl) {
 
 // The heights 1 .. hb of a tree-pass workgroup's subtree (hb: tree_pass_height), and where it keeps them in LDS.
 template <int LOGK>
-static void sub_levels(const Geom& g, SubLevels* out) {
+static void sub_levels(const Geom& g, uint32_t hb, SubLevels* out) {
   constexpr int K = Fan<LOGK>::K;
   SubLevels sl{};
-  sl.hb = tree_pass_height(g);
+  sl.hb = hb;
   uint32_t off = 0;
   for (uint32_t h = 1; h <= sl.hb; ++h) {
     const uint32_t j = h - 1;
@@ -710,16 +710,35 @@ static void sub_levels(const Geom& g, SubLevels* out) {
   *out = sl;
 }
 
+// Large batches at K = 32: the pass may take its subtrees of 32 height-1 nodes, one wave each, where tree_pass_height() gives
+// them 1024; height 3 is then the work of a kernel behind it, so that the next reader finds what it expects.  A workgroup of 512
+// lanes goes through its claimed nodes 256 at a time, a trip to memory or two each, and a tree has few such workgroups.  `sample` and
+// `update`, us, subtrees of 1024 and of 32: 1.5 million leaves (46 of the large ones) 2^14 elements 20.9 and 20.6, 2^16
+// 29.8 and 25.6, 2^20 190 and 130; 2^22 leaves (128) 2^15 21.9 and 22.6, 2^16 26.4 and 26.0, 2^20 134 and 113; 2^23 (256) 2^17
+// 35.0 and 35.9, 2^18 52.7 and 51.5, 2^20 129 and 123; 2^24 (512) 2^18 51.1 and 57.7, 2^20 129 and 132.
+// The same beside the rows and weights of a step that updates its own batch: 2^16 on 2^22 leaves 28.4 and 26.1, 2^18 on 2^23 83.3
+// and 60.0.  A batch known before (`earlier`) has its claims over with sooner: 2^16 on 2^21 leaves 19.6 and 18.4, on 2^22 17.7 and 18.8.
+static bool low_subtrees(const Geom& g, const Tuning& tn, uint32_t B, bool earlier = false) {
+  if (g.logK != 5 || tree_pass_height(g) != 3 || lazy_top_height(g, tn) != 3) return false;
+  const uint64_t roots = g.n[3], over_trees = roots * g.T;
+  return over_trees <= (earlier ? 64u : 128u) ? B >= 512u * roots : over_trees <= (earlier ? 128u : 256u) && B >= 1024u * roots;
+}
+template <int LOGK>
+static hipError_t launch_height_3_k(const Geom& g, const Tuning& tn, hipStream_t s) {
+  const uint64_t threads = (uint64_t)g.n[3] * Fan<LOGK>::LPS;
+  PER_LAUNCH(KID_RESUM_DENSE, k_resum_dense<LOGK>, dim3((uint32_t)((threads + 63) / 64), g.T), dim3(64), 0, s, g, 3u, 0u, g.n[3]);
+  return hipGetLastError();
+}
+
 // Sub-level descriptors and workgroup size of the tree pass for the update batch claimed with `c`.
 template <int LOGK>
-static hipError_t tree_pass_shape(const Geom& g, const Tuning& tn, const ClaimArgs& c, SubLevels* out,
+static hipError_t tree_pass_shape(const Geom& g, const Tuning& tn, const ClaimArgs& c, uint32_t hb, SubLevels* out,
                                   uint32_t* tblock_out) {
   const uint32_t B = c.B;
-  const uint32_t hb = tree_pass_height(g);
   if (hb > (uint32_t)kSubSlots || hb > (uint32_t)kMaxPassHeight<LOGK>)
     return hipErrorInvalidValue;   // cannot happen for fanouts and capacities accepted at create
   SubLevels sl;
-  sub_levels<LOGK>(g, &sl);
+  sub_levels<LOGK>(g, hb, &sl);
   sl.group_batch = c.group_mode ? c.B : 0u;
   // Unless told otherwise: enough lane groups to rebuild in one sweep twice the dirty height-1 nodes a
   // subtree gets on average (never more than it has), so that small batches do not launch idle waves.
@@ -756,9 +775,10 @@ static hipError_t tree_pass_shape(const Geom& g, const Tuning& tn, const ClaimAr
 
 template <int LOGK>
 static hipError_t launch_tree_k(const Geom& g, const Tuning& tn, const ClaimArgs& c, hipStream_t s) {
+  const bool low = low_subtrees(g, tn, c.B);
   SubLevels sl;
   uint32_t tblock;
-  hipError_t e = tree_pass_shape<LOGK>(g, tn, c, &sl, &tblock);
+  hipError_t e = tree_pass_shape<LOGK>(g, tn, c, low ? 2u : tree_pass_height(g), &sl, &tblock);
   if (e != hipSuccess) return e;
   if (tblock > 512) tblock = 512;
   const uint32_t chain = (lazy_top_height(g, tn) ? 0u : 1u) | (c.fold_max ? 2u : 0u);
@@ -776,7 +796,8 @@ static hipError_t launch_tree_k(const Geom& g, const Tuning& tn, const ClaimArgs
     if (c.track_min) { PER_UPDATE_TREE(true, false, NoBatch{}); } else { PER_UPDATE_TREE(false, false, NoBatch{}); }
   }
 #undef PER_UPDATE_TREE
-  return hipGetLastError();
+  e = hipGetLastError();
+  return e == hipSuccess && low ? launch_height_3_k<LOGK>(g, tn, s) : e;
 }
 
 // The update of a small batch as one kernel.
@@ -785,7 +806,7 @@ static hipError_t launch_update_here_k(const Geom& g, const Tuning& tn, ClaimArg
   SubLevels sl;
   uint32_t tblock;
   c.group_mode = 0;
-  hipError_t e = tree_pass_shape<LOGK>(g, tn, c, &sl, &tblock);
+  hipError_t e = tree_pass_shape<LOGK>(g, tn, c, tree_pass_height(g), &sl, &tblock);
   if (e != hipSuccess) return e;
   SmallBatch batch{c, 64};
   while (batch.slots < 2 * c.B) batch.slots *= 2;
@@ -806,13 +827,15 @@ static hipError_t launch_update_here_k(const Geom& g, const Tuning& tn, ClaimArg
   return hipGetLastError();
 }
 
-// The tree pass of the update batch claimed with `c` together with the weights and row jobs in `a` / `rows`.
+// The tree pass of the update batch claimed with `c` together with the weights and row jobs in `a` / `rows` (earlier: the batch
+// was known before the sampling kernel).
 template <int LOGK>
 static hipError_t launch_tree_finish_k(const Geom& g, const Tuning& tn, const ClaimArgs& c, const FieldTable* rows,
-                                       const FinishArgs& a, hipStream_t s) {
+                                       const FinishArgs& a, bool earlier, hipStream_t s) {
+  const bool low = low_subtrees(g, tn, c.B, earlier);
   SubLevels sl;
   uint32_t tblock;
-  hipError_t e = tree_pass_shape<LOGK>(g, tn, c, &sl, &tblock);
+  hipError_t e = tree_pass_shape<LOGK>(g, tn, c, low ? 2u : tree_pass_height(g), &sl, &tblock);
   if (e != hipSuccess) return e;
   if (tblock > 512) tblock = 512;   // half the lanes of a compute unit are left to the other jobs
   FieldTable ft{};
@@ -836,7 +859,8 @@ static hipError_t launch_tree_finish_k(const Geom& g, const Tuning& tn, const Cl
     if (wide) { PER_TREE_FINISH(false, true); } else { PER_TREE_FINISH(false, false); }
   }
 #undef PER_TREE_FINISH
-  return hipGetLastError();
+  e = hipGetLastError();
+  return e == hipSuccess && low ? launch_height_3_k<LOGK>(g, tn, s) : e;
 }
 
 // Does a batch of B elements in leaf order claim faster in runs than leaf by leaf?  The atomics of the leaf by leaf form
@@ -858,7 +882,7 @@ static bool runs_pay(const Geom& g, uint32_t B) {
   const uint64_t elements = (uint64_t)B * g.T;
   if ((uint64_t)B * 128u < g.N || elements < 1u << 16) return false;
   SubLevels sl;
-  sub_levels<LOGK>(g, &sl);
+  sub_levels<LOGK>(g, tree_pass_height(g), &sl);
   const uint64_t subtrees = (uint64_t)g.n[sl.hb] * g.T;
   const bool large = sl.list_cap >= 512u;
   if (large && (sl.list_cap >= 2048u || subtrees < 32u)) return false;

@@ -2063,6 +2063,31 @@ def test_small_subtrees_of_the_tree_pass(K, N, T):
     m.compare_status()
 
 
+@pytest.mark.parametrize("claim_form", ["group", "leaf"], indirect=True)
+@pytest.mark.parametrize("N,T,B", [((1 << 20) + 1, 1, 512 * 33), ((1 << 20) + 1, 1, 512 * 33 - 1), (1_200_001, 2, 512 * 37), ((1 << 21) + 1, 1, 1024 * 65), ((1 << 21) + 1, 1, 512 * 65)])
+def test_large_batches_in_small_subtrees(claim_form, N, T, B):
+    """K = 32: batches from the size on at which the tree pass takes its subtrees at height 2 and leaves height 3 to a kernel behind
+    it, and of one element less: updates, steps of both forms, through a position map, with the tree's minimum kept."""
+    log(f"large batches in small subtrees N={N} T={T} B={B}")
+    rng = np.random.default_rng(N + B)
+    m = Mirror(32, N, T, (5,))
+    m.insert(N, prio=wl._draw_priorities("lognormal_0_1", rng, (T, N)), chunk=1 << 19)
+    new = lambda: wl._draw_updates("absnormal1_eps_pow0.6", rng, (T, B))  # noqa: E731
+    for norm in ("batch", "buffer"):
+        m.set_weight_norm(norm)
+        gi, ci = m.sample(wl.uniform01(rng, (T, B)), 0.5)
+        m.update(ci, new())
+        m.compare_tree()
+        m.sample_gather_update(wl.uniform01(rng, (T, B)), 0.5, True, new(), alias=False)
+        m.step_call(wl.uniform01(rng, (T, B)), 0.5, True, new())
+        m.compare_tree()
+        pos = np.stack([rng.permutation(B) for _ in range(T)]).astype(np.uint32)
+        m.insert_step_call(3, None, wl.uniform01(rng, (T, B)), 0.5, True, new(), pos)
+        m.compare_tree(heights=(1, 2, 3, 4))
+    m.compare_min_priority()
+    m.compare_status()
+
+
 @pytest.mark.parametrize("N", [(1 << 23) + 1, (1 << 24) + 1])
 @pytest.mark.parametrize("norm", ["batch", "buffer"])
 def test_largest_subtrees_of_the_tree_pass(N, norm, claim_form):
