@@ -50,32 +50,92 @@ __device__ __forceinline__ void claim_in_group(const Geom& g, uint32_t t, uint32
 
 // Dense batches (ClaimArgs::runs: a group gets a quarter of an element or more on the average): consecutive elements of the
 // batch for leaves of one group, as a sampled batch has them (it is in leaf order), claim together.  The last of such a
-// run within a wave raises the group's entry for all of it; the entry then holds the run's length (2 .. 64) with the sign
+// run raises the group's entry for all of it; the entry then holds the run's length (2 .. 127) with the sign
 // bit set, which no valid priority has beside such bits, in place of the value, and the tree pass reads the run's elements
 // from the batch.  What is displaced from an entry, or does not get in, goes leaf by leaf as before, element by element if
-// it is a run.  Runs are disjoint pieces of the batch, so the run with the latest last element is later than every
-// element of the others.  (One element at a time, 2^20 elements on 2^24 leaves take 1.6 million atomics of the leaf by leaf
-// form besides 2^20 on the entries: 64 us; the tree pass then picks those leaves' stamps up one by one.)
-__device__ __forceinline__ uint32_t run_length(uint32_t lo) { return (lo >> 31) && (lo & 0x7FFFFFFFu) >= 2u && (lo & 0x7FFFFFFFu) <= 64u ? lo & 0x7Fu : 1u; }
-__device__ __forceinline__ void claim_run(const Geom& g, uint32_t t, const ClaimArgs& c, uint32_t base, uint32_t j, uint32_t i,
-                                          uint32_t vbits, uint32_t count) {
+// it is a run: the lanes of the wave take an element each.  Runs are disjoint pieces of the batch, so the run with the latest
+// last element is later than every element of the others.  (One element at a time, 2^20 elements on 2^24 leaves take 1.6
+// million atomics of the leaf by leaf form besides 2^20 on the entries: 64 us; the tree pass then picks those leaves' stamps
+// up one by one.)
+// A wave takes the runs that begin among its 64 elements, to their end among the next 64; only where all of those belong to
+// the run do they make one of their own.  So a batch in leaf order whose groups have no more than 64 elements each displaces
+// nothing.  (Runs that ended with the wave's elements left the first part of every run on such a border to be displaced, and one
+// lane claimed its elements in turn: 2^20 elements on 2^20 leaves 39.4 us at K = 16, 66.2 at K = 64, 8.4 and 9.2 so; on 2^24, 10.5
+// both: what its returning atomics take.)
+__device__ __forceinline__ uint32_t run_length(uint32_t lo) { return (lo >> 31) && (lo & 0x7FFFFFFFu) >= 2u && (lo & 0x7FFFFFFFu) <= 127u ? lo & 0x7Fu : 1u; }
+struct RunElement {
+  uint32_t i, vbits, group;
+  bool ok;
+};
+// Element j of the batch (none beyond its end).  What is not valid has a group of its own among its 64, so it ends every run.
+__device__ __forceinline__ RunElement run_element(const Geom& g, uint32_t t, const ClaimArgs& c, uint32_t j, uint32_t& flags) {
+  RunElement e{0xFFFFFFFFu, 0u, 0u, false};
+  if (j < c.B) {
+    e.vbits = __float_as_uint(c.prio[(size_t)t * c.B + j]);
+    e.i = c.idx[(size_t)t * c.B + j];
+    if (!(e.i < c.size)) flags |= 1u;
+    else if (!valid_priority(__uint_as_float(e.vbits))) flags |= 2u;
+    else e.ok = true;
+  }
+  e.group = e.ok ? e.i >> (g.logK == 6 ? 6u : 5u) : 0xFFFFFFC0u | (j & 63u);
+  return e;
+}
+__device__ __forceinline__ unsigned long long group_begins(uint32_t group, uint32_t before, unsigned lane) {   // (before: the group in front of lane 0's)
+  const uint32_t below = (uint32_t)__builtin_amdgcn_update_dpp((int)before, (int)group, 0x138 /* wave_shr:1: from the lane below */, 0xF, 0xF, false);
+  return __ballot((lane == 0 ? before : below) != group);
+}
+// Called by whole waves with their 64 elements, from `first_j` on.
+__device__ __forceinline__ void claim_runs(const Geom& g, uint32_t t, const ClaimArgs& c, uint32_t base, uint32_t first_j, uint32_t& mx, uint32_t& flags) {
+  const unsigned lane = threadIdx.x & 63u;
   const uint32_t lg = g.logK == 6 ? 6u : 5u;
-  const uint32_t slot = i & ((1u << lg) - 1u);
-  const uint32_t mine_hi = ((base + j) << 6) | slot, mine_lo = count > 1 ? 0x80000000u | count : vbits;
-  const unsigned long long mine = ((unsigned long long)mine_hi << 32) | mine_lo;
-  const unsigned long long old =
-      atomicMax(reinterpret_cast<unsigned long long*>(g.nclaim) + (size_t)t * g.nclaim_stride + (i >> lg), mine);
-  const uint32_t old_hi = (uint32_t)(old >> 32);
-  if ((old_hi >> 6) < base) return;
-  const bool stays = mine > old;
-  const uint32_t out_hi = stays ? old_hi : mine_hi, out_lo = stays ? (uint32_t)old : mine_lo, n = run_length(out_lo);
-  if (n == 1) {
-    if (count == 1 && run_length((uint32_t)old) == 1 && (old_hi & 63u) == slot) return;   // (one leaf: the later of the two dominates)
-    claim_leaf(g, t, (i & ~((1u << lg) - 1u)) | (out_hi & 63u), out_hi >> 6, out_lo);
-  } else {
-    const uint32_t last = (out_hi >> 6) - base;
-    for (uint32_t e = last + 1 - n; e <= last; ++e)
-      claim_leaf(g, t, c.idx[(size_t)t * c.B + e], base + e, __float_as_uint(c.prio[(size_t)t * c.B + e]));
+  uint32_t not_here = 0;
+  const RunElement mine = run_element(g, t, c, first_j + lane, flags);
+  const RunElement next = run_element(g, t, c, first_j + 64u + lane, not_here);
+  RunElement front{0, 0, 0xFFFFFFFEu, false};   // (in front of the batch: nothing like any element)
+  if (first_j) front = run_element(g, t, c, first_j - 1u, not_here);
+  const uint32_t vb = mine.ok && __uint_as_float(mine.vbits) > 0.0f ? mine.vbits : 0u;
+  mx = vb > mx ? vb : mx;
+  unsigned long long starts = group_begins(mine.group, front.group, lane);
+  if (!starts) starts = 1;   // (all of one run that began before: a run of its own)
+  const unsigned long long next_starts = group_begins(next.group, (uint32_t)__builtin_amdgcn_readlane((int)mine.group, 63), lane);
+  const uint32_t beyond = next_starts ? (uint32_t)__builtin_ctzll(next_starts) : 0u;   // elements of the last run among the next 64
+  const unsigned long long upto = starts & (~0ull >> (63u - lane));                    // (none: the run began before this wave's elements)
+  const bool ends = lane == 63u || ((starts >> (lane + 1u)) & 1u);
+  uint32_t i = mine.i, vbits = mine.vbits, j = first_j + lane, count = 0;
+  if (mine.ok && ends && upto) count = lane - (63u - (unsigned)__builtin_clzll(upto)) + 1u;
+  if (beyond) {
+    const uint32_t li = (uint32_t)__builtin_amdgcn_readlane((int)next.i, (int)(beyond - 1u)), lv = (uint32_t)__builtin_amdgcn_readlane((int)next.vbits, (int)(beyond - 1u));
+    if (lane == 63u && count) {
+      i = li;
+      vbits = lv;
+      j += beyond;
+      count += beyond;
+    }
+  }
+  uint32_t out_last = 0, out_n = 0;   // a run that goes leaf by leaf
+  if (count) {
+    const uint32_t slot = i & ((1u << lg) - 1u);
+    const uint32_t mine_hi = ((base + j) << 6) | slot, mine_lo = count > 1 ? 0x80000000u | count : vbits;
+    const unsigned long long claim = ((unsigned long long)mine_hi << 32) | mine_lo;
+    const unsigned long long old =
+        atomicMax(reinterpret_cast<unsigned long long*>(g.nclaim) + (size_t)t * g.nclaim_stride + (i >> lg), claim);
+    const uint32_t old_hi = (uint32_t)(old >> 32);
+    if ((old_hi >> 6) >= base) {
+      const bool stays = claim > old;
+      const uint32_t out_hi = stays ? old_hi : mine_hi, out_lo = stays ? (uint32_t)old : mine_lo, n = run_length(out_lo);
+      if (n > 1) {
+        out_last = (out_hi >> 6) - base;
+        out_n = n;
+      } else if (!(count == 1 && run_length((uint32_t)old) == 1 && (old_hi & 63u) == slot)) {   // (one leaf: the later of the two dominates)
+        claim_leaf(g, t, (i & ~((1u << lg) - 1u)) | (out_hi & 63u), out_hi >> 6, out_lo);
+      }
+    }
+  }
+  for (unsigned long long left = __ballot(out_n != 0); left; left &= left - 1) {
+    const int of = __builtin_ctzll(left);
+    const uint32_t n = (uint32_t)__builtin_amdgcn_readlane((int)out_n, of), e0 = (uint32_t)__builtin_amdgcn_readlane((int)out_last, of) + 1u - n;
+    for (uint32_t e = lane; e < n; e += 64u)
+      claim_leaf(g, t, c.idx[(size_t)t * c.B + e0 + e], base + e0 + e, __float_as_uint(c.prio[(size_t)t * c.B + e0 + e]));
   }
 }
 
@@ -106,7 +166,7 @@ __device__ __forceinline__ void leave_claim_base(const Geom& g, uint32_t t, uint
 
 // Claims elements of the batch, strided over the job's workgroups.  Called by whole workgroups.
 // TD: the batch may hold temporal-difference errors to be turned into priorities first (only the
-// stand-alone claim kernel carries that code).  RUNS: see claim_run.
+// stand-alone claim kernel carries that code).  RUNS: see claim_runs.
 template <bool TD = false, bool RUNS = false>
 __device__ __forceinline__ void claim_job(const Geom& g, uint32_t t, const ClaimArgs& c, uint32_t job_block,
                                           uint32_t job_blocks) {
@@ -118,30 +178,7 @@ __device__ __forceinline__ void claim_job(const Geom& g, uint32_t t, const Claim
   for (uint32_t base = job_block * blockDim.x; base < c.B; base += job_blocks * blockDim.x) {
     const uint32_t j = base + threadIdx.x;
     if constexpr (RUNS) {
-      const unsigned lane = threadIdx.x & 63u;
-      uint32_t i = 0xFFFFFFFFu;
-      float v = 0.0f;
-      if (j < c.B) {
-        v = c.prio[(size_t)t * c.B + j];
-        i = c.idx[(size_t)t * c.B + j];
-      }
-      bool ok = false;
-      if (j < c.B) {
-        if (!(i < c.size)) flags |= 1u;
-        else if (!valid_priority(v)) flags |= 2u;
-        else ok = true;
-      }
-      const uint32_t group = ok ? i >> (g.logK == 6 ? 6u : 5u) : 0xFFFFFFC0u | lane;   // (an invalid element ends every run)
-      const uint32_t below = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)group, 0x138 /* wave_shr:1: from the lane below */, 0xF, 0xF, true);
-      const bool begins = lane == 0 || below != group;
-      const unsigned long long starts = __ballot(begins);
-      const bool ends = lane == 63u || ((starts >> (lane + 1u)) & 1u);
-      if (ok && ends) {
-        const unsigned start = 63u - (unsigned)__builtin_clzll(starts & (~0ull >> (63u - lane)));
-        claim_run(g, t, c, first, j, i, __float_as_uint(v), lane - start + 1u);
-      }
-      const uint32_t vb = ok && v > 0.0f ? __float_as_uint(v) : 0u;
-      mx = vb > mx ? vb : mx;
+      if (j - (threadIdx.x & 63u) < c.B) claim_runs(g, t, c, first, j - (threadIdx.x & 63u), mx, flags);   // (the same for the wave)
     } else if (j < c.B) {
       float v = c.prio[(size_t)t * c.B + j];
       if constexpr (TD) {

@@ -108,7 +108,7 @@ struct ClaimArgs {
   uint32_t group_mode;     // the batch claims through the group entries (else leaf by leaf)
   uint32_t track_min;      // the tree pass also renews min1 of the height-1 nodes it rebuilds
   uint32_t fold_max;       // the tree pass also folds max_pend into the running maximum
-  uint32_t runs;           // group_mode: consecutive elements for one group claim together (see claim_run)
+  uint32_t runs;           // group_mode: consecutive elements for one group claim together (see claim_runs)
   const uint32_t* idx;     // [T][B]
   const uint32_t* pos;     // null, or [T][B] positions: element j targets idx[pos[j]] (the leaf drawn by sample pos[j] of the
                            // sampling call the update is fused with); a position >= B makes the element invalid
@@ -263,7 +263,7 @@ struct Tuning {
   uint32_t insert_small;      // small inserts run as one kernel (one workgroup per tree)
   uint32_t claim_in_sample;   // fused steps may run the claim phase in the sampling kernel (two kernels per step)
   uint32_t group_claim;       // update batches claim through the group entries whenever they are short enough
-  uint32_t update_runs;       // per_update claims in runs (see claim_run): 0 never, 1 where it pays off, 2 wherever it can
+  uint32_t update_runs;       // per_update claims in runs (see claim_runs): 0 never, 1 where it pays off, 2 wherever it can
   uint32_t insert_ride;       // per_insert_step lets its sampling kernel carry the insertion where that is possible
   uint32_t sample_block_auto; // sample_block is the default, not a size that was asked for
   uint32_t whole_rows;        // gathers of several fields move whole rows through LDS where the rows are short enough

@@ -1938,6 +1938,32 @@ def test_updates_claimed_in_runs(K, N, T, norm):
         assert m.gpu.min_priority().cpu().numpy().tobytes() == want.tobytes()
 
 
+@pytest.mark.parametrize("claim_form", ["group"], indirect=True)   # (the other forms claim no runs)
+@pytest.mark.parametrize("K,N", [(2, 9000), (8, 20000), (16, 70001), (32, 150_001), (64, 70001)])
+def test_runs_on_either_side_of_a_wave_s_elements(claim_form, K, N):
+    """Runs of 1 to 200 elements in one claim group, beginning and ending anywhere among a wave's 64 elements and filling some
+    waves whole, in leaf order and with groups that come again; invalid elements that cut them."""
+    log(f"runs and waves K={K} N={N}")
+    rng = np.random.default_rng(N)
+    per = 64 if K == 64 else 32
+    groups = N // per
+    for kind in range(4):
+        m = Mirror(K, N, 1, ())
+        m.gpu.set_tuning("update_runs", 2)
+        m.insert(N, prio=wl._draw_priorities("exponential_1", rng, (1, N)))
+        for r in range(3):
+            lengths = rng.choice([1, 2, 3, 31, 62, 63, 64, 65, 66, 126, 127, 128, 129, 191, 192, 193, 200], 400)
+            at = np.sort(rng.integers(0, groups, 400)) if kind % 2 == 0 else rng.integers(0, groups, 400)
+            idx = np.concatenate([np.sort(rng.integers(0, per, n)) + per * g for n, g in zip(lengths, at)])[None].astype(np.uint32)
+            prio = (rng.random(idx.shape) * 3).astype(np.float32)
+            if kind >= 2:
+                prio[:, rng.random(idx.shape[1]) < 0.01] = np.float32("nan")
+                idx[:, rng.random(idx.shape[1]) < 0.01] = N + 7
+            m.update(idx, prio)
+            m.compare_tree()
+        m.compare_status()
+
+
 @pytest.mark.parametrize("K,N,T,B", [(16, 70001, 1, 65535), (16, 70001, 1, 65536), (4, 20001, 4, 16384), (64, 70001, 1, 196607), (64, 70001, 1, 196608),
                                      (64, 16500, 64, 1100), (32, 1 << 20, 1, 196608), (32, 1100000, 1, 196607), (32, 1100000, 1, 196608)])
 def test_updates_either_side_of_the_rule_for_runs(K, N, T, B):
