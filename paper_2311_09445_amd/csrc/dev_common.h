@@ -53,6 +53,11 @@ __device__ __forceinline__ int butterfly_move(int x) {
                                  : 0x140;    // row_mirror
   return __builtin_amdgcn_update_dpp(0, x, ctrl, 0xF, 0xF, true);
 }
+// The value of lane I of this lane's four.
+template <int I>
+__device__ __forceinline__ int quad_lane(int x) {
+  return __builtin_amdgcn_update_dpp(0, x, I * 0x55 /* quad_perm [I,I,I,I] */, 0xF, 0xF, true);
+}
 template <int LOGLPS, int STEP = 0>
 __device__ __forceinline__ float butterfly_sum(float s) {
   if constexpr (STEP < LOGLPS) {

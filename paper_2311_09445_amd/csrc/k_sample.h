@@ -851,11 +851,11 @@ static hipError_t launch_sample_walk(const Geom& tree, const Geom& g, const Tuni
   if (loop) {
     gx = (uint32_t)(held() / g.T < 2 ? 2 : held() / g.T);   // (at least two: one workgroup alone finishes the weights of the block it holds)
     if (gx > blocks) gx = blocks;
-    // Where the leaves stay in the second-level caches (32 MiB), no more workgroups than it takes for all to have as many blocks
-    // as the busiest: `sample` and `update` of 2^19 on 3 million leaves at K = 32 87.6 -> 83.5 us, on 2^20 at K = 16
+    // Where the leaves take up to half the second-level caches (32 MiB), no more workgroups than it takes for all to have as many
+    // blocks as the busiest: `sample` and `update` of 2^19 on 3 million leaves at K = 32 87.6 -> 83.5 us, on 2^20 at K = 16
     // 67.2 -> 63.5.  On 2^24 leaves at K = 32 the workgroups without a last block leave more of the memory to the
-    // others: 78.2 so, 80.2 with as many blocks each.
-    if ((uint64_t)g.N * g.T * 4u <= 32u << 20 && gx > 2) {
+    // others: 78.2 so, 80.2 with as many blocks each; 286 222 on 7.9 million at K = 16 50.4 and 52.1.
+    if ((uint64_t)g.N * g.T * 4u <= 16u << 20 && gx > 2) {
       const uint32_t rounds = (blocks + gx - 1) / gx;
       gx = (blocks + rounds - 1) / rounds;
       if (gx < 2) gx = 2;

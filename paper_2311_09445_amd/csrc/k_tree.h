@@ -37,7 +37,7 @@ struct SubLevels {
 template <int LOGK>
 constexpr int kMaxPassHeight = LOGK == 1 ? 13 : LOGK == 2 ? 6 : LOGK == 3 ? 4 : LOGK <= 5 ? 3 : 2;
 
-// The batch itself, for a tree pass over a batch that claimed in runs (see claim_run).
+// The batch itself, for a tree pass over a batch that claimed in runs (see claim_runs).
 struct BatchRef {
   const uint32_t* idx;   // [T][B]
   const float* prio;
@@ -282,6 +282,12 @@ __device__ __forceinline__ void tree_job(const Geom& g, const SubLevels& sl, uin
     // Two nodes per lane group and sweep, the loads of both issued before the first store: a
     // second sweep would otherwise cost a second trip to memory.
     using LeafVec = typename std::conditional<LOGK == 1, float2, float4>::type;
+    // RUNS: the lanes of a four that rebuild one node (K >= 16) fetch two of eight elements of its run each and hand them to
+    // each other by quad permutes.  (Every lane fetching four for itself: eight loads beside the one of its leaves where
+    // there are four now, and a trip to memory for every four elements of a longer run: 2^20 elements on 2^20 leaves
+    // 19.2 us at K = 16, 51.2 at K = 64, 17.0 and 42.9 so; on 2^24 at K = 32 34.0 and 33.9.)
+    constexpr bool QUADS = RUNS && LPS >= 4;
+    constexpr uint32_t RUN_WORDS = QUADS ? 2u : 4u;
     struct Item {
       bool ok;
       uint32_t node, my;
@@ -290,8 +296,8 @@ __device__ __forceinline__ void tree_job(const Geom& g, const SubLevels& sl, uin
       uint2 s[RUNS ? 1 : 4];   // (RUNS: of the lane's first dirty leaf; few leaves are)
       uint2 e;
       uint32_t mn;   // (TRACK_MIN only)
-      uint32_t ri[RUNS ? 4 : 1];   // (RUNS: the first elements of the entry's run; a longer one is read on in finish)
-      float rv[RUNS ? 4 : 1];
+      uint32_t ri[RUNS ? RUN_WORDS : 1];   // (RUNS: the first elements of the entry's run; a longer one is read on in finish)
+      float rv[RUNS ? RUN_WORDS : 1];
     };
     // A set bit means the leaf was claimed leaf by leaf in this batch: its stamp entry holds the winner's value.
     auto fetch = [&](uint32_t item) -> Item {
@@ -314,11 +320,13 @@ __device__ __forceinline__ void tree_job(const Geom& g, const SubLevels& sl, uin
         if (it.e.y >= 0xC0000000u) {
           const size_t e0 = (size_t)t * batch.B + (it.e.y & 0x3FFFFFFFu) + 1u - it.e.x;
 #pragma unroll
-          for (uint32_t k = 0; k < 4; ++k)
-            if (k < it.e.x) {
-              it.ri[k] = batch.idx[e0 + k];
-              it.rv[k] = batch.prio[e0 + k];
+          for (uint32_t k = 0; k < RUN_WORDS; ++k) {
+            const uint32_t el = QUADS ? 4 * k + (threadIdx.x & 3u) : k;
+            if (el < it.e.x) {
+              it.ri[k] = batch.idx[e0 + el];
+              it.rv[k] = batch.prio[e0 + el];
             }
+          }
         }
       }
       if constexpr (RUNS) {
@@ -357,22 +365,47 @@ __device__ __forceinline__ void tree_job(const Geom& g, const SubLevels& sl, uin
           const uint32_t l = i & (uint32_t)(K - 1);
           if (LOGK == 1 || (l >> 2) == q) set(LOGK == 1 ? l : l & 3u, v);
         };
-#pragma unroll
-        for (uint32_t k = 0; k < 4; ++k)
-          if (k < it.e.x) take(it.ri[RUNS ? k : 0], it.rv[RUNS ? k : 0]);
         if constexpr (RUNS) {
           const size_t e0 = (size_t)t * batch.B + (it.e.y & 0x3FFFFFFFu) + 1u - it.e.x;
-          for (uint32_t k0 = 4; k0 < it.e.x; k0 += 4) {   // (four at a time: an element at a time is a trip to memory each)
-            uint32_t i[4];
-            float v[4];
+          if constexpr (QUADS) {
+            auto four = [&](uint32_t k, uint32_t ei, float ev4) {   // elements k .. k + 3, one in each lane of the four
+              if (k >= it.e.x) return;                               // (the same for the lanes of a node)
+              const int i = (int)ei, v = __float_as_int(ev4);
+              take((uint32_t)quad_lane<0>(i), __int_as_float(quad_lane<0>(v)));
+              if (k + 1 < it.e.x) take((uint32_t)quad_lane<1>(i), __int_as_float(quad_lane<1>(v)));
+              if (k + 2 < it.e.x) take((uint32_t)quad_lane<2>(i), __int_as_float(quad_lane<2>(v)));
+              if (k + 3 < it.e.x) take((uint32_t)quad_lane<3>(i), __int_as_float(quad_lane<3>(v)));
+            };
+            four(0, it.ri[0], it.rv[0]);
+            four(4, it.ri[1], it.rv[1]);
+            for (uint32_t k0 = 8; k0 < it.e.x; k0 += 16) {   // (sixteen at a time: fewer are a trip to memory each)
+              uint32_t i[4];
+              float v[4];
 #pragma unroll
-            for (uint32_t k = 0; k < 4; ++k) {
-              const uint32_t at = k0 + k < it.e.x ? k0 + k : it.e.x - 1;
-              i[k] = batch.idx[e0 + at];
-              v[k] = batch.prio[e0 + at];
+              for (uint32_t w = 0; w < 4; ++w) {
+                const uint32_t el = k0 + 4 * w + (threadIdx.x & 3u), at = el < it.e.x ? el : it.e.x - 1;
+                i[w] = batch.idx[e0 + at];
+                v[w] = batch.prio[e0 + at];
+              }
+#pragma unroll
+              for (uint32_t w = 0; w < 4; ++w) four(k0 + 4 * w, i[w], v[w]);
             }
+          } else {
 #pragma unroll
-            for (uint32_t k = 0; k < 4; ++k) take(i[k], v[k]);   // (the last element again beyond the end)
+            for (uint32_t k = 0; k < 4; ++k)
+              if (k < it.e.x) take(it.ri[k], it.rv[k]);
+            for (uint32_t k0 = 4; k0 < it.e.x; k0 += 4) {   // (four at a time: an element at a time is a trip to memory each)
+              uint32_t i[4];
+              float v[4];
+#pragma unroll
+              for (uint32_t k = 0; k < 4; ++k) {
+                const uint32_t at = k0 + k < it.e.x ? k0 + k : it.e.x - 1;
+                i[k] = batch.idx[e0 + at];
+                v[k] = batch.prio[e0 + at];
+              }
+#pragma unroll
+              for (uint32_t k = 0; k < 4; ++k) take(i[k], v[k]);   // (the last element again beyond the end)
+            }
           }
         }
       };
@@ -865,28 +898,31 @@ static hipError_t launch_tree_finish_k(const Geom& g, const Tuning& tn, const Cl
 
 // Does a batch of B elements in leaf order claim faster in runs than leaf by leaf?  The atomics of the leaf by leaf form
 // cost by the element, wherever they go; in runs the tree pass waits for the elements that it reads back, the longer the
-// more of them one workgroup has.  So, from a quarter of an element per group of 32 leaves on:
-//  - from 65 536 elements in all on (leaf by leaf and in runs: 2^20 leaves at K = 16: 2^15 elements 8.3 and 8.8 us, 2^16
-//    11.7 and 10.9, 2^18 37.5 and 21.0; 16 trees of 2^16 leaves at K = 8: 4096 each 12.2 and 10.7);
+// more of them one workgroup has.  So, from a quarter of an element per group of 32 leaves on (us of `sample` and `update`, leaf by
+// leaf and in runs, where K is 16 or more):
+//  - from 65 536 elements in all on, if there is one in 56 leaves (at K = 16 below 2^17 elements: in 32; 2^20 leaves: 2^16 elements
+//    at K = 16 22.9 and 21.2, at K = 64 26.8 and 24.5, 2^18 at K = 16 55.4 and 30.8; 2^22 leaves: 2^16 at K = 64 24.4 and 26.1, at K = 16
+//    22.8 and 24.0, 2^17 34.3 and 29.8, 28.2 and 28.4; 178 351 on 2^23 at K = 16 41.8 and 39.4), or from 196 608 on (2^24 leaves: 2^17 at K = 16 35.3 and 36.2, 2^18 50.5 and 48.7); at K = 16 from 16 384 on with one in 12 leaves
+//    (70 000 leaves: 2^14 20.4 and 19.5; 300 000: 2^14 17.5 and 18.0, 2^15 20.3 and 18.9);
 //  - where the pass has few workgroups of many elements, from 196 608 on: subtrees of 512 or more height-1 nodes (2^22
-//    leaves at K = 32: 2^17 elements 17.9 and 21.8, 2^18 31 and 27; 2^24 at K = 4: 2^18 55 and 57, 2^19 73 and 70), or fewer
-//    than 256 subtrees at K = 64, whose runs are the longest (286 877 leaves: 170 423 elements 40 and 64; 2^20 leaves:
-//    2^17 22.0 and 21.8);
-//  - not with fewer than 32 such large subtrees (86 850 leaves at K = 32, 3 of them: 221 563 elements 105 and 189; 16
-//    trees of 148 120 leaves, 80 of them: 39 182 each 92 and 53), nor from 2048 nodes on (2^24 leaves at K = 2: 2^20
-//    elements 255 and 302).
-// Over 419 shapes drawn (every fanout, 2^16 .. 2^24 leaves, 1 .. 16 trees, 2^14 .. 2^20 elements) the chosen form takes 1.3 %
-// longer than the better one in the mean, leaf by leaf throughout 40 %, runs throughout 9 %.
+//    leaves at K = 32: 2^17 elements 30.2 both, 2^18 50.5 and 38.0; 2^24 at K = 4, `update` alone: 2^18 55 and 57, 2^19 73 and 70), or fewer
+//    than 256 subtrees at K = 64, whose runs are the longest (70 000 leaves: 2^17 elements 77 and 86); fewer than 256 at
+//    K = 32 from 1500 elements each on (70 000 leaves, 69 of them: 2^16 30.4 and 35.0, 2^17 58.2 and 53.7);
+//  - not with fewer than 32 such large subtrees (`update` alone, 16 trees of 148 120 leaves at K = 32, 80 of them: 39 182 each 92 and
+//    53), nor from 2048 nodes on (2^24 leaves at K = 2: 2^20 elements 255 and 302).
 template <int LOGK>
 static bool runs_pay(const Geom& g, uint32_t B) {
   const uint64_t elements = (uint64_t)B * g.T;
-  if ((uint64_t)B * 128u < g.N || elements < 1u << 16) return false;
+  if ((uint64_t)B * 128u < g.N || elements < (LOGK == 4 ? 1u << 14 : 1u << 16)) return false;
+  if (elements < 1u << 16) return (uint64_t)B * 12u >= g.N;
   SubLevels sl;
   sub_levels<LOGK>(g, tree_pass_height(g), &sl);
   const uint64_t subtrees = (uint64_t)g.n[sl.hb] * g.T;
   const bool large = sl.list_cap >= 512u;
   if (large && (sl.list_cap >= 2048u || subtrees < 32u)) return false;
-  return elements >= (large || (LOGK == 6 && subtrees < 256u) ? 3u << 16 : 1u << 16);
+  if (large || (LOGK == 6 && subtrees < 256u)) return elements >= 3u << 16;
+  if (LOGK == 5 && subtrees < 256u) return elements >= 1500u * subtrees;
+  return LOGK < 4 || (uint64_t)B * (LOGK == 4 && elements < 1u << 17 ? 32u : 56u) >= g.N || elements >= 3u << 16;
 }
 
 template <int LOGK>
