@@ -1938,6 +1938,43 @@ def test_updates_claimed_in_runs(K, N, T, norm):
         assert m.gpu.min_priority().cpu().numpy().tobytes() == want.tobytes()
 
 
+@pytest.mark.parametrize("K,N,T,B", [(2, 3000, 1, 700), (4, 70001, 2, 500), (8, 9000, 1, 3000), (16, 70001, 1, 4100), (16, 1 << 18, 3, 900), (32, 1 << 20, 1, 8200), (64, 70001, 1, 2500)])
+def test_many_elements_for_few_leaves(K, N, T, B):
+    """New rows with a priority far above the rest, so that a sampled batch names their leaves over and over, side by side; invalid
+    priorities among the elements of one leaf, the last ones of a wave's included; the batch claimed by its sampling lanes, through a
+    position map, by workgroups of its own and by the stand-alone update."""
+    log(f"few leaves K={K} N={N} T={T} B={B}")
+    rng = np.random.default_rng(N + B)
+    m = Mirror(K, N, T, ())
+    m.insert(N, prio=rng.random((T, N)).astype(np.float32))
+
+    def new(n=B):
+        p = wl._draw_updates("absnormal1_eps_pow0.6", rng, (T, n))
+        p[:, rng.random(n) < 0.1] = np.float32("nan")
+        p[:, 63::64] = np.float32("nan")
+        return p
+
+    for r in range(2):
+        m.insert(5, prio=(N * (1 + rng.random((T, 5)))).astype(np.float32))
+        m.step_call(wl.uniform01(rng, (T, B)), 0.5, True, new())
+        m.compare_tree()
+        m.insert_step_call(3, None, wl.uniform01(rng, (T, B)), 0.5, True, new())
+        m.compare_tree()
+        m.insert(4)
+        pos = np.stack([np.sort(rng.integers(0, B, B)) for _ in range(T)]).astype(np.uint32)
+        m.step_call(wl.uniform01(rng, (T, B)), 0.5, True, new(), pos)
+        m.insert(4)
+        m.sample_gather_update(wl.uniform01(rng, (T, B)), 0.5, True, new(), alias=False)
+        m.insert(4)
+        m.sample_gather_update(wl.uniform01(rng, (T, B)), 0.5, True, new(), alias=True)
+        m.compare_tree()
+        few = rng.integers(0, N, 7)
+        m.update(np.sort(rng.choice(few, (T, B)), axis=1).astype(np.uint32), new())
+        m.update(rng.choice(few, (T, B)).astype(np.uint32), new())
+        m.compare_tree()
+    m.compare_status()
+
+
 @pytest.mark.parametrize("claim_form", ["group"], indirect=True)   # (the other forms claim no runs)
 @pytest.mark.parametrize("K,N", [(2, 9000), (8, 20000), (16, 70001), (32, 150_001), (64, 70001)])
 def test_runs_on_either_side_of_a_wave_s_elements(claim_form, K, N):
