@@ -680,7 +680,7 @@ template <int LOGK>
 static hipError_t launch_tree_finish_k(const Geom& g, const Tuning& tn, const ClaimArgs& c, const FieldTable* rows,
                                        const FinishArgs& a, bool earlier, hipStream_t s);
 
-// Waves of a sampling workgroup (carried: rows of the insertion that the launch carries, or 0).  Every workgroup copies the
+// Waves of a sampling workgroup (carried: what the launch carries of an insertion).  Every workgroup copies the
 // top of the tree and, behind an update, rebuilds it from the roots of the tree pass's subtrees.  One wave needs no barriers
 // for that and leaves the samples to the most compute units; with more than 256 roots the copy wants more lanes, beyond 1024
 // fewer workgroups that make it.  One and two waves (us per step, K = 16): 2^18 leaves, 4096 samples, 4 new rows 13.7 and
@@ -692,16 +692,38 @@ static hipError_t launch_tree_finish_k(const Geom& g, const Tuning& tn, const Cl
 // least it may have (up to two waves, up to eight on many trees).  On 64 trees it is better worked out by few workgroups of
 // eight waves unless the trees are small (1000 samples, 4 rows each, eight waves and two: 2^18 leaves at K = 16 26.7 and 27.5,
 // 4096 27.3 and 26.2; 48 trees of 2^18 18.7 and 18.4, 8 of 4096 17.9 and 13.5).
-static uint32_t sample_waves(const Geom& g, const Tuning& tn, uint32_t B, uint32_t carried) {
+// The rows of a carried insertion are moved by workgroups of the same size, whole rows each, a sweep of the lanes after the other.
+// Where that takes more than four sweeps (rows of many pieces: odd lengths go by bytes) it is the largest size again, two waves on up
+// to seven trees, eight on more (4 rows each; one wave and two, 441 samples on 300 000 leaves at K = 16: 319 bytes, five sweeps, 12.6 both,
+// 511 14.6 and 12.7, 1033 20.9 and 15.8; two waves and eight, 256 samples on 8 trees of 50 000: 511 bytes, four sweeps, 13.0 and 13.3, 639 13.8 and
+// 13.4, 1033 17.6 and 15.0).
+struct CarriedRows {
+  uint32_t n, pieces;   // rows per tree, elements that one is moved in
+  uint32_t movers(uint32_t lanes) const {   // as many as it takes to move every element in one sweep (whole rows each; at most 32)
+    const uint64_t all = ((uint64_t)n * pieces + lanes - 1) / lanes;
+    const uint32_t most = n < 32u ? n : 32u;
+    return all < 1 ? 1u : all < most ? (uint32_t)all : most;
+  }
+  uint64_t sweeps(uint32_t lanes) const { return ((uint64_t)((n + movers(lanes) - 1) / movers(lanes)) * pieces + lanes - 1) / lanes; }
+};
+static CarriedRows carried_rows(const FieldTable* ft, uint32_t n) {
+  CarriedRows c{n, 0};
+  if (ft)
+    for (uint32_t f = 0; f < ft->n_fields; ++f)
+      if (ft->io[f]) c.pieces += ft->bytes[f] / ft->vec[f];
+  return c;
+}
+static uint32_t sample_waves(const Geom& g, const Tuning& tn, uint32_t B, const CarriedRows& carried) {
   const uint32_t hb = lazy_top_height(g, tn);
   uint32_t waves = 2;
   if (hb && g.n[hb] > 1024u && g.logK == 3) waves = 4;
   if (hb >= 3 && (g.logK == 4 || g.logK == 5) && g.n[hb] > 48u && g.n[hb] <= 256u && (uint64_t)B * g.T <= 16384u) waves = 1;
-  if (!carried) return waves;
+  if (!carried.n) return waves;
   if (g.T >= 64u && g.N > 8192u) return 8;
-  const uint32_t lanes = ((carried - 1) / g.K + 2) * g.K, most = g.T >= 8u ? 8u : 2u;
+  const uint32_t lanes = ((carried.n - 1) / g.K + 2) * g.K, most = g.T >= 8u ? 8u : 2u;
   const uint32_t least = (lanes + 63u) / 64u < most ? (lanes + 63u) / 64u : most;
-  return waves > least ? waves : least;
+  if (waves < least) waves = least;
+  return waves < most && carried.sweeps(waves * 64u) > 4 ? most : waves;
 }
 constexpr uint32_t kLoopWaves = 4;   // (of the kernel that loops over blocks with few rows: see StageRow)
 
@@ -712,7 +734,7 @@ struct SampleShape {
   TopCopy tc;
   uint32_t waves, wave_bytes, top_bytes;
 };
-static SampleShape sample_shape(const Geom& g, const Tuning& tn, uint32_t B, uint32_t stale_hb, bool weights_behind, uint32_t carried = 0,
+static SampleShape sample_shape(const Geom& g, const Tuning& tn, uint32_t B, uint32_t stale_hb, bool weights_behind, const CarriedRows& carried = {},
                                 SampleLoop loop = LOOP_NONE, bool wide = false) {
   constexpr uint32_t kLdsCap = 128 * 1024;
   SampleShape sh{};
@@ -808,7 +830,7 @@ bool sample_can_carry_insert(const Geom& g, const Tuning& tn, uint32_t B, const 
       if (ft->io[f]) bytes += (uint64_t)n * ft->bytes[f];
   if (bytes > 256 * 1024) return false;
   // the top copy must reach down to the height the top is rebuilt from
-  const SampleShape sh = sample_shape(g, tn, B, hb, true, n);
+  const SampleShape sh = sample_shape(g, tn, B, hb, true, carried_rows(ft, n));
   if (sh.tc.nslots == 0 || g.H - sh.tc.nslots > hb) return false;
   // the runs of the patch must fit the workgroup, and the patch its share of the LDS
   InsertRide rd{};
@@ -827,7 +849,8 @@ static hipError_t launch_sample_walk(const Geom& tree, const Geom& g, const Tuni
                                   const float* u, const RngArgs& rng, uint32_t* out_idx, float* out_w,
                                   float* out_prio, uint32_t weight_mode, uint32_t stale_hb, const FieldTable* rows,
                                   const ClaimArgs* claim, int claim_mode, const InsertRide* ride, hipStream_t s) {
-  SampleShape sh = sample_shape(g, tn, B, stale_hb, rows || claim, ride ? ride->n : 0u, LOOP_NONE, TREE != LOGK);
+  const CarriedRows carried = ride ? carried_rows(&ride->rows, ride->n) : CarriedRows{};
+  SampleShape sh = sample_shape(g, tn, B, stale_hb, rows || claim, carried, LOOP_NONE, TREE != LOGK);
   // No more workgroups than the device holds at once (their staging rows fill its LDS): they take further blocks of
   // samples in turn, with the top of the tree in place and the next uniforms under way, where workgroups of a second
   // round would begin with their arguments and the top of the tree again, two of the five trips to memory of a block.
@@ -842,7 +865,7 @@ static hipError_t launch_sample_walk(const Geom& tree, const Geom& g, const Tuni
   const SampleLoop loop = ride || (uint64_t)((B + sh.waves * 64 - 1) / (sh.waves * 64)) * g.T <= held() ? LOOP_NONE
                           : few_rows(g, B)                                                              ? LOOP_FEW_ROWS
                                                                                                         : LOOP_ALL_ROWS;
-  if (loop) sh = sample_shape(g, tn, B, stale_hb, rows || claim, 0, loop, TREE != LOGK);
+  if (loop) sh = sample_shape(g, tn, B, stale_hb, rows || claim, {}, loop, TREE != LOGK);
   const TopCopy& tc = sh.tc;
   const uint32_t waves = sh.waves;
   const uint32_t block = waves * 64;
@@ -887,14 +910,7 @@ static hipError_t launch_sample_walk(const Geom& tree, const Geom& g, const Tuni
     if (stale < 0 || stale_hb != lazy_top_height(g, tn) || claim_mode == CLAIM_BLOCKS) return hipErrorInvalidValue;
     rd = *ride;
     if (!plan_ride(g, tc, block, stale_hb, &rd)) return hipErrorInvalidValue;
-    // movers: as many as it takes to move every row element in one sweep (whole rows each; at most 32)
-    uint64_t row_elements = 0;
-    for (uint32_t f = 0; f < rd.rows.n_fields; ++f)
-      if (rd.rows.io[f]) row_elements += (uint64_t)rd.n * (rd.rows.bytes[f] / rd.rows.vec[f]);
-    rd.movers = (uint32_t)((row_elements + block - 1) / block);
-    if (rd.movers > rd.n) rd.movers = rd.n;
-    if (rd.movers > 32) rd.movers = 32;
-    if (rd.movers < 1) rd.movers = 1;
+    rd.movers = carried.movers(block);
     bytes += (size_t)rd.floats * 4;
   }
   if (bytes < tn.sample_min_lds) bytes = tn.sample_min_lds;   // asking for more LDS than needed spreads workgroups over more CUs

@@ -1508,6 +1508,27 @@ def test_insert_carried_by_the_step(K, N, T, B, fb, rides):
     m.compare_status()
 
 
+@pytest.mark.parametrize("claim_form", ["group"], indirect=True)
+@pytest.mark.parametrize("K,N,T,B,fb", [(16, 300_000, 1, 441, (255,)), (16, 300_000, 1, 441, (319,)), (16, 300_000, 1, 441, (1033, 4)), (16, 50_000, 8, 256, (511,)),
+                                        (16, 50_000, 8, 256, (639, 16)), (32, 1_700_000, 1, 130, (1033,)), (16, 4096, 64, 70, (1033,))])
+def test_carried_rows_of_many_pieces(claim_form, K, N, T, B, fb):
+    """Rows that a mover of the smallest sampling workgroups takes four sweeps of its lanes for, and more, where the workgroups are larger."""
+    log(f"carried rows of many pieces K={K} N={N} T={T} B={B} fb={fb}")
+    rng = np.random.default_rng(N + B)
+    m = Mirror(K, N, T, fb, oracle_payload=False)
+    m.gpu.set_tuning("step_on_chip", 0)
+    m.insert(N, prio=wl._draw_priorities("exponential_1", rng, (T, N)), with_rows=False)
+    m.gpu.profile(True)
+    for n in (1, 4, 23, 64):
+        ins = (wl._draw_priorities("exponential_1", rng, (T, n)) * np.float32(N)).astype(np.float32)   # (the new rows are drawn)
+        before = kernel_launches(m)
+        m.insert_step_call(n, ins, wl.uniform01(rng, (T, B)), 0.5, True, wl._draw_updates("absnormal1_eps_pow0.6", rng, (T, B)))
+        assert n > 16 or kernel_launches(m).get("k_insert_bulk", 0) == before.get("k_insert_bulk", 0)
+        m.compare_tree()
+    m.gpu.profile(False)
+    m.compare_status()
+
+
 @pytest.mark.parametrize("K,N,T,B,most", [(16, 20000, 8, 300, 128), (8, 9000, 9, 600, 128), (4, 3000, 16, 512, 128), (32, 70001, 8, 513, 128), (32, 70001, 32, 512, 64),
                                           (64, 9000, 4, 512, 16), (64, 9000, 4, 511, 0)])
 def test_largest_carried_insertions(K, N, T, B, most):
