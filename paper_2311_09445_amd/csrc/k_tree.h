@@ -56,7 +56,13 @@ using BatchParam = typename std::conditional<HERE, SmallBatch, typename std::con
 // its own subtree into a table in LDS, keyed by leaf, where the latest valid element of a leaf wins by an LDS atomic; the
 // leaves' bits go into a word (two for K = 64) per height-1 node.  No stamps and no dirty bits in memory then, and no
 // kernel of its own: 512 temporal-difference errors on 100 000 leaves at K = 64, 5.2 us, 6.9 as two kernels.
-constexpr uint32_t kHereBatch = 2048;      // largest batch claimed so (the table has 12 bytes per slot, two slots per element)
+constexpr uint32_t kHereBatch = 2048;      // largest batch claimed so
+constexpr uint32_t kHereSlotBytes = 12;    // of the table of claimed leaves: a key, an element and its value
+static uint32_t here_slots(uint32_t B) {   // (at least two per element)
+  uint32_t slots = 64;
+  while (slots < 2 * B) slots *= 2;
+  return slots;
+}
 // Most elements read over all workgroups (2048 by 1024 of them: 10.5 us, 7.7 as two kernels; 1024: 6.2 and 7.6).
 constexpr uint64_t kHereReads = 1u << 20;
 struct LeafTable {
@@ -833,22 +839,43 @@ static hipError_t launch_tree_k(const Geom& g, const Tuning& tn, const ClaimArgs
   return e == hipSuccess && low ? launch_height_3_k<LOGK>(g, tn, s) : e;
 }
 
-// The update of a small batch as one kernel.
+// The height of the subtrees in which a small batch is updated by one kernel, or 0 where two are faster.  Many workgroups of small
+// subtrees (tree_pass_height()) are faster than few of large ones (subtree_height()) while the device holds them all at once, which
+// their tables of claimed leaves limit; at K = 16 up to 2048 of them.  us per `update` as two kernels, in small subtrees and in large ones:
+//  - K = 32: 1024 elements of each of 4 trees of 287 219 leaves, 1124 small subtrees 7.3, 6.9 and 7.0, 1500 7.3, 13.5 and 8.0; 1500 on
+//    600 000 leaves, 586 of them 6.3, 9.3 and 6.9, of each of 16 trees of 30 000, 480 of them 8.1, 6.7 and 20.2; 282 of each of 8 of 455 000, 3560 of
+//    them 7.7, 8.7 and 6.0.
+//  - K = 16: 2048 of each of 4 trees of 16 384, 256 of them 9.5, 5.6 and 6.8; 200 of each of 32, 2048 of them 7.9, 5.5 and 5.7, of each of 64, 4096
+//    of them 8.3, 6.3 and 5.8.
+// In large ones a workgroup works through what a whole part of the tree gets, four nodes at a time: at K = 32 (1024 nodes) 128 elements on
+// the average, 64 on one to three trees (2^20 leaves: 2048 6.8, 10.3 and 6.7; 16 trees of 200 000: 512 of each, 73 a subtree 7.5, 9.0 and 6.8, 2048
+// 8.6, 28.5 and 10.1).
+static uint32_t update_here_height(const Geom& g, uint32_t B) {
+  if (B > kHereBatch) return 0;
+  const uint32_t hb = tree_pass_height(g), large = subtree_height(g);
+  if (hb < large) {
+    const uint64_t table = (uint64_t)here_slots(B) * kHereSlotBytes, held = 256u * (128u * 1024u / table), trees = g.T;
+    if (g.n[hb] * trees <= held && (g.logK == 5 || g.n[hb] * trees <= 2048u)) return hb;
+    if (g.logK == 5 && B > (trees >= 4u ? 128u : 64u) * (uint64_t)g.n[large]) return 0;
+  }
+  return (uint64_t)g.n[large] * g.T * B <= kHereReads ? large : 0u;
+}
+
+// The update of a small batch as one kernel, in subtrees of height hb.
 template <int LOGK>
-static hipError_t launch_update_here_k(const Geom& g, const Tuning& tn, ClaimArgs c, hipStream_t s) {
+static hipError_t launch_update_here_k(const Geom& g, const Tuning& tn, ClaimArgs c, uint32_t hb, hipStream_t s) {
   SubLevels sl;
   uint32_t tblock;
   c.group_mode = 0;
-  hipError_t e = tree_pass_shape<LOGK>(g, tn, c, tree_pass_height(g), &sl, &tblock);
+  hipError_t e = tree_pass_shape<LOGK>(g, tn, c, hb, &sl, &tblock);
   if (e != hipSuccess) return e;
-  SmallBatch batch{c, 64};
-  while (batch.slots < 2 * c.B) batch.slots *= 2;
+  const SmallBatch batch{c, here_slots(c.B)};
   uint32_t want = (c.B + 255) / 256 * 64;   // (the batch in one sweep of four elements per lane)
   if (want > tblock && !tn.tree_block) tblock = want;
   if (tblock > 512) tblock = 512;
   const uint32_t chain = lazy_top_height(g, tn) ? 0u : 1u;
   const size_t words = sl.list_cap * (LOGK == 6 ? 2u : 1u);
-  const size_t lds = tree_lds_bytes<LOGK>(sl) + 4 + (size_t)batch.slots * 12 + words * 4;
+  const size_t lds = tree_lds_bytes<LOGK>(sl) + 4 + (size_t)batch.slots * kHereSlotBytes + words * 4;
 #define PER_UPDATE_HERE(TM)                                                                                               \
   do {                                                                                                                    \
     e = grant_lds<&k_update_tree<LOGK, TM, false, true>>(tn, lds);                                                        \
@@ -929,9 +956,8 @@ template <int LOGK>
 static hipError_t launch_update_k(const Geom& g, const Tuning& tn, ClaimArgs c, hipStream_t s) {
   const uint32_t block = tn.update_block;
   const bool can_run = c.group_mode && !c.from_td && !c.pos, force_runs = can_run && tn.update_runs == 2;
-  if (c.group_mode && tn.claim_in_sample && !c.pos && !force_runs && c.B <= kHereBatch &&
-      (uint64_t)g.n[tree_pass_height(g)] * g.T * c.B <= kHereReads)
-    return launch_update_here_k<LOGK>(g, tn, c, s);
+  if (c.group_mode && tn.claim_in_sample && !c.pos && !force_runs)
+    if (const uint32_t hb = update_here_height(g, c.B)) return launch_update_here_k<LOGK>(g, tn, c, hb, s);
   c.runs = force_runs || (can_run && tn.update_runs && runs_pay<LOGK>(g, c.B)) ? 1u : 0u;
   if (c.runs) {
     PER_LAUNCH(KID_UPDATE_CLAIM, k_update_claim<true>, dim3((c.B + block - 1) / block, g.T), dim3(block), 0, s, g, c);

@@ -2222,6 +2222,33 @@ def test_small_batches_claimed_in_the_tree_pass(K, N, T, norm):
     m.compare_status()
 
 
+@pytest.mark.parametrize("claim_form", ["group"], indirect=True)   # (the others claim by a kernel of its own)
+@pytest.mark.parametrize("K,N,T,B,one", [(16, 14_800, 64, 512, True), (16, 8192, 64, 282, True), (16, 8193, 64, 282, True), (16, 12_616, 16, 2048, True),
+                                         (16, 4097, 4, 2048, True), (32, 1 << 20, 1, 1024, True), (32, 1 << 20, 1, 1025, True), (32, 600_000, 1, 1216, True),
+                                         (32, 600_000, 1, 1217, False), (32, 287_219, 4, 1152, True), (32, 287_219, 4, 1153, False), (32, 30_000, 1, 2048, True),
+                                         (8, 1 << 19, 4, 256, True), (8, 1 << 19, 4, 257, False), (16, 12_616, 16, 2049, False)])
+def test_small_batches_are_one_kernel(claim_form, K, N, T, B, one):
+    """Updates of batches that one kernel claims and writes, in subtrees of the tree pass and in larger ones, up to the largest that
+    it takes and of one element more."""
+    log(f"one kernel K={K} N={N} T={T} B={B}")
+    rng = np.random.default_rng(N + B)
+    m = Mirror(K, N, T, ())
+    m.insert(N, prio=wl._draw_priorities("lognormal_0_1", rng, (T, N)))
+    for r in range(3):
+        idx = rng.integers(0, N if r < 2 else min(N, 500), (T, B)).astype(np.uint32)
+        if r == 1:
+            m.sample(wl.uniform01(rng, (T, 100)), 0.5)             # (the top is no longer stale)
+        m.gpu.profile(True)
+        m.update(idx, (rng.random((T, B)) * 4).astype(np.float32))
+        launched = kernel_launches(m)
+        m.gpu.profile(False)
+        assert (launched == {"k_update_tree": 1}) == one, launched
+        if r != 1:
+            m.sample(wl.uniform01(rng, (T, 100)), 0.5)             # (rebuilds the top from what the pass has left)
+        m.compare_tree()
+    m.compare_status()
+
+
 # ---------------------------------------------------------------------------------------------
 # per_run_requests: a queue of op-coded requests in one launch.  Same results as the calls, in queue order.
 # ---------------------------------------------------------------------------------------------
