@@ -67,50 +67,77 @@ struct RunElement {
   uint32_t i, vbits, group;
   bool ok;
 };
-// Element j of the batch (none beyond its end).  What is not valid has a group of its own among its 64, so it ends every run.
-__device__ __forceinline__ RunElement run_element(const Geom& g, uint32_t t, const ClaimArgs& c, uint32_t j, uint32_t& flags) {
-  RunElement e{0xFFFFFFFFu, 0u, 0u, false};
-  if (j < c.B) {
-    e.vbits = __float_as_uint(c.prio[(size_t)t * c.B + j]);
-    e.i = c.idx[(size_t)t * c.B + j];
-    if (!(e.i < c.size)) flags |= 1u;
-    else if (!valid_priority(__uint_as_float(e.vbits))) flags |= 2u;
-    else e.ok = true;
-  }
-  e.group = e.ok ? e.i >> (g.logK == 6 ? 6u : 5u) : 0xFFFFFFC0u | (j & 63u);
-  return e;
+// Element j of the batch, of which i and v are what memory holds (none beyond the batch's end).  What is not valid has a group of
+// its own among its 64, so it ends every run.
+__device__ __forceinline__ RunElement run_element(const Geom& g, const ClaimArgs& c, uint32_t j, uint32_t i, float v, uint32_t& flags) {
+  const bool here = j < c.B, named = here && i < c.size, good = valid_priority(v);
+  flags |= here && !named ? 1u : named && !good ? 2u : 0u;
+  const bool ok = named && good;
+  return RunElement{i, __float_as_uint(v), ok ? i >> (g.logK == 6 ? 6u : 5u) : 0xFFFFFFC0u | (j & 63u), ok};
 }
 __device__ __forceinline__ unsigned long long group_begins(uint32_t group, uint32_t before, unsigned lane) {   // (before: the group in front of lane 0's)
   const uint32_t below = (uint32_t)__builtin_amdgcn_update_dpp((int)before, (int)group, 0x138 /* wave_shr:1: from the lane below */, 0xF, 0xF, false);
   return __ballot((lane == 0 ? before : below) != group);
 }
-// Called by whole waves with their 64 elements, from `first_j` on.
+// Of the elements of a run that stand side by side for one leaf the last dominates the others: a run begins with the last element of its
+// first leaf, and one that goes leaf by leaf passes such elements over.  Where most of a run is dominated so its last element claims
+// alone, and what dominates before it goes to the leaves' stamps at once: the tree pass would wait for every sixteen elements of the
+// run.  (Priorities with a long tail: most of a batch may be for a handful of leaves, whose stamps the elements of displaced runs
+// raised one behind the other.  `update` of batches sampled from such priorities, all elements claimed and so: 131 072 on 2^20 leaves at K = 32 55.6
+// and 17.4 us, on 2^21 at K = 64 79 and 16.4, 62 033 on 574 707 at K = 16 22.3 and 11.4, 2^18 on 2^22 at K = 8 171 and 18.6, 2^20 on 2^24 at K = 32
+// 69.5 and 40.0.  Batches in no order, whose runs are of one element, pay for what is looked at: 5870 elements of each of 16 trees of 5870
+// leaves at K = 4 18.1 us, 16.8 leaf by leaf, 2^18 on 896 794 at K = 8 39.5 and 39.0.)
+// Called by whole waves with their 64 elements, from `first_j` on.  All loads are under way before the first is looked at.
 __device__ __forceinline__ void claim_runs(const Geom& g, uint32_t t, const ClaimArgs& c, uint32_t base, uint32_t first_j, uint32_t& mx, uint32_t& flags) {
   const unsigned lane = threadIdx.x & 63u;
   const uint32_t lg = g.logK == 6 ? 6u : 5u;
+  const uint32_t* idx = c.idx + (size_t)t * c.B;
+  const float* prio = c.prio + (size_t)t * c.B;
+  const uint32_t j_mine = first_j + lane, j_next = j_mine + 64u, j_front = first_j ? first_j - 1u : 0u, end = c.B - 1u;
+  const uint32_t i_mine = idx[min_u32(j_mine, end)], i_next = idx[min_u32(j_next, end)], i_front = idx[j_front];
+  const float v_mine = prio[min_u32(j_mine, end)], v_next = prio[min_u32(j_next, end)], v_front = prio[j_front];
   uint32_t not_here = 0;
-  const RunElement mine = run_element(g, t, c, first_j + lane, flags);
-  const RunElement next = run_element(g, t, c, first_j + 64u + lane, not_here);
-  RunElement front{0, 0, 0xFFFFFFFEu, false};   // (in front of the batch: nothing like any element)
-  if (first_j) front = run_element(g, t, c, first_j - 1u, not_here);
+  const RunElement mine = run_element(g, c, j_mine, i_mine, v_mine, flags);
+  const RunElement next = run_element(g, c, j_next, i_next, v_next, not_here);
+  const RunElement before = run_element(g, c, j_front, i_front, v_front, not_here);
+  const uint32_t front = first_j ? before.group : 0xFFFFFFFEu;   // (in front of the batch: nothing like any element)
   const uint32_t vb = mine.ok && __uint_as_float(mine.vbits) > 0.0f ? mine.vbits : 0u;
   mx = vb > mx ? vb : mx;
-  unsigned long long starts = group_begins(mine.group, front.group, lane);
+  unsigned long long starts = group_begins(mine.group, front, lane);
   if (!starts) starts = 1;   // (all of one run that began before: a run of its own)
   const unsigned long long next_starts = group_begins(next.group, (uint32_t)__builtin_amdgcn_readlane((int)mine.group, 63), lane);
   const uint32_t beyond = next_starts ? (uint32_t)__builtin_ctzll(next_starts) : 0u;   // elements of the last run among the next 64
+  // lanes whose element is for another leaf than the one in front of it (of elements of one run: all of them are valid)
+  const unsigned long long leaves = group_begins(mine.i, 0u, lane);
+  const unsigned long long next_leaves = group_begins(next.i, (uint32_t)__builtin_amdgcn_readlane((int)mine.i, 63), lane);
   const unsigned long long upto = starts & (~0ull >> (63u - lane));                    // (none: the run began before this wave's elements)
   const bool ends = lane == 63u || ((starts >> (lane + 1u)) & 1u);
-  uint32_t i = mine.i, vbits = mine.vbits, j = first_j + lane, count = 0;
-  if (mine.ok && ends && upto) count = lane - (63u - (unsigned)__builtin_clzll(upto)) + 1u;
+  uint32_t i = mine.i, vbits = mine.vbits, j = j_mine, count = 0, of_leaves = 0;
+  if (mine.ok && ends && upto) {
+    const unsigned start = 63u - (unsigned)__builtin_clzll(upto);
+    const unsigned long long later = leaves & (~0ull >> (63u - lane)) & ~(~0ull >> (63u - start));   // leaves that begin behind the run's first
+    count = later ? lane - (unsigned)__builtin_ctzll(later) + 2u : 1u;
+    of_leaves = 1u + (uint32_t)__popcll(later);
+  }
   if (beyond) {
     const uint32_t li = (uint32_t)__builtin_amdgcn_readlane((int)next.i, (int)(beyond - 1u)), lv = (uint32_t)__builtin_amdgcn_readlane((int)next.vbits, (int)(beyond - 1u));
+    const unsigned long long later = next_leaves & (~0ull >> (64u - beyond));
     if (lane == 63u && count) {
       i = li;
       vbits = lv;
       j += beyond;
-      count += beyond;
+      count = count > 1 ? count + beyond : later ? beyond - (uint32_t)__builtin_ctzll(later) + 1u : 1u;
+      of_leaves += (uint32_t)__popcll(later);
     }
+  }
+  const bool alone = count > 8u + 2u * of_leaves;
+  if (const unsigned long long split = __ballot(alone)) {   // (a bit per run, at its last lane)
+    if (alone) count = 1;
+    const unsigned last = lane + (unsigned)__builtin_ctzll(((starts >> 1) | 1ull << 63) >> lane);   // of this lane's run
+    const bool to_end = beyond != 0 && (split >> 63);
+    if ((split >> last) & 1u && ((lane < last && (leaves >> (lane + 1u)) & 1u) || (lane == 63u && to_end && next_leaves & 1u)))
+      claim_leaf(g, t, mine.i, base + j_mine, mine.vbits);
+    if (to_end && lane + 1u < beyond && (next_leaves >> (lane + 1u)) & 1u) claim_leaf(g, t, next.i, base + j_next, next.vbits);
   }
   uint32_t out_last = 0, out_n = 0;   // a run that goes leaf by leaf
   if (count) {
@@ -131,11 +158,18 @@ __device__ __forceinline__ void claim_runs(const Geom& g, uint32_t t, const Clai
       }
     }
   }
-  for (unsigned long long left = __ballot(out_n != 0); left; left &= left - 1) {
+  if (out_n && out_n <= 4u) {   // (short ones, as batches in no order have them: a lane each)
+    const uint32_t e0 = out_last + 1u - out_n;
+    for (uint32_t e = 0; e < out_n; ++e) claim_leaf(g, t, idx[e0 + e], base + e0 + e, __float_as_uint(prio[e0 + e]));
+  }
+  for (unsigned long long left = __ballot(out_n > 4u); left; left &= left - 1) {
     const int of = __builtin_ctzll(left);
     const uint32_t n = (uint32_t)__builtin_amdgcn_readlane((int)out_n, of), e0 = (uint32_t)__builtin_amdgcn_readlane((int)out_last, of) + 1u - n;
-    for (uint32_t e = lane; e < n; e += 64u)
-      claim_leaf(g, t, c.idx[(size_t)t * c.B + e0 + e], base + e0 + e, __float_as_uint(c.prio[(size_t)t * c.B + e0 + e]));
+    for (uint32_t e = lane; e < n; e += 64u) {
+      const uint32_t leaf = idx[e0 + e], above = idx[min_u32(e0 + e + 1u, e0 + n - 1u)];
+      const float v = prio[e0 + e];
+      if (e + 1u == n || above != leaf) claim_leaf(g, t, leaf, base + e0 + e, __float_as_uint(v));
+    }
   }
 }
 

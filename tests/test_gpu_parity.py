@@ -2022,6 +2022,44 @@ def test_runs_on_either_side_of_a_wave_s_elements(claim_form, K, N):
         m.compare_status()
 
 
+@pytest.mark.parametrize("claim_form", ["group"], indirect=True)   # (the other forms claim no runs)
+@pytest.mark.parametrize("K,N,T", [(2, 9000, 1), (4, 4097, 3), (8, 20000, 1), (16, 70001, 2), (32, 150_001, 1), (64, 70001, 1)])
+def test_runs_of_repeated_leaves(claim_form, K, N, T):
+    """Runs most of whose elements the next one overwrites, at the edge of what still claims as a run and far beyond it, across the
+    ends of a wave's elements, in leaf order and with groups and leaves that come again; invalid elements among them."""
+    log(f"repeated leaves K={K} N={N} T={T}")
+    rng = np.random.default_rng(N)
+    per = 64 if K == 64 else 32
+    groups = N // per
+    m = Mirror(K, N, T, ())
+    m.gpu.set_tuning("update_runs", 2)
+    m.insert(N, prio=wl._draw_priorities("exponential_1", rng, (T, N)))
+    for kind in range(6):
+        batches = []
+        for t in range(T):
+            parts = []
+            for _ in range(120):
+                g = int(rng.integers(0, groups if kind % 2 else min(groups, 9)))
+                if kind < 2:       # a few leaves in a row, the last repeated so often that the run is one element short of going apart, or not
+                    n = int(rng.integers(1, 12))
+                    parts.append(per * g + np.concatenate([rng.permutation(per)[:n], np.full(n + 9 + int(rng.integers(0, 3)), rng.integers(0, per))]))
+                else:              # stretches of one leaf each
+                    at = np.sort(rng.integers(0, per, 4)) if kind < 4 else rng.integers(0, per, 4)
+                    parts.append(per * g + np.repeat(at, rng.choice([1, 2, 3, 20, 61, 64, 65, 130], 4)))
+            batches.append(np.concatenate(parts))
+        B = min(len(b) for b in batches)
+        idx = np.stack([b[:B] for b in batches]).astype(np.uint32)
+        if kind == 3:
+            idx = np.sort(idx, axis=1)
+        prio = (rng.random(idx.shape) * 3).astype(np.float32)
+        for r in range(2):
+            m.update(idx, prio)
+            m.compare_tree()
+            prio[rng.random(idx.shape) < 0.02] = np.float32("nan")
+            idx[rng.random(idx.shape) < 0.02] = N + 7
+    m.compare_status()
+
+
 @pytest.mark.parametrize("K,N,T,B", [(16, 70001, 1, 65535), (16, 70001, 1, 65536), (4, 20001, 4, 16384), (64, 70001, 1, 196607), (64, 70001, 1, 196608),
                                      (64, 16500, 64, 1100), (32, 1 << 20, 1, 196608), (32, 1100000, 1, 196607), (32, 1100000, 1, 196608)])
 def test_updates_either_side_of_the_rule_for_runs(K, N, T, B):
