@@ -743,8 +743,8 @@ static SampleShape sample_shape(const Geom& g, const Tuning& tn, uint32_t B, uin
   // workgroup size: the configured size, or the whole batch in one workgroup when it is small and no kernel comes behind
   // that could finish the weights (where one does, several workgroups are faster from the third wave on: a step of 1024
   // samples on 2^20 leaves at K = 4 takes 20.8 us with one and 16.3 with eight, of 512 at K = 16 12.8 and 11.7);
-  // bounded by the LDS the staging rows need
-  uint32_t max_waves = sh.wave_bytes ? (uint32_t)(kLdsCap / 2 / sh.wave_bytes) : 16u;
+  // bounded by the LDS the staging rows need (wide, the walk by sixteens: not, since the trees that it serves had no staging rows before)
+  uint32_t max_waves = sh.wave_bytes && !wide ? (uint32_t)(kLdsCap / 2 / sh.wave_bytes) : 16u;
   if (max_waves > 16) max_waves = 16;
   if (max_waves < 1) max_waves = 1;
   uint32_t waves = tn.sample_block / 64;
@@ -996,13 +996,16 @@ static Geom of_sixteen(const Geom& g) {
 // 14.5, 2193 on 1 055 898 at K = 4 17.5 -> 15.0; over 90 drawn steps of both fanouts none took longer by more than the runs differ.
 // Not where the sampling kernel rebuilds a stale top of such a tree or carries an insertion, nor where it folds the tree's
 // minimum (by the real height 1).
+// Up to 1024 samples with nothing behind them are one workgroup's, with the weights: 1024 on 131 072 leaves at K = 2 7.1 us by every
+// height, 6.0 by sixteens; at K = 4 5.7 and 6.0 from the ninth wave on (512: 4.9 both, of 2^20 leaves 64 4.5 and 4.3).
 template <int LOGK>
 static hipError_t launch_sample_k(const Geom& g, const Tuning& tn, uint32_t B, uint32_t size, float beta,
                                   const float* u, const RngArgs& rng, uint32_t* out_idx, float* out_w,
                                   float* out_prio, uint32_t weight_mode, uint32_t stale_hb, const FieldTable* rows,
                                   const ClaimArgs* claim, int claim_mode, const InsertRide* ride, bool whole_sums, hipStream_t s) {
   if constexpr (LOGK <= 2) {
-    bool wide = whole_sums && !ride && !(weight_mode & kWeightMinHere) && g.H * LOGK > 4u;
+    const bool one_workgroup = !rows && !claim && !stale_hb && B > 512u && B <= 1024u;   // of more than eight waves
+    bool wide = whole_sums && !ride && !(weight_mode & kWeightMinHere) && g.H * LOGK > 4u && !(LOGK == 2 && one_workgroup);
     if (wide && stale_hb) {
       const SampleShape sh = sample_shape(g, tn, B, stale_hb, rows || claim);
       wide = !sh.tc.nslots || g.H - sh.tc.nslots > stale_hb;

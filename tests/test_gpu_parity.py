@@ -1902,6 +1902,30 @@ def test_walks_by_sixteens(K, N, T, B):
             walks()
 
 
+@pytest.mark.parametrize("claim_form", ["group"], indirect=True)   # (no claims decide here)
+@pytest.mark.parametrize("K,N,T", [(2, 2048, 1), (2, 70001, 2), (2, 1 << 20, 1), (4, 2048, 1), (4, 70001, 2), (4, 1 << 20, 1)])
+def test_samplings_of_one_workgroup(claim_form, K, N, T):
+    """Up to 1024 samples by themselves, on trees of fanout 2 and 4 that walks go through by sixteens or by every height: one kernel, its
+    weights included, where the top is not stale."""
+    log(f"one workgroup K={K} N={N} T={T}")
+    rng = np.random.default_rng(N + K)
+    m = Mirror(K, N, T, ())
+    prio = wl._draw_priorities("lognormal_0_1", rng, (T, N))
+    prio[:, rng.random(N) < 0.2] = 0.0
+    m.insert(N, prio=prio)
+    m.sample(wl.uniform01(rng, (T, 9)), 0.4)
+    for B in (1, 64, 511, 512, 513, 768, 769, 960, 1023, 1024, 1025):
+        for beta in (0.4, 1.0):
+            m.gpu.profile(True)
+            m.sample(wl.uniform01(rng, (T, B)), beta)
+            launched = kernel_launches(m)
+            m.gpu.profile(False)
+            assert launched == ({"k_sample": 1} if B <= 1024 else {"k_sample": 1, "k_weights": 1}), (B, launched)
+        m.update(rng.integers(0, N, (T, 30)).astype(np.uint32), rng.random((T, 30)).astype(np.float32))
+        m.sample(wl.uniform01(rng, (T, B)), 0.7)                   # (behind a top left stale)
+    m.compare_status()
+
+
 @pytest.mark.parametrize("claim_form", ["group"], indirect=True)   # (no claims in these calls)
 @pytest.mark.parametrize("K,N,T,B", [(8, 1 << 20, 1, 33000), (16, 700_001, 1, 33021), (16, 1 << 22, 1, 40001), (32, 1 << 20, 2, 20001), (32, 1 << 22, 1, 33000),
                                      (64, 300_001, 1, 40000), (64, 1 << 22, 1, 33000)])
