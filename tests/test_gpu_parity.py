@@ -1944,6 +1944,35 @@ def test_samples_of_more_groups_than_a_wave_stages(claim_form, K, N, T, B):
     m.compare_status()
 
 
+@pytest.mark.parametrize("claim_form", ["group"], indirect=True)   # (no claims in these calls)
+@pytest.mark.parametrize("K,N,T,B", [(16, 70001, 1, 33021), (32, 200_003, 2, 20001), (64, 300_001, 1, 40000),       # few groups to a wave
+                                     (16, 577_000, 1, 33021), (32, 650_001, 1, 40001), (64, 888_001, 1, 40001)])    # almost seven eighths of its rows
+def test_few_staging_rows_in_several_rounds(claim_form, K, N, T, B):
+    """The looping sampling kernel with fewer staging rows than lanes, and waves whose samples lie in more groups than it has rows:
+    where the leaves have little priority, and where uniforms leave their range."""
+    log(f"few rows in rounds K={K} N={N} T={T} B={B}")
+    rows, groups = {16: 48, 32: 32, 64: 24}[K], 64 * N / (B * K)
+    assert groups * (1 - np.exp(-64 / groups)) <= 0.875 * rows   # (above it a wave has a row for every lane)
+    rng = np.random.default_rng(B + N)
+    m = Mirror(K, N, T, ())
+    m.gpu.set_tuning("sample_min_lds", 100_000)   # (one workgroup per compute unit)
+    prio = wl._draw_priorities("exponential_1", rng, (T, N))
+    prio[:, N // 5: N // 2] *= 0.01
+    m.insert(N, prio=prio)
+
+    def groups_of_a_wave(ci):
+        whole = ci[:, : B // 64 * 64].reshape(T, -1, 64) // K
+        return 1 + (np.diff(whole.astype(np.int64), axis=2) != 0).sum(axis=2)
+
+    u = wl.uniform01(rng, (T, B))
+    gi, ci = m.sample(u, 0.4)
+    assert groups_of_a_wave(ci).max() > rows
+    u[:, ::2] = (rng.random(u[:, ::2].shape) * 40000 - 20000).astype(np.float32)
+    gi, ci = m.sample(u, 0.4)
+    assert np.median(groups_of_a_wave(ci)) > rows
+    m.compare_status()
+
+
 @pytest.mark.parametrize("K,N,T", [(2, 5000, 1), (4, 4097, 2), (8, 9000, 1), (16, 70001, 2), (32, 200003, 1), (64, 70001, 2)])
 @pytest.mark.parametrize("norm", ["batch", "buffer"])
 def test_updates_claimed_in_runs(K, N, T, norm):
