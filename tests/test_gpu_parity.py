@@ -2128,6 +2128,17 @@ def test_updates_either_side_of_the_rule_for_runs(K, N, T, B):
     m.compare_status()
 
 
+@pytest.mark.parametrize("claim_form", ["group"], indirect=True)   # (the other forms claim no runs)
+@pytest.mark.parametrize("K,N,T,B", [(4, 20001, 4, 16383), (16, 70001, 1, 16383), (16, 70001, 1, 16384), (16, 12 << 14, 1, 1 << 14), (16, (12 << 14) + 1, 1, 1 << 14),
+                                     (16, 32 << 16, 1, 1 << 16), (16, (32 << 16) + 1, 1, 1 << 16), (16, 56 << 17, 1, 1 << 17), (16, (56 << 17) + 1, 1, 1 << 17),
+                                     (32, 70000, 1, 103_499), (32, 70000, 1, 103_500), (32, 56 << 14, 4, 1 << 14), (32, (56 << 14) + 1, 4, 1 << 14),
+                                     (64, 56 << 16, 1, 1 << 16), (64, (56 << 16) + 1, 1, 1 << 16)])
+def test_updates_at_every_line_of_the_rule_for_runs(claim_form, K, N, T, B):
+    """Sampled batches, then the same in no order, one element or one leaf to either side of where per_update changes to claims in runs:
+    the fewest elements, elements per leaf (one in 12, 32, 56) and elements per subtree (1500 of 69)."""
+    test_updates_either_side_of_the_rule_for_runs(K, N, T, B)
+
+
 @pytest.mark.parametrize("K,N,T,fb,sizes", [
     (2, 3001, 1, (16, 4, 4, 16, 1), (17, 1500, 3001, 1)), (4, 70001, 1, (5,), (18, 333, 20000)), (8, 50001, 2, (68, 24, 4, 68, 1), (1, 700, 50001)),
     (16, 70001, 3, (68, 24, 4, 68, 1), (15, 4097, 47000, 69999)), (32, 150001, 1, (5, 129, 2), (31, 33000, 140001)),
