@@ -1973,6 +1973,46 @@ def test_few_staging_rows_in_several_rounds(claim_form, K, N, T, B):
     m.compare_status()
 
 
+@pytest.mark.parametrize("claim_form", ["group"], indirect=True)   # (no claims decide here)
+@pytest.mark.parametrize("K,N,T,B", [(2, 3000, 2, 500), (2, 300_001, 1, 4000), (4, 3000, 2, 500), (4, 300_001, 1, 4000)])
+def test_captured_walks_behind_changes_added(claim_form, K, N, T, B):
+    """A captured sampling of fanout 2 and 4, changes added between its replays: every replay goes by the nodes as they are stored, as a
+    call outside captures then does, and both go by the sums again where the tree has been put in order."""
+    log(f"captured walks K={K} N={N} T={T} B={B}")
+    rng = np.random.default_rng(K + N)
+    m = Mirror(K, N, T, ())
+    m.gpu.set_tuning("step_on_chip", 0)
+    m.insert(N, prio=wl._draw_priorities("lognormal_0_1", rng, (T, N)))
+    u_host = wl.uniform01(rng, (T, B))
+    u = dev(u_host)
+    m.sample(u_host, 0.5)
+    got = [torch.empty((T, B), dtype=d, device="cuda") for d in (torch.int32, torch.float32, torch.float32)]
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        m.gpu.sample(u, 0.5, out_idx=got[0], out_weight=got[1], out_prio=got[2])
+
+    def replayed():
+        for x in got:
+            x.zero_()
+        graph.replay()
+        m.gpu.note_replay()
+        torch.cuda.synchronize()
+        return [x.cpu().numpy().tobytes() for x in got]
+
+    call = lambda: [x.cpu().numpy().tobytes() for x in m.gpu.sample(u, 0.5)]   # noqa: E731
+    want, _, _ = m.cpu.sample(u_host, 0.5, True)
+    assert replayed()[0] == want.tobytes()
+    for r in range(3):
+        add_changes(m.gpu, rng, 60)
+        stored = replayed()
+        assert stored == call() == replayed()
+    m.gpu.rebuild()
+    in_order = call()
+    assert in_order == replayed()
+    assert in_order[0] != stored[0]   # (the changes have left what the two ways tell apart)
+
+
 @pytest.mark.parametrize("K,N,T", [(2, 5000, 1), (4, 4097, 2), (8, 9000, 1), (16, 70001, 2), (32, 200003, 1), (64, 70001, 2)])
 @pytest.mark.parametrize("norm", ["batch", "buffer"])
 def test_updates_claimed_in_runs(K, N, T, norm):
