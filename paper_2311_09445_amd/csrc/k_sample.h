@@ -729,7 +729,8 @@ constexpr uint32_t kLoopWaves = 4;   // (of the kernel that loops over blocks wi
 
 // Workgroup size and top copy of a sampling launch for batch B (stale_hb: the height the stale top is rebuilt
 // from, or 0).  The copy: at most kTopSlots of the topmost heights (below the root), within the LDS budget, and
-// only while a height is small next to what the workgroup's samples would fetch from it one by one.
+// only while a height is small next to what the workgroup's samples would fetch from it one by one.  A launch that carries an
+// insertion leaves the leaves out: the walk takes the new ones from the patch, behind the copy.
 struct SampleShape {
   TopCopy tc;
   uint32_t waves, wave_bytes, top_bytes;
@@ -756,7 +757,7 @@ static SampleShape sample_shape(const Geom& g, const Tuning& tn, uint32_t B, uin
   const uint32_t block = waves * 64;
   TopCopy& tc = sh.tc;
   uint64_t top = 0;
-  for (int l = (int)g.H - 1; l >= 0 && tc.nslots < (uint32_t)kTopSlots; --l) {
+  for (int l = (int)g.H - 1; l >= (carried.n ? 1 : 0) && tc.nslots < (uint32_t)kTopSlots; --l) {
     const uint64_t cnt = (uint64_t)g.n[l + 1] * K;
     const uint64_t add = cnt * 4;
     if (top + add > tn.lds_budget_bytes || top + add + (uint64_t)waves * sh.wave_bytes > kLdsCap) break;

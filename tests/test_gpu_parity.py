@@ -1529,6 +1529,30 @@ def test_carried_rows_of_many_pieces(claim_form, K, N, T, B, fb):
     m.compare_status()
 
 
+@pytest.mark.parametrize("claim_form", ["group"], indirect=True)
+@pytest.mark.parametrize("K,N,T,B,n,fb", [(8, 513, 2, 600, 5, ()), (8, 700, 1, 300, 16, (16,)), (8, 1024, 1, 512, 1, (4,)), (8, 2000, 8, 600, 64, ()), (8, 4096, 8, 600, 5, (1033,)),
+                                          (16, 1300, 8, 600, 128, (4,)), (16, 4096, 8, 600, 5, (1033,)), (32, 2100, 9, 600, 60, (1033,)), (32, 4096, 16, 512, 5, (1033,))])
+def test_carried_insertions_on_trees_of_few_leaves(claim_form, K, N, T, B, n, fb):
+    """Insertions carried by sampling kernels whose copy of the top could hold every height of the tree, the leaves too: the samples of the
+    step see the new rows, and its update of them counts."""
+    log(f"carried insertions, few leaves K={K} N={N} T={T} B={B} n={n} fb={fb}")
+    rng = np.random.default_rng(N + B)
+    m = Mirror(K, N, T, fb, oracle_payload=False)
+    m.gpu.set_tuning("step_on_chip", 0)
+    m.insert(N, prio=wl._draw_priorities("exponential_1", rng, (T, N)))
+    m.gpu.profile(True)
+    for it in range(4):
+        m.update(rng.integers(0, N, (T, 50)).astype(np.uint32), (rng.random((T, 50)) * 9).astype(np.float32))
+        before = kernel_launches(m)
+        ins = (rng.random((T, n)) * 20).astype(np.float32) if it % 2 else None
+        m.insert_step_call(n, ins, wl.uniform01(rng, (T, B)), 0.5, True, wl._draw_updates("absnormal1_eps_pow0.6", rng, (T, B)))
+        after = kernel_launches(m)
+        assert not any(k.startswith("k_insert") and v != before.get(k, 0) for k, v in after.items()), after
+        m.compare_tree()
+    m.gpu.profile(False)
+    m.compare_status()
+
+
 @pytest.mark.parametrize("K,N,T,B,most", [(16, 20000, 8, 300, 128), (8, 9000, 9, 600, 128), (4, 3000, 16, 512, 128), (32, 70001, 8, 513, 128), (32, 70001, 32, 512, 64),
                                           (64, 9000, 4, 512, 16), (64, 9000, 4, 511, 0)])
 def test_largest_carried_insertions(K, N, T, B, most):
