@@ -149,6 +149,19 @@ __device__ __forceinline__ void lds_tree_load(const LevelTable& tab, const LdsTr
   if (top_at < end) *reinterpret_cast<Floats4*>(lt.tree + top_at) = top;
   for (uint32_t e = top_at + 4u * lanes; e < end; e += 4u * lanes) *reinterpret_cast<Floats4*>(lt.tree + e) = above(e);
 }
+// A root that the tree pass has left to its reader while its children are current (trees of three heights whose pass works in
+// subtrees of the root's children): it is summed here, from the copy, and stored, since not every step changes the tree.  By one lane,
+// 0.3 us; a kernel in front that does it takes 4.5 with its launch, in every replay of a captured step (two steps of 64 samples to a
+// graph: on 4096 leaves at K = 16 20.2 us with that kernel, 16.4 so).  In builds of its own: with a branch for it, lists of 100 steps took
+// 0.4 to 2.3 % longer.  Called by the team's first lane, behind the copy; who reads the root first is this lane's wave, or comes
+// by a barrier before.
+template <int LOGK>
+__device__ __forceinline__ void sum_stale_root(const LevelTable& tab, const LdsTree& lt) {
+  static_assert(Wide<LOGK>::LH == 1, "a level is a height");
+  const float root = sum_chunks<Wide<LOGK>::R / 4>(static_cast<const float*>(lt.tree) + lt.off[lt.V - 1u]);
+  lt.tree[lt.off[lt.V]] = root;
+  as_global(tab.lvl[lt.H])[0] = root;
+}
 // The heights between level v and the next one, from a group of sixteen at level v: a lane per group.  (Nodes beyond a
 // height's last are zero, as its padding is.)
 template <int LOGK, typename P>
@@ -1163,8 +1176,8 @@ static TeamForm team_form(uint32_t samples, uint32_t inserted) {
 // keep that order (see TreeView::sync).
 // 100 steps on 10 000 leaves at K = 16 (32 samples, 4 new rows of 41 bytes): 166 us; 1001 us as one phase after the
 // other by the whole workgroup with a full barrier between them.
-// AHEAD: no step reads what a step returns.
-template <int LOGK, TeamForm FORM, int MEM, bool AHEAD>
+// AHEAD: no step reads what a step returns.  ROOT: the root is not current (see sum_stale_root).
+template <int LOGK, TeamForm FORM, int MEM, bool AHEAD, bool ROOT = false>
 __global__ void __launch_bounds__(1024)
 k_run_steps(StreamKernelArgs ka) {
   constexpr bool WAVE = FORM == TEAM_ONE_WAVE, apart = FORM != TEAM_ALL, SPANS = FORM == TEAM_WAVES_SPANS || FORM == TEAM_ALL;
@@ -1249,6 +1262,9 @@ k_run_steps(StreamKernelArgs ka) {
   tv.team = team;
   tv.met = 0;
   __syncthreads();
+  if constexpr (ROOT) {
+    if (tid == 0) sum_stale_root<LOGK>(tab, lt);
+  }
   uint32_t flags = 0;
   float lane_max = __uint_as_float(s_max);   // (WAVE: the lanes' share of it; else s_max counts)
 
@@ -2158,11 +2174,11 @@ static hipError_t launch_run_steps_k(const Geom& g, const Tuning& tn, const Stre
   ka.a.rows_stride = a.rows.row_stride;
   ka.a.ins_stride = a.ins.row_stride;
   const uint32_t mem = a.plan.levels_in_memory;
-#define PER_RUN(F, M, A)                                                                                \
+#define PER_RUN(...)                                                                                    \
   do {                                                                                                  \
-    hipError_t e = grant_lds<&k_run_steps<LOGK, F, M, A>>(tn, bytes);                                   \
+    hipError_t e = grant_lds<&k_run_steps<LOGK, __VA_ARGS__>>(tn, bytes);                               \
     if (e != hipSuccess) return e;                                                                      \
-    PER_LAUNCH(KID_RUN_STEPS, (k_run_steps<LOGK, F, M, A>), dim3(g.T), dim3(1024), bytes, s, ka);       \
+    PER_LAUNCH(KID_RUN_STEPS, (k_run_steps<LOGK, __VA_ARGS__>), dim3(g.T), dim3(1024), bytes, s, ka);   \
   } while (0)
 #define PER_RUN_WHERE(F, A)                                                                             \
   do {                                                                                                  \
@@ -2172,7 +2188,17 @@ static hipError_t launch_run_steps_k(const Geom& g, const Tuning& tn, const Stre
   do {                                                                                                  \
     if (a.ahead) PER_RUN_WHERE(F, true); else PER_RUN_WHERE(F, false);                                  \
   } while (0)
-  if (mem > 1) {   // (built for single steps whose gathers go in runs only)
+  if (a.sum_root) {   // (built for what ensure_sums asks for)
+    if (mem || !a.ahead) return hipErrorInvalidValue;
+    if constexpr (LOGK == 4 || LOGK == 5) {
+      if (form == TEAM_ONE_WAVE) PER_RUN(TEAM_ONE_WAVE, 0, true, true);
+      else if (form == TEAM_WAVES) PER_RUN(TEAM_WAVES, 0, true, true);
+      else if (form == TEAM_WAVES_SPANS) PER_RUN(TEAM_WAVES_SPANS, 0, true, true);
+      else PER_RUN(TEAM_ALL, 0, true, true);
+    } else {
+      return hipErrorInvalidValue;
+    }
+  } else if (mem > 1) {   // (built for single steps whose gathers go in runs only)
     if (a.n_steps != 1 || !a.ahead || !a.upd_is_sampled || form > TEAM_WAVES) return hipErrorInvalidValue;
     if (form == TEAM_ONE_WAVE) PER_RUN(TEAM_ONE_WAVE, 2, true); else PER_RUN(TEAM_WAVES, 2, true);
   } else if (form == TEAM_ONE_WAVE) PER_RUN_WHEN(TEAM_ONE_WAVE);

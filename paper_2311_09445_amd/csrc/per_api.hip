@@ -224,8 +224,20 @@ hipError_t rebuild_heights(per_t* p, hipStream_t s) {
   }
   return e;
 }
+// Is the root the only node that an update has left stale, and can the on-chip kernel of steps sum it from the copy that it holds?  (Only
+// fanouts 16 and 32 have trees of three heights whose tree pass stops below the root; they fit the chip whole, or not at all.)
+bool root_alone_stale(const per_t* p, const StreamPlan& plan) {
+  return p->stale_hb == 2 && p->g.H == 3 && (p->g.logK == 4 || p->g.logK == 5) && p->sums == SUMS_WHOLE && plan.levels_in_memory == 0;
+}
 // Before an on-chip launch, which loads whole heights from memory: the topmost heights are current, and sums of their children.
-hipError_t ensure_sums(per_t* p, hipStream_t s) { return p->sums == SUMS_WHOLE ? ensure_top(p, s) : rebuild_heights(p, s); }
+// steps: the launch is of these, and sums the root if nothing else is stale (it is current behind it).
+hipError_t ensure_sums(per_t* p, hipStream_t s, StreamCall* steps = nullptr) {
+  if (steps) {
+    steps->sum_root = steps->ahead && root_alone_stale(p, steps->plan);
+    if (steps->sum_root) return hipSuccess;
+  }
+  return p->sums == SUMS_WHOLE ? ensure_top(p, s) : rebuild_heights(p, s);
+}
 // Before a tree pass: the heights it does not rewrite in full (up to its workgroup roots) must not be stale below
 // those roots.
 hipError_t prepare_tree_pass(per_t* p, hipStream_t s) {
@@ -708,7 +720,7 @@ static bool step_on_chip(per_t* p, uint32_t n, const void* const* d_field_src, c
   // first, which the usual way does on its way: worth it once, where steps follow steps, not where such calls (steps that go
   // the usual way for another reason among them) and steps take turns.
   p->step_before = true;
-  if (!forced && p->stale_hb && !after_step) return false;
+  if (!forced && p->stale_hb && !root_alone_stale(p, a.plan) && !after_step) return false;
   a.cursor = (uint32_t)p->cursor;
   a.size = (uint32_t)p->size;
   a.upd_is_sampled = 1;
@@ -731,8 +743,9 @@ static bool step_on_chip(per_t* p, uint32_t n, const void* const* d_field_src, c
   a.ins_slots = d_ins_out_idx;
   p->min_stale = true;   // (as per_run_steps)
   p->tables_valid = false;
-  hipError_t e = ensure_sums(p, s);
+  hipError_t e = ensure_sums(p, s, &a);
   if (e == hipSuccess) e = launch_run_steps(p->g, p->tn, a, s);
+  if (e == hipSuccess) p->stale_hb = 0;
   const uint64_t N = p->cfg.capacity;
   p->cursor = (p->cursor + n) % N;
   p->size = p->size + n > N ? N : p->size + n;
@@ -952,8 +965,9 @@ int per_run_steps(per_t* p, uint32_t n_steps, uint32_t n_insert, uint32_t B, con
   if (n_insert) (void)fill_fields(p, const_cast<void* const*>(reinterpret_cast<const void* const*>(io->d_ins_rows)), &a.ins);
   (void)fill_fields(p, io->d_rows_out, &a.rows);
   plan_stream_rows(&a);
-  hipError_t e = ensure_sums(p, s);
+  hipError_t e = ensure_sums(p, s, &a);
   if (e == hipSuccess) e = launch_run_steps(p->g, p->tn, a, s);
+  if (e == hipSuccess) p->stale_hb = 0;
   const uint64_t N = p->cfg.capacity, added = (uint64_t)n_steps * n_insert;
   p->cursor = (p->cursor + added) % N;
   p->size = p->size + added > N ? N : p->size + added;

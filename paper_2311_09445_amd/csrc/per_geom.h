@@ -184,6 +184,7 @@ struct StreamCall : StreamArgs {    // with the fields, of which the kernel has 
   // worked out by plan_stream_rows
   RowItems placed, gathered;
   uint32_t run;                     // length of the runs that the gather is shared out in (0: it cannot be, see gather_run)
+  bool sum_root;                    // the root in memory is not current, its children are (see sum_stale_root)
 };
 
 // A queue of op-coded requests run by one workgroup per tree on an LDS copy of the tree (see k_run_requests).

@@ -1087,6 +1087,71 @@ def test_steps_on_the_chip_draw_and_replay_as_the_kernels_do(K, N):
             assert a.cpu().numpy().tobytes() == b.cpu().numpy().tobytes(), f"result {k}"
 
 
+@pytest.mark.parametrize("claim_form", ["group"], indirect=True)   # (the on-chip launches claim by themselves)
+@pytest.mark.parametrize("K,N,T", [(8, 513, 2), (8, 4096, 1), (16, 1025, 1), (16, 1040, 4), (16, 4096, 2), (16, 9000, 1), (32, 2049, 1), (32, 4096, 4), (32, 30_000, 1), (64, 4097, 1), (64, 30_000, 2)])
+@pytest.mark.parametrize("B", [40, 130, 600])
+def test_on_chip_launches_sum_a_stale_root(claim_form, K, N, T, B):
+    """Trees whose root alone an update leaves stale: a step and a list of steps that change nothing are one launch behind it (K = 16, 32),
+    also replayed, and what they and a queue leave in memory is whole: the root too, where a step has no valid element."""
+    from paper_2311_09445_amd.per import OP_SAMPLE
+    log(f"stale root K={K} N={N} T={T} B={B}")
+    rng = np.random.default_rng(N + B)
+    m = Mirror(K, N, T, {40: (), 130: (1033,), 600: (16,)}[B])   # (130: more row pieces than its row waves have under way at once)
+    assert m.gpu.run_steps_fits() and m.gpu.H >= 3
+    m.insert(N, prio=wl._draw_priorities("exponential_1", rng, (T, N)))
+    m.gpu.set_tuning("step_on_chip", 2)
+    new = lambda: wl._draw_updates("absnormal1_eps_pow0.6", rng, (T, B))   # noqa: E731
+    change = lambda: m.update(rng.integers(0, N, (T, 50)).astype(np.uint32), (rng.random((T, 50)) * 9).astype(np.float32))   # noqa: E731
+
+    def one_launch(call):
+        m.gpu.profile(True)
+        call()
+        launched = kernel_launches(m)
+        m.gpu.profile(False)
+        assert launched["k_run_steps"] == 1 and (m.gpu.H > 3 or K > 32 or not any(k.startswith("k_resum") for k in launched)), launched
+
+    u = wl.uniform01(rng, (T, B))
+    for values in (new(), np.full((T, B), np.nan, np.float32)):
+        change()
+        (one_launch if B <= 512 else lambda call: call())(lambda: m.step_call(u, 0.5, True, values))
+        m.compare_tree()
+    change()
+    m.insert_step_call(5, None, u, 0.5, True, new())
+    m.compare_tree()
+    idx, w, v = (torch.zeros((1, T, B), dtype=d, device="cuda") for d in (torch.int32, torch.float32, torch.float32))
+    beta = dev(np.full(1, 0.5, np.float32))
+    change()
+    one_launch(lambda: m.gpu.run_steps(dev(u[None]), beta, idx, w, v))   # (changes nothing)
+    ci, _, cv = m.cpu.sample(u, 0.5, True)
+    assert np.array_equal(idx_to_host(idx)[0], ci) and v.cpu().numpy()[0].tobytes() == cv.tobytes()
+    m.compare_tree()
+    change()
+    queue = m.gpu.prepare_requests([{"op": OP_SAMPLE, "u": dev(u), "beta": 0.5, "idx": idx[0], "out_weight": w[0], "out_prio": v[0]}])
+    idx.zero_()
+    m.gpu.run_requests(queue)
+    ci, _, cv = m.cpu.sample(u, 0.5, True)
+    assert np.array_equal(idx_to_host(idx)[0], ci) and v.cpu().numpy()[0].tobytes() == cv.tobytes()
+    m.compare_tree()
+    up_host = new()
+    u_dev, up = dev(u), dev(up_host)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        for _ in range(2):
+            m.gpu.step(u_dev, 0.5, up, out_idx=idx[0], out_weight=w[0], out_prio=v[0])
+    for r in range(3):
+        if r:
+            change()
+        graph.replay()
+        m.gpu.note_replay()
+        for _ in range(2):
+            ci, _, cv = m.cpu.sample(u, 0.5, True)
+            m.cpu.update(ci, up_host)
+        assert np.array_equal(idx_to_host(idx)[0], ci) and v.cpu().numpy()[0].tobytes() == cv.tobytes()
+        m.compare_tree()
+    m.compare_status()
+
+
 @pytest.mark.parametrize("K,N", [(2, 1), (2, 16), (2, 17), (2, 33), (2, 513), (4, 5), (4, 65), (4, 4097), (8, 9), (8, 520), (8, 1025), (16, 17),
                                  (16, 2049), (16, 36000), (32, 33), (32, 4100), (64, 65), (64, 8200),   # 64, 65, 128, 129 nodes on a level and around
                                  (2, 19400), (4, 29000), (8, 33900), (64, 38200), (8, 272000), (64, 2400000)])   # the most that fit, with and without their leaves
