@@ -83,10 +83,14 @@ __device__ __forceinline__ unsigned long long group_begins(uint32_t group, uint3
 // first leaf, and one that goes leaf by leaf passes such elements over.  Where most of a run is dominated so its last element claims
 // alone, and what dominates before it goes to the leaves' stamps at once: the tree pass would wait for every sixteen elements of the
 // run.  (Priorities with a long tail: most of a batch may be for a handful of leaves, whose stamps the elements of displaced runs
-// raised one behind the other.  `update` of batches sampled from such priorities, all elements claimed and so: 131 072 on 2^20 leaves at K = 32 55.6
-// and 17.4 us, on 2^21 at K = 64 79 and 16.4, 62 033 on 574 707 at K = 16 22.3 and 11.4, 2^18 on 2^22 at K = 8 171 and 18.6, 2^20 on 2^24 at K = 32
-// 69.5 and 40.0.  Batches in no order, whose runs are of one element, pay for what is looked at: 5870 elements of each of 16 trees of 5870
-// leaves at K = 4 18.1 us, 16.8 leaf by leaf, 2^18 on 896 794 at K = 8 39.5 and 39.0.)
+// raised one behind the other.  `update` of batches sampled from such priorities, all elements claimed and so: 131 072 on 2^20 leaves at K = 32 51
+// and 16.0 us, on 2^21 at K = 64 28.3 and 14.8, 62 033 on 574 707 at K = 16 27.5 and 11.6, 2^18 on 2^22 at K = 8 51 and 17.8, 2^20 on 2^24 at K = 32
+// 100 and 38.8.  Batches in no order, whose runs are of one element, pay for what is looked at: 5870 elements of each of 16 trees of 5870
+// leaves at K = 4 18.2 us, 17.0 leaf by leaf, 2^18 on 896 794 at K = 8 38.9 both, 2^14 on 70 000 at K = 16 11.4 and 10.4.)
+// Most of a run: more than two elements a leaf at K = 32 and 64, where the tree pass has few workgroups, three below.  Dense batches of
+// ordinary priorities have 1.3 to 3, and their leaves one by one are as many atomics as before (all as runs, above two and above three: 16 384 of
+// each of 64 trees of 8560 leaves at K = 4 28.9, 40.0 and 27.3 us, 326 737 of each of two of 117 667 33.8, 39.0 and 33.0; four elements a
+// leaf, 80 000 on 20 000 leaves at K = 8, 36.5, 16.1 and 27.2; 98 000 on 70 000 at K = 32 40.0, 36.1, 40).
 // Called by whole waves with their 64 elements, from `first_j` on.  All loads are under way before the first is looked at.
 __device__ __forceinline__ void claim_runs(const Geom& g, uint32_t t, const ClaimArgs& c, uint32_t base, uint32_t first_j, uint32_t& mx, uint32_t& flags) {
   const unsigned lane = threadIdx.x & 63u;
@@ -130,7 +134,7 @@ __device__ __forceinline__ void claim_runs(const Geom& g, uint32_t t, const Clai
       of_leaves += (uint32_t)__popcll(later);
     }
   }
-  const bool alone = count > 8u + 2u * of_leaves;
+  const bool alone = count > 8u + (g.logK <= 4u ? 3u : 2u) * of_leaves;
   if (const unsigned long long split = __ballot(alone)) {   // (a bit per run, at its last lane)
     if (alone) count = 1;
     const unsigned last = lane + (unsigned)__builtin_ctzll(((starts >> 1) | 1ull << 63) >> lane);   // of this lane's run

@@ -2224,7 +2224,8 @@ def test_runs_of_repeated_leaves(claim_form, K, N, T):
                 g = int(rng.integers(0, groups if kind % 2 else min(groups, 9)))
                 if kind < 2:       # a few leaves in a row, the last repeated so often that the run is one element short of going apart, or not
                     n = int(rng.integers(1, 12))
-                    parts.append(per * g + np.concatenate([rng.permutation(per)[:n], np.full(n + 9 + int(rng.integers(0, 3)), rng.integers(0, per))]))
+                    again = (n if K > 16 else 2 * n) + 9 + int(rng.integers(0, 3))
+                    parts.append(per * g + np.concatenate([rng.permutation(per)[:n], np.full(again, rng.integers(0, per))]))
                 else:              # stretches of one leaf each
                     at = np.sort(rng.integers(0, per, 4)) if kind < 4 else rng.integers(0, per, 4)
                     parts.append(per * g + np.repeat(at, rng.choice([1, 2, 3, 20, 61, 64, 65, 130], 4)))
