@@ -926,17 +926,23 @@ static hipError_t launch_tree_finish_k(const Geom& g, const Tuning& tn, const Cl
 // Does a batch of B elements in leaf order claim faster in runs than leaf by leaf?  The atomics of the leaf by leaf form
 // cost by the element, wherever they go; in runs the tree pass waits for the elements that it reads back, the longer the
 // more of them one workgroup has.  So, from a quarter of an element per group of 32 leaves on (us of `sample` and `update`, leaf by
-// leaf and in runs, where K is 16 or more):
+// leaf and in runs):
 //  - from 65 536 elements in all on, if there is one in 56 leaves (at K = 16 below 2^17 elements: in 32; 2^20 leaves: 2^16 elements
-//    at K = 16 22.9 and 21.2, at K = 64 26.8 and 24.5, 2^18 at K = 16 55.4 and 30.8; 2^22 leaves: 2^16 at K = 64 24.4 and 26.1, at K = 16
-//    22.8 and 24.0, 2^17 34.3 and 29.8, 28.2 and 28.4; 178 351 on 2^23 at K = 16 41.8 and 39.4), or from 196 608 on (2^24 leaves: 2^17 at K = 16 35.3 and 36.2, 2^18 50.5 and 48.7); at K = 16 from 16 384 on with one in 12 leaves
-//    (70 000 leaves: 2^14 20.4 and 19.5; 300 000: 2^14 17.5 and 18.0, 2^15 20.3 and 18.9);
+//    at K = 16 22.4 and 19.9, at K = 64 26.0 and 23.7, 2^18 at K = 16 53.0 and 28.4; 2^22 leaves: 2^16 at K = 64 23.5 and 24.1, at K = 16
+//    21.9 and 22.6, 2^17 31.2 and 27.6, 25.9 and 24.9; 178 351 on 2^23 at K = 16 32.5 and 30.6), or from 196 608 on (2^24 leaves: 2^17 at
+//    K = 16 32.5 and 32.4, 2^18 43.7 and 41.5); at K = 16 from 16 384 on with one in 12 leaves (70 000 leaves: 2^14 20.7 and 19.5;
+//    300 000: 2^14 17.5 and 17.9, 2^15 20.4 and 18.7);
 //  - where the pass has few workgroups of many elements, from 196 608 on: subtrees of 512 or more height-1 nodes (2^22
-//    leaves at K = 32: 2^17 elements 30.2 both, 2^18 50.5 and 38.0; 2^24 at K = 4, `update` alone: 2^18 55 and 57, 2^19 73 and 70), or fewer
-//    than 256 subtrees at K = 64, whose runs are the longest (70 000 leaves: 2^17 elements 77 and 86); fewer than 256 at
-//    K = 32 from 1500 elements each on (70 000 leaves, 69 of them: 2^16 30.4 and 35.0, 2^17 58.2 and 53.7);
-//  - not with fewer than 32 such large subtrees (`update` alone, 16 trees of 148 120 leaves at K = 32, 80 of them: 39 182 each 92 and
-//    53), nor from 2048 nodes on (2^24 leaves at K = 2: 2^20 elements 255 and 302).
+//    leaves at K = 32: 2^17 elements 28.9 and 28.3, 2^18 45.6 and 33.6; 2^24 at K = 4: 2^18 76 and 77, 2^19 102 and 98), or fewer
+//    than 256 subtrees at K = 64, whose runs are the longest (70 000 leaves: 2^17 elements 42.7 and 81, 2^18 51 and 42.6; the
+//    line is too low in between: `update` of 200 000 on 200 000 33 and 45); fewer than 256 at K = 32 from 3500 elements each on, where
+//    most go leaf by leaf all the same (70 000 leaves, 69 of them: 2^16 26.2 and 34.5, 2^17 34.5 and 53.7, 2^18 42.8 and 40.0; 200 000,
+//    `update` alone: 540 000 46 and 53, 800 000 54 and 41);
+//  - not with fewer than 32 subtrees of so many nodes (trees of 1025 to 4094 leaves at K = 2, one subtree each; `update` of 8192 elements
+//    of each of 16 trees of 4000 26.7 and 46.6), nor from 2048 nodes on (2^24 leaves at K = 2: 2^20 elements 299 and 346).
+// Over 110 shapes drawn (every fanout, 2^16 .. 2^24 leaves, 1 .. 16 trees, 2^14 .. 2^20 elements) the chosen form takes 1.2 % longer than
+// the better one in the mean, with exponential priorities as with ones of a long tail; leaf by leaf throughout 34 %.
+// Sampled batches, that is: those in no order lose up to a tenth by runs (2^14 on 70 000 leaves at K = 16, `update` alone, 10.4 and 11.4).
 template <int LOGK>
 static bool runs_pay(const Geom& g, uint32_t B) {
   const uint64_t elements = (uint64_t)B * g.T;
@@ -948,7 +954,7 @@ static bool runs_pay(const Geom& g, uint32_t B) {
   const bool large = sl.list_cap >= 512u;
   if (large && (sl.list_cap >= 2048u || subtrees < 32u)) return false;
   if (large || (LOGK == 6 && subtrees < 256u)) return elements >= 3u << 16;
-  if (LOGK == 5 && subtrees < 256u) return elements >= 1500u * subtrees;
+  if (LOGK == 5 && subtrees < 256u) return elements >= 3500u * subtrees;
   return LOGK < 4 || (uint64_t)B * (LOGK == 4 && elements < 1u << 17 ? 32u : 56u) >= g.N || elements >= 3u << 16;
 }
 

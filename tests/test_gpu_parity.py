@@ -2261,11 +2261,11 @@ def test_updates_either_side_of_the_rule_for_runs(K, N, T, B):
 @pytest.mark.parametrize("claim_form", ["group"], indirect=True)   # (the other forms claim no runs)
 @pytest.mark.parametrize("K,N,T,B", [(4, 20001, 4, 16383), (16, 70001, 1, 16383), (16, 70001, 1, 16384), (16, 12 << 14, 1, 1 << 14), (16, (12 << 14) + 1, 1, 1 << 14),
                                      (16, 32 << 16, 1, 1 << 16), (16, (32 << 16) + 1, 1, 1 << 16), (16, 56 << 17, 1, 1 << 17), (16, (56 << 17) + 1, 1, 1 << 17),
-                                     (32, 70000, 1, 103_499), (32, 70000, 1, 103_500), (32, 56 << 14, 4, 1 << 14), (32, (56 << 14) + 1, 4, 1 << 14),
+                                     (32, 70000, 1, 241_499), (32, 70000, 1, 241_500), (32, 56 << 14, 4, 1 << 14), (32, (56 << 14) + 1, 4, 1 << 14),
                                      (64, 56 << 16, 1, 1 << 16), (64, (56 << 16) + 1, 1, 1 << 16)])
 def test_updates_at_every_line_of_the_rule_for_runs(claim_form, K, N, T, B):
     """Sampled batches, then the same in no order, one element or one leaf to either side of where per_update changes to claims in runs:
-    the fewest elements, elements per leaf (one in 12, 32, 56) and elements per subtree (1500 of 69)."""
+    the fewest elements, elements per leaf (one in 12, 32, 56) and elements per subtree (3500 of 69)."""
     test_updates_either_side_of_the_rule_for_runs(K, N, T, B)
 
 
