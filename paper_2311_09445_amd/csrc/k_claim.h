@@ -89,7 +89,7 @@ __device__ __forceinline__ unsigned long long group_begins(uint32_t group, uint3
 // leaves at K = 4 18.2 us, 17.0 leaf by leaf, 2^18 on 896 794 at K = 8 38.9 both, 2^14 on 70 000 at K = 16 11.4 and 10.4.)
 // Most of a run: more than two elements a leaf at K = 32 and 64, where the tree pass has few workgroups, three below.  Dense batches of
 // ordinary priorities have 1.3 to 3, and their leaves one by one are as many atomics as before (all as runs, above two and above three: 16 384 of
-// each of 64 trees of 8560 leaves at K = 4 28.9, 40.0 and 27.3 us, 326 737 of each of two of 117 667 33.8, 39.0 and 33.0; four elements a
+// each of 64 trees of 8560 leaves at K = 4 28.9, 40.0 and 27.3 us, 326 737 of each of two of 117 667 34.4, 39.0 and 30.5; four elements a
 // leaf, 80 000 on 20 000 leaves at K = 8, 36.5, 16.1 and 27.2; 98 000 on 70 000 at K = 32 40.0, 36.1, 40).
 // Called by whole waves with their 64 elements, from `first_j` on.  All loads are under way before the first is looked at.
 __device__ __forceinline__ void claim_runs(const Geom& g, uint32_t t, const ClaimArgs& c, uint32_t base, uint32_t first_j, uint32_t& mx, uint32_t& flags) {

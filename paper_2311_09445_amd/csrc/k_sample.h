@@ -72,10 +72,10 @@ __device__ __forceinline__ void stage_group_per_lane(const float* __restrict__ l
 // chunk computes once for all lanes of the group, and the number of its node:
 //   [K children][K / 4 chunk sums][node] pad
 // rows an odd number of 16-byte units apart, so that lanes on different rows read different banks.
-// A wave has fewer rows than lanes (ROWS, about 5 KB) and takes its groups in rounds of as many: a sample in sixteen leaves
+// A wave has fewer rows than lanes (ROWS: 5.4 KB at K = 16, 5.6 at 32, 8.1 at 64; at K = 8 all 64 are 3.1) and takes its groups in rounds of as many: a sample in sixteen leaves
 // or more, as large batches have it, seldom needs a second round, and the waves wait for memory two thirds of their time
 // (counters: 63 % at three waves per SIMD with 64 rows each, 11 KB at K = 32), which more of them fill.  In workgroups of four
-// waves, so that no more of them copy the top than before: 2^20 samples on 2^24 leaves 28.2 -> 24 us at K = 32 (33 in
+// waves, so that no more of them copy the top than before: 2^20 samples on 2^24 leaves 28.2 -> 25.6 us at K = 32 (33 in
 // workgroups of two), with the `update` behind them 172 -> 148 at K = 64, 142 -> 138 at K = 16, 166 -> 159 at K = 8.
 template <int LOGK, bool FEW = true>
 struct StageRow {
@@ -94,7 +94,10 @@ static uint32_t stage_floats(uint32_t logK, bool few) {
   return logK == 3 ? stage_floats_k<3>(few) : logK == 4 ? stage_floats_k<4>(few) : logK == 5 ? stage_floats_k<5>(few) : logK == 6 ? stage_floats_k<6>(few) : 0u;
 }
 // Few rows: where 64 samples, spread evenly over the leaves, lie in no more groups than seven eighths of them.  (K = 32, `sample` and
-// `update`: 2^18 samples on 2^24 leaves 51.9 us with 64 rows, 53.7 with 32; 2^20 samples 141 and 138.)
+// `update`: 2^18 samples on 2^24 leaves 51.9 us with 64 rows, 53.7 with 32; 2^20 samples 141 and 138.  Other fanouts, 64 rows and few,
+// groups 0.85 and 0.95 of the rows: K = 16 on 2^24 leaves 77.9 and 72.6, 66.7 and 62.4, on 2^22 31.7 and 31.6, 29.6 and 29.5, but where
+// less is staged 1 % the other way, 2^20 leaves at 0.6 22.4 and 22.7; K = 64 on 2^24 83.8 and 64.8, 79.2 and 61.8, on 2^22 31.0 and 30.2,
+// 30.3 and 29.2: there the line could lie higher.)
 static bool few_rows(const Geom& g, uint32_t B) {
   const double groups = 64.0 * (double)g.N / ((double)B * (double)g.K);
   const int rows = g.logK == 4 ? StageRow<4>::ROWS : g.logK == 5 ? StageRow<5>::ROWS : g.logK == 6 ? StageRow<6>::ROWS : 64;
@@ -687,7 +690,8 @@ static hipError_t launch_tree_finish_k(const Geom& g, const Tuning& tn, const Cl
 // 13.0, 8192 and none 12.6 and 12.1; 2^20 leaves, earlier-batch form of 8192 11.1 and 10.8, 2^22 (1024 roots) 13.3 and
 // 13.9; K = 32, 2^22 leaves, 8192: 13.6 and 13.2.  Two and four: 2^20 leaves at K = 8 (2048 roots), earlier-batch form of
 // 8192, 13.0 and 12.5.  (Fewer than 48 roots: 0.93 to 1.02 times; K = 8 the same, K = 64 0.97 to 1.01; 131 072 samples on 2^23
-// leaves at K = 32 35.3 and 36.0.)
+// leaves at K = 32 35.3 and 36.0.  About the lines: K = 16, one wave and two, 256 roots, 16 384 samples 14.6 and 15.0, 24 576 16.2 and 16.1; 512
+// roots, 2048 samples 12.2 and 11.9, 8192 12.8 both; K = 8, two and four, 1024 roots, 8192 samples 12.2 and 12.6, 2048 roots 13.6 and 13.2.)
 // Every workgroup works a carried insertion out for itself, a run of child groups of which must fit its lanes: that is the
 // least it may have (up to two waves, up to eight on many trees).  On 64 trees it is better worked out by few workgroups of
 // eight waves unless the trees are small (1000 samples, 4 rows each, eight waves and two: 2^18 leaves at K = 16 26.7 and 27.5,
@@ -855,7 +859,7 @@ static hipError_t launch_sample_walk(const Geom& tree, const Geom& g, const Tuni
   // No more workgroups than the device holds at once (their staging rows fill its LDS): they take further blocks of
   // samples in turn, with the top of the tree in place and the next uniforms under way, where workgroups of a second
   // round would begin with their arguments and the top of the tree again, two of the five trips to memory of a block.
-  // (2^20 samples on 2^24 leaves at K = 32: 59 us with a workgroup per block, 24 so, with the rows of descend_staged.)
+  // (2^20 samples on 2^24 leaves at K = 32: 59 us with a workgroup per block, 25.6 so, with the rows of descend_staged.)
   const uint64_t units = compute_units(tn.device);
   auto held = [&]() -> uint64_t {   // workgroups the device holds
     uint64_t bytes = (uint64_t)sh.top_bytes + (uint64_t)sh.waves * sh.wave_bytes, by_waves = 32 / sh.waves;

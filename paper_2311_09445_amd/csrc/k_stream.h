@@ -2129,8 +2129,9 @@ static void plan_shares(const RowItems& it, uint32_t run, uint32_t rws, uint2 (&
 // Where rows are shared evenly, pieces of one byte among them, the two fits are off by up to 15 %, and the chip has to be ahead
 // by a tenth, not by 3 % (35 samples with rows of 1033 bytes on each of 64 trees of 1074 leaves at K = 4: 13.2 us as kernels, 15.6 on the
 // chip; 63 of 165 bytes on 2416 leaves at K = 64: 9.2 and 10.0).
-// Of 580 shapes that the constants were not fitted to (profiles/step_ways.txt) 501 go on the chip, one of them 2.4 % slower for it;
-// the way taken is 0.8 % behind the better one on average.
+// Of 580 shapes that the constants were not fitted to (profiles/step_ways.txt) 501 go on the chip, two of them 2.3 and 5.7 % slower
+// for it; the way taken is 0.9 % behind the better one on average.  (The kernels are up to 8 us faster at K = 2 and 4 than when the
+// constants were fitted, and 5 at K = 32 on few leaves, and still the slower way nearly wherever the fits say so.)
 // Batches beyond 256 at K > 2 are left out, though several trees of a few thousand leaves would gain (410 samples on each of 4 trees
 // of 27 915 leaves at K = 32: 16.8 and 13.1): of 71 such shapes that the fits would take, three lose 6 to 13 %.
 bool step_on_chip_pays(const Geom& g, const Tuning& tn, const StreamCall& a) {
