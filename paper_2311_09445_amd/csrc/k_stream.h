@@ -152,8 +152,8 @@ __device__ __forceinline__ void lds_tree_load(const LevelTable& tab, const LdsTr
 // A root that the tree pass has left to its reader while its children are current (trees of three heights whose pass works in
 // subtrees of the root's children): it is summed here, from the copy, and stored, since not every step changes the tree.  By one lane,
 // 0.3 us; a kernel in front that does it takes 4.5 with its launch, in every replay of a captured step (two steps of 64 samples to a
-// graph: on 4096 leaves at K = 16 20.2 us with that kernel, 16.4 so).  In builds of its own: with a branch for it, lists of 100 steps took
-// 0.4 to 2.3 % longer.  Called by the team's first lane, behind the copy; who reads the root first is this lane's wave, or comes
+// graph: on 4096 leaves at K = 16 20.2 us with that kernel, 16.4 so; a queue of a sampling and an update there 18.7 and 14.4).  In builds of
+// its own: with a branch for it, lists of 100 steps took 0.4 to 2.3 % longer, a queue of rounds of 512 0.8.  Called by the team's first lane, behind the copy; who reads the root first is this lane's wave, or comes
 // by a barrier before.
 template <int LOGK>
 __device__ __forceinline__ void sum_stale_root(const LevelTable& tab, const LdsTree& lt) {
@@ -1589,7 +1589,7 @@ __device__ __forceinline__ uint32_t lay_out_round(uint32_t x, uint32_t y, uint32
   }
   return used;
 }
-template <int LOGK, TeamForm FORM, int MEM>
+template <int LOGK, TeamForm FORM, int MEM, bool ROOT = false>
 __global__ void __launch_bounds__(1024)
 k_run_requests(QueueKernelArgs ka) {
   constexpr bool WAVE = FORM == TEAM_ONE_WAVE, apart = FORM != TEAM_ALL;
@@ -1696,6 +1696,9 @@ k_run_requests(QueueKernelArgs ka) {
   tv.met = 0;
   const bool lists = !(apart && in_team) && rw == 1;   // (the wave that fills the lists of fields from then on)
   __syncthreads();
+  if constexpr (ROOT) {   // (see sum_stale_root)
+    if (tid == 0) sum_stale_root<LOGK>(tab, lt);
+  }
   uint32_t flags = 0;
   float lane_max = __uint_as_float(s_max);   // (WAVE: the lanes' share of it; else s_max counts)
 
@@ -2219,7 +2222,7 @@ hipError_t launch_run_steps(const Geom& g, const Tuning& tn, const StreamCall& a
 }
 
 template <int LOGK>
-static hipError_t launch_run_requests_k(const Geom& g, const Tuning& tn, const QueueArgs& a, hipStream_t s) {
+static hipError_t launch_run_requests_k(const Geom& g, const Tuning& tn, const QueueArgs& a, bool sum_root, hipStream_t s) {
   QueueKernelArgs ka{};
   ka.g = g;
   ka.a = a;
@@ -2227,17 +2230,26 @@ static hipError_t launch_run_requests_k(const Geom& g, const Tuning& tn, const Q
   const size_t bytes = (size_t)a.plan.floats * 4;
   const TeamForm form = team_form(a.most, 0);
   const bool mem = a.plan.levels_in_memory != 0;
-#define PER_RUN(F, M)                                                                                   \
-  do {                                                                                                  \
-    hipError_t e = grant_lds<&k_run_requests<LOGK, F, M>>(tn, bytes);                                   \
-    if (e != hipSuccess) return e;                                                                      \
-    PER_LAUNCH(KID_RUN_REQUESTS, (k_run_requests<LOGK, F, M>), dim3(g.T), dim3(1024), bytes, s, ka);    \
+#define PER_RUN(...)                                                                                        \
+  do {                                                                                                      \
+    hipError_t e = grant_lds<&k_run_requests<LOGK, __VA_ARGS__>>(tn, bytes);                                \
+    if (e != hipSuccess) return e;                                                                          \
+    PER_LAUNCH(KID_RUN_REQUESTS, (k_run_requests<LOGK, __VA_ARGS__>), dim3(g.T), dim3(1024), bytes, s, ka); \
   } while (0)
 #define PER_RUN_WHERE(F)                                                                                \
   do {                                                                                                  \
     if (mem) PER_RUN(F, 1); else PER_RUN(F, 0);                                                         \
   } while (0)
-  if (form == TEAM_ONE_WAVE) PER_RUN_WHERE(TEAM_ONE_WAVE);
+  if (sum_root) {
+    if (mem) return hipErrorInvalidValue;
+    if constexpr (LOGK == 4 || LOGK == 5) {
+      if (form == TEAM_ONE_WAVE) PER_RUN(TEAM_ONE_WAVE, 0, true);
+      else if (form == TEAM_WAVES) PER_RUN(TEAM_WAVES, 0, true);
+      else PER_RUN(TEAM_ALL, 0, true);
+    } else {
+      return hipErrorInvalidValue;
+    }
+  } else if (form == TEAM_ONE_WAVE) PER_RUN_WHERE(TEAM_ONE_WAVE);
   else if (form == TEAM_WAVES) PER_RUN_WHERE(TEAM_WAVES);
   else PER_RUN_WHERE(TEAM_ALL);
 #undef PER_RUN_WHERE
@@ -2245,8 +2257,8 @@ static hipError_t launch_run_requests_k(const Geom& g, const Tuning& tn, const Q
   return hipGetLastError();
 }
 
-hipError_t launch_run_requests(const Geom& g, const Tuning& tn, const QueueArgs& a, hipStream_t s) {
-#define CALL(L) launch_run_requests_k<L>(g, tn, a, s)
+hipError_t launch_run_requests(const Geom& g, const Tuning& tn, const QueueArgs& a, bool sum_root, hipStream_t s) {
+#define CALL(L) launch_run_requests_k<L>(g, tn, a, sum_root, s)
   PER_DISPATCH_LOGK(g.logK, CALL)
 #undef CALL
 }

@@ -224,18 +224,16 @@ hipError_t rebuild_heights(per_t* p, hipStream_t s) {
   }
   return e;
 }
-// Is the root the only node that an update has left stale, and can the on-chip kernel of steps sum it from the copy that it holds?  (Only
+// Is the root the only node that an update has left stale, and can the on-chip kernels sum it from the copy that they hold?  (Only
 // fanouts 16 and 32 have trees of three heights whose tree pass stops below the root; they fit the chip whole, or not at all.)
 bool root_alone_stale(const per_t* p, const StreamPlan& plan) {
   return p->stale_hb == 2 && p->g.H == 3 && (p->g.logK == 4 || p->g.logK == 5) && p->sums == SUMS_WHOLE && plan.levels_in_memory == 0;
 }
 // Before an on-chip launch, which loads whole heights from memory: the topmost heights are current, and sums of their children.
-// steps: the launch is of these, and sums the root if nothing else is stale (it is current behind it).
-hipError_t ensure_sums(per_t* p, hipStream_t s, StreamCall* steps = nullptr) {
-  if (steps) {
-    steps->sum_root = steps->ahead && root_alone_stale(p, steps->plan);
-    if (steps->sum_root) return hipSuccess;
-  }
+// *sum_root, if the launch can: it has to sum the root, nothing else is stale (it is current behind it).
+hipError_t ensure_sums(per_t* p, hipStream_t s, const StreamPlan& plan, bool can_sum_root, bool* sum_root) {
+  *sum_root = can_sum_root && root_alone_stale(p, plan);
+  if (*sum_root) return hipSuccess;
   return p->sums == SUMS_WHOLE ? ensure_top(p, s) : rebuild_heights(p, s);
 }
 // Before a tree pass: the heights it does not rewrite in full (up to its workgroup roots) must not be stale below
@@ -743,7 +741,7 @@ static bool step_on_chip(per_t* p, uint32_t n, const void* const* d_field_src, c
   a.ins_slots = d_ins_out_idx;
   p->min_stale = true;   // (as per_run_steps)
   p->tables_valid = false;
-  hipError_t e = ensure_sums(p, s, &a);
+  hipError_t e = ensure_sums(p, s, a.plan, a.ahead != 0, &a.sum_root);
   if (e == hipSuccess) e = launch_run_steps(p->g, p->tn, a, s);
   if (e == hipSuccess) p->stale_hb = 0;
   const uint64_t N = p->cfg.capacity;
@@ -965,7 +963,7 @@ int per_run_steps(per_t* p, uint32_t n_steps, uint32_t n_insert, uint32_t B, con
   if (n_insert) (void)fill_fields(p, const_cast<void* const*>(reinterpret_cast<const void* const*>(io->d_ins_rows)), &a.ins);
   (void)fill_fields(p, io->d_rows_out, &a.rows);
   plan_stream_rows(&a);
-  hipError_t e = ensure_sums(p, s, &a);
+  hipError_t e = ensure_sums(p, s, a.plan, a.ahead != 0, &a.sum_root);
   if (e == hipSuccess) e = launch_run_steps(p->g, p->tn, a, s);
   if (e == hipSuccess) p->stale_hb = 0;
   const uint64_t N = p->cfg.capacity, added = (uint64_t)n_steps * n_insert;
@@ -1056,8 +1054,10 @@ int per_run_requests(per_t* p, uint32_t n_requests, const per_request* h_request
   a.size = (uint32_t)p->size;
   a.queue = d_requests;
   a.plan = p->list_plan;
-  hipError_t e = ensure_sums(p, s);
-  if (e == hipSuccess) e = launch_run_requests(p->g, p->tn, a, s);
+  bool sum_root;
+  hipError_t e = ensure_sums(p, s, a.plan, true, &sum_root);
+  if (e == hipSuccess) e = launch_run_requests(p->g, p->tn, a, sum_root, s);
+  if (e == hipSuccess) p->stale_hb = 0;
   p->cursor = cursor;
   p->size = size;
   return hip_rc(e);

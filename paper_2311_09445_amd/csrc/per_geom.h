@@ -320,7 +320,7 @@ StreamPlan stream_step_plan(const Geom& g);   // for a step by itself
 void plan_stream_rows(StreamCall* a);         // (needs n_insert, B, ins, rows)
 bool step_on_chip_pays(const Geom& g, const Tuning& tn, const StreamCall& a);
 hipError_t launch_run_steps(const Geom& g, const Tuning& tn, const StreamCall& a, hipStream_t s);
-hipError_t launch_run_requests(const Geom& g, const Tuning& tn, const QueueArgs& a, hipStream_t s);
+hipError_t launch_run_requests(const Geom& g, const Tuning& tn, const QueueArgs& a, bool sum_root, hipStream_t s);   // (sum_root: as of StreamCall)
 hipError_t launch_get_priority(const Geom& g, const Tuning& tn, uint32_t n, const uint32_t* idx, float* out, hipStream_t s);
 hipError_t launch_read_scalars(const Geom& g, int which, uint32_t weight_mode, float* out, hipStream_t s);
 hipError_t launch_clear_status(const Geom& g, hipStream_t s);

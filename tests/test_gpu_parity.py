@@ -1091,8 +1091,8 @@ def test_steps_on_the_chip_draw_and_replay_as_the_kernels_do(K, N):
 @pytest.mark.parametrize("K,N,T", [(8, 513, 2), (8, 4096, 1), (16, 1025, 1), (16, 1040, 4), (16, 4096, 2), (16, 9000, 1), (32, 2049, 1), (32, 4096, 4), (32, 30_000, 1), (64, 4097, 1), (64, 30_000, 2)])
 @pytest.mark.parametrize("B", [40, 130, 600])
 def test_on_chip_launches_sum_a_stale_root(claim_form, K, N, T, B):
-    """Trees whose root alone an update leaves stale: a step and a list of steps that change nothing are one launch behind it (K = 16, 32),
-    also replayed, and what they and a queue leave in memory is whole: the root too, where a step has no valid element."""
+    """Trees whose root alone an update leaves stale: a step, a list of steps that change nothing and a queue are one launch behind it (K = 16, 32),
+    also replayed, and what they leave in memory is whole: the root too, where a step has no valid element."""
     from paper_2311_09445_amd.per import OP_SAMPLE
     log(f"stale root K={K} N={N} T={T} B={B}")
     rng = np.random.default_rng(N + B)
@@ -1103,12 +1103,12 @@ def test_on_chip_launches_sum_a_stale_root(claim_form, K, N, T, B):
     new = lambda: wl._draw_updates("absnormal1_eps_pow0.6", rng, (T, B))   # noqa: E731
     change = lambda: m.update(rng.integers(0, N, (T, 50)).astype(np.uint32), (rng.random((T, 50)) * 9).astype(np.float32))   # noqa: E731
 
-    def one_launch(call):
+    def one_launch(call, name="k_run_steps"):
         m.gpu.profile(True)
         call()
         launched = kernel_launches(m)
         m.gpu.profile(False)
-        assert launched["k_run_steps"] == 1 and (m.gpu.H > 3 or K > 32 or not any(k.startswith("k_resum") for k in launched)), launched
+        assert launched[name] == 1 and (m.gpu.H > 3 or K > 32 or not any(k.startswith("k_resum") for k in launched)), launched
 
     u = wl.uniform01(rng, (T, B))
     for values in (new(), np.full((T, B), np.nan, np.float32)):
@@ -1128,7 +1128,7 @@ def test_on_chip_launches_sum_a_stale_root(claim_form, K, N, T, B):
     change()
     queue = m.gpu.prepare_requests([{"op": OP_SAMPLE, "u": dev(u), "beta": 0.5, "idx": idx[0], "out_weight": w[0], "out_prio": v[0]}])
     idx.zero_()
-    m.gpu.run_requests(queue)
+    one_launch(lambda: m.gpu.run_requests(queue), "k_run_requests")
     ci, _, cv = m.cpu.sample(u, 0.5, True)
     assert np.array_equal(idx_to_host(idx)[0], ci) and v.cpu().numpy()[0].tobytes() == cv.tobytes()
     m.compare_tree()
