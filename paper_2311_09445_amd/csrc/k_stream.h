@@ -153,8 +153,8 @@ __device__ __forceinline__ void lds_tree_load(const LevelTable& tab, const LdsTr
 // subtrees of the root's children): it is summed here, from the copy, and stored, since not every step changes the tree.  By one lane,
 // 0.3 us; a kernel in front that does it takes 4.5 with its launch, in every replay of a captured step (two steps of 64 samples to a
 // graph: on 4096 leaves at K = 16 20.2 us with that kernel, 16.4 so; a queue of a sampling and an update there 18.7 and 14.4).  In builds of
-// its own: with a branch for it, lists of 100 steps took 0.4 to 2.3 % longer, a queue of rounds of 512 0.8.  Called by the team's first lane, behind the copy; who reads the root first is this lane's wave, or comes
-// by a barrier before.
+// their own: with a branch for it, lists of 100 steps took 0.4 to 2.3 % longer, a queue of rounds of 512 0.8.  Called by the team's first
+// lane, behind the copy; who reads the root first is this lane's wave, or comes by a barrier before.
 template <int LOGK>
 __device__ __forceinline__ void sum_stale_root(const LevelTable& tab, const LdsTree& lt) {
   static_assert(Wide<LOGK>::LH == 1, "a level is a height");
